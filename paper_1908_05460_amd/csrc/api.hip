@@ -1,6 +1,7 @@
 // C ABI of libwgrad (declared in include/wgrad.h): argument validation and dispatch.
 // Everything here runs on the host; validation precedes the first launch.
 #include <mutex>
+#include <vector>
 
 #include "exact_stream_kernel.hpp"
 
@@ -208,12 +209,13 @@ void make_groups(const wgrad_conv_desc *layers, const uint8_t *method, int n, in
     }
 }
 
-size_t method_ws(const Geometry &g, int method)
-{
-    if (method == WGRAD_EXACT) { const ExactPlan pl = plan_exact(g); return pl.ok ? pl.ws_bytes : 0; }
-    if (method == WGRAD_APPROX) return plan_approx(g).ws_bytes;
-    return 0;
-}
+// A group's geometry and the plans of its method, made once per call (by its first layer).
+struct LayerPlan {
+    Geometry g;
+    ExactPlan ex;
+    ApproxPlan ap;
+    size_t ws;                       // bytes of one member's slice of the workspace
+};
 
 }  // namespace
 
@@ -240,25 +242,47 @@ static void make_groups_topk(const wgrad_conv_desc *layers, const uint8_t *metho
     }
 }
 
+// Groups of a run, and the plan of each group's first layer; the status of the first layer that has no plan.
+static int plan_groups(const wgrad_conv_desc *layers, const uint8_t *method, int n, int topk, int *group,
+                       std::vector<LayerPlan> &plan)
+{
+    make_groups_topk(layers, method, n, topk, group);
+    plan.resize(n);
+    for (int i = 0; i < n; ++i) {
+        if (group[i] != i) continue;
+        LayerPlan &p = plan[i];
+        const int rc = make_geometry(&layers[i], p.g);
+        if (rc != WGRAD_OK) return rc;
+        p.ws = 0;
+        if (method[i] == WGRAD_EXACT) {
+            p.ex = plan_exact(p.g);
+            p.ws = p.ex.ok ? p.ex.ws_bytes : 0;
+        } else if (method[i] == WGRAD_APPROX) {
+            if (topk > 0) p.ws = topk_ws_bytes(p.g, layer_topk(p.g, topk));
+            else {
+                p.ap = plan_approx(p.g);
+                p.ws = p.ap.ws_bytes;
+            }
+        }
+    }
+    return WGRAD_OK;
+}
+
+// every group keeps its partials until the final reduction
+static size_t schedule_ws_bytes(const int *group, const std::vector<LayerPlan> &plan, int n)
+{
+    size_t need = 0;
+    for (int i = 0; i < n; ++i) need += align_up(plan[group[i]].ws);
+    return need;
+}
+
 static size_t schedule_ws_bytes(const wgrad_conv_desc *layers, const uint8_t *method, int32_t nlayers, int topk)
 {
     if (!layers || !method || nlayers <= 0 || nlayers > 4096) return 0;
     int group[4096];
-    make_groups_topk(layers, method, nlayers, topk, group);
-    size_t need = 0;
-    for (int i = 0; i < nlayers; ++i) {
-        if (group[i] != i) continue;
-        Geometry g;
-        if (make_geometry(&layers[i], g) != WGRAD_OK) return 0;
-        int members = 0;
-        for (int j = i; j < nlayers; ++j) members += group[j] == i;
-        if (topk > 0 && method[i] == WGRAD_APPROX) {
-            need += align_up(topk_ws_bytes(g, layer_topk(g, topk))) * members;
-            continue;
-        }
-        need += align_up(method_ws(g, method[i])) * members;       // every group keeps its partials until the final reduction
-    }
-    return need;
+    std::vector<LayerPlan> plan;
+    if (plan_groups(layers, method, nlayers, topk, group, plan) != WGRAD_OK) return 0;
+    return schedule_ws_bytes(group, plan, nlayers);
 }
 
 extern "C" size_t conv_wgrad_schedule_workspace_bytes(const wgrad_conv_desc *layers, const uint8_t *method, int32_t nlayers)
@@ -287,18 +311,23 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
         if (!dW[i]) return WGRAD_INVALID_ARG;
         if (method[i] == WGRAD_EXACT || method[i] == WGRAD_APPROX) {
             if (!X[i] || !dY[i]) return WGRAD_INVALID_ARG;
-            if (method[i] == WGRAD_EXACT && !plan_exact(g).ok) return WGRAD_UNSUPPORTED;
         } else if (method[i] == WGRAD_RANDOM && !(sigma >= 0.0f)) {
             return WGRAD_INVALID_ARG;
         }
     }
-    if (!ws_ok(ws, ws_bytes, schedule_ws_bytes(layers, method, nlayers, topk))) return WGRAD_WORKSPACE_TOO_SMALL;
+    int group[4096];
+    std::vector<LayerPlan> plan;
+    {
+        const int rc = plan_groups(layers, method, nlayers, topk, group, plan);
+        if (rc != WGRAD_OK) return rc;
+    }
+    for (int i = 0; i < nlayers; ++i)
+        if (method[i] == WGRAD_EXACT && !plan[group[i]].ex.ok) return WGRAD_UNSUPPORTED;
+    if (!ws_ok(ws, ws_bytes, schedule_ws_bytes(group, plan, nlayers))) return WGRAD_WORKSPACE_TOO_SMALL;
 
     // pass 2: enqueue on the caller's stream: one launch sequence per group of exact or approximated
     // layers, then one reduction of all their partial results, then the zero and the random fills
     hipStream_t st = (hipStream_t)stream;
-    int group[4096];
-    make_groups_topk(layers, method, nlayers, topk, group);
     CombineQueue queue;
     MultiQueue multi;
     int nexact = 0;
@@ -306,33 +335,27 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     MultiQueue *mq = nexact > 1 && tune_int("WGRAD_MULTI", 1) ? &multi : nullptr;
     // workgroups of a multi-shape launch are shared out to the groups in proportion to their work
     double exact_flops = 0;
+    // groups that the fp32 multi-shape launch carries (those of the 2x2-plane form add nothing to its shares)
     auto group_flops = [&](int i) {
-        double f = 0;
-        for (int j = i; j < nlayers; ++j)
-            if (group[j] == i) {
-                Geometry gj;
-                make_geometry(&layers[j], gj);
-                double w = 2.0 * gj.N * gj.K * gj.Ho * gj.Wo * (double)gj.crs();
-                // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of
-                // input channels (bound by the dY stream), strides (a window four times the tile)
-                if (gj.C < 16) w *= tune_int("WGRAD_MULTI_W_FLAT", 20) / 10.0;
-                if (gj.sh > 1 || gj.sw > 1) w *= tune_int("WGRAD_MULTI_W_STRIDE", 25) / 10.0;
-                // 4x4 planes: their tiles are half as long (the window of eight images does not fit next to a
-                // second workgroup's), so a FLOP takes longer there even with the halo-only taps left out (swept)
-                const int wc = plan_exact(gj).wc;
-                if (wc == 1) w *= tune_int("WGRAD_MULTI_W_WC1", 125) / 100.0;
-                if (wc == 2) w *= tune_int("WGRAD_MULTI_W_WC2", 100) / 100.0;
-                f += w;
-            }
-        return f;
+        const ExactPlan &ex = plan[i].ex;
+        if (ex.plane2 || ex.x3 == 2) return 0.0;
+        const Geometry &g = plan[i].g;
+        double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
+        // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of
+        // input channels (bound by the dY stream), strides (a window four times the tile)
+        if (g.C < 16) w *= tune_int("WGRAD_MULTI_W_FLAT", 20) / 10.0;
+        if (g.sh > 1 || g.sw > 1) w *= tune_int("WGRAD_MULTI_W_STRIDE", 25) / 10.0;
+        // 4x4 planes: their tiles are half as long (the window of eight images does not fit next to a
+        // second workgroup's), so a FLOP takes longer there even with the halo-only taps left out (swept)
+        if (ex.wc == 1) w *= tune_int("WGRAD_MULTI_W_WC1", 125) / 100.0;
+        if (ex.wc == 2) w *= tune_int("WGRAD_MULTI_W_WC2", 100) / 100.0;
+        int members = 0;
+        for (int j = i; j < nlayers; ++j) members += group[j] == i;
+        return w * members;
     };
     if (mq)
         for (int i = 0; i < nlayers; ++i)
-            if (method[i] == WGRAD_EXACT && group[i] == i) {
-                Geometry gi;
-                make_geometry(&layers[i], gi);
-                if (!plan_exact(gi).plane2) exact_flops += group_flops(i);   // (those groups have a launch of their own)
-            }
+            if (method[i] == WGRAD_EXACT && group[i] == i) exact_flops += group_flops(i);
     int napprox = 0;
     for (int i = 0; i < nlayers; ++i) napprox += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i;
     int ntopk = 0;
@@ -346,17 +369,15 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     int nbf16 = 0;
     for (int i = 0; i < nlayers; ++i) {
         if ((method[i] != WGRAD_EXACT && method[i] != WGRAD_APPROX) || group[i] != i || layers[i].dtype != WGRAD_BF16) continue;
-        Geometry g;
-        make_geometry(&layers[i], g);
-        nbf16 += method[i] == WGRAD_EXACT ? plan_exact(g).mm16 : (topk == 0 ? plan_approx(g).mm : 0);
+        nbf16 += method[i] == WGRAD_EXACT ? plan[i].ex.mm16 : (topk == 0 ? plan[i].ap.mm : 0);
     }
     Bf16Queue *bq = nbf16 > 1 && tune_int("WGRAD_BF16_MULTI", 1) ? bf16_queue_new(sq) : nullptr;
+    X3Queue *xq = x3_queue_new();
     char *ws_next = (char *)ws;
     int rc = WGRAD_OK;
     for (int i = 0; i < nlayers && rc == WGRAD_OK; ++i) {
         if ((method[i] != WGRAD_EXACT && method[i] != WGRAD_APPROX) || group[i] != i) continue;
-        Geometry g;
-        make_geometry(&layers[i], g);
+        const Geometry &g = plan[i].g;
         Batch b{};
         for (int j = i; j < nlayers; ++j)
             if (group[j] == i) { b.X[b.n] = X[j]; b.dY[b.n] = dY[j]; b.dW[b.n] = dW[j]; ++b.n; }
@@ -366,16 +387,16 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
             // slot -- while a workgroup's share stays near 100 us; stacks with more work than that get two or
             // three rounds of 768, which evens out the groups' different speeds at the end of the launch
             // (VGG-19 at N = 128, 102 GFLOP: 768 -> 2304 workgroups, exact phase -7 %)
-            if (mq) {
+            if (mq && exact_flops > 0) {
                 int rounds = (int)(exact_flops / 34e9 + 0.5);
                 rounds = rounds < 1 ? 1 : (rounds > 3 ? 3 : rounds);
                 share = (int)(tune_int("WGRAD_MULTI_TOTAL", 768 * rounds) * group_flops(i) / exact_flops + 0.5);
             }
-            rc = launch_exact(g, plan_exact(g), b, ws_next, st, &queue, mq, share < 8 ? 8 : share, bq);
+            rc = launch_exact(g, plan[i].ex, b, ws_next, st, &queue, mq, share < 8 ? 8 : share, bq, xq);
         }
         else if (topk > 0) {
             const int k = layer_topk(g, topk);
-            const size_t slice = align_up(topk_ws_bytes(g, k));
+            const size_t slice = align_up(plan[i].ws);
             // a group of layers in one fused launch where that form takes them; otherwise layer by layer
             if (!(b.n > 1 && launch_topk_group(g, b, k, scale, ws_next, slice, st, &rc, fq, &queue)))
                 for (int j = 0; j < b.n && rc == WGRAD_OK; ++j)
@@ -384,12 +405,14 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
             ws_next += slice * b.n;
             continue;
         }
-        else rc = launch_approx(g, plan_approx(g), b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq);
-        ws_next += align_up(method_ws(g, method[i])) * b.n;
+        else rc = launch_approx(g, plan[i].ap, b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq);
+        ws_next += align_up(plan[i].ws) * b.n;
     }
     if (sq) {
         if (rc == WGRAD_OK) rc = select_flush(*sq, st);
     }
+    if (rc == WGRAD_OK) rc = x3_flush(*xq, st, &queue);
+    x3_queue_delete(xq);
     if (rc == WGRAD_OK && mq) rc = multi_flush(multi, st);
     if (bq) {
         if (rc == WGRAD_OK) rc = bf16_flush(*bq, st);

@@ -80,6 +80,12 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nblocks)
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ---- internal launchers (host). Each validates nothing: the C ABI layer did. ----
+// fp32 on the bf16 matrix core (exact_x3.hip)
+struct X3Plan {
+    int variant, ktiles, ctiles, splits;
+    int nti, ht, iht, twc, h_tiles, w_tiles, n_groups, nch, ch, packed, halo, vlo, xcol0;
+    int lds;
+};
 struct ExactPlan {
     int nt, wk, tap_mode;            // MFMA column tiles per wave, waves along K, column mapping
     int ktiles, ctiles, splits;
@@ -92,6 +98,8 @@ struct ExactPlan {
     int img4;                        // streaming form, 4x4 planes: image-uniform position order (a step contracts one position of four images)
     int mm16;                        // bf16 matrix-core form of the streaming kernel
     int direct;                      // general form: no tile of whole output rows fits the LDS
+    int x3;                          // fp32 as three bf16 pieces on the bf16 matrix core: 0 no, 1 if alone, 2 in a run of several layers too
+    X3Plan x3p;
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     size_t lds_bytes, ws_bytes;
     bool ok;
@@ -106,6 +114,13 @@ bool plane2_takes(const Geometry &g);
 struct MultiQueue;
 int launch_exact_plane2(const Geometry &g, const Batch &b, hipStream_t st, MultiQueue *mq = nullptr);
 struct CombineQueue;
+bool plan_exact_x3(const Geometry &g, X3Plan &pl);
+struct X3Queue;
+X3Queue *x3_queue_new();
+void x3_queue_delete(X3Queue *q);
+int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine);
+int launch_exact_x3(const Geometry &g, const X3Plan &plan, const Batch &b, void *ws, size_t slice_bytes, hipStream_t st,
+                    CombineQueue *defer, X3Queue *q);
 void plan_exact_direct(const Geometry &g, ExactPlan &pl);
 int launch_exact_direct(const Geometry &g, const ExactPlan &pl, const void *X, const void *dY, float *dW, void *ws,
                         hipStream_t st, CombineQueue *defer);
@@ -129,7 +144,8 @@ bool planes_bf16_takes(const Geometry &g);
 int launch_exact_bf16_planes(const Geometry &g, const Batch &b, hipStream_t st, const SparseA *sparse = nullptr);
 struct CombineQueue;
 int launch_exact(const Geometry &g, const ExactPlan &pl, const Batch &b, void *ws, hipStream_t st,
-                 CombineQueue *defer = nullptr, MultiQueue *mq = nullptr, int mq_blocks = 0, Bf16Queue *bq = nullptr);
+                 CombineQueue *defer = nullptr, MultiQueue *mq = nullptr, int mq_blocks = 0, Bf16Queue *bq = nullptr,
+                 X3Queue *xq = nullptr);
 int choose_splits(const ExactPlan &pl, int nprob, int want_blocks = 0);
 size_t exact_ws_per_problem(const Geometry &g, const ExactPlan &pl);
 

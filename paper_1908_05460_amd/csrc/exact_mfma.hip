@@ -482,7 +482,7 @@ int choose_splits(const ExactPlan &pl, int nprob, int want_blocks)
     return (int)best;
 }
 
-ExactPlan plan_exact(const Geometry &g, bool allow_stream)
+static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream)
 {
     ExactPlan pl{};
     const int RS = g.R * g.S;
@@ -572,9 +572,32 @@ ExactPlan plan_exact(const Geometry &g, bool allow_stream)
     pl.ws_bytes = pl.splits > 1 ? align_up((size_t)pl.splits * g.dw_elems() * 4) : 0;
     // tensors that are not 16-byte aligned fall back to the staged form at launch: size for both
     if (pl.stream || pl.mm16) {
-        const size_t alt = plan_exact(g, false).ws_bytes;
+        const size_t alt = plan_exact_forms(g, false).ws_bytes;
         if (alt > pl.ws_bytes) pl.ws_bytes = alt;
     }
+    return pl;
+}
+
+// The plan of a shape: the fp32 and bf16 forms above, and beside them the three-piece form (exact_x3.hip), which takes
+// what the streaming form cannot (27x27 planes, 48 -> 96, N = 32: 76 -> 35 us; 224x224, 64 -> 64, N = 4: 302 -> 88) and
+// all but two kinds of what it can: long strided reductions, whose windows are mostly staging (128 -> 128 @ 56x56, stride
+// 2, N = 16, 3.7 GFLOP: 86 us against 60; at 0.2 to 0.9 GFLOP 13 to 23 against 16 to 29), and, in a run of several layers,
+// layers so short that one launch of all of them wins (ResNet-20 at N = 16 to 64: 36 to 67 us against 55 to 74; its
+// 0.6-GFLOP layers at N = 128 are over the line: 107 -> 93).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
+// 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
+// against 14.8).
+ExactPlan plan_exact(const Geometry &g, bool allow_stream)
+{
+    ExactPlan pl = plan_exact_forms(g, allow_stream);
+    if (!allow_stream || pl.plane2 || !tune_int("WGRAD_X3", 1)) return pl;
+    const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
+    if (pl.stream && g.sw > 1 && gflop >= 1.5) return pl;
+    const int use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
+    if (!use || !plan_exact_x3(g, pl.x3p)) return pl;
+    pl.x3 = use;
+    const size_t need = pl.x3p.splits > 1 ? align_up((size_t)pl.x3p.splits * g.dw_elems() * 4) : 0;
+    if (need > pl.ws_bytes) pl.ws_bytes = need;
+    pl.ok = true;
     return pl;
 }
 
@@ -624,8 +647,9 @@ static int launch_exact_staged(const Geometry &g, const ExactPlan &pl, const voi
                                void *ws, hipStream_t st, CombineQueue *defer);
 
 int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void *ws, hipStream_t st, CombineQueue *defer,
-                 MultiQueue *mq, int mq_blocks, Bf16Queue *bq)
+                 MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq)
 {
+    if (plan.x3 == 2 || (plan.x3 && !mq)) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // likewise (bf16, 2x2 and 4x4 planes)
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {

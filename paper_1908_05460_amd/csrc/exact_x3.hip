@@ -1,0 +1,370 @@
+// Host side of the three-piece bf16 form of the exact filter gradient (exact_x3_kernel.hpp): which shapes take it,
+// their tiles, and launches that carry several shapes.
+#include <algorithm>
+
+#include "exact_x3_kernel.hpp"
+
+namespace wgrad {
+
+// (id, SH, NTC, S, SW, RAG, HALO, RPC, NCH, DI, XI, KP, CP, CH)
+#define WGRAD_X3_VARIANTS(X) \
+    X(0, 32, 3, 3, 1, false, false, 1, 16, 2, 3, 17, 25, 32) X(1, 32, 3, 3, 1, false, true, 1, 16, 2, 3, 23, 25, 32) \
+    X(2, 32, 3, 3, 1, true, true, 1, 16, 2, 3, 23, 25, 32) X(3, 32, 3, 3, 1, false, false, 2, 16, 2, 3, 17, 25, 32) \
+    X(4, 16, 3, 3, 1, false, false, 1, 16, 1, 2, 17, 33, 16) X(5, 16, 3, 3, 1, true, true, 1, 16, 1, 2, 23, 33, 16) \
+    X(6, 16, 3, 3, 2, false, false, 1, 16, 1, 3, 17, 69, 16) X(7, 16, 3, 3, 2, true, true, 1, 16, 1, 3, 23, 69, 16) \
+    X(8, 16, 1, 3, 1, false, false, 1, 16, 1, 1, 17, 25, 7) X(9, 16, 1, 3, 1, true, true, 1, 16, 1, 1, 23, 25, 7) \
+    X(10, 32, 1, 3, 1, false, false, 1, 16, 2, 2, 17, 25, 12) X(11, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
+    X(12, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
+constexpr int kX3Variants = 13;
+
+struct X3Variant { int sh, ntc, s, sw, rag, halo, rpc, nch, di, xi, kp, cp, ch, lds, occ; };
+static const X3Variant kVariant[kX3Variants] = {
+#define X(ID, ...) {__VA_ARGS__, X3Config<__VA_ARGS__>::kLds, X3Config<__VA_ARGS__>::kOcc},
+    WGRAD_X3_VARIANTS(X)
+#undef X
+};
+// workgroups that the chip holds at once
+static int x3_resident(const X3Variant &v) { return kNumCU * std::max(1, std::min(160 * 1024 / v.lds, v.occ)); }
+
+// The parameters are read through the kernel-argument segment pointer: indexing the by-value argument with a run-time
+// group number would make the compiler copy all of it into scratch memory first.
+template <class T>
+__global__ __launch_bounds__(kBlock, T::kOcc) void wgrad_exact_x3(const X3Multi)
+{
+    extern __shared__ __align__(16) char x3_smem[];
+    const X3Multi *mp = (const X3Multi *)__builtin_amdgcn_kernarg_segment_ptr();
+    const int n = mp->n;
+    int gi = 0;
+    for (int i = 1; i < n; ++i) gi += (int)blockIdx.x >= mp->begin[i];
+    const int bid = (int)blockIdx.x - mp->begin[gi], nblk = mp->count[gi];
+    if (bid >= nblk) return;
+    const int first = mp->first[gi];
+    x3_body<T>(mp->s[gi], mp->X + first, mp->dY + first, mp->out + first, x3_smem, bid, nblk);
+}
+
+static int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
+// Tile of a variant for a shape, or false.
+static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
+{
+    const X3Variant &v = kVariant[id];
+    const int half = v.s / 2;
+    int dmin = 0, dmax = 0;
+    for (int s = 0; s < v.s; ++s) { dmin = std::min(dmin, x3_shift(s, v.s, v.sw)); dmax = std::max(dmax, x3_shift(s, v.s, v.sw)); }
+    const int vlo = std::max(dmin, floor_div(g.pw - half, v.sw));
+    const int vhi = std::min(g.Wo - 1 + dmax, floor_div(g.W - 1 + g.pw - half, v.sw));
+    const int vw = vhi - vlo + 1;
+    if (vw < 1) return false;                            // (every product meets only padding)
+    pl.vlo = vlo;
+    pl.xcol0 = v.sw * vlo + half - g.pw;
+    if (!v.rag && (g.Wo % 4 || g.W % 4 || vlo != 0 || pl.xcol0 != 0)) return false;
+    pl.packed = v.ntc == 1;
+    if (!pl.packed && v.ntc != g.R) return false;
+    pl.ktiles = (g.K + v.sh - 1) / v.sh;
+    if (pl.packed) {
+        pl.ctiles = (g.C * g.R + v.sh * v.ntc - 1) / (v.sh * v.ntc);
+        pl.ch = std::min(g.C, (v.sh * v.ntc - 1) / g.R + 2);
+        if (pl.ch > v.ch) return false;
+    } else {
+        pl.ctiles = (g.C + v.sh - 1) / v.sh;
+        pl.ch = std::min(v.sh, g.C);
+    }
+    if (v.rpc == 2) {
+        if (g.W != 4 || g.Wo != 4 || g.Ho != 4 || g.H != 4 || g.sh != 1 || g.R != 3 || vlo != 0 || vw != 4) return false;
+    }
+    const int vwc = v.rpc == 2 ? 1 : (vw + 7) / 8;           // (images of a tile, its rows and chunk columns are packed in 4, 8 and 4 bits)
+    long best = -1;
+    int best_x = 0;
+    for (int twc = 1; twc <= std::min(vwc, v.nch); ++twc) {
+        const int w_tiles = (vwc + twc - 1) / twc;
+        if (twc > 1 && (vwc + twc - 2) / (twc - 1) == w_tiles) continue;      // the same number of narrower tiles does
+        const int halo = v.s > 1 && v.rpc == 1 && (w_tiles > 1 || vlo > 0 || vlo + 8 * twc < g.Wo);
+        if (halo && !v.halo) continue;
+        for (int ht = v.rpc; ht <= g.Ho; ht += v.rpc) {
+            if (ht / v.rpc * twc > v.nch) break;
+            int nti = ht >= g.Ho ? std::min(g.N, v.nch / (ht / v.rpc * twc)) : 1;
+            const int iht = (ht - 1) * g.sh + g.R;
+            if (iht > 255) break;
+            for (; nti >= 1; --nti) {
+                const int xr = nti * iht / v.rpc * twc;                        // staged chunks of a channel and phase
+                if ((long)pl.ch * xr > (long)v.xi * kBlock) continue;
+                if (halo && v.sh * nti * ht * 2 > kBlock) continue;
+                const int nch = nti * (ht / v.rpc) * twc;
+                // (the last chunk of a dY channel is the chunk of zeros)
+                if ((halo ? 1 + nti * ht * (twc + 1) : nch) + 1 > v.kp || xr * v.sw > v.cp) continue;
+                const long tiles = (long)w_tiles * ((g.Ho + ht - 1) / ht) * ((g.N + nti - 1) / nti);
+                if (best >= 0 && (tiles > best || (tiles == best && xr >= best_x))) continue;
+                best = tiles; best_x = xr;
+                pl.nti = nti; pl.ht = ht; pl.iht = iht; pl.twc = twc; pl.nch = nch; pl.halo = halo;
+                pl.w_tiles = w_tiles; pl.h_tiles = (g.Ho + ht - 1) / ht; pl.n_groups = (g.N + nti - 1) / nti;
+            }
+        }
+    }
+    if (best < 0) return false;
+    pl.lds = v.lds;
+    // index arithmetic: 32-bit element offsets within a tile, fast divisions of the tile number
+    if ((long)pl.nti * g.K * g.Ho * g.Wo >= (1l << 28) || (long)(pl.nti + 1) * g.C * g.H * g.W >= (1l << 28)) return false;
+    if (best * std::max(pl.w_tiles, pl.h_tiles) >= (1l << 31)) return false;
+    pl.variant = id;
+    return true;
+}
+
+// us that a workgroup spends on a tile when `share` of them are on its CU: bounded by the matrix instructions of all, or
+// by its own staging and matrix instructions one after the other
+static double x3_tile_us(const X3Variant &v, int share)
+{
+    const double mfma = (double)v.nch / (64 / v.sh) / 4 * 6 * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
+    const double stage = 0.3 + 0.33 * (v.di + v.xi * v.sw);
+    return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
+}
+static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(v) / kNumCU); }
+// tiles a workgroup adds up in one accumulator: the error of the fp32 sums grows with their length (64 -> 64 @ 32x32, N = 128:
+// 3.9e-7 of the result at 8 tiles, 4.7e-7 at 16, 1.9e-6 at 128; the fp32 matrix core's kernel: 6.5e-7)
+constexpr long kX3MostTiles = 32;
+constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
+
+// How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of
+// workgroups, `count` of each, `life` us long, sorted by falling life.
+static double x3_makespan(int slots, const double *life, const long *count, int n)
+{
+    struct { double at; long n; } free_at[64];
+    int used = 1;
+    free_at[0] = {0.0, slots};
+    double end = 0;
+    for (int i = 0; i < n; ++i) {
+        long left = count[i];
+        while (left > 0) {
+            int e = 0;
+            for (int j = 1; j < used; ++j)
+                if (free_at[j].at < free_at[e].at) e = j;
+            // whole rounds on the earliest slots while they stay the earliest
+            const long take = std::min(left, free_at[e].n);
+            const double done = free_at[e].at + life[i];
+            left -= take;
+            end = std::max(end, done);
+            int same = -1;
+            for (int j = 0; j < used; ++j)
+                if (free_at[j].at > done - 0.05 && free_at[j].at < done + 0.05) same = j;
+            if (take == free_at[e].n && same < 0) free_at[e].at = done;
+            else {
+                free_at[e].n -= take;
+                if (same >= 0) free_at[same].n += take;
+                else if (used < 64) free_at[used++] = {done, take};
+                else free_at[e].n += take, free_at[e].at = done;              // (too many kinds: an estimate does)
+                if (free_at[e].n == 0) free_at[e] = free_at[--used];
+            }
+        }
+    }
+    return end;
+}
+
+// us that writing and reading back `splits` partial results of a tensor take
+static double x3_partial_us(const Geometry &g, long splits, int nprob)
+{
+    return splits > 1 ? (double)splits * nprob * g.dw_elems() * 8 / 4.5e6 : 0.0;
+}
+
+// How many workgroups share the reduction of one problem of `nprob`: the time of the launch, plus the traffic of the
+// partial results.
+static int x3_choose_splits(const Geometry &g, const X3Plan &pl, int nprob)
+{
+    const X3Variant &v = kVariant[pl.variant];
+    const long tiles = (long)pl.w_tiles * pl.h_tiles * pl.n_groups, outs = (long)pl.ktiles * pl.ctiles * nprob;
+    const int slots = x3_resident(v);
+    const double t = x3_tile_us(v);
+    double best_cost = 1e30;
+    int best = 1;
+    const long most = std::min(tiles, std::max({1l, 2 * slots / outs, (tiles + kX3MostTiles - 1) / kX3MostTiles}));
+    for (long per = (tiles + most - 1) / most; per <= std::max(kX3MostTiles, (tiles + most - 1) / most) && per <= tiles; per += std::max(1l, per / 16)) {
+        const long s = (tiles + per - 1) / per, n = outs * s;
+        double life = kX3Fixed + per * t;
+        if (n <= kNumCU) life = kX3Fixed + per * x3_tile_us(v, 1);      // a CU to itself
+        const double cost = x3_makespan(slots, &life, &n, 1) + (s > 1 ? 2.0 : 0.0) + x3_partial_us(g, s, nprob);
+        if (cost < best_cost) { best_cost = cost; best = (int)s; }
+    }
+    return best;
+}
+
+bool plan_exact_x3(const Geometry &g, X3Plan &best)
+{
+    if (g.bf16 || g.W < 4 || g.Wo < 4 || g.pw >= 4096) return false;
+    const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
+    double best_cost = 1e30;
+    for (int id = 0; id < kX3Variants; ++id) {
+        const X3Variant &v = kVariant[id];
+        if (v.s != g.S || v.sw != g.sw) continue;
+        X3Plan pl{};
+        if (!x3_tile(g, id, pl)) continue;
+        // Matrix instructions, in units of a 16x16 tile of the result.  Long reductions do better with 32x32 tiles (a
+        // staged element serves twice as many of them; 128 -> 128 @ 16x16, N = 128: 56 us against 65), short ones with
+        // 16x16 tiles, whose workgroups are quicker to set up and share a CU by four (N = 16: 21 us against 22.5;
+        // 48 -> 96 @ 27x27, N = 32, where 32x32 tiles would be a third padding besides: 35 against 49).
+        double cost = (double)pl.ktiles * pl.ctiles * pl.w_tiles * pl.h_tiles * pl.n_groups * v.nch * v.ntc *
+                      (v.sh == 32 ? 4.0 : (gflop < 2.0 ? 0.9 : 1.15));
+        cost *= v.rag ? 1.1 : (v.halo ? 1.02 : 1.0);
+        if (cost < best_cost) { best_cost = cost; best = pl; }
+    }
+    if (best_cost >= 1e30) return false;
+    best.splits = x3_choose_splits(g, best, 1);
+    return true;
+}
+
+// ---- launches ----
+struct X3Group {
+    Geometry g;
+    X3Plan pl;
+    Batch b;
+    float *ws;                   // the group's slice of the workspace: slice_stride floats per problem
+    long slice_stride;
+};
+struct X3Queue {
+    std::vector<X3Group> item;
+};
+X3Queue *x3_queue_new() { return new X3Queue(); }
+void x3_queue_delete(X3Queue *q) { delete q; }
+
+static void x3_fill(const X3Group &it, X3Shape &s)
+{
+    const Geometry &g = it.g;
+    const X3Plan &pl = it.pl;
+    s.g = g;
+    s.per_prob = pl.ktiles * pl.ctiles * pl.splits;
+    s.ktiles = pl.ktiles; s.ctiles = pl.ctiles; s.splits = pl.splits;
+    s.nti = pl.nti; s.ht = pl.ht; s.iht = pl.iht; s.twc = pl.twc;
+    s.h_tiles = pl.h_tiles; s.w_tiles = pl.w_tiles; s.n_groups = pl.n_groups;
+    s.nch = pl.nch; s.ch = pl.ch; s.packed = pl.packed;
+    s.halo = pl.halo; s.vlo = pl.vlo; s.xcol0 = pl.xcol0;
+    const int rpc = kVariant[pl.variant].rpc;
+    s.d_nch = FastDiv(pl.nch);
+    s.d_twc = FastDiv(pl.twc);
+    s.d_ht = FastDiv(pl.ht / rpc);
+    s.d_xrow = FastDiv(pl.nti * pl.iht / rpc * pl.twc);
+    s.d_iht = FastDiv(pl.iht);
+    s.d_htiles = FastDiv(pl.h_tiles);
+    s.d_wtiles = FastDiv(pl.w_tiles);
+    s.d_r = FastDiv(g.R);
+}
+
+static int x3_launch(void (*kernel)(const X3Multi), const X3Multi &m, int blocks, size_t lds, hipStream_t st)
+{
+    // more than 64 KB of dynamic LDS has to be granted per kernel function (the CU has 160 KB)
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return WGRAD_LAUNCH_FAILED;
+    WGRAD_LAUNCH(kernel, dim3((unsigned)blocks), dim3(kBlock), lds, st, m);
+    return launch_status();
+}
+
+static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
+{
+    X3Multi m{};
+    m.n = n;
+    size_t lds = 0;
+    int blocks = 0, tensors = 0;
+    for (int i = 0; i < n; ++i) {
+        const X3Group &q = *it[i];
+        x3_fill(q, m.s[i]);
+        m.begin[i] = blocks;
+        m.count[i] = m.s[i].per_prob * q.b.n;
+        m.first[i] = tensors;
+        for (int j = 0; j < q.b.n; ++j, ++tensors) {
+            m.X[tensors] = (const float *)q.b.X[j];
+            m.dY[tensors] = (const float *)q.b.dY[j];
+            m.out[tensors] = q.pl.splits > 1 ? q.ws + (long)j * q.slice_stride : q.b.dW[j];
+        }
+        blocks += (m.count[i] + 7) / 8 * 8;
+        lds = std::max(lds, (size_t)q.pl.lds);
+    }
+    m.begin[n] = blocks;
+    switch (it[0]->pl.variant) {
+#define X(ID, ...) case ID: return x3_launch(wgrad_exact_x3<X3Config<__VA_ARGS__>>, m, blocks, lds, st);
+        WGRAD_X3_VARIANTS(X)
+#undef X
+        default: return WGRAD_UNSUPPORTED;
+    }
+}
+
+// Issues what was collected, in launches of several groups (longest workgroups first), cut so that a launch's workgroups
+// fill the chip about evenly; the partial results are recorded in `combine`.
+int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
+{
+    int rc = WGRAD_OK;
+    auto tiles_of = [](const X3Group &it) { return (long)it.pl.w_tiles * it.pl.h_tiles * it.pl.n_groups; };
+    std::stable_sort(q.item.begin(), q.item.end(), [](const X3Group &a, const X3Group &b) { return a.pl.variant < b.pl.variant; });
+    for (size_t first = 0; first < q.item.size() && rc == WGRAD_OK;) {
+        X3Group *sel[kX3MultiMax];
+        int n = 0, tensors = 0;
+        const X3Variant &v = kVariant[q.item[first].pl.variant];
+        while (first < q.item.size() && n < kX3MultiMax && tensors + q.item[first].b.n <= kX3Tensors &&
+               &kVariant[q.item[first].pl.variant] == &v) {
+            tensors += q.item[first].b.n;
+            sel[n++] = &q.item[first++];
+        }
+        const int slots = x3_resident(v);
+        const double t = x3_tile_us(v);
+        // Candidates: workgroups of `share` of the launch's even share of work, the first of a pair where the result is
+        // large (its partial results are what splitting costs), the second elsewhere, to fill what those leave free.
+        static const double kShare[][2] = {{1.0, 1.0}, {1.0, 0.5}, {1.0, 0.33}, {0.67, 0.67}, {0.67, 0.33}, {0.5, 0.5}, {0.5, 0.25}, {0.33, 0.33}, {0.25, 0.25}};
+        long largest = 0;
+        double total = 0;                                // workgroup-tiles
+        for (int i = 0; i < n; ++i) {
+            total += (double)tiles_of(*sel[i]) * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n;
+            largest = std::max(largest, sel[i]->g.dw_elems());
+        }
+        double best_cost = 1e30, life[kX3MultiMax], best_life[kX3MultiMax];
+        int best[kX3MultiMax], now[kX3MultiMax];
+        for (const auto &share : kShare) {
+            double sorted[kX3MultiMax], partial = 0;
+            long count[kX3MultiMax];
+            for (int i = 0; i < n; ++i) {
+                const long tiles = tiles_of(*sel[i]);
+                const double target = std::max(1.0, total / slots * share[2 * sel[i]->g.dw_elems() < largest]);
+                long s = (long)(tiles / target + 0.95);
+                s = std::max(s, (tiles + kX3MostTiles - 1) / kX3MostTiles);
+                s = std::max(1l, std::min(s, (long)std::min<long>(sel[i]->pl.splits, tiles)));
+                now[i] = (int)s;
+                partial += x3_partial_us(sel[i]->g, s, sel[i]->b.n);
+                life[i] = kX3Fixed + (double)((tiles + s - 1) / s) * t;
+                int j = i;
+                for (; j > 0 && sorted[j - 1] < life[i]; --j) { sorted[j] = sorted[j - 1]; count[j] = count[j - 1]; }
+                sorted[j] = life[i];
+                count[j] = s * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n;
+            }
+            const double cost = x3_makespan(slots, sorted, count, n) + partial;
+            if (cost < best_cost) {
+                best_cost = cost;
+                std::copy(now, now + n, best);
+                std::copy(life, life + n, best_life);
+            }
+        }
+        const X3Group *order[kX3MultiMax];
+        for (int i = 0; i < n && rc == WGRAD_OK; ++i) {
+            sel[i]->pl.splits = best[i];
+            if (best[i] > 1)
+                rc = launch_combine(sel[i]->ws, sel[i]->slice_stride, best[i], sel[i]->g.dw_elems(), 1.0f, sel[i]->b.dW, sel[i]->b.n, st, combine);
+            int j = i;
+            for (; j > 0 && life[j - 1] < best_life[i]; --j) { life[j] = life[j - 1]; order[j] = order[j - 1]; }
+            life[j] = best_life[i];
+            order[j] = sel[i];
+        }
+        if (rc == WGRAD_OK) rc = x3_launch_groups(order, n, st);
+    }
+    q.item.clear();
+    return rc;
+}
+
+// One group of identical layers: its own launch, or (with a queue) collected for x3_flush.
+int launch_exact_x3(const Geometry &g, const X3Plan &plan, const Batch &b, void *ws, size_t slice_bytes, hipStream_t st,
+                    CombineQueue *defer, X3Queue *q)
+{
+    X3Group it{g, plan, b, (float *)ws, (long)(slice_bytes / 4)};
+    if (q) {
+        q->item.push_back(it);
+        return WGRAD_OK;
+    }
+    if (b.n > 1) it.pl.splits = std::min(plan.splits, x3_choose_splits(g, plan, b.n));
+    const X3Group *one = &it;
+    const int rc = x3_launch_groups(&one, 1, st);
+    if (rc != WGRAD_OK || it.pl.splits == 1) return rc;
+    return launch_combine(it.ws, it.slice_stride, it.pl.splits, g.dw_elems(), 1.0f, b.dW, b.n, st, defer);
+}
+
+}  // namespace wgrad

@@ -1,0 +1,548 @@
+// Exact filter gradient for fp32 inputs on the bf16 matrix core.
+//
+// An fp32 number is the exact sum of three bf16 numbers (8 significant bits each, rounded to nearest:
+// x = h + m + l with |m| <= 2^-8 |x|, |l| <= 2^-17 |x|), a product of two bf16 numbers is exact in fp32, and of
+// the nine products of two such sums the six largest leave out less than 2^-24 |x y|: the rounding of one fp32
+// product.  Six bf16 matrix instructions (1/16 of the fp32 instruction's time per product) therefore replace one
+// fp32 one, with fp32 accumulation as before.  The split has fp32's whole range; a tile that holds an infinity, a
+// NaN or a value whose h rounds to infinity is recomputed by its workgroup with plain fp32 multiply-adds
+// (x3_general), where the pieces would make NaNs of infinities.
+//
+// Implicit GEMM, rows = output channels k, columns = (input channel, filter row), reduction = "slots": the columns
+// of X (stride 1) or of one phase of X (column mod stride), eight consecutive slots of one output row being one
+// 16-byte chunk -- the operand of one lane.  The filter column s is applied by shifting the dY operand, in
+// registers, by the distance between a slot and the output column that sees it through tap s (shift_of): a word
+// read from each side of the chunk and four v_alignbit serve all filter rows and channels, and every X operand is
+// one aligned 16-byte LDS read.
+//
+// A workgroup owns SH output channels x NTC * SH columns and a range of tiles (nti images x ht output rows x twc
+// chunks, at most NCH chunks); its four wavefronts take a quarter of a tile's chunks each, with the whole output
+// tile in their accumulators, and add them up through LDS at the end, so that a workgroup writes one partial
+// result.  All irregularity -- odd widths, any padding, strides, ragged last tiles, any alignment -- is met while
+// staging: dY and X rows are loaded in 16-byte pieces (4-byte aligned), split, and written to LDS as chunks of
+// each piece, zero outside the tensors.  Two workgroups share a CU: one stages while the other multiplies.
+#pragma once
+#include "exact_common.hpp"
+
+namespace wgrad {
+
+typedef __bf16 x3_bf8 __attribute__((ext_vector_type(8)));
+typedef __bf16 x3_bf2 __attribute__((ext_vector_type(2)));
+typedef float x3_f16 __attribute__((ext_vector_type(16)));
+typedef uint32_t x3_u4 __attribute__((ext_vector_type(4)));
+
+struct X3Shape {
+    Geometry g;
+    int per_prob, ktiles, ctiles, splits;
+    int nti, ht, iht, twc;       // tile: images, output rows, input rows, chunks per row
+    int h_tiles, w_tiles, n_groups;
+    int nch;                     // live chunks of a tile (the table points the rest at a chunk of zeros)
+    int ch;                      // channels staged per column tile
+    int packed;                  // columns numbered c * R + r; otherwise column tile t is filter row t of SH channels (R = 1: channels t*SH..)
+    int halo;                    // staged rows of dY carry their neighbours' words (tiles that are not whole rows)
+    int vlo, xcol0;              // slot 0: its dY column, its X column in phase 0
+    FastDiv d_nch, d_twc, d_ht, d_xrow, d_iht, d_htiles, d_wtiles, d_r;
+};
+
+constexpr int kX3MultiMax = 9;       // groups per launch
+constexpr int kX3Tensors = 24;       // problems per launch
+struct X3Multi {
+    int n;
+    int begin[kX3MultiMax + 1];      // first workgroup of each group (multiples of 8); begin[n] = grid size
+    int count[kX3MultiMax];
+    int first[kX3MultiMax];          // the group's first problem in the tensor tables
+    X3Shape s[kX3MultiMax];
+    const float *X[kX3Tensors], *dY[kX3Tensors];
+    float *out[kX3Tensors];          // per problem: dW when splits == 1, else partials [splits][K][C*R*S]
+};
+static_assert(sizeof(X3Multi) <= 4096, "kernel arguments");
+
+// filter column s of a filter of width S at stride SW: the phase of X it reads, and slot - output column
+__host__ __device__ constexpr int x3_shift(int s, int S, int SW) { return (s - S / 2 + 8 * SW) / SW - 8; }
+__host__ __device__ constexpr int x3_phase(int s, int S, int SW) { return (s - S / 2 + 8 * SW) % SW; }
+
+// A = dY chunk as words w[0..3] with its neighbour words; element i of the result is element i - D of the row.
+template <int D, bool HALF>
+__device__ __forceinline__ x3_bf8 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
+{
+    x3_u4 o;
+    auto mid = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_alignbit(hi, lo, 16); };
+    if (HALF) {                      // two rows of four: zeros come in from both sides of each half
+        if (D == 0) o = w;
+        else if (D == -1) o = x3_u4{mid(w[0], w[1]), w[1] >> 16, mid(w[2], w[3]), w[3] >> 16};
+        else o = x3_u4{w[0] << 16, mid(w[0], w[1]), w[2] << 16, mid(w[2], w[3])};
+    } else if (D == 0) o = w;
+    else if (D == -1) o = x3_u4{mid(w[0], w[1]), mid(w[1], w[2]), mid(w[2], w[3]), mid(w[3], R)};
+    else if (D == 1) o = x3_u4{mid(L, w[0]), mid(w[0], w[1]), mid(w[1], w[2]), mid(w[2], w[3])};
+    else if (D == -2) o = x3_u4{w[1], w[2], w[3], R};
+    else o = x3_u4{L, w[0], w[1], w[2]};
+    return __builtin_bit_cast(x3_bf8, o);
+}
+
+// Two fp32 numbers -> one word (bf16 pair) of each piece
+__device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l)
+{
+    // (written out: from a conversion in C the compiler makes a second instruction for the low half alone)
+    auto pk = [](float a, float b) {
+        uint32_t v;
+        asm("v_cvt_pk_bf16_f32 %0, %1, %2" : "=v"(v) : "v"(a), "v"(b));
+        return v;
+    };
+    h = pk(x0, x1);
+    const float r0 = x0 - __uint_as_float(h << 16), r1 = x1 - __uint_as_float(h & 0xffff0000u);
+    m = pk(r0, r1);
+    const float q0 = r0 - __uint_as_float(m << 16), q1 = r1 - __uint_as_float(m & 0xffff0000u);
+    l = pk(q0, q1);
+}
+
+// v = four columns loaded at a column clamped into the row, d = wanted column - loaded column: the wanted four,
+// zero where they lie outside the row
+__device__ __forceinline__ void x3_realign(float (&v)[4], int d)
+{
+    if (d >= 0) {
+        if (d & 1) { v[0] = v[1]; v[1] = v[2]; v[2] = v[3]; v[3] = 0.f; }
+        if (d & 2) { v[0] = v[2]; v[1] = v[3]; v[2] = v[3] = 0.f; }
+        if (d >= 4) v[0] = v[1] = v[2] = v[3] = 0.f;
+    } else {
+        const int e = -d;
+        if (e & 1) { v[3] = v[2]; v[2] = v[1]; v[1] = v[0]; v[0] = 0.f; }
+        if (e & 2) { v[3] = v[1]; v[2] = v[0]; v[0] = v[1] = 0.f; }
+        if (e >= 4) v[0] = v[1] = v[2] = v[3] = 0.f;
+    }
+}
+
+// The workgroup's whole result with fp32 multiply-adds straight from the tensors, X read as zero outside its bounds: its
+// tiles' slots, and in the first and last tile of a row the positions whose tap lies beyond all slots.
+template <int SH, int NTC, int S, int SW, int NTHR>
+__device__ __forceinline__ void x3_general(const X3Shape &p, const float *X, const float *dY, float *out, int k0, int coltile,
+                                        int c_first, int wt_begin, int wt_end, int slots)
+{
+    const Geometry &g = p.g;
+    const int CRS = g.C * g.R * S;
+    for (int o = threadIdx.x; o < SH * NTC * SH * S; o += NTHR) {
+        const int s = o % S, col = (o / S) % (NTC * SH), k = k0 + o / (S * NTC * SH);
+        int c, r;
+        if (p.packed) { c = (coltile * NTC * SH + col) / g.R; r = (coltile * NTC * SH + col) % g.R; }
+        else if (g.R == 1) { c = c_first + col; r = 0; }
+        else { c = c_first + col % SH; r = col / SH; }
+        if (k >= g.K || c >= g.C) continue;
+        float acc = 0.f;
+        for (int wt = wt_begin; wt < wt_end; ++wt) {
+            const int wti = wt % p.w_tiles, hti = wt / p.w_tiles % p.h_tiles, n0 = wt / (p.w_tiles * p.h_tiles) * p.nti;
+            for (int n = n0; n < n0 + p.nti && n < g.N; ++n)
+                for (int h = hti * p.ht; h < (hti + 1) * p.ht && h < g.Ho; ++h) {
+                    const int ih = h * g.sh + r - g.ph;
+                    const float *y = dY + (((long)n * g.K + k) * g.Ho + h) * g.Wo, *x = X + (((long)n * g.C + c) * g.H + ih) * g.W;
+                    const int v0 = p.vlo + wti * slots - x3_shift(s, S, SW);
+                    const int w0 = wti && v0 > 0 ? v0 : 0, w1 = wti + 1 < p.w_tiles ? v0 + slots : g.Wo;
+                    for (int w = w0; w < w1 && w < g.Wo; ++w) {
+                        const int iw = w * SW + s - g.pw;
+                        acc = fmaf(y[w], ih >= 0 && ih < g.H && iw >= 0 && iw < g.W ? x[iw] : 0.f, acc);
+                    }
+                }
+        }
+        out[(long)k * CRS + (c * g.R + r) * S + s] = acc;
+    }
+}
+
+// SH: rows and columns of the matrix instruction (32: 32x32x16, 16: 16x16x32).  NTC: column tiles.  S: filter width.
+// SW: column stride.  RAG: rows whose width is not a multiple of four, or that start before column 0 of a tensor.
+// HALO: tiles may be parts of rows.  RPC: rows per chunk (2: rows of four slots).  NCH: chunks of a tile; DI, XI:
+// staging items per thread; KP, CP: LDS chunks per channel of dY and of X (odd: conflict-free 16-byte reads); CH: channels
+// of X (compile-time, so that the operand reads have immediate offsets).
+template <int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int RPC_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
+struct X3Config {
+    static constexpr int SH = SH_, NTC = NTC_, S = S_, SW = SW_, RPC = RPC_, NCH = NCH_, DI = DI_, XI = XI_, KP = KP_, CP = CP_, CH = CH_, NW = 4;
+    static constexpr bool RAG = RAG_, HALO = HALO_;
+    static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG ? 3 : 4);      // workgroups that share a CU
+    static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
+    static constexpr int kBuf = 16 + 3 * kDy + 16 + 3 * kX;             // of a tile (16 spare bytes before each: a word left of a chunk 0)
+    static constexpr int SR = SH == 32 ? 1 : S;                         // filter columns per round of the final exchange
+    static constexpr int kEx = NW * SR * SH * (SH + 4) * 4;             // bytes of a round (two alternate)
+    static constexpr int kOutP = NTC * SH * S + 4;                      // pitch of the result tile gathered in LDS (16-byte rows)
+    static constexpr int kHead = NCH * 4 + 16;                          // the chunk table and a flag
+    static constexpr int kTail = 2 * kEx + SH * kOutP * 4;
+    static constexpr int kLds = kHead + (kBuf > kTail ? kBuf : kTail);
+};
+
+template <class T>
+__device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt, const float *const *dYt, float *const *outt,
+                                        char *smem, int bid, int nblk)
+{
+    constexpr int SH = T::SH, NTC = T::NTC, S = T::S, SW = T::SW, RPC = T::RPC, NCH = T::NCH, DI = T::DI, XI = T::XI, KP = T::KP, CP = T::CP,
+                  NW = T::NW, NTHR = 64 * NW;
+    constexpr bool RAG = T::RAG, HALO = T::HALO, HALF = RPC == 2;
+    constexpr int CPS = 64 / SH;                        // chunks per step (lane groups of an operand)
+    constexpr int NST = NCH / (CPS * NW);                // steps per wavefront and tile
+    constexpr int AV = SH * SH / 64;                    // accumulator registers per output tile
+    static_assert(NCH % (CPS * NW) == 0 && DI * NTHR >= SH * NCH, "tile");
+    typedef float acc_t __attribute__((ext_vector_type(AV)));
+
+    const Geometry &g = p.g;
+    const int tid = threadIdx.x, lane = tid & 63, wq = tid >> 6;
+    const int i = lane & (SH - 1), kk = lane / SH;
+    const int R = g.R, CRS = g.C * R * S, L = g.Ho * g.Wo;
+
+    uint32_t *const tab = (uint32_t *)smem;                       // [NCH] chunk -> A offset | B offset << 12 | mask left << 30 | mask right << 31
+    uint32_t *const flag = tab + NCH;                        // set when the pieces cannot represent the tile
+    char *const buf = smem + T::kHead;                  // dY [3][SH][KP] chunks, X [3][CH][CP] chunks
+    constexpr int dy_piece = T::kDy, x_piece = T::kX, kDyAt = 16, kXAt = 16 + 3 * T::kDy + 16;
+
+    const int logical_all = xcd_contiguous_id(bid, nblk);
+    const int prob = logical_all / p.per_prob;
+    const int logical = logical_all - prob * p.per_prob;
+    const float *const Xp = Xt[prob], *const dYp = dYt[prob];
+    const int coltile = logical % p.ctiles;
+    const int ktile = (logical / p.ctiles) % p.ktiles;
+    const int split = logical / (p.ctiles * p.ktiles);
+    const int k0 = ktile * SH;
+    const int c_first = p.packed ? coltile * NTC * SH / R : coltile * SH * (R == 1 ? NTC : 1);
+
+    const int tiles_total = p.h_tiles * p.w_tiles * p.n_groups;
+    const int wt_begin = (int)((long)split * tiles_total / p.splits);
+    const int wt_end = (int)((long)(split + 1) * tiles_total / p.splits);
+
+    // ---- staging items, decoded once: where in the tile (LDS chunk | image << 16 | row << 20 | chunk column << 28, all
+    //      ones: none) and the row's element offset from the tile's first row ----
+    uint32_t d_at[DI], d_off[DI], x_at[XI], x_off[XI], h_at = ~0u, h_off = 0;
+    auto at_dst = [](uint32_t a) { return (a & 0xffffu) * 16u; };
+    auto at_n = [](uint32_t a) { return (int)(a >> 16 & 15u); };
+    auto at_row = [](uint32_t a) { return (int)(a >> 20 & 255u); };
+    auto at_wc = [](uint32_t a) { return (int)(a >> 28); };
+#pragma unroll
+    for (int u = 0; u < DI; ++u) {
+        const int e = tid + u * NTHR;
+        d_at[u] = ~0u; d_off[u] = 0;
+        if (e < SH * p.nch) {
+            uint32_t k_l, chk, row, wc, n_l, h_l;
+            p.d_nch.divmod(e, k_l, chk);
+            p.d_twc.divmod(chk, row, wc);
+            p.d_ht.divmod(row, n_l, h_l);               // (HALF: h_l counts pairs of rows)
+            const uint32_t idx = HALO && p.halo ? 1 + row * (p.twc + 1) + wc : chk;
+            if (k0 + (int)k_l < g.K) d_at[u] = (k_l * KP + idx) | n_l << 16 | h_l * RPC << 20 | wc << 28;
+            d_off[u] = (n_l * g.K + k_l) * L + h_l * RPC * g.Wo;
+        }
+    }
+    if (HALO && p.halo && tid < SH * p.nti * p.ht * 2) {           // one of a row's two neighbour words per thread
+        const uint32_t side = tid & 1, k_l = (tid >> 1) / (p.nti * p.ht), row = (tid >> 1) % (p.nti * p.ht);
+        if (k0 + (int)k_l < g.K) h_at = (k_l * KP + row * (p.twc + 1) + (side ? p.twc + 1 : 0)) | row / p.ht << 16 | row % p.ht << 20 | side << 28;
+        h_off = (row / p.ht * g.K + k_l) * L + row % p.ht * g.Wo;
+    }
+#pragma unroll
+    for (int u = 0; u < XI; ++u) {
+        const int e = tid + u * NTHR;
+        x_at[u] = ~0u; x_off[u] = 0;
+        if (e < p.ch * (int)p.d_xrow.d) {
+            uint32_t c_l, rem, row, wc, n_l, ih_l;
+            p.d_xrow.divmod(e, c_l, rem);
+            p.d_twc.divmod(rem, row, wc);
+            p.d_iht.divmod(HALF ? row * 2 : row, n_l, ih_l);
+            if (c_first + (int)c_l < g.C) x_at[u] = (c_l * CP + row * p.twc * SW + wc) | n_l << 16 | ih_l << 20 | wc << 28;
+            x_off[u] = (n_l * g.C + c_l) * (g.H * g.W) + ih_l * g.W;
+        }
+    }
+
+    float dr[DI][8], xr[XI][8 * SW], hr[2];
+    struct Tile { int n0, h0, wc0; };
+    auto tile_of = [&](int wt) {
+        uint32_t q, wti, ng, hti;
+        p.d_wtiles.divmod(wt, q, wti);
+        p.d_htiles.divmod(q, ng, hti);
+        return Tile{(int)ng * p.nti, (int)hti * p.ht, (int)wti * p.twc};
+    };
+    // Loads go through a buffer descriptor of 2^31 bytes from the tile's first row; what is to be zero is asked for
+    // beyond it, and the hardware answers 0 without a memory access: nothing is masked afterwards.
+    constexpr uint32_t kDead = 0x80000000u;
+    auto rsrc_of = [&](const float *base) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, kDead, 0x00020000); };
+    // four columns of a row (element offset `row`) from any column
+    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, bool live, uint32_t row, int col, int width, float *v) {
+        int c = col;
+        if (RAG) c = col < 0 ? 0 : (col > width - 4 ? width - 4 : col);
+        live = live && (RAG ? (unsigned)(col + 3) < (unsigned)(width + 3) : col < width);
+        const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, live ? (row + (uint32_t)c) * 4u : kDead, 0, 0);
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(q[e]);
+    };
+    auto fix4 = [&](int col, int width, float *v) {      // RAG: the four that were clamped into the row, back to their columns
+        float q[4] = {v[0], v[1], v[2], v[3]};
+        x3_realign(q, col - (col < 0 ? 0 : (col > width - 4 ? width - 4 : col)));
+#pragma unroll
+        for (int e = 0; e < 4; ++e) v[e] = q[e];
+    };
+    auto halo_col = [&](const Tile &t) { return (t.wc0 + (at_wc(h_at) ? p.twc : 0)) * 8 + p.vlo - (at_wc(h_at) ? 0 : 2); };
+    // (opaque: the fields are taken out of the word where they are used, not kept in registers of their own across the loop)
+    auto fresh = [](uint32_t v) { asm volatile("" : "+v"(v)); return v; };
+    auto load_tile = [&](int wt) {
+        const Tile t = tile_of(wt);
+        const int n_left = g.N - t.n0, h_left = g.Ho - t.h0;
+        const auto yb = rsrc_of(dYp + ((long)t.n0 * g.K + k0) * L + (long)t.h0 * g.Wo);
+#pragma unroll
+        for (int u = 0; u < DI; ++u) {
+            const uint32_t at = fresh(d_at[u]);
+            const bool live = at != ~0u && at_n(at) < n_left && at_row(at) < h_left;
+            const int col = HALF ? 0 : (at_wc(at) + t.wc0) * 8 + p.vlo;
+            load4(yb, live, d_off[u], col, g.Wo, dr[u]);
+            if (HALF) load4(yb, live && at_row(at) + 1 < h_left, d_off[u] + g.Wo, 0, g.Wo, dr[u] + 4);
+            else load4(yb, live, d_off[u], col + 4, g.Wo, dr[u] + 4);
+        }
+        if (HALO && p.halo) {
+            const int col = halo_col(t);
+            const bool live = h_at != ~0u && at_n(h_at) < n_left && at_row(h_at) < h_left;
+#pragma unroll
+            for (int e = 0; e < 2; ++e)
+                hr[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
+                    yb, live && (unsigned)(col + e) < (unsigned)g.Wo ? (h_off + col + e) * 4u : kDead, 0, 0));
+        }
+        // (the first input row of a tile may lie above the plane: offsets count from it, dead rows are never asked for)
+        const int ih0 = t.h0 * g.sh - g.ph;
+        const auto xb = rsrc_of(Xp + ((long)t.n0 * g.C + c_first) * g.H * g.W);
+        const uint32_t row0 = (uint32_t)(ih0 * g.W);
+#pragma unroll
+        for (int u = 0; u < XI; ++u) {
+            const uint32_t at = fresh(x_at[u]);
+            const int ih = ih0 + at_row(at);
+            const bool here = at != ~0u && at_n(at) < n_left;
+            const bool live = here && (unsigned)ih < (unsigned)g.H;
+            const int col = HALF ? 0 : (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
+            load4(xb, live, x_off[u] + row0, col, g.W, xr[u]);
+            if (HALF) load4(xb, here && (unsigned)(ih + 1) < (unsigned)g.H, x_off[u] + row0 + g.W, 0, g.W, xr[u] + 4);
+            else {
+#pragma unroll
+                for (int q = 1; q < 2 * SW; ++q) load4(xb, live, x_off[u] + row0, col + 4 * q, g.W, xr[u] + 4 * q);
+            }
+        }
+    };
+    auto put = [&](const float (&v)[8], char *dst, int piece) {
+        x3_u4 h, m, l;
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+            uint32_t a, b, c;
+            x3_split2(v[2 * e], v[2 * e + 1], a, b, c);
+            h[e] = a; m[e] = b; l[e] = c;
+        }
+        *(x3_u4 *)dst = h;
+        *(x3_u4 *)(dst + piece) = m;
+        *(x3_u4 *)(dst + 2 * piece) = l;
+    };
+    auto commit_tile = [&](int wt) {
+        Tile t{0, 0, 0};
+        if (RAG) t = tile_of(wt);
+#pragma unroll
+        for (int u = 0; u < DI; ++u) {
+            const uint32_t at = fresh(d_at[u]);
+            if (RAG) {
+                const int col = (at_wc(at) + t.wc0) * 8 + p.vlo;
+                fix4(col, g.Wo, dr[u]);
+                fix4(col + 4, g.Wo, dr[u] + 4);
+            }
+            if (at != ~0u) put(dr[u], buf + kDyAt + at_dst(at), dy_piece);
+        }
+        if (HALO && p.halo) {
+            uint32_t h, m, l;
+            x3_split2(hr[0], hr[1], h, m, l);
+            if (h_at != ~0u) {
+                char *const dst = buf + kDyAt + at_dst(h_at) + (at_wc(h_at) ? 0 : 12);
+                *(uint32_t *)dst = h;
+                *(uint32_t *)(dst + dy_piece) = m;
+                *(uint32_t *)(dst + 2 * dy_piece) = l;
+            }
+        }
+#pragma unroll
+        for (int u = 0; u < XI; ++u) {
+            const uint32_t at = fresh(x_at[u]);
+            if (RAG) {
+                const int col = (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
+#pragma unroll
+                for (int q = 0; q < 2 * SW; ++q) fix4(col + 4 * q, g.W, xr[u] + 4 * q);
+            }
+            if (at != ~0u) {
+#pragma unroll
+                for (int f = 0; f < SW; ++f) {
+                    float v[8];
+#pragma unroll
+                    for (int e = 0; e < 8; ++e) v[e] = xr[u][e * SW + f];
+                    put(v, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece);
+                }
+            }
+        }
+    };
+
+    load_tile(wt_begin);
+
+    // ---- tables and the chunks of zeros, while the first loads are in flight ----
+    for (int q = tid; q < NCH; q += NTHR) {
+        uint32_t e = (KP - 1) * 16 | 3u << 30;   // (zeros times the first, finite or recomputed, chunk of X)
+        if (q < p.nch) {
+            uint32_t row, wc, n_l, h_l;
+            p.d_twc.divmod(q, row, wc);
+            p.d_ht.divmod(row, n_l, h_l);
+            const int a = HALO && p.halo ? 1 + row * (p.twc + 1) + wc : q;
+            const int b = HALF ? (n_l * p.iht + 2 * h_l) * 8 : ((n_l * p.iht + h_l * g.sh) * p.twc * SW + wc) * 16;
+            e = a * 16 | b << 12;
+            if (!HALO || !p.halo) e |= (wc == 0 ? 1u << 30 : 0u) | ((int)wc + 1 == p.twc ? 1u << 31 : 0u);
+        }
+        tab[q] = e;
+    }
+    if (tid == 0) *flag = 0;
+    for (int e = tid; e < 3 * SH; e += NTHR) *(x3_u4 *)(buf + kDyAt + (e * KP + KP - 1) * 16) = x3_u4{0u, 0u, 0u, 0u};
+    if (k0 + SH > g.K || c_first + T::CH > g.C) {
+        // rows and columns beyond the result are never staged: zeros, so that no left-over bits make infinities of them
+        for (int e = tid; e < T::kBuf / 16; e += NTHR) *(x3_u4 *)(buf + e * 16) = x3_u4{0u, 0u, 0u, 0u};
+        __syncthreads();
+    }
+
+    acc_t acc[NTC][S];
+#pragma unroll
+    for (int t = 0; t < NTC; ++t)
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int v = 0; v < AV; ++v) acc[t][s][v] = 0.f;
+
+    // this lane's columns: byte offset of (channel, filter row) in a piece of X
+    int coloff[NTC];
+    const int row_bytes = HALF ? 8 : p.twc * SW * 16;
+#pragma unroll
+    for (int t = 0; t < NTC; ++t) {
+        int c_l = i + (R == 1 ? t * SH : 0), r = R == 1 ? 0 : t;
+        if (p.packed) {
+            const int col = coltile * NTC * SH + t * SH + i;
+            uint32_t c, rr;
+            p.d_r.divmod(col < g.C * R ? col : c_first * R, c, rr);
+            c_l = (int)c - c_first; r = (int)rr;
+        }
+        if (c_l >= p.ch) c_l = p.ch - 1;                // a column beyond C: some staged channel, never written out
+        coloff[t] = c_l * CP * 16 + r * row_bytes;
+    }
+    const char *const a_row = buf + kDyAt + i * KP * 16, *const Xs = buf + kXAt;
+    for (int wt = wt_begin; wt < wt_end; ++wt) {
+        if (wt != wt_begin) __syncthreads();            // everyone has left the previous tile
+        // The scheduling fences keep the matrix instructions out of the staging: an instruction that waits for the matrix
+        // core holds up what follows it, and then both workgroups of a CU stage while neither multiplies (N = 512,
+        // 128 -> 128 @ 16x16: 190 us without them, 155 with).
+        __builtin_amdgcn_sched_barrier(0);
+        commit_tile(wt);
+        __builtin_amdgcn_sched_barrier(0);
+        if (wt + 1 < wt_end) load_tile(wt + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+#pragma unroll
+        for (int st = 0; st < NST; ++st) {
+            const uint32_t e = tab[(wq * NST + st) * CPS + kk];
+            const char *const ap = a_row + (e & 0xfff);
+            const char *const bp = Xs + ((e >> 12) & 0x3fff);
+            // the products of dY's smallest piece first; a piece's shifted operands serve every column tile, X's pieces
+            // are read again for each (reads that the LDS has to spare, against 24 registers that the loop has not)
+#pragma unroll
+            for (int qa = 2; qa >= 0; --qa) {
+                const x3_u4 w = *(const x3_u4 *)(ap + qa * dy_piece);
+                uint32_t lw = 0, rw = 0;
+                if (S > 1 && !HALF) {
+                    lw = *(const uint32_t *)(ap + qa * dy_piece - 4);
+                    rw = *(const uint32_t *)(ap + qa * dy_piece + 16);
+                    if (e & (1u << 30)) lw = 0;
+                    if (e & (1u << 31)) rw = 0;
+                }
+                x3_bf8 a[S];
+                a[0] = x3_shifted<x3_shift(0, S, SW), HALF>(lw, w, rw);
+                if constexpr (S > 1) a[1] = x3_shifted<x3_shift(1, S, SW), HALF>(lw, w, rw);
+                if constexpr (S > 2) a[2] = x3_shifted<x3_shift(2, S, SW), HALF>(lw, w, rw);
+                if constexpr (S > 3) a[3] = x3_shifted<x3_shift(3, S, SW), HALF>(lw, w, rw);
+                if constexpr (S > 4) a[4] = x3_shifted<x3_shift(4, S, SW), HALF>(lw, w, rw);
+#pragma unroll
+                for (int t = 0; t < NTC; ++t) {
+#pragma unroll
+                    for (int f = 0; f < SW; ++f) {
+                        bool used = false;
+#pragma unroll
+                        for (int s = 0; s < S; ++s) used |= x3_phase(s, S, SW) == f;
+                        if (!used) continue;
+                        const char *const q0 = bp + coloff[t] + f * p.twc * 16;
+#pragma unroll
+                        for (int qb = 2 - qa; qb >= 0; --qb) {
+                            x3_bf8 b;
+                            if (HALF) {
+                                const uint2 lo = *(const uint2 *)(q0 + qb * x_piece), hi = *(const uint2 *)(q0 + qb * x_piece + 8);
+                                b = __builtin_bit_cast(x3_bf8, x3_u4{lo.x, lo.y, hi.x, hi.y});
+                            } else b = *(const x3_bf8 *)(q0 + qb * x_piece);
+#pragma unroll
+                            for (int s = 0; s < S; ++s) {
+                                if (x3_phase(s, S, SW) != f) continue;
+                                if constexpr (SH == 32) acc[t][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], b, acc[t][s], 0, 0, 0);
+                                else acc[t][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b, acc[t][s], 0, 0, 0);
+                            }
+                        }
+                    }
+                }
+            }
+        }
+        __builtin_amdgcn_sched_barrier(0);
+    }
+
+    // An infinity, a NaN or a value whose largest piece rounds to infinity makes infinities or NaNs of every product it
+    // enters, and an accumulator keeps them: one look at the sums finds what the pieces could not represent.
+    float worst[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int t = 0; t < NTC; ++t)
+#pragma unroll
+        for (int s = 0; s < S; ++s)
+#pragma unroll
+            for (int v = 0; v < AV; ++v) worst[v & 3] = fmaf(acc[t][s][v], 0.f, worst[v & 3]);
+    const float any = (worst[0] + worst[1]) + (worst[2] + worst[3]);
+    if (any != any) *flag = 1;
+    __syncthreads();
+    float *const out = outt[prob] + (long)split * g.K * CRS;
+    if (*(volatile uint32_t *)flag) {
+        x3_general<SH, NTC, S, SW, NTHR>(p, Xp, dYp, out, k0, coltile, c_first, wt_begin, wt_end, HALF ? 4 : p.twc * 8);
+        return;
+    }
+    // ---- the wavefronts' sums: through LDS, SR filter columns of a column tile at a time (four rows of a lane side by
+    //      side, two buffers, one barrier a round), gathered as rows of the result and written out in whole lines ----
+    constexpr int KTP = SH + 4, SR = T::SR, P = T::kOutP;
+    float *const rows = (float *)(buf + 2 * T::kEx);    // [SH][P]
+#pragma unroll
+    for (int ts = 0; ts < NTC * S; ts += SR) {
+        const int t = ts / S, s0 = ts % S;
+        float *const red = (float *)(buf + (ts / SR & 1) * T::kEx);      // [NW][SR][SH columns][KTP]
+#pragma unroll
+        for (int s = 0; s < SR; ++s)
+#pragma unroll
+            for (int v = 0; v < AV / 4; ++v) {
+                const acc_t &z = acc[ts / S][ts % S + s];
+                *(float4_t *)(red + ((wq * SR + s) * SH + i) * KTP + (SH == 32 ? 8 * v + 4 * kk : 4 * kk)) =
+                    float4_t{z[4 * v], z[4 * v + 1], z[4 * v + 2], z[4 * v + 3]};
+            }
+        __syncthreads();
+        for (int o = tid; o < SH / 4 * SH * SR; o += NTHR) {
+            const int col = o % SH, rq = o / SH % (SH / 4), sl = o / (SH * SH / 4);
+            float4_t sum = *(const float4_t *)(red + (sl * SH + col) * KTP + 4 * rq);
+#pragma unroll
+            for (int w = 1; w < NW; ++w) sum += *(const float4_t *)(red + ((w * SR + sl) * SH + col) * KTP + 4 * rq);
+            // entry of an output channel's row: (c * R + r) * S + s
+            const int lc = (p.packed || R == 1 ? t * SH + col : col * R + t) * S + s0 + sl;
+#pragma unroll
+            for (int v = 0; v < 4; ++v) rows[(4 * rq + v) * P + lc] = sum[v];
+        }
+    }
+    __syncthreads();
+    {
+        const int j0 = (p.packed ? coltile * NTC * SH : c_first * R) * S;
+        const int cols = p.packed || R == 1 ? NTC * SH * S : SH * R * S, n = CRS - j0 < cols ? CRS - j0 : cols;
+        if (n == NTC * SH * S && k0 + SH <= g.K && CRS % 4 == 0 && j0 % 4 == 0 && ((uintptr_t)out & 15) == 0) {
+            constexpr int Q = NTC * SH * S / 4, IT = (SH * Q + NTHR - 1) / NTHR;
+            float *const dst = out + (long)k0 * CRS + j0;
+#pragma unroll
+            for (int u = 0; u < IT; ++u) {
+                const int e = tid + u * NTHR, row = e / Q, x = e % Q * 4;
+                if (SH * Q % NTHR == 0 || e < SH * Q) *(float4_t *)(dst + (long)row * CRS + x) = *(const float4_t *)(rows + row * P + x);
+            }
+        } else {
+            for (int row = wq; row < SH && k0 + row < g.K; row += NW) {
+                float *const dst = out + (long)(k0 + row) * CRS + j0;
+                for (int x = lane; x < n; x += 64) dst[x] = rows[row * P + x];
+            }
+        }
+    }
+}
+
+}  // namespace wgrad

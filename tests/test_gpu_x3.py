@@ -1,0 +1,132 @@
+"""The exact gradient of fp32 layers as three bf16 pieces on the bf16 matrix core: the shapes where its tiles, its
+staging and its result tile have edges, the inputs that the pieces cannot represent, and its error against fp64."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1908_05460_amd import binding as B
+from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+# N, C, H, W, K, R, S, stride_h, stride_w, pad_h, pad_w; N such that the shape takes this form: 0.03 GFLOP, with at most 16
+# channels on a side 0.5, and any size where rows or planes are odd or rows too long for the streaming form
+EDGES = [
+    (3, 33, 32, 32, 65, 3, 3, 1, 1, 1, 1),      # one channel and one output channel over a 32 tile
+    (8, 31, 16, 16, 31, 3, 3, 1, 1, 1, 1),      # one under
+    (9, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1),        # a last tile of one image
+    (73, 40, 4, 4, 40, 3, 3, 1, 1, 1, 1),       # two rows per chunk, a last tile of one image
+    (2, 32, 27, 27, 32, 3, 3, 1, 1, 1, 1),      # a row's last chunk holds three columns; last tile of three rows
+    (1, 32, 5, 300, 32, 3, 3, 1, 1, 1, 1),      # rows cut into column tiles: neighbour words on both sides
+    (1, 64, 9, 130, 64, 3, 3, 1, 1, 1, 1),      # the last column tile holds two columns
+    (160, 20, 7, 4, 20, 3, 3, 1, 1, 1, 1),      # the narrowest rows
+    (2, 20, 6, 7, 20, 3, 3, 1, 1, 0, 0),        # no padding: the output starts left of the input's first column
+    (2, 20, 6, 7, 20, 3, 3, 1, 1, 3, 4),        # more padding than the filter needs
+    (2, 20, 9, 21, 24, 3, 3, 2, 2, 1, 1),       # strides, odd width
+    (2, 20, 9, 20, 24, 3, 3, 3, 2, 0, 2),
+    (40, 20, 9, 20, 24, 3, 3, 2, 1, 1, 1),      # stride in rows alone
+    (500, 3, 20, 24, 40, 3, 3, 1, 1, 1, 1),     # (channel, filter row) columns
+    (2, 9, 12, 13, 40, 3, 3, 1, 1, 1, 1),
+    (2, 33, 11, 14, 18, 5, 5, 1, 1, 2, 2),
+    (40, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1),     # several workgroups share the reduction
+    (1, 1, 5, 5, 1, 3, 3, 1, 1, 1, 1),
+]
+
+
+def mk(t):
+    N, C, H, W, K, R, S, sh, sw, ph, pw = t
+    return B.desc(N, C, H, W, K, R, S, stride=sh, pad=ph, stride_w=sw, pad_w=pw)
+
+
+def run(d, X, dY):
+    import torch
+    dW = torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda")
+    return B.conv_wgrad_exact(d, X, dY, dW=dW).cpu().numpy()
+
+
+@pytest.mark.parametrize("t", EDGES)
+def test_edges_match_the_oracle(t):
+    d = mk(t)
+    X, dY = rand_inputs(d, 99)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    # fp32 sums of exact products: far inside the fp32 tolerance (a lost piece would cost 4e-3, 2e-5 or 1e-7)
+    assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), want) < TOL["fp32"] / 50
+
+
+@pytest.mark.parametrize("t", [EDGES[4], EDGES[5], EDGES[12], EDGES[13], EDGES[15]])
+def test_tensors_aligned_to_their_elements_only(t):
+    import torch
+    d = mk(t)
+    X, dY = rand_inputs(d, 5)
+    Xu = torch.empty(X.size + 1, device="cuda")[1:].view(X.shape).copy_(to_gpu(X))
+    dYu = torch.empty(dY.size + 3, device="cuda")[3:].view(dY.shape).copy_(to_gpu(dY))
+    assert np.array_equal(run(d, Xu, dYu), run(d, to_gpu(X), to_gpu(dY)))
+
+
+@pytest.mark.parametrize("t", [EDGES[0], EDGES[3], EDGES[4], EDGES[6], EDGES[10], EDGES[13]])
+@pytest.mark.parametrize("where", ["X", "dY"])
+@pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38])
+def test_values_the_pieces_cannot_hold(t, where, bad):
+    """An infinity meets zeros and both signs in its pieces' products, and 3.4e38 rounds to infinity as bf16: the result
+    is the definition's all the same, infinities where it has them and everything untouched by the value finite."""
+    d = mk(t)
+    X, dY = rand_inputs(d, 7)
+    a = X if where == "X" else dY
+    for at in ((0, 0, 0, 0), (-1, -1, -1, -1), (0, 1 % a.shape[1], a.shape[2] // 2, a.shape[3] // 2)):
+        a[at] = bad
+    with np.errstate(all="ignore"):
+        want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+        want32 = want.astype(np.float32)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    assert np.array_equal(np.isnan(got), np.isnan(want32))
+    assert np.array_equal(got[np.isinf(want32)], want32[np.isinf(want32)])
+    fine = np.isfinite(want32)
+    # entries that sum the huge value are compared at their own size, the rest at theirs
+    big = fine & (np.abs(want) > 1e30)
+    for part in (big, fine & ~big):
+        if part.any():
+            assert normwise_err(got[part], want[part]) < TOL["fp32"]
+
+
+@pytest.mark.parametrize("scale", [(1e15, 1e15), (1e-12, 1e-12), (1e-20, 1e18), (1e25, 1e-25)])
+def test_scales_far_from_one(scale):
+    d = mk(EDGES[0])
+    X, dY = rand_inputs(d, 11)
+    X, dY = X * np.float32(scale[0]), dY * np.float32(scale[1])
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), want) < TOL["fp32"] / 50
+
+
+def test_wide_range_of_magnitudes_within_a_tensor():
+    """Elements of 2^-40 .. 2^40 side by side: every product keeps fp32's relative precision, so an output channel of
+    small gradients is as exact as one of large ones."""
+    d = mk((4, 32, 12, 12, 64, 3, 3, 1, 1, 1, 1))
+    X, dY = rand_inputs(d, 13)
+    dY *= np.exp2(np.linspace(-40, 40, d.K)).astype(np.float32)[None, :, None, None]
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    for k in range(d.K):
+        assert normwise_err(got[k], want[k]) < TOL["fp32"] / 50
+
+
+def test_error_is_that_of_fp32_sums():
+    """64 -> 64 @ 32x32 at N = 128: the fp32 matrix core's kernel is 6.5e-7 of the result (2-norm) off."""
+    d = mk((128, 64, 32, 32, 64, 3, 3, 1, 1, 1, 1))
+    X, dY = rand_inputs(d, 17)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    assert np.linalg.norm(got - want) < 6.5e-7 * np.linalg.norm(want)
+
+
+def test_run_of_layers_equals_the_single_calls_to_rounding():
+    """Layers of several variants, and more groups than a launch carries, in one schedule run."""
+    import torch
+    shapes = EDGES + [(5, 64 + 8 * i, 16, 16, 64, 3, 3, 1, 1, 1, 1) for i in range(10)] + [(40, 128, 16, 16, 128, 3, 3, 1, 1, 1, 1)] * 3
+    ds = [mk(t) for t in shapes]
+    data = [tuple(to_gpu(a) for a in rand_inputs(d, 100 + i)) for i, d in enumerate(ds)]
+    out = [torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda") for d in ds]
+    s = B.Schedule(ds, [x for x, _ in data], [y for _, y in data], out)
+    m = [B.EXACT] * len(ds)
+    s.run(m, B.alloc_workspace(s.workspace_bytes(m)))
+    for d, (X, dY), got in zip(ds, data, out):
+        assert normwise_err(got.cpu().numpy(), run(d, X, dY).astype(np.float64)) < TOL["fp32"] / 50
