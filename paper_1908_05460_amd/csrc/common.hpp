@@ -80,7 +80,7 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nblocks)
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ---- internal launchers (host). Each validates nothing: the C ABI layer did. ----
-// fp32 on the bf16 matrix core (exact_x3.hip)
+// fp32 as three bf16 pieces, or bf16, on the bf16 matrix core (exact_x3.hip)
 struct X3Plan {
     int variant, ktiles, ctiles, splits;
     int nti, ht, iht, twc, h_tiles, w_tiles, n_groups, nch, ch, packed, halo, vlo, xcol0;
@@ -98,7 +98,7 @@ struct ExactPlan {
     int img4;                        // streaming form, 4x4 planes: image-uniform position order (a step contracts one position of four images)
     int mm16;                        // bf16 matrix-core form of the streaming kernel
     int direct;                      // general form: no tile of whole output rows fits the LDS
-    int x3;                          // fp32 as three bf16 pieces on the bf16 matrix core: 0 no, 1 if alone, 2 in a run of several layers too
+    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 in a run of several layers too
     X3Plan x3p;
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     size_t lds_bytes, ws_bytes;
@@ -115,6 +115,7 @@ struct MultiQueue;
 int launch_exact_plane2(const Geometry &g, const Batch &b, hipStream_t st, MultiQueue *mq = nullptr);
 struct CombineQueue;
 bool plan_exact_x3(const Geometry &g, X3Plan &pl);
+bool x3_needs_alignment(const X3Plan &pl);
 struct X3Queue;
 X3Queue *x3_queue_new();
 void x3_queue_delete(X3Queue *q);

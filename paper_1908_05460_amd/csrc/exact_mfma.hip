@@ -592,6 +592,19 @@ ExactPlan plan_exact(const Geometry &g, bool allow_stream)
     if (!allow_stream || pl.plane2 || !tune_int("WGRAD_X3", 1)) return pl;
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     if (pl.stream && g.sw > 1 && gflop >= 1.5) return pl;
+    if (g.bf16) {
+        // one piece, one product.  All that the bf16 kernel of exact_bf16.hip does not take (224x224, 64 -> 64, N = 4: 393 ->
+        // 46 us; 28x28, 128 -> 128, N = 64: 147 -> 41; ResNet-20, whose layers ran widened to fp32 one by one, N = 30 / 128 /
+        // 512: 95 / 150 / 355 -> 40 / 51 / 124), and of what that takes short reductions alone (64 -> 64 @ 32x32, N = 16:
+        // 17.9 -> 14.5, N = 128: 28 against 30, N = 512: 57 against 64; VGG-19 in runs: 459 against 469)
+        if (pl.mm16 && gflop >= 4.0) return pl;
+        if (!plan_exact_x3(g, pl.x3p)) return pl;
+        pl.x3 = pl.mm16 ? 1 : 2;
+        const size_t need = pl.x3p.splits > 1 ? align_up((size_t)pl.x3p.splits * g.dw_elems() * 4) : 0;
+        if (need > pl.ws_bytes) pl.ws_bytes = need;
+        pl.ok = true;
+        return pl;
+    }
     const int use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
     if (!use || !plan_exact_x3(g, pl.x3p)) return pl;
     pl.x3 = use;
@@ -649,9 +662,9 @@ static int launch_exact_staged(const Geometry &g, const ExactPlan &pl, const voi
 int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void *ws, hipStream_t st, CombineQueue *defer,
                  MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq)
 {
-    if (plan.x3 == 2 || (plan.x3 && !mq)) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
-    if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // likewise (bf16, 2x2 and 4x4 planes)
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The
         // workgroup target is for the whole launch: a batch splits each reduction less finely.

@@ -1,46 +1,21 @@
 // Host side of the three-piece bf16 form of the exact filter gradient (exact_x3_kernel.hpp): which shapes take it,
 // their tiles, and launches that carry several shapes.
 #include <algorithm>
+#include <vector>
 
 #include "exact_x3_kernel.hpp"
 
 namespace wgrad {
 
-// (id, SH, NTC, S, SW, RAG, HALO, RPC, NCH, DI, XI, KP, CP, CH)
-#define WGRAD_X3_VARIANTS(X) \
-    X(0, 32, 3, 3, 1, false, false, 1, 16, 2, 3, 17, 25, 32) X(1, 32, 3, 3, 1, false, true, 1, 16, 2, 3, 23, 25, 32) \
-    X(2, 32, 3, 3, 1, true, true, 1, 16, 2, 3, 23, 25, 32) X(3, 32, 3, 3, 1, false, false, 2, 16, 2, 3, 17, 25, 32) \
-    X(4, 16, 3, 3, 1, false, false, 1, 16, 1, 2, 17, 33, 16) X(5, 16, 3, 3, 1, true, true, 1, 16, 1, 2, 23, 33, 16) \
-    X(6, 16, 3, 3, 2, false, false, 1, 16, 1, 3, 17, 69, 16) X(7, 16, 3, 3, 2, true, true, 1, 16, 1, 3, 23, 69, 16) \
-    X(8, 16, 1, 3, 1, false, false, 1, 16, 1, 1, 17, 25, 7) X(9, 16, 1, 3, 1, true, true, 1, 16, 1, 1, 23, 25, 7) \
-    X(10, 32, 1, 3, 1, false, false, 1, 16, 2, 2, 17, 25, 12) X(11, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
-    X(12, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
-constexpr int kX3Variants = 13;
-
-struct X3Variant { int sh, ntc, s, sw, rag, halo, rpc, nch, di, xi, kp, cp, ch, lds, occ; };
+struct X3Variant { int bf, sh, ntc, s, sw, rag, halo, rpc, nch, di, xi, kp, cp, ch, lds, occ; };
 static const X3Variant kVariant[kX3Variants] = {
 #define X(ID, ...) {__VA_ARGS__, X3Config<__VA_ARGS__>::kLds, X3Config<__VA_ARGS__>::kOcc},
-    WGRAD_X3_VARIANTS(X)
+    WGRAD_X3_VARIANTS_FP32(X)
+    WGRAD_X3_VARIANTS_BF16(X)
 #undef X
 };
 // workgroups that the chip holds at once
 static int x3_resident(const X3Variant &v) { return kNumCU * std::max(1, std::min(160 * 1024 / v.lds, v.occ)); }
-
-// The parameters are read through the kernel-argument segment pointer: indexing the by-value argument with a run-time
-// group number would make the compiler copy all of it into scratch memory first.
-template <class T>
-__global__ __launch_bounds__(kBlock, T::kOcc) void wgrad_exact_x3(const X3Multi)
-{
-    extern __shared__ __align__(16) char x3_smem[];
-    const X3Multi *mp = (const X3Multi *)__builtin_amdgcn_kernarg_segment_ptr();
-    const int n = mp->n;
-    int gi = 0;
-    for (int i = 1; i < n; ++i) gi += (int)blockIdx.x >= mp->begin[i];
-    const int bid = (int)blockIdx.x - mp->begin[gi], nblk = mp->count[gi];
-    if (bid >= nblk) return;
-    const int first = mp->first[gi];
-    x3_body<T>(mp->s[gi], mp->X + first, mp->dY + first, mp->out + first, x3_smem, bid, nblk);
-}
 
 static int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b); }
 // Tile of a variant for a shape, or false.
@@ -74,14 +49,14 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
     const int vwc = v.rpc == 2 ? 1 : (vw + 7) / 8;           // (images of a tile, its rows and chunk columns are packed in 4, 8 and 4 bits)
     long best = -1;
     int best_x = 0;
-    for (int twc = 1; twc <= std::min(vwc, v.nch); ++twc) {
+    for (int twc = 1; twc <= std::min({vwc, v.nch, 16}); ++twc) {
         const int w_tiles = (vwc + twc - 1) / twc;
         if (twc > 1 && (vwc + twc - 2) / (twc - 1) == w_tiles) continue;      // the same number of narrower tiles does
         const int halo = v.s > 1 && v.rpc == 1 && (w_tiles > 1 || vlo > 0 || vlo + 8 * twc < g.Wo);
         if (halo && !v.halo) continue;
         for (int ht = v.rpc; ht <= g.Ho; ht += v.rpc) {
             if (ht / v.rpc * twc > v.nch) break;
-            int nti = ht >= g.Ho ? std::min(g.N, v.nch / (ht / v.rpc * twc)) : 1;
+            int nti = ht >= g.Ho ? std::min({g.N, v.nch / (ht / v.rpc * twc), 16}) : 1;
             const int iht = (ht - 1) * g.sh + g.R;
             if (iht > 255) break;
             for (; nti >= 1; --nti) {
@@ -112,8 +87,8 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
 // by its own staging and matrix instructions one after the other
 static double x3_tile_us(const X3Variant &v, int share)
 {
-    const double mfma = (double)v.nch / (64 / v.sh) / 4 * 6 * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
-    const double stage = 0.3 + 0.33 * (v.di + v.xi * v.sw);
+    const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.bf ? 1 : 6) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
+    const double stage = 0.3 + (v.bf ? 0.1 : 0.33) * (v.di + v.xi * v.sw);
     return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
 }
 static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(v) / kNumCU); }
@@ -184,14 +159,17 @@ static int x3_choose_splits(const Geometry &g, const X3Plan &pl, int nprob)
     return best;
 }
 
+// whether the variant reads bf16 rows in 8-byte pieces (4-byte aligned tensors), not element by element
+bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].bf && !kVariant[pl.variant].rag; }
+
 bool plan_exact_x3(const Geometry &g, X3Plan &best)
 {
-    if (g.bf16 || g.W < 4 || g.Wo < 4 || g.pw >= 4096) return false;
+    if (g.W < 4 || g.Wo < 4 || g.pw >= 4096) return false;
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     double best_cost = 1e30;
     for (int id = 0; id < kX3Variants; ++id) {
         const X3Variant &v = kVariant[id];
-        if (v.s != g.S || v.sw != g.sw) continue;
+        if (v.bf != g.bf16 || v.s != g.S || v.sw != g.sw) continue;
         X3Plan pl{};
         if (!x3_tile(g, id, pl)) continue;
         // Matrix instructions, in units of a 16x16 tile of the result.  Long reductions do better with 32x32 tiles (a
@@ -199,7 +177,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
         // 16x16 tiles, whose workgroups are quicker to set up and share a CU by four (N = 16: 21 us against 22.5;
         // 48 -> 96 @ 27x27, N = 32, where 32x32 tiles would be a third padding besides: 35 against 49).
         double cost = (double)pl.ktiles * pl.ctiles * pl.w_tiles * pl.h_tiles * pl.n_groups * v.nch * v.ntc *
-                      (v.sh == 32 ? 4.0 : (gflop < 2.0 ? 0.9 : 1.15));
+                      (v.sh == 32 ? 4.0 : (gflop < (g.bf16 ? 12.0 : 2.0) ? 0.9 : 1.15));
         cost *= v.rag ? 1.1 : (v.halo ? 1.02 : 1.0);
         if (cost < best_cost) { best_cost = cost; best = pl; }
     }
@@ -244,15 +222,6 @@ static void x3_fill(const X3Group &it, X3Shape &s)
     s.d_r = FastDiv(g.R);
 }
 
-static int x3_launch(void (*kernel)(const X3Multi), const X3Multi &m, int blocks, size_t lds, hipStream_t st)
-{
-    // more than 64 KB of dynamic LDS has to be granted per kernel function (the CU has 160 KB)
-    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
-        return WGRAD_LAUNCH_FAILED;
-    WGRAD_LAUNCH(kernel, dim3((unsigned)blocks), dim3(kBlock), lds, st, m);
-    return launch_status();
-}
-
 static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
 {
     X3Multi m{};
@@ -266,17 +235,18 @@ static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
         m.count[i] = m.s[i].per_prob * q.b.n;
         m.first[i] = tensors;
         for (int j = 0; j < q.b.n; ++j, ++tensors) {
-            m.X[tensors] = (const float *)q.b.X[j];
-            m.dY[tensors] = (const float *)q.b.dY[j];
+            m.X[tensors] = q.b.X[j];
+            m.dY[tensors] = q.b.dY[j];
             m.out[tensors] = q.pl.splits > 1 ? q.ws + (long)j * q.slice_stride : q.b.dW[j];
         }
         blocks += (m.count[i] + 7) / 8 * 8;
         lds = std::max(lds, (size_t)q.pl.lds);
     }
     m.begin[n] = blocks;
+    if (it[0]->pl.variant >= kX3FirstBf16) return x3_launch_bf16(it[0]->pl.variant, m, blocks, lds, st);
     switch (it[0]->pl.variant) {
 #define X(ID, ...) case ID: return x3_launch(wgrad_exact_x3<X3Config<__VA_ARGS__>>, m, blocks, lds, st);
-        WGRAD_X3_VARIANTS(X)
+        WGRAD_X3_VARIANTS_FP32(X)
 #undef X
         default: return WGRAD_UNSUPPORTED;
     }

@@ -21,6 +21,8 @@
 // result.  All irregularity -- odd widths, any padding, strides, ragged last tiles, any alignment -- is met while
 // staging: dY and X rows are loaded in 16-byte pieces (4-byte aligned), split, and written to LDS as chunks of
 // each piece, zero outside the tensors.  Two workgroups share a CU: one stages while the other multiplies.
+// bf16 inputs are their own only piece: the same kernel with one product per pair serves the bf16 shapes that
+// exact_bf16_kernel.hpp does not take.
 #pragma once
 #include "exact_common.hpp"
 
@@ -52,7 +54,7 @@ struct X3Multi {
     int count[kX3MultiMax];
     int first[kX3MultiMax];          // the group's first problem in the tensor tables
     X3Shape s[kX3MultiMax];
-    const float *X[kX3Tensors], *dY[kX3Tensors];
+    const void *X[kX3Tensors], *dY[kX3Tensors];
     float *out[kX3Tensors];          // per problem: dW when splits == 1, else partials [splits][K][C*R*S]
 };
 static_assert(sizeof(X3Multi) <= 4096, "kernel arguments");
@@ -113,8 +115,8 @@ __device__ __forceinline__ void x3_realign(float (&v)[4], int d)
 
 // The workgroup's whole result with fp32 multiply-adds straight from the tensors, X read as zero outside its bounds: its
 // tiles' slots, and in the first and last tile of a row the positions whose tap lies beyond all slots.
-template <int SH, int NTC, int S, int SW, int NTHR>
-__device__ __forceinline__ void x3_general(const X3Shape &p, const float *X, const float *dY, float *out, int k0, int coltile,
+template <bool BF, int SH, int NTC, int S, int SW, int NTHR>
+__device__ __forceinline__ void x3_general(const X3Shape &p, const void *X, const void *dY, float *out, int k0, int coltile,
                                         int c_first, int wt_begin, int wt_end, int slots)
 {
     const Geometry &g = p.g;
@@ -132,12 +134,12 @@ __device__ __forceinline__ void x3_general(const X3Shape &p, const float *X, con
             for (int n = n0; n < n0 + p.nti && n < g.N; ++n)
                 for (int h = hti * p.ht; h < (hti + 1) * p.ht && h < g.Ho; ++h) {
                     const int ih = h * g.sh + r - g.ph;
-                    const float *y = dY + (((long)n * g.K + k) * g.Ho + h) * g.Wo, *x = X + (((long)n * g.C + c) * g.H + ih) * g.W;
+                    const long y0 = (((long)n * g.K + k) * g.Ho + h) * g.Wo, x0 = (((long)n * g.C + c) * g.H + ih) * g.W;
                     const int v0 = p.vlo + wti * slots - x3_shift(s, S, SW);
                     const int w0 = wti && v0 > 0 ? v0 : 0, w1 = wti + 1 < p.w_tiles ? v0 + slots : g.Wo;
                     for (int w = w0; w < w1 && w < g.Wo; ++w) {
                         const int iw = w * SW + s - g.pw;
-                        acc = fmaf(y[w], ih >= 0 && ih < g.H && iw >= 0 && iw < g.W ? x[iw] : 0.f, acc);
+                        acc = fmaf(load_elem<BF>(dY, y0 + w), ih >= 0 && ih < g.H && iw >= 0 && iw < g.W ? load_elem<BF>(X, x0 + iw) : 0.f, acc);
                     }
                 }
         }
@@ -145,18 +147,20 @@ __device__ __forceinline__ void x3_general(const X3Shape &p, const float *X, con
     }
 }
 
-// SH: rows and columns of the matrix instruction (32: 32x32x16, 16: 16x16x32).  NTC: column tiles.  S: filter width.
+// BF: bf16 inputs, which are their own only piece.  SH: rows and columns of the matrix instruction (32: 32x32x16, 16: 16x16x32).  NTC: column tiles.  S: filter width.
 // SW: column stride.  RAG: rows whose width is not a multiple of four, or that start before column 0 of a tensor.
 // HALO: tiles may be parts of rows.  RPC: rows per chunk (2: rows of four slots).  NCH: chunks of a tile; DI, XI:
 // staging items per thread; KP, CP: LDS chunks per channel of dY and of X (odd: conflict-free 16-byte reads); CH: channels
 // of X (compile-time, so that the operand reads have immediate offsets).
-template <int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int RPC_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
+template <bool BF_, int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int RPC_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
 struct X3Config {
     static constexpr int SH = SH_, NTC = NTC_, S = S_, SW = SW_, RPC = RPC_, NCH = NCH_, DI = DI_, XI = XI_, KP = KP_, CP = CP_, CH = CH_, NW = 4;
-    static constexpr bool RAG = RAG_, HALO = HALO_;
+    static constexpr bool BF = BF_, RAG = RAG_, HALO = HALO_;
+    static constexpr int NP = BF ? 1 : 3;                               // pieces of a number
+    static constexpr int DR = BF && !RAG ? 4 : 8;                       // registers of a chunk on its way to LDS
     static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG ? 3 : 4);      // workgroups that share a CU
     static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
-    static constexpr int kBuf = 16 + 3 * kDy + 16 + 3 * kX;             // of a tile (16 spare bytes before each: a word left of a chunk 0)
+    static constexpr int kBuf = 16 + NP * kDy + 16 + NP * kX;            // of a tile (16 spare bytes before each: a word left of a chunk 0)
     static constexpr int SR = SH == 32 ? 1 : S;                         // filter columns per round of the final exchange
     static constexpr int kEx = NW * SR * SH * (SH + 4) * 4;             // bytes of a round (two alternate)
     static constexpr int kOutP = NTC * SH * S + 4;                      // pitch of the result tile gathered in LDS (16-byte rows)
@@ -166,12 +170,13 @@ struct X3Config {
 };
 
 template <class T>
-__device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt, const float *const *dYt, float *const *outt,
+__device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt, const void *const *dYt, float *const *outt,
                                         char *smem, int bid, int nblk)
 {
     constexpr int SH = T::SH, NTC = T::NTC, S = T::S, SW = T::SW, RPC = T::RPC, NCH = T::NCH, DI = T::DI, XI = T::XI, KP = T::KP, CP = T::CP,
                   NW = T::NW, NTHR = 64 * NW;
-    constexpr bool RAG = T::RAG, HALO = T::HALO, HALF = RPC == 2;
+    constexpr bool BF = T::BF, RAG = T::RAG, HALO = T::HALO, HALF = RPC == 2;
+    constexpr int NP = T::NP, DR = T::DR, ESZ = BF ? 2 : 4;
     constexpr int CPS = 64 / SH;                        // chunks per step (lane groups of an operand)
     constexpr int NST = NCH / (CPS * NW);                // steps per wavefront and tile
     constexpr int AV = SH * SH / 64;                    // accumulator registers per output tile
@@ -185,13 +190,13 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
 
     uint32_t *const tab = (uint32_t *)smem;                       // [NCH] chunk -> A offset | B offset << 12 | mask left << 30 | mask right << 31
     uint32_t *const flag = tab + NCH;                        // set when the pieces cannot represent the tile
-    char *const buf = smem + T::kHead;                  // dY [3][SH][KP] chunks, X [3][CH][CP] chunks
-    constexpr int dy_piece = T::kDy, x_piece = T::kX, kDyAt = 16, kXAt = 16 + 3 * T::kDy + 16;
+    char *const buf = smem + T::kHead;                  // dY [NP][SH][KP] chunks, X [NP][CH][CP] chunks
+    constexpr int dy_piece = T::kDy, x_piece = T::kX, kDyAt = 16, kXAt = 16 + NP * T::kDy + 16;
 
     const int logical_all = xcd_contiguous_id(bid, nblk);
     const int prob = logical_all / p.per_prob;
     const int logical = logical_all - prob * p.per_prob;
-    const float *const Xp = Xt[prob], *const dYp = dYt[prob];
+    const char *const Xp = (const char *)Xt[prob], *const dYp = (const char *)dYt[prob];
     const int coltile = logical % p.ctiles;
     const int ktile = (logical / p.ctiles) % p.ktiles;
     const int split = logical / (p.ctiles * p.ktiles);
@@ -242,7 +247,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
         }
     }
 
-    float dr[DI][8], xr[XI][8 * SW], hr[2];
+    uint32_t dr[DI][DR], xr[XI][DR * SW], hr[2];
     struct Tile { int n0, h0, wc0; };
     auto tile_of = [&](int wt) {
         uint32_t q, wti, ng, hti;
@@ -253,21 +258,34 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
     // Loads go through a buffer descriptor of 2^31 bytes from the tile's first row; what is to be zero is asked for
     // beyond it, and the hardware answers 0 without a memory access: nothing is masked afterwards.
     constexpr uint32_t kDead = 0x80000000u;
-    auto rsrc_of = [&](const float *base) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, kDead, 0x00020000); };
-    // four columns of a row (element offset `row`) from any column
-    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, bool live, uint32_t row, int col, int width, float *v) {
-        int c = col;
-        if (RAG) c = col < 0 ? 0 : (col > width - 4 ? width - 4 : col);
-        live = live && (RAG ? (unsigned)(col + 3) < (unsigned)(width + 3) : col < width);
-        const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, live ? (row + (uint32_t)c) * 4u : kDead, 0, 0);
+    auto rsrc_of = [&](const char *base) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, kDead, 0x00020000); };
+    // Four columns of a row (element offset `row`) from any column.  fp32 rows that are ragged are read at a column
+    // clamped into the row and realigned when they are staged; ragged bf16 rows (2-byte aligned) element by element.
+    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, bool live, uint32_t row, int col, int width, uint32_t *v) {
+        if constexpr (BF && RAG) {
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = __uint_as_float(q[e]);
+            for (int e = 0; e < 4; ++e)
+                v[e] = __builtin_amdgcn_raw_buffer_load_b16(rs, live && (unsigned)(col + e) < (unsigned)width ? (row + (uint32_t)(col + e)) * 2u : kDead, 0, 0);
+        } else if constexpr (BF) {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, live && col < width ? (row + (uint32_t)col) * 2u : kDead, 0, 0);
+            v[0] = q[0]; v[1] = q[1];
+        } else {
+            int c = col;
+            if (RAG) c = col < 0 ? 0 : (col > width - 4 ? width - 4 : col);
+            live = live && (RAG ? (unsigned)(col + 3) < (unsigned)(width + 3) : col < width);
+            const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, live ? (row + (uint32_t)c) * 4u : kDead, 0, 0);
+#pragma unroll
+            for (int e = 0; e < 4; ++e) v[e] = q[e];
+        }
     };
-    auto fix4 = [&](int col, int width, float *v) {      // RAG: the four that were clamped into the row, back to their columns
-        float q[4] = {v[0], v[1], v[2], v[3]};
+    constexpr bool FIX = RAG && !BF;
+    auto fix4 = [&](int col, int width, uint32_t *v) {   // the four that were clamped into the row, back to their columns
+        float q[4];
+#pragma unroll
+        for (int e = 0; e < 4; ++e) q[e] = __uint_as_float(v[e]);
         x3_realign(q, col - (col < 0 ? 0 : (col > width - 4 ? width - 4 : col)));
 #pragma unroll
-        for (int e = 0; e < 4; ++e) v[e] = q[e];
+        for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(q[e]);
     };
     auto halo_col = [&](const Tile &t) { return (t.wc0 + (at_wc(h_at) ? p.twc : 0)) * 8 + p.vlo - (at_wc(h_at) ? 0 : 2); };
     // (opaque: the fields are taken out of the word where they are used, not kept in registers of their own across the loop)
@@ -275,27 +293,29 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
     auto load_tile = [&](int wt) {
         const Tile t = tile_of(wt);
         const int n_left = g.N - t.n0, h_left = g.Ho - t.h0;
-        const auto yb = rsrc_of(dYp + ((long)t.n0 * g.K + k0) * L + (long)t.h0 * g.Wo);
+        const auto yb = rsrc_of(dYp + (((long)t.n0 * g.K + k0) * L + (long)t.h0 * g.Wo) * ESZ);
 #pragma unroll
         for (int u = 0; u < DI; ++u) {
             const uint32_t at = fresh(d_at[u]);
             const bool live = at != ~0u && at_n(at) < n_left && at_row(at) < h_left;
             const int col = HALF ? 0 : (at_wc(at) + t.wc0) * 8 + p.vlo;
             load4(yb, live, d_off[u], col, g.Wo, dr[u]);
-            if (HALF) load4(yb, live && at_row(at) + 1 < h_left, d_off[u] + g.Wo, 0, g.Wo, dr[u] + 4);
-            else load4(yb, live, d_off[u], col + 4, g.Wo, dr[u] + 4);
+            if (HALF) load4(yb, live && at_row(at) + 1 < h_left, d_off[u] + g.Wo, 0, g.Wo, dr[u] + DR / 2);
+            else load4(yb, live, d_off[u], col + 4, g.Wo, dr[u] + DR / 2);
         }
         if (HALO && p.halo) {
             const int col = halo_col(t);
             const bool live = h_at != ~0u && at_n(h_at) < n_left && at_row(h_at) < h_left;
 #pragma unroll
-            for (int e = 0; e < 2; ++e)
-                hr[e] = __uint_as_float(__builtin_amdgcn_raw_buffer_load_b32(
-                    yb, live && (unsigned)(col + e) < (unsigned)g.Wo ? (h_off + col + e) * 4u : kDead, 0, 0));
+            for (int e = 0; e < 2; ++e) {
+                const uint32_t off = live && (unsigned)(col + e) < (unsigned)g.Wo ? (h_off + col + e) * (uint32_t)ESZ : kDead;
+                if constexpr (BF) hr[e] = __builtin_amdgcn_raw_buffer_load_b16(yb, off, 0, 0);
+                else hr[e] = __builtin_amdgcn_raw_buffer_load_b32(yb, off, 0, 0);
+            }
         }
         // (the first input row of a tile may lie above the plane: offsets count from it, dead rows are never asked for)
         const int ih0 = t.h0 * g.sh - g.ph;
-        const auto xb = rsrc_of(Xp + ((long)t.n0 * g.C + c_first) * g.H * g.W);
+        const auto xb = rsrc_of(Xp + ((long)t.n0 * g.C + c_first) * g.H * g.W * ESZ);
         const uint32_t row0 = (uint32_t)(ih0 * g.W);
 #pragma unroll
         for (int u = 0; u < XI; ++u) {
@@ -305,63 +325,79 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
             const bool live = here && (unsigned)ih < (unsigned)g.H;
             const int col = HALF ? 0 : (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
             load4(xb, live, x_off[u] + row0, col, g.W, xr[u]);
-            if (HALF) load4(xb, here && (unsigned)(ih + 1) < (unsigned)g.H, x_off[u] + row0 + g.W, 0, g.W, xr[u] + 4);
+            if (HALF) load4(xb, here && (unsigned)(ih + 1) < (unsigned)g.H, x_off[u] + row0 + g.W, 0, g.W, xr[u] + DR / 2);
             else {
 #pragma unroll
-                for (int q = 1; q < 2 * SW; ++q) load4(xb, live, x_off[u] + row0, col + 4 * q, g.W, xr[u] + 4 * q);
+                for (int q = 1; q < 2 * SW; ++q) load4(xb, live, x_off[u] + row0, col + 4 * q, g.W, xr[u] + DR / 2 * q);
             }
         }
     };
-    auto put = [&](const float (&v)[8], char *dst, int piece) {
+    // a chunk's pieces to LDS; v(e): its element e (fp32 bits, or bf16 bits in the low half)
+    auto put = [&](auto v, char *dst, int piece) {
         x3_u4 h, m, l;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            uint32_t a, b, c;
-            x3_split2(v[2 * e], v[2 * e + 1], a, b, c);
-            h[e] = a; m[e] = b; l[e] = c;
+            if constexpr (BF) h[e] = __builtin_amdgcn_perm(v(2 * e + 1), v(2 * e), 0x05040100u);
+            else {
+                uint32_t a, b, c;
+                x3_split2(__uint_as_float(v(2 * e)), __uint_as_float(v(2 * e + 1)), a, b, c);
+                h[e] = a; m[e] = b; l[e] = c;
+            }
         }
         *(x3_u4 *)dst = h;
-        *(x3_u4 *)(dst + piece) = m;
-        *(x3_u4 *)(dst + 2 * piece) = l;
+        if constexpr (!BF) {
+            *(x3_u4 *)(dst + piece) = m;
+            *(x3_u4 *)(dst + 2 * piece) = l;
+        }
+    };
+    // element i of a run of columns in staging registers
+    auto elem = [&](const uint32_t *v, int i) -> uint32_t {
+        if constexpr (DR == 4) return i & 1 ? v[i / 2] >> 16 : v[i / 2];
+        else return v[i];
     };
     auto commit_tile = [&](int wt) {
         Tile t{0, 0, 0};
-        if (RAG) t = tile_of(wt);
+        if (FIX) t = tile_of(wt);
 #pragma unroll
         for (int u = 0; u < DI; ++u) {
             const uint32_t at = fresh(d_at[u]);
-            if (RAG) {
+            if constexpr (FIX) {
                 const int col = (at_wc(at) + t.wc0) * 8 + p.vlo;
                 fix4(col, g.Wo, dr[u]);
                 fix4(col + 4, g.Wo, dr[u] + 4);
             }
-            if (at != ~0u) put(dr[u], buf + kDyAt + at_dst(at), dy_piece);
+            if (at != ~0u) {
+                if constexpr (DR == 4) *(x3_u4 *)(buf + kDyAt + at_dst(at)) = x3_u4{dr[u][0], dr[u][1], dr[u][2], dr[u][3]};
+                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece);
+            }
         }
         if (HALO && p.halo) {
-            uint32_t h, m, l;
-            x3_split2(hr[0], hr[1], h, m, l);
+            uint32_t h, m = 0, l = 0;
+            if constexpr (BF) h = hr[0] | hr[1] << 16;
+            else x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), h, m, l);
             if (h_at != ~0u) {
                 char *const dst = buf + kDyAt + at_dst(h_at) + (at_wc(h_at) ? 0 : 12);
                 *(uint32_t *)dst = h;
-                *(uint32_t *)(dst + dy_piece) = m;
-                *(uint32_t *)(dst + 2 * dy_piece) = l;
+                if constexpr (!BF) {
+                    *(uint32_t *)(dst + dy_piece) = m;
+                    *(uint32_t *)(dst + 2 * dy_piece) = l;
+                }
             }
         }
 #pragma unroll
         for (int u = 0; u < XI; ++u) {
             const uint32_t at = fresh(x_at[u]);
-            if (RAG) {
+            if constexpr (FIX) {
                 const int col = (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
 #pragma unroll
                 for (int q = 0; q < 2 * SW; ++q) fix4(col + 4 * q, g.W, xr[u] + 4 * q);
             }
             if (at != ~0u) {
+                if constexpr (DR == 4 && SW == 1) *(x3_u4 *)(buf + kXAt + at_dst(at)) = x3_u4{xr[u][0], xr[u][1], xr[u][2], xr[u][3]};
+                else {
 #pragma unroll
-                for (int f = 0; f < SW; ++f) {
-                    float v[8];
-#pragma unroll
-                    for (int e = 0; e < 8; ++e) v[e] = xr[u][e * SW + f];
-                    put(v, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece);
+                    for (int f = 0; f < SW; ++f)
+                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece);
                 }
             }
         }
@@ -384,7 +420,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
         tab[q] = e;
     }
     if (tid == 0) *flag = 0;
-    for (int e = tid; e < 3 * SH; e += NTHR) *(x3_u4 *)(buf + kDyAt + (e * KP + KP - 1) * 16) = x3_u4{0u, 0u, 0u, 0u};
+    for (int e = tid; e < NP * SH; e += NTHR) *(x3_u4 *)(buf + kDyAt + (e * KP + KP - 1) * 16) = x3_u4{0u, 0u, 0u, 0u};
     if (k0 + SH > g.K || c_first + T::CH > g.C) {
         // rows and columns beyond the result are never staged: zeros, so that no left-over bits make infinities of them
         for (int e = tid; e < T::kBuf / 16; e += NTHR) *(x3_u4 *)(buf + e * 16) = x3_u4{0u, 0u, 0u, 0u};
@@ -434,7 +470,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
             // the products of dY's smallest piece first; a piece's shifted operands serve every column tile, X's pieces
             // are read again for each (reads that the LDS has to spare, against 24 registers that the loop has not)
 #pragma unroll
-            for (int qa = 2; qa >= 0; --qa) {
+            for (int qa = NP - 1; qa >= 0; --qa) {
                 const x3_u4 w = *(const x3_u4 *)(ap + qa * dy_piece);
                 uint32_t lw = 0, rw = 0;
                 if (S > 1 && !HALF) {
@@ -459,7 +495,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
                         if (!used) continue;
                         const char *const q0 = bp + coloff[t] + f * p.twc * 16;
 #pragma unroll
-                        for (int qb = 2 - qa; qb >= 0; --qb) {
+                        for (int qb = NP - 1 - qa; qb >= 0; --qb) {
                             x3_bf8 b;
                             if (HALF) {
                                 const uint2 lo = *(const uint2 *)(q0 + qb * x_piece), hi = *(const uint2 *)(q0 + qb * x_piece + 8);
@@ -493,7 +529,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
     __syncthreads();
     float *const out = outt[prob] + (long)split * g.K * CRS;
     if (*(volatile uint32_t *)flag) {
-        x3_general<SH, NTC, S, SW, NTHR>(p, Xp, dYp, out, k0, coltile, c_first, wt_begin, wt_end, HALF ? 4 : p.twc * 8);
+        x3_general<BF, SH, NTC, S, SW, NTHR>(p, Xp, dYp, out, k0, coltile, c_first, wt_begin, wt_end, HALF ? 4 : p.twc * 8);
         return;
     }
     // ---- the wavefronts' sums: through LDS, SR filter columns of a column tile at a time (four rows of a lane side by
@@ -544,5 +580,50 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const float *const *Xt
         }
     }
 }
+
+// (id, BF, SH, NTC, S, SW, RAG, HALO, RPC, NCH, DI, XI, KP, CP, CH)
+#define WGRAD_X3_VARIANTS_FP32(X) \
+    X(0, false, 32, 3, 3, 1, false, false, 1, 16, 2, 3, 17, 25, 32) X(1, false, 32, 3, 3, 1, false, true, 1, 16, 2, 3, 23, 25, 32) \
+    X(2, false, 32, 3, 3, 1, true, true, 1, 16, 2, 3, 23, 25, 32) X(3, false, 32, 3, 3, 1, false, false, 2, 16, 2, 3, 17, 25, 32) \
+    X(4, false, 16, 3, 3, 1, false, false, 1, 16, 1, 2, 17, 33, 16) X(5, false, 16, 3, 3, 1, true, true, 1, 16, 1, 2, 23, 33, 16) \
+    X(6, false, 16, 3, 3, 2, false, false, 1, 16, 1, 3, 17, 69, 16) X(7, false, 16, 3, 3, 2, true, true, 1, 16, 1, 3, 23, 69, 16) \
+    X(8, false, 16, 1, 3, 1, false, false, 1, 16, 1, 1, 17, 25, 7) X(9, false, 16, 1, 3, 1, true, true, 1, 16, 1, 1, 23, 25, 7) \
+    X(10, false, 32, 1, 3, 1, false, false, 1, 16, 2, 2, 17, 25, 12) X(11, false, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
+    X(12, false, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
+#define WGRAD_X3_VARIANTS_BF16(X) \
+    X(13, true, 32, 3, 3, 1, false, false, 1, 32, 4, 5, 33, 41, 32) X(14, true, 32, 3, 3, 1, false, true, 1, 16, 2, 3, 23, 25, 32) \
+    X(15, true, 32, 3, 3, 1, true, true, 1, 16, 2, 3, 23, 25, 32) \
+    X(16, true, 16, 3, 3, 1, false, false, 1, 32, 2, 3, 33, 41, 16) X(17, true, 16, 3, 3, 1, true, true, 1, 32, 2, 3, 43, 41, 16) \
+    X(18, true, 16, 3, 3, 2, false, false, 1, 16, 1, 3, 17, 69, 16) X(19, true, 16, 3, 3, 2, true, true, 1, 16, 1, 3, 23, 69, 16) \
+    X(20, true, 16, 1, 3, 1, false, false, 1, 32, 2, 2, 33, 41, 7) X(21, true, 16, 1, 3, 1, true, true, 1, 32, 2, 2, 43, 41, 7) \
+    X(22, true, 32, 1, 3, 1, false, false, 1, 32, 4, 2, 33, 41, 12) X(23, true, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
+    X(24, true, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
+constexpr int kX3Variants = 25, kX3FirstBf16 = 13;
+
+// The parameters are read through the kernel-argument segment pointer: indexing the by-value argument with a run-time
+// group number would make the compiler copy all of it into scratch memory first.
+template <class T>
+__global__ __launch_bounds__(kBlock, T::kOcc) void wgrad_exact_x3(const X3Multi)
+{
+    extern __shared__ __align__(16) char x3_smem[];
+    const X3Multi *mp = (const X3Multi *)__builtin_amdgcn_kernarg_segment_ptr();
+    const int n = mp->n;
+    int gi = 0;
+    for (int i = 1; i < n; ++i) gi += (int)blockIdx.x >= mp->begin[i];
+    const int bid = (int)blockIdx.x - mp->begin[gi], nblk = mp->count[gi];
+    if (bid >= nblk) return;
+    const int first = mp->first[gi];
+    x3_body<T>(mp->s[gi], mp->X + first, mp->dY + first, mp->out + first, x3_smem, bid, nblk);
+}
+
+inline int x3_launch(void (*kernel)(const X3Multi), const X3Multi &m, int blocks, size_t lds, hipStream_t st)
+{
+    // more than 64 KB of dynamic LDS has to be granted per kernel function (the CU has 160 KB)
+    if (lds > 64 * 1024 && hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds) != hipSuccess)
+        return WGRAD_LAUNCH_FAILED;
+    WGRAD_LAUNCH(kernel, dim3((unsigned)blocks), dim3(kBlock), lds, st, m);
+    return launch_status();
+}
+int x3_launch_bf16(int variant, const X3Multi &m, int blocks, size_t lds, hipStream_t st);      // instantiated in a file of their own
 
 }  // namespace wgrad

@@ -1,5 +1,6 @@
-"""The exact gradient of fp32 layers as three bf16 pieces on the bf16 matrix core: the shapes where its tiles, its
-staging and its result tile have edges, the inputs that the pieces cannot represent, and its error against fp64."""
+"""The exact gradient of fp32 layers as three bf16 pieces on the bf16 matrix core, and of bf16 layers as one: the shapes
+where its tiles, its staging and its result tile have edges, the inputs that the pieces cannot represent, and its error
+against fp64."""
 import numpy as np
 import pytest
 
@@ -33,9 +34,9 @@ EDGES = [
 ]
 
 
-def mk(t):
+def mk(t, dtype="fp32"):
     N, C, H, W, K, R, S, sh, sw, ph, pw = t
-    return B.desc(N, C, H, W, K, R, S, stride=sh, pad=ph, stride_w=sw, pad_w=pw)
+    return B.desc(N, C, H, W, K, R, S, stride=sh, pad=ph, stride_w=sw, pad_w=pw, dtype=B.BF16 if dtype == "bf16" else B.F32)
 
 
 def run(d, X, dY):
@@ -44,10 +45,11 @@ def run(d, X, dY):
     return B.conv_wgrad_exact(d, X, dY, dW=dW).cpu().numpy()
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("t", EDGES)
-def test_edges_match_the_oracle(t):
-    d = mk(t)
-    X, dY = rand_inputs(d, 99)
+def test_edges_match_the_oracle(t, dtype):
+    d = mk(t, dtype)
+    X, dY = rand_inputs(d, 99, dtype)
     want = oracle.wgrad_exact(oracle_shape(d), X, dY)
     # fp32 sums of exact products: far inside the fp32 tolerance (a lost piece would cost 4e-3, 2e-5 or 1e-7)
     assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), want) < TOL["fp32"] / 50
@@ -61,6 +63,33 @@ def test_tensors_aligned_to_their_elements_only(t):
     Xu = torch.empty(X.size + 1, device="cuda")[1:].view(X.shape).copy_(to_gpu(X))
     dYu = torch.empty(dY.size + 3, device="cuda")[3:].view(dY.shape).copy_(to_gpu(dY))
     assert np.array_equal(run(d, Xu, dYu), run(d, to_gpu(X), to_gpu(dY)))
+
+
+@pytest.mark.parametrize("t", [EDGES[1], EDGES[4], EDGES[13]])
+def test_bf16_tensors_aligned_to_their_elements_only(t):
+    """Whole rows are read in 8-byte pieces; a tensor that starts at any even address takes the older kernels."""
+    import torch
+    d = mk(t, "bf16")
+    X, dY = (to_gpu(a) for a in rand_inputs(d, 5, "bf16"))
+    Xu = torch.empty(X.numel() + 1, dtype=torch.bfloat16, device="cuda")[1:].view(X.shape).copy_(X)
+    dYu = torch.empty(dY.numel() + 3, dtype=torch.bfloat16, device="cuda")[3:].view(dY.shape).copy_(dY)
+    assert normwise_err(run(d, Xu, dYu), run(d, X, dY).astype(np.float64)) < TOL["fp32"] / 50
+
+
+@pytest.mark.parametrize("t", [EDGES[0], EDGES[4], EDGES[6]])
+@pytest.mark.parametrize("where", ["X", "dY"])
+@pytest.mark.parametrize("bad", [0x7F80, 0xFF80, 0x7FC0])
+def test_bf16_infinities_and_nans(t, where, bad):
+    d = mk(t, "bf16")
+    X, dY = rand_inputs(d, 7, "bf16")
+    a = X if where == "X" else dY
+    for at in ((0, 0, 0, 0), (-1, -1, -1, -1), (0, 1 % a.shape[1], a.shape[2] // 2, a.shape[3] // 2)):
+        a[at] = bad
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    fine = np.isfinite(want)
+    assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+    assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / 50
 
 
 @pytest.mark.parametrize("t", [EDGES[0], EDGES[3], EDGES[4], EDGES[6], EDGES[10], EDGES[13]])
@@ -118,12 +147,13 @@ def test_error_is_that_of_fp32_sums():
     assert np.linalg.norm(got - want) < 6.5e-7 * np.linalg.norm(want)
 
 
-def test_run_of_layers_equals_the_single_calls_to_rounding():
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
     """Layers of several variants, and more groups than a launch carries, in one schedule run."""
     import torch
     shapes = EDGES + [(5, 64 + 8 * i, 16, 16, 64, 3, 3, 1, 1, 1, 1) for i in range(10)] + [(40, 128, 16, 16, 128, 3, 3, 1, 1, 1, 1)] * 3
-    ds = [mk(t) for t in shapes]
-    data = [tuple(to_gpu(a) for a in rand_inputs(d, 100 + i)) for i, d in enumerate(ds)]
+    ds = [mk(t, dtype) for t in shapes]
+    data = [tuple(to_gpu(a) for a in rand_inputs(d, 100 + i, dtype)) for i, d in enumerate(ds)]
     out = [torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda") for d in ds]
     s = B.Schedule(ds, [x for x, _ in data], [y for _, y in data], out)
     m = [B.EXACT] * len(ds)
