@@ -1443,7 +1443,7 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
     // (16 K multiply-adds per instruction against 64), even though all but one of a map's slots are zero
     // -- up to maps of 256 positions; beyond, the fused kernel below is bound by its dY stream and wins
     if (allow_mm && g.bf16 && g.Ho * g.Wo <= 256 && tune_int("WGRAD_APPROX_MM", 1)) {
-        const ExactPlan ex = plan_exact(g);
+        const ExactPlan ex = plan_exact_plain(g);
         if (ex.ok && ex.mm16) {
             pl.mm = 1;
             pl.ex = ex;
@@ -1460,7 +1460,7 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
     }
     // fp32 inputs on planes of up to four positions: the exact matrix-core kernel on the sparsified dY
     if (allow_mm && !g.bf16 && g.Ho * g.Wo <= 4 && tune_int("WGRAD_APPROX_SX", 1)) {
-        const ExactPlan ex = plan_exact(g);
+        const ExactPlan ex = plan_exact_plain(g);
         if (ex.ok && ex.stream) {
             pl.sx = 1;
             pl.ex = ex;

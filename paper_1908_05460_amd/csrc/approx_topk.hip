@@ -184,16 +184,21 @@ bool topk_sparse_exact(const Geometry &g, int k, ExactPlan &ex)
 {
     if (!tune_int("WGRAD_TOPK_SX", 1)) return false;
     const int L = g.Ho * g.Wo;
-    ex = plan_exact(g);
+    ex = plan_exact_plain(g);
     if (!ex.ok) return false;
     // the bf16 matrix-core kernel runs a dense layer in the time the gather needs for one kept position
     const bool fast_bf16 = ex.mm16 && k >= 2;
     // large maps, few channels: the fused kernel, unless the bf16 matrix core beats it (maps of up to 256 positions)
-    if (topk_takes_fused(g, k)) return fast_bf16 && L <= 256;
-    const ApproxPlan ap = plan_approx(g, /*allow_lds=*/true, /*allow_fused=*/false, /*allow_mm=*/false);
-    const bool lds = ap.use_lds && ap.m * k <= 64;
-    const bool dense_enough = L <= 4 || (lds ? k >= 2 && k * 14 >= L : k * 80 >= L);
-    return fast_bf16 || ((ex.stream || ex.mm16) && dense_enough);
+    bool take;
+    if (topk_takes_fused(g, k)) take = fast_bf16 && L <= 256;
+    else {
+        const ApproxPlan ap = plan_approx(g, /*allow_lds=*/true, /*allow_fused=*/false, /*allow_mm=*/false);
+        const bool lds = ap.use_lds && ap.m * k <= 64;
+        const bool dense_enough = L <= 4 || (lds ? k >= 2 && k * 14 >= L : k * 80 >= L);
+        take = fast_bf16 || ((ex.stream || ex.mm16) && dense_enough);
+    }
+    if (take) ex = plan_exact(g);
+    return take;
 }
 
 int topk_chunks(const Geometry &g)

@@ -104,7 +104,8 @@ struct ExactPlan {
     size_t lds_bytes, ws_bytes;
     bool ok;
 };
-ExactPlan plan_exact(const Geometry &g, bool allow_stream = true);
+ExactPlan plan_exact(const Geometry &g);
+ExactPlan plan_exact_plain(const Geometry &g);      // without the form of exact_x3.hip
 bool plan_exact_stream(const Geometry &g, ExactPlan &pl);
 struct MultiQueue;
 int launch_exact_stream(const Geometry &g, const ExactPlan &pl, const Batch &b, float *const *out, hipStream_t st,

@@ -482,7 +482,8 @@ int choose_splits(const ExactPlan &pl, int nprob, int want_blocks)
     return (int)best;
 }
 
-static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream)
+// sized = false: only which form takes the shape, without its split and workspace
+static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream, bool sized = true)
 {
     ExactPlan pl{};
     const int RS = g.R * g.S;
@@ -568,6 +569,7 @@ static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream)
 
     pl.h_tiles = (g.Ho + pl.ht - 1) / pl.ht;
     pl.n_groups = (g.N + pl.nti - 1) / pl.nti;
+    if (!sized) return pl;
     pl.splits = choose_splits(pl, 1);
     pl.ws_bytes = pl.splits > 1 ? align_up((size_t)pl.splits * g.dw_elems() * 4) : 0;
     // tensors that are not 16-byte aligned fall back to the staged form at launch: size for both
@@ -586,33 +588,33 @@ static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream)
 // 0.6-GFLOP layers at N = 128 are over the line: 107 -> 93).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
 // against 14.8).
-ExactPlan plan_exact(const Geometry &g, bool allow_stream)
+ExactPlan plan_exact(const Geometry &g)
 {
-    ExactPlan pl = plan_exact_forms(g, allow_stream);
-    if (!allow_stream || pl.plane2 || !tune_int("WGRAD_X3", 1)) return pl;
+    ExactPlan pl = plan_exact_forms(g, true, false);
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
-    if (pl.stream && g.sw > 1 && gflop >= 1.5) return pl;
-    if (g.bf16) {
+    int use;
+    if (pl.plane2) use = 0;
+    else if (g.bf16) {
         // one piece, one product.  All that the bf16 kernel of exact_bf16.hip does not take (224x224, 64 -> 64, N = 4: 393 ->
         // 46 us; 28x28, 128 -> 128, N = 64: 147 -> 41; ResNet-20, whose layers ran widened to fp32 one by one, N = 30 / 128 /
         // 512: 95 / 150 / 355 -> 40 / 51 / 124), and of what that takes short reductions alone (64 -> 64 @ 32x32, N = 16:
         // 17.9 -> 14.5, N = 128: 28 against 30, N = 512: 57 against 64; VGG-19 in runs: 459 against 469)
-        if (pl.mm16 && gflop >= 4.0) return pl;
-        if (!plan_exact_x3(g, pl.x3p)) return pl;
-        pl.x3 = pl.mm16 ? 1 : 2;
-        const size_t need = pl.x3p.splits > 1 ? align_up((size_t)pl.x3p.splits * g.dw_elems() * 4) : 0;
-        if (need > pl.ws_bytes) pl.ws_bytes = need;
-        pl.ok = true;
-        return pl;
-    }
-    const int use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
-    if (!use || !plan_exact_x3(g, pl.x3p)) return pl;
+        use = !pl.mm16 ? 2 : (gflop < 4.0 ? 1 : 0);
+    } else if (pl.stream && g.sw > 1 && gflop >= 1.5) use = 0;
+    else use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
+    X3Plan x3{};
+    if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3)) return plan_exact_plain(g);
+    // (the other form's split and workspace only where a call may come back to it)
+    if (use == 1 || x3_needs_alignment(x3)) pl = plan_exact_plain(g);
     pl.x3 = use;
-    const size_t need = pl.x3p.splits > 1 ? align_up((size_t)pl.x3p.splits * g.dw_elems() * 4) : 0;
+    pl.x3p = x3;
+    const size_t need = x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
     if (need > pl.ws_bytes) pl.ws_bytes = need;
     pl.ok = true;
     return pl;
 }
+
+ExactPlan plan_exact_plain(const Geometry &g) { return plan_exact_forms(g, true); }
 
 template <int NT, int WK, bool BF16, int XV>
 static void launch_inst(const ExactParams &p, int grid, size_t lds, hipStream_t st)
@@ -697,7 +699,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
     }
     // staged form: one problem at a time (shapes or alignments the streaming form does not take),
     // each in its own slice of the workspace
-    const ExactPlan pl = (plan.stream || plan.mm16) ? plan_exact(g, false) : plan;
+    const ExactPlan pl = (plan.stream || plan.mm16) ? plan_exact_forms(g, false) : plan;
     for (int i = 0; i < b.n; ++i) {
         char *slice = (char *)ws + (size_t)i * align_up(plan.ws_bytes);
         if (pl.direct) {
