@@ -482,8 +482,8 @@ int choose_splits(const ExactPlan &pl, int nprob, int want_blocks)
     return (int)best;
 }
 
-// sized = false: only which form takes the shape, without its split and workspace
-static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream, bool sized = true)
+// Which form takes the shape; its split and workspace are size_exact's.
+static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream)
 {
     ExactPlan pl{};
     const int RS = g.R * g.S;
@@ -569,12 +569,17 @@ static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream, bool siz
 
     pl.h_tiles = (g.Ho + pl.ht - 1) / pl.ht;
     pl.n_groups = (g.N + pl.nti - 1) / pl.nti;
-    if (!sized) return pl;
+    return pl;
+}
+
+static ExactPlan size_exact(const Geometry &g, ExactPlan pl)
+{
+    if (!pl.ok || pl.direct) return pl;
     pl.splits = choose_splits(pl, 1);
     pl.ws_bytes = pl.splits > 1 ? align_up((size_t)pl.splits * g.dw_elems() * 4) : 0;
     // tensors that are not 16-byte aligned fall back to the staged form at launch: size for both
     if (pl.stream || pl.mm16) {
-        const size_t alt = plan_exact_forms(g, false).ws_bytes;
+        const size_t alt = size_exact(g, plan_exact_forms(g, false)).ws_bytes;
         if (alt > pl.ws_bytes) pl.ws_bytes = alt;
     }
     return pl;
@@ -590,7 +595,7 @@ static ExactPlan plan_exact_forms(const Geometry &g, bool allow_stream, bool siz
 // against 14.8).
 ExactPlan plan_exact(const Geometry &g)
 {
-    ExactPlan pl = plan_exact_forms(g, true, false);
+    ExactPlan pl = plan_exact_forms(g, true);
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     int use;
     if (pl.plane2) use = 0;
@@ -603,9 +608,9 @@ ExactPlan plan_exact(const Geometry &g)
     } else if (pl.stream && g.sw > 1 && gflop >= 1.5) use = 0;
     else use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
     X3Plan x3{};
-    if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3)) return plan_exact_plain(g);
+    if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3)) return size_exact(g, pl);
     // (the other form's split and workspace only where a call may come back to it)
-    if (use == 1 || x3_needs_alignment(x3)) pl = plan_exact_plain(g);
+    if (use == 1 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
     pl.x3 = use;
     pl.x3p = x3;
     const size_t need = x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
@@ -614,7 +619,7 @@ ExactPlan plan_exact(const Geometry &g)
     return pl;
 }
 
-ExactPlan plan_exact_plain(const Geometry &g) { return plan_exact_forms(g, true); }
+ExactPlan plan_exact_plain(const Geometry &g) { return size_exact(g, plan_exact_forms(g, true)); }
 
 template <int NT, int WK, bool BF16, int XV>
 static void launch_inst(const ExactParams &p, int grid, size_t lds, hipStream_t st)
@@ -699,7 +704,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
     }
     // staged form: one problem at a time (shapes or alignments the streaming form does not take),
     // each in its own slice of the workspace
-    const ExactPlan pl = (plan.stream || plan.mm16) ? plan_exact_forms(g, false) : plan;
+    const ExactPlan pl = (plan.stream || plan.mm16) ? size_exact(g, plan_exact_forms(g, false)) : plan;
     for (int i = 0; i < b.n; ++i) {
         char *slice = (char *)ws + (size_t)i * align_up(plan.ws_bytes);
         if (pl.direct) {
