@@ -338,7 +338,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     // groups that the fp32 multi-shape launch carries (those of the 2x2-plane form add nothing to its shares)
     auto group_flops = [&](int i) {
         const ExactPlan &ex = plan[i].ex;
-        if (ex.plane2 || ex.x3 == 2) return 0.0;
+        if (ex.plane2 || ex.x3 >= 2) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
         // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of

@@ -98,7 +98,7 @@ struct ExactPlan {
     int img4;                        // streaming form, 4x4 planes: image-uniform position order (a step contracts one position of four images)
     int mm16;                        // bf16 matrix-core form of the streaming kernel
     int direct;                      // general form: no tile of whole output rows fits the LDS
-    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 in a run of several layers too
+    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run of several layers only
     X3Plan x3p;
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     size_t lds_bytes, ws_bytes;

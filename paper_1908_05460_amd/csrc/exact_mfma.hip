@@ -592,13 +592,15 @@ static ExactPlan size_exact(const Geometry &g, ExactPlan pl)
 // layers so short that one launch of all of them wins (ResNet-20 at N = 16 to 64: 36 to 67 us against 55 to 74; its
 // 0.6-GFLOP layers at N = 128 are over the line: 107 -> 93).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
-// against 14.8).
+// against 14.8).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
+// of its own is what costs (VGG-19, N = 128: 50 us of it against 39); alone that is the faster one (512 -> 512, N = 128:
+// 15.4 us against 24.3).
 ExactPlan plan_exact(const Geometry &g)
 {
     ExactPlan pl = plan_exact_forms(g, true);
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     int use;
-    if (pl.plane2) use = 0;
+    if (pl.plane2) use = gflop >= 1.0 ? 3 : 0;
     else if (g.bf16) {
         // one piece, one product.  All that the bf16 kernel of exact_bf16.hip does not take (224x224, 64 -> 64, N = 4: 393 ->
         // 46 us; 28x28, 128 -> 128, N = 64: 147 -> 41; ResNet-20, whose layers ran widened to fp32 one by one, N = 30 / 128 /
@@ -610,7 +612,7 @@ ExactPlan plan_exact(const Geometry &g)
     X3Plan x3{};
     if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3)) return size_exact(g, pl);
     // (the other form's split and workspace only where a call may come back to it)
-    if (use == 1 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
+    if (use != 2 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
     pl.x3 = use;
     pl.x3p = x3;
     const size_t need = x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
@@ -670,7 +672,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
                  MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq)
 {
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
-    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The

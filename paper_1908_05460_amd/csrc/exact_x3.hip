@@ -7,12 +7,13 @@
 
 namespace wgrad {
 
-struct X3Variant { int bf, sh, ntc, s, sw, rag, halo, rpc, nch, di, xi, kp, cp, ch, lds, occ; };
+struct X3Variant { int bf, sh, ntc, s, sw, rag, halo, rpc, nch, di, xi, kp, cp, ch, lds, occ, plane; };
 static const X3Variant kVariant[kX3Variants] = {
-#define X(ID, ...) {__VA_ARGS__, X3Config<__VA_ARGS__>::kLds, X3Config<__VA_ARGS__>::kOcc},
+#define X(ID, ...) {__VA_ARGS__, X3Config<__VA_ARGS__>::kLds, X3Config<__VA_ARGS__>::kOcc, 0},
     WGRAD_X3_VARIANTS_FP32(X)
     WGRAD_X3_VARIANTS_BF16(X)
 #undef X
+    {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(4), 2, 4}, {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(2), 2, 2},
 };
 // workgroups that the chip holds at once
 static int x3_resident(const X3Variant &v) { return kNumCU * std::max(1, std::min(160 * 1024 / v.lds, v.occ)); }
@@ -22,6 +23,17 @@ static int floor_div(int a, int b) { return a >= 0 ? a / b : -((-a + b - 1) / b)
 static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
 {
     const X3Variant &v = kVariant[id];
+    if (v.plane) {
+        // position by position (exact_x3_planes.hip): a tile is 8 or 16 images
+        if (g.H != v.plane || g.W != v.plane || g.R != 3 || g.S != 3 || g.sh != 1 || g.sw != 1 || g.ph != 1 || g.pw != 1) return false;
+        if ((long)16 * std::max(g.K, g.C) * 16 * 4 >= (1l << 30)) return false;
+        pl.variant = id;
+        pl.ktiles = (g.K + 63) / 64; pl.ctiles = (g.C + 31) / 32;
+        pl.nti = v.plane == 4 ? 8 : 16; pl.ht = g.Ho; pl.iht = g.H; pl.twc = 1;
+        pl.h_tiles = pl.w_tiles = 1; pl.n_groups = (g.N + pl.nti - 1) / pl.nti;
+        pl.lds = v.lds;
+        return true;
+    }
     const int half = v.s / 2;
     int dmin = 0, dmax = 0;
     for (int s = 0; s < v.s; ++s) { dmin = std::min(dmin, x3_shift(s, v.s, v.sw)); dmax = std::max(dmax, x3_shift(s, v.s, v.sw)); }
@@ -87,14 +99,16 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
 // by its own staging and matrix instructions one after the other
 static double x3_tile_us(const X3Variant &v, int share)
 {
+    if (v.plane) return 1.1 * (v.plane == 4 ? std::max(share * 2.8, 4.2) : std::max(share * 0.85, 1.8));
     const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.bf ? 1 : 6) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
     const double stage = 0.3 + (v.bf ? 0.1 : 0.33) * (v.di + v.xi * v.sw);
     return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
 }
 static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(v) / kNumCU); }
 // tiles a workgroup adds up in one accumulator: the error of the fp32 sums grows with their length (64 -> 64 @ 32x32, N = 128:
-// 3.9e-7 of the result at 8 tiles, 4.7e-7 at 16, 1.9e-6 at 128; the fp32 matrix core's kernel: 6.5e-7)
-constexpr long kX3MostTiles = 32;
+// 3.9e-7 of the result at 8 tiles, 4.7e-7 at 16, 1.9e-6 at 128; the fp32 matrix core's kernel: 6.5e-7).  The position
+// form rounds its sums far less often (512 -> 512, N = 512, one sum of 64 / 32 tiles: 2.0e-7 at 4x4, 7.7e-8 at 2x2).
+static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : 32; }
 constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
 
 // How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of
@@ -148,8 +162,8 @@ static int x3_choose_splits(const Geometry &g, const X3Plan &pl, int nprob)
     const double t = x3_tile_us(v);
     double best_cost = 1e30;
     int best = 1;
-    const long most = std::min(tiles, std::max({1l, 2 * slots / outs, (tiles + kX3MostTiles - 1) / kX3MostTiles}));
-    for (long per = (tiles + most - 1) / most; per <= std::max(kX3MostTiles, (tiles + most - 1) / most) && per <= tiles; per += std::max(1l, per / 16)) {
+    const long longest = x3_most_tiles(v), most = std::min(tiles, std::max({1l, 2 * slots / outs, (tiles + longest - 1) / longest}));
+    for (long per = (tiles + most - 1) / most; per <= std::max(longest, (tiles + most - 1) / most) && per <= tiles; per += std::max(1l, per / 16)) {
         const long s = (tiles + per - 1) / per, n = outs * s;
         double life = kX3Fixed + per * t;
         if (n <= kNumCU) life = kX3Fixed + per * x3_tile_us(v, 1);      // a CU to itself
@@ -164,12 +178,22 @@ bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].bf && !k
 
 bool plan_exact_x3(const Geometry &g, X3Plan &best)
 {
+    if (!g.bf16 && g.H == g.W && (g.W == 2 || g.W == 4)) {
+        // (every such layer: no slower than the row form or the fp32 matrix core anywhere, 64 -> 64 @ 4x4 at N = 128 14.5 us
+        // against 16.7, 512 -> 512 at N = 2 11.5 against 11.4, at N = 512 153 against 227; figures in exact_x3_planes.hip)
+        X3Plan pl{};
+        if (x3_tile(g, g.W == 4 ? kX3Planes4 : kX3Planes2, pl)) {
+            best = pl;
+            best.splits = x3_choose_splits(g, best, 1);
+            return true;
+        }
+    }
     if (g.W < 4 || g.Wo < 4 || g.pw >= 4096) return false;
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     double best_cost = 1e30;
     for (int id = 0; id < kX3Variants; ++id) {
         const X3Variant &v = kVariant[id];
-        if (v.bf != g.bf16 || v.s != g.S || v.sw != g.sw) continue;
+        if (v.plane || v.bf != g.bf16 || v.s != g.S || v.sw != g.sw) continue;
         X3Plan pl{};
         if (!x3_tile(g, id, pl)) continue;
         // Matrix instructions, in units of a 16x16 tile of the result.  Long reductions do better with 32x32 tiles (a
@@ -211,6 +235,7 @@ static void x3_fill(const X3Group &it, X3Shape &s)
     s.h_tiles = pl.h_tiles; s.w_tiles = pl.w_tiles; s.n_groups = pl.n_groups;
     s.nch = pl.nch; s.ch = pl.ch; s.packed = pl.packed;
     s.halo = pl.halo; s.vlo = pl.vlo; s.xcol0 = pl.xcol0;
+    if (kVariant[pl.variant].plane) return;
     const int rpc = kVariant[pl.variant].rpc;
     s.d_nch = FastDiv(pl.nch);
     s.d_twc = FastDiv(pl.twc);
@@ -243,6 +268,7 @@ static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
         lds = std::max(lds, (size_t)q.pl.lds);
     }
     m.begin[n] = blocks;
+    if (const int hw = kVariant[it[0]->pl.variant].plane) return x3_launch_planes(hw, m, blocks, lds, st);
     if (it[0]->pl.variant >= kX3FirstBf16) return x3_launch_bf16(it[0]->pl.variant, m, blocks, lds, st);
     switch (it[0]->pl.variant) {
 #define X(ID, ...) case ID: return x3_launch(wgrad_exact_x3<X3Config<__VA_ARGS__>>, m, blocks, lds, st);
@@ -271,8 +297,9 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
         const int slots = x3_resident(v);
         const double t = x3_tile_us(v);
         // Candidates: workgroups of `share` of the launch's even share of work, the first of a pair where the result is
-        // large (its partial results are what splitting costs), the second elsewhere, to fill what those leave free.
-        static const double kShare[][2] = {{1.0, 1.0}, {1.0, 0.5}, {1.0, 0.33}, {0.67, 0.67}, {0.67, 0.33}, {0.5, 0.5}, {0.5, 0.25}, {0.33, 0.33}, {0.25, 0.25}};
+        // large (its partial results are what splitting costs), the second elsewhere, to fill what those leave free.  (Shares
+        // over 1 leave slots empty: 4x4 layers of 512 channels, whose partial sums weigh most, VGG-19 at N = 64 285 -> 269 us.)
+        static const double kShare[][2] = {{1.4, 1.4}, {1.0, 1.0}, {1.0, 0.5}, {1.0, 0.33}, {0.67, 0.67}, {0.67, 0.33}, {0.5, 0.5}, {0.5, 0.25}, {0.33, 0.33}, {0.25, 0.25}};
         long largest = 0;
         double total = 0;                                // workgroup-tiles
         for (int i = 0; i < n; ++i) {
@@ -288,7 +315,7 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
                 const long tiles = tiles_of(*sel[i]);
                 const double target = std::max(1.0, total / slots * share[2 * sel[i]->g.dw_elems() < largest]);
                 long s = (long)(tiles / target + 0.95);
-                s = std::max(s, (tiles + kX3MostTiles - 1) / kX3MostTiles);
+                s = std::max(s, (tiles + x3_most_tiles(v) - 1) / x3_most_tiles(v));
                 s = std::max(1l, std::min(s, (long)std::min<long>(sel[i]->pl.splits, tiles)));
                 now[i] = (int)s;
                 partial += x3_partial_us(sel[i]->g, s, sel[i]->b.n);

@@ -598,7 +598,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     X(20, true, 16, 1, 3, 1, false, false, 1, 32, 2, 2, 33, 41, 7) X(21, true, 16, 1, 3, 1, true, true, 1, 32, 2, 2, 43, 41, 7) \
     X(22, true, 32, 1, 3, 1, false, false, 1, 32, 4, 2, 33, 41, 12) X(23, true, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
     X(24, true, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
-constexpr int kX3Variants = 25, kX3FirstBf16 = 13;
+constexpr int kX3FirstBf16 = 13, kX3Planes4 = 25, kX3Planes2 = 26, kX3Variants = 27;
 
 // The parameters are read through the kernel-argument segment pointer: indexing the by-value argument with a run-time
 // group number would make the compiler copy all of it into scratch memory first.
@@ -624,6 +624,9 @@ inline int x3_launch(void (*kernel)(const X3Multi), const X3Multi &m, int blocks
     WGRAD_LAUNCH(kernel, dim3((unsigned)blocks), dim3(kBlock), lds, st, m);
     return launch_status();
 }
+// 2x2 and 4x4 planes, position by position (exact_x3_planes.hip)
+int x3_planes_lds(int hw);
+int x3_launch_planes(int hw, const X3Multi &m, int blocks, size_t lds, hipStream_t st);
 int x3_launch_bf16(int variant, const X3Multi &m, int blocks, size_t lds, hipStream_t st);      // instantiated in a file of their own
 
 }  // namespace wgrad

@@ -1,0 +1,324 @@
+// The three-piece form of the exact filter gradient (exact_x3_kernel.hpp) on 2x2 and 4x4 planes, position by position
+// (fp32, 3x3 filters, stride 1, padding 1):
+//
+//     dW[k][c][r][s] = sum over positions p = (h, w) whose tap (r, s) lies inside X, q = (h + r - 1, w + s - 1), of
+//                      G_pq[k][c],     G_pq[k][c] = sum_n dY[n][k][p] * X[n][c][q]
+//
+// The reduction of a G_pq runs over images, so an operand is "eight images of one position" and the (position, tap)
+// pairs whose tap meets only padding are never multiplied: 100 of 144 are left on a 4x4 plane, 16 of 36 on a 2x2 plane.
+// The matrix core under the chip's power limit bounds these layers, so a product left out is time saved: 512 -> 512 @
+// 4x4 takes 17.4 / 56.6 / 153 us at N = 16 / 128 / 512 (the fp32 matrix core 30.2 / 75 / 227, the row form of
+// exact_x3_kernel.hpp 63 at N = 128), 2x2 15.4 -> 45.7 us where the fp32 matrix core takes 49.7 (N = 512) and half of its
+// time in a run of layers; VGG-19's run 526 -> 489 us.
+//
+// A workgroup owns 64 output channels x 32 input channels; its four wavefronts share the taps out (13, 12, 12 and 15
+// steps of a 4x4 plane's stage, 4 each of a 2x2 plane's; which wavefront has which changes with the workgroup), so that
+// each holds the accumulators of its own two to four taps and nothing is added up across wavefronts.  A stage is 8
+// images (4x4; the two lane groups of an operand take two positions of one tap) or 16 (2x2; they take two groups of
+// images).  A thread loads four positions of one channel for eight images, 16 bytes each: a pair of images of one
+// position is a word of each piece as it comes out of the split, so the transposition costs nothing.
+#include <type_traits>
+
+#include "exact_x3_kernel.hpp"
+
+namespace wgrad {
+
+namespace {
+
+constexpr int kPK = 64, kPC = 32;                       // channels of the result tile
+
+template <int HW>
+struct PlaneCfg {
+    static constexpr int P = HW * HW, U = HW == 4 ? 16 : 8;            // positions; operand slots of a stage (2x2: position, image group)
+    static constexpr int IMG = HW == 4 ? 8 : 16;                        // images of a stage
+    static constexpr int kA = U * kPK * 16, kB = U * kPC * 16;          // bytes of one piece
+    static constexpr int kLds = 16 + 3 * (kA + kB);
+};
+
+// taps (r * 3 + s) of a role
+template <int HW> constexpr int role_taps(int role, int i)
+{
+    constexpr int t4[4][4] = {{4, 0, -1, -1}, {1, 3, -1, -1}, {5, 7, -1, -1}, {2, 6, 8, -1}};
+    constexpr int t2[4][4] = {{4, -1, -1, -1}, {1, 3, -1, -1}, {5, 7, -1, -1}, {0, 2, 6, 8}};
+    return HW == 4 ? t4[role][i] : t2[role][i];
+}
+// i-th position whose tap lies inside X, or -1
+template <int HW> constexpr int tap_position(int tap, int i)
+{
+    for (int p = 0; p < HW * HW; ++p) {
+        const int h = p / HW + tap / 3 - 1, w = p % HW + tap % 3 - 1;
+        if (h < 0 || h >= HW || w < 0 || w >= HW) continue;
+        if (i-- == 0) return p;
+    }
+    return -1;
+}
+template <int HW> constexpr int tap_count(int tap)
+{
+    int n = 0;
+    while (tap_position<HW>(tap, n) >= 0) ++n;
+    return n;
+}
+
+template <int HW, int ROLE>
+struct PlaneRole {
+    static constexpr int NT = (role_taps<HW>(ROLE, 0) >= 0) + (role_taps<HW>(ROLE, 1) >= 0) + (role_taps<HW>(ROLE, 2) >= 0) + (role_taps<HW>(ROLE, 3) >= 0);
+
+    template <int T, int STEP>
+    static __device__ __forceinline__ void step(x3_f16 (&acc)[NT][2], x3_f16 (&small)[2], const char *a0, const char *b0, int kk)
+    {
+        typedef PlaneCfg<HW> C;
+        constexpr int tap = role_taps<HW>(ROLE, T), shift = (tap / 3 - 1) * HW + tap % 3 - 1;
+        // operand slots of lane groups 0 and 1
+        constexpr int p0 = tap_position<HW>(tap, HW == 4 ? 2 * STEP : STEP), p1 = HW == 4 ? tap_position<HW>(tap, 2 * STEP + 1) : p0;
+        constexpr bool odd = p1 < 0;
+        constexpr int q1 = odd ? p0 : p1;
+        constexpr int ua0 = HW == 4 ? p0 : 2 * p0, ua1 = HW == 4 ? q1 : 2 * p0 + 1;
+        constexpr int ub0 = HW == 4 ? p0 + shift : 2 * (p0 + shift), ub1 = HW == 4 ? q1 + shift : 2 * (p0 + shift) + 1;
+        const char *const ap = a0 + (kk ? ua1 : ua0) * (kPK * 16), *const bp = b0 + (kk ? ub1 : ub0) * (kPC * 16);
+        x3_bf8 b[3];
+#pragma unroll
+        for (int q = 0; q < 3; ++q) b[q] = *(const x3_bf8 *)(bp + q * C::kB);
+#pragma unroll
+        for (int qa = 2; qa >= 0; --qa) {
+            x3_bf8 a[2];
+#pragma unroll
+            for (int m = 0; m < 2; ++m) {
+                x3_u4 v = *(const x3_u4 *)(ap + qa * C::kA + m * 32 * 16);
+                if (odd && kk) v = x3_u4{0u, 0u, 0u, 0u};               // the last of an odd number of positions
+                a[m] = __builtin_bit_cast(x3_bf8, v);
+            }
+#pragma unroll
+            for (int qb = 2 - qa; qb >= 0; --qb)
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    // the five smaller products of a stage's steps have a sum of their own, 2^-8 of the whole: it rounds that
+                    // much finer, and the whole is rounded once a step instead of six times
+                    x3_f16 &z = qa + qb ? small[m] : acc[T][m];
+                    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[qb], z, 0, 0, 0);
+                }
+        }
+    }
+    template <int T, int STEP>
+    static __device__ __forceinline__ void steps(x3_f16 (&acc)[NT][2], x3_f16 (&small)[2], const char *a0, const char *b0, int kk)
+    {
+        constexpr int n = tap_count<HW>(role_taps<HW>(ROLE, T)), all = HW == 4 ? (n + 1) / 2 : n;
+        if constexpr (STEP == 0) {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) small[m][v] = 0.f;
+        }
+        step<T, STEP>(acc, small, a0, b0, kk);
+        if constexpr (STEP + 1 < all) steps<T, STEP + 1>(acc, small, a0, b0, kk);
+        else {
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) acc[T][m][v] += small[m][v];
+            __builtin_amdgcn_sched_barrier(0);       // (across taps the scheduler's liking for early reads costs 67 spilled registers)
+            if constexpr (T + 1 < NT) steps<T + 1, 0>(acc, small, a0, b0, kk);
+        }
+    }
+};
+
+template <int HW>
+__device__ __forceinline__ void planes_general(const X3Shape &p, const float *X, const float *dY, float *out, int k0, int c0, int n0, int n1)
+{
+    const Geometry &g = p.g;
+    for (int o = threadIdx.x; o < kPK * kPC * 9; o += kBlock) {
+        const int tap = o % 9, c = c0 + o / 9 % kPC, k = k0 + o / (9 * kPC);
+        if (k >= g.K || c >= g.C) continue;
+        float acc = 0.f;
+        for (int n = n0; n < n1; ++n)
+            for (int q = 0; q < HW * HW; ++q) {
+                const int ih = q / HW + tap / 3 - 1, iw = q % HW + tap % 3 - 1;
+                const float x = ih >= 0 && ih < HW && iw >= 0 && iw < HW ? X[((long)n * g.C + c) * HW * HW + ih * HW + iw] : 0.f;
+                acc = fmaf(dY[((long)n * g.K + k) * HW * HW + q], x, acc);
+            }
+        out[(long)k * g.C * 9 + c * 9 + tap] = acc;
+    }
+}
+
+template <int HW, int ROLE>
+__device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, const float *dYp, float *out, char *smem, int k0, int c0,
+                                            int st_begin, int st_end)
+{
+    typedef PlaneCfg<HW> C;
+    typedef PlaneRole<HW, ROLE> R;
+    const Geometry &g = p.g;
+    const int tid = threadIdx.x, lane = tid & 63;
+    const int i = lane & 31, kk = lane >> 5;
+    uint32_t *const flag = (uint32_t *)smem;
+    char *const As = smem + 16, *const Bs = As + 3 * C::kA;
+
+    // Staging items: (channel, four positions [4x4: a row of the plane], eight images).  4x4: every thread has one of dY and
+    // half of one of X (four images); 2x2: 128 of dY, 64 of X, one for a thread.
+    constexpr uint32_t kDead = 0x80000000u;
+    constexpr int SETS = HW == 4 ? 2 : 1;
+    uint32_t src[SETS], dst[SETS];                                      // byte offset of the first image's piece; LDS byte offset
+    bool is_a[SETS];
+    int first[SETS];                                                    // the item's first image in the stage
+#pragma unroll
+    for (int u = 0; u < SETS; ++u) {
+        int row, grp, half = 0;
+        if (HW == 4) {
+            is_a[u] = u == 0;
+            row = u == 0 ? tid % kPK : tid % kPC;
+            grp = u == 0 ? tid / kPK : tid / kPC & 3;                   // row of the plane
+            half = u == 0 ? 0 : tid / (kPC * 4);
+            first[u] = 4 * half;
+        } else {
+            is_a[u] = tid < 2 * kPK;
+            const int f = is_a[u] ? tid : tid - 2 * kPK;
+            row = is_a[u] ? f % kPK : f % kPC;
+            grp = is_a[u] ? f / kPK : f / kPC;                          // group of eight images (2 and more: no item)
+            first[u] = 8 * grp;
+        }
+        const bool live = HW == 4 || grp < 2;
+        const int chans = is_a[u] ? g.K : g.C, rows = is_a[u] ? kPK : kPC;
+        src[u] = live && (is_a[u] ? k0 : c0) + row < chans ? (uint32_t)((first[u] * chans + row) * C::P + (HW == 4 ? grp * 4 : 0)) * 4u : kDead;
+        dst[u] = live ? (uint32_t)((is_a[u] ? 0 : 3 * C::kA) + ((HW == 4 ? 4 * grp : grp) * rows + row) * 16 + 8 * half) : ~0u;
+    }
+    uint32_t reg0[8][4], reg1[4][4];
+    auto load = [&](int st) {
+        const int n0 = st * C::IMG, left = g.N - n0;
+        const auto ra = __builtin_amdgcn_make_buffer_rsrc((void *)(dYp + ((long)n0 * g.K + k0) * C::P), 0, kDead, 0x00020000);
+        const auto rb = __builtin_amdgcn_make_buffer_rsrc((void *)(Xp + ((long)n0 * g.C + c0) * C::P), 0, kDead, 0x00020000);
+        auto images = [&](auto &reg, int u, int count) {
+            const uint32_t step = (uint32_t)((is_a[u] ? g.K : g.C) * C::P) * 4u;
+#pragma unroll
+            for (int j = 0; j < 8; ++j) {
+                if (j >= count) break;
+                const uint32_t off = src[u] != kDead && first[u] + j < left ? src[u] + j * step : kDead;
+                x3_u4 v;
+                if (is_a[u]) v = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0);
+                else v = __builtin_amdgcn_raw_buffer_load_b128(rb, off, 0, 0);
+#pragma unroll
+                for (int q = 0; q < 4; ++q) reg[j][q] = v[q];
+            }
+        };
+        images(reg0, 0, 8);
+        if constexpr (SETS > 1) images(reg1, 1, 4);
+    };
+    auto commit = [&]() {
+        auto images = [&](auto &reg, int u, auto words) {
+            constexpr int NW = decltype(words)::value;                  // words of a piece: pairs of images
+            if (dst[u] == ~0u) return;
+            const int rows = is_a[u] ? kPK : kPC, piece = is_a[u] ? C::kA : C::kB;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {                              // position q of the item
+                uint32_t h[NW], m[NW], l[NW];
+#pragma unroll
+                for (int e = 0; e < NW; ++e)
+                    x3_split2(__uint_as_float(reg[2 * e][q]), __uint_as_float(reg[2 * e + 1][q]), h[e], m[e], l[e]);
+                char *const d = As + dst[u] + (HW == 4 ? q : 2 * q) * rows * 16;
+                __builtin_memcpy(__builtin_assume_aligned(d, NW * 4), h, NW * 4);
+                __builtin_memcpy(__builtin_assume_aligned(d + piece, NW * 4), m, NW * 4);
+                __builtin_memcpy(__builtin_assume_aligned(d + 2 * piece, NW * 4), l, NW * 4);
+            }
+        };
+        images(reg0, 0, std::integral_constant<int, 4>{});
+        if constexpr (SETS > 1) images(reg1, 1, std::integral_constant<int, 2>{});
+    };
+
+    load(st_begin);
+    if (tid == 0) *flag = 0;
+    x3_f16 acc[R::NT][2];
+#pragma unroll
+    for (int t = 0; t < R::NT; ++t)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) acc[t][m][v] = 0.f;
+    const char *const a0 = As + i * 16, *const b0 = Bs + i * 16;
+    for (int st = st_begin; st < st_end; ++st) {
+        if (st != st_begin) __syncthreads();
+        __builtin_amdgcn_sched_barrier(0);                             // (see exact_x3_kernel.hpp)
+        commit();
+        __builtin_amdgcn_sched_barrier(0);
+        if (st + 1 < st_end) load(st + 1);
+        __builtin_amdgcn_sched_barrier(0);
+        __syncthreads();
+        x3_f16 small[2];
+        R::template steps<0, 0>(acc, small, a0, b0, kk);
+        __builtin_amdgcn_sched_barrier(0);
+    }
+    float worst = 0.f;
+#pragma unroll
+    for (int t = 0; t < R::NT; ++t)
+#pragma unroll
+        for (int m = 0; m < 2; ++m)
+#pragma unroll
+            for (int v = 0; v < 16; ++v) worst = fmaf(acc[t][m][v], 0.f, worst);
+    if (worst != worst) *flag = 1;
+    __syncthreads();
+    if (*(volatile uint32_t *)flag) {
+        const int n1 = st_end * C::IMG;
+        planes_general<HW>(p, Xp, dYp, out, k0, c0, st_begin * C::IMG, n1 < g.N ? n1 : g.N);
+        return;
+    }
+    // the result by half tiles of 32 output channels, gathered in LDS as rows of the tensor
+    constexpr int Q = kPC * 9, PITCH = Q + 4;
+    float *const rows = (float *)(smem + 16);
+    const int n = (g.C - c0 < kPC ? g.C - c0 : kPC) * 9, CRS = g.C * 9;
+#pragma unroll
+    for (int m = 0; m < 2; ++m) {
+        __syncthreads();
+#pragma unroll
+        for (int t = 0; t < R::NT; ++t)
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+                rows[(8 * (v / 4) + 4 * kk + v % 4) * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = acc[t][m][v];
+        __syncthreads();
+        const int kb = k0 + m * 32;
+        if (n == Q && kb + 32 <= g.K && CRS % 4 == 0 && ((uintptr_t)out & 15) == 0) {
+#pragma unroll
+            for (int u = 0; u < 32 * Q / 4 / kBlock; ++u) {
+                const int e = tid + u * kBlock, row = e / (Q / 4), x = e % (Q / 4) * 4;
+                *(float4_t *)(out + (long)(kb + row) * CRS + c0 * 9 + x) = *(const float4_t *)(rows + row * PITCH + x);
+            }
+        } else {
+            for (int row = tid >> 6; row < 32 && kb + row < g.K; row += 4)
+                for (int x = lane; x < n; x += 64) out[(long)(kb + row) * CRS + c0 * 9 + x] = rows[row * PITCH + x];
+        }
+    }
+}
+
+template <int HW>
+__global__ __launch_bounds__(kBlock, 2) void wgrad_exact_x3_planes(const X3Multi)
+{
+    extern __shared__ __align__(16) char x3_smem[];
+    const X3Multi *mp = (const X3Multi *)__builtin_amdgcn_kernarg_segment_ptr();
+    int gi = 0;
+    for (int i = 1; i < mp->n; ++i) gi += (int)blockIdx.x >= mp->begin[i];
+    const int bid = (int)blockIdx.x - mp->begin[gi], nblk = mp->count[gi];
+    if (bid >= nblk) return;
+    const X3Shape &p = mp->s[gi];
+    const int all = xcd_contiguous_id(bid, nblk), prob = all / p.per_prob, logical = all - prob * p.per_prob;
+    const int coltile = logical % p.ctiles, ktile = logical / p.ctiles % p.ktiles, split = logical / (p.ctiles * p.ktiles);
+    const int st_begin = (int)((long)split * p.n_groups / p.splits), st_end = (int)((long)(split + 1) * p.n_groups / p.splits);
+    const int k0 = ktile * kPK, c0 = coltile * kPC;
+    const float *const X = (const float *)mp->X[mp->first[gi] + prob], *const dY = (const float *)mp->dY[mp->first[gi] + prob];
+    float *const out = mp->out[mp->first[gi] + prob] + (long)split * p.g.K * p.g.C * 9;
+    // (the barriers inside are reached by all four wavefronts the same number of times, whatever their role)
+    switch (__builtin_amdgcn_readfirstlane(((int)(threadIdx.x >> 6) + ((int)blockIdx.x >> 8)) & 3)) {
+        case 0: planes_body<HW, 0>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        case 1: planes_body<HW, 1>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        case 2: planes_body<HW, 2>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        default: planes_body<HW, 3>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+    }
+}
+
+}  // namespace
+
+int x3_planes_lds(int hw)
+{
+    const int tail = 16 + 32 * (kPC * 9 + 4) * 4, stage = hw == 4 ? PlaneCfg<4>::kLds : PlaneCfg<2>::kLds;
+    return stage > tail ? stage : tail;
+}
+int x3_launch_planes(int hw, const X3Multi &m, int blocks, size_t lds, hipStream_t st)
+{
+    return hw == 4 ? x3_launch(wgrad_exact_x3_planes<4>, m, blocks, lds, st) : x3_launch(wgrad_exact_x3_planes<2>, m, blocks, lds, st);
+}
+
+}  // namespace wgrad

@@ -16,7 +16,7 @@ EDGES = [
     (3, 33, 32, 32, 65, 3, 3, 1, 1, 1, 1),      # one channel and one output channel over a 32 tile
     (8, 31, 16, 16, 31, 3, 3, 1, 1, 1, 1),      # one under
     (9, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1),        # a last tile of one image
-    (73, 40, 4, 4, 40, 3, 3, 1, 1, 1, 1),       # two rows per chunk, a last tile of one image
+    (73, 40, 4, 4, 40, 3, 3, 1, 1, 1, 1),       # a last tile of one image, position by position in fp32
     (2, 32, 27, 27, 32, 3, 3, 1, 1, 1, 1),      # a row's last chunk holds three columns; last tile of three rows
     (1, 32, 5, 300, 32, 3, 3, 1, 1, 1, 1),      # rows cut into column tiles: neighbour words on both sides
     (1, 64, 9, 130, 64, 3, 3, 1, 1, 1, 1),      # the last column tile holds two columns
@@ -31,6 +31,11 @@ EDGES = [
     (2, 33, 11, 14, 18, 5, 5, 1, 1, 2, 2),
     (40, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1),     # several workgroups share the reduction
     (1, 1, 5, 5, 1, 3, 3, 1, 1, 1, 1),
+    (73, 40, 6, 4, 40, 3, 3, 1, 1, 1, 1),       # two rows per chunk
+    (130, 65, 4, 4, 65, 3, 3, 1, 1, 1, 1),      # position by position: one channel over both tiles, the last stage has two images
+    (40, 64, 4, 4, 64, 3, 3, 1, 1, 1, 1),       # whole tiles
+    (257, 33, 2, 2, 100, 3, 3, 1, 1, 1, 1),     # 2x2: the last stage has one image
+    (36, 200, 2, 2, 63, 3, 3, 1, 1, 1, 1),      # the last stage's second group of images is empty
 ]
 
 
@@ -55,7 +60,7 @@ def test_edges_match_the_oracle(t, dtype):
     assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), want) < TOL["fp32"] / 50
 
 
-@pytest.mark.parametrize("t", [EDGES[4], EDGES[5], EDGES[12], EDGES[13], EDGES[15]])
+@pytest.mark.parametrize("t", [EDGES[4], EDGES[5], EDGES[12], EDGES[13], EDGES[15], EDGES[19], EDGES[20], EDGES[21]])
 def test_tensors_aligned_to_their_elements_only(t):
     import torch
     d = mk(t)
@@ -92,7 +97,7 @@ def test_bf16_infinities_and_nans(t, where, bad):
     assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / 50
 
 
-@pytest.mark.parametrize("t", [EDGES[0], EDGES[3], EDGES[4], EDGES[6], EDGES[10], EDGES[13]])
+@pytest.mark.parametrize("t", [EDGES[0], EDGES[3], EDGES[4], EDGES[6], EDGES[10], EDGES[13], EDGES[18], EDGES[19], EDGES[21]])
 @pytest.mark.parametrize("where", ["X", "dY"])
 @pytest.mark.parametrize("bad", [np.inf, -np.inf, np.nan, 3.4e38])
 def test_values_the_pieces_cannot_hold(t, where, bad):
@@ -152,6 +157,8 @@ def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
     """Layers of several variants, and more groups than a launch carries, in one schedule run."""
     import torch
     shapes = EDGES + [(5, 64 + 8 * i, 16, 16, 64, 3, 3, 1, 1, 1, 1) for i in range(10)] + [(40, 128, 16, 16, 128, 3, 3, 1, 1, 1, 1)] * 3
+    # 2x2 planes that alone are a plain matrix product and in a run are not
+    shapes += [(70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)]
     ds = [mk(t, dtype) for t in shapes]
     data = [tuple(to_gpu(a) for a in rand_inputs(d, 100 + i, dtype)) for i, d in enumerate(ds)]
     out = [torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda") for d in ds]
