@@ -35,17 +35,37 @@ __device__ __forceinline__ unsigned long long group_max(unsigned long long v, in
     return v;
 }
 
+// Reduction over a wavefront by lane shifts within rows and broadcasts across them; the result is lane 63's, made uniform.
+template <bool MAX>
+__device__ __forceinline__ int wave_extreme(int v)
+{
+    auto step = [&](int o) { v = MAX ? (o > v ? o : v) : (o < v ? o : v); };
+    step(__builtin_amdgcn_update_dpp(v, v, 0x111, 0xf, 0xf, false));        // row_shr:1, 2, 4, 8
+    step(__builtin_amdgcn_update_dpp(v, v, 0x112, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(v, v, 0x114, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(v, v, 0x118, 0xf, 0xf, false));
+    step(__builtin_amdgcn_update_dpp(v, v, 0x142, 0xa, 0xf, false));        // row_bcast:15, 31
+    step(__builtin_amdgcn_update_dpp(v, v, 0x143, 0xc, 0xf, false));
+    return __builtin_amdgcn_readlane(v, 63);
+}
+
 // A group of G lanes per map (WIDE = false; G a power of two, 64 / G maps per wavefront, so that maps of four
 // positions take a lane each and not a wavefront each), or one workgroup per map for maps of more than 1024
 // positions (WIDE = true: few, long maps would otherwise leave most of the chip idle).  Pass j finds the largest
-// key below the one pass j-1 found, so no list of taken positions is kept; the map's sum rides along with pass 0.
-// Maps of up to T*REG entries (T = G or 256 threads) stay in registers between the passes, longer ones are
-// read again (from L2).
+// key below the one pass j-1 found; the map's sum rides along with pass 0.  Maps of up to T*REG entries (T = G or
+// 256 threads) stay in registers between the passes, longer ones are read again (from L2).
+//
+// What bounds it is vector instructions (a workgroup of 56x56 maps reads 12 KB, which takes a fraction of that), so
+// the registers hold magnitudes alone, a thread keeps its own best as (magnitude, register) and goes over its
+// registers again only when its best was the one taken, and `vec` (positions in quads: a multiple of four to a map,
+// words of four bytes aligned) reads four positions at a time, past the end of a map without a branch.
+// 56x56 maps, N = 32, K = 64, k = 4: 20.8 -> 14.0 us.  Up to 16384 positions stay in registers (to 4096 before: with the
+// gather, 112x112, N = 4, K = 64, k = 4: 50 -> 18 us; 36x229, N = 7, K = 173, k = 8 in bf16: 66 -> 32).
 template <bool BF16, int REG, bool WIDE>
 __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ dY, long maps, int len, int Wo,
                                                       int k, int G, int32_t *__restrict__ hw_out,
                                                       int32_t *__restrict__ flat_out, float *__restrict__ sum_a,
-                                                      float *__restrict__ sum_b, void *__restrict__ sparse, float w)
+                                                      float *__restrict__ sum_b, void *__restrict__ sparse, float w, bool vec)
 {
     const int T = WIDE ? kBlock : G;
     __shared__ unsigned long long wg_best[2][kBlock / 64];      // WIDE: the wavefronts' maxima, double-buffered over passes
@@ -56,18 +76,47 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
     if (map >= maps) return;                      // whole groups leave together (WIDE: the grid is exactly maps)
     const long base = map * len;
 
-    unsigned long long held[REG > 0 ? REG : 1];
+    constexpr int kTaken = -1, kAbsent = -2;                    // below every magnitude
+    int mag[REG > 0 ? REG : 1];
+    // (positions of a thread grow with the register, so the first of equal magnitudes is the smallest position)
+    auto position = [&](int i) { return vec ? 4 * (lane + T * (i / 4)) + i % 4 : lane + T * i; };
     float sum = 0.f;
-    if (REG > 0) {
+    if constexpr (REG > 0) {
+        constexpr uint32_t kDead = 0x80000000u;                 // beyond the buffer: reads as zero
+        constexpr int ES = BF16 ? 2 : 4;
+        const long first = WIDE ? (long)blockIdx.x : (long)blockIdx.x * (kBlock / 64) * (64 / G);
+        const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)dY + first * len * ES), 0, kDead, 0x00020000);
+        const uint32_t off = (uint32_t)(map - first) * (uint32_t)(len * ES);
+        uint32_t bits[REG];
+        if (vec) {
+#pragma unroll
+            for (int i = 0; i < REG; i += 4) {
+                const int e = position(i);
+                const uint32_t at = e < len ? off + (uint32_t)(e * ES) : kDead;
+                if constexpr (BF16) {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0);
+                    bits[i] = v[0] << 16; bits[i + 1] = v[0] & 0xffff0000u; bits[i + 2] = v[1] << 16; bits[i + 3] = v[1] & 0xffff0000u;
+                } else {
+                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0);
+#pragma unroll
+                    for (int q = 0; q < 4; ++q) bits[i + q] = v[q];
+                }
+            }
+        } else {
+#pragma unroll
+            for (int i = 0; i < REG; ++i) {
+                const int e = position(i);
+                const uint32_t at = e < len ? off + (uint32_t)(e * ES) : kDead;
+                if constexpr (BF16) bits[i] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, at, 0, 0) << 16;
+                else bits[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0);
+            }
+        }
 #pragma unroll
         for (int i = 0; i < REG; ++i) {
-            const int e = lane + T * i;
-            held[i] = 0ull;                        // below every real key: ~pos is never 0 for pos < 2^32-1
-            if (e < len) {
-                const uint32_t b = load_bits<BF16>(dY, base + e);
-                held[i] = rank_key(b, (uint32_t)e);
-                sum += __uint_as_float(b);
-            }
+            int m = (int)(bits[i] & 0x7fffffffu);
+            m = m > 0x7f800000 ? 0 : m;
+            mag[i] = position(i) < len ? m : kAbsent;
+            sum += __uint_as_float(bits[i]);
         }
     } else {
         for (int e = lane; e < len; e += T) sum += __uint_as_float(load_bits<BF16>(dY, base + e));
@@ -80,13 +129,24 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
     }
 
     unsigned long long below = ~0ull;
+    int own = kAbsent, own_reg = 0;                              // the thread's best
+    auto scan = [&]() {
+        own = mag[0], own_reg = 0;
+#pragma unroll
+        for (int i = 1; i < REG; ++i)
+            if (mag[i] > own) own = mag[i], own_reg = i;
+    };
+    if (REG > 0) scan();
     for (int j = 0; j < k; ++j) {
         unsigned long long best = 0ull;
+        const int own_pos = position(own_reg);
         if (REG > 0) {
-#pragma unroll
-            for (int i = 0; i < REG; ++i) {
-                const unsigned long long c = held[i] < below ? held[i] : 0ull;
-                best = c > best ? c : best;
+            if (WIDE || G == 64) {
+                const int m = wave_extreme<true>(own), pos = wave_extreme<false>(own == m ? own_pos : 0x7fffffff);
+                if (m >= 0) best = (unsigned long long)(uint32_t)m << 32 | (uint32_t)~pos;
+            } else {
+                if (own >= 0) best = (unsigned long long)(uint32_t)own << 32 | (uint32_t)~own_pos;
+                best = group_max(best, G);
             }
         } else {
             for (int e = lane; e < len; e += T) {
@@ -94,8 +154,8 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
                 c = c < below ? c : 0ull;
                 best = c > best ? c : best;
             }
+            best = group_max(best, WIDE ? 64 : G);
         }
-        best = group_max(best, WIDE ? 64 : G);
         if (WIDE) {
             // pass j writes buffer j & 1; the barrier of pass j+1 separates its readers from pass j+2's writers
             if ((threadIdx.x & 63) == 0) wg_best[j & 1][threadIdx.x >> 6] = best;
@@ -104,6 +164,11 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
             for (int w = 0; w < kBlock / 64; ++w) best = wg_best[j & 1][w] > best ? wg_best[j & 1][w] : best;
         }
         below = best;
+        if (REG > 0 && own >= 0 && own_pos == (int)~(uint32_t)best) {
+#pragma unroll
+            for (int i = 0; i < REG; ++i) mag[i] = i == own_reg ? kTaken : mag[i];
+            scan();
+        }
         if (threadIdx.x == 0 || (!WIDE && lane == 0)) {
             const int32_t pos = (int32_t)~(uint32_t)best;
             if (flat_out) flat_out[map * k + j] = pos;
@@ -130,8 +195,8 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
         if (REG > 0) {
 #pragma unroll
             for (int i = 0; i < REG; ++i) {
-                const int e = lane + T * i;
-                if (e < len) put(e, held[i] >= below);
+                const int e = position(i);
+                if (e < len) put(e, mag[i] == kTaken);
             }
         } else {
             for (int e = lane; e < len; e += T)
@@ -142,37 +207,60 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
 
 // One thread per filter-gradient entry (ko, c, r, s) and batch chunk: it walks the chunk's
 // images and the k kept positions of map (n, ko), adding (sum/k) times the input element
-// its tap sees there (zero outside the image).
+// its tap sees there (zero outside the image).  The loads bound it: kDeep positions, then kDeep
+// elements, are in flight at a time, and an XCD takes whole chunks, so that the input of a chunk
+// is fetched into one L2 and not into all eight.
+// 64 -> 64 @ 56x56, N = 32, k = 4: 23.2 -> 12.4 us.
 template <bool BF16>
 __global__ __launch_bounds__(kBlock) void topk_gather(const void *__restrict__ X, const int32_t *__restrict__ hw,
                                                       const float *__restrict__ sum, float *__restrict__ out,
-                                                      Geometry g, int k, float inv_k, int chunk_n, float scale)
+                                                      Geometry g, int k, float inv_k, int chunk_n, float scale, int eblocks)
 {
-    const long o = (long)blockIdx.x * kBlock + threadIdx.x;
+    constexpr int kDeep = 8;
+    const int logical = xcd_contiguous_id((int)blockIdx.x, (int)gridDim.x), chunk = logical / eblocks;
+    const long o = (long)(logical - chunk * eblocks) * kBlock + threadIdx.x;
     const int RS = g.R * g.S, CRS = g.C * RS;
     if (o >= (long)g.K * CRS) return;
     const int ko = (int)(o / CRS), q = (int)(o % CRS);
-    const int c = q / RS, r = (q % RS) / g.S, s = q % g.S;
-    const int n_begin = blockIdx.y * chunk_n;
+    const int c = q / RS, r = (q % RS) / g.S - g.ph, s = (q % RS) % g.S - g.pw;
+    const int n_begin = chunk * chunk_n;
     const int n_end = n_begin + chunk_n < g.N ? n_begin + chunk_n : g.N;
-    float acc = 0.f;
-    for (int n = n_begin; n < n_end; ++n) {
-        const long m = (long)n * g.K + ko;
-        const float share = sum[m] * inv_k;
-        const long plane = ((long)n * g.C + c) * g.H;
-        float part = 0.f;
-#pragma unroll 4
-        for (int j = 0; j < k; ++j) {
-            const int p = hw[m * k + j];
-            const int ih = (p >> 16) * g.sh + r - g.ph, iw = (p & 0xffff) * g.sw + s - g.pw;
-            if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W) {
-                const long xi = (plane + ih) * g.W + iw;
-                part += BF16 ? bf16_bits_to_float(((const uint16_t *)X)[xi]) : ((const float *)X)[xi];
+    float acc = 0.f, part = 0.f;
+    int n = n_begin, j = 0;                                      // next kept position of the chunk
+    while (n < n_end) {
+        int at[kDeep], img[kDeep];
+        bool last[kDeep];                                        // of its map
+        float share[kDeep], x[kDeep];
+#pragma unroll
+        for (int u = 0; u < kDeep; ++u) {
+            img[u] = n;
+            share[u] = 0.f;
+            const long m = (long)(n < n_end ? n : n_end - 1) * g.K + ko;
+            at[u] = hw[m * k + j];
+            last[u] = j == k - 1;
+            if (last[u]) share[u] = sum[m];
+            if (n < n_end && ++j == k) { j = 0; ++n; }
+        }
+#pragma unroll
+        for (int u = 0; u < kDeep; ++u) {
+            const int ih = (at[u] >> 16) * g.sh + r, iw = (at[u] & 0xffff) * g.sw + s;
+            const bool inside = img[u] < n_end && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+            const long plane = ((long)(img[u] < n_end ? img[u] : n_end - 1) * g.C + c) * g.H * g.W;
+            const long xi = plane + (inside ? (long)ih * g.W + iw : 0l);
+            const float v = BF16 ? bf16_bits_to_float(((const uint16_t *)X)[xi]) : ((const float *)X)[xi];
+            x[u] = inside ? v : 0.f;
+        }
+        // the same sums in the same order, whatever kDeep: a map's k elements, then their share
+#pragma unroll
+        for (int u = 0; u < kDeep; ++u) {
+            part += x[u];
+            if (img[u] < n_end && last[u]) {
+                acc = fmaf(share[u] * inv_k, part, acc);
+                part = 0.f;
             }
         }
-        acc = fmaf(share, part, acc);
     }
-    out[(long)blockIdx.y * g.K * CRS + o] = acc * scale;
+    out[(long)chunk * g.K * CRS + o] = acc * scale;
 }
 
 // When the kept positions are a sizeable share of a map, gathering their patches moves as much data as the
@@ -279,11 +367,14 @@ int launch_approx_topk(const Geometry &g, const void *X, const void *dY, float *
     const long waves = (maps + 64 / G - 1) / (64 / G);
     const long grid = wide ? maps : (waves + kBlock / 64 - 1) / (kBlock / 64);
     if (grid >= (1l << 31)) return WGRAD_UNSUPPORTED;
-#define SEL_ARGS dim3((unsigned)grid), dim3(kBlock), 0, st, dY, maps, len, g.Wo, k, G, hw, idx_out, sum, sum_out, sparse, scale / k
+    const bool vec = len % 4 == 0 && ((uintptr_t)dY & 3) == 0;
+#define SEL_ARGS dim3((unsigned)grid), dim3(kBlock), 0, st, dY, maps, len, g.Wo, k, G, hw, idx_out, sum, sum_out, sparse, scale / k, vec
 #define SEL_PICK(BF)                                                                     \
     if (len <= 256)       WGRAD_LAUNCH((topk_select<BF, 4, false>), SEL_ARGS);           \
     else if (len <= 1024) WGRAD_LAUNCH((topk_select<BF, 16, false>), SEL_ARGS);          \
     else if (len <= 4096) WGRAD_LAUNCH((topk_select<BF, 16, true>), SEL_ARGS);           \
+    else if (len <= 8192) WGRAD_LAUNCH((topk_select<BF, 32, true>), SEL_ARGS);          \
+    else if (len <= 16384) WGRAD_LAUNCH((topk_select<BF, 64, true>), SEL_ARGS);         \
     else                  WGRAD_LAUNCH((topk_select<BF, 0, true>), SEL_ARGS)
     if (g.bf16) { SEL_PICK(true); } else { SEL_PICK(false); }
 #undef SEL_PICK
@@ -305,10 +396,11 @@ int launch_approx_topk(const Geometry &g, const void *X, const void *dY, float *
     const int nchunk = (g.N + chunk_n - 1) / chunk_n;
     const long entries = g.dw_elems();
     float *out = nchunk > 1 ? partials : dW;
-    const dim3 gg((unsigned)((entries + kBlock - 1) / kBlock), (unsigned)nchunk);
+    const int eblocks = (int)((entries + kBlock - 1) / kBlock);
+    const dim3 gg((unsigned)eblocks * (unsigned)nchunk);
     const float gscale = nchunk > 1 ? 1.0f : scale;
-    if (g.bf16) WGRAD_LAUNCH((topk_gather<true>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale);
-    else        WGRAD_LAUNCH((topk_gather<false>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale);
+    if (g.bf16) WGRAD_LAUNCH((topk_gather<true>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale, eblocks);
+    else        WGRAD_LAUNCH((topk_gather<false>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale, eblocks);
     rc = launch_status();
     if (rc != WGRAD_OK || nchunk == 1) return rc;
     float *dst[1] = {dW};

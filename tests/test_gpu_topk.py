@@ -41,13 +41,33 @@ def test_topk_matches_oracle(t, k, dtype):
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("hw,k", [((1, 4097), 8), ((64, 128), 5), ((3, 2731), 4), ((128, 128), 6), ((5, 3277), 3), ((13, 13), 4),
+                                  ((1, 1023), 64)])
+def test_topk_of_long_maps_and_of_maps_at_any_element(hw, k, dtype):
+    """On both sides of the lengths at which the registers held per thread change (8192 and 16384), with many equal
+    magnitudes, in quads and one by one; a dY that starts at an odd element selects the same."""
+    import torch
+    Ho, Wo = hw
+    d = B.desc(11, 2, Ho, Wo, 3, R=1, S=1, pad=0, dtype=B.BF16 if dtype == "bf16" else B.F32)
+    X, dY = rand_inputs(d, 31, dtype)
+    vals = (np.random.default_rng(k).integers(-40, 41, size=dY.shape) * 0.25).astype(np.float32)
+    dY = inputs.float32_to_bf16_bits(vals) if dtype == "bf16" else vals
+    check(d, X, dY, k, dtype)
+    aligned, Xg = to_gpu(dY), to_gpu(X)
+    odd = torch.empty(aligned.numel() + 1, dtype=aligned.dtype, device="cuda")[1:].view(aligned.shape).copy_(aligned)
+    idx = [torch.full((d.N, d.K, k), -7, dtype=torch.int32, device="cuda") for _ in range(2)]
+    out = [B.conv_wgrad_approx_topk(d, Xg, t, k, idx_out=i).cpu().numpy() for t, i in zip((aligned, odd), idx)]
+    assert torch.equal(idx[0], idx[1]) and normwise_err(out[1], out[0].astype(np.float64)) <= TOL["fp32"]
+
+
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("hw,k", [((1, 1), 1), ((2, 2), 4), ((1, 3), 2), ((4, 4), 16), ((8, 8), 5), ((7, 9), 63),
                                   ((16, 16), 7), ((17, 16), 9), ((32, 32), 64), ((33, 31), 12), ((64, 48), 6),
                                   ((41, 25), 4), ((64, 64), 3), ((80, 64), 5), ((3, 1700), 8)])
 def test_topk_order_under_heavy_ties(hw, k, dtype):
     # few distinct magnitudes: the order among equals (lower flat index first) decides nearly every rank;
     # the map lengths cover every register-resident variant of the selection (a wavefront per map up to 1024
-    # positions, a workgroup per map beyond) and the re-reading one (more than 4096 positions)
+    # positions, a workgroup per map beyond)
     Ho, Wo = hw
     d = B.desc(5, 2, Ho, Wo, 9, R=1, S=1, pad=0, dtype=B.BF16 if dtype == "bf16" else B.F32)
     rng = np.random.default_rng(Ho * 100 + Wo + k)
