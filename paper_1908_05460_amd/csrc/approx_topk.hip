@@ -49,27 +49,31 @@ __device__ __forceinline__ int wave_extreme(int v)
     return __builtin_amdgcn_readlane(v, 63);
 }
 
-// A group of G lanes per map (WIDE = false; G a power of two, 64 / G maps per wavefront, so that maps of four
+// A group of G lanes per map (WG = 0; G a power of two, 64 / G maps per wavefront, so that maps of four
 // positions take a lane each and not a wavefront each), or one workgroup per map for maps of more than 1024
-// positions (WIDE = true: few, long maps would otherwise leave most of the chip idle).  Pass j finds the largest
+// positions (WG = its threads: few, long maps would otherwise leave most of the chip idle).  Pass j finds the largest
 // key below the one pass j-1 found; the map's sum rides along with pass 0.  Maps of up to T*REG entries (T = G or
-// 256 threads) stay in registers between the passes, longer ones are read again (from L2).
+// WG threads) stay in registers between the passes, longer ones are read again (from L2).
 //
 // What bounds it is vector instructions (a workgroup of 56x56 maps reads 12 KB, which takes a fraction of that), so
 // the registers hold magnitudes alone, a thread keeps its own best as (magnitude, register) and goes over its
 // registers again only when its best was the one taken, and `vec` (positions in quads: a multiple of four to a map,
 // words of four bytes aligned) reads four positions at a time, past the end of a map without a branch.
-// 56x56 maps, N = 32, K = 64, k = 4: 20.8 -> 14.0 us.  Up to 16384 positions stay in registers (to 4096 before: with the
+// 56x56 maps, N = 32, K = 64, k = 4: 20.8 -> 14.0 us.  Up to 57344 positions stay in registers (to 4096 before: with the
 // gather, 112x112, N = 4, K = 64, k = 4: 50 -> 18 us; 36x229, N = 7, K = 173, k = 8 in bf16: 66 -> 32).
-template <bool BF16, int REG, bool WIDE>
-__global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ dY, long maps, int len, int Wo,
+// Beyond 16384 the workgroup has 1024 threads (146x154, N = 17, K = 13, k = 8: 140 -> 29 us; 224x224, N = 4, K = 64, k = 4:
+// 272 -> 36); at 56 positions a thread some 50 registers spill, which costs less than reading the map k times.
+template <bool BF16, int REG, int WG>
+__global__ __launch_bounds__(WG ? WG : kBlock) void topk_select(const void *__restrict__ dY, long maps, int len, int Wo,
                                                       int k, int G, int32_t *__restrict__ hw_out,
                                                       int32_t *__restrict__ flat_out, float *__restrict__ sum_a,
                                                       float *__restrict__ sum_b, void *__restrict__ sparse, float w, bool vec)
 {
-    const int T = WIDE ? kBlock : G;
-    __shared__ unsigned long long wg_best[2][kBlock / 64];      // WIDE: the wavefronts' maxima, double-buffered over passes
-    __shared__ float wg_sum[kBlock / 64];
+    constexpr bool WIDE = WG > 0;
+    constexpr int WAVES = (WIDE ? WG : kBlock) / 64;
+    const int T = WIDE ? WG : G;
+    __shared__ unsigned long long wg_best[2][WAVES];      // WIDE: the wavefronts' maxima, double-buffered over passes
+    __shared__ float wg_sum[WAVES];
     const int lane = WIDE ? threadIdx.x : (threadIdx.x & 63) % G;
     const long map = WIDE ? (long)blockIdx.x
                           : ((long)blockIdx.x * (kBlock / 64) + (threadIdx.x >> 6)) * (64 / G) + (threadIdx.x & 63) / G;
@@ -87,36 +91,42 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
         const long first = WIDE ? (long)blockIdx.x : (long)blockIdx.x * (kBlock / 64) * (64 / G);
         const auto rsrc = __builtin_amdgcn_make_buffer_rsrc((void *)((const char *)dY + first * len * ES), 0, kDead, 0x00020000);
         const uint32_t off = (uint32_t)(map - first) * (uint32_t)(len * ES);
-        uint32_t bits[REG];
-        if (vec) {
+        // (in two halves where the bits of all of a thread's positions beside their magnitudes would spill)
+        constexpr int PART = REG > 32 ? REG / 2 : (WG > 256 ? REG / 2 : REG);
 #pragma unroll
-            for (int i = 0; i < REG; i += 4) {
-                const int e = position(i);
-                const uint32_t at = e < len ? off + (uint32_t)(e * ES) : kDead;
-                if constexpr (BF16) {
-                    const auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0);
-                    bits[i] = v[0] << 16; bits[i + 1] = v[0] & 0xffff0000u; bits[i + 2] = v[1] << 16; bits[i + 3] = v[1] & 0xffff0000u;
-                } else {
-                    const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0);
+        for (int i0 = 0; i0 < REG; i0 += PART) {
+            uint32_t bits[PART];
+            if (vec) {
 #pragma unroll
-                    for (int q = 0; q < 4; ++q) bits[i + q] = v[q];
+                for (int i = 0; i < PART; i += 4) {
+                    const int e = position(i0 + i);
+                    const uint32_t at = e < len ? off + (uint32_t)(e * ES) : kDead;
+                    if constexpr (BF16) {
+                        const auto v = __builtin_amdgcn_raw_buffer_load_b64(rsrc, at, 0, 0);
+                        bits[i] = v[0] << 16; bits[i + 1] = v[0] & 0xffff0000u; bits[i + 2] = v[1] << 16; bits[i + 3] = v[1] & 0xffff0000u;
+                    } else {
+                        const auto v = __builtin_amdgcn_raw_buffer_load_b128(rsrc, at, 0, 0);
+#pragma unroll
+                        for (int q = 0; q < 4; ++q) bits[i + q] = v[q];
+                    }
+                }
+            } else {
+#pragma unroll
+                for (int i = 0; i < PART; ++i) {
+                    const int e = position(i0 + i);
+                    const uint32_t at = e < len ? off + (uint32_t)(e * ES) : kDead;
+                    if constexpr (BF16) bits[i] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, at, 0, 0) << 16;
+                    else bits[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0);
                 }
             }
-        } else {
 #pragma unroll
-            for (int i = 0; i < REG; ++i) {
-                const int e = position(i);
-                const uint32_t at = e < len ? off + (uint32_t)(e * ES) : kDead;
-                if constexpr (BF16) bits[i] = (uint32_t)(uint16_t)__builtin_amdgcn_raw_buffer_load_b16(rsrc, at, 0, 0) << 16;
-                else bits[i] = __builtin_amdgcn_raw_buffer_load_b32(rsrc, at, 0, 0);
+            for (int i = 0; i < PART; ++i) {
+                int m = (int)(bits[i] & 0x7fffffffu);
+                m = m > 0x7f800000 ? 0 : m;
+                mag[i0 + i] = position(i0 + i) < len ? m : kAbsent;
+                sum += __uint_as_float(bits[i]);
             }
-        }
-#pragma unroll
-        for (int i = 0; i < REG; ++i) {
-            int m = (int)(bits[i] & 0x7fffffffu);
-            m = m > 0x7f800000 ? 0 : m;
-            mag[i] = position(i) < len ? m : kAbsent;
-            sum += __uint_as_float(bits[i]);
+            if (PART < REG) __builtin_amdgcn_sched_barrier(0);
         }
     } else {
         for (int e = lane; e < len; e += T) sum += __uint_as_float(load_bits<BF16>(dY, base + e));
@@ -125,7 +135,9 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
     if (WIDE) {
         if ((threadIdx.x & 63) == 0) wg_sum[threadIdx.x >> 6] = sum;
         __syncthreads();
-        sum = (wg_sum[0] + wg_sum[1]) + (wg_sum[2] + wg_sum[3]);
+        sum = 0.f;
+#pragma unroll
+        for (int w = 0; w < WAVES; w += 4) sum += (wg_sum[w] + wg_sum[w + 1]) + (wg_sum[w + 2] + wg_sum[w + 3]);
     }
 
     unsigned long long below = ~0ull;
@@ -161,7 +173,7 @@ __global__ __launch_bounds__(kBlock) void topk_select(const void *__restrict__ d
             if ((threadIdx.x & 63) == 0) wg_best[j & 1][threadIdx.x >> 6] = best;
             __syncthreads();
 #pragma unroll
-            for (int w = 0; w < kBlock / 64; ++w) best = wg_best[j & 1][w] > best ? wg_best[j & 1][w] : best;
+            for (int w = 0; w < WAVES; ++w) best = wg_best[j & 1][w] > best ? wg_best[j & 1][w] : best;
         }
         below = best;
         if (REG > 0 && own >= 0 && own_pos == (int)~(uint32_t)best) {
@@ -368,17 +380,19 @@ int launch_approx_topk(const Geometry &g, const void *X, const void *dY, float *
     const long grid = wide ? maps : (waves + kBlock / 64 - 1) / (kBlock / 64);
     if (grid >= (1l << 31)) return WGRAD_UNSUPPORTED;
     const bool vec = len % 4 == 0 && ((uintptr_t)dY & 3) == 0;
-#define SEL_ARGS dim3((unsigned)grid), dim3(kBlock), 0, st, dY, maps, len, g.Wo, k, G, hw, idx_out, sum, sum_out, sparse, scale / k, vec
-#define SEL_PICK(BF)                                                                     \
-    if (len <= 256)       WGRAD_LAUNCH((topk_select<BF, 4, false>), SEL_ARGS);           \
-    else if (len <= 1024) WGRAD_LAUNCH((topk_select<BF, 16, false>), SEL_ARGS);          \
-    else if (len <= 4096) WGRAD_LAUNCH((topk_select<BF, 16, true>), SEL_ARGS);           \
-    else if (len <= 8192) WGRAD_LAUNCH((topk_select<BF, 32, true>), SEL_ARGS);          \
-    else if (len <= 16384) WGRAD_LAUNCH((topk_select<BF, 64, true>), SEL_ARGS);         \
-    else                  WGRAD_LAUNCH((topk_select<BF, 0, true>), SEL_ARGS)
+#define SEL(BF, REG, WG) WGRAD_LAUNCH((topk_select<BF, REG, WG>), dim3((unsigned)grid), dim3(WG ? WG : kBlock), 0, st, dY, maps, len, g.Wo, k, G, hw, idx_out, sum, sum_out, sparse, scale / k, vec)
+#define SEL_PICK(BF)                                     \
+    if (len <= 256)        SEL(BF, 4, 0);                \
+    else if (len <= 1024)  SEL(BF, 16, 0);               \
+    else if (len <= 4096)  SEL(BF, 16, 256);             \
+    else if (len <= 8192)  SEL(BF, 32, 256);             \
+    else if (len <= 16384) SEL(BF, 64, 256);             \
+    else if (len <= 32768) SEL(BF, 32, 1024);            \
+    else if (len <= 57344) SEL(BF, 56, 1024);            \
+    else                   SEL(BF, 0, 256)
     if (g.bf16) { SEL_PICK(true); } else { SEL_PICK(false); }
 #undef SEL_PICK
-#undef SEL_ARGS
+#undef SEL
     rc = launch_status();
     if (rc != WGRAD_OK) return rc;
 

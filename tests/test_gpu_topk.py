@@ -42,9 +42,10 @@ def test_topk_matches_oracle(t, k, dtype):
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("hw,k", [((1, 4097), 8), ((64, 128), 5), ((3, 2731), 4), ((128, 128), 6), ((5, 3277), 3), ((13, 13), 4),
+                                  ((128, 256), 4), ((224, 224), 5), ((32, 1792), 2), ((5, 11469), 3),
                                   ((1, 1023), 64)])
 def test_topk_of_long_maps_and_of_maps_at_any_element(hw, k, dtype):
-    """On both sides of the lengths at which the registers held per thread change (8192 and 16384), with many equal
+    """On both sides of the lengths at which the registers held per thread change (8192, 16384, 32768, 57344), with many equal
     magnitudes, in quads and one by one; a dY that starts at an odd element selects the same."""
     import torch
     Ho, Wo = hw
