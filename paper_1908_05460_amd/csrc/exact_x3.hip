@@ -37,10 +37,15 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
     const int half = v.s / 2;
     int dmin = 0, dmax = 0;
     for (int s = 0; s < v.s; ++s) { dmin = std::min(dmin, x3_shift(s, v.s, v.sw)); dmax = std::max(dmax, x3_shift(s, v.s, v.sw)); }
-    const int vlo = std::max(dmin, floor_div(g.pw - half, v.sw));
-    const int vhi = std::min(g.Wo - 1 + dmax, floor_div(g.W - 1 + g.pw - half, v.sw));
+    int vlo = std::max(dmin, floor_div(g.pw - half, v.sw));
+    int vhi = std::min(g.Wo - 1 + dmax, floor_div(g.W - 1 + g.pw - half, v.sw));
+    if (vhi < vlo) return false;                         // (every product meets only padding)
+    // Every column of dY meets a slot through some tap, also where the padding is as wide as the filter and the column's
+    // taps all lie in it: an infinity or NaN there makes NaNs of the padding's zeros, and a column that no slot reaches
+    // would never enter a sum.
+    vlo = std::min(vlo, dmax);
+    vhi = std::max(vhi, g.Wo - 1 + dmin);
     const int vw = vhi - vlo + 1;
-    if (vw < 1) return false;                            // (every product meets only padding)
     pl.vlo = vlo;
     pl.xcol0 = v.sw * vlo + half - g.pw;
     if (!v.rag && (g.Wo % 4 || g.W % 4 || vlo != 0 || pl.xcol0 != 0)) return false;

@@ -122,6 +122,28 @@ def test_values_the_pieces_cannot_hold(t, where, bad):
             assert normwise_err(got[part], want[part]) < TOL["fp32"]
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("t", [
+    (2, 20, 6, 7, 24, 3, 3, 1, 1, 3, 4),
+    (3, 64, 32, 32, 64, 3, 3, 1, 1, 3, 3),
+    (2, 20, 9, 21, 24, 3, 3, 2, 2, 5, 5),
+    (2, 33, 11, 14, 18, 5, 5, 1, 1, 6, 7),
+])
+def test_nan_in_a_column_that_sees_only_padding(t, dtype):
+    """Padding as wide as the filter: the outermost columns of dY meet nothing but zeros, and a NaN there is still a
+    NaN of every entry of its output channel."""
+    d = mk(t, dtype)
+    X, dY = rand_inputs(d, 3, dtype)
+    Xg = to_gpu(X)
+    for w in range(d.Wo):
+        bad = dY.copy()
+        bad[0, 1, d.Ho // 2, w] = 0x7FC0 if dtype == "bf16" else np.nan
+        if w in (0, d.Wo // 2):
+            assert np.array_equal(np.isnan(oracle.wgrad_exact(oracle_shape(d), X, bad)).all(axis=(1, 2, 3)), np.arange(d.K) == 1)
+        got = run(d, Xg, to_gpu(bad))
+        assert np.isnan(got[1]).all() and np.isfinite(np.delete(got, 1, axis=0)).all(), w
+
+
 @pytest.mark.parametrize("scale", [(1e15, 1e15), (1e-12, 1e-12), (1e-20, 1e18), (1e25, 1e-25)])
 def test_scales_far_from_one(scale):
     d = mk(EDGES[0])
