@@ -4,9 +4,11 @@
 // x = h + m + l with |m| <= 2^-8 |x|, |l| <= 2^-17 |x|), a product of two bf16 numbers is exact in fp32, and of
 // the nine products of two such sums the six largest leave out less than 2^-24 |x y|: the rounding of one fp32
 // product.  Six bf16 matrix instructions (1/16 of the fp32 instruction's time per product) therefore replace one
-// fp32 one, with fp32 accumulation as before.  The split has fp32's whole range; a tile that holds an infinity, a
-// NaN or a value whose h rounds to infinity is recomputed by its workgroup with plain fp32 multiply-adds
-// (x3_general), where the pieces would make NaNs of infinities.
+// fp32 one, with fp32 accumulation as before.  bf16's smallest step is 2^-133, so both operands are scaled by 2^16 as
+// they are split, and the sums scaled back: every fp32 number then has its 24 bits in the pieces (unscaled, numbers
+// below 2^-110 lost bits of them: a tensor of 1e-36 was 2.5e-5 off).  What holds an infinity, a NaN or a number beyond
+// 2^111, or has a sum beyond 2^96, is recomputed by its workgroup with plain fp32 multiply-adds (x3_general), where the
+// pieces would make NaNs of infinities.
 //
 // Implicit GEMM, rows = output channels k, columns = (input channel, filter row), reduction = "slots": the columns
 // of X (stride 1) or of one phase of X (column mod stride), eight consecutive slots of one output row being one
@@ -81,9 +83,13 @@ __device__ __forceinline__ x3_bf8 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
     return __builtin_bit_cast(x3_bf8, o);
 }
 
-// Two fp32 numbers -> one word (bf16 pair) of each piece
+constexpr float kX3Scale = 65536.f, kX3Unscale = 1.f / (kX3Scale * kX3Scale);      // of an operand; of a sum of products
+
+// Two fp32 numbers, scaled -> one word (bf16 pair) of each piece
 __device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l)
 {
+    x0 *= kX3Scale;
+    x1 *= kX3Scale;
     // (written out: from a conversion in C the compiler makes a second instruction for the low half alone)
     auto pk = [](float a, float b) {
         uint32_t v;
@@ -544,7 +550,8 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         for (int s = 0; s < SR; ++s)
 #pragma unroll
             for (int v = 0; v < AV / 4; ++v) {
-                const acc_t &z = acc[ts / S][ts % S + s];
+                acc_t z = acc[ts / S][ts % S + s];
+                if (!BF) z *= kX3Unscale;               // (before they are added up, which could leave fp32's range)
                 *(float4_t *)(red + ((wq * SR + s) * SH + i) * KTP + (SH == 32 ? 8 * v + 4 * kk : 4 * kk)) =
                     float4_t{z[4 * v], z[4 * v + 1], z[4 * v + 2], z[4 * v + 3]};
             }

@@ -268,7 +268,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
         for (int t = 0; t < R::NT; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                rows[(8 * (v / 4) + 4 * kk + v % 4) * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = acc[t][m][v];
+                rows[(8 * (v / 4) + 4 * kk + v % 4) * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = acc[t][m][v] * kX3Unscale;
         __syncthreads();
         const int kb = k0 + m * 32;
         if (n == Q && kb + 32 <= g.K && CRS % 4 == 0 && ((uintptr_t)out & 15) == 0) {

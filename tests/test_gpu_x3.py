@@ -144,9 +144,12 @@ def test_nan_in_a_column_that_sees_only_padding(t, dtype):
         assert np.isnan(got[1]).all() and np.isfinite(np.delete(got, 1, axis=0)).all(), w
 
 
-@pytest.mark.parametrize("scale", [(1e15, 1e15), (1e-12, 1e-12), (1e-20, 1e18), (1e25, 1e-25)])
-def test_scales_far_from_one(scale):
-    d = mk(EDGES[0])
+@pytest.mark.parametrize("t", [EDGES[0], EDGES[4], EDGES[10], EDGES[19], EDGES[21]])
+@pytest.mark.parametrize("scale", [(1e15, 1e15), (1e-12, 1e-12), (1e-20, 1e18), (1e25, 1e-25), (1e31, 1e-3), (1e30, 1e-32),
+                                   (1e30, 1e-34), (1e30, 1e-36), (1e-36, 1e30), (1e30, 1e-39), (1e-40, 1e36)])
+def test_scales_far_from_one(t, scale):
+    """Down to tensors of subnormal numbers: the pieces hold every fp32 number whole."""
+    d = mk(t)
     X, dY = rand_inputs(d, 11)
     X, dY = X * np.float32(scale[0]), dY * np.float32(scale[1])
     want = oracle.wgrad_exact(oracle_shape(d), X, dY)
