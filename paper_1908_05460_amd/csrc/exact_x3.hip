@@ -110,10 +110,13 @@ static double x3_tile_us(const X3Variant &v, int share)
     return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
 }
 static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(v) / kNumCU); }
-// tiles a workgroup adds up in one accumulator: the error of the fp32 sums grows with their length (64 -> 64 @ 32x32, N = 128:
-// 3.9e-7 of the result at 8 tiles, 4.7e-7 at 16, 1.9e-6 at 128; the fp32 matrix core's kernel: 6.5e-7).  The position
-// form rounds its sums far less often (512 -> 512, N = 512, one sum of 64 / 32 tiles: 2.0e-7 at 4x4, 7.7e-8 at 2x2).
-static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : 32; }
+// tiles a workgroup adds up in one accumulator: the error of the fp32 sums grows with their length (of the result's 2-norm,
+// 64 -> 64 @ 32x32, N = 200, 13 tiles of 32-wide sums: 3.1e-7; 6 -> 196 @ 80x138, N = 34, 32 tiles: 4.4e-7; the fp32 matrix
+// core's kernels 6.9e-7 in both; 16-wide tiles, whose smaller products have their own sums, 1.4e-7 at 32 tiles).  bf16's
+// tiles of 32 chunks are two steps each: 182 -> 211 @ 22x8, N = 61, 1.9e-7 at 31 of them, 1.4e-7 at 16, the fp32 matrix
+// core's kernel 1.3e-7.  The position form rounds its sums far less often (512 -> 512, N = 512, one sum of 64 / 32 tiles:
+// 2.0e-7 at 4x4, 7.7e-8 at 2x2).
+static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : (v.bf && v.sh == 16 && v.nch == 32 ? 16 : 32); }
 constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
 
 // How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of

@@ -86,10 +86,10 @@ __device__ __forceinline__ x3_bf8 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
 constexpr float kX3Scale = 65536.f, kX3Unscale = 1.f / (kX3Scale * kX3Scale);      // of an operand; of a sum of products
 
 // Two fp32 numbers, scaled -> one word (bf16 pair) of each piece
-__device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l)
+__device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l, float scale = kX3Scale)
 {
-    x0 *= kX3Scale;
-    x1 *= kX3Scale;
+    x0 *= scale;
+    x1 *= scale;
     // (written out: from a conversion in C the compiler makes a second instruction for the low half alone)
     auto pk = [](float a, float b) {
         uint32_t v;
@@ -163,8 +163,9 @@ struct X3Config {
     static constexpr int SH = SH_, NTC = NTC_, S = S_, SW = SW_, RPC = RPC_, NCH = NCH_, DI = DI_, XI = XI_, KP = KP_, CP = CP_, CH = CH_, NW = 4;
     static constexpr bool BF = BF_, RAG = RAG_, HALO = HALO_;
     static constexpr int NP = BF ? 1 : 3;                               // pieces of a number
+    static constexpr bool OWN = !BF && SH == 16 && S <= 3;                // the smaller products have sums of their own
     static constexpr int DR = BF && !RAG ? 4 : 8;                       // registers of a chunk on its way to LDS
-    static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG ? 3 : 4);      // workgroups that share a CU
+    static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG || (OWN && NTC > 1) ? 3 : 4);      // workgroups that share a CU
     static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
     static constexpr int kBuf = 16 + NP * kDy + 16 + NP * kX;            // of a tile (16 spare bytes before each: a word left of a chunk 0)
     static constexpr int SR = SH == 32 ? 1 : S;                         // filter columns per round of the final exchange
@@ -338,15 +339,19 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             }
         }
     };
+    // The matrix core rounds downwards what it adds to a larger sum, and five of the six products are small: the sums of the
+    // products come out low, by as much as 4.5e-7 of the result's size (64 -> 64 @ 224x224, N = 4).  Every other workgroup of
+    // a reduction sums the negated products, so that what they lose cancels.
+    const float dy_scale = split & 1 ? -kX3Scale : kX3Scale;
     // a chunk's pieces to LDS; v(e): its element e (fp32 bits, or bf16 bits in the low half)
-    auto put = [&](auto v, char *dst, int piece) {
+    auto put = [&](auto v, char *dst, int piece, float scale) {
         x3_u4 h, m, l;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
             if constexpr (BF) h[e] = __builtin_amdgcn_perm(v(2 * e + 1), v(2 * e), 0x05040100u);
             else {
                 uint32_t a, b, c;
-                x3_split2(__uint_as_float(v(2 * e)), __uint_as_float(v(2 * e + 1)), a, b, c);
+                x3_split2(__uint_as_float(v(2 * e)), __uint_as_float(v(2 * e + 1)), a, b, c, scale);
                 h[e] = a; m[e] = b; l[e] = c;
             }
         }
@@ -374,13 +379,13 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             }
             if (at != ~0u) {
                 if constexpr (DR == 4) *(x3_u4 *)(buf + kDyAt + at_dst(at)) = x3_u4{dr[u][0], dr[u][1], dr[u][2], dr[u][3]};
-                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece);
+                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, dy_scale);
             }
         }
         if (HALO && p.halo) {
             uint32_t h, m = 0, l = 0;
             if constexpr (BF) h = hr[0] | hr[1] << 16;
-            else x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), h, m, l);
+            else x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), h, m, l, dy_scale);
             if (h_at != ~0u) {
                 char *const dst = buf + kDyAt + at_dst(h_at) + (at_wc(h_at) ? 0 : 12);
                 *(uint32_t *)dst = h;
@@ -403,7 +408,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 else {
 #pragma unroll
                     for (int f = 0; f < SW; ++f)
-                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece);
+                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, kX3Scale);
                 }
             }
         }
@@ -441,6 +446,16 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
             for (int v = 0; v < AV; ++v) acc[t][s][v] = 0.f;
 
+    // 16-wide tiles: the five smaller products have a sum of their own, 2^-8 of the whole, which rounds that much finer; the
+    // whole is then rounded once a step instead of six times
+    acc_t small[T::OWN ? NTC : 1][T::OWN ? S : 1];
+#pragma unroll
+    for (int t = 0; t < (T::OWN ? NTC : 1); ++t)
+#pragma unroll
+        for (int s = 0; s < (T::OWN ? S : 1); ++s)
+#pragma unroll
+            for (int v = 0; v < AV; ++v) small[t][s][v] = 0.f;
+
     // this lane's columns: byte offset of (channel, filter row) in a piece of X
     int coloff[NTC];
     const int row_bytes = HALF ? 8 : p.twc * SW * 16;
@@ -468,29 +483,46 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         if (wt + 1 < wt_end) load_tile(wt + 1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
+        auto a_words = [&](uint32_t e, int qa, uint32_t &lw, uint32_t &rw) {       // a dY chunk of a piece and its neighbour words
+            const char *const ap = a_row + (e & 0xfff) + qa * dy_piece;
+            lw = rw = 0;
+            if (S > 1 && !HALF) {
+                lw = *(const uint32_t *)(ap - 4);
+                rw = *(const uint32_t *)(ap + 16);
+                if (e & (1u << 30)) lw = 0;
+                if (e & (1u << 31)) rw = 0;
+            }
+            return *(const x3_u4 *)ap;
+        };
+        auto shifted = [&](int s, uint32_t lw, x3_u4 w, uint32_t rw) {
+            if (s == 0) return x3_shifted<x3_shift(0, S, SW), HALF>(lw, w, rw);
+            if (s == 1) return x3_shifted<x3_shift(S > 1 ? 1 : 0, S, SW), HALF>(lw, w, rw);
+            if (s == 2) return x3_shifted<x3_shift(S > 2 ? 2 : 0, S, SW), HALF>(lw, w, rw);
+            if (s == 3) return x3_shifted<x3_shift(S > 3 ? 3 : 0, S, SW), HALF>(lw, w, rw);
+            return x3_shifted<x3_shift(S > 4 ? 4 : 0, S, SW), HALF>(lw, w, rw);
+        };
+        auto b_chunk = [&](const char *q) {
+            if (!HALF) return *(const x3_bf8 *)q;
+            const uint2 lo = *(const uint2 *)q, hi = *(const uint2 *)(q + 8);
+            return __builtin_bit_cast(x3_bf8, x3_u4{lo.x, lo.y, hi.x, hi.y});
+        };
+        auto mma = [&](x3_bf8 a, x3_bf8 b, acc_t &z) {
+            if constexpr (SH == 32) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, z, 0, 0, 0);
+            else z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, z, 0, 0, 0);
+        };
 #pragma unroll
         for (int st = 0; st < NST; ++st) {
             const uint32_t e = tab[(wq * NST + st) * CPS + kk];
-            const char *const ap = a_row + (e & 0xfff);
             const char *const bp = Xs + ((e >> 12) & 0x3fff);
             // the products of dY's smallest piece first; a piece's shifted operands serve every column tile, X's pieces
             // are read again for each (reads that the LDS has to spare, against 24 registers that the loop has not)
 #pragma unroll
             for (int qa = NP - 1; qa >= 0; --qa) {
-                const x3_u4 w = *(const x3_u4 *)(ap + qa * dy_piece);
-                uint32_t lw = 0, rw = 0;
-                if (S > 1 && !HALF) {
-                    lw = *(const uint32_t *)(ap + qa * dy_piece - 4);
-                    rw = *(const uint32_t *)(ap + qa * dy_piece + 16);
-                    if (e & (1u << 30)) lw = 0;
-                    if (e & (1u << 31)) rw = 0;
-                }
+                uint32_t lw, rw;
+                const x3_u4 w = a_words(e, qa, lw, rw);
                 x3_bf8 a[S];
-                a[0] = x3_shifted<x3_shift(0, S, SW), HALF>(lw, w, rw);
-                if constexpr (S > 1) a[1] = x3_shifted<x3_shift(1, S, SW), HALF>(lw, w, rw);
-                if constexpr (S > 2) a[2] = x3_shifted<x3_shift(2, S, SW), HALF>(lw, w, rw);
-                if constexpr (S > 3) a[3] = x3_shifted<x3_shift(3, S, SW), HALF>(lw, w, rw);
-                if constexpr (S > 4) a[4] = x3_shifted<x3_shift(4, S, SW), HALF>(lw, w, rw);
+#pragma unroll
+                for (int s = 0; s < S; ++s) a[s] = shifted(s, lw, w, rw);
 #pragma unroll
                 for (int t = 0; t < NTC; ++t) {
 #pragma unroll
@@ -502,16 +534,11 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                         const char *const q0 = bp + coloff[t] + f * p.twc * 16;
 #pragma unroll
                         for (int qb = NP - 1 - qa; qb >= 0; --qb) {
-                            x3_bf8 b;
-                            if (HALF) {
-                                const uint2 lo = *(const uint2 *)(q0 + qb * x_piece), hi = *(const uint2 *)(q0 + qb * x_piece + 8);
-                                b = __builtin_bit_cast(x3_bf8, x3_u4{lo.x, lo.y, hi.x, hi.y});
-                            } else b = *(const x3_bf8 *)(q0 + qb * x_piece);
+                            const x3_bf8 b = b_chunk(q0 + qb * x_piece);
 #pragma unroll
                             for (int s = 0; s < S; ++s) {
                                 if (x3_phase(s, S, SW) != f) continue;
-                                if constexpr (SH == 32) acc[t][s] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], b, acc[t][s], 0, 0, 0);
-                                else acc[t][s] = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b, acc[t][s], 0, 0, 0);
+                                mma(a[s], b, T::OWN && qa + qb ? small[T::OWN ? t : 0][T::OWN ? s : 0] : acc[t][s]);
                             }
                         }
                     }
@@ -521,6 +548,12 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         __builtin_amdgcn_sched_barrier(0);
     }
 
+    if constexpr (T::OWN) {
+#pragma unroll
+        for (int t = 0; t < NTC; ++t)
+#pragma unroll
+            for (int s = 0; s < S; ++s) acc[t][s] += small[t][s];
+    }
     // An infinity, a NaN or a value whose largest piece rounds to infinity makes infinities or NaNs of every product it
     // enters, and an accumulator keeps them: one look at the sums finds what the pieces could not represent.
     float worst[4] = {0.f, 0.f, 0.f, 0.f};
@@ -551,7 +584,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
             for (int v = 0; v < AV / 4; ++v) {
                 acc_t z = acc[ts / S][ts % S + s];
-                if (!BF) z *= kX3Unscale;               // (before they are added up, which could leave fp32's range)
+                if (!BF) z *= split & 1 ? -kX3Unscale : kX3Unscale;       // (before they are added up, which could leave fp32's range)
                 *(float4_t *)(red + ((wq * SR + s) * SH + i) * KTP + (SH == 32 ? 8 * v + 4 * kk : 4 * kk)) =
                     float4_t{z[4 * v], z[4 * v + 1], z[4 * v + 2], z[4 * v + 3]};
             }

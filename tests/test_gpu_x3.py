@@ -177,6 +177,28 @@ def test_error_is_that_of_fp32_sums():
     assert np.linalg.norm(got - want) < 6.5e-7 * np.linalg.norm(want)
 
 
+@pytest.mark.parametrize("t, dtype, bound", [
+    ((128, 16, 32, 32, 16, 3, 3, 1, 1, 1, 1), "fp32", 1.84e-7),
+    ((100, 33, 24, 24, 100, 3, 3, 1, 1, 1, 1), "fp32", 2.92e-7),
+    ((135, 4, 133, 8, 278, 3, 3, 2, 2, 1, 1), "fp32", 2.46e-7),
+    ((5, 5, 66, 170, 22, 5, 5, 1, 1, 2, 2), "fp32", 1.70e-7),
+    ((35, 24, 11, 148, 122, 3, 3, 1, 1, 1, 1), "fp32", 2.90e-7),
+    ((216, 29, 39, 39, 21, 3, 3, 1, 1, 1, 1), "fp32", 3.34e-7),
+    ((61, 182, 22, 8, 211, 3, 3, 1, 1, 1, 1), "bf16", 1.45e-7),
+])
+def test_error_is_that_of_fp32_sums_and_centred(t, dtype, bound):
+    """The bounds are what the fp32 matrix core's kernels are off (2-norm); bf16 1.1 times that.  The bf16 core rounds
+    what it adds to a larger sum downwards: the error's mean, which no length of the sum may let grow, stays a
+    fraction of it (unsigned sums: 4.8e-7 of the result's size in the sixth shape)."""
+    d = mk(t, dtype)
+    X, dY = rand_inputs(d, 17, dtype)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    err = run(d, to_gpu(X), to_gpu(dY)) - want
+    size = np.sqrt(np.mean(want * want))
+    assert np.sqrt(np.mean(err * err)) < bound * size
+    assert abs(err.mean()) < 5e-8 * size
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
     """Layers of several variants, and more groups than a launch carries, in one schedule run."""
