@@ -7,13 +7,13 @@
 
 namespace wgrad {
 
-struct X3Variant { int bf, sh, ntc, s, sw, rag, halo, rpc, nch, di, xi, kp, cp, ch, lds, occ, plane; };
+struct X3Variant { int bf, sh, ntc, s, sw, rag, halo, nch, di, xi, kp, cp, ch, lds, occ, plane; };
 static const X3Variant kVariant[kX3Variants] = {
 #define X(ID, ...) {__VA_ARGS__, X3Config<__VA_ARGS__>::kLds, X3Config<__VA_ARGS__>::kOcc, 0},
     WGRAD_X3_VARIANTS_FP32(X)
     WGRAD_X3_VARIANTS_BF16(X)
 #undef X
-    {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(4), 2, 4}, {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(2), 2, 2},
+    {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(4), 2, 4}, {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(2), 2, 2},
 };
 // workgroups that the chip holds at once
 static int x3_resident(const X3Variant &v) { return kNumCU * std::max(1, std::min(160 * 1024 / v.lds, v.occ)); }
@@ -60,27 +60,24 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
         pl.ctiles = (g.C + v.sh - 1) / v.sh;
         pl.ch = std::min(v.sh, g.C);
     }
-    if (v.rpc == 2) {
-        if (g.W != 4 || g.Wo != 4 || g.Ho != 4 || g.H != 4 || g.sh != 1 || g.R != 3 || vlo != 0 || vw != 4) return false;
-    }
-    const int vwc = v.rpc == 2 ? 1 : (vw + 7) / 8;           // (images of a tile, its rows and chunk columns are packed in 4, 8 and 4 bits)
+    const int vwc = (vw + 7) / 8;                            // (images of a tile, its rows and chunk columns are packed in 4, 8 and 4 bits)
     long best = -1;
     int best_x = 0;
     for (int twc = 1; twc <= std::min({vwc, v.nch, 16}); ++twc) {
         const int w_tiles = (vwc + twc - 1) / twc;
         if (twc > 1 && (vwc + twc - 2) / (twc - 1) == w_tiles) continue;      // the same number of narrower tiles does
-        const int halo = v.s > 1 && v.rpc == 1 && (w_tiles > 1 || vlo > 0 || vlo + 8 * twc < g.Wo);
+        const int halo = w_tiles > 1 || vlo > 0 || vlo + 8 * twc < g.Wo;
         if (halo && !v.halo) continue;
-        for (int ht = v.rpc; ht <= g.Ho; ht += v.rpc) {
-            if (ht / v.rpc * twc > v.nch) break;
-            int nti = ht >= g.Ho ? std::min({g.N, v.nch / (ht / v.rpc * twc), 16}) : 1;
+        for (int ht = 1; ht <= g.Ho; ++ht) {
+            if (ht * twc > v.nch) break;
+            int nti = ht >= g.Ho ? std::min({g.N, v.nch / (ht * twc), 16}) : 1;
             const int iht = (ht - 1) * g.sh + g.R;
             if (iht > 255) break;
             for (; nti >= 1; --nti) {
-                const int xr = nti * iht / v.rpc * twc;                        // staged chunks of a channel and phase
+                const int xr = nti * iht * twc;                        // staged chunks of a channel and phase
                 if ((long)pl.ch * xr > (long)v.xi * kBlock) continue;
                 if (halo && v.sh * nti * ht * 2 > kBlock) continue;
-                const int nch = nti * (ht / v.rpc) * twc;
+                const int nch = nti * ht * twc;
                 // (the last chunk of a dY channel is the chunk of zeros)
                 if ((halo ? 1 + nti * ht * (twc + 1) : nch) + 1 > v.kp || xr * v.sw > v.cp) continue;
                 const long tiles = (long)w_tiles * ((g.Ho + ht - 1) / ht) * ((g.N + nti - 1) / nti);
@@ -244,11 +241,10 @@ static void x3_fill(const X3Group &it, X3Shape &s)
     s.nch = pl.nch; s.ch = pl.ch; s.packed = pl.packed;
     s.halo = pl.halo; s.vlo = pl.vlo; s.xcol0 = pl.xcol0;
     if (kVariant[pl.variant].plane) return;
-    const int rpc = kVariant[pl.variant].rpc;
     s.d_nch = FastDiv(pl.nch);
     s.d_twc = FastDiv(pl.twc);
-    s.d_ht = FastDiv(pl.ht / rpc);
-    s.d_xrow = FastDiv(pl.nti * pl.iht / rpc * pl.twc);
+    s.d_ht = FastDiv(pl.ht);
+    s.d_xrow = FastDiv(pl.nti * pl.iht * pl.twc);
     s.d_iht = FastDiv(pl.iht);
     s.d_htiles = FastDiv(pl.h_tiles);
     s.d_wtiles = FastDiv(pl.w_tiles);

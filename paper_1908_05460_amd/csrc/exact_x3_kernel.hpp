@@ -42,7 +42,7 @@ struct X3Shape {
     int h_tiles, w_tiles, n_groups;
     int nch;                     // live chunks of a tile (the table points the rest at a chunk of zeros)
     int ch;                      // channels staged per column tile
-    int packed;                  // columns numbered c * R + r; otherwise column tile t is filter row t of SH channels (R = 1: channels t*SH..)
+    int packed;                  // columns numbered c * R + r; otherwise column tile t is filter row t of SH channels
     int halo;                    // staged rows of dY carry their neighbours' words (tiles that are not whole rows)
     int vlo, xcol0;              // slot 0: its dY column, its X column in phase 0
     FastDiv d_nch, d_twc, d_ht, d_xrow, d_iht, d_htiles, d_wtiles, d_r;
@@ -66,16 +66,12 @@ __host__ __device__ constexpr int x3_shift(int s, int S, int SW) { return (s - S
 __host__ __device__ constexpr int x3_phase(int s, int S, int SW) { return (s - S / 2 + 8 * SW) % SW; }
 
 // A = dY chunk as words w[0..3] with its neighbour words; element i of the result is element i - D of the row.
-template <int D, bool HALF>
+template <int D>
 __device__ __forceinline__ x3_bf8 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
 {
     x3_u4 o;
     auto mid = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_alignbit(hi, lo, 16); };
-    if (HALF) {                      // two rows of four: zeros come in from both sides of each half
-        if (D == 0) o = w;
-        else if (D == -1) o = x3_u4{mid(w[0], w[1]), w[1] >> 16, mid(w[2], w[3]), w[3] >> 16};
-        else o = x3_u4{w[0] << 16, mid(w[0], w[1]), w[2] << 16, mid(w[2], w[3])};
-    } else if (D == 0) o = w;
+    if (D == 0) o = w;
     else if (D == -1) o = x3_u4{mid(w[0], w[1]), mid(w[1], w[2]), mid(w[2], w[3]), mid(w[3], R)};
     else if (D == 1) o = x3_u4{mid(L, w[0]), mid(w[0], w[1]), mid(w[1], w[2]), mid(w[2], w[3])};
     else if (D == -2) o = x3_u4{w[1], w[2], w[3], R};
@@ -131,7 +127,6 @@ __device__ __forceinline__ void x3_general(const X3Shape &p, const void *X, cons
         const int s = o % S, col = (o / S) % (NTC * SH), k = k0 + o / (S * NTC * SH);
         int c, r;
         if (p.packed) { c = (coltile * NTC * SH + col) / g.R; r = (coltile * NTC * SH + col) % g.R; }
-        else if (g.R == 1) { c = c_first + col; r = 0; }
         else { c = c_first + col % SH; r = col / SH; }
         if (k >= g.K || c >= g.C) continue;
         float acc = 0.f;
@@ -155,12 +150,12 @@ __device__ __forceinline__ void x3_general(const X3Shape &p, const void *X, cons
 
 // BF: bf16 inputs, which are their own only piece.  SH: rows and columns of the matrix instruction (32: 32x32x16, 16: 16x16x32).  NTC: column tiles.  S: filter width.
 // SW: column stride.  RAG: rows whose width is not a multiple of four, or that start before column 0 of a tensor.
-// HALO: tiles may be parts of rows.  RPC: rows per chunk (2: rows of four slots).  NCH: chunks of a tile; DI, XI:
+// HALO: tiles may be parts of rows.  NCH: chunks of a tile; DI, XI:
 // staging items per thread; KP, CP: LDS chunks per channel of dY and of X (odd: conflict-free 16-byte reads); CH: channels
 // of X (compile-time, so that the operand reads have immediate offsets).
-template <bool BF_, int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int RPC_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
+template <bool BF_, int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
 struct X3Config {
-    static constexpr int SH = SH_, NTC = NTC_, S = S_, SW = SW_, RPC = RPC_, NCH = NCH_, DI = DI_, XI = XI_, KP = KP_, CP = CP_, CH = CH_, NW = 4;
+    static constexpr int SH = SH_, NTC = NTC_, S = S_, SW = SW_, NCH = NCH_, DI = DI_, XI = XI_, KP = KP_, CP = CP_, CH = CH_, NW = 4;
     static constexpr bool BF = BF_, RAG = RAG_, HALO = HALO_;
     static constexpr int NP = BF ? 1 : 3;                               // pieces of a number
     static constexpr bool OWN = !BF && SH == 16 && S <= 3;                // the smaller products have sums of their own
@@ -180,9 +175,9 @@ template <class T>
 __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt, const void *const *dYt, float *const *outt,
                                         char *smem, int bid, int nblk)
 {
-    constexpr int SH = T::SH, NTC = T::NTC, S = T::S, SW = T::SW, RPC = T::RPC, NCH = T::NCH, DI = T::DI, XI = T::XI, KP = T::KP, CP = T::CP,
+    constexpr int SH = T::SH, NTC = T::NTC, S = T::S, SW = T::SW, NCH = T::NCH, DI = T::DI, XI = T::XI, KP = T::KP, CP = T::CP,
                   NW = T::NW, NTHR = 64 * NW;
-    constexpr bool BF = T::BF, RAG = T::RAG, HALO = T::HALO, HALF = RPC == 2;
+    constexpr bool BF = T::BF, RAG = T::RAG, HALO = T::HALO;
     constexpr int NP = T::NP, DR = T::DR, ESZ = BF ? 2 : 4;
     constexpr int CPS = 64 / SH;                        // chunks per step (lane groups of an operand)
     constexpr int NST = NCH / (CPS * NW);                // steps per wavefront and tile
@@ -208,7 +203,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     const int ktile = (logical / p.ctiles) % p.ktiles;
     const int split = logical / (p.ctiles * p.ktiles);
     const int k0 = ktile * SH;
-    const int c_first = p.packed ? coltile * NTC * SH / R : coltile * SH * (R == 1 ? NTC : 1);
+    const int c_first = p.packed ? coltile * NTC * SH / R : coltile * SH;
 
     const int tiles_total = p.h_tiles * p.w_tiles * p.n_groups;
     const int wt_begin = (int)((long)split * tiles_total / p.splits);
@@ -229,10 +224,10 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             uint32_t k_l, chk, row, wc, n_l, h_l;
             p.d_nch.divmod(e, k_l, chk);
             p.d_twc.divmod(chk, row, wc);
-            p.d_ht.divmod(row, n_l, h_l);               // (HALF: h_l counts pairs of rows)
+            p.d_ht.divmod(row, n_l, h_l);
             const uint32_t idx = HALO && p.halo ? 1 + row * (p.twc + 1) + wc : chk;
-            if (k0 + (int)k_l < g.K) d_at[u] = (k_l * KP + idx) | n_l << 16 | h_l * RPC << 20 | wc << 28;
-            d_off[u] = (n_l * g.K + k_l) * L + h_l * RPC * g.Wo;
+            if (k0 + (int)k_l < g.K) d_at[u] = (k_l * KP + idx) | n_l << 16 | h_l << 20 | wc << 28;
+            d_off[u] = (n_l * g.K + k_l) * L + h_l * g.Wo;
         }
     }
     if (HALO && p.halo && tid < SH * p.nti * p.ht * 2) {           // one of a row's two neighbour words per thread
@@ -248,7 +243,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             uint32_t c_l, rem, row, wc, n_l, ih_l;
             p.d_xrow.divmod(e, c_l, rem);
             p.d_twc.divmod(rem, row, wc);
-            p.d_iht.divmod(HALF ? row * 2 : row, n_l, ih_l);
+            p.d_iht.divmod(row, n_l, ih_l);
             if (c_first + (int)c_l < g.C) x_at[u] = (c_l * CP + row * p.twc * SW + wc) | n_l << 16 | ih_l << 20 | wc << 28;
             x_off[u] = (n_l * g.C + c_l) * (g.H * g.W) + ih_l * g.W;
         }
@@ -305,10 +300,9 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         for (int u = 0; u < DI; ++u) {
             const uint32_t at = fresh(d_at[u]);
             const bool live = at != ~0u && at_n(at) < n_left && at_row(at) < h_left;
-            const int col = HALF ? 0 : (at_wc(at) + t.wc0) * 8 + p.vlo;
+            const int col = (at_wc(at) + t.wc0) * 8 + p.vlo;
             load4(yb, live, d_off[u], col, g.Wo, dr[u]);
-            if (HALF) load4(yb, live && at_row(at) + 1 < h_left, d_off[u] + g.Wo, 0, g.Wo, dr[u] + DR / 2);
-            else load4(yb, live, d_off[u], col + 4, g.Wo, dr[u] + DR / 2);
+            load4(yb, live, d_off[u], col + 4, g.Wo, dr[u] + DR / 2);
         }
         if (HALO && p.halo) {
             const int col = halo_col(t);
@@ -328,15 +322,10 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         for (int u = 0; u < XI; ++u) {
             const uint32_t at = fresh(x_at[u]);
             const int ih = ih0 + at_row(at);
-            const bool here = at != ~0u && at_n(at) < n_left;
-            const bool live = here && (unsigned)ih < (unsigned)g.H;
-            const int col = HALF ? 0 : (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
-            load4(xb, live, x_off[u] + row0, col, g.W, xr[u]);
-            if (HALF) load4(xb, here && (unsigned)(ih + 1) < (unsigned)g.H, x_off[u] + row0 + g.W, 0, g.W, xr[u] + DR / 2);
-            else {
+            const bool live = at != ~0u && at_n(at) < n_left && (unsigned)ih < (unsigned)g.H;
+            const int col = (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
 #pragma unroll
-                for (int q = 1; q < 2 * SW; ++q) load4(xb, live, x_off[u] + row0, col + 4 * q, g.W, xr[u] + DR / 2 * q);
-            }
+            for (int q = 0; q < 2 * SW; ++q) load4(xb, live, x_off[u] + row0, col + 4 * q, g.W, xr[u] + DR / 2 * q);
         }
     };
     // The matrix core rounds downwards what it adds to a larger sum, and five of the six products are small: the sums of the
@@ -424,7 +413,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             p.d_twc.divmod(q, row, wc);
             p.d_ht.divmod(row, n_l, h_l);
             const int a = HALO && p.halo ? 1 + row * (p.twc + 1) + wc : q;
-            const int b = HALF ? (n_l * p.iht + 2 * h_l) * 8 : ((n_l * p.iht + h_l * g.sh) * p.twc * SW + wc) * 16;
+            const int b = ((n_l * p.iht + h_l * g.sh) * p.twc * SW + wc) * 16;
             e = a * 16 | b << 12;
             if (!HALO || !p.halo) e |= (wc == 0 ? 1u << 30 : 0u) | ((int)wc + 1 == p.twc ? 1u << 31 : 0u);
         }
@@ -458,10 +447,10 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 
     // this lane's columns: byte offset of (channel, filter row) in a piece of X
     int coloff[NTC];
-    const int row_bytes = HALF ? 8 : p.twc * SW * 16;
+    const int row_bytes = p.twc * SW * 16;
 #pragma unroll
     for (int t = 0; t < NTC; ++t) {
-        int c_l = i + (R == 1 ? t * SH : 0), r = R == 1 ? 0 : t;
+        int c_l = i, r = t;
         if (p.packed) {
             const int col = coltile * NTC * SH + t * SH + i;
             uint32_t c, rr;
@@ -483,62 +472,39 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         if (wt + 1 < wt_end) load_tile(wt + 1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        auto a_words = [&](uint32_t e, int qa, uint32_t &lw, uint32_t &rw) {       // a dY chunk of a piece and its neighbour words
-            const char *const ap = a_row + (e & 0xfff) + qa * dy_piece;
-            lw = rw = 0;
-            if (S > 1 && !HALF) {
-                lw = *(const uint32_t *)(ap - 4);
-                rw = *(const uint32_t *)(ap + 16);
-                if (e & (1u << 30)) lw = 0;
-                if (e & (1u << 31)) rw = 0;
-            }
-            return *(const x3_u4 *)ap;
-        };
-        auto shifted = [&](int s, uint32_t lw, x3_u4 w, uint32_t rw) {
-            if (s == 0) return x3_shifted<x3_shift(0, S, SW), HALF>(lw, w, rw);
-            if (s == 1) return x3_shifted<x3_shift(S > 1 ? 1 : 0, S, SW), HALF>(lw, w, rw);
-            if (s == 2) return x3_shifted<x3_shift(S > 2 ? 2 : 0, S, SW), HALF>(lw, w, rw);
-            if (s == 3) return x3_shifted<x3_shift(S > 3 ? 3 : 0, S, SW), HALF>(lw, w, rw);
-            return x3_shifted<x3_shift(S > 4 ? 4 : 0, S, SW), HALF>(lw, w, rw);
-        };
-        auto b_chunk = [&](const char *q) {
-            if (!HALF) return *(const x3_bf8 *)q;
-            const uint2 lo = *(const uint2 *)q, hi = *(const uint2 *)(q + 8);
-            return __builtin_bit_cast(x3_bf8, x3_u4{lo.x, lo.y, hi.x, hi.y});
-        };
-        auto mma = [&](x3_bf8 a, x3_bf8 b, acc_t &z) {
-            if constexpr (SH == 32) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b, z, 0, 0, 0);
-            else z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a, b, z, 0, 0, 0);
-        };
 #pragma unroll
         for (int st = 0; st < NST; ++st) {
             const uint32_t e = tab[(wq * NST + st) * CPS + kk];
+            const char *const ap = a_row + (e & 0xfff);
             const char *const bp = Xs + ((e >> 12) & 0x3fff);
             // the products of dY's smallest piece first; a piece's shifted operands serve every column tile, X's pieces
             // are read again for each (reads that the LDS has to spare, against 24 registers that the loop has not)
 #pragma unroll
             for (int qa = NP - 1; qa >= 0; --qa) {
-                uint32_t lw, rw;
-                const x3_u4 w = a_words(e, qa, lw, rw);
+                const x3_u4 w = *(const x3_u4 *)(ap + qa * dy_piece);
+                uint32_t lw = *(const uint32_t *)(ap + qa * dy_piece - 4), rw = *(const uint32_t *)(ap + qa * dy_piece + 16);
+                if (e & (1u << 30)) lw = 0;
+                if (e & (1u << 31)) rw = 0;
                 x3_bf8 a[S];
-#pragma unroll
-                for (int s = 0; s < S; ++s) a[s] = shifted(s, lw, w, rw);
+                a[0] = x3_shifted<x3_shift(0, S, SW)>(lw, w, rw);
+                a[1] = x3_shifted<x3_shift(1, S, SW)>(lw, w, rw);
+                a[2] = x3_shifted<x3_shift(2, S, SW)>(lw, w, rw);
+                if constexpr (S > 3) a[3] = x3_shifted<x3_shift(3, S, SW)>(lw, w, rw);
+                if constexpr (S > 4) a[4] = x3_shifted<x3_shift(4, S, SW)>(lw, w, rw);
 #pragma unroll
                 for (int t = 0; t < NTC; ++t) {
 #pragma unroll
                     for (int f = 0; f < SW; ++f) {
-                        bool used = false;
-#pragma unroll
-                        for (int s = 0; s < S; ++s) used |= x3_phase(s, S, SW) == f;
-                        if (!used) continue;
                         const char *const q0 = bp + coloff[t] + f * p.twc * 16;
 #pragma unroll
                         for (int qb = NP - 1 - qa; qb >= 0; --qb) {
-                            const x3_bf8 b = b_chunk(q0 + qb * x_piece);
+                            const x3_bf8 b = *(const x3_bf8 *)(q0 + qb * x_piece);
 #pragma unroll
                             for (int s = 0; s < S; ++s) {
                                 if (x3_phase(s, S, SW) != f) continue;
-                                mma(a[s], b, T::OWN && qa + qb ? small[T::OWN ? t : 0][T::OWN ? s : 0] : acc[t][s]);
+                                acc_t &z = T::OWN && qa + qb ? small[T::OWN ? t : 0][T::OWN ? s : 0] : acc[t][s];
+                                if constexpr (SH == 32) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], b, z, 0, 0, 0);
+                                else z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b, z, 0, 0, 0);
                             }
                         }
                     }
@@ -568,7 +534,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     __syncthreads();
     float *const out = outt[prob] + (long)split * g.K * CRS;
     if (*(volatile uint32_t *)flag) {
-        x3_general<BF, SH, NTC, S, SW, NTHR>(p, Xp, dYp, out, k0, coltile, c_first, wt_begin, wt_end, HALF ? 4 : p.twc * 8);
+        x3_general<BF, SH, NTC, S, SW, NTHR>(p, Xp, dYp, out, k0, coltile, c_first, wt_begin, wt_end, p.twc * 8);
         return;
     }
     // ---- the wavefronts' sums: through LDS, SR filter columns of a column tile at a time (four rows of a lane side by
@@ -595,7 +561,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
             for (int w = 1; w < NW; ++w) sum += *(const float4_t *)(red + ((w * SR + sl) * SH + col) * KTP + 4 * rq);
             // entry of an output channel's row: (c * R + r) * S + s
-            const int lc = (p.packed || R == 1 ? t * SH + col : col * R + t) * S + s0 + sl;
+            const int lc = (p.packed ? t * SH + col : col * R + t) * S + s0 + sl;
 #pragma unroll
             for (int v = 0; v < 4; ++v) rows[(4 * rq + v) * P + lc] = sum[v];
         }
@@ -603,7 +569,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     __syncthreads();
     {
         const int j0 = (p.packed ? coltile * NTC * SH : c_first * R) * S;
-        const int cols = p.packed || R == 1 ? NTC * SH * S : SH * R * S, n = CRS - j0 < cols ? CRS - j0 : cols;
+        const int cols = p.packed ? NTC * SH * S : SH * R * S, n = CRS - j0 < cols ? CRS - j0 : cols;
         if (n == NTC * SH * S && k0 + SH <= g.K && CRS % 4 == 0 && j0 % 4 == 0 && ((uintptr_t)out & 15) == 0) {
             constexpr int Q = NTC * SH * S / 4, IT = (SH * Q + NTHR - 1) / NTHR;
             float *const dst = out + (long)k0 * CRS + j0;
@@ -621,24 +587,22 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     }
 }
 
-// (id, BF, SH, NTC, S, SW, RAG, HALO, RPC, NCH, DI, XI, KP, CP, CH)
+// (id, BF, SH, NTC, S, SW, RAG, HALO, NCH, DI, XI, KP, CP, CH)
 #define WGRAD_X3_VARIANTS_FP32(X) \
-    X(0, false, 32, 3, 3, 1, false, false, 1, 16, 2, 3, 17, 25, 32) X(1, false, 32, 3, 3, 1, false, true, 1, 16, 2, 3, 23, 25, 32) \
-    X(2, false, 32, 3, 3, 1, true, true, 1, 16, 2, 3, 23, 25, 32) X(3, false, 32, 3, 3, 1, false, false, 2, 16, 2, 3, 17, 25, 32) \
-    X(4, false, 16, 3, 3, 1, false, false, 1, 16, 1, 2, 17, 33, 16) X(5, false, 16, 3, 3, 1, true, true, 1, 16, 1, 2, 23, 33, 16) \
-    X(6, false, 16, 3, 3, 2, false, false, 1, 16, 1, 3, 17, 69, 16) X(7, false, 16, 3, 3, 2, true, true, 1, 16, 1, 3, 23, 69, 16) \
-    X(8, false, 16, 1, 3, 1, false, false, 1, 16, 1, 1, 17, 25, 7) X(9, false, 16, 1, 3, 1, true, true, 1, 16, 1, 1, 23, 25, 7) \
-    X(10, false, 32, 1, 3, 1, false, false, 1, 16, 2, 2, 17, 25, 12) X(11, false, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
-    X(12, false, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
+    X(0, false, 32, 3, 3, 1, false, false, 16, 2, 3, 17, 25, 32) X(1, false, 32, 3, 3, 1, false, true, 16, 2, 3, 23, 25, 32) \
+    X(2, false, 32, 3, 3, 1, true, true, 16, 2, 3, 23, 25, 32) X(3, false, 16, 3, 3, 1, false, false, 16, 1, 2, 17, 33, 16) \
+    X(4, false, 16, 3, 3, 1, true, true, 16, 1, 2, 23, 33, 16) X(5, false, 16, 3, 3, 2, false, false, 16, 1, 3, 17, 69, 16) \
+    X(6, false, 16, 3, 3, 2, true, true, 16, 1, 3, 23, 69, 16) X(7, false, 16, 1, 3, 1, false, false, 16, 1, 1, 17, 25, 7) \
+    X(8, false, 16, 1, 3, 1, true, true, 16, 1, 1, 23, 25, 7) X(9, false, 32, 1, 3, 1, false, false, 16, 2, 2, 17, 25, 12) \
+    X(10, false, 32, 1, 3, 1, true, true, 16, 2, 2, 23, 25, 12) X(11, false, 16, 5, 5, 1, true, true, 16, 1, 3, 23, 49, 16)
 #define WGRAD_X3_VARIANTS_BF16(X) \
-    X(13, true, 32, 3, 3, 1, false, false, 1, 32, 4, 5, 33, 41, 32) X(14, true, 32, 3, 3, 1, false, true, 1, 16, 2, 3, 23, 25, 32) \
-    X(15, true, 32, 3, 3, 1, true, true, 1, 16, 2, 3, 23, 25, 32) \
-    X(16, true, 16, 3, 3, 1, false, false, 1, 32, 2, 3, 33, 41, 16) X(17, true, 16, 3, 3, 1, true, true, 1, 32, 2, 3, 43, 41, 16) \
-    X(18, true, 16, 3, 3, 2, false, false, 1, 16, 1, 3, 17, 69, 16) X(19, true, 16, 3, 3, 2, true, true, 1, 16, 1, 3, 23, 69, 16) \
-    X(20, true, 16, 1, 3, 1, false, false, 1, 32, 2, 2, 33, 41, 7) X(21, true, 16, 1, 3, 1, true, true, 1, 32, 2, 2, 43, 41, 7) \
-    X(22, true, 32, 1, 3, 1, false, false, 1, 32, 4, 2, 33, 41, 12) X(23, true, 32, 1, 3, 1, true, true, 1, 16, 2, 2, 23, 25, 12) \
-    X(24, true, 16, 5, 5, 1, true, true, 1, 16, 1, 3, 23, 49, 16)
-constexpr int kX3FirstBf16 = 13, kX3Planes4 = 25, kX3Planes2 = 26, kX3Variants = 27;
+    X(12, true, 32, 3, 3, 1, false, false, 32, 4, 5, 33, 41, 32) X(13, true, 32, 3, 3, 1, false, true, 16, 2, 3, 23, 25, 32) \
+    X(14, true, 32, 3, 3, 1, true, true, 16, 2, 3, 23, 25, 32) X(15, true, 16, 3, 3, 1, false, false, 32, 2, 3, 33, 41, 16) \
+    X(16, true, 16, 3, 3, 1, true, true, 32, 2, 3, 43, 41, 16) X(17, true, 16, 3, 3, 2, false, false, 16, 1, 3, 17, 69, 16) \
+    X(18, true, 16, 3, 3, 2, true, true, 16, 1, 3, 23, 69, 16) X(19, true, 16, 1, 3, 1, false, false, 32, 2, 2, 33, 41, 7) \
+    X(20, true, 16, 1, 3, 1, true, true, 32, 2, 2, 43, 41, 7) X(21, true, 32, 1, 3, 1, false, false, 32, 4, 2, 33, 41, 12) \
+    X(22, true, 32, 1, 3, 1, true, true, 16, 2, 2, 23, 25, 12) X(23, true, 16, 5, 5, 1, true, true, 16, 1, 3, 23, 49, 16)
+constexpr int kX3FirstBf16 = 12, kX3Planes4 = 24, kX3Planes2 = 25, kX3Variants = 26;
 
 // The parameters are read through the kernel-argument segment pointer: indexing the by-value argument with a run-time
 // group number would make the compiler copy all of it into scratch memory first.

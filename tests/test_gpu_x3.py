@@ -31,7 +31,7 @@ EDGES = [
     (2, 33, 11, 14, 18, 5, 5, 1, 1, 2, 2),
     (40, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1),     # several workgroups share the reduction
     (1, 1, 5, 5, 1, 3, 3, 1, 1, 1, 1),
-    (73, 40, 6, 4, 40, 3, 3, 1, 1, 1, 1),       # two rows per chunk
+    (73, 40, 6, 4, 40, 3, 3, 1, 1, 1, 1),       # rows of half a chunk
     (130, 65, 4, 4, 65, 3, 3, 1, 1, 1, 1),      # position by position: one channel over both tiles, the last stage has two images
     (40, 64, 4, 4, 64, 3, 3, 1, 1, 1, 1),       # whole tiles
     (257, 33, 2, 2, 100, 3, 3, 1, 1, 1, 1),     # 2x2: the last stage has one image
