@@ -7,7 +7,7 @@
 // fp32 one, with fp32 accumulation as before.  bf16's smallest step is 2^-133, so both operands are scaled by 2^16 as
 // they are split, and the sums scaled back: every fp32 number then has its 24 bits in the pieces (unscaled, numbers
 // below 2^-110 lost bits of them: a tensor of 1e-36 was 2.5e-5 off).  What holds an infinity, a NaN or a number beyond
-// 2^111, or has a sum beyond 2^96, is recomputed by its workgroup with plain fp32 multiply-adds (x3_general), where the
+// 2^111, or has a sum beyond 2^96, is recomputed by its workgroup on the fp32 matrix core, from the same tiles: the
 // pieces would make NaNs of infinities.
 //
 // Implicit GEMM, rows = output channels k, columns = (input channel, filter row), reduction = "slots": the columns
@@ -26,6 +26,8 @@
 // bf16 inputs are their own only piece: the same kernel with one product per pair serves the bf16 shapes that
 // exact_bf16_kernel.hpp does not take.
 #pragma once
+#include <type_traits>
+
 #include "exact_common.hpp"
 
 namespace wgrad {
@@ -112,39 +114,6 @@ __device__ __forceinline__ void x3_realign(float (&v)[4], int d)
         if (e & 1) { v[3] = v[2]; v[2] = v[1]; v[1] = v[0]; v[0] = 0.f; }
         if (e & 2) { v[3] = v[1]; v[2] = v[0]; v[0] = v[1] = 0.f; }
         if (e >= 4) v[0] = v[1] = v[2] = v[3] = 0.f;
-    }
-}
-
-// The workgroup's whole result with fp32 multiply-adds straight from the tensors, X read as zero outside its bounds: its
-// tiles' slots, and in the first and last tile of a row the positions whose tap lies beyond all slots.
-template <bool BF, int SH, int NTC, int S, int SW, int NTHR>
-__device__ __forceinline__ void x3_general(const X3Shape &p, const void *X, const void *dY, float *out, int k0, int coltile,
-                                        int c_first, int wt_begin, int wt_end, int slots)
-{
-    const Geometry &g = p.g;
-    const int CRS = g.C * g.R * S;
-    for (int o = threadIdx.x; o < SH * NTC * SH * S; o += NTHR) {
-        const int s = o % S, col = (o / S) % (NTC * SH), k = k0 + o / (S * NTC * SH);
-        int c, r;
-        if (p.packed) { c = (coltile * NTC * SH + col) / g.R; r = (coltile * NTC * SH + col) % g.R; }
-        else { c = c_first + col % SH; r = col / SH; }
-        if (k >= g.K || c >= g.C) continue;
-        float acc = 0.f;
-        for (int wt = wt_begin; wt < wt_end; ++wt) {
-            const int wti = wt % p.w_tiles, hti = wt / p.w_tiles % p.h_tiles, n0 = wt / (p.w_tiles * p.h_tiles) * p.nti;
-            for (int n = n0; n < n0 + p.nti && n < g.N; ++n)
-                for (int h = hti * p.ht; h < (hti + 1) * p.ht && h < g.Ho; ++h) {
-                    const int ih = h * g.sh + r - g.ph;
-                    const long y0 = (((long)n * g.K + k) * g.Ho + h) * g.Wo, x0 = (((long)n * g.C + c) * g.H + ih) * g.W;
-                    const int v0 = p.vlo + wti * slots - x3_shift(s, S, SW);
-                    const int w0 = wti && v0 > 0 ? v0 : 0, w1 = wti + 1 < p.w_tiles ? v0 + slots : g.Wo;
-                    for (int w = w0; w < w1 && w < g.Wo; ++w) {
-                        const int iw = w * SW + s - g.pw;
-                        acc = fmaf(load_elem<BF>(dY, y0 + w), ih >= 0 && ih < g.H && iw >= 0 && iw < g.W ? load_elem<BF>(X, x0 + iw) : 0.f, acc);
-                    }
-                }
-        }
-        out[(long)k * CRS + (c * g.R + r) * S + s] = acc;
     }
 }
 
@@ -332,8 +301,13 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     // products come out low, by as much as 4.5e-7 of the result's size (64 -> 64 @ 224x224, N = 4).  Every other workgroup of
     // a reduction sums the negated products, so that what they lose cancels.
     const float dy_scale = split & 1 ? -kX3Scale : kX3Scale;
-    // a chunk's pieces to LDS; v(e): its element e (fp32 bits, or bf16 bits in the low half)
-    auto put = [&](auto v, char *dst, int piece, float scale) {
+    // a chunk's pieces (plain: its fp32 numbers, in the place of the first two) to LDS; v(e): its element e (fp32 bits, or bf16 bits in the low half)
+    auto put = [&](auto v, char *dst, int piece, float scale, auto plain) {
+        if constexpr (decltype(plain)::value && !BF) {
+            *(x3_u4 *)dst = x3_u4{v(0), v(1), v(2), v(3)};
+            *(x3_u4 *)(dst + piece) = x3_u4{v(4), v(5), v(6), v(7)};
+            return;
+        }
         x3_u4 h, m, l;
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
@@ -355,7 +329,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         if constexpr (DR == 4) return i & 1 ? v[i / 2] >> 16 : v[i / 2];
         else return v[i];
     };
-    auto commit_tile = [&](int wt) {
+    auto commit_tile = [&](int wt, auto plain) {
         Tile t{0, 0, 0};
         if (FIX) t = tile_of(wt);
 #pragma unroll
@@ -368,15 +342,18 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             }
             if (at != ~0u) {
                 if constexpr (DR == 4) *(x3_u4 *)(buf + kDyAt + at_dst(at)) = x3_u4{dr[u][0], dr[u][1], dr[u][2], dr[u][3]};
-                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, dy_scale);
+                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, dy_scale, plain);
             }
         }
-        if (HALO && p.halo) {
-            uint32_t h, m = 0, l = 0;
-            if constexpr (BF) h = hr[0] | hr[1] << 16;
-            else x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), h, m, l, dy_scale);
-            if (h_at != ~0u) {
-                char *const dst = buf + kDyAt + at_dst(h_at) + (at_wc(h_at) ? 0 : 12);
+        if (HALO && p.halo && h_at != ~0u) {
+            char *const chunk = buf + kDyAt + at_dst(h_at);
+            if constexpr (decltype(plain)::value && !BF) {
+                *(uint2 *)(chunk + (at_wc(h_at) ? 0 : dy_piece + 8)) = uint2{hr[0], hr[1]};
+            } else {
+                uint32_t h, m = 0, l = 0;
+                if constexpr (BF) h = hr[0] | hr[1] << 16;
+                else x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), h, m, l, dy_scale);
+                char *const dst = chunk + (at_wc(h_at) ? 0 : 12);
                 *(uint32_t *)dst = h;
                 if constexpr (!BF) {
                     *(uint32_t *)(dst + dy_piece) = m;
@@ -397,7 +374,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 else {
 #pragma unroll
                     for (int f = 0; f < SW; ++f)
-                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, kX3Scale);
+                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, kX3Scale, plain);
                 }
             }
         }
@@ -467,7 +444,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         // core holds up what follows it, and then both workgroups of a CU stage while neither multiplies (N = 512,
         // 128 -> 128 @ 16x16: 190 us without them, 155 with).
         __builtin_amdgcn_sched_barrier(0);
-        commit_tile(wt);
+        commit_tile(wt, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
         if (wt + 1 < wt_end) load_tile(wt + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -532,11 +509,89 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     const float any = (worst[0] + worst[1]) + (worst[2] + worst[3]);
     if (any != any) *flag = 1;
     __syncthreads();
-    float *const out = outt[prob] + (long)split * g.K * CRS;
+    float unscale = BF ? 1.f : (split & 1 ? -kX3Unscale : kX3Unscale);
     if (*(volatile uint32_t *)flag) {
-        x3_general<BF, SH, NTC, S, SW, NTHR>(p, Xp, dYp, out, k0, coltile, c_first, wt_begin, wt_end, p.twc * 8);
-        return;
+        // Once more on the fp32 matrix core, with the tiles' numbers as they are: a lane's chunk goes through it column by
+        // column, dY's own eight and the two on each side, each with the X of its tap's slot.  X counts only where that
+        // column of dY exists (an infinity of X is no product of a row's end), and a column whose slot lies before the
+        // first chunk or behind the last meets the padding's zero.  (64 -> 64 @ 32x32, N = 128, 60 us: one infinity 128, an
+        // infinity to every map or nothing but NaNs 190; with scalar multiply-adds from memory 4900 and 6500.)
+        unscale = 1.f;
+#pragma unroll
+        for (int t = 0; t < NTC; ++t)
+#pragma unroll
+            for (int s = 0; s < S; ++s)
+#pragma unroll
+                for (int v = 0; v < AV; ++v) acc[t][s][v] = 0.f;
+        load_tile(wt_begin);
+        for (int wt = wt_begin; wt < wt_end; ++wt) {
+            __syncthreads();
+            commit_tile(wt, std::true_type{});
+            if (wt + 1 < wt_end) load_tile(wt + 1);
+            __syncthreads();
+            const Tile tile = tile_of(wt);
+#pragma unroll 1
+            for (int st = 0; st < NST; ++st) {
+                const int q = (wq * NST + st) * CPS + kk;
+                const uint32_t e = tab[q];
+                uint32_t row, wc, n_l, h_l;
+                p.d_twc.divmod(q < p.nch ? q : 0, row, wc);
+                p.d_ht.divmod(row, n_l, h_l);
+                const bool live = q < p.nch && tile.n0 + (int)n_l < g.N && tile.h0 + (int)h_l < g.Ho;
+                const int chunk = tile.wc0 + (int)wc, col0 = chunk * 8 + p.vlo;
+                const bool first = chunk == 0, last = chunk + 1 == p.w_tiles * p.twc;
+                const char *const ap = a_row + (e & 0xfff), *const bp = Xs + ((e >> 12) & 0x3fff);
+                float y[12], x[8];                      // dY's columns col0 - 2 .. col0 + 9, X's slots
+                auto words = [](const char *at, float *v, int n) {      // n bf16 numbers
+#pragma unroll
+                    for (int i = 0; i < n; i += 2) {
+                        const uint32_t w = *(const uint32_t *)(at + 2 * i);
+                        v[i] = __uint_as_float(w << 16); v[i + 1] = __uint_as_float(w & 0xffff0000u);
+                    }
+                };
+                auto floats = [](const char *at, float *v, int n) {
+#pragma unroll
+                    for (int i = 0; i < n; ++i) v[i] = ((const float *)at)[i];
+                };
+                if constexpr (BF) words(ap - 4, y, 12);
+                else {
+                    floats(ap + dy_piece - 8, y, 2);
+                    floats(ap, y + 2, 4);
+                    floats(ap + dy_piece, y + 6, 4);
+                    floats(ap + 16, y + 10, 2);
+                }
+                if (e & (1u << 30)) y[0] = y[1] = 0.f;
+                if (e & (1u << 31)) y[10] = y[11] = 0.f;
+#pragma unroll
+                for (int t = 0; t < NTC; ++t)
+#pragma unroll
+                    for (int f = 0; f < SW; ++f) {
+                        const char *const q0 = bp + coloff[t] + f * p.twc * 16;
+                        if constexpr (BF) words(q0, x, 8);
+                        else {
+                            floats(q0, x, 4);
+                            floats(q0 + x_piece, x + 4, 4);
+                        }
+#pragma unroll
+                        for (int s = 0; s < S; ++s) {
+                            if (x3_phase(s, S, SW) != f) continue;
+#pragma unroll
+                            for (int i = 0; i < 12; ++i) {
+                                const int j = i - 2 + x3_shift(s, S, SW);
+                                const bool slot = j >= 0 && j < 8;
+                                const float a = slot || (j < 0 ? first : last) ? y[i] : 0.f;
+                                const float b = slot && live && (unsigned)(col0 + i - 2) < (unsigned)g.Wo ? x[slot ? j : 0] : 0.f;
+                                if constexpr (SH == 32) acc[t][s] = __builtin_amdgcn_mfma_f32_32x32x2f32(a, b, acc[t][s], 0, 0, 0);
+                                else acc[t][s] = __builtin_amdgcn_mfma_f32_16x16x4f32(a, b, acc[t][s], 0, 0, 0);
+                            }
+                            __builtin_amdgcn_sched_barrier(0);
+                        }
+                    }
+            }
+        }
+        __syncthreads();
     }
+    float *const out = outt[prob] + (long)split * g.K * CRS;
     // ---- the wavefronts' sums: through LDS, SR filter columns of a column tile at a time (four rows of a lane side by
     //      side, two buffers, one barrier a round), gathered as rows of the result and written out in whole lines ----
     constexpr int KTP = SH + 4, SR = T::SR, P = T::kOutP;
@@ -550,7 +605,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
             for (int v = 0; v < AV / 4; ++v) {
                 acc_t z = acc[ts / S][ts % S + s];
-                if (!BF) z *= split & 1 ? -kX3Unscale : kX3Unscale;       // (before they are added up, which could leave fp32's range)
+                if (!BF) z *= unscale;                  // (before they are added up, which could leave fp32's range)
                 *(float4_t *)(red + ((wq * SR + s) * SH + i) * KTP + (SH == 32 ? 8 * v + 4 * kk : 4 * kk)) =
                     float4_t{z[4 * v], z[4 * v + 1], z[4 * v + 2], z[4 * v + 3]};
             }

@@ -119,25 +119,36 @@ struct PlaneRole {
             if constexpr (T + 1 < NT) steps<T + 1, 0>(acc, small, a0, b0, kk);
         }
     }
-};
 
-template <int HW>
-__device__ __forceinline__ void planes_general(const X3Shape &p, const float *X, const float *dY, float *out, int k0, int c0, int n0, int n1)
-{
-    const Geometry &g = p.g;
-    for (int o = threadIdx.x; o < kPK * kPC * 9; o += kBlock) {
-        const int tap = o % 9, c = c0 + o / 9 % kPC, k = k0 + o / (9 * kPC);
-        if (k >= g.K || c >= g.C) continue;
-        float acc = 0.f;
-        for (int n = n0; n < n1; ++n)
-            for (int q = 0; q < HW * HW; ++q) {
-                const int ih = q / HW + tap / 3 - 1, iw = q % HW + tap % 3 - 1;
-                const float x = ih >= 0 && ih < HW && iw >= 0 && iw < HW ? X[((long)n * g.C + c) * HW * HW + ih * HW + iw] : 0.f;
-                acc = fmaf(dY[((long)n * g.K + k) * HW * HW + q], x, acc);
+    // A stage's numbers themselves (eight images: four in the place of the first piece, four in the second's) on the fp32
+    // matrix core, image by image.  Every position of dY takes part in every tap: one whose tap lies outside X meets a
+    // zero there, which a NaN or infinity of dY makes a NaN of.
+    template <int T>
+    static __device__ __forceinline__ void plain_steps(x3_f16 (&acc)[NT][2], const char *a0, const char *b0, int kk)
+    {
+        typedef PlaneCfg<HW> C;
+        constexpr int tap = role_taps<HW>(ROLE, T), dh = tap / 3 - 1, dw = tap % 3 - 1;
+#pragma unroll 1
+        for (int step = 0; step < (HW == 4 ? C::P / 2 : C::P); ++step) {
+            const int p = HW == 4 ? 2 * step + kk : step, h = p / HW + dh, w = p % HW + dw;
+            const bool here = h >= 0 && h < HW && w >= 0 && w < HW;
+            const int q = here ? h * HW + w : p;
+            const char *const ap = a0 + (HW == 4 ? p : 2 * p + kk) * (kPK * 16), *const bp = b0 + (HW == 4 ? q : 2 * q + kk) * (kPC * 16);
+#pragma unroll
+            for (int half = 0; half < 2; ++half) {
+                float4_t b = *(const float4_t *)(bp + half * C::kB);
+                if (!here) b = float4_t{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+                for (int m = 0; m < 2; ++m) {
+                    const float4_t a = *(const float4_t *)(ap + half * C::kA + m * 32 * 16);
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) acc[T][m] = __builtin_amdgcn_mfma_f32_32x32x2f32(a[j], b[j], acc[T][m], 0, 0, 0);
+                }
             }
-        out[(long)k * g.C * 9 + c * 9 + tap] = acc;
+        }
+        if constexpr (T + 1 < NT) plain_steps<T + 1>(acc, a0, b0, kk);
     }
-}
+};
 
 template <int HW, int ROLE>
 __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, const float *dYp, float *out, char *smem, int k0, int c0,
@@ -158,28 +169,31 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     uint32_t src[SETS], dst[SETS];                                      // byte offset of the first image's piece; LDS byte offset
     bool is_a[SETS];
     int first[SETS];                                                    // the item's first image in the stage
+    auto items = [&](int tid) {
 #pragma unroll
-    for (int u = 0; u < SETS; ++u) {
-        int row, grp, half = 0;
-        if (HW == 4) {
-            is_a[u] = u == 0;
-            row = u == 0 ? tid % kPK : tid % kPC;
-            grp = u == 0 ? tid / kPK : tid / kPC & 3;                   // row of the plane
-            half = u == 0 ? 0 : tid / (kPC * 4);
-            first[u] = 4 * half;
-        } else {
-            is_a[u] = tid < 2 * kPK;
-            const int f = is_a[u] ? tid : tid - 2 * kPK;
-            row = is_a[u] ? f % kPK : f % kPC;
-            grp = is_a[u] ? f / kPK : f / kPC;                          // group of eight images (2 and more: no item)
-            first[u] = 8 * grp;
+        for (int u = 0; u < SETS; ++u) {
+            int row, grp, half = 0;
+            if (HW == 4) {
+                is_a[u] = u == 0;
+                row = u == 0 ? tid % kPK : tid % kPC;
+                grp = u == 0 ? tid / kPK : tid / kPC & 3;                   // row of the plane
+                half = u == 0 ? 0 : tid / (kPC * 4);
+                first[u] = 4 * half;
+            } else {
+                is_a[u] = tid < 2 * kPK;
+                const int f = is_a[u] ? tid : tid - 2 * kPK;
+                row = is_a[u] ? f % kPK : f % kPC;
+                grp = is_a[u] ? f / kPK : f / kPC;                          // group of eight images (2 and more: no item)
+                first[u] = 8 * grp;
+            }
+            const bool live = HW == 4 || grp < 2;
+            const int chans = is_a[u] ? g.K : g.C, rows = is_a[u] ? kPK : kPC;
+            src[u] = live && (is_a[u] ? k0 : c0) + row < chans ? (uint32_t)((first[u] * chans + row) * C::P + (HW == 4 ? grp * 4 : 0)) * 4u : kDead;
+            dst[u] = live ? (uint32_t)((is_a[u] ? 0 : 3 * C::kA) + ((HW == 4 ? 4 * grp : grp) * rows + row) * 16 + 8 * half) : ~0u;
         }
-        const bool live = HW == 4 || grp < 2;
-        const int chans = is_a[u] ? g.K : g.C, rows = is_a[u] ? kPK : kPC;
-        src[u] = live && (is_a[u] ? k0 : c0) + row < chans ? (uint32_t)((first[u] * chans + row) * C::P + (HW == 4 ? grp * 4 : 0)) * 4u : kDead;
-        dst[u] = live ? (uint32_t)((is_a[u] ? 0 : 3 * C::kA) + ((HW == 4 ? 4 * grp : grp) * rows + row) * 16 + 8 * half) : ~0u;
-    }
-    uint32_t reg0[8][4], reg1[4][4];
+    };
+    items(tid);
+    x3_u4 reg0[8], reg1[4];
     auto load = [&](int st) {
         const int n0 = st * C::IMG, left = g.N - n0;
         const auto ra = __builtin_amdgcn_make_buffer_rsrc((void *)(dYp + ((long)n0 * g.K + k0) * C::P), 0, kDead, 0x00020000);
@@ -190,31 +204,42 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
             for (int j = 0; j < 8; ++j) {
                 if (j >= count) break;
                 const uint32_t off = src[u] != kDead && first[u] + j < left ? src[u] + j * step : kDead;
-                x3_u4 v;
-                if (is_a[u]) v = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0);
-                else v = __builtin_amdgcn_raw_buffer_load_b128(rb, off, 0, 0);
-#pragma unroll
-                for (int q = 0; q < 4; ++q) reg[j][q] = v[q];
+                if (is_a[u]) reg[j] = __builtin_amdgcn_raw_buffer_load_b128(ra, off, 0, 0);
+                else reg[j] = __builtin_amdgcn_raw_buffer_load_b128(rb, off, 0, 0);
             }
         };
         images(reg0, 0, 8);
         if constexpr (SETS > 1) images(reg1, 1, 4);
     };
-    auto commit = [&]() {
+    auto commit = [&](auto plain) {
         auto images = [&](auto &reg, int u, auto words) {
             constexpr int NW = decltype(words)::value;                  // words of a piece: pairs of images
             if (dst[u] == ~0u) return;
             const int rows = is_a[u] ? kPK : kPC, piece = is_a[u] ? C::kA : C::kB;
+            if constexpr (decltype(plain)::value) {
+                const int half = NW == 2 ? first[u] / 4 : 0;            // an item of four images is the first or the second four
 #pragma unroll
-            for (int q = 0; q < 4; ++q) {                              // position q of the item
-                uint32_t h[NW], m[NW], l[NW];
+                for (int h = 0; h < NW / 2; ++h)
 #pragma unroll
-                for (int e = 0; e < NW; ++e)
-                    x3_split2(__uint_as_float(reg[2 * e][q]), __uint_as_float(reg[2 * e + 1][q]), h[e], m[e], l[e]);
-                char *const d = As + dst[u] + (HW == 4 ? q : 2 * q) * rows * 16;
-                __builtin_memcpy(__builtin_assume_aligned(d, NW * 4), h, NW * 4);
-                __builtin_memcpy(__builtin_assume_aligned(d + piece, NW * 4), m, NW * 4);
-                __builtin_memcpy(__builtin_assume_aligned(d + 2 * piece, NW * 4), l, NW * 4);
+                    for (int q = 0; q < 4; ++q)
+                        *(x3_u4 *)(As + dst[u] - 8 * half + (h + half) * piece + (HW == 4 ? q : 2 * q) * rows * 16) =
+                            x3_u4{reg[4 * h][q], reg[4 * h + 1][q], reg[4 * h + 2][q], reg[4 * h + 3][q]};
+            } else {
+#pragma unroll
+                for (int q = 0; q < 4; ++q) {                          // position q of the item
+                    typedef uint32_t words_t __attribute__((ext_vector_type(NW)));
+                    words_t h, m, l;
+#pragma unroll
+                    for (int e = 0; e < NW; ++e) {
+                        uint32_t x, y, z;
+                        x3_split2(__uint_as_float(reg[2 * e][q]), __uint_as_float(reg[2 * e + 1][q]), x, y, z);
+                        h[e] = x; m[e] = y; l[e] = z;
+                    }
+                    char *const d = As + dst[u] + (HW == 4 ? q : 2 * q) * rows * 16;
+                    *(words_t *)d = h;
+                    *(words_t *)(d + piece) = m;
+                    *(words_t *)(d + 2 * piece) = l;
+                }
             }
         };
         images(reg0, 0, std::integral_constant<int, 4>{});
@@ -224,17 +249,20 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     load(st_begin);
     if (tid == 0) *flag = 0;
     x3_f16 acc[R::NT][2];
+    auto clear = [&]() {
 #pragma unroll
-    for (int t = 0; t < R::NT; ++t)
+        for (int t = 0; t < R::NT; ++t)
 #pragma unroll
-        for (int m = 0; m < 2; ++m)
+            for (int m = 0; m < 2; ++m)
 #pragma unroll
-            for (int v = 0; v < 16; ++v) acc[t][m][v] = 0.f;
+                for (int v = 0; v < 16; ++v) acc[t][m][v] = 0.f;
+    };
+    clear();
     const char *const a0 = As + i * 16, *const b0 = Bs + i * 16;
     for (int st = st_begin; st < st_end; ++st) {
         if (st != st_begin) __syncthreads();
         __builtin_amdgcn_sched_barrier(0);                             // (see exact_x3_kernel.hpp)
-        commit();
+        commit(std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
         if (st + 1 < st_end) load(st + 1);
         __builtin_amdgcn_sched_barrier(0);
@@ -252,10 +280,21 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
             for (int v = 0; v < 16; ++v) worst = fmaf(acc[t][m][v], 0.f, worst);
     if (worst != worst) *flag = 1;
     __syncthreads();
-    if (*(volatile uint32_t *)flag) {
-        const int n1 = st_end * C::IMG;
-        planes_general<HW>(p, Xp, dYp, out, k0, c0, st_begin * C::IMG, n1 < g.N ? n1 : g.N);
-        return;
+    float unscale = kX3Unscale;
+    if (*(volatile uint32_t *)flag) {                                  // (see exact_x3_kernel.hpp)
+        unscale = 1.f;
+        int again = tid;
+        asm volatile("" : "+v"(again));             // (decoded again, not kept in registers over the loop above)
+        items(again);
+        clear();
+        load(st_begin);
+        for (int st = st_begin; st < st_end; ++st) {
+            __syncthreads();
+            commit(std::true_type{});
+            if (st + 1 < st_end) load(st + 1);
+            __syncthreads();
+            R::template plain_steps<0>(acc, a0, b0, kk);
+        }
     }
     // the result by half tiles of 32 output channels, gathered in LDS as rows of the tensor
     constexpr int Q = kPC * 9, PITCH = Q + 4;
@@ -268,7 +307,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
         for (int t = 0; t < R::NT; ++t)
 #pragma unroll
             for (int v = 0; v < 16; ++v)
-                rows[(8 * (v / 4) + 4 * kk + v % 4) * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = acc[t][m][v] * kX3Unscale;
+                rows[(8 * (v / 4) + 4 * kk + v % 4) * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = acc[t][m][v] * unscale;
         __syncthreads();
         const int kb = k0 + m * 32;
         if (n == Q && kb + 32 <= g.K && CRS % 4 == 0 && ((uintptr_t)out & 15) == 0) {

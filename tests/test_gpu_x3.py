@@ -7,6 +7,7 @@ import pytest
 import oracle
 from paper_1908_05460_amd import binding as B
 from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
+from tests.x3_shapes import PLANS
 
 pytestmark = pytest.mark.gpu
 
@@ -44,10 +45,13 @@ def mk(t, dtype="fp32"):
     return B.desc(N, C, H, W, K, R, S, stride=sh, pad=ph, stride_w=sw, pad_w=pw, dtype=B.BF16 if dtype == "bf16" else B.F32)
 
 
-def run(d, X, dY):
+def torch_nan(d):
     import torch
-    dW = torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda")
-    return B.conv_wgrad_exact(d, X, dY, dW=dW).cpu().numpy()
+    return torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda")
+
+
+def run(d, X, dY):
+    return B.conv_wgrad_exact(d, X, dY, dW=torch_nan(d)).cpu().numpy()
 
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
@@ -58,6 +62,33 @@ def test_edges_match_the_oracle(t, dtype):
     want = oracle.wgrad_exact(oracle_shape(d), X, dY)
     # fp32 sums of exact products: far inside the fp32 tolerance (a lost piece would cost 4e-3, 2e-5 or 1e-7)
     assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), want) < TOL["fp32"] / 50
+
+
+@pytest.mark.parametrize("variant, t, dtype, halo", PLANS)
+def test_every_variant_matches_the_oracle(variant, t, dtype, halo):
+    """Several tiles to a workgroup: the next tile's loads, LDS reuse, neighbour words and uneven shares of a reduction;
+    then with infinities and NaNs, which only what they meet may show."""
+    d = mk(t, dtype)
+    X, dY = rand_inputs(d, 99, dtype)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    assert normwise_err(got, want) < TOL["fp32"] / 50
+    size = np.sqrt(np.mean(want * want))
+    bits = {np.inf: 0x7F80, -np.inf: 0xFF80, np.nan: 0x7FC0}
+    ends = ((0, 0, 0, 0), (-1, -1, -1, -1), (-1, 1, 0, -1), (0, -1, -1, 0))
+    for bad, where in ((np.inf, X), (-np.inf, dY), (np.nan, dY)):
+        kept = [where[at] for at in ends]
+        for at in ends:
+            where[at] = bits[bad] if dtype == "bf16" else bad
+        with np.errstate(all="ignore"):
+            want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+        got = run(d, to_gpu(X), to_gpu(dY))
+        fine = np.isfinite(want)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+        if fine.any():
+            assert np.abs(got[fine] - want[fine]).max() < TOL["fp32"] * size
+        for at, v in zip(ends, kept):
+            where[at] = v
 
 
 @pytest.mark.parametrize("t", [EDGES[4], EDGES[5], EDGES[12], EDGES[13], EDGES[15], EDGES[19], EDGES[20], EDGES[21]])
@@ -214,3 +245,22 @@ def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
     s.run(m, B.alloc_workspace(s.workspace_bytes(m)))
     for d, (X, dY), got in zip(ds, data, out):
         assert normwise_err(got.cpu().numpy(), run(d, X, dY).astype(np.float64)) < TOL["fp32"] / 50
+
+
+def test_infinities_in_a_run_of_layers():
+    """2x2 planes of whole tiles take the position form in a run only."""
+    shapes = [EDGES[0], EDGES[4], EDGES[19], (70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)]
+    ds = [mk(t) for t in shapes]
+    data = [rand_inputs(d, 200 + i) for i, d in enumerate(ds)]
+    for X, dY in data:
+        dY[0, 0, 0, 0], dY[-1, 5, -1, -1], X[1, 3, 0, 0] = np.inf, np.nan, -np.inf
+    out = [torch_nan(d) for d in ds]
+    s = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
+    m = [B.EXACT] * len(ds)
+    s.run(m, B.alloc_workspace(s.workspace_bytes(m)))
+    for d, (X, dY), got in zip(ds, data, out):
+        with np.errstate(all="ignore"):
+            want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+        got, fine = got.cpu().numpy(), np.isfinite(want)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+        assert normwise_err(got[fine], want[fine]) < TOL["fp32"]
