@@ -7,7 +7,7 @@ import pytest
 import oracle
 from paper_1908_05460_amd import binding as B
 from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
-from tests.x3_shapes import PLANS
+from tests.x3_shapes import PLANS, plan
 
 pytestmark = pytest.mark.gpu
 
@@ -232,9 +232,11 @@ def test_error_is_that_of_fp32_sums_and_centred(t, dtype, bound):
 
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
-    """Layers of several variants, and more groups than a launch carries, in one schedule run."""
+    """Layers of several variants, and of one variant more groups (9) and layers (24) than a launch carries, in one run."""
     import torch
-    shapes = EDGES + [(5, 64 + 8 * i, 16, 16, 64, 3, 3, 1, 1, 1, 1) for i in range(10)] + [(40, 128, 16, 16, 128, 3, 3, 1, 1, 1, 1)] * 3
+    many = [(5, 64 + 16 * i, 17, 17, 64, 3, 3, 1, 1, 1, 1) for i in range(10)]      # ten groups of three
+    assert len({plan(t, dtype)[0].variant for t in many}) == 1 and all(plan(t, dtype)[1] == 2 for t in many)
+    shapes = EDGES + many * 3 + [(40, 128, 16, 16, 128, 3, 3, 1, 1, 1, 1)] * 3
     # 2x2 planes that alone are a plain matrix product and in a run are not
     shapes += [(70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)]
     ds = [mk(t, dtype) for t in shapes]
