@@ -452,12 +452,35 @@ def run_sweep(args, name):
     return res
 
 
+def short(out):
+    """The line without what a reader of the tail of a log does not need (readers keep a few KB of it): no per-layer
+    rows, checksums or notes, and of the nested configurations the times, rates and fractions."""
+    def bare(d):
+        return {k: bare(v) if isinstance(v, dict) else v for k, v in d.items() if k not in ("note", "how")}
+
+    def nested(c):
+        d = {k: c[k] for k in ("ms_per_step", "dtype", "phase_ms", "speedup_approx_vs_exact") if k in c}
+        for k in ("roofline", "roofline_approx"):
+            if k in c:
+                d[k] = {f: c[k][f] for f in ("achieved", "unit", "frac", "frac_valid_taps") if f in c[k]}
+        if "sweep" in c:
+            d["sweep_ms_per_iter"] = {k: v["ms_per_iter"] for k, v in c["sweep"].items()}
+        return d
+
+    line = {k: bare(v) if isinstance(v, dict) else v for k, v in out.items()
+            if k not in ("per_layer", "input_checksums_crc32", "configs", "paper_context")}
+    line["configs"] = {k: nested(c) for k, c in out["configs"].items()}
+    return line
+
+
 def main():
     ap = argparse.ArgumentParser()
     ap.add_argument("--gpus", type=int, default=1)
     ap.add_argument("--steps", type=int, default=50)
     ap.add_argument("--warmup", type=int, default=10)
     ap.add_argument("--workload", default=HEADLINE)
+    ap.add_argument("--full", action="store_true",
+                    help="the whole line: per-layer rows, checksums, notes and the other configurations in full (34 KB)")
     ap.add_argument("--no-extras", action="store_true",
                     help="only the headline workload: no machine ceilings and no nested results of the other configurations")
     ap.add_argument("--copies", type=int, default=0, help="distinct input sets to rotate (0 = enough for 1 GB)")
@@ -534,7 +557,7 @@ def main():
     out["wall_s"] = round(time.perf_counter() - t_begin, 1)
     out["paper_context"] = ("paper: approx kernel incl. transposes >= 3x faster than cuDNN 7.4.2 backward-filter "
                             "on a Titan Xp for most layers; end-to-end training speedup 3.5% (ResNet-20) to ~7%")
-    print(json.dumps(out))
+    print(json.dumps(out if args.full else short(out)))
 
 
 if __name__ == "__main__":
