@@ -171,7 +171,8 @@ int conv_wgrad_random(const wgrad_conv_desc *desc, float *dW, float sigma,
                       uint64_t seed, uint64_t offset, void *stream);
 
 /* Bytes of device scratch the given method needs for this layer (0 for
- * WGRAD_ZERO and WGRAD_RANDOM).  Returns 0 for an invalid descriptor too; use a
+ * WGRAD_ZERO and WGRAD_RANDOM) in this version of the library; another may need
+ * more or less, so ask the one that runs.  Returns 0 for an invalid descriptor too; use a
  * compute call to learn why a descriptor is rejected. */
 size_t conv_wgrad_workspace_bytes(const wgrad_conv_desc *desc, wgrad_method method);
 

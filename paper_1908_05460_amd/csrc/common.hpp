@@ -117,6 +117,8 @@ int launch_exact_plane2(const Geometry &g, const Batch &b, hipStream_t st, Multi
 struct CombineQueue;
 bool plan_exact_x3(const Geometry &g, X3Plan &pl);
 bool x3_needs_alignment(const X3Plan &pl);
+bool x3_ragged(const X3Plan &pl);
+int x3_tile_rows(const X3Plan &pl);
 struct X3Queue;
 X3Queue *x3_queue_new();
 void x3_queue_delete(X3Queue *q);

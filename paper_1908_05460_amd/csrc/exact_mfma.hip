@@ -585,12 +585,39 @@ static ExactPlan size_exact(const Geometry &g, ExactPlan pl)
     return pl;
 }
 
+// Where the forms above are the faster ones although the three-piece form takes the shape (of 2000 shapes timed both ways;
+// us of this form / of the older one, N, C -> K @ H x W):
+static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan &x3, double gflop)
+{
+    const bool strided = g.sw > 1, whole = g.C % 16 == 0 && g.K % 16 == 0;
+    if (g.bf16) {
+        // few channels: long rows, which are staged element by element (249, 3 -> 128 @ 56x56, stride 2: 50 / 35; 12, 3 -> 128
+        // @ 112x112: 43 / 33; 67, 7 -> 32 @ 112x112: 108 / 59)
+        if (!pl.stream) return false;
+        if (pl.nt == 2) return strided ? g.Wo >= 28 && gflop >= 0.2 : gflop >= 1.0;
+        return pl.nt == 4 && x3_ragged(x3) && g.C >= 6 && gflop >= 0.6;
+    }
+    // filters of at most two tiles of columns in all (three input channels): dY's stream bounds them, and the staging's split
+    // is work beside it (53, 3 -> 128 @ 64x64: 57 / 35; stride 2, 164: 76 / 33)
+    if (pl.nt == 2 && (strided ? g.Wo >= 12 : pl.stream && g.Wo >= 16)) return true;
+    // of four (up to seven channels; 37, 7 -> 97 @ 64x64: 67 / 43; stride 2, 58, 4 -> 126 @ 30x146: 60 / 48)
+    if (pl.nt == 4 && (strided ? g.C <= 5 && g.Wo >= 8 && gflop >= 0.15 : pl.stream && g.Wo >= 40 && gflop >= 0.5 && x3_tile_rows(x3) == 16)) return true;
+    if (g.S == 5 && pl.stream && g.C <= 5 && gflop >= 1.2) return true;              // 8, 3 -> 128 @ 112x112, 5x5: 78 / 65
+    if (pl.nt != 9 || !strided) return false;
+    // strides: planes of four columns, half of whose chunks are empty (44, 128 -> 512 @ 8x8: 31 / 25; 145, 256 -> 256 @ 7x7:
+    // 126 / 88), and whole rows that the form has to cut (23, 64 -> 64 @ 56x56: 43 / 39)
+    if (pl.stream) return x3_ragged(x3) ? gflop >= 1.0 && g.Wo >= 24 && whole : g.Wo <= 4 && gflop >= 0.8;
+    return gflop >= 1.0 && (g.Wo <= 4 || (g.Wo == 5 && g.C % 64 == 0 && g.K % 64 == 0));
+}
+
 // The plan of a shape: the fp32 and bf16 forms above, and beside them the three-piece form (exact_x3.hip), which takes
 // what the streaming form cannot (27x27 planes, 48 -> 96, N = 32: 76 -> 35 us; 224x224, 64 -> 64, N = 4: 302 -> 88) and
 // all but two kinds of what it can: long strided reductions, whose windows are mostly staging (128 -> 128 @ 56x56, stride
 // 2, N = 16, 3.7 GFLOP: 86 us against 60; at 0.2 to 0.9 GFLOP 13 to 23 against 16 to 29), and, in a run of several layers,
-// layers so short that one launch of all of them wins (ResNet-20 at N = 16 to 64: 36 to 67 us against 55 to 74; its
-// 0.6-GFLOP layers at N = 128 are over the line: 107 -> 93).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
+// layers of less than 0.5 GFLOP.  That line was drawn where one launch of all of a run's short layers won (ResNet-20 at N =
+// 16 to 64: 36 to 67 us against 55 to 74), before the 16-wide tiles' smaller products had sums of their own and three of
+// their workgroups, not four, shared a CU; by now it lies too high (without a line, N = 32 / 64 / 96 / 128: 49 -> 45, 68 ->
+// 60, 87 -> 76, 93 -> 91 us; the fp32 matrix core alone at N = 128 107).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
 // against 14.8).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
 // of its own is what costs (VGG-19, N = 128: 50 us of it against 39); alone that is the faster one (512 -> 512, N = 128:
@@ -610,7 +637,7 @@ ExactPlan plan_exact(const Geometry &g)
     } else if (pl.stream && g.sw > 1 && gflop >= 1.5) use = 0;
     else use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
     X3Plan x3{};
-    if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3)) return size_exact(g, pl);
+    if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) return size_exact(g, pl);
     // (the other form's split and workspace only where a call may come back to it)
     if (use != 2 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
     pl.x3 = use;

@@ -103,7 +103,7 @@ static double x3_tile_us(const X3Variant &v, int share)
 {
     if (v.plane) return 1.1 * (v.plane == 4 ? std::max(share * 2.8, 4.2) : std::max(share * 0.85, 1.8));
     const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.bf ? 1 : 6) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
-    const double stage = 0.3 + (v.bf ? 0.1 : 0.33) * (v.di + v.xi * v.sw);
+    const double stage = 0.3 + (v.rag && v.sw > 1 ? 0.6 : (v.bf ? 0.1 : 0.33)) * (v.di + v.xi * v.sw);
     return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
 }
 static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(v) / kNumCU); }
@@ -181,6 +181,10 @@ static int x3_choose_splits(const Geometry &g, const X3Plan &pl, int nprob)
 // whether the variant reads bf16 rows in 8-byte pieces (4-byte aligned tensors), not element by element
 bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].bf && !kVariant[pl.variant].rag; }
 
+// whether the variant stages rows of any width and cut rows; output channels of its tile
+bool x3_ragged(const X3Plan &pl) { return kVariant[pl.variant].rag; }
+int x3_tile_rows(const X3Plan &pl) { return kVariant[pl.variant].sh; }
+
 bool plan_exact_x3(const Geometry &g, X3Plan &best)
 {
     if (!g.bf16 && g.H == g.W && (g.W == 2 || g.W == 4)) {
@@ -207,7 +211,9 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
         // 48 -> 96 @ 27x27, N = 32, where 32x32 tiles would be a third padding besides: 35 against 49).
         double cost = (double)pl.ktiles * pl.ctiles * pl.w_tiles * pl.h_tiles * pl.n_groups * v.nch * v.ntc *
                       (v.sh == 32 ? 4.0 : (gflop < (g.bf16 ? 12.0 : 2.0) ? 0.9 : 1.15));
-        cost *= v.rag ? 1.1 : (v.halo ? 1.02 : 1.0);
+        // (ragged bf16 rows are loaded element by element: 64 -> 64 @ 56x56, stride 2, N = 128, 162 us that way, 56 with whole
+        // rows and fewer of them to a tile)
+        cost *= v.rag ? (v.bf ? (v.sw > 1 ? 2.5 : 1.5) : 1.1) : (v.halo ? 1.02 : 1.0);
         if (cost < best_cost) { best_cost = cost; best = pl; }
     }
     if (best_cost >= 1e30) return false;

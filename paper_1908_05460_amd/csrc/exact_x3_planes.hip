@@ -6,10 +6,11 @@
 //
 // The reduction of a G_pq runs over images, so an operand is "eight images of one position" and the (position, tap)
 // pairs whose tap meets only padding are never multiplied: 100 of 144 are left on a 4x4 plane, 16 of 36 on a 2x2 plane.
-// The matrix core under the chip's power limit bounds these layers, so a product left out is time saved: 512 -> 512 @
-// 4x4 takes 17.4 / 56.6 / 153 us at N = 16 / 128 / 512 (the fp32 matrix core 30.2 / 75 / 227, the row form of
-// exact_x3_kernel.hpp 63 at N = 128), 2x2 15.4 -> 45.7 us where the fp32 matrix core takes 49.7 (N = 512) and half of its
-// time in a run of layers; VGG-19's run 526 -> 489 us.
+// Matrix instructions and the staging's vector instructions (three to each) take turns: the matrix core is busy 43 % of
+// the cycles of VGG-19's launch, at 2.27 GHz, so a product left out is time saved.  512 -> 512 @ 4x4 takes 16.9 / 53.8 /
+// 150 us at N = 16 / 128 / 512 (the fp32 matrix core 28.8 / 72 / 228, the row form of exact_x3_kernel.hpp 63 at N = 128),
+// 2x2 15.4 -> 45.7 us where the fp32 matrix core takes 49.7 (N = 512) and half of its time in a run of layers; VGG-19's
+// run 526 -> 489 us.
 //
 // A workgroup owns 64 output channels x 32 input channels; its four wavefronts share the taps out (13, 12, 12 and 15
 // steps of a 4x4 plane's stage, 4 each of a 2x2 plane's; which wavefront has which changes with the workgroup), so that

@@ -27,7 +27,7 @@ EDGES = [
     (2, 20, 9, 21, 24, 3, 3, 2, 2, 1, 1),       # strides, odd width
     (2, 20, 9, 20, 24, 3, 3, 3, 2, 0, 2),
     (40, 20, 9, 20, 24, 3, 3, 2, 1, 1, 1),      # stride in rows alone
-    (500, 3, 20, 24, 40, 3, 3, 1, 1, 1, 1),     # (channel, filter row) columns
+    (500, 3, 20, 12, 80, 3, 3, 1, 1, 1, 1),     # (channel, filter row) columns
     (2, 9, 12, 13, 40, 3, 3, 1, 1, 1, 1),
     (2, 33, 11, 14, 18, 5, 5, 1, 1, 2, 2),
     (40, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1),     # several workgroups share the reduction

@@ -20,7 +20,7 @@ PLANS = [
     (7, (49, 33, 36, 4, 33, 3, 3, 3, 1, 1, 1), "fp32", 0),
     (8, (37, 33, 18, 12, 33, 3, 3, 3, 1, 1, 0), "fp32", 1),
     (8, (25, 65, 35, 6, 33, 3, 3, 3, 1, 0, 0), "fp32", 0),
-    (9, (179, 10, 18, 64, 55, 1, 3, 1, 1, 0, 1), "fp32", 0),
+    (9, (16, 97, 71, 8, 159, 3, 3, 1, 1, 1, 1), "fp32", 0),
     (10, (57, 9, 25, 128, 40, 1, 3, 1, 1, 0, 3), "fp32", 1),
     (10, (107, 11, 51, 64, 13, 1, 3, 3, 1, 0, 0), "fp32", 0),
     (11, (112, 5, 37, 4, 65, 5, 5, 3, 1, 0, 3), "fp32", 1),
@@ -41,13 +41,29 @@ PLANS = [
     (20, (125, 40, 15, 19, 10, 3, 3, 3, 1, 0, 0), "bf16", 0),
     (21, (139, 8, 43, 32, 65, 1, 3, 1, 1, 0, 1), "bf16", 0),
     (22, (92, 8, 15, 70, 40, 1, 3, 1, 1, 0, 3), "bf16", 1),
-    (22, (167, 11, 45, 4, 65, 3, 3, 3, 1, 1, 1), "bf16", 0),
     (23, (218, 5, 15, 4, 65, 5, 5, 1, 1, 0, 3), "bf16", 1),
     (23, (106, 8, 20, 8, 65, 5, 5, 1, 1, 2, 0), "bf16", 0),
     (24, (74, 250, 4, 4, 450, 3, 3, 1, 1, 1, 1), "fp32", 0),
     (25, (162, 250, 2, 2, 450, 3, 3, 1, 1, 1, 1), "fp32", 0),
 ]
 VARIANTS = 26
+
+# layers that the older forms answer sooner (us of this form / of the older one)
+OLDER = [
+    ((53, 3, 64, 64, 128, 3, 3, 1, 1, 1, 1), "fp32"),       # 57 / 35
+    ((164, 3, 64, 64, 128, 3, 3, 2, 2, 1, 1), "fp32"),      # 76 / 33
+    ((190, 3, 12, 37, 161, 3, 3, 2, 2, 1, 1), "fp32"),      # 49 / 30
+    ((37, 7, 64, 64, 97, 3, 3, 1, 1, 1, 1), "fp32"),        # 67 / 43
+    ((58, 4, 30, 146, 126, 3, 3, 2, 2, 1, 1), "fp32"),      # 60 / 48
+    ((8, 3, 112, 112, 128, 5, 5, 1, 1, 2, 2), "fp32"),      # 78 / 65
+    ((44, 128, 8, 8, 512, 3, 3, 2, 2, 1, 1), "fp32"),       # 31 / 25
+    ((145, 256, 7, 7, 256, 3, 3, 2, 2, 1, 1), "fp32"),      # 126 / 88
+    ((125, 256, 17, 9, 128, 3, 3, 2, 2, 1, 1), "fp32"),     # 152 / 99
+    ((23, 64, 56, 56, 64, 3, 3, 2, 2, 1, 1), "fp32"),       # 43 / 39
+    ((249, 3, 56, 56, 128, 3, 3, 2, 2, 1, 1), "bf16"),      # 50 / 35
+    ((12, 3, 112, 112, 128, 3, 3, 1, 1, 1, 1), "bf16"),     # 43 / 33
+    ((67, 7, 112, 112, 32, 3, 3, 1, 1, 1, 1), "bf16"),      # 108 / 59
+]
 
 
 class _Geometry(ct.Structure):
