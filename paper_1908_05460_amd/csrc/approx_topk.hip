@@ -3,6 +3,8 @@
 // position carries sum/k, so that the k = 1 case is Algorithm 1 and the retained mass is
 // the map's sum whatever k is.  Two kernels: selection, then a gather over the kept
 // positions; the batch-chunk partials go through the common reduction.
+#include <type_traits>
+
 #include "common.hpp"
 
 namespace wgrad {
@@ -221,57 +223,80 @@ __global__ __launch_bounds__(WG ? WG : kBlock) void topk_select(const void *__re
 // images and the k kept positions of map (n, ko), adding (sum/k) times the input element
 // its tap sees there (zero outside the image).  The loads bound it: kDeep positions, then kDeep
 // elements, are in flight at a time, and an XCD takes whole chunks, so that the input of a chunk
-// is fetched into one L2 and not into all eight.
-// 64 -> 64 @ 56x56, N = 32, k = 4: 23.2 -> 12.4 us.
-template <bool BF16>
+// is fetched into one L2 and not into all eight.  On small planes, whose loads hit, the addresses bound it instead: what a
+// wavefront shares is added in scalar registers, a lane's part is 32 bits wide and its products 24 (FAR: sizes beyond
+// that, with 64-bit parts).
+// 64 -> 64 @ 56x56, N = 32, k = 4: 23.2 -> 12.4 us; 215 -> 62 @ 9x6, 5x5, stride 2, N = 84, k = 8: 282 -> 183 (216 without
+// the loads ahead).
+template <bool BF16, bool FAR>
 __global__ __launch_bounds__(kBlock) void topk_gather(const void *__restrict__ X, const int32_t *__restrict__ hw,
                                                       const float *__restrict__ sum, float *__restrict__ out,
                                                       Geometry g, int k, float inv_k, int chunk_n, float scale, int eblocks)
 {
     constexpr int kDeep = 8;
-    const int logical = xcd_contiguous_id((int)blockIdx.x, (int)gridDim.x), chunk = logical / eblocks;
+    const int logical = xcd_contiguous_id((int)blockIdx.x, (int)gridDim.x), chunk = __builtin_amdgcn_readfirstlane(logical / eblocks);
     const long o = (long)(logical - chunk * eblocks) * kBlock + threadIdx.x;
     const int RS = g.R * g.S, CRS = g.C * RS;
     if (o >= (long)g.K * CRS) return;
     const int ko = (int)(o / CRS), q = (int)(o % CRS);
     const int c = q / RS, r = (q % RS) / g.S - g.ph, s = (q % RS) % g.S - g.pw;
+    constexpr int ES = BF16 ? 2 : 4;
+    using part_t = std::conditional_t<FAR, uint64_t, uint32_t>;
+    const part_t c_at = (part_t)c * (part_t)g.H * (part_t)g.W * ES, hw_at = (part_t)ko * (part_t)k * 4, sum_at = (part_t)ko * 4;
+    auto times = [](int a, int b) { return FAR ? (part_t)a * (part_t)b : (part_t)(uint32_t)__mul24(a, b); };
     const int n_begin = chunk * chunk_n;
     const int n_end = n_begin + chunk_n < g.N ? n_begin + chunk_n : g.N;
     float acc = 0.f, part = 0.f;
-    int n = n_begin, j = 0;                                      // next kept position of the chunk
-    while (n < n_end) {
-        int at[kDeep], img[kDeep];
-        bool last[kDeep];                                        // of its map
-        float share[kDeep], x[kDeep];
+    // the next kept position of the chunk: its image, its map's entries of filter 0, its place among the map's k
+    const char *image = (const char *)X + (long)n_begin * g.C * g.H * g.W * ES;
+    const int32_t *kept = hw + (long)n_begin * g.K * k;
+    const float *sums = sum + (long)n_begin * g.K;
+    const long next_image = (long)g.C * g.H * g.W * ES, next_map = (long)(g.K - 1) * k + 1;
+    long left = (long)(n_end - n_begin) * k;
+    int j = 0;
+    auto batch = [&](auto whole) {                               // of kDeep positions; not whole: the last one is read again
+        constexpr bool WHOLE = decltype(whole)::value;
+        int at[kDeep];
+        const char *img[kDeep];
+        bool valid[kDeep], last[kDeep];                          // last of its map
+        float share[kDeep];
+        uint32_t x[kDeep];                                       // as loaded
 #pragma unroll
         for (int u = 0; u < kDeep; ++u) {
-            img[u] = n;
-            share[u] = 0.f;
-            const long m = (long)(n < n_end ? n : n_end - 1) * g.K + ko;
-            at[u] = hw[m * k + j];
+            valid[u] = WHOLE || u < left;
+            img[u] = image;
+            at[u] = *(const int32_t *)((const char *)kept + hw_at);
             last[u] = j == k - 1;
-            if (last[u]) share[u] = sum[m];
-            if (n < n_end && ++j == k) { j = 0; ++n; }
+            share[u] = 0.f;
+            if (last[u]) share[u] = *(const float *)((const char *)sums + sum_at);
+            if (WHOLE || u + 1 < left) {
+                ++j;
+                if (j == k) { j = 0; image += next_image; sums += g.K; kept += next_map; }
+                else ++kept;
+            }
         }
 #pragma unroll
         for (int u = 0; u < kDeep; ++u) {
-            const int ih = (at[u] >> 16) * g.sh + r, iw = (at[u] & 0xffff) * g.sw + s;
-            const bool inside = img[u] < n_end && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
-            const long plane = ((long)(img[u] < n_end ? img[u] : n_end - 1) * g.C + c) * g.H * g.W;
-            const long xi = plane + (inside ? (long)ih * g.W + iw : 0l);
-            const float v = BF16 ? bf16_bits_to_float(((const uint16_t *)X)[xi]) : ((const float *)X)[xi];
-            x[u] = inside ? v : 0.f;
+            const int ih = (int)times(at[u] >> 16, g.sh) + r, iw = (int)times(at[u] & 0xffff, g.sw) + s;
+            const bool inside = (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+            const part_t xi = c_at + (inside ? times(ih, g.W) + (part_t)iw : 0) * ES;
+            const uint32_t v = BF16 ? *(const uint16_t *)(img[u] + xi) : *(const uint32_t *)(img[u] + xi);
+            x[u] = v & (inside && valid[u] ? ~0u : 0u);          // (a choice of v or 0 becomes a branch, which waits for its load)
         }
         // the same sums in the same order, whatever kDeep: a map's k elements, then their share
 #pragma unroll
         for (int u = 0; u < kDeep; ++u) {
-            part += x[u];
-            if (img[u] < n_end && last[u]) {
+            part += BF16 ? bf16_bits_to_float((uint16_t)x[u]) : __uint_as_float(x[u]);
+            if (valid[u] && last[u]) {
                 acc = fmaf(share[u] * inv_k, part, acc);
                 part = 0.f;
             }
         }
-    }
+        left -= kDeep;
+    };
+    // (the pointers stop at the chunk's last position: a whole batch may end there only if nothing is read after it)
+    while (left >= kDeep) batch(std::true_type{});
+    if (left > 0) batch(std::false_type{});
     out[(long)chunk * g.K * CRS + o] = acc * scale;
 }
 
@@ -413,8 +438,13 @@ int launch_approx_topk(const Geometry &g, const void *X, const void *dY, float *
     const int eblocks = (int)((entries + kBlock - 1) / kBlock);
     const dim3 gg((unsigned)eblocks * (unsigned)nchunk);
     const float gscale = nchunk > 1 ? 1.0f : scale;
-    if (g.bf16) WGRAD_LAUNCH((topk_gather<true>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale, eblocks);
-    else        WGRAD_LAUNCH((topk_gather<false>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale, eblocks);
+    // (kept rows and columns beyond the first bound their stride by the padded plane's side; without any the product is zero)
+    const bool far = (long)g.C * g.H * g.W * (g.bf16 ? 2 : 4) >= (1l << 32) || (long)g.K * k * 4 >= (1l << 32) ||
+                     (long)g.H + 2l * g.ph >= (1l << 23) || (long)g.W + 2l * g.pw >= (1l << 23);
+#define GATHER(BF, FAR) WGRAD_LAUNCH((topk_gather<BF, FAR>), gg, dim3(kBlock), 0, st, X, hw, sum, out, g, k, 1.0f / k, chunk_n, gscale, eblocks)
+    if (g.bf16) { if (far) GATHER(true, true); else GATHER(true, false); }
+    else        { if (far) GATHER(false, true); else GATHER(false, false); }
+#undef GATHER
     rc = launch_status();
     if (rc != WGRAD_OK || nchunk == 1) return rc;
     float *dst[1] = {dW};

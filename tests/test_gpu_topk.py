@@ -84,6 +84,17 @@ def test_topk_order_under_heavy_ties(hw, k, dtype):
     assert np.array_equal(idx[0, 0], np.arange(k)) and idx[0, 1, 0] == Ho * Wo - 1
 
 
+@pytest.mark.parametrize("side", [(1 << 23) - 3, (1 << 23) - 2, 1 << 23])
+@pytest.mark.parametrize("tall", [True, False])
+def test_planes_on_both_sides_of_24_bit_coordinates(side, tall):
+    """The gather's products have 24 bits while a padded plane's side does."""
+    t = (2, 1, side, 1, 3, 3, 1, 512, 1, 1, 0) if tall else (2, 1, 1, side, 3, 1, 3, 1, 512, 0, 1)
+    d = mk(t)
+    X, dY = rand_inputs(d, 77)
+    dY[:, :, -1, -1] = 9.0                                      # kept: the largest coordinate
+    check(d, X, dY, 3, "fp32")
+
+
 def test_k_equal_one_is_algorithm_1():
     import torch
     for t in (SMALL[0], SMALL[4], SMALL[7]):
