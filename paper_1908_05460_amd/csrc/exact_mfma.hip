@@ -620,8 +620,9 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // 60, 87 -> 76, 93 -> 91 us; the fp32 matrix core alone at N = 128 107).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
 // against 14.8).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
-// of its own is what costs (VGG-19, N = 128: 50 us of it against 39); alone that is the faster one (512 -> 512, N = 128:
-// 15.4 us against 24.3).
+// of its own is what costs, and two or more of one shape at a time (with a small layer beside them, N = 64 / 128 / 256: one 23 /
+// 31 / 46 us against 34 / 47 / 62 that way, two 38 / 49 / 76 against 37 / 49 / 73, four 44 / 65 / 104 against 42 / 56 / 84);
+// alone the plain product is the faster one (512 -> 512, N = 128: 15.4 us against 24.3).
 ExactPlan plan_exact(const Geometry &g)
 {
     ExactPlan pl = plan_exact_forms(g, true);
@@ -699,7 +700,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
                  MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq)
 {
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
-    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The

@@ -211,7 +211,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
         // 48 -> 96 @ 27x27, N = 32, where 32x32 tiles would be a third padding besides: 35 against 49).
         double cost = (double)pl.ktiles * pl.ctiles * pl.w_tiles * pl.h_tiles * pl.n_groups * v.nch * v.ntc *
                       (v.sh == 32 ? 4.0 : (gflop < (g.bf16 ? 12.0 : 2.0) ? 0.9 : 1.15));
-        // (ragged bf16 rows are loaded element by element: 64 -> 64 @ 56x56, stride 2, N = 128, 162 us that way, 56 with whole
+        // (ragged bf16 rows are loaded element by element: 64 -> 64 @ 56x56, stride 2, N = 128, 162 us that way, 53 with whole
         // rows and fewer of them to a tile)
         cost *= v.rag ? (v.bf ? (v.sw > 1 ? 2.5 : 1.5) : 1.1) : (v.halo ? 1.02 : 1.0);
         if (cost < best_cost) { best_cost = cost; best = pl; }

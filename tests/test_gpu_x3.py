@@ -237,8 +237,9 @@ def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
     many = [(5, 64 + 16 * i, 17, 17, 64, 3, 3, 1, 1, 1, 1) for i in range(10)]      # ten groups of three
     assert len({plan(t, dtype)[0].variant for t in many}) == 1 and all(plan(t, dtype)[1] == 2 for t in many)
     shapes = EDGES + many * 3 + [(40, 128, 16, 16, 128, 3, 3, 1, 1, 1, 1)] * 3
-    # 2x2 planes that alone are a plain matrix product and in a run are not
-    shapes += [(70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)]
+    # 2x2 planes that alone are a plain matrix product and, two of a shape in a run, are not
+    shapes += [(70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)] * 2
+    shapes += [(66, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1)]           # one of a shape: as alone
     ds = [mk(t, dtype) for t in shapes]
     data = [tuple(to_gpu(a) for a in rand_inputs(d, 100 + i, dtype)) for i, d in enumerate(ds)]
     out = [torch.full((d.K, d.C, d.R, d.S), float("nan"), device="cuda") for d in ds]
@@ -250,8 +251,9 @@ def test_run_of_layers_equals_the_single_calls_to_rounding(dtype):
 
 
 def test_infinities_in_a_run_of_layers():
-    """2x2 planes of whole tiles take the position form in a run only."""
-    shapes = [EDGES[0], EDGES[4], EDGES[19], (70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)]
+    """2x2 planes of whole tiles take the position form in a run only, two or more of a shape."""
+    shapes = [EDGES[0], EDGES[4], EDGES[19]]
+    shapes += [(70, 512, 2, 2, 512, 3, 3, 1, 1, 1, 1), (140, 272, 2, 2, 528, 3, 3, 1, 1, 1, 1)] * 2
     ds = [mk(t) for t in shapes]
     data = [rand_inputs(d, 200 + i) for i, d in enumerate(ds)]
     for X, dY in data:
