@@ -591,6 +591,19 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 {
     const bool strided = g.sw > 1, whole = g.C % 16 == 0 && g.K % 16 == 0;
     if (g.bf16) {
+        // planes of four columns, half of whose chunks are empty: where the bf16 kernel's tiles are at least half full (one image
+        // to a tile: 47, 256 -> 512 @ 4x4: 25 / 36) and its grid is one round of a workgroup per CU with loops of three tiles and
+        // more (100, 256 -> 256: 25 / 21; 40, 512 -> 512: 23 / 15; shorter ones: 54, 64 -> 512 @ 6x4: 16 / 18), or the work is long
+        // (82, 58 -> 512 @ 16x4: 35 / 25); partial sums where the other form has none take a longer loop of that (24, 256 -> 512
+        // @ 8x4: 16 / 20; 28, 152 -> 512 @ 16x4: 28 / 20; 48, 512 -> 512 @ 4x4, two workgroups to a CU: 25 / 28)
+        if (pl.mm16) {
+            const long splits = choose_splits(pl, 1), tiles = (long)pl.n_groups * pl.h_tiles;
+            const bool one_round = pl.ktiles * pl.ctiles * splits <= kNumCU && tiles > 2 * splits;
+            if (g.Wo > 4 || 2 * pl.q < pl.qpad) return false;
+            if (splits == 1) return one_round;
+            if (x3.splits == 1) return one_round && (long)x3.w_tiles * x3.h_tiles * x3.n_groups > 9;
+            return one_round ? gflop > 0.9 || g.Ho <= 4 : gflop >= 2.5;
+        }
         // few channels: long rows, which are staged element by element (249, 3 -> 128 @ 56x56, stride 2: 50 / 35; 12, 3 -> 128
         // @ 112x112: 43 / 33; 67, 7 -> 32 @ 112x112: 108 / 59)
         if (!pl.stream) return false;

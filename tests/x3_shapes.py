@@ -63,6 +63,11 @@ OLDER = [
     ((249, 3, 56, 56, 128, 3, 3, 2, 2, 1, 1), "bf16"),      # 50 / 35
     ((12, 3, 112, 112, 128, 3, 3, 1, 1, 1, 1), "bf16"),     # 43 / 33
     ((67, 7, 112, 112, 32, 3, 3, 1, 1, 1, 1), "bf16"),      # 108 / 59
+    ((100, 256, 4, 4, 256, 3, 3, 1, 1, 1, 1), "bf16"),      # 25 / 21
+    ((40, 512, 4, 4, 512, 3, 3, 1, 1, 1, 1), "bf16"),       # 23 / 15
+    ((28, 152, 16, 4, 512, 3, 3, 1, 1, 1, 1), "bf16"),      # 28 / 20
+    ((82, 58, 16, 4, 512, 3, 3, 1, 1, 1, 1), "bf16"),       # 35 / 25
+    ((90, 256, 4, 4, 512, 3, 3, 1, 1, 1, 1), "bf16"),       # 30 / 26
 ]
 
 
