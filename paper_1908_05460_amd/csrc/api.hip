@@ -373,6 +373,11 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     }
     Bf16Queue *bq = nbf16 > 1 && tune_int("WGRAD_BF16_MULTI", 1) ? bf16_queue_new(sq) : nullptr;
     X3Queue *xq = x3_queue_new();
+    RowsQueue *rq = rows_queue_new();
+    int nrows = 0;
+    for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && (plan[i].ex.rows == 1 || plan[i].ex.rows == 2);
+    for (int i = 0; i < nlayers; ++i)
+        if (method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows == 3 && nrows == 0) plan[i].ex.rows = 0;
     char *ws_next = (char *)ws;
     int rc = WGRAD_OK;
     for (int i = 0; i < nlayers && rc == WGRAD_OK; ++i) {
@@ -392,7 +397,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
                 rounds = rounds < 1 ? 1 : (rounds > 3 ? 3 : rounds);
                 share = (int)(tune_int("WGRAD_MULTI_TOTAL", 768 * rounds) * group_flops(i) / exact_flops + 0.5);
             }
-            rc = launch_exact(g, plan[i].ex, b, ws_next, st, &queue, mq, share < 8 ? 8 : share, bq, xq);
+            rc = launch_exact(g, plan[i].ex, b, ws_next, st, &queue, mq, share < 8 ? 8 : share, bq, xq, rq);
         }
         else if (topk > 0) {
             const int k = layer_topk(g, topk);
@@ -413,6 +418,8 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     }
     if (rc == WGRAD_OK) rc = x3_flush(*xq, st, &queue);
     x3_queue_delete(xq);
+    if (rc == WGRAD_OK) rc = rows_flush(*rq, st, &queue);
+    rows_queue_delete(rq);
     if (rc == WGRAD_OK && mq) rc = multi_flush(multi, st);
     if (bq) {
         if (rc == WGRAD_OK) rc = bf16_flush(*bq, st);

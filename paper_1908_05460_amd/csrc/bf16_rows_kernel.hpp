@@ -1,0 +1,357 @@
+// Filter gradient of bf16 layers (3x3, stride 1, padding 1) on planes of 4x4, 8x8, 16x16 or 32x32, row after row.
+//
+// Rows of the product = output channels, columns = input channels at one filter tap, reduction = positions.  A workgroup
+// owns 64 x 64 channels and a range of images; each of its eight wavefronts 32 x 32 channels and four or five of the nine taps
+// (v_mfma_f32_32x32x16_bf16, 16 accumulators a tap): filter column 0 and the centre, or filter column 2 and the other two of
+// the middle column; a SIMD has one of either.  The wavefront walks down the rows.  A step is one row of
+// sixteen positions per lane: a lane of an operand is (channel, half), its sixteen slots are half a row (W = 32), a row of
+// one image (16), the same row of two images (8) or of four (4), so a group is 1, 2, 4 or 8 images.
+//   - Filter row r of a step pairs the step's row of dY with the row of X one higher or lower, i.e. with registers of the
+//     step before or after: every row of X is read from LDS once by a wavefront and kept for three steps.
+//   - Filter columns 0 and 2 are X shifted by one element (v_alignbit), made once per row; a wavefront needs one of them.
+//   - Rows above and below the plane are not multiplied; columns beside it are zeros that the shift brings in.  (Where dY
+//     holds an infinity or a NaN in its first or last row, whose product with the padding is a NaN: see the end.)
+// So 8 or 10 matrix instructions come with about 13 others.  That ratio is what bounds such a kernel here: measured on this core,
+// a vector instruction between 32x32x16 instructions costs 1.3 clocks of their 36, between 16x16x32 ones 2 of 19 -- they
+// do not run side by side -- and the row-window kernel (exact_bf16_kernel.hpp) has 3.6 of them to each.
+//   - X and dY go to LDS by loads that bypass the registers, four rows (16 KB of each) at a time, the next four while these
+//     are multiplied; one barrier in four steps.  A channel's 16-byte pieces are permuted by its number (XOR), so that the
+//     lanes of an operand read fall on all banks.  Loads past the end of a tensor bring zeros: ragged batches and
+//     channel tiles need nothing else.
+//   - A sum of many products in one register loses more to rounding than the older kernel's many short ones did, so every
+//     kRowsFold blocks the sums are added to a second set of registers.  That is what the split of the taps buys: nine taps of
+//     32 x 32 channels in one wavefront leave no room for it.  (Split into three filter columns and twelve wavefronts the
+//     operands' reads were half again as many, and LDS bound the kernel: 128 -> 128 @ 16x16, N = 512: 44 us against 37.)
+// 38.7 GFLOP alone (64 -> 64 @ 32x32 to 512 -> 512 @ 4x4, N = 512): 36 to 41 us, 9 of them set-up and write-out (the row-window
+// kernel: 44 to 55); VGG-19's run, 395 GFLOP: 320 us, where the card's power, not the kernel's instructions, sets the clock.
+#pragma once
+#include <type_traits>
+
+#include "exact_common.hpp"
+
+namespace wgrad {
+
+typedef __bf16 br_bf8 __attribute__((ext_vector_type(8)));
+typedef float br_f16 __attribute__((ext_vector_type(16)));
+typedef uint32_t br_u2 __attribute__((ext_vector_type(2)));
+typedef uint32_t br_u4 __attribute__((ext_vector_type(4)));
+typedef uint32_t br_u8 __attribute__((ext_vector_type(8)));
+
+constexpr int kRowsTile = 64;                        // channels of a workgroup's tile, each way
+constexpr int kRowsThreads = 512;                    // eight wavefronts: two to a SIMD, one of either kind
+constexpr int kRowsBlock = kRowsTile * 256;          // bytes of four rows of an operand: 256 a channel
+constexpr int kRowsSlot = 2 * kRowsBlock;            // X and dY
+constexpr int kRowsRing = 4;                         // slots: the copies of three blocks are under way while one is multiplied
+constexpr int kRowsPitch = kRowsTile * 9 + 4;        // floats of a row of the result on its way out
+constexpr int kRowsLds = kRowsRing * kRowsSlot > kRowsTile * kRowsPitch * 4 ? kRowsRing * kRowsSlot : kRowsTile * kRowsPitch * 4;
+constexpr int kRowsFold = 4;                         // blocks that a sum runs over before it is added to the rest
+
+struct RowsParams {
+    const void *X[kMaxBatch], *dY[kMaxBatch];
+    float *out[kMaxBatch];                           // dW, or the partials of the batch chunks
+    int N, C, K;
+    int ctiles, ktiles;                              // of 64 channels
+    int chunks, chunk_n;                             // chunk_n: a multiple of the images of a group
+};
+
+// images of a group
+__host__ __device__ constexpr int rows_images(int W) { return 32 / W; }
+
+// 16 bytes a lane from the buffer to LDS at dst + 16 * lane, not waited for.  (The whole offset is the lanes': the range check
+// subtracts a scalar one from the buffer's size, which wraps where it is the larger.)
+__device__ __forceinline__ void rows_copy(br_u4 buf, uint32_t off, uint32_t dst)
+{
+    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(buf) : "memory");
+}
+__device__ __forceinline__ br_u4 rows_buffer(const void *p, uint32_t bytes)
+{
+    const uint64_t a = (uint64_t)p;
+    return br_u4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)),
+                 (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
+}
+
+// S: 0: the wavefront has the taps of filter column 0 and the centre, 2: those of filter column 2 and the rest of column 1
+template <int W, int S>
+__device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int bid, int nblk, int prob)
+{
+    constexpr int GI = rows_images(W), H = W;
+    constexpr int NB = H / 4;                        // blocks of four rows in a plane
+    int lane = threadIdx.x & 63, sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) & 3;
+    asm volatile("" : "+v"(lane), "+s"(sub));        // (nothing of one variant is computed ahead for all of a kernel's)
+    const int i32 = lane & 31, half = lane >> 5;
+    const int kw = sub & 1, cw = sub >> 1;
+    const int logical = xcd_contiguous_id(bid, nblk);
+    const int kt = logical % p.ktiles, rest = logical / p.ktiles, ct = rest % p.ctiles, chunk = rest / p.ctiles;
+    const int k0 = kt * kRowsTile, c0 = ct * kRowsTile;
+    const int n_begin = chunk * p.chunk_n;
+    const int n_end = n_begin + p.chunk_n < p.N ? n_begin + p.chunk_n : p.N;
+    const int C = p.C, K = p.K;
+    const int blocks = (n_end - n_begin + GI - 1) / GI * NB;
+    constexpr uint32_t plane = H * W * 2;
+    const uint32_t ximg = (uint32_t)C * plane, yimg = (uint32_t)K * plane;
+
+    // ---- copies, by the wavefronts of four taps: one moves four channels (1 KB); wavefront `sub` moves channels
+    //      16 sub .. 16 sub + 15 of X and of dY ----
+    constexpr bool COPIES = S == 0;
+    const br_u4 xbuf = rows_buffer((const char *)p.X[prob] + (size_t)n_begin * ximg, (uint32_t)(p.N - n_begin) * ximg);
+    const br_u4 ybuf = rows_buffer((const char *)p.dY[prob] + (size_t)n_begin * yimg, (uint32_t)(p.N - n_begin) * yimg);
+    const uint32_t lds_at = (uint32_t)(uintptr_t)(__attribute__((address_space(3))) char *)smem;
+    auto piece_off = [&](int piece, uint32_t img) {  // of a channel's piece (16 bytes) from the channel's first row
+        if constexpr (W == 32) return (uint32_t)piece * 16;
+        else if constexpr (W == 16) return (uint32_t)(piece >> 3) * img + (piece & 7) * 16;
+        else if constexpr (W == 8) return (uint32_t)(piece >> 2) * img + (piece & 3) * 16;
+        else return (uint32_t)(piece >> 1) * img + (piece & 1) * 16;
+    };
+    const int pc = (lane & 15) ^ (lane >> 4);        // of an even copy; an odd one's channels are 4 (mod 8)
+    const uint32_t xl[2] = {piece_off(pc, ximg) + (lane >> 4) * plane, piece_off(pc ^ 4, ximg) + (lane >> 4) * plane};
+    const uint32_t yl[2] = {piece_off(pc, yimg) + (lane >> 4) * plane, piece_off(pc ^ 4, yimg) + (lane >> 4) * plane};
+    const uint32_t xg0 = (uint32_t)(c0 + 16 * sub) * plane, yg0 = (uint32_t)(k0 + 16 * sub) * plane;
+    uint32_t xg = xg0, yg = yg0;                     // of the block to copy next
+    int copied = 0;
+    auto copy_block = [&](int slot) {
+        if constexpr (COPIES) {
+            const uint32_t at = lds_at + slot * kRowsSlot + 16 * sub * 256;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                rows_copy(xbuf, xl[q & 1] + (xg + 4 * q * plane), at + q * 1024);
+                rows_copy(ybuf, yl[q & 1] + (yg + 4 * q * plane), at + kRowsBlock + q * 1024);
+            }
+            ++copied;
+            const bool wrap = copied % NB == 0;
+            xg += wrap ? GI * ximg - (uint32_t)(NB - 1) * (8 * W) : 8 * W;
+            yg += wrap ? GI * yimg - (uint32_t)(NB - 1) * (8 * W) : 8 * W;
+            if (copied >= blocks) { xg = xg0; yg = yg0; }        // past the last block: the first again, not read
+        }
+    };
+
+    // ---- operand reads: sixteen slots of row s of the block at `base`, by channel ----
+    const uint32_t piece0 = W == 32 ? 2 * half : 8 * half;
+    const uint32_t rd = (uint32_t)i32 * 256 + ((piece0 ^ (i32 & 7)) * 16);
+    auto read_row = [&](uint32_t base, int s) {
+        if constexpr (W == 4) {
+            br_u8 v;
+#pragma unroll
+            for (int q = 0; q < 4; ++q) {
+                const br_u2 u = *(const br_u2 *)(smem + ((rd ^ (uint32_t)(q * 32 + (s >> 1) * 16)) + base + (s & 1) * 8));
+                v[2 * q] = u[0]; v[2 * q + 1] = u[1];
+            }
+            return v;
+        } else {
+            constexpr uint32_t SECOND = W == 8 ? 64 : 16;
+            const uint32_t at = W == 32 ? s * 64 : (W == 16 ? s * 32 : s * 16);
+            const br_u4 u = *(const br_u4 *)(smem + ((rd ^ at) + base)), v = *(const br_u4 *)(smem + ((rd ^ (at ^ SECOND)) + base));
+            return br_u8{u[0], u[1], u[2], u[3], v[0], v[1], v[2], v[3]};
+        }
+    };
+    // W = 32: the word beside the half row, from the other half: right of the first half (S = 2), left of the second (S = 0)
+    const uint32_t rd_side = (uint32_t)i32 * 256 + (((S == 2 ? 2 : 1) ^ (i32 & 7)) * 16) + (S == 2 ? 0 : 12);
+    auto read_side = [&](uint32_t base, int s) -> uint32_t {
+        if constexpr (W == 32) return *(const uint32_t *)(smem + ((rd_side ^ (uint32_t)(s * 64)) + base));
+        else return 0u;
+    };
+    auto mid = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_alignbit(hi, lo, 16); };
+    auto shifted = [&](const br_u8 &v, uint32_t side) {      // the row as filter column S sees it
+        if constexpr (S == 0) {
+            const uint32_t L = W == 32 && half ? side : 0u;
+            if constexpr (W >= 16) return br_u8{mid(L, v[0]), mid(v[0], v[1]), mid(v[1], v[2]), mid(v[2], v[3]), mid(v[3], v[4]), mid(v[4], v[5]), mid(v[5], v[6]), mid(v[6], v[7])};
+            else if constexpr (W == 8) return br_u8{v[0] << 16, mid(v[0], v[1]), mid(v[1], v[2]), mid(v[2], v[3]), v[4] << 16, mid(v[4], v[5]), mid(v[5], v[6]), mid(v[6], v[7])};
+            else return br_u8{v[0] << 16, mid(v[0], v[1]), v[2] << 16, mid(v[2], v[3]), v[4] << 16, mid(v[4], v[5]), v[6] << 16, mid(v[6], v[7])};
+        } else {
+            const uint32_t R = W == 32 && !half ? side : 0u;
+            if constexpr (W >= 16) return br_u8{mid(v[0], v[1]), mid(v[1], v[2]), mid(v[2], v[3]), mid(v[3], v[4]), mid(v[4], v[5]), mid(v[5], v[6]), mid(v[6], v[7]), mid(v[7], R)};
+            else if constexpr (W == 8) return br_u8{mid(v[0], v[1]), mid(v[1], v[2]), mid(v[2], v[3]), v[3] >> 16, mid(v[4], v[5]), mid(v[5], v[6]), mid(v[6], v[7]), v[7] >> 16};
+            else return br_u8{mid(v[0], v[1]), v[1] >> 16, mid(v[2], v[3]), v[3] >> 16, mid(v[4], v[5]), v[5] >> 16, mid(v[6], v[7]), v[7] >> 16};
+        }
+    };
+
+    // sums of the last blocks, and of those before: filter rows 0, 1, 2 of column S, then the centre, or rows 0 and 2 of column 1
+    constexpr int T = S == 0 ? 4 : 5;
+    br_f16 acc[T], sum[T];
+#pragma unroll
+    for (int r = 0; r < T; ++r)
+#pragma unroll
+        for (int i = 0; i < 16; ++i) acc[r][i] = sum[r][i] = 0.f;
+    auto lo = [](const br_u8 &v) { return __builtin_bit_cast(br_bf8, __builtin_shufflevector(v, v, 0, 1, 2, 3)); };
+    auto hi = [](const br_u8 &v) { return __builtin_bit_cast(br_bf8, __builtin_shufflevector(v, v, 4, 5, 6, 7)); };
+    auto first_half = [&](const br_u8 &a, const br_u8 &x, int r) { acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo(a), lo(x), acc[r], 0, 0, 0); };
+    auto second_half = [&](const br_u8 &a, const br_u8 &x, int r) { acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi(a), hi(x), acc[r], 0, 0, 0); };
+
+    // The copies of the next block have landed (those of two more may be under way) and own reads are over; then everyone's.
+    auto meet = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(8 * (kRowsRing - 2)) : "memory"); };
+
+    br_u8 x[3], m[3];                                // row q of the stream of rows is x[q % 3], shifted, and m[q % 3] as it is
+    br_u8 a[2];                                      // and of dY a[q % 2]
+    const uint32_t xbase = (uint32_t)cw * 8192, ybase = kRowsBlock + (uint32_t)kw * 8192;
+    int slot = 0, b = 0, fold = kRowsFold;
+    // One block of four steps.  PH: the number (mod 3) of its first row in the stream; FIRST, LAST: its place in the
+    // plane.  At the start of a step its row of dY and the rows of X up to its own are in registers.
+    auto block = [&](auto ph_c, auto first_c, auto last_c) {
+        constexpr int PH = decltype(ph_c)::value;
+        constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
+        const uint32_t cur = (uint32_t)slot * kRowsSlot, nxt = (uint32_t)((slot + 1) % kRowsRing) * kRowsSlot;
+#pragma unroll
+        for (int s = 0; s < 4; ++s) {
+            const br_u8 &xp = x[(PH + s + 2) % 3], &xc = x[(PH + s) % 3];
+            const br_u8 &mp = m[(PH + s + 2) % 3], &mc = m[(PH + s) % 3];
+            br_u8 &xn = x[(PH + s + 1) % 3], &mn = m[(PH + s + 1) % 3];
+            const br_u8 &ac = a[s & 1];
+            const bool above = !(FIRST && s == 0), below = !(LAST && s == 3);
+            if (s == 3) {
+                meet();                              // the next block is in LDS, this one's last rows are in registers
+                copy_block(slot);
+            }
+            const uint32_t from = s == 3 ? nxt : cur;
+            const br_u8 v = read_row(from + xbase, (s + 1) & 3);
+            const uint32_t side = read_side(from + xbase, (s + 1) & 3);
+            a[(s + 1) & 1] = read_row(from + ybase, (s + 1) & 3);
+            first_half(ac, xc, 1);
+            if (S == 0) first_half(ac, mc, 3);
+            if (above) {
+                first_half(ac, xp, 0);
+                if (S == 2) first_half(ac, mp, 3);
+            }
+            second_half(ac, xc, 1);
+            if (S == 0) second_half(ac, mc, 3);
+            if (above) {
+                second_half(ac, xp, 0);
+                if (S == 2) second_half(ac, mp, 3);
+            }
+            xn = shifted(v, side);
+            mn = v;
+            if (below) {
+                first_half(ac, xn, 2);
+                if (S == 2) first_half(ac, mn, 4);
+                second_half(ac, xn, 2);
+                if (S == 2) second_half(ac, mn, 4);
+            }
+        }
+        slot = (slot + 1) % kRowsRing;
+        ++b;
+    };
+    auto fold_sums = [&]() {
+#pragma unroll
+        for (int r = 0; r < T; ++r) {
+            sum[r] += acc[r];
+#pragma unroll
+            for (int i = 0; i < 16; ++i) acc[r][i] = 0.f;
+        }
+    };
+    typedef std::integral_constant<int, 0> i0;
+    typedef std::integral_constant<int, 1> i1;
+    typedef std::integral_constant<int, 2> i2;
+    typedef std::true_type yes;
+    typedef std::false_type no;
+
+#pragma unroll
+    for (int i = 0; i < kRowsRing; ++i) {
+        copy_block(i);
+        if (i == kRowsRing - 2) meet();
+    }
+    const bool active = c0 + 32 * cw < C;
+    if (!active)                                     // a wavefront without channels only copies
+        for (; b < blocks; ++b, slot = (slot + 1) % kRowsRing) {
+            meet();
+            copy_block(slot);
+        }
+    if (active) {
+    m[0] = read_row(xbase, 0);
+    x[0] = shifted(m[0], read_side(xbase, 0));
+    a[0] = read_row(ybase, 0);
+    // a plane starts with its first row in x[0]; what follows its last row -- the next plane's first -- is moved there
+    while (true) {
+        if constexpr (NB == 1) {
+            block(i0(), yes(), yes());
+            x[0] = x[1]; m[0] = m[1];
+        } else if constexpr (NB == 2) {
+            block(i0(), yes(), no());
+            block(i1(), no(), yes());
+            x[0] = x[2]; m[0] = m[2];
+        } else if constexpr (NB == 4) {
+            block(i0(), yes(), no());
+            block(i1(), no(), no());
+            block(i2(), no(), no());
+            block(i0(), no(), yes());
+            x[0] = x[1]; m[0] = m[1];
+        } else {
+            block(i0(), yes(), no());
+#pragma unroll 1
+            for (int q = 0; q < 2; ++q) {
+                block(i1(), no(), no());
+                block(i2(), no(), no());
+                block(i0(), no(), no());
+                fold_sums();
+            }
+            block(i1(), no(), yes());
+            x[0] = x[2]; m[0] = m[2];
+        }
+        // (before the loop is left: after the test the compiler moves all accumulators through memory)
+        if constexpr (NB == 4) fold_sums();
+        if constexpr (NB < 4)
+            if (b >= fold) { fold = b + kRowsFold; fold_sums(); }
+        if (b == blocks) break;
+    }
+    }
+#pragma unroll
+    for (int r = 0; r < T; ++r) acc[r] += sum[r];
+
+    // An infinity or a NaN of dY reaches the sums of filter row 1.  In the first or last row it also meets the padding,
+    // through filter row 0 or 2, whose sums are NaN then: products that were left out above.
+    bool odd = false;
+#pragma unroll
+    for (int i = 0; i < 16; ++i) odd = odd || !(fabsf(acc[1][i]) < __builtin_inff());
+    if (__any(odd)) {
+        auto special = [](uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; };
+        uint32_t seen = 0;                           // of output channel i32: bit 0: in a first row, bit 1: in a last row
+        for (int n = n_begin + half; n < n_end; n += 2) {
+            const uint32_t *const map = (const uint32_t *)((const char *)p.dY[prob] + (size_t)n * yimg + (size_t)(k0 + 32 * kw + i32) * plane);
+            for (int e = 0; e < W / 2; ++e) seen |= (special(map[e]) ? 1u : 0u) | (special(map[(H - 1) * (W / 2) + e]) ? 2u : 0u);
+        }
+        seen |= __shfl_xor(seen, 32, 64);
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            const uint32_t f = __shfl(seen, 8 * (i >> 2) + 4 * half + (i & 3), 64);
+            if (f & 1) acc[0][i] = __builtin_nanf("");
+            if (f & 2) acc[2][i] = __builtin_nanf("");
+            if (S == 2 && (f & 1)) acc[T - 2][i] = __builtin_nanf("");
+            if (S == 2 && (f & 2)) acc[T - 1][i] = __builtin_nanf("");
+        }
+    }
+
+    // The tile goes out through LDS, as whole rows of 576 values (lane: column i32, rows 8 * (i / 4) + 4 * half + i % 4); the
+    // copies past the end have landed before.
+    asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
+    float *const tile = (float *)smem;
+    if (active) {
+#pragma unroll
+        for (int i = 0; i < 16; ++i) {
+            float *const t = tile + (32 * kw + 8 * (i >> 2) + 4 * half + (i & 3)) * kRowsPitch + (32 * cw + i32) * 9;
+#pragma unroll
+            for (int r = 0; r < 3; ++r) t[3 * r + S] = acc[r][i];
+            if (S == 0) t[4] = acc[3][i];
+            else { t[1] = acc[T - 2][i]; t[7] = acc[T - 1][i]; }
+        }
+    }
+    __syncthreads();
+    float *const out = p.out[prob] + (size_t)chunk * K * C * 9 + ((size_t)k0 * C + c0) * 9;
+    const int width = (C - c0 < kRowsTile ? C - c0 : kRowsTile) * 9;
+    if (C % 4 == 0 && ((uintptr_t)p.out[prob] & 15) == 0) {
+        for (int e = threadIdx.x; e < kRowsTile * (kRowsTile * 9 / 4); e += kRowsThreads) {
+            const int k = e / (kRowsTile * 9 / 4), q = e % (kRowsTile * 9 / 4) * 4;
+            if (q < width) *(float4_t *)(out + (size_t)k * C * 9 + q) = *(const float4_t *)(tile + k * kRowsPitch + q);
+        }
+    } else {
+        for (int e = threadIdx.x; e < kRowsTile * kRowsTile * 9; e += kRowsThreads) {
+            const int k = e / (kRowsTile * 9), q = e % (kRowsTile * 9);
+            if (q < width) out[(size_t)k * C * 9 + q] = tile[k * kRowsPitch + q];
+        }
+    }
+}
+
+template <int W>
+__device__ __forceinline__ void rows_body(const RowsParams &p, char *smem, int bid, int nblk, int prob)
+{
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) == 0) rows_wave<W, 0>(p, smem, bid, nblk, prob);
+    else rows_wave<W, 2>(p, smem, bid, nblk, prob);
+}
+
+}  // namespace wgrad

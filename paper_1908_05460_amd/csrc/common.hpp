@@ -100,6 +100,8 @@ struct ExactPlan {
     int direct;                      // general form: no tile of whole output rows fits the LDS
     int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run of several layers only
     X3Plan x3p;
+    int rows;                        // bf16_rows.hip's form: 0 no, 1 in a run of several exact layers, 2 always, 3 in a run with a layer of 1 or 2
+    int rows_chunks;                 // ... the most batch chunks
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     size_t lds_bytes, ws_bytes;
     bool ok;
@@ -125,6 +127,17 @@ void x3_queue_delete(X3Queue *q);
 int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine);
 int launch_exact_x3(const Geometry &g, const X3Plan &plan, const Batch &b, void *ws, size_t slice_bytes, hipStream_t st,
                     CombineQueue *defer, X3Queue *q);
+// how long n kinds of workgroups, count[i] of them that live life[i], take on so many slots, one kind after the other
+double makespan_us(int slots, const double *life, const long *count, int n);
+// bf16, planes of 4x4, 8x8, 16x16 or 32x32, row after row (bf16_rows.hip)
+bool rows_takes(const Geometry &g);
+int rows_max_chunks(const Geometry &g);
+struct RowsQueue;
+RowsQueue *rows_queue_new();
+void rows_queue_delete(RowsQueue *q);
+int rows_flush(RowsQueue &q, hipStream_t st, CombineQueue *combine);
+int launch_rows(const Geometry &g, const Batch &b, int max_chunks, void *ws, size_t stride, hipStream_t st, CombineQueue *defer,
+                RowsQueue *queue);
 void plan_exact_direct(const Geometry &g, ExactPlan &pl);
 int launch_exact_direct(const Geometry &g, const ExactPlan &pl, const void *X, const void *dY, float *dW, void *ws,
                         hipStream_t st, CombineQueue *defer);
@@ -149,7 +162,7 @@ int launch_exact_bf16_planes(const Geometry &g, const Batch &b, hipStream_t st, 
 struct CombineQueue;
 int launch_exact(const Geometry &g, const ExactPlan &pl, const Batch &b, void *ws, hipStream_t st,
                  CombineQueue *defer = nullptr, MultiQueue *mq = nullptr, int mq_blocks = 0, Bf16Queue *bq = nullptr,
-                 X3Queue *xq = nullptr);
+                 X3Queue *xq = nullptr, RowsQueue *rq = nullptr);
 int choose_splits(const ExactPlan &pl, int nprob, int want_blocks = 0);
 size_t exact_ws_per_problem(const Geometry &g, const ExactPlan &pl);
 

@@ -636,7 +636,7 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // of its own is what costs, and two or more of one shape at a time (with a small layer beside them, N = 64 / 128 / 256: one 23 /
 // 31 / 46 us against 34 / 47 / 62 that way, two 38 / 49 / 76 against 37 / 49 / 73, four 44 / 65 / 104 against 42 / 56 / 84);
 // alone the plain product is the faster one (512 -> 512, N = 128: 15.4 us against 24.3).
-ExactPlan plan_exact(const Geometry &g)
+static ExactPlan plan_exact_x3_or_older(const Geometry &g)
 {
     ExactPlan pl = plan_exact_forms(g, true);
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
@@ -659,6 +659,26 @@ ExactPlan plan_exact(const Geometry &g)
     const size_t need = x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
     if (need > pl.ws_bytes) pl.ws_bytes = need;
     pl.ok = true;
+    return pl;
+}
+
+ExactPlan plan_exact(const Geometry &g)
+{
+    ExactPlan pl = plan_exact_x3_or_older(g);
+    // bf16 on 4x4 to 32x32 planes, row after row: in a run of several layers always, where one launch takes them all (VGG-19
+    // exact, N = 16 / 64 / 160 / 512: 104 / 143 / 211 / 470 us -> 58 / 85 / 154 / 372; under half the masks of a schedule 1.4 to
+    // 1.7 times as fast).  Alone from 9 GFLOP on (38.7 GFLOP, 64 -> 64 @ 32x32 / 128 -> 128 @ 16x16 / 256 -> 256 @ 8x8: 58.6 / 50.8 /
+    // 50.7 -> 46.7 / 42.4 / 42.1; 9.7 GFLOP 27 to 31 -> 25 to 28; shorter ones either way: 64, 128 -> 128 @ 16x16 26.8 -> 24.1, but 25,
+    // 128 -> 128 @ 32x32 26.3 -> 29.0), not on 4x4, whose position-major kernel splits nothing (512 -> 512, N = 512: 29.3
+    // against 43.8).  A first layer of a few channels leaves most of a tile empty (3 -> 64 @ 32x32, N = 512: 21.8 against 33.9): it
+    // joins others where it is short (VGG-19, N = 16 / 64 / 160: 57 / 93 / 156 us with it, 71 / 94 / 162 without; 512: 376 against 361).
+    const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
+    if (rows_takes(g) && (g.C >= 16 || gflop < 1.0)) {
+        pl.rows = g.C < 16 ? 3 : (g.W > 4 && gflop >= 9.0 ? 2 : 1);
+        pl.rows_chunks = rows_max_chunks(g);
+        const size_t need = pl.rows_chunks > 1 ? align_up((size_t)pl.rows_chunks * g.dw_elems() * 4) : 0;
+        if (need > pl.ws_bytes) pl.ws_bytes = need;
+    }
     return pl;
 }
 
@@ -710,8 +730,10 @@ static int launch_exact_staged(const Geometry &g, const ExactPlan &pl, const voi
                                void *ws, hipStream_t st, CombineQueue *defer);
 
 int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void *ws, hipStream_t st, CombineQueue *defer,
-                 MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq)
+                 MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq, RowsQueue *rq)
 {
+    if ((plan.rows == 2 || (plan.rows != 0 && mq)) && batch_aligned(g, b, 8, 8))
+        return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
     if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums

@@ -118,7 +118,7 @@ constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and 
 
 // How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of
 // workgroups, `count` of each, `life` us long, sorted by falling life.
-static double x3_makespan(int slots, const double *life, const long *count, int n)
+double makespan_us(int slots, const double *life, const long *count, int n)
 {
     struct { double at; long n; } free_at[64];
     int used = 1;
@@ -172,7 +172,7 @@ static int x3_choose_splits(const Geometry &g, const X3Plan &pl, int nprob)
         const long s = (tiles + per - 1) / per, n = outs * s;
         double life = kX3Fixed + per * t;
         if (n <= kNumCU) life = kX3Fixed + per * x3_tile_us(v, 1);      // a CU to itself
-        const double cost = x3_makespan(slots, &life, &n, 1) + (s > 1 ? 2.0 : 0.0) + x3_partial_us(g, s, nprob);
+        const double cost = makespan_us(slots, &life, &n, 1) + (s > 1 ? 2.0 : 0.0) + x3_partial_us(g, s, nprob);
         if (cost < best_cost) { best_cost = cost; best = (int)s; }
     }
     return best;
@@ -335,7 +335,7 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
                 sorted[j] = life[i];
                 count[j] = s * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n;
             }
-            const double cost = x3_makespan(slots, sorted, count, n) + partial;
+            const double cost = makespan_us(slots, sorted, count, n) + partial;
             if (cost < best_cost) {
                 best_cost = cost;
                 std::copy(now, now + n, best);

@@ -1,0 +1,72 @@
+"""bf16 layers row after row (4x4 to 32x32 planes): edges of its tiles, groups of images and batch chunks, in runs of several
+layers (which take it whatever their size) and alone, against the oracle on every dW entry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1908_05460_amd import binding as B
+from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+# (N, C, HW, K): a group is 32 / HW images and a tile 64 channels; a second tile of 1, 32, 33 or 36 channels, batches that end
+# within a group, one image, and (with 64 channels on a side and many images) several chunks of several blocks each
+SHAPES = [(1, 16, 4, 64), (9, 65, 4, 64), (67, 64, 4, 128), (300, 100, 4, 64),
+          (1, 20, 8, 64), (6, 97, 8, 64), (43, 64, 8, 192), (150, 36, 8, 64),
+          (1, 64, 16, 64), (5, 100, 16, 64), (38, 128, 16, 64), (90, 17, 16, 128),
+          (1, 33, 32, 64), (4, 64, 32, 128), (21, 40, 32, 64), (60, 64, 32, 64)]
+
+
+def desc(t):
+    N, C, HW, K = t
+    return B.desc(N, C, HW, HW, K, R=3, S=3, pad=1, dtype=B.BF16)
+
+
+def run_exact(ds, data):
+    import torch
+    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
+    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
+    mask = np.full(len(ds), B.EXACT, np.uint8)
+    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)))
+    torch.cuda.synchronize()
+    return [o.cpu().numpy() for o in out]
+
+
+@pytest.mark.parametrize("hw", [4, 8, 16, 32])
+def test_runs_match_the_oracle(hw):
+    """All shapes of one plane size in one launch, two layers of the first."""
+    shapes = [t for t in SHAPES if t[2] == hw]
+    ds = [desc(t) for t in [shapes[0]] + shapes]
+    data = [rand_inputs(d, 40 + i, "bf16") for i, d in enumerate(ds)]
+    for d, (X, dY), got in zip(ds, data, run_exact(ds, data)):
+        # fp32 sums of exact products
+        assert normwise_err(got, oracle.wgrad_exact(oracle_shape(d), X, dY)) < TOL["fp32"] / 50
+
+
+def test_alone_matches_the_oracle():
+    """From 9 GFLOP on a layer takes the form alone; the last batch chunk is shorter than the others."""
+    d = desc((131, 128, 16, 128))
+    X, dY = rand_inputs(d, 3, "bf16")
+    got = B.conv_wgrad_exact(d, to_gpu(X), to_gpu(dY)).cpu().numpy()
+    assert normwise_err(got, oracle.wgrad_exact(oracle_shape(d), X, dY)) < TOL["fp32"] / 50
+
+
+@pytest.mark.parametrize("where", ["X", "dY"])
+@pytest.mark.parametrize("bad", [0x7F80, 0xFF80, 0x7FC0])
+def test_infinities_and_nans(where, bad):
+    """Rows above and below a plane are not multiplied, and an infinity or a NaN of dY beside them makes NaNs of the
+    padding's zeros all the same; one of X reaches only what sees it."""
+    ds = [desc(t) for t in ((9, 33, 4, 64), (5, 33, 8, 64), (3, 33, 16, 64), (2, 33, 32, 64))]
+    data = []
+    for d in ds:
+        X, dY = rand_inputs(d, 7, "bf16")
+        a = X if where == "X" else dY
+        for at in ((0, 0, 0, 0), (-1, -1, -1, -1), (0, 1, 0, a.shape[3] // 2), (-1, 2, a.shape[2] // 2, 0)):
+            a[at] = bad
+        data.append((X, dY))
+    for d, (X, dY), got in zip(ds, data, run_exact(ds, data)):
+        with np.errstate(all="ignore"):
+            want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+        fine = np.isfinite(want)
+        assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+        assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / 50
