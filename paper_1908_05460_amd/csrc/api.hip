@@ -374,6 +374,9 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     Bf16Queue *bq = nbf16 > 1 && tune_int("WGRAD_BF16_MULTI", 1) ? bf16_queue_new(sq) : nullptr;
     X3Queue *xq = x3_queue_new();
     RowsQueue *rq = rows_queue_new();
+    RegsQueue *rgq = regs_queue_new();
+    int nregs4 = 0;                  // groups on 4x4 planes that the form of planes in registers takes
+    for (int i = 0; i < nlayers; ++i) nregs4 += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.regs == 1 && plan[i].g.H == 4;
     int nrows = 0;
     for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && (plan[i].ex.rows == 1 || plan[i].ex.rows == 2);
     for (int i = 0; i < nlayers; ++i)
@@ -410,12 +413,15 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
             ws_next += slice * b.n;
             continue;
         }
-        else rc = launch_approx(g, plan[i].ap, b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq);
+        else rc = launch_approx(g, plan[i].ap, b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq,
+                                plan[i].ap.regs == 2 && nregs4 == 0 ? nullptr : rgq);
         ws_next += align_up(plan[i].ws) * b.n;
     }
     if (sq) {
         if (rc == WGRAD_OK) rc = select_flush(*sq, st);
     }
+    if (rc == WGRAD_OK) rc = regs_flush(*rgq, st, &queue);
+    regs_queue_delete(rgq);
     if (rc == WGRAD_OK) rc = x3_flush(*xq, st, &queue);
     x3_queue_delete(xq);
     if (rc == WGRAD_OK) rc = rows_flush(*rq, st, &queue);

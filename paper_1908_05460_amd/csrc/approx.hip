@@ -95,6 +95,7 @@ struct ApproxBatch {
     int32_t *hw[kMaxBatch];      // packed (row << 16 | col) of every map
     float *sum[kMaxBatch];       // signed sum of every map
     float *out[kMaxBatch];       // dW, or the batch-chunk partials
+    int hw_row = 65536, hw_col = 1, hw_base = 0;   // hw = row * hw_row + col * hw_col + hw_base, for a consumer that wants another form
 };
 
 // (bx, by): the workgroup's number within its problem, and the problem
@@ -151,7 +152,7 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
     if (map < maps && gl == 0) {
         const int32_t pos = (int32_t)~(uint32_t)packed;
         if (flat_out) flat_out[map] = pos;
-        if (hw_out) hw_out[map] = ((pos / Wo) << 16) | (pos % Wo);   // (row, col), for the gather
+        if (hw_out) hw_out[map] = __mul24(pos / Wo, ab.hw_row) + __mul24(pos % Wo, ab.hw_col) + ab.hw_base;   // for the gather
         if (sum_a) sum_a[map] = sum;
         if (sum_b) sum_b[map] = sum;
     }
@@ -1432,11 +1433,26 @@ int fused_flush(FusedQueue &q, hipStream_t st)
 #define WGRAD_GATHER_BLOCKS 512
 #endif
 
-ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool allow_mm)
+ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool allow_mm, bool allow_regs)
 {
     ApproxPlan pl{};
     const long outs = g.dw_elems();
     const int HW = g.H * g.W;
+    if (allow_regs && allow_lds && allow_fused && allow_mm && regs_takes(g)) {
+        // (tensors that are not 16-byte aligned take the form below: the workspace is that one's, and the batch is not
+        // cut into more chunks than it holds)
+        const ApproxPlan alt = plan_approx(g, true, true, true, false);
+        pl.regs = g.H == 2 ? 2 : 1;
+        size_t off = 0;
+        pl.off_idx = off; off += align_up((size_t)g.N * g.K * 4);
+        pl.off_sum = off; off += align_up((size_t)g.N * g.K * 4);
+        pl.off_part = off;
+        const size_t room = alt.ws_bytes > off ? (alt.ws_bytes - off) / ((size_t)outs * 4) : 0;
+        pl.chunks = regs_max_chunks(g, room < 2 ? 1 : (int)std::min<size_t>(room, 64));
+        pl.chunk_n = (g.N + pl.chunks - 1) / pl.chunks;
+        pl.ws_bytes = std::max(alt.ws_bytes, off);
+        return pl;
+    }
     // bf16 inputs, shapes the bf16 matrix-core kernel takes: the approximated gradient is the exact
     // one of the sparsified dY (Section 2.4), and contracting that on the matrix core -- the operand
     // built in registers from each map's selected position and sum -- outruns any gather from LDS
@@ -1709,14 +1725,17 @@ bool topk_gather_lds(const Geometry &g, const void *X, const int32_t *hw, const 
 
 int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, float scale,
                   int32_t *idx_out, float *sum_out, void *ws, hipStream_t st, CombineQueue *defer, FusedQueue *fq,
-                  Bf16Queue *bq, GatherQueue *gq, SelectQueue *sq)
+                  Bf16Queue *bq, GatherQueue *gq, SelectQueue *sq, RegsQueue *rgq)
 {
     // a queued launch needs its reduction queued behind it: without a reduction queue nothing is queued
-    if (!defer) { gq = nullptr; fq = nullptr; bq = nullptr; sq = nullptr; }
+    if (!defer) { gq = nullptr; fq = nullptr; bq = nullptr; sq = nullptr; rgq = nullptr; }
     bool aligned = true;
     for (int i = 0; i < b.n; ++i)
         aligned = aligned && ((uintptr_t)b.X[i] % (g.bf16 ? 8 : 16)) == 0 && ((uintptr_t)b.dY[i] % (g.bf16 ? 8 : 16)) == 0;
-    ApproxPlan pl = ((plan.use_lds || plan.fused || plan.mm) && !aligned) ? plan_approx(g, false, false, false) : plan;   // (the sparsified form has no alignment needs: the exact launcher falls back by itself)
+    // 2x2 planes: too little work to fill the chip with an image after the other (512 -> 512, N = 128, alone: 35 us against 21 of
+    // the sparsified form; four such layers 44 against 49), but beside layers on 4x4 planes they take 5 us each
+    ApproxPlan pl = (plan.regs && !aligned) || (plan.regs == 2 && !rgq) ? plan_approx(g, true, true, true, false) : plan;
+    if ((pl.use_lds || pl.fused || pl.mm) && !aligned) pl = plan_approx(g, false, false, false);   // (the sparsified form has no alignment needs: the exact launcher falls back by itself)
     const long outs = g.dw_elems();
     if (pl.use_lds && (b.n > 1 || gq)) {
         // the workgroup target is for the whole launch: a batch of layers chunks each layer's images less finely
@@ -1762,6 +1781,18 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     }
     const float kscale = pl.chunks > 1 ? 1.0f : scale;
     int rc;
+    if (pl.regs) {
+        if (rgq && regs_full(*rgq)) {
+            rc = sq ? select_flush(*sq, st) : WGRAD_OK;
+            if (rc == WGRAD_OK) rc = regs_flush(*rgq, st, defer);
+            if (rc != WGRAD_OK) return rc;
+        }
+        const RegsPosition at = regs_position(g);
+        ab.hw_row = at.row; ab.hw_col = at.col; ab.hw_base = at.base;
+        rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rgq ? sq : nullptr);
+        if (rc != WGRAD_OK) return rc;
+        return launch_regs(g, b, ab.hw, ab.sum, pl.chunks, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
+    }
     if (pl.sx) {
         // the group's workspace (b.n slices of plan.ws_bytes, contiguous) is cut anew: the sparsified tensors of
         // all problems first, then one region for the exact kernel's partials of the whole batch

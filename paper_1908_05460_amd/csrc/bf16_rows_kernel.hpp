@@ -28,13 +28,13 @@
 #include <type_traits>
 
 #include "exact_common.hpp"
+#include "lds_copy.hpp"
 
 namespace wgrad {
 
 typedef __bf16 br_bf8 __attribute__((ext_vector_type(8)));
 typedef float br_f16 __attribute__((ext_vector_type(16)));
 typedef uint32_t br_u2 __attribute__((ext_vector_type(2)));
-typedef uint32_t br_u4 __attribute__((ext_vector_type(4)));
 typedef uint32_t br_u8 __attribute__((ext_vector_type(8)));
 
 constexpr int kRowsTile = 64;                        // channels of a workgroup's tile, each way
@@ -56,19 +56,6 @@ struct RowsParams {
 
 // images of a group
 __host__ __device__ constexpr int rows_images(int W) { return 32 / W; }
-
-// 16 bytes a lane from the buffer to LDS at dst + 16 * lane, not waited for.  (The whole offset is the lanes': the range check
-// subtracts a scalar one from the buffer's size, which wraps where it is the larger.)
-__device__ __forceinline__ void rows_copy(br_u4 buf, uint32_t off, uint32_t dst)
-{
-    asm volatile("s_mov_b32 m0, %0\n\ts_nop 0\n\tbuffer_load_dwordx4 %1, %2, 0 offen lds" ::"s"(dst), "v"(off), "s"(buf) : "memory");
-}
-__device__ __forceinline__ br_u4 rows_buffer(const void *p, uint32_t bytes)
-{
-    const uint64_t a = (uint64_t)p;
-    return br_u4{(uint32_t)__builtin_amdgcn_readfirstlane((int)(uint32_t)a), (uint32_t)__builtin_amdgcn_readfirstlane((int)((uint32_t)(a >> 32) & 0xffffu)),
-                 (uint32_t)__builtin_amdgcn_readfirstlane((int)bytes), 0x00020000u};
-}
 
 // S: 0: the wavefront has the taps of filter column 0 and the centre, 2: those of filter column 2 and the rest of column 1
 template <int W, int S>

@@ -170,13 +170,15 @@ struct ApproxPlan {
     int chunks, chunk_n;             // batch chunks whose partial sums are combined afterwards
     int use_lds, fused, m, nb, pitch, wp, ctiles, ktiles;   // LDS form of the gather: tile shape
     int mm;                          // contraction on the bf16 matrix core from the selection results
+    int regs;                        // fp32, planes held in registers (approx_regs.hip): 0 no, 1 always, 2 in a run beside layers on 4x4 planes
     int sx;                          // fp32, planes of up to four positions: exact kernel on the sparsified dY
     ExactPlan ex;                    // its plan
     size_t off_idx, off_sum, off_part, off_sparse, ws_bytes;
 };
-ApproxPlan plan_approx(const Geometry &g, bool allow_lds = true, bool allow_fused = true, bool allow_mm = true);
+ApproxPlan plan_approx(const Geometry &g, bool allow_lds = true, bool allow_fused = true, bool allow_mm = true, bool allow_regs = true);
 struct FusedQueue;
 struct GatherQueue;
+struct RegsQueue;
 // selections of several layer groups collected for one launch; the queues of their consumers (the LDS gathers, the
 // sparse-operand launches of the bf16 matrix-core kernel) issue it before they issue themselves
 struct SelectQueue;
@@ -187,7 +189,19 @@ int launch_select(const Geometry &g, const void *dY, int32_t *idx, float *sum, h
 int launch_approx(const Geometry &g, const ApproxPlan &pl, const Batch &b, float scale,
                   int32_t *idx_out, float *sum_out, void *ws, hipStream_t st, CombineQueue *defer = nullptr,
                   FusedQueue *fq = nullptr, Bf16Queue *bq = nullptr, GatherQueue *gq = nullptr,
-                  SelectQueue *sq = nullptr);
+                  SelectQueue *sq = nullptr, RegsQueue *rgq = nullptr);
+// approximated fp32 layers on 8x8, 4x4 and 2x2 planes (approx_regs.hip); a map's position as the kernel reads it is
+// row * its row + col * its col + its base
+struct RegsPosition { int row, col, base; };
+bool regs_takes(const Geometry &g);
+RegsPosition regs_position(const Geometry &g);
+int regs_max_chunks(const Geometry &g, int cap);
+RegsQueue *regs_queue_new();
+void regs_queue_delete(RegsQueue *q);
+bool regs_full(const RegsQueue &q);
+int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine);
+int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, float scale,
+                void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue);
 // LDS-form gathers of several layer groups, collected for one launch
 GatherQueue *gather_queue_new(SelectQueue *selects = nullptr);
 void gather_queue_delete(GatherQueue *q);

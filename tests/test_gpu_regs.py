@@ -1,0 +1,80 @@
+"""Approximated fp32 layers on 8x8, 4x4 and 2x2 planes, whose planes lie in registers: tiles of four and of eight wavefronts, one image,
+stages that end early, batch chunks, strides, alone and in runs, against the oracle on every dW entry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1908_05460_amd import binding as B
+from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
+
+pytestmark = pytest.mark.gpu
+
+# (N, C, HW, K, stride): a stage is 2 images of 8x8 planes, 4 of 4x4 or 16 of 2x2 ones; K = 160 has no whole tile of eight wavefronts
+SHAPES = [(1, 64, 4, 128, 1), (5, 64, 4, 160, 1), (16, 128, 4, 128, 2), (67, 192, 4, 256, 1), (128, 64, 4, 128, 1),
+          (1, 64, 2, 128, 1), (17, 64, 2, 160, 1), (33, 128, 2, 128, 2), (70, 192, 2, 256, 1),
+          (1, 64, 8, 128, 1), (5, 64, 8, 160, 1), (16, 128, 8, 128, 2), (43, 192, 8, 256, 1), (128, 64, 8, 128, 1)]
+BOUND = TOL["fp32"] / 50        # fp32 sums of up to 128 products
+
+
+def desc(t):
+    N, C, HW, K, stride = t
+    return B.desc(N, C, HW, HW, K, R=3, S=3, stride=stride, pad=1)
+
+
+def run_approx(ds, data):
+    import torch
+    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
+    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
+    mask = np.full(len(ds), B.APPROX, np.uint8)
+    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)), scale=0.25)
+    torch.cuda.synchronize()
+    return [o.cpu().numpy() for o in out]
+
+
+@pytest.mark.parametrize("t", SHAPES)
+def test_alone_matches_the_oracle(t):
+    import torch
+    d = desc(t)
+    X, dY = rand_inputs(d, 5)
+    want, want_idx, _ = oracle.wgrad_approx(oracle_shape(d), X, dY)
+    idx = torch.full((d.N, d.K), -1, dtype=torch.int32, device="cuda")
+    got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY), idx_out=idx).cpu().numpy()
+    assert normwise_err(got, want) < BOUND
+    assert np.array_equal(idx.cpu().numpy(), want_idx)
+
+
+@pytest.mark.parametrize("shapes", [SHAPES, [SHAPES[4], SHAPES[8], SHAPES[4]], [SHAPES[3]] * 9 + SHAPES])
+def test_runs_match_the_oracle(shapes):
+    """Several shapes and layers of one shape in one launch, more groups than a launch carries.  (2x2 planes take the form beside
+    4x4 ones only.)"""
+    ds = [desc(t) for t in shapes]
+    data = [rand_inputs(d, 60 + i) for i, d in enumerate(ds)]
+    for d, (X, dY), got in zip(ds, data, run_approx(ds, data)):
+        assert normwise_err(got * 4, oracle.wgrad_approx(oracle_shape(d), X, dY)[0]) < BOUND
+
+
+@pytest.mark.parametrize("hw", [2, 4, 8])
+def test_unaligned_tensors(hw):
+    """A tensor that does not begin at a multiple of 16 bytes takes another form, in the same workspace."""
+    import torch
+    d = desc((9, 64, hw, 128, 1))
+    X, dY = rand_inputs(d, 8)
+    buf = torch.zeros(X.size + 1, device="cuda")
+    buf[1:] = to_gpu(X).flatten()
+    got = B.conv_wgrad_approx(d, buf[1:].view(X.shape), to_gpu(dY)).cpu().numpy()
+    assert normwise_err(got, oracle.wgrad_approx(oracle_shape(d), X, dY)[0]) < BOUND
+
+
+@pytest.mark.parametrize("hw", [2, 4, 8])
+def test_infinities(hw):
+    """An infinity of X reaches only the taps whose kept position sees it."""
+    ds = [desc((6, 64, hw, 128, 1)), desc((7, 64, 4, 128, 1))]
+    data = [rand_inputs(d, 9) for d in ds]
+    data[0][0][2, 3, hw - 1, 0] = np.inf
+    data[0][0][5, 60, 0, hw - 1] = -np.inf
+    with np.errstate(all="ignore"):
+        want = oracle.wgrad_approx(oracle_shape(ds[0]), *data[0])[0]
+    got = run_approx(ds, data)[0] * 4
+    fine = np.isfinite(want)
+    assert not fine.all() and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+    assert normwise_err(got[fine], want[fine]) < BOUND
