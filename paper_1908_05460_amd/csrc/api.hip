@@ -374,7 +374,10 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     Bf16Queue *bq = nbf16 > 1 && tune_int("WGRAD_BF16_MULTI", 1) ? bf16_queue_new(sq) : nullptr;
     X3Queue *xq = x3_queue_new();
     RowsQueue *rq = rows_queue_new();
+    RowsQueue *rsq = rows_queue_new_sparse(sq);
     RegsQueue *rgq = regs_queue_new();
+    int nsparse = 0;                 // approximated bf16 groups that go row after row
+    for (int i = 0; i < nlayers; ++i) nsparse += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.rows;
     int nregs4 = 0;                  // groups on 4x4 planes that the form of planes in registers takes
     for (int i = 0; i < nlayers; ++i) nregs4 += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.regs == 1 && plan[i].g.H == 4;
     int nrows = 0;
@@ -414,12 +417,14 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
             continue;
         }
         else rc = launch_approx(g, plan[i].ap, b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq,
-                                plan[i].ap.regs == 2 && nregs4 == 0 ? nullptr : rgq);
+                                plan[i].ap.regs == 2 && nregs4 == 0 ? nullptr : rgq, nsparse == 1 && b.n == 1 ? nullptr : rsq);
         ws_next += align_up(plan[i].ws) * b.n;
     }
     if (sq) {
         if (rc == WGRAD_OK) rc = select_flush(*sq, st);
     }
+    if (rc == WGRAD_OK) rc = rows_flush(*rsq, st, &queue);
+    rows_queue_delete(rsq);
     if (rc == WGRAD_OK) rc = regs_flush(*rgq, st, &queue);
     regs_queue_delete(rgq);
     if (rc == WGRAD_OK) rc = x3_flush(*xq, st, &queue);

@@ -96,6 +96,7 @@ struct ApproxBatch {
     float *sum[kMaxBatch];       // signed sum of every map
     float *out[kMaxBatch];       // dW, or the batch-chunk partials
     int hw_row = 65536, hw_col = 1, hw_base = 0;   // hw = row * hw_row + col * hw_col + hw_base, for a consumer that wants another form
+    int hw_word = 0;             // hw = the sum, rounded to bf16, << 16 | position
 };
 
 // (bx, by): the workgroup's number within its problem, and the problem
@@ -152,7 +153,10 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
     if (map < maps && gl == 0) {
         const int32_t pos = (int32_t)~(uint32_t)packed;
         if (flat_out) flat_out[map] = pos;
-        if (hw_out) hw_out[map] = __mul24(pos / Wo, ab.hw_row) + __mul24(pos % Wo, ab.hw_col) + ab.hw_base;   // for the gather
+        if (hw_out && ab.hw_word) {
+            const uint32_t b = __float_as_uint(sum);
+            hw_out[map] = (int32_t)(((b + 0x7fffu + ((b >> 16) & 1u)) & 0xffff0000u) | (uint32_t)pos);
+        } else if (hw_out) hw_out[map] = __mul24(pos / Wo, ab.hw_row) + __mul24(pos % Wo, ab.hw_col) + ab.hw_base;   // for the gather
         if (sum_a) sum_a[map] = sum;
         if (sum_b) sum_b[map] = sum;
     }
@@ -1471,6 +1475,10 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
             pl.ws_bytes = off;
             const size_t alt = plan_approx(g, false, false, false).ws_bytes;
             if (alt > pl.ws_bytes) pl.ws_bytes = alt;
+            if (rows_takes(g) && tune_int("WGRAD_ROWS_SPARSE", 1)) {
+                pl.rows = 1;
+                pl.rows_chunks = rows_max_chunks(g, true, ex.splits);
+            }
             return pl;
         }
     }
@@ -1725,10 +1733,10 @@ bool topk_gather_lds(const Geometry &g, const void *X, const int32_t *hw, const 
 
 int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, float scale,
                   int32_t *idx_out, float *sum_out, void *ws, hipStream_t st, CombineQueue *defer, FusedQueue *fq,
-                  Bf16Queue *bq, GatherQueue *gq, SelectQueue *sq, RegsQueue *rgq)
+                  Bf16Queue *bq, GatherQueue *gq, SelectQueue *sq, RegsQueue *rgq, RowsQueue *rsq)
 {
     // a queued launch needs its reduction queued behind it: without a reduction queue nothing is queued
-    if (!defer) { gq = nullptr; fq = nullptr; bq = nullptr; sq = nullptr; rgq = nullptr; }
+    if (!defer) { gq = nullptr; fq = nullptr; bq = nullptr; sq = nullptr; rgq = nullptr; rsq = nullptr; }
     bool aligned = true;
     for (int i = 0; i < b.n; ++i)
         aligned = aligned && ((uintptr_t)b.X[i] % (g.bf16 ? 8 : 16)) == 0 && ((uintptr_t)b.dY[i] % (g.bf16 ? 8 : 16)) == 0;
@@ -1814,17 +1822,27 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     }
     bool aligned16 = true;
     for (int i = 0; i < b.n; ++i) aligned16 = aligned16 && ((uintptr_t)b.X[i] % 16) == 0;
-    if (pl.mm && planes_bf16_takes(g) && aligned16 && (!bq || g.H <= tune_int("WGRAD_BF16_PLANES_APPROX_SHARED_HW", 2))) {
-        // 2x2 planes, and 4x4 planes in single calls: the position-major kernel, its A operand built from the
-        // selections; it writes dW itself.  (In a schedule run the selections and the sparse-operand launches of the
-        // layers on 4x4 planes share launches with the other layers', which measured faster than this kernel with a
-        // selection and a launch per group.)
+    // 2x2 planes, and 4x4 planes alone unless the batch is long and the tiles few: the position-major kernel, its A operand built
+    // from the selections; it writes dW itself, a workgroup all images.  (512 -> 512 @ 4x4, N = 512, alone: 36 us, row after row
+    // 52; three such layers in a run 84 against 76; 64 -> 64 30 against 19)
+    const bool few = g.N >= 384 && (g.K / 64) * ((g.C + 63) / 64) <= 4;
+    if (pl.mm && planes_bf16_takes(g) && aligned16 && (g.H <= 2 || (!rsq && !few))) {
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, nullptr);
         if (rc != WGRAD_OK) return rc;
         SparseA sp{};
         for (int i = 0; i < b.n; ++i) { sp.hw[i] = ab.hw[i]; sp.sum[i] = ab.sum[i]; }
         sp.scale = scale;
         return launch_exact_bf16_planes(g, b, st, &sp);
+    }
+    // (a handful of positions alone: 64 -> 64 @ 4x4, N = 4: 14.3 us, 13.6 below)
+    if (pl.mm && pl.rows && (rsq || g.N * g.H * g.W >= 128)) {
+        ab.hw_word = 1;
+        for (int i = 0; i < kMaxBatch; ++i) ab.sum[i] = nullptr;
+        rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rsq ? sq : nullptr);   // (a queued consumer issues queued selections first)
+        if (rc != WGRAD_OK) return rc;
+        Batch mb = b;
+        for (int i = 0; i < b.n; ++i) mb.dY[i] = ab.hw[i];
+        return launch_rows_sparse(g, mb, scale, pl.rows_chunks, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rsq);
     }
     if (pl.mm) {
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, bq ? sq : nullptr);   // (a queued consumer issues queued selections first)

@@ -19,9 +19,9 @@ struct RowsMulti {
 static_assert(sizeof(RowsMulti) <= 4096, "kernel arguments");
 
 // The groups of a run as one grid: a workgroup looks its group up in the kernel arguments, read in place.
-__global__ __launch_bounds__(kRowsThreads, 2) void wgrad_bf16_rows(const RowsMulti)
+template <bool SPARSE>
+__device__ __forceinline__ void rows_group(char *rows_smem)
 {
-    extern __shared__ char rows_smem[];
     const RowsMulti *mp = (const RowsMulti *)__builtin_amdgcn_kernarg_segment_ptr();
     const int n = mp->n;
     int gi = 0;
@@ -30,11 +30,24 @@ __global__ __launch_bounds__(kRowsThreads, 2) void wgrad_bf16_rows(const RowsMul
     if (prob >= mp->nprob[gi]) return;
     const RowsParams &p = mp->p[gi];
     switch (mp->W[gi]) {
-        case 4: rows_body<4>(p, rows_smem, bid - prob * per, per, prob); break;
-        case 8: rows_body<8>(p, rows_smem, bid - prob * per, per, prob); break;
-        case 16: rows_body<16>(p, rows_smem, bid - prob * per, per, prob); break;
-        default: rows_body<32>(p, rows_smem, bid - prob * per, per, prob); break;
+        case 4: rows_body<4, SPARSE>(p, rows_smem, bid - prob * per, per, prob); break;
+        case 8: rows_body<8, SPARSE>(p, rows_smem, bid - prob * per, per, prob); break;
+        case 16: rows_body<16, SPARSE>(p, rows_smem, bid - prob * per, per, prob); break;
+        default:
+            if constexpr (!SPARSE) rows_body<32, SPARSE>(p, rows_smem, bid - prob * per, per, prob);
+            break;
     }
+}
+__global__ __launch_bounds__(kRowsThreads, 2) void wgrad_bf16_rows(const RowsMulti)
+{
+    extern __shared__ char rows_smem[];
+    rows_group<false>(rows_smem);
+}
+// the approximated gradient, from the selections
+__global__ __launch_bounds__(kRowsThreads, 2) void approx_bf16_rows(const RowsMulti)
+{
+    extern __shared__ char rows_smem[];
+    rows_group<true>(rows_smem);
 }
 
 struct RowsItem {
@@ -45,10 +58,19 @@ struct RowsItem {
     int max_chunks;
 };
 struct RowsQueue {
+    bool sparse = false;             // approximated layers: dY[] of the batches are the maps' words
+    SelectQueue *sel = nullptr;      // selections that must be issued before these launches
+    float scale = 1.0f;
     int n = 0;
     RowsItem item[kRowsMultiMax];
 };
 RowsQueue *rows_queue_new() { return new RowsQueue; }
+RowsQueue *rows_queue_new_sparse(SelectQueue *selects)
+{
+    RowsQueue *q = new RowsQueue;
+    q->sparse = true; q->sel = selects;
+    return q;
+}
 void rows_queue_delete(RowsQueue *q) { delete q; }
 
 bool rows_takes(const Geometry &g)
@@ -64,9 +86,9 @@ static int rows_groups(const Geometry &g) { return (g.N + rows_images(g.W) - 1) 
 // How the batches of `n` groups of layers, launched together, are cut: chunks[i] workgroups share the images of every tile
 // of group i.  A workgroup has a CU to itself and takes block_us for each block of four rows; finer cuts fill the CUs more
 // evenly and cost partial results.  life[i]: of a workgroup of group i, as cut.
-static void rows_cut(const RowsItem *const *it, int n, int *chunks, double *life)
+static void rows_cut(const RowsItem *const *it, int n, bool sparse, int *chunks, double *life)
 {
-    const double block_us = tune_int("WGRAD_ROWS_BLOCK_NS", 1600) * 1e-3, fixed_us = 9.0;
+    const double block_us = sparse ? tune_int("WGRAD_ROWS_SPARSE_NS", 900) * 1e-3 : tune_int("WGRAD_ROWS_BLOCK_NS", 1600) * 1e-3, fixed_us = 9.0;
     static const double kShare[] = {1.5, 1.25, 1.1, 1.0, 0.9, 0.8, 0.67, 0.57, 0.5, 0.4, 0.33, 0.25, 0.2};
     double total = 0;
     for (int i = 0; i < n; ++i) total += (double)rows_groups(it[i]->g) * (it[i]->g.H / 4) * rows_tiles(it[i]->g) * it[i]->b.n;
@@ -101,27 +123,31 @@ static void rows_cut(const RowsItem *const *it, int n, int *chunks, double *life
 }
 
 // The most chunks a call may cut a layer into (the workspace holds their partial results): as for the layer alone.
-int rows_max_chunks(const Geometry &g)
+int rows_max_chunks(const Geometry &g, bool sparse, int cap)
 {
     RowsItem I{};
-    I.g = g; I.b.n = 1; I.max_chunks = 1 << 20;
+    I.g = g; I.b.n = 1; I.max_chunks = cap;
     const RowsItem *one = &I;
     int ch;
     double life;
-    rows_cut(&one, 1, &ch, &life);
+    rows_cut(&one, 1, sparse, &ch, &life);
     return ch;
 }
 
 int rows_flush(RowsQueue &q, hipStream_t st, CombineQueue *combine)
 {
     if (q.n == 0) return WGRAD_OK;
+    if (q.sel) {
+        const int rc = select_flush(*q.sel, st);
+        if (rc != WGRAD_OK) return rc;
+    }
     const RowsItem *it[kRowsMultiMax];
     int chunks[kRowsMultiMax];
     for (int i = 0; i < q.n; ++i) it[i] = &q.item[i];
     const int n = q.n;
     q.n = 0;
     double life[kRowsMultiMax];
-    rows_cut(it, n, chunks, life);
+    rows_cut(it, n, q.sparse, chunks, life);
     int order[kRowsMultiMax];                        // longest workgroups first
     for (int i = 0; i < n; ++i) {
         int j = i;
@@ -139,6 +165,7 @@ int rows_flush(RowsQueue &q, hipStream_t st, CombineQueue *combine)
         p.N = g.N; p.C = g.C; p.K = g.K;
         p.ctiles = (g.C + kRowsTile - 1) / kRowsTile; p.ktiles = g.K / kRowsTile;
         p.chunks = ch; p.chunk_n = (groups + ch - 1) / ch * rows_images(g.W);
+        p.scale = ch > 1 ? 1.0f : q.scale;
         for (int j = 0; j < kMaxBatch; ++j) {
             const int k = j < I.b.n ? j : 0;
             p.X[j] = I.b.X[k]; p.dY[j] = I.b.dY[k];
@@ -151,13 +178,14 @@ int rows_flush(RowsQueue &q, hipStream_t st, CombineQueue *combine)
         blocks += (m.per_prob[o] * I.b.n + 7) / 8 * 8;
     }
     m.begin[n] = blocks;
-    if (hipFuncSetAttribute((const void *)wgrad_bf16_rows, hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds) != hipSuccess)
+    if (hipFuncSetAttribute(q.sparse ? (const void *)approx_bf16_rows : (const void *)wgrad_bf16_rows, hipFuncAttributeMaxDynamicSharedMemorySize, kRowsLds) != hipSuccess)
         return WGRAD_LAUNCH_FAILED;
-    WGRAD_LAUNCH(wgrad_bf16_rows, dim3((unsigned)blocks), dim3(kRowsThreads), kRowsLds, st, m);
+    if (q.sparse) WGRAD_LAUNCH(approx_bf16_rows, dim3((unsigned)blocks), dim3(kRowsThreads), kRowsLds, st, m);
+    else WGRAD_LAUNCH(wgrad_bf16_rows, dim3((unsigned)blocks), dim3(kRowsThreads), kRowsLds, st, m);
     int rc = launch_status();
     for (int i = 0; i < n && rc == WGRAD_OK; ++i)
         if (chunks[i] > 1)
-            rc = launch_combine((const float *)it[i]->part, (long)(it[i]->stride / 4), chunks[i], it[i]->g.dw_elems(), 1.0f, it[i]->b.dW,
+            rc = launch_combine((const float *)it[i]->part, (long)(it[i]->stride / 4), chunks[i], it[i]->g.dw_elems(), q.scale, it[i]->b.dW,
                                 it[i]->b.n, st, combine);
     return rc;
 }
@@ -174,6 +202,18 @@ int launch_rows(const Geometry &g, const Batch &b, int max_chunks, void *ws, siz
     }
     q.item[q.n++] = RowsItem{g, b, (char *)ws, stride, max_chunks};
     return queue ? WGRAD_OK : rows_flush(local, st, defer);
+}
+
+// The same for the approximated gradient; b.dY: the maps' words, selected already (or recorded to be, in the queue's selections).
+int launch_rows_sparse(const Geometry &g, const Batch &b, float scale, int max_chunks, void *part, size_t stride, hipStream_t st,
+                       CombineQueue *defer, RowsQueue *queue)
+{
+    RowsQueue local;
+    local.sparse = true;
+    RowsQueue &q = queue ? *queue : local;
+    q.scale = scale;                                 // (one for all layers of a run)
+    const int rc = launch_rows(g, b, max_chunks, part, stride, st, defer, &q);
+    return rc != WGRAD_OK || queue ? rc : rows_flush(local, st, defer);
 }
 
 }  // namespace wgrad

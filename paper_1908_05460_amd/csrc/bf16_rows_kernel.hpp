@@ -24,6 +24,16 @@
 //     operands' reads were half again as many, and LDS bound the kernel: 128 -> 128 @ 16x16, N = 512: 44 us against 37.)
 // 38.7 GFLOP alone (64 -> 64 @ 32x32 to 512 -> 512 @ 4x4, N = 512): 36 to 41 us, 9 of them set-up and write-out (the row-window
 // kernel: 44 to 55); VGG-19's run, 395 GFLOP: 320 us, where the card's power, not the kernel's instructions, sets the clock.
+//
+// SPARSE: the approximated gradient, which is the exact one of a dY with one value in each map (planes of up to 16x16).  That is a
+// structured-sparse operand: of four consecutive positions at most one is not zero, and v_smfmac_f32_32x32x32_bf16
+// contracts 32 such positions in the time of 16 (18.0 ns on a SIMD; two v_mfma_f32_32x32x16_bf16 34 to 38).  dY is not read
+// again: a map is one word, its sum rounded to bf16 and its position, 256 bytes of them an image instead of 64 planes.
+//   - A lane's four groups of four positions lie, by the instruction's layout, in both halves of the lanes' slots of X: groups 0 and
+//     1 in the first half's, 2 and 3 in the second's, each in those 8 * half .. 8 * half + 7 (measured with one-hot operands).
+//   - Each group has the sum in one of two kept places and the position's column as its index; which row and group of four
+//     the position is in decides, by one comparison a group and step, whether it is there or a zero.
+//   - One value a map and image: the sums need no second set of registers.
 #pragma once
 #include <type_traits>
 
@@ -36,6 +46,7 @@ typedef __bf16 br_bf8 __attribute__((ext_vector_type(8)));
 typedef float br_f16 __attribute__((ext_vector_type(16)));
 typedef uint32_t br_u2 __attribute__((ext_vector_type(2)));
 typedef uint32_t br_u8 __attribute__((ext_vector_type(8)));
+typedef __bf16 br_bf16 __attribute__((ext_vector_type(16)));
 
 constexpr int kRowsTile = 64;                        // channels of a workgroup's tile, each way
 constexpr int kRowsThreads = 512;                    // eight wavefronts: two to a SIMD, one of either kind
@@ -46,23 +57,30 @@ constexpr int kRowsPitch = kRowsTile * 9 + 4;        // floats of a row of the r
 constexpr int kRowsLds = kRowsRing * kRowsSlot > kRowsTile * kRowsPitch * 4 ? kRowsRing * kRowsSlot : kRowsTile * kRowsPitch * 4;
 constexpr int kRowsFold = 4;                         // blocks that a sum runs over before it is added to the rest
 
+constexpr int kRowsSparseSlot = kRowsBlock + 4096;   // SPARSE: X, and the maps of up to 16 images, 256 bytes an image
+constexpr int kRowsSparseRing = 6;
+static_assert(kRowsSparseRing * kRowsSparseSlot <= kRowsLds, "LDS");
+
 struct RowsParams {
-    const void *X[kMaxBatch], *dY[kMaxBatch];
+    const void *X[kMaxBatch], *dY[kMaxBatch];        // SPARSE: dY: the maps, [N][K] words: bf16 sum << 16 | position
     float *out[kMaxBatch];                           // dW, or the partials of the batch chunks
     int N, C, K;
     int ctiles, ktiles;                              // of 64 channels
     int chunks, chunk_n;                             // chunk_n: a multiple of the images of a group
+    float scale;                                     // SPARSE: applied when the result is written
 };
 
 // images of a group
 __host__ __device__ constexpr int rows_images(int W) { return 32 / W; }
 
 // S: 0: the wavefront has the taps of filter column 0 and the centre, 2: those of filter column 2 and the rest of column 1
-template <int W, int S>
+template <int W, int S, bool SPARSE>
 __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int bid, int nblk, int prob)
 {
     constexpr int GI = rows_images(W), H = W;
     constexpr int NB = H / 4;                        // blocks of four rows in a plane
+    constexpr int RING = SPARSE ? kRowsSparseRing : kRowsRing, SLOT = SPARSE ? kRowsSparseSlot : kRowsSlot;
+    static_assert(!SPARSE || W <= 16, "a lane has at most four maps, a position's row and group of four 6 bits");
     int lane = threadIdx.x & 63, sub = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6) & 3;
     asm volatile("" : "+v"(lane), "+s"(sub));        // (nothing of one variant is computed ahead for all of a kernel's)
     const int i32 = lane & 31, half = lane >> 5;
@@ -75,7 +93,7 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
     const int C = p.C, K = p.K;
     const int blocks = (n_end - n_begin + GI - 1) / GI * NB;
     constexpr uint32_t plane = H * W * 2;
-    const uint32_t ximg = (uint32_t)C * plane, yimg = (uint32_t)K * plane;
+    const uint32_t ximg = (uint32_t)C * plane, yimg = (uint32_t)K * (SPARSE ? 4u : plane);
 
     // ---- copies, by the wavefronts of four taps: one moves four channels (1 KB); wavefront `sub` moves channels
     //      16 sub .. 16 sub + 15 of X and of dY ----
@@ -89,31 +107,40 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
         else if constexpr (W == 8) return (uint32_t)(piece >> 2) * img + (piece & 3) * 16;
         else return (uint32_t)(piece >> 1) * img + (piece & 1) * 16;
     };
-    const int pc = (lane & 15) ^ (lane >> 4);        // of an even copy; an odd one's channels are 4 (mod 8)
-    const uint32_t xl[2] = {piece_off(pc, ximg) + (lane >> 4) * plane, piece_off(pc ^ 4, ximg) + (lane >> 4) * plane};
-    const uint32_t yl[2] = {piece_off(pc, yimg) + (lane >> 4) * plane, piece_off(pc ^ 4, yimg) + (lane >> 4) * plane};
-    const uint32_t xg0 = (uint32_t)(c0 + 16 * sub) * plane, yg0 = (uint32_t)(k0 + 16 * sub) * plane;
+    uint32_t xl[4], yl[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {                    // the copy's channels are 4q .. 4q + 3 of sixteen
+        const int pc = (lane & 15) ^ (4 * q + (lane >> 4));
+        xl[q] = piece_off(pc, ximg) + (lane >> 4) * plane;
+        yl[q] = piece_off(pc, yimg) + (lane >> 4) * plane;
+    }
+    const uint32_t xg0 = (uint32_t)(c0 + 16 * sub) * plane, yg0 = (uint32_t)(SPARSE ? k0 * 4 : (k0 + 16 * sub) * plane);
+    // SPARSE: the maps of four images; of none past the group: zeros
+    const int mimg = 4 * sub + (lane >> 4);
+    const uint32_t ml = mimg < GI ? (uint32_t)mimg * yimg + (lane & 15) * 16 : 0x80000000u;
     uint32_t xg = xg0, yg = yg0;                     // of the block to copy next
     int copied = 0;
     auto copy_block = [&](int slot) {
         if constexpr (COPIES) {
-            const uint32_t at = lds_at + slot * kRowsSlot + 16 * sub * 256;
+            const uint32_t at = lds_at + slot * SLOT + 16 * sub * 256;
 #pragma unroll
             for (int q = 0; q < 4; ++q) {
-                rows_copy(xbuf, xl[q & 1] + (xg + 4 * q * plane), at + q * 1024);
-                rows_copy(ybuf, yl[q & 1] + (yg + 4 * q * plane), at + kRowsBlock + q * 1024);
+                rows_copy(xbuf, xl[q] + (xg + 4 * q * plane), at + q * 1024);
+                if constexpr (!SPARSE) rows_copy(ybuf, yl[q] + (yg + 4 * q * plane), at + kRowsBlock + q * 1024);
             }
+            if constexpr (SPARSE) rows_copy(ybuf, ml + (mimg < GI ? yg : 0u), lds_at + slot * SLOT + kRowsBlock + sub * 1024);
             ++copied;
             const bool wrap = copied % NB == 0;
             xg += wrap ? GI * ximg - (uint32_t)(NB - 1) * (8 * W) : 8 * W;
-            yg += wrap ? GI * yimg - (uint32_t)(NB - 1) * (8 * W) : 8 * W;
+            if constexpr (SPARSE) yg += wrap ? GI * yimg : 0u;
+            else yg += wrap ? GI * yimg - (uint32_t)(NB - 1) * (8 * W) : 8 * W;
             if (copied >= blocks) { xg = xg0; yg = yg0; }        // past the last block: the first again, not read
         }
     };
 
     // ---- operand reads: sixteen slots of row s of the block at `base`, by channel ----
     const uint32_t piece0 = W == 32 ? 2 * half : 8 * half;
-    const uint32_t rd = (uint32_t)i32 * 256 + ((piece0 ^ (i32 & 7)) * 16);
+    const uint32_t rd = (uint32_t)i32 * 256 + ((piece0 ^ (i32 & 15)) * 16);
     auto read_row = [&](uint32_t base, int s) {
         if constexpr (W == 4) {
             br_u8 v;
@@ -131,7 +158,7 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
         }
     };
     // W = 32: the word beside the half row, from the other half: right of the first half (S = 2), left of the second (S = 0)
-    const uint32_t rd_side = (uint32_t)i32 * 256 + (((S == 2 ? 2 : 1) ^ (i32 & 7)) * 16) + (S == 2 ? 0 : 12);
+    const uint32_t rd_side = (uint32_t)i32 * 256 + (((S == 2 ? 2 : 1) ^ (i32 & 15)) * 16) + (S == 2 ? 0 : 12);
     auto read_side = [&](uint32_t base, int s) -> uint32_t {
         if constexpr (W == 32) return *(const uint32_t *)(smem + ((rd_side ^ (uint32_t)(s * 64)) + base));
         else return 0u;
@@ -153,29 +180,69 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
 
     // sums of the last blocks, and of those before: filter rows 0, 1, 2 of column S, then the centre, or rows 0 and 2 of column 1
     constexpr int T = S == 0 ? 4 : 5;
-    br_f16 acc[T], sum[T];
+    br_f16 acc[T], sum[SPARSE ? 1 : T];
 #pragma unroll
     for (int r = 0; r < T; ++r)
 #pragma unroll
-        for (int i = 0; i < 16; ++i) acc[r][i] = sum[r][i] = 0.f;
+        for (int i = 0; i < 16; ++i) acc[r][i] = sum[SPARSE ? 0 : r][i] = 0.f;
     auto lo = [](const br_u8 &v) { return __builtin_bit_cast(br_bf8, __builtin_shufflevector(v, v, 0, 1, 2, 3)); };
     auto hi = [](const br_u8 &v) { return __builtin_bit_cast(br_bf8, __builtin_shufflevector(v, v, 4, 5, 6, 7)); };
     auto first_half = [&](const br_u8 &a, const br_u8 &x, int r) { acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(lo(a), lo(x), acc[r], 0, 0, 0); };
     auto second_half = [&](const br_u8 &a, const br_u8 &x, int r) { acc[r] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(hi(a), hi(x), acc[r], 0, 0, 0); };
 
+    // SPARSE: the lane's maps of a group of images, and its operand for row `row` of the planes
+    constexpr int MAPS = W == 4 ? 4 : 2;
+    constexpr int PLACES = W == 4 ? 1 : 2;           // groups of four positions of a row that a lane has of a map
+    uint32_t word[MAPS], value[MAPS][PLACES], row_of[MAPS], index = 0;
+    auto read_maps = [&](uint32_t base) {
+#pragma unroll
+        for (int m = 0; m < MAPS; ++m) {
+            const int img = W == 4 ? 4 * (m >> 1) + 2 * half + (m & 1) : (W == 8 ? 2 * m + half : m);
+            word[m] = *(const uint32_t *)(smem + base + kRowsBlock + img * 256 + (32 * kw + i32) * 4);
+        }
+    };
+    auto take_maps = [&]() {
+        index = 0;
+#pragma unroll
+        for (int m = 0; m < MAPS; ++m) {
+            const uint32_t pos = word[m] & 0xffffu, col = pos & 3, v = word[m] & 0xffff0000u;
+            const uint32_t placed = col == 3 ? v : v >> 16;      // in the first kept place, whose index is the column, or the second, whose is 3
+            const uint32_t nibble = col == 3 ? 12u : col | 12u;
+            row_of[m] = pos / W;
+            if constexpr (W == 4) value[m][0] = placed;
+            else
+#pragma unroll
+                for (int j = 0; j < 2; ++j) value[m][j] = ((pos >> 2) & (W / 4 - 1)) == (uint32_t)((W == 16 ? 2 * half : 0) + j) ? placed : 0u;
+            index |= W == 4 ? nibble << (4 * m) : (nibble | nibble << 4) << (8 * m);
+        }
+    };
+    auto operand = [&](int row) {
+        br_u4 a;
+#pragma unroll
+        for (int j = 0; j < 4; ++j) {
+            const int m = j / PLACES;
+            a[j] = row_of[m] == (uint32_t)row ? value[m][j % PLACES] : 0u;
+        }
+        return a;
+    };
+    auto both_halves = [&](const br_u4 &a, const br_u8 &x, int r) {
+        acc[r] = __builtin_amdgcn_smfmac_f32_32x32x32_bf16(__builtin_bit_cast(br_bf8, a), __builtin_bit_cast(br_bf16, x), acc[r], (int)index, 0, 0);
+    };
+
     // The copies of the next block have landed (those of two more may be under way) and own reads are over; then everyone's.
-    auto meet = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"(8 * (kRowsRing - 2)) : "memory"); };
+    auto meet = [&]() { asm volatile("s_waitcnt vmcnt(%0) lgkmcnt(0)\n\ts_barrier" ::"n"((SPARSE ? 5 : 8) * (RING - 2)) : "memory"); };
 
     br_u8 x[3], m[3];                                // row q of the stream of rows is x[q % 3], shifted, and m[q % 3] as it is
     br_u8 a[2];                                      // and of dY a[q % 2]
+    br_u8 ahead;                                     // SPARSE: the row of X after the next step's
     const uint32_t xbase = (uint32_t)cw * 8192, ybase = kRowsBlock + (uint32_t)kw * 8192;
     int slot = 0, b = 0, fold = kRowsFold;
     // One block of four steps.  PH: the number (mod 3) of its first row in the stream; FIRST, LAST: its place in the
     // plane.  At the start of a step its row of dY and the rows of X up to its own are in registers.
-    auto block = [&](auto ph_c, auto first_c, auto last_c) {
-        constexpr int PH = decltype(ph_c)::value;
+    auto block = [&](auto ph_c, auto first_c, auto last_c, auto at_c) {
+        constexpr int PH = decltype(ph_c)::value, AT = decltype(at_c)::value;
         constexpr bool FIRST = decltype(first_c)::value, LAST = decltype(last_c)::value;
-        const uint32_t cur = (uint32_t)slot * kRowsSlot, nxt = (uint32_t)((slot + 1) % kRowsRing) * kRowsSlot;
+        const uint32_t cur = (uint32_t)slot * SLOT, nxt = (uint32_t)((slot + 1) % RING) * SLOT;
 #pragma unroll
         for (int s = 0; s < 4; ++s) {
             const br_u8 &xp = x[(PH + s + 2) % 3], &xc = x[(PH + s) % 3];
@@ -183,6 +250,29 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
             br_u8 &xn = x[(PH + s + 1) % 3], &mn = m[(PH + s + 1) % 3];
             const br_u8 &ac = a[s & 1];
             const bool above = !(FIRST && s == 0), below = !(LAST && s == 3);
+            if constexpr (SPARSE) {
+                const br_u4 sp = operand(4 * AT + s);
+                if (s == 2) {
+                    meet();
+                    copy_block(slot);
+                }
+                const br_u8 after = read_row((s >= 2 ? nxt : cur) + xbase, (s + 2) & 3);       // (two rows ahead: there is room to wait longer)
+                if (LAST && s == 3) read_maps(nxt);
+                both_halves(sp, xc, 1);
+                if (S == 0) both_halves(sp, mc, 3);
+                if (above) {
+                    both_halves(sp, xp, 0);
+                    if (S == 2) both_halves(sp, mp, 3);
+                }
+                xn = shifted(ahead, 0);
+                mn = ahead;
+                if (below) {
+                    both_halves(sp, xn, 2);
+                    if (S == 2) both_halves(sp, mn, 4);
+                }
+                ahead = after;
+                continue;
+            }
             if (s == 3) {
                 meet();                              // the next block is in LDS, this one's last rows are in registers
                 copy_block(slot);
@@ -212,12 +302,13 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
                 if (S == 2) second_half(ac, mn, 4);
             }
         }
-        slot = (slot + 1) % kRowsRing;
+        if constexpr (SPARSE && LAST) take_maps();
+        slot = (slot + 1) % RING;
         ++b;
     };
     auto fold_sums = [&]() {
 #pragma unroll
-        for (int r = 0; r < T; ++r) {
+        for (int r = 0; r < (SPARSE ? 0 : T); ++r) {
             sum[r] += acc[r];
 #pragma unroll
             for (int i = 0; i < 16; ++i) acc[r][i] = 0.f;
@@ -226,60 +317,70 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
     typedef std::integral_constant<int, 0> i0;
     typedef std::integral_constant<int, 1> i1;
     typedef std::integral_constant<int, 2> i2;
+    typedef std::integral_constant<int, 3> i3;
     typedef std::true_type yes;
     typedef std::false_type no;
 
 #pragma unroll
-    for (int i = 0; i < kRowsRing; ++i) {
+    for (int i = 0; i < RING; ++i) {
         copy_block(i);
-        if (i == kRowsRing - 2) meet();
+        if (i == RING - 2) meet();
     }
     const bool active = c0 + 32 * cw < C;
     if (!active)                                     // a wavefront without channels only copies
-        for (; b < blocks; ++b, slot = (slot + 1) % kRowsRing) {
+        for (; b < blocks; ++b, slot = (slot + 1) % RING) {
             meet();
             copy_block(slot);
         }
     if (active) {
     m[0] = read_row(xbase, 0);
     x[0] = shifted(m[0], read_side(xbase, 0));
-    a[0] = read_row(ybase, 0);
+    if constexpr (SPARSE) {
+        read_maps(0);
+        take_maps();
+        ahead = read_row(xbase, 1);
+    } else a[0] = read_row(ybase, 0);
     // a plane starts with its first row in x[0]; what follows its last row -- the next plane's first -- is moved there
     while (true) {
         if constexpr (NB == 1) {
-            block(i0(), yes(), yes());
+            block(i0(), yes(), yes(), i0());
             x[0] = x[1]; m[0] = m[1];
         } else if constexpr (NB == 2) {
-            block(i0(), yes(), no());
-            block(i1(), no(), yes());
+            block(i0(), yes(), no(), i0());
+            block(i1(), no(), yes(), i1());
             x[0] = x[2]; m[0] = m[2];
         } else if constexpr (NB == 4) {
-            block(i0(), yes(), no());
-            block(i1(), no(), no());
-            block(i2(), no(), no());
-            block(i0(), no(), yes());
+            block(i0(), yes(), no(), i0());
+            block(i1(), no(), no(), i1());
+            block(i2(), no(), no(), i2());
+            block(i0(), no(), yes(), i3());
             x[0] = x[1]; m[0] = m[1];
         } else {
-            block(i0(), yes(), no());
+            block(i0(), yes(), no(), i0());
 #pragma unroll 1
             for (int q = 0; q < 2; ++q) {
-                block(i1(), no(), no());
-                block(i2(), no(), no());
-                block(i0(), no(), no());
+                block(i1(), no(), no(), i0());       // (the last argument is for SPARSE alone, which has no such planes)
+                block(i2(), no(), no(), i0());
+                block(i0(), no(), no(), i0());
                 fold_sums();
             }
-            block(i1(), no(), yes());
+            block(i1(), no(), yes(), i0());
             x[0] = x[2]; m[0] = m[2];
         }
         // (before the loop is left: after the test the compiler moves all accumulators through memory)
         if constexpr (NB == 4) fold_sums();
-        if constexpr (NB < 4)
+        if constexpr (NB < 4 && !SPARSE)
             if (b >= fold) { fold = b + kRowsFold; fold_sums(); }
         if (b == blocks) break;
     }
     }
+    if constexpr (SPARSE) {
 #pragma unroll
-    for (int r = 0; r < T; ++r) acc[r] += sum[r];
+        for (int r = 0; r < T; ++r) acc[r] *= p.scale;
+    } else {
+#pragma unroll
+        for (int r = 0; r < T; ++r) acc[r] += sum[r];
+    }
 
     // An infinity or a NaN of dY reaches the sums of filter row 1.  In the first or last row it also meets the padding,
     // through filter row 0 or 2, whose sums are NaN then: products that were left out above.
@@ -290,6 +391,11 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
         auto special = [](uint32_t w) { return (w & 0x7f80u) == 0x7f80u || (w & 0x7f800000u) == 0x7f800000u; };
         uint32_t seen = 0;                           // of output channel i32: bit 0: in a first row, bit 1: in a last row
         for (int n = n_begin + half; n < n_end; n += 2) {
+            if constexpr (SPARSE) {
+                const uint32_t w = *(const uint32_t *)((const char *)p.dY[prob] + (size_t)n * yimg + (size_t)(k0 + 32 * kw + i32) * 4);
+                if ((w & 0x7f800000u) == 0x7f800000u) seen |= ((w & 0xffffu) < W ? 1u : 0u) | ((w & 0xffffu) >= (H - 1) * W ? 2u : 0u);
+                continue;
+            }
             const uint32_t *const map = (const uint32_t *)((const char *)p.dY[prob] + (size_t)n * yimg + (size_t)(k0 + 32 * kw + i32) * plane);
             for (int e = 0; e < W / 2; ++e) seen |= (special(map[e]) ? 1u : 0u) | (special(map[(H - 1) * (W / 2) + e]) ? 2u : 0u);
         }
@@ -334,11 +440,11 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
     }
 }
 
-template <int W>
+template <int W, bool SPARSE>
 __device__ __forceinline__ void rows_body(const RowsParams &p, char *smem, int bid, int nblk, int prob)
 {
-    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) == 0) rows_wave<W, 0>(p, smem, bid, nblk, prob);
-    else rows_wave<W, 2>(p, smem, bid, nblk, prob);
+    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) == 0) rows_wave<W, 0, SPARSE>(p, smem, bid, nblk, prob);
+    else rows_wave<W, 2, SPARSE>(p, smem, bid, nblk, prob);
 }
 
 }  // namespace wgrad

@@ -131,9 +131,13 @@ int launch_exact_x3(const Geometry &g, const X3Plan &plan, const Batch &b, void 
 double makespan_us(int slots, const double *life, const long *count, int n);
 // bf16, planes of 4x4, 8x8, 16x16 or 32x32, row after row (bf16_rows.hip)
 bool rows_takes(const Geometry &g);
-int rows_max_chunks(const Geometry &g);
+int rows_max_chunks(const Geometry &g, bool sparse = false, int cap = 1 << 20);
 struct RowsQueue;
+struct SelectQueue;
 RowsQueue *rows_queue_new();
+RowsQueue *rows_queue_new_sparse(SelectQueue *selects);      // of approximated layers
+int launch_rows_sparse(const Geometry &g, const Batch &b, float scale, int max_chunks, void *part, size_t stride, hipStream_t st,
+                       CombineQueue *defer, RowsQueue *queue);
 void rows_queue_delete(RowsQueue *q);
 int rows_flush(RowsQueue &q, hipStream_t st, CombineQueue *combine);
 int launch_rows(const Geometry &g, const Batch &b, int max_chunks, void *ws, size_t stride, hipStream_t st, CombineQueue *defer,
@@ -169,6 +173,7 @@ size_t exact_ws_per_problem(const Geometry &g, const ExactPlan &pl);
 struct ApproxPlan {
     int chunks, chunk_n;             // batch chunks whose partial sums are combined afterwards
     int use_lds, fused, m, nb, pitch, wp, ctiles, ktiles;   // LDS form of the gather: tile shape
+    int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm), and the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
     int regs;                        // fp32, planes held in registers (approx_regs.hip): 0 no, 1 always, 2 in a run beside layers on 4x4 planes
     int sx;                          // fp32, planes of up to four positions: exact kernel on the sparsified dY
@@ -189,7 +194,7 @@ int launch_select(const Geometry &g, const void *dY, int32_t *idx, float *sum, h
 int launch_approx(const Geometry &g, const ApproxPlan &pl, const Batch &b, float scale,
                   int32_t *idx_out, float *sum_out, void *ws, hipStream_t st, CombineQueue *defer = nullptr,
                   FusedQueue *fq = nullptr, Bf16Queue *bq = nullptr, GatherQueue *gq = nullptr,
-                  SelectQueue *sq = nullptr, RegsQueue *rgq = nullptr);
+                  SelectQueue *sq = nullptr, RegsQueue *rgq = nullptr, RowsQueue *rsq = nullptr);
 // approximated fp32 layers on 8x8, 4x4 and 2x2 planes (approx_regs.hip); a map's position as the kernel reads it is
 // row * its row + col * its col + its base
 struct RegsPosition { int row, col, base; };

@@ -70,3 +70,42 @@ def test_infinities_and_nans(where, bad):
         fine = np.isfinite(want)
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
         assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / 50
+
+
+def rounded_sums(d, idx, sums):
+    """dY as the approximated gradient contracts it: each map's sum, rounded to bf16 (to nearest even), at its position."""
+    b = sums.astype(np.float32).view(np.uint32)
+    out = np.zeros((d.N * d.K, d.Ho * d.Wo), np.uint16)
+    out[np.arange(d.N * d.K), idx.ravel()] = ((b + 0x7FFF + ((b >> 16) & 1)) >> 16).astype(np.uint16).ravel()
+    return out.reshape(d.N, d.K, d.Ho, d.Wo)
+
+
+@pytest.mark.parametrize("t", [t for t in SHAPES if t[2] <= 16] + [(131, 128, 16, 128)])
+def test_approximated_alone(t):
+    import torch
+    d = desc(t)
+    X, dY = rand_inputs(d, 21, "bf16")
+    idx = torch.full((d.N, d.K), -1, dtype=torch.int32, device="cuda")
+    sums = torch.empty((d.N, d.K), device="cuda")
+    got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY), scale=0.5, idx_out=idx, sum_out=sums).cpu().numpy()
+    idx, sums = idx.cpu().numpy(), sums.cpu().numpy()
+    assert np.array_equal(idx, oracle.select(oracle_shape(d), dY)[0])
+    want = oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx, sums)) * 0.5
+    assert normwise_err(got, want) < TOL["fp32"] / 50       # fp32 sums of exact products, whichever form takes the shape
+
+
+def test_approximated_runs():
+    """All shapes in one launch; more groups than one carries."""
+    import torch
+    ds = [desc(t) for t in SHAPES if t[2] <= 16]
+    data = [rand_inputs(d, 80 + i, "bf16") for i, d in enumerate(ds)]
+    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
+    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
+    mask = np.full(len(ds), B.APPROX, np.uint8)
+    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)), scale=0.25)
+    torch.cuda.synchronize()
+    for d, (X, dY), got in zip(ds, data, out):
+        idx, sums = oracle.select(oracle_shape(d), dY)
+        want = oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx, sums)) * 0.25
+        # a sum in 32 bits may round the other way than one in 64: one map's term of N in error by 2^-8
+        assert normwise_err(got.cpu().numpy(), want) < 2.0 ** -8
