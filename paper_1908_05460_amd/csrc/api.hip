@@ -338,7 +338,9 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     // groups that the fp32 multi-shape launch carries (those of the 2x2-plane form add nothing to its shares)
     auto group_flops = [&](int i) {
         const ExactPlan &ex = plan[i].ex;
-        if (ex.plane2 || ex.x3 >= 2) return 0.0;
+        int members = 0;
+        for (int j = i; j < nlayers; ++j) members += group[j] == i;
+        if (ex.plane2 || ex.x3 == 2 || (ex.x3 >= 3 && members > 1)) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
         // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of
@@ -349,8 +351,6 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
         // second workgroup's), so a FLOP takes longer there even with the halo-only taps left out (swept)
         if (ex.wc == 1) w *= tune_int("WGRAD_MULTI_W_WC1", 125) / 100.0;
         if (ex.wc == 2) w *= tune_int("WGRAD_MULTI_W_WC2", 100) / 100.0;
-        int members = 0;
-        for (int j = i; j < nlayers; ++j) members += group[j] == i;
         return w * members;
     };
     if (mq)
@@ -374,12 +374,16 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     Bf16Queue *bq = nbf16 > 1 && tune_int("WGRAD_BF16_MULTI", 1) ? bf16_queue_new(sq) : nullptr;
     X3Queue *xq = x3_queue_new();
     RowsQueue *rq = rows_queue_new();
-    RowsQueue *rsq = rows_queue_new_sparse(sq);
-    RegsQueue *rgq = regs_queue_new();
     int nsparse = 0;                 // approximated bf16 groups that go row after row
     for (int i = 0; i < nlayers; ++i) nsparse += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.rows;
-    int nregs4 = 0;                  // groups on 4x4 planes that the form of planes in registers takes
-    for (int i = 0; i < nlayers; ++i) nregs4 += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.regs == 1 && plan[i].g.H == 4;
+    RowsQueue *rsq = nsparse > 0 ? rows_queue_new_sparse(sq) : nullptr;
+    int nregs = 0, nregs4 = 0;       // groups that the form of planes in registers takes; those on 4x4 planes
+    for (int i = 0; i < nlayers; ++i) {
+        if (topk != 0 || method[i] != WGRAD_APPROX || group[i] != i || !plan[i].ap.regs) continue;
+        ++nregs;
+        nregs4 += plan[i].g.H == 4;
+    }
+    RegsQueue *rgq = nregs > 0 ? regs_queue_new() : nullptr;
     int nrows = 0;
     for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && (plan[i].ex.rows == 1 || plan[i].ex.rows == 2);
     for (int i = 0; i < nlayers; ++i)
@@ -423,10 +427,14 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     if (sq) {
         if (rc == WGRAD_OK) rc = select_flush(*sq, st);
     }
-    if (rc == WGRAD_OK) rc = rows_flush(*rsq, st, &queue);
-    rows_queue_delete(rsq);
-    if (rc == WGRAD_OK) rc = regs_flush(*rgq, st, &queue);
-    regs_queue_delete(rgq);
+    if (rsq) {
+        if (rc == WGRAD_OK) rc = rows_flush(*rsq, st, &queue);
+        rows_queue_delete(rsq);
+    }
+    if (rgq) {
+        if (rc == WGRAD_OK) rc = regs_flush(*rgq, st, &queue);
+        regs_queue_delete(rgq);
+    }
     if (rc == WGRAD_OK) rc = x3_flush(*xq, st, &queue);
     x3_queue_delete(xq);
     if (rc == WGRAD_OK) rc = rows_flush(*rq, st, &queue);

@@ -1453,6 +1453,7 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
         pl.off_part = off;
         const size_t room = alt.ws_bytes > off ? (alt.ws_bytes - off) / ((size_t)outs * 4) : 0;
         pl.chunks = regs_max_chunks(g, room < 2 ? 1 : (int)std::min<size_t>(room, 64));
+        if (g.H == 4 && room >= 2) pl.chunks = std::max(pl.chunks, 2);
         pl.chunk_n = (g.N + pl.chunks - 1) / pl.chunks;
         pl.ws_bytes = std::max(alt.ws_bytes, off);
         return pl;
@@ -1741,7 +1742,7 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     for (int i = 0; i < b.n; ++i)
         aligned = aligned && ((uintptr_t)b.X[i] % (g.bf16 ? 8 : 16)) == 0 && ((uintptr_t)b.dY[i] % (g.bf16 ? 8 : 16)) == 0;
     // 2x2 planes: too little work to fill the chip with an image after the other (512 -> 512, N = 128, alone: 35 us against 21 of
-    // the sparsified form; four such layers 44 against 49), but beside layers on 4x4 planes they take 5 us each
+    // the sparsified form; four such layers 44 against 49), but beside layers on 4x4 planes they take 7 us each
     ApproxPlan pl = (plan.regs && !aligned) || (plan.regs == 2 && !rgq) ? plan_approx(g, true, true, true, false) : plan;
     if ((pl.use_lds || pl.fused || pl.mm) && !aligned) pl = plan_approx(g, false, false, false);   // (the sparsified form has no alignment needs: the exact launcher falls back by itself)
     const long outs = g.dw_elems();
@@ -1799,7 +1800,9 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
         ab.hw_row = at.row; ab.hw_col = at.col; ab.hw_base = at.base;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rgq ? sq : nullptr);
         if (rc != WGRAD_OK) return rc;
-        return launch_regs(g, b, ab.hw, ab.sum, pl.chunks, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
+        // 4x4: a layer alone among its shape goes in two halves, whose shorter sums are closer to 64 bits (256 -> 512, N = 128:
+        // 1.46e-7 against 1.09e-7)
+        return launch_regs(g, b, ab.hw, ab.sum, g.H == 4 && b.n == 1 && g.N > 64 ? std::min(2, pl.chunks) : 1, pl.chunks, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
     }
     if (pl.sx) {
         // the group's workspace (b.n slices of plan.ws_bytes, contiguous) is cut anew: the sparsified tensors of

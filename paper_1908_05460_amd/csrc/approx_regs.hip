@@ -1,21 +1,22 @@
 // Approximated filter gradient of fp32 layers (3x3, padding 1) on 8x8, 4x4 and 2x2 planes: the planes in registers.
 //
 // dW[k][c][tap] = sum over n of sum[n][k] * X[n][c][position(n, k) + tap].  A lane is an input channel and a wavefront eight output
-// channels.  Read from LDS patch by patch, each multiply-add costs an LDS read of its own, two clocks of a CU for each that
+// channels (2x2: four).  Read from LDS patch by patch, each multiply-add costs an LDS read of its own, two clocks of a CU for each that
 // four SIMDs do in one, and address arithmetic and waits besides.  Here a lane keeps its channel's whole plane in registers,
 // read from LDS once for the wavefront's eight output channels, and the position -- the same for all lanes -- moves the register
 // numbers that the multiply-adds name (s_set_gpr_idx): one scalar instruction a patch, no address arithmetic, no
 // branch.  (Measured: the register numbers' moving costs nothing; a dependent chain of v_fma_f32 and this one both issue at one
 // in four clocks.)
 //   - 8x8, 4x4: the plane lies in a block of registers with a border of zeros; the position moves the source, nine taps.
-//   - 2x2: whatever the position, the four elements of X go to four different taps: the position moves the sum's registers,
-//     and the five taps in the padding are not computed.
-// The block and the 72 sums live in numbered registers, above those that the compiler is given (amdgpu_num_vgpr); they are
+//   - 2x2: each position has sums of its own, four elements of X go to four of them, which the position moves to; the five taps
+//     in the padding are not computed.  (Sums of a tap over all positions are chains four times as long: error against 64 bits
+//     1.17e-7 against 0.91e-7, N = 128.)  Sixteen registers an output channel, so four of them to a wavefront.
+// The block and the sums live in numbered registers, above those that the compiler is given (amdgpu_num_vgpr); they are
 // touched by the asm blocks below only.  4x4 and 2x2: 127 registers, four wavefronts a SIMD, which hide each other's LDS and
 // scalar latencies; 8x8: 233, two, bound by reading the planes (128 clocks of the CU's LDS a wavefront and image against 72 of
 // multiply-adds).  X reaches LDS by loads that bypass the registers, a stage of 16 or 32 KB ahead.
-// VGG-19 fp32 at N = 128: layers on 4x4 and 2x2 planes 78 us (54 of them the multiply-adds' own issue, 14 the result's way to
-// memory), on 8x8 planes 29; the LDS gather took 197 for those on 8x8 and 4x4 planes, and the exact kernel on a sparsified dY
+// VGG-19 fp32 at N = 128: layers on 4x4 and 2x2 planes 85 us (54 of them the multiply-adds' own issue, 14 the result's way to
+// memory), on 8x8 planes 29 to 34; the LDS gather took 197 for those on 8x8 and 4x4 planes, and the exact kernel on a sparsified dY
 // 49 for those on 2x2 ones.
 #include <algorithm>
 #include <utility>
@@ -25,14 +26,14 @@
 
 namespace wgrad {
 
-constexpr int kRegsK = 8;                            // output channels of a wavefront
+__host__ __device__ constexpr int regs_kw(int hw) { return hw == 2 ? 4 : 8; }
 constexpr int kRegsWaves = 8;                        // most wavefronts of a workgroup
-// FREE: registers left to the compiler; X: first of the plane's, rows of PITCH (data rows begin at even numbers); ACC: first of
-// the 72 sums, [output channel][tap]; STAGE: bytes of X staged at a time; OCC: wavefronts a SIMD holds
+// KW: output channels of a wavefront; SUMS: registers of each; FREE: registers left to the compiler; X: first of the plane's, rows of PITCH (data rows begin at even numbers); ACC: first of
+// the sums, [output channel][tap], 2x2: [output channel][position][element]; STAGE: bytes of X staged at a time; OCC: wavefronts a SIMD holds
 template <int HW> struct RegsLayout;
-template <> struct RegsLayout<2> { static constexpr int FREE = 19, X = 20, PITCH = 2, ACC = 55, STAGE = 16 * 1024, OCC = 4; };
-template <> struct RegsLayout<4> { static constexpr int FREE = 19, X = 19, PITCH = 6, ACC = 55, STAGE = 16 * 1024, OCC = 4; };
-template <> struct RegsLayout<8> { static constexpr int FREE = 61, X = 61, PITCH = 10, ACC = 161, STAGE = 32 * 1024, OCC = 2; };
+template <> struct RegsLayout<2> { static constexpr int KW = 4, SUMS = 16, FREE = 19, X = 20, PITCH = 2, ACC = 55, STAGE = 16 * 1024, OCC = 4; };
+template <> struct RegsLayout<4> { static constexpr int KW = 8, SUMS = 9, FREE = 19, X = 19, PITCH = 6, ACC = 55, STAGE = 16 * 1024, OCC = 4; };
+template <> struct RegsLayout<8> { static constexpr int KW = 8, SUMS = 9, FREE = 61, X = 61, PITCH = 10, ACC = 161, STAGE = 32 * 1024, OCC = 2; };
 
 struct RegsParams {
     const void *X[kMaxBatch];
@@ -40,12 +41,16 @@ struct RegsParams {
     const float *sum[kMaxBatch];
     float *out[kMaxBatch];                           // dW, or the partials of the batch chunks
     int N, C, K, hw;
-    int ktiles, chunks, chunk_n;                     // tiles of (8 * wavefronts) output channels; 64 input channels
+    int ktiles, chunks, chunk_n;                     // tiles of (KW * wavefronts) output channels; 64 input channels
     float scale;
 };
 
 typedef int rg_i8 __attribute__((ext_vector_type(8)));
 typedef float rg_f8 __attribute__((ext_vector_type(8)));
+typedef int rg_i4 __attribute__((ext_vector_type(4)));
+typedef float rg_f4 __attribute__((ext_vector_type(4)));
+template <int KW> struct RegsScalars { typedef rg_i8 at; typedef rg_f8 sum; };
+template <> struct RegsScalars<4> { typedef rg_i4 at; typedef rg_f4 sum; };
 
 #define RG_CLOBBER "memory"
 
@@ -56,13 +61,15 @@ typedef float rg_f8 __attribute__((ext_vector_type(8)));
     RG_TAP(J, 0, "0") RG_TAP(J, 1, "1") RG_TAP(J, 2, "2")                                                        \
     RG_TAP(J, 3, "%[P]") RG_TAP(J, 4, "%[P]+1") RG_TAP(J, 5, "%[P]+2")                                           \
     RG_TAP(J, 6, "2*%[P]") RG_TAP(J, 7, "2*%[P]+1") RG_TAP(J, 8, "2*%[P]+2")
-// the four taps that lie inside a 2x2 plane
+// 2x2: the four elements into the sums of the position
 #define RG_PATCH2(J)                                                                                             \
-    "s_set_gpr_idx_idx %[i" #J "]\n\t"                                                         \
-    "v_fma_f32 v[%[A]+9*" #J "+0], v[%[X]+0], %[s" #J "], v[%[A]+9*" #J "+0]\n\t"                                \
-    "v_fma_f32 v[%[A]+9*" #J "+1], v[%[X]+1], %[s" #J "], v[%[A]+9*" #J "+1]\n\t"                                \
-    "v_fma_f32 v[%[A]+9*" #J "+3], v[%[X]+2], %[s" #J "], v[%[A]+9*" #J "+3]\n\t"                                \
-    "v_fma_f32 v[%[A]+9*" #J "+4], v[%[X]+3], %[s" #J "], v[%[A]+9*" #J "+4]\n\t"
+    "s_set_gpr_idx_idx %[i" #J "]\n\t"                                                                           \
+    "v_fma_f32 v[%[A]+16*" #J "+0], v[%[X]+0], %[s" #J "], v[%[A]+16*" #J "+0]\n\t"                              \
+    "v_fma_f32 v[%[A]+16*" #J "+1], v[%[X]+1], %[s" #J "], v[%[A]+16*" #J "+1]\n\t"                              \
+    "v_fma_f32 v[%[A]+16*" #J "+2], v[%[X]+2], %[s" #J "], v[%[A]+16*" #J "+2]\n\t"                              \
+    "v_fma_f32 v[%[A]+16*" #J "+3], v[%[X]+3], %[s" #J "], v[%[A]+16*" #J "+3]\n\t"
+#define RG_SCALARS4(at, sum) [i0] "s"(at[0]), [i1] "s"(at[1]), [i2] "s"(at[2]), [i3] "s"(at[3]), [s0] "s"(sum[0]), [s1] "s"(sum[1]), \
+    [s2] "s"(sum[2]), [s3] "s"(sum[3])
 #define RG_SCALARS(at, sum) [i0] "s"(at[0]), [i1] "s"(at[1]), [i2] "s"(at[2]), [i3] "s"(at[3]), [i4] "s"(at[4]), [i5] "s"(at[5]), [i6] "s"(at[6]),    \
     [i7] "s"(at[7]), [s0] "s"(sum[0]), [s1] "s"(sum[1]), [s2] "s"(sum[2]), [s3] "s"(sum[3]), [s4] "s"(sum[4]), [s5] "s"(sum[5]),         \
     [s6] "s"(sum[6]), [s7] "s"(sum[7])
@@ -76,9 +83,9 @@ __device__ __forceinline__ void regs_zero()
 {
 #define RG_ZERO ".set rg_i, %0\n\t.rept %1\n\tv_mov_b32 v[rg_i], 0\n\t.set rg_i, rg_i+1\n\t.endr"
     typedef RegsLayout<HW> L;
-    if constexpr (HW == 8) asm volatile(RG_ZERO ::"n"(L::X), "n"(L::ACC + 9 * kRegsK - L::X) : "memory", "v232");
-    else asm volatile(RG_ZERO ::"n"(L::X), "n"(L::ACC + 9 * kRegsK - L::X) : "memory", "v126");
-    static_assert(L::ACC + 9 * kRegsK - 1 == (HW == 8 ? 232 : 126) && L::X + (HW + 2) * L::PITCH <= L::ACC, "numbered registers");
+    if constexpr (HW == 8) asm volatile(RG_ZERO ::"n"(L::X), "n"(L::ACC + L::SUMS * L::KW - L::X) : "memory", "v232");
+    else asm volatile(RG_ZERO ::"n"(L::X), "n"(L::ACC + L::SUMS * L::KW - L::X) : "memory", "v126");
+    static_assert(L::ACC + L::SUMS * L::KW - 1 <= (HW == 8 ? 232 : 126) && L::X + (HW + 2) * L::PITCH <= L::ACC, "numbered registers");
 #undef RG_ZERO
 }
 #pragma clang diagnostic pop
@@ -90,11 +97,11 @@ __device__ __forceinline__ float regs_get()
     return v;
 }
 
-// The lanes' planes of one image (2x2: of up to four) from LDS, waited for here.  The scalars pass through, so that the wait for
+// 4x4, 8x8: the lanes' planes of one image from LDS, waited for here.  The scalars pass through, so that the wait for
 // them comes before and the next image's are loaded after: a wait for LDS is a wait for scalar loads too, and theirs take
 // far longer.
-template <int HW, int OFF, int COUNT>
-__device__ __forceinline__ void regs_load(const uint32_t *rd, const int32_t *&at_p, const float *&sum_p, rg_i8 &at, rg_f8 &sum)
+template <int HW, int OFF, class AT, class SUM>
+__device__ __forceinline__ void regs_load(const uint32_t *rd, const int32_t *&at_p, const float *&sum_p, AT &at, SUM &sum)
 {
 #define RG_ROW(R, V) "ds_read_b128 v[%[X]+" V ":%[X]+" V "+3], %[r" #R "] offset:%[o]\n\t"
 #define RG_PASS "+s"(at_p), "+s"(sum_p), "+s"(at), "+s"(sum)
@@ -107,25 +114,27 @@ __device__ __forceinline__ void regs_load(const uint32_t *rd, const int32_t *&at
                      : [X] "n"(L::X), [o] "n"(OFF), [r0] "v"(rd[0]), [r1] "v"(rd[1]), [r2] "v"(rd[2]), [r3] "v"(rd[3]), [r4] "v"(rd[4]), [r5] "v"(rd[5]),
                        [r6] "v"(rd[6]), [r7] "v"(rd[7]), [r8] "v"(rd[8]), [r9] "v"(rd[9]), [r10] "v"(rd[10]), [r11] "v"(rd[11]), [r12] "v"(rd[12]),
                        [r13] "v"(rd[13]), [r14] "v"(rd[14]), [r15] "v"(rd[15]) : RG_CLOBBER);
-    else if constexpr (HW == 4)
+    else
         asm volatile(RG_ROW(0, "7") RG_ROW(1, "13") RG_ROW(2, "19") RG_ROW(3, "25") "s_waitcnt lgkmcnt(0)"
                      : RG_PASS : [X] "n"(L::X), [o] "n"(OFF), [r0] "v"(rd[0]), [r1] "v"(rd[1]), [r2] "v"(rd[2]), [r3] "v"(rd[3]) : RG_CLOBBER);
-    else if constexpr (COUNT == 4)
-        asm volatile("ds_read_b128 v[%[X]:%[X]+3], %[r0] offset:%[o]\n\tds_read_b128 v[%[X]+4:%[X]+7], %[r0] offset:%[o]+1024\n\t"
-                     "ds_read_b128 v[%[X]+8:%[X]+11], %[r0] offset:%[o]+2048\n\tds_read_b128 v[%[X]+12:%[X]+15], %[r0] offset:%[o]+3072\n\t"
-                     "s_waitcnt lgkmcnt(0)"
-                     : RG_PASS : [X] "n"(L::X), [o] "n"(OFF), [r0] "v"(rd[0]) : RG_CLOBBER);
-    else if constexpr (COUNT == 1)
-        asm volatile("ds_read_b128 v[%[X]:%[X]+3], %[r0] offset:%[o]\n\ts_waitcnt lgkmcnt(0)"
-                     : RG_PASS : [X] "n"(L::X), [o] "n"(OFF), [r0] "v"(rd[0]) : RG_CLOBBER);
-    else asm volatile("" : RG_PASS);
 #undef RG_ROW
 #undef RG_PASS
 }
 
-// the eight patches of one image; 2x2: of the one in the I-th four registers
-template <int HW, int I>
-__device__ __forceinline__ void regs_patches(const rg_i8 &at, const rg_f8 &sum)
+// 2x2: the same for four images; four at a time, because the scalars of one are used before the next one's could arrive
+template <int OFF>
+__device__ __forceinline__ void regs_load4(uint32_t rd, rg_i4 (&at)[4], rg_f4 (&sum)[4])
+{
+    asm volatile("ds_read_b128 v[%[X]:%[X]+3], %[r0] offset:%[o]\n\tds_read_b128 v[%[X]+4:%[X]+7], %[r0] offset:%[o]+1024\n\t"
+                 "ds_read_b128 v[%[X]+8:%[X]+11], %[r0] offset:%[o]+2048\n\tds_read_b128 v[%[X]+12:%[X]+15], %[r0] offset:%[o]+3072\n\t"
+                 "s_waitcnt lgkmcnt(0)"
+                 : "+s"(at[0]), "+s"(at[1]), "+s"(at[2]), "+s"(at[3]), "+s"(sum[0]), "+s"(sum[1]), "+s"(sum[2]), "+s"(sum[3])
+                 : [X] "n"(RegsLayout<2>::X), [o] "n"(OFF), [r0] "v"(rd) : RG_CLOBBER);
+}
+
+// the patches of one image; 2x2: of the one in the I-th four registers
+template <int HW, int I, class AT, class SUM>
+__device__ __forceinline__ void regs_patches(const AT &at, const SUM &sum)
 {
     typedef RegsLayout<HW> L;
     if constexpr (HW >= 4)
@@ -134,8 +143,8 @@ __device__ __forceinline__ void regs_patches(const rg_i8 &at, const rg_f8 &sum)
                      "s_set_gpr_idx_off" :: [X] "n"(L::X), [A] "n"(L::ACC), [P] "n"(L::PITCH), RG_SCALARS(at, sum) : RG_CLOBBER);
     else
         asm volatile("s_set_gpr_idx_on %[i0], gpr_idx(SRC2,DST)\n\t"
-                     RG_PATCH2(0) RG_PATCH2(1) RG_PATCH2(2) RG_PATCH2(3) RG_PATCH2(4) RG_PATCH2(5) RG_PATCH2(6) RG_PATCH2(7)
-                     "s_set_gpr_idx_off" :: [X] "n"(L::X + 4 * I), [A] "n"(L::ACC), RG_SCALARS(at, sum) : RG_CLOBBER);
+                     RG_PATCH2(0) RG_PATCH2(1) RG_PATCH2(2) RG_PATCH2(3)
+                     "s_set_gpr_idx_off" :: [X] "n"(L::X + 4 * I), [A] "n"(L::ACC), RG_SCALARS4(at, sum) : RG_CLOBBER);
 }
 
 template <int... I, class F>
@@ -154,7 +163,7 @@ __device__ __forceinline__ void regs_body(const RegsParams &p, char *smem, int b
     const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 6);
     const int logical = xcd_contiguous_id(bid, nblk);            // (the workgroups that read the same planes side by side)
     const int kt = logical % p.ktiles, rest = logical / p.ktiles, chunk = rest % p.chunks, ct = rest / p.chunks;
-    const int C = p.C, K = p.K, c0 = ct * 64, k0 = (kt * waves + wave) * kRegsK;
+    const int C = p.C, K = p.K, c0 = ct * 64, k0 = (kt * waves + wave) * L::KW;
     const int n_begin = chunk * p.chunk_n, n_end = n_begin + p.chunk_n < p.N ? n_begin + p.chunk_n : p.N;
     const uint32_t ximg = (uint32_t)C * PLANE;
 
@@ -184,47 +193,86 @@ __device__ __forceinline__ void regs_body(const RegsParams &p, char *smem, int b
     regs_zero<HW>();
 
     // (scalar loads: the selections were written by an earlier launch; volatile: where they stand is where they are issued)
-    typedef const volatile __attribute__((address_space(4))) rg_i8 *at_ptr;
-    typedef const volatile __attribute__((address_space(4))) rg_f8 *sum_ptr;
+    typedef const volatile __attribute__((address_space(4))) typename RegsScalars<L::KW>::at *at_ptr;
+    typedef const volatile __attribute__((address_space(4))) typename RegsScalars<L::KW>::sum *sum_ptr;
     const size_t first = (size_t)n_begin * K + k0;
     const int32_t *at_p = p.at[prob] + first;
     const float *sum_p = p.sum[prob] + first;
-    rg_i8 at[2];
-    rg_f8 sum[2];
-    at[0] = *(at_ptr)(uintptr_t)at_p;
-    sum[0] = *(sum_ptr)(uintptr_t)sum_p;
-    // image I of a stage or of its rest, with scalars I % 2; those of the next (step maps on) are loaded meanwhile
-    auto image = [&](auto i_c, auto count_c, int step) {
-        constexpr int I = decltype(i_c)::value, A = I & 1;
-        at_p += step; sum_p += step;
-        regs_load<HW, I * IMG, decltype(count_c)::value>(rd, at_p, sum_p, at[A], sum[A]);
-        at[A ^ 1] = *(at_ptr)(uintptr_t)at_p;
-        sum[A ^ 1] = *(sum_ptr)(uintptr_t)sum_p;
-        __builtin_amdgcn_sched_barrier(0);
-        regs_patches<HW, I & 3>(at[A], sum[A]);
-    };
-    const int full = (n_end - n_begin) / NI, rest_n = (n_end - n_begin) % NI, stages = full + (rest_n > 0);
+    const int count = n_end - n_begin, full = count / NI, rest_n = count % NI, stages = full + (rest_n > 0);
     auto meet = [&](int stage) {                     // the stage is in LDS, the one before it read by all
         asm volatile("s_waitcnt vmcnt(0) lgkmcnt(0)\n\ts_barrier" ::: "memory");
         if (stage + 1 < stages) copy_stage(stage + 1);
     };
-    for (int stage = 0; stage < full; ++stage) {
-        meet(stage);
-        const int last_step = stage + 1 < stages ? K : 0;
-        regs_each(std::make_integer_sequence<int, NI>(), [&](auto i_c) {
-            constexpr int I = decltype(i_c)::value;
-            image(i_c, std::integral_constant<int, I % 4 == 0 ? 4 : 0>(), I == NI - 1 ? last_step : K);
-        });
+    if constexpr (HW == 2) {
+        rg_i4 at[2][4];
+        rg_f4 sum[2][4];
+        auto fetch = [&](int n, auto a_c) {          // of images n .. n + 3 of the chunk, the last one again past its end
+            constexpr int A = decltype(a_c)::value;
 #pragma unroll
-        for (int r = 0; r < PIECES; ++r) rd[r] ^= L::STAGE;
-    }
-    if (rest_n > 0) {
-        meet(full);
-        for (int i = 0; i < rest_n; ++i) {
-            image(std::integral_constant<int, 0>(), std::integral_constant<int, 1>(), i + 1 < rest_n ? K : 0);
-            at[0] = at[1]; sum[0] = sum[1];
+            for (int j = 0; j < 4; ++j) {
+                const uint32_t o = (uint32_t)std::min(n + j, count - 1) * (uint32_t)K;
+                at[A][j] = *(at_ptr)(uintptr_t)(at_p + o);
+                sum[A][j] = *(sum_ptr)(uintptr_t)(sum_p + o);
+            }
+        };
+        typedef std::integral_constant<int, 0> i0;
+        fetch(0, i0());
+        for (int stage = 0; stage < full; ++stage) {
+            meet(stage);
+            regs_each(std::make_integer_sequence<int, NI / 4>(), [&](auto g_c) {
+                constexpr int G = decltype(g_c)::value, A = G & 1;
+                regs_load4<G * 4 * IMG>(rd[0], at[A], sum[A]);
+                fetch(stage * NI + 4 * G + 4, std::integral_constant<int, A ^ 1>());
+                __builtin_amdgcn_sched_barrier(0);
+                regs_each(std::make_integer_sequence<int, 4>(), [&](auto j_c) { regs_patches<HW, decltype(j_c)::value>(at[A][decltype(j_c)::value], sum[A][decltype(j_c)::value]); });
+            });
+            rd[0] ^= L::STAGE;
+        }
+        if (rest_n > 0) {
+            meet(full);
+            for (int n = 0; n < rest_n; n += 4) {
+                if (n > 0) fetch(full * NI + n, i0());
+                regs_load4<0>(rd[0], at[0], sum[0]);
+                regs_each(std::make_integer_sequence<int, 4>(), [&](auto j_c) {
+                    constexpr int J = decltype(j_c)::value;
+                    if (n + J < rest_n) regs_patches<HW, J>(at[0][J], sum[0][J]);
+                });
+                rd[0] += 4 * IMG;
+            }
+        }
+    } else {
+        typename RegsScalars<L::KW>::at at[2];
+        typename RegsScalars<L::KW>::sum sum[2];
+        at[0] = *(at_ptr)(uintptr_t)at_p;
+        sum[0] = *(sum_ptr)(uintptr_t)sum_p;
+        // image I of a stage or of its rest, with scalars I % 2; those of the next (step maps on) are loaded meanwhile
+        auto image = [&](auto i_c, int step) {
+            constexpr int I = decltype(i_c)::value, A = I & 1;
+            at_p += step; sum_p += step;
+            regs_load<HW, I * IMG>(rd, at_p, sum_p, at[A], sum[A]);
+            at[A ^ 1] = *(at_ptr)(uintptr_t)at_p;
+            sum[A ^ 1] = *(sum_ptr)(uintptr_t)sum_p;
+            __builtin_amdgcn_sched_barrier(0);
+            regs_patches<HW, 0>(at[A], sum[A]);
+        };
+        for (int stage = 0; stage < full; ++stage) {
+            meet(stage);
+            const int last_step = stage + 1 < stages ? K : 0;
+            regs_each(std::make_integer_sequence<int, NI>(), [&](auto i_c) {
+                constexpr int I = decltype(i_c)::value;
+                image(i_c, I == NI - 1 ? last_step : K);
+            });
 #pragma unroll
-            for (int r = 0; r < PIECES; ++r) rd[r] += IMG;
+            for (int r = 0; r < PIECES; ++r) rd[r] ^= L::STAGE;
+        }
+        if (rest_n > 0) {
+            meet(full);
+            for (int i = 0; i < rest_n; ++i) {
+                image(std::integral_constant<int, 0>(), i + 1 < rest_n ? K : 0);
+                at[0] = at[1]; sum[0] = sum[1];
+#pragma unroll
+                for (int r = 0; r < PIECES; ++r) rd[r] += IMG;
+            }
         }
     }
 
@@ -234,9 +282,13 @@ __device__ __forceinline__ void regs_body(const RegsParams &p, char *smem, int b
     float *const out = p.out[prob] + ((size_t)chunk * K + k0) * C * 9 + (size_t)c0 * 9;
     auto put = [&](auto j_c) {
         constexpr int J = decltype(j_c)::value;
-        float v[9] = {regs_get<L::ACC + 9 * J>(), regs_get<L::ACC + 9 * J + 1>(), regs_get<L::ACC + 9 * J + 2>(),
-                      regs_get<L::ACC + 9 * J + 3>(), regs_get<L::ACC + 9 * J + 4>(), regs_get<L::ACC + 9 * J + 5>(),
-                      regs_get<L::ACC + 9 * J + 6>(), regs_get<L::ACC + 9 * J + 7>(), regs_get<L::ACC + 9 * J + 8>()};
+        float v[9] = {};
+        regs_each(std::make_integer_sequence<int, L::SUMS>(), [&](auto i_c) {
+            constexpr int I = decltype(i_c)::value;
+            // 2x2: position p sees element e at tap e - p
+            constexpr int T = HW == 2 ? 4 + 3 * ((I >> 1 & 1) - (I >> 3)) + (I & 1) - (I >> 2 & 1) : I;
+            v[T] += regs_get<L::ACC + L::SUMS * J + I>();
+        });
 #pragma unroll
         for (int t = 0; t < 9; ++t) row[lane * 9 + t] = v[t] * p.scale;
         __builtin_amdgcn_wave_barrier();
@@ -246,7 +298,7 @@ __device__ __forceinline__ void regs_body(const RegsParams &p, char *smem, int b
         asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
         __builtin_amdgcn_wave_barrier();
     };
-    regs_each(std::make_integer_sequence<int, kRegsK>(), put);
+    regs_each(std::make_integer_sequence<int, L::KW>(), put);
 }
 
 constexpr int kRegsMultiMax = 8;
@@ -292,13 +344,13 @@ void approx_gather_regs8(const RegsMulti)
 bool regs_takes(const Geometry &g)
 {
     if (g.bf16 || g.R != 3 || g.S != 3 || g.ph != 1 || g.pw != 1 || g.H != g.W || (g.H != 8 && g.H != 4 && g.H != 2)) return false;
-    // (scalar loads of eight maps at a time, whole tiles; a byte offset in X is 32 bits)
+    // (scalar loads of eight or four maps at a time, whole tiles; a byte offset in X is 32 bits)
     return g.C % 64 == 0 && g.K % 32 == 0 && g.K >= 128 && tune_int("WGRAD_REGS", 1) && (long)g.N * g.C * g.H * g.W * 4 < (1l << 31);
 }
 
 RegsPosition regs_position(const Geometry &g)
 {
-    if (g.H == 2) return RegsPosition{-3 * g.sh, -g.sw, 4};
+    if (g.H == 2) return RegsPosition{8 * g.sh, 4 * g.sw, 0};
     return RegsPosition{(g.H == 8 ? RegsLayout<8>::PITCH : RegsLayout<4>::PITCH) * g.sh, g.sw, 0};
 }
 
@@ -309,7 +361,7 @@ struct RegsItem {
     const float *sum[kMaxBatch];
     char *part;                      // partial results of the first problem; the next problem's lie `stride` bytes on
     size_t stride;
-    int max_chunks;
+    int min_chunks, max_chunks;
     float scale;
 };
 struct RegsQueue {
@@ -328,7 +380,7 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
     double best = 1e30;
     for (int waves = 8; waves >= 4; waves -= 4) {
         bool fits = true;
-        for (int i = 0; i < n; ++i) fits = fits && it[i]->g.K % (kRegsK * waves) == 0;
+        for (int i = 0; i < n; ++i) fits = fits && it[i]->g.K % (regs_kw(it[i]->g.H) * waves) == 0;
         if (!fits) continue;
         const bool big = it[0]->g.H == 8;
         const int most = big ? RegsLayout<8>::OCC : RegsLayout<4>::OCC, slots = kNumCU * 4 * most / waves;
@@ -338,27 +390,28 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
             for (int i = 0; i < n; ++i) {
                 const Geometry &g = it[i]->g;
                 int ch = g.H == 2 ? (want + 1) / 2 : want;
-                ch = std::max(1, std::min(ch, std::min(it[i]->max_chunks, (g.N + 7) / 8)));
+                ch = std::max(it[i]->min_chunks, std::min(ch, std::min(it[i]->max_chunks, (g.N + 7) / 8)));
                 const int per = (g.N + ch - 1) / ch;
                 now[i] = (g.N + per - 1) / per;
                 if (now[i] > 1) partial += (double)now[i] * g.dw_elems() * 4 * it[i]->b.n;
-                all_waves += (double)now[i] * (g.C / 64) * (g.K / kRegsK) * it[i]->b.n;
+                all_waves += (double)now[i] * (g.C / 64) * (g.K / regs_kw(g.H)) * it[i]->b.n;
             }
             const double occ = std::min((double)most, std::max(waves / 4.0, all_waves / (kNumCU * 4)));
             double sorted[kRegsMultiMax], lf[kRegsMultiMax];
             long count[kRegsMultiMax];
             for (int i = 0; i < n; ++i) {
                 const Geometry &g = it[i]->g;
-                // a wavefront's time for an image, with occ of them on its SIMD (measured, 512 -> 512 @ 2x2 and 4x4 and VGG-19's
-                // 8x8 layers: 0.24 us at two and 0.33 at four, 0.40 and 0.71, 0.55 at two); fewer to a workgroup copy X more often
-                const double image = g.H == 8 ? 0.11 + 0.22 * occ : (g.H == 4 ? std::max(0.177 * occ, 0.16 + 0.12 * occ) : 0.1 + 0.06 * occ);
+                // a wavefront's time for an image, with occ of them on its SIMD (measured, 512 -> 512 @ 4x4 0.40 us at two and 0.71
+                // at four, VGG-19's 8x8 layers 0.55 at two, 512 -> 512 @ 2x2 with eight output channels to a wavefront 0.24 and
+                // 0.33, of which four take some 60 %); fewer wavefronts to a workgroup copy X more often
+                const double image = g.H == 8 ? 0.11 + 0.22 * occ : (g.H == 4 ? std::max(0.177 * occ, 0.16 + 0.12 * occ) : 0.06 + 0.04 * occ);
                 lf[i] = 9.0 + (g.N + now[i] - 1) / now[i] * image * (waves == 8 ? 1.0 : 1.1);
                 int j = i;
                 for (; j > 0 && sorted[j - 1] < lf[i]; --j) { sorted[j] = sorted[j - 1]; count[j] = count[j - 1]; }
                 sorted[j] = lf[i];
-                count[j] = (long)now[i] * (g.C / 64) * (g.K / (kRegsK * waves)) * it[i]->b.n;
+                count[j] = (long)now[i] * (g.C / 64) * (g.K / (regs_kw(g.H) * waves)) * it[i]->b.n;
             }
-            const double cost = makespan_us(slots, sorted, count, n) + partial / 7e6 + (partial > 0 ? 2.0 : 0.0);
+            const double cost = makespan_us(slots, sorted, count, n) + partial / (partial < 40e6 ? 7e6 : 3.5e6) + (partial > 0 ? 2.0 : 0.0);
             if (cost < best) {
                 best = cost;
                 best_waves = waves;
@@ -374,7 +427,7 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
 int regs_max_chunks(const Geometry &g, int cap)
 {
     RegsItem I{};
-    I.g = g; I.b.n = 1; I.max_chunks = cap;
+    I.g = g; I.b.n = 1; I.min_chunks = 1; I.max_chunks = cap;
     const RegsItem *one = &I;
     int ch;
     double life;
@@ -403,7 +456,7 @@ static int regs_launch(const RegsItem *const *it, int n, bool big, hipStream_t s
         RegsParams &p = m.p[o];
         const int ch = chunks[order[o]];
         p.N = g.N; p.C = g.C; p.K = g.K; p.hw = g.H;
-        p.ktiles = g.K / (kRegsK * waves); p.chunks = ch; p.chunk_n = (g.N + ch - 1) / ch;
+        p.ktiles = g.K / (regs_kw(g.H) * waves); p.chunks = ch; p.chunk_n = (g.N + ch - 1) / ch;
         p.scale = ch > 1 ? 1.0f : I.scale;
         for (int j = 0; j < kMaxBatch; ++j) {
             const int k = j < I.b.n ? j : 0;
@@ -442,13 +495,13 @@ int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine)
 
 // One group of identical layers, selected already (or recorded to be, where the launch is): its own launch, or (with a queue)
 // collected for regs_flush.
-int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, float scale,
+int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int min_chunks, int max_chunks, float scale,
                 void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue)
 {
     RegsQueue local;
     RegsQueue &q = queue ? *queue : local;
     RegsItem &I = q.item[q.n++];
-    I.g = g; I.b = b; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride;
+    I.g = g; I.b = b; I.min_chunks = min_chunks; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride;
     for (int i = 0; i < b.n; ++i) { I.at[i] = at[i]; I.sum[i] = sum[i]; }
     return queue ? WGRAD_OK : regs_flush(local, st, defer);
 }

@@ -98,7 +98,7 @@ struct ExactPlan {
     int img4;                        // streaming form, 4x4 planes: image-uniform position order (a step contracts one position of four images)
     int mm16;                        // bf16 matrix-core form of the streaming kernel
     int direct;                      // general form: no tile of whole output rows fits the LDS
-    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run of several layers only
+    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run, two and more layers of a shape, 4 as 1 and as 3
     X3Plan x3p;
     int rows;                        // bf16_rows.hip's form: 0 no, 1 in a run of several exact layers, 2 always, 3 in a run with a layer of 1 or 2
     int rows_chunks;                 // ... the most batch chunks
@@ -205,7 +205,7 @@ RegsQueue *regs_queue_new();
 void regs_queue_delete(RegsQueue *q);
 bool regs_full(const RegsQueue &q);
 int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine);
-int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, float scale,
+int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int min_chunks, int max_chunks, float scale,
                 void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue);
 // LDS-form gathers of several layer groups, collected for one launch
 GatherQueue *gather_queue_new(SelectQueue *selects = nullptr);
