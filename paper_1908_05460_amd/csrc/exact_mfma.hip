@@ -627,10 +627,10 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // what the streaming form cannot (27x27 planes, 48 -> 96, N = 32: 76 -> 35 us; 224x224, 64 -> 64, N = 4: 302 -> 88) and
 // all but two kinds of what it can: long strided reductions, whose windows are mostly staging (128 -> 128 @ 56x56, stride
 // 2, N = 16, 3.7 GFLOP: 86 us against 60; at 0.2 to 0.9 GFLOP 13 to 23 against 16 to 29), and, in a run of several layers,
-// layers of less than 0.5 GFLOP.  That line was drawn where one launch of all of a run's short layers won (ResNet-20 at N =
-// 16 to 64: 36 to 67 us against 55 to 74), before the 16-wide tiles' smaller products had sums of their own and three of
-// their workgroups, not four, shared a CU; by now it lies too high (without a line, N = 32 / 64 / 96 / 128: 49 -> 45, 68 ->
-// 60, 87 -> 76, 93 -> 91 us; the fp32 matrix core alone at N = 128 107).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
+// short ones: of less than 0.5 GFLOP where strided or the only one of their shape, else of less than 0.14 (ResNet-20, every
+// layer exact / every other one, N = 80: 74.1 -> 69.4 / 72.5 -> 65.7 us with the line at 0.3, N = 48: 57.9 -> 50.2 / 50.8 -> 51.2 at 0.2,
+// N = 32: 46.7 -> 43.5 / 47.6 -> 45.3 at 0.1, N = 16: 34.4 -> 35.7 / 32.9 -> 35.7 at 0.05; with the last layer alone
+// exact, N = 48: 42.6 -> 45.3 at 0.2).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
 // against 14.8).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
 // of its own is what costs, and two or more of one shape at a time (with a small layer beside them, N = 64 / 128 / 256: one 23 /
@@ -649,7 +649,11 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
         // 17.9 -> 14.5, N = 128: 28 against 30, N = 512: 57 against 64; VGG-19 in runs: 459 against 469)
         use = !pl.mm16 ? 2 : (gflop < 4.0 ? 1 : 0);
     } else if (pl.stream && g.sw > 1 && gflop >= 1.5) use = 0;
-    else use = !pl.stream || gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 500) * 1e-3 ? 2 : (gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0);
+    else if (!pl.stream || gflop >= 0.5) use = 2;
+    else {
+        const bool alone = gflop >= 0.03 && g.K > 16 && g.C > 16, run = g.sw == 1 && gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 140) * 1e-3;
+        use = run ? (alone ? 4 : 3) : (alone ? 1 : 0);
+    }
     X3Plan x3{};
     if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) return size_exact(g, pl);
     // (the other form's split and workspace only where a call may come back to it)
@@ -735,7 +739,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
     if ((plan.rows == 2 || (plan.rows != 0 && mq)) && batch_aligned(g, b, 8, 8))
         return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
-    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 4 && !mq && !bq) || (plan.x3 >= 3 && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The

@@ -268,3 +268,21 @@ def test_infinities_in_a_run_of_layers():
         got, fine = got.cpu().numpy(), np.isfinite(want)
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
         assert normwise_err(got[fine], want[fine]) < TOL["fp32"]
+
+
+# ResNet-20's shapes in runs, on both sides of the lines for short layers: 0.14 GFLOP for two layers of a shape, 0.5 for one and
+# for strides
+@pytest.mark.parametrize("N", [29, 30, 48, 107])
+def test_short_layers_in_runs(N):
+    import torch
+    shapes = [(N, 16, 32, 32, 16, 3, 3, 1, 1, 1, 1)] * 2 + [(N, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1)] * 3 \
+        + [(N, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1), (N, 16, 32, 32, 32, 3, 3, 2, 2, 1, 1)]
+    ds = [mk(t) for t in shapes]
+    data = [rand_inputs(d, 90 + i) for i, d in enumerate(ds)]
+    out = [torch_nan(d) for d in ds]
+    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
+    mask = np.full(len(ds), B.EXACT, np.uint8)
+    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)))
+    torch.cuda.synchronize()
+    for d, (X, dY), got in zip(ds, data, out):
+        assert normwise_err(got.cpu().numpy(), oracle.wgrad_exact(oracle_shape(d), X, dY)) < TOL["fp32"] / 10
