@@ -340,7 +340,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
         const ExactPlan &ex = plan[i].ex;
         int members = 0;
         for (int j = i; j < nlayers; ++j) members += group[j] == i;
-        if (ex.plane2 || ex.x3 == 2 || (ex.x3 >= 3 && members > 1)) return 0.0;
+        if (ex.plane2 || ex.x3 == 2 || ((ex.x3 == 3 || ex.x3_run) && members > 1)) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
         // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of

@@ -98,11 +98,12 @@ struct ExactPlan {
     int img4;                        // streaming form, 4x4 planes: image-uniform position order (a step contracts one position of four images)
     int mm16;                        // bf16 matrix-core form of the streaming kernel
     int direct;                      // general form: no tile of whole output rows fits the LDS
-    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run, two and more layers of a shape, 4 as 1 and as 3
+    int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run of several layers only
     X3Plan x3p;
     int rows;                        // bf16_rows.hip's form: 0 no, 1 in a run of several exact layers, 2 always, 3 in a run with a layer of 1 or 2
     int rows_chunks;                 // ... the most batch chunks
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
+    int x3_run;                      // x3's form also in a run, for two and more layers of a shape
     size_t lds_bytes, ws_bytes;
     bool ok;
 };

@@ -630,7 +630,8 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // short ones: of less than 0.5 GFLOP where strided or the only one of their shape, else of less than 0.14 (ResNet-20, every
 // layer exact / every other one, N = 80: 74.1 -> 69.4 / 72.5 -> 65.7 us with the line at 0.3, N = 48: 57.9 -> 50.2 / 50.8 -> 51.2 at 0.2,
 // N = 32: 46.7 -> 43.5 / 47.6 -> 45.3 at 0.1, N = 16: 34.4 -> 35.7 / 32.9 -> 35.7 at 0.05; with the last layer alone
-// exact, N = 48: 42.6 -> 45.3 at 0.2).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
+// exact, N = 48: 42.6 -> 45.3 at 0.2), and batches under 16, which keep to the launch of many small groups (8, 64 -> 128 @ 16x16,
+// two layers and a small one, 34 us there, 27 here).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
 // against 14.8).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
 // of its own is what costs, and two or more of one shape at a time (with a small layer beside them, N = 64 / 128 / 256: one 23 /
@@ -641,6 +642,7 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
     ExactPlan pl = plan_exact_forms(g, true);
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     int use;
+    bool run = false;
     if (pl.plane2) use = gflop >= 1.0 ? 3 : 0;
     else if (g.bf16) {
         // one piece, one product.  All that the bf16 kernel of exact_bf16.hip does not take (224x224, 64 -> 64, N = 4: 393 ->
@@ -651,14 +653,15 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
     } else if (pl.stream && g.sw > 1 && gflop >= 1.5) use = 0;
     else if (!pl.stream || gflop >= 0.5) use = 2;
     else {
-        const bool alone = gflop >= 0.03 && g.K > 16 && g.C > 16, run = g.sw == 1 && gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 140) * 1e-3;
-        use = run ? (alone ? 4 : 3) : (alone ? 1 : 0);
+        use = gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0;
+        run = g.sw == 1 && g.N >= 16 && gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 140) * 1e-3;
     }
     X3Plan x3{};
-    if (!tune_int("WGRAD_X3", 1) || !use || !plan_exact_x3(g, x3) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) return size_exact(g, pl);
+    if (!tune_int("WGRAD_X3", 1) || (!use && !run) || !plan_exact_x3(g, x3) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) return size_exact(g, pl);
     // (the other form's split and workspace only where a call may come back to it)
     if (use != 2 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
     pl.x3 = use;
+    pl.x3_run = run;
     pl.x3p = x3;
     const size_t need = x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
     if (need > pl.ws_bytes) pl.ws_bytes = need;
@@ -739,7 +742,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
     if ((plan.rows == 2 || (plan.rows != 0 && mq)) && batch_aligned(g, b, 8, 8))
         return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
-    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 4 && !mq && !bq) || (plan.x3 >= 3 && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || ((plan.x3 == 3 || plan.x3_run) && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The
