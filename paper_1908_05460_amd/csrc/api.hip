@@ -385,7 +385,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     }
     RegsQueue *rgq = nregs > 0 ? regs_queue_new() : nullptr;
     int nrows = 0;
-    for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && (plan[i].ex.rows == 1 || plan[i].ex.rows == 2);
+    for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows == 1;
     for (int i = 0; i < nlayers; ++i)
         if (method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows == 3 && nrows == 0) plan[i].ex.rows = 0;
     char *ws_next = (char *)ws;

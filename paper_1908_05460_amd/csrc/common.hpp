@@ -100,7 +100,7 @@ struct ExactPlan {
     int direct;                      // general form: no tile of whole output rows fits the LDS
     int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run of several layers only
     X3Plan x3p;
-    int rows;                        // bf16_rows.hip's form: 0 no, 1 in a run of several exact layers, 2 always, 3 in a run with a layer of 1 or 2
+    int rows;                        // bf16_rows.hip's form: 0 no, 1 in a run of several exact layers, 3 in a run with a layer of 1
     int rows_chunks;                 // ... the most batch chunks
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     int x3_run;                      // x3's form also in a run, for two and more layers of a shape
@@ -122,6 +122,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &pl);
 bool x3_needs_alignment(const X3Plan &pl);
 bool x3_ragged(const X3Plan &pl);
 int x3_tile_rows(const X3Plan &pl);
+bool x3_fit(X3Plan &pl, long room);
 struct X3Queue;
 X3Queue *x3_queue_new();
 void x3_queue_delete(X3Queue *q);

@@ -660,10 +660,12 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
     if (!tune_int("WGRAD_X3", 1) || (!use && !run) || !plan_exact_x3(g, x3) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) return size_exact(g, pl);
     // (the other form's split and workspace only where a call may come back to it)
     if (use != 2 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
+    // (in a run only: the workspace stays the other form's)
+    if (!use && !x3_fit(x3, (long)(pl.ws_bytes / ((size_t)g.dw_elems() * 4)))) return pl;
     pl.x3 = use;
     pl.x3_run = run;
     pl.x3p = x3;
-    const size_t need = x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
+    const size_t need = use && x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
     if (need > pl.ws_bytes) pl.ws_bytes = need;
     pl.ok = true;
     return pl;
@@ -672,19 +674,19 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
 ExactPlan plan_exact(const Geometry &g)
 {
     ExactPlan pl = plan_exact_x3_or_older(g);
-    // bf16 on 4x4 to 32x32 planes, row after row: in a run of several layers always, where one launch takes them all (VGG-19
-    // exact, N = 16 / 64 / 160 / 512: 104 / 143 / 211 / 470 us -> 58 / 85 / 154 / 372; under half the masks of a schedule 1.4 to
-    // 1.7 times as fast).  Alone from 9 GFLOP on (38.7 GFLOP, 64 -> 64 @ 32x32 / 128 -> 128 @ 16x16 / 256 -> 256 @ 8x8: 58.6 / 50.8 /
-    // 50.7 -> 46.7 / 42.4 / 42.1; 9.7 GFLOP 27 to 31 -> 25 to 28; shorter ones either way: 64, 128 -> 128 @ 16x16 26.8 -> 24.1, but 25,
-    // 128 -> 128 @ 32x32 26.3 -> 29.0), not on 4x4, whose position-major kernel splits nothing (512 -> 512, N = 512: 29.3
-    // against 43.8).  A first layer of a few channels leaves most of a tile empty (3 -> 64 @ 32x32, N = 512: 21.8 against 33.9): it
-    // joins others where it is short (VGG-19, N = 16 / 64 / 160: 57 / 93 / 156 us with it, 71 / 94 / 162 without; 512: 376 against 361).
+    // bf16 on 4x4 to 32x32 planes, row after row: in a run of several layers, where one launch takes them all (VGG-19 exact, N =
+    // 16 / 64 / 160 / 512: 104 / 143 / 211 / 470 us -> 58 / 85 / 154 / 372; under half the masks of a schedule 1.4 to 1.7 times as
+    // fast).  Not alone: it needs 256 partial results of a tile to fill the chip, the row-window kernel half as many, and the
+    // workspace is that one's (38.7 GFLOP, 64 -> 64 @ 32x32 / 128 -> 128 @ 16x16 / 512 -> 512 @ 8x8: 52.3 / 49.6 / 145 us, here with
+    // 256 workgroups 46.6 / 42.4 / 115, with 128 54.3 / 50.3 / 152); on 4x4 the position-major kernel splits nothing (512 -> 512,
+    // N = 512: 29.3 against 43.8).  A first layer of a few channels leaves most of a tile empty (3 -> 64 @ 32x32, N = 512: 21.8
+    // against 33.9): it joins others where it is short (VGG-19, N = 16 / 64 / 160: 57 / 93 / 156 us with it, 71 / 94 / 162 without; 512:
+    // 376 against 361).
     const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
     if (rows_takes(g) && (g.C >= 16 || gflop < 1.0)) {
-        pl.rows = g.C < 16 ? 3 : (g.W > 4 && gflop >= 9.0 ? 2 : 1);
-        pl.rows_chunks = rows_max_chunks(g);
-        const size_t need = pl.rows_chunks > 1 ? align_up((size_t)pl.rows_chunks * g.dw_elems() * 4) : 0;
-        if (need > pl.ws_bytes) pl.ws_bytes = need;
+        pl.rows = g.C < 16 ? 3 : 1;
+        // no more chunks than the other forms' workspace holds: a buffer that sufficed for them suffices
+        pl.rows_chunks = (int)std::max<size_t>(1, std::min<size_t>(pl.ws_bytes / ((size_t)g.dw_elems() * 4), 1024));
     }
     return pl;
 }
@@ -739,7 +741,7 @@ static int launch_exact_staged(const Geometry &g, const ExactPlan &pl, const voi
 int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void *ws, hipStream_t st, CombineQueue *defer,
                  MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq, RowsQueue *rq)
 {
-    if ((plan.rows == 2 || (plan.rows != 0 && mq)) && batch_aligned(g, b, 8, 8))
+    if (plan.rows != 0 && mq && batch_aligned(g, b, 8, 8))
         return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
     if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || ((plan.x3 == 3 || plan.x3_run) && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);

@@ -185,6 +185,14 @@ bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].bf && !k
 bool x3_ragged(const X3Plan &pl) { return kVariant[pl.variant].rag; }
 int x3_tile_rows(const X3Plan &pl) { return kVariant[pl.variant].sh; }
 
+// at most `room` partial results; false if a workgroup would then add up more tiles than x3_most_tiles
+bool x3_fit(X3Plan &pl, long room)
+{
+    const long tiles = (long)pl.w_tiles * pl.h_tiles * pl.n_groups;
+    pl.splits = (int)std::max(1l, std::min((long)pl.splits, room));
+    return (tiles + pl.splits - 1) / pl.splits <= x3_most_tiles(kVariant[pl.variant]);
+}
+
 bool plan_exact_x3(const Geometry &g, X3Plan &best)
 {
     if (!g.bf16 && g.H == g.W && (g.W == 2 || g.W == 4)) {

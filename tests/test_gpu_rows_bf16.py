@@ -1,5 +1,5 @@
 """bf16 layers row after row (4x4 to 32x32 planes): edges of its tiles, groups of images and batch chunks, in runs of several
-layers (which take it whatever their size) and alone, against the oracle on every dW entry."""
+layers and (approximated ones) alone, against the oracle on every dW entry."""
 import numpy as np
 import pytest
 
@@ -44,7 +44,7 @@ def test_runs_match_the_oracle(hw):
 
 
 def test_alone_matches_the_oracle():
-    """From 9 GFLOP on a layer takes the form alone; the last batch chunk is shorter than the others."""
+    """A long layer alone, which another form takes; the last batch chunk is shorter than the others."""
     d = desc((131, 128, 16, 128))
     X, dY = rand_inputs(d, 3, "bf16")
     got = B.conv_wgrad_exact(d, to_gpu(X), to_gpu(dY)).cpu().numpy()
