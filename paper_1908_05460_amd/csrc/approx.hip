@@ -1837,8 +1837,9 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
         sp.scale = scale;
         return launch_exact_bf16_planes(g, b, st, &sp);
     }
-    // (a handful of positions alone: 64 -> 64 @ 4x4, N = 4: 14.3 us, 13.6 below)
-    if (pl.mm && pl.rows && (rsq || g.N * g.H * g.W >= 128)) {
+    // (a handful of positions alone: 64 -> 64 @ 4x4, N = 4: 14.3 us, 13.6 below; it copies X in 16-byte pieces, the form below
+    // reads 8 bytes at a time)
+    if (pl.mm && pl.rows && aligned16 && (rsq || g.N * g.H * g.W >= 128)) {
         ab.hw_word = 1;
         for (int i = 0; i < kMaxBatch; ++i) ab.sum[i] = nullptr;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rsq ? sq : nullptr);   // (a queued consumer issues queued selections first)

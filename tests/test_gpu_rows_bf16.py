@@ -109,3 +109,39 @@ def test_approximated_runs():
         want = oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx, sums)) * 0.25
         # a sum in 32 bits may round the other way than one in 64: one map's term of N in error by 2^-8
         assert normwise_err(got.cpu().numpy(), want) < 2.0 ** -8
+
+
+def shifted(a, by):
+    """The tensor `by` elements into an allocation."""
+    import torch
+    t = to_gpu(a)
+    buf = torch.empty(t.numel() + by, dtype=t.dtype, device="cuda")
+    buf[by:] = t.flatten()
+    return buf[by:].view(t.shape)
+
+
+@pytest.mark.parametrize("hw", [4, 8, 16])
+@pytest.mark.parametrize("by", [4, 8])
+def test_tensors_aligned_to_8_and_to_16_bytes(hw, by):
+    """The kernels copy 16 bytes at a time; an X that begins between two multiples of 16 takes another form, alone and in runs."""
+    import torch
+    ds = [desc((38, 64, hw, 128)), desc((38, 128, hw, 64)), desc((38, 128, 8, 128))]
+    data = [rand_inputs(d, 30 + i, "bf16") for i, d in enumerate(ds)]
+    Xs, dYs = [shifted(x, by) for x, _ in data], [shifted(y, by) for _, y in data]
+    assert all(x.data_ptr() % 16 == by * 2 % 16 for x in Xs)
+    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
+    S = B.Schedule(ds, Xs, dYs, out)
+    for method in (B.EXACT, B.APPROX):
+        mask = np.full(len(ds), method, np.uint8)
+        S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)), scale=1.0)
+        torch.cuda.synchronize()
+        for d, X, dY, (x, y), run in zip(ds, Xs, dYs, data, out):
+            if method == B.EXACT:
+                alone, want = B.conv_wgrad_exact(d, X, dY), oracle.wgrad_exact(oracle_shape(d), x, y)
+            else:
+                idx = torch.empty((d.N, d.K), dtype=torch.int32, device="cuda")
+                sums = torch.empty((d.N, d.K), device="cuda")
+                alone = B.conv_wgrad_approx(d, X, dY, idx_out=idx, sum_out=sums)
+                want = oracle.wgrad_exact(oracle_shape(d), x, rounded_sums(d, idx.cpu().numpy(), sums.cpu().numpy()))
+            for got in (run, alone):
+                assert normwise_err(got.cpu().numpy(), want) < TOL["fp32"] / 50
