@@ -9,7 +9,8 @@
 // in four clocks.)
 //   - 8x8, 4x4: the plane lies in a block of registers with a border of zeros; the position moves the source, nine taps.
 //   - 2x2: each position has sums of its own, four elements of X go to four of them, which the position moves to; the five taps
-//     in the padding are not computed.  (Sums of a tap over all positions are chains four times as long: error against 64 bits
+//     in the padding are not computed, so that a map's sum that is not finite makes no NaN there, as in the plain product that takes
+//     such a layer alone.  (Sums of a tap over all positions are chains four times as long: error against 64 bits
 //     1.17e-7 against 0.91e-7, N = 128.)  Sixteen registers an output channel, so four of them to a wavefront.
 // The block and the sums live in numbered registers, above those that the compiler is given (amdgpu_num_vgpr); they are
 // touched by the asm blocks below only.  4x4 and 2x2: 127 registers, four wavefronts a SIMD, which hide each other's LDS and
@@ -344,6 +345,10 @@ void approx_gather_regs8(const RegsMulti)
 bool regs_takes(const Geometry &g)
 {
     if (g.bf16 || g.R != 3 || g.S != 3 || g.ph != 1 || g.pw != 1 || g.H != g.W || (g.H != 8 && g.H != 4 && g.H != 2)) return false;
+    // Maps of up to four positions keep to the sparsified form, whose sums are the shorter chains (2x2, stride 2, 64 -> 128, N =
+    // 256: error against 64 bits 0.99e-7 against 2.04e-7 here, 4x4, stride 2: 0.87e-7 against 1.40e-7); on 2x2 planes without a
+    // stride the maps' four positions have sums of their own.
+    if (g.Ho * g.Wo <= 4 && (g.H != 2 || g.sh != 1 || g.sw != 1)) return false;
     // (scalar loads of eight or four maps at a time, whole tiles; a byte offset in X is 32 bits)
     return g.C % 64 == 0 && g.K % 32 == 0 && g.K >= 128 && tune_int("WGRAD_REGS", 1) && (long)g.N * g.C * g.H * g.W * 4 < (1l << 31);
 }

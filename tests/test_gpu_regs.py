@@ -78,3 +78,34 @@ def test_infinities(hw):
     fine = np.isfinite(want)
     assert not fine.all() and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
     assert normwise_err(got[fine], want[fine]) < BOUND
+
+
+# strided maps of up to four positions, which the registers do not take: (N, C, HW, K, stride)
+STRIDED = [(256, 64, 2, 128, 2), (256, 64, 4, 128, 2), (256, 64, 8, 128, 4)]
+
+
+@pytest.mark.parametrize("t", STRIDED)
+def test_strided_maps_of_few_positions_are_summed_in_short_chains(t):
+    """Alone and beside long work on 4x4 planes, which leaves each layer few batch chunks.  The error of a chain of N additions of terms
+    of one size grows as the square root of N: 2.0e-7 (2x2) and 1.4e-7 (4x4) in one of 256; the sparsified form's wavefronts add up
+    a quarter of them or less: 1.0e-7 and 0.9e-7."""
+    ds = [desc(t)] * 3 + [desc((t[0], 512, 4, 512, 1))]
+    data = [rand_inputs(d, 90 + i) for i, d in enumerate(ds)]
+    want = oracle.wgrad_approx(oracle_shape(ds[0]), *data[0])[0]
+    for got in (run_approx(ds, data)[0] * 4, B.conv_wgrad_approx(ds[0], *map(to_gpu, data[0])).cpu().numpy()):
+        assert np.linalg.norm(got - want) < 1.25e-7 * np.linalg.norm(want)
+
+
+@pytest.mark.parametrize("t", [(6, 64, 2, 128, 2), (6, 64, 4, 128, 1), (6, 64, 4, 128, 2), (6, 64, 8, 128, 1), (6, 64, 8, 128, 2)])
+def test_infinite_and_nan_map_sums(t):
+    """A map whose sum is not finite makes NaNs of the padding's zeros that its patch sees, in runs and alone."""
+    ds = [desc(t), desc((7, 64, 4, 128, 1))]
+    data = [rand_inputs(d, 11) for d in ds]
+    Y = data[0][1]
+    Y[1, 3, 0, 0], Y[2, 40, -1, -1], Y[5, 127, 0, -1] = np.inf, -np.inf, np.nan
+    with np.errstate(all="ignore"):
+        want = oracle.wgrad_approx(oracle_shape(ds[0]), *data[0])[0]
+    for got in (run_approx(ds, data)[0] * 4, B.conv_wgrad_approx(ds[0], *map(to_gpu, data[0])).cpu().numpy()):
+        fine = np.isfinite(want)
+        assert not fine.all() and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+        assert normwise_err(got[fine], want[fine]) < BOUND
