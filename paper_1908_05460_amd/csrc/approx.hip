@@ -1452,8 +1452,10 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
         pl.off_sum = off; off += align_up((size_t)g.N * g.K * 4);
         pl.off_part = off;
         const size_t room = alt.ws_bytes > off ? (alt.ws_bytes - off) / ((size_t)outs * 4) : 0;
-        pl.chunks = regs_max_chunks(g, room < 2 ? 1 : (int)std::min<size_t>(room, 64));
-        if (g.H == 4 && room >= 2) pl.chunks = std::max(pl.chunks, 2);
+        if (alt.use_lds) {
+            pl.ctiles = alt.ctiles; pl.ktiles = alt.ktiles; pl.gather_n = alt.gather_n;
+        }
+        pl.chunks = std::max(regs_max_chunks(g, room < 2 ? 1 : (int)std::min<size_t>(room, 64)), alt.use_lds ? alt.chunks : 1);
         pl.chunk_n = (g.N + pl.chunks - 1) / pl.chunks;
         pl.ws_bytes = std::max(alt.ws_bytes, off);
         return pl;
@@ -1542,6 +1544,7 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
     if (chunks < 1) chunks = 1;
     pl.chunk_n = (int)((g.N + chunks - 1) / chunks);
     pl.chunks = (g.N + pl.chunk_n - 1) / pl.chunk_n;
+    if (pl.use_lds) pl.gather_n = pl.chunk_n;
     size_t off = 0;
     pl.off_idx = off; off += align_up((size_t)g.N * g.K * 4);
     pl.off_sum = off; off += align_up((size_t)g.N * g.K * 4);
@@ -1732,6 +1735,21 @@ bool topk_gather_lds(const Geometry &g, const void *X, const int32_t *hw, const 
     return true;
 }
 
+// Images of a batch chunk of the LDS gather for nprob layers in one launch, alone or (shared) beside other groups'
+static int gather_chunk_n(const ApproxPlan &pl, int N, int nprob, bool shared)
+{
+    if (nprob == 1 && !shared) return pl.gather_n;
+    // the workgroup target is for the whole launch: a batch of layers chunks each layer's images less finely
+    const long tiles = (long)pl.ctiles * pl.ktiles * nprob;
+    // (a group that shares its launch with others: half as many, longer workgroups -- the next group's fill the chip
+    // as these finish, and the partial sums halve)
+    const int want_blocks = shared ? tune_int("WGRAD_GATHER_BLOCKS_SHARED", WGRAD_GATHER_BLOCKS / 2)
+                                   : tune_int("WGRAD_GATHER_BLOCKS", WGRAD_GATHER_BLOCKS);
+    const long chunks = tiles >= want_blocks ? 1 : (want_blocks + tiles - 1) / tiles;
+    // never more than planned: the workspace holds that many partials
+    return chunks < (N + pl.gather_n - 1) / pl.gather_n ? (int)((N + chunks - 1) / chunks) : pl.gather_n;
+}
+
 int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, float scale,
                   int32_t *idx_out, float *sum_out, void *ws, hipStream_t st, CombineQueue *defer, FusedQueue *fq,
                   Bf16Queue *bq, GatherQueue *gq, SelectQueue *sq, RegsQueue *rgq, RowsQueue *rsq)
@@ -1746,18 +1764,9 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     ApproxPlan pl = (plan.regs && !aligned) || (plan.regs == 2 && !rgq) ? plan_approx(g, true, true, true, false) : plan;
     if ((pl.use_lds || pl.fused || pl.mm) && !aligned) pl = plan_approx(g, false, false, false);   // (the sparsified form has no alignment needs: the exact launcher falls back by itself)
     const long outs = g.dw_elems();
-    if (pl.use_lds && (b.n > 1 || gq)) {
-        // the workgroup target is for the whole launch: a batch of layers chunks each layer's images less finely
-        const long tiles = (long)pl.ctiles * pl.ktiles * b.n;
-        // (a group that shares its launch with others: half as many, longer workgroups -- the next group's fill the chip
-        // as these finish, and the partial sums halve)
-        const int want_blocks = gq ? tune_int("WGRAD_GATHER_BLOCKS_SHARED", WGRAD_GATHER_BLOCKS / 2)
-                                   : tune_int("WGRAD_GATHER_BLOCKS", WGRAD_GATHER_BLOCKS);
-        long chunks = tiles >= want_blocks ? 1 : (want_blocks + tiles - 1) / tiles;
-        if (chunks < pl.chunks) {       // never more than planned: the workspace holds pl.chunks partials
-            pl.chunk_n = (int)((g.N + chunks - 1) / chunks);
-            pl.chunks = (g.N + pl.chunk_n - 1) / pl.chunk_n;
-        }
+    if (pl.use_lds) {
+        pl.chunk_n = gather_chunk_n(pl, g.N, b.n, gq != nullptr);
+        pl.chunks = (g.N + pl.chunk_n - 1) / pl.chunk_n;
     }
     if (pl.fused && (b.n > 1 || fq)) {
         long chunks;
@@ -1800,9 +1809,9 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
         ab.hw_row = at.row; ab.hw_col = at.col; ab.hw_base = at.base;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rgq ? sq : nullptr);
         if (rc != WGRAD_OK) return rc;
-        // 4x4: a layer alone among its shape goes in two halves, whose shorter sums are closer to 64 bits (256 -> 512, N = 128:
-        // 1.46e-7 against 1.09e-7)
-        return launch_regs(g, b, ab.hw, ab.sum, g.H == 4 && b.n == 1 && g.N > 64 ? std::min(2, pl.chunks) : 1, pl.chunks, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
+        // (no more lost to rounding than the LDS gather loses, as it would cut the batch here)
+        const int most_n = pl.gather_n > 0 ? gather_chunk_n(pl, g.N, b.n, gq != nullptr) : g.N;
+        return launch_regs(g, b, ab.hw, ab.sum, pl.chunks, most_n, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
     }
     if (pl.sx) {
         // the group's workspace (b.n slices of plan.ws_bytes, contiguous) is cut anew: the sparsified tensors of

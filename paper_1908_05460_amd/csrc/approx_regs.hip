@@ -366,7 +366,7 @@ struct RegsItem {
     const float *sum[kMaxBatch];
     char *part;                      // partial results of the first problem; the next problem's lie `stride` bytes on
     size_t stride;
-    int min_chunks, max_chunks;
+    int max_chunks, most_n;          // most chunks, most images of one (see regs_allowed)
     float scale;
 };
 struct RegsQueue {
@@ -375,6 +375,18 @@ struct RegsQueue {
 };
 RegsQueue *regs_queue_new() { return new RegsQueue; }
 void regs_queue_delete(RegsQueue *q) { delete q; }
+
+// The number of chunks nearest to `want` that loses no more to rounding than chunks of most_n images do.  Those are the longest: the
+// square of the error against 64 bits grows by 0.011e-14 for each image of a chunk, beside 0.66e-14 (512 -> 512 @ 4x4, N = 128
+// in one / two / four chunks 1.45e-7 / 1.21e-7 / 1.09e-7).  Several chunks cost about as much as three images each (N = 8 in one 0.86e-7, in
+// two 0.87e-7; N = 16 in one 0.915e-7, in four 0.915e-7), so a short batch may stay whole, and others are not cut into less than
+// sixteen images (128 -> 160 @ 4x4, N = 128, two layers 1.11e-7 in sixteen chunks, 1.07e-7 in seven).
+static int regs_allowed(const RegsItem &I, int want)
+{
+    const int N = I.g.N, least = (N + I.most_n - 1) / I.most_n, most = std::min(I.max_chunks, std::max(least, (N + 15) / 16));
+    if (want < least && N <= I.most_n + 3 * least) return 1;
+    return std::max(least, std::min(want, most));
+}
 
 // How the batches of n groups of layers, launched together, are cut, and how many wavefronts a workgroup has (eight share the
 // copies of X among twice as many output channels as four do, four make twice as many workgroups).
@@ -395,7 +407,7 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
             for (int i = 0; i < n; ++i) {
                 const Geometry &g = it[i]->g;
                 int ch = g.H == 2 ? (want + 1) / 2 : want;
-                ch = std::max(it[i]->min_chunks, std::min(ch, std::min(it[i]->max_chunks, (g.N + 7) / 8)));
+                ch = regs_allowed(*it[i], ch);
                 const int per = (g.N + ch - 1) / ch;
                 now[i] = (g.N + per - 1) / per;
                 if (now[i] > 1) partial += (double)now[i] * g.dw_elems() * 4 * it[i]->b.n;
@@ -432,7 +444,7 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
 int regs_max_chunks(const Geometry &g, int cap)
 {
     RegsItem I{};
-    I.g = g; I.b.n = 1; I.min_chunks = 1; I.max_chunks = cap;
+    I.g = g; I.b.n = 1; I.max_chunks = cap; I.most_n = g.N;
     const RegsItem *one = &I;
     int ch;
     double life;
@@ -500,13 +512,13 @@ int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine)
 
 // One group of identical layers, selected already (or recorded to be, where the launch is): its own launch, or (with a queue)
 // collected for regs_flush.
-int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int min_chunks, int max_chunks, float scale,
+int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, int most_n, float scale,
                 void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue)
 {
     RegsQueue local;
     RegsQueue &q = queue ? *queue : local;
     RegsItem &I = q.item[q.n++];
-    I.g = g; I.b = b; I.min_chunks = min_chunks; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride;
+    I.g = g; I.b = b; I.max_chunks = max_chunks; I.most_n = most_n; I.scale = scale; I.part = (char *)part; I.stride = stride;
     for (int i = 0; i < b.n; ++i) { I.at[i] = at[i]; I.sum[i] = sum[i]; }
     return queue ? WGRAD_OK : regs_flush(local, st, defer);
 }

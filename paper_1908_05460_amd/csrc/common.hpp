@@ -175,6 +175,7 @@ size_t exact_ws_per_problem(const Geometry &g, const ExactPlan &pl);
 struct ApproxPlan {
     int chunks, chunk_n;             // batch chunks whose partial sums are combined afterwards
     int use_lds, fused, m, nb, pitch, wp, ctiles, ktiles;   // LDS form of the gather: tile shape
+    int gather_n;                    // images of the LDS form's batch chunk alone; also where `regs` stands in for that form, which loses no more to rounding
     int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm), and the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
     int regs;                        // fp32, planes held in registers (approx_regs.hip): 0 no, 1 always, 2 in a run beside layers on 4x4 planes
@@ -207,7 +208,7 @@ RegsQueue *regs_queue_new();
 void regs_queue_delete(RegsQueue *q);
 bool regs_full(const RegsQueue &q);
 int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine);
-int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int min_chunks, int max_chunks, float scale,
+int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, int most_n, float scale,
                 void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue);
 // LDS-form gathers of several layer groups, collected for one launch
 GatherQueue *gather_queue_new(SelectQueue *selects = nullptr);

@@ -109,3 +109,21 @@ def test_infinite_and_nan_map_sums(t):
         fine = np.isfinite(want)
         assert not fine.all() and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
         assert normwise_err(got[fine], want[fine]) < BOUND
+
+
+@pytest.mark.parametrize("t, most, beside", [((16, 512, 4, 512, 1), 8, 0), ((128, 256, 4, 512, 1), 32, 1), ((33, 256, 8, 512, 1), 11, 3),
+                                             ((64, 256, 8, 512, 1), 16, 0), ((128, 64, 4, 128, 1), 8, 1)])
+def test_length_of_the_sums(t, most, beside):
+    """The images of a batch chunk, read off a sum that starts with 2^24: the ones that follow it in its chain are lost, those of the
+    other chunks are not."""
+    d = desc(t)
+    X, dY = np.ones((d.N, d.C, d.H, d.W), np.float32), np.zeros((d.N, d.K, d.Ho, d.Wo), np.float32)
+    X[0] = 2.0 ** 24
+    dY[:, :, 1, 1] = 1
+    if beside:
+        b = desc((d.N, 512, 4, 512, 1))
+        got = run_approx([d] + [b] * beside, [(X, dY)] + [rand_inputs(b, 1)] * beside)[0] * 4
+    else:
+        got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY)).cpu().numpy()
+    lost = d.N - 1 - (got - 2.0 ** 24)
+    assert 0 <= lost.min() and lost.max() <= most               # (most - 1, and one where the sum is odd)
