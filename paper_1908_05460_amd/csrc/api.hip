@@ -296,6 +296,40 @@ extern "C" size_t conv_wgrad_schedule_topk_workspace_bytes(const wgrad_conv_desc
     return topk >= 1 && topk <= kTopKMax ? schedule_ws_bytes(layers, method, nlayers, topk) : 0;
 }
 
+static int group_members(const int *group, int n, int first)
+{
+    int members = 0;
+    for (int j = first; j < n; ++j) members += group[j] == first;
+    return members;
+}
+
+// Which groups take the forms that pay in a run only where enough work shares their launch.  On entry the plans say which could, on
+// return which do.
+static void choose_run_forms(const uint8_t *method, int n, const int *group, std::vector<LayerPlan> &plan)
+{
+    auto each = [&](int which, auto &&f) {
+        for (int i = 0; i < n; ++i)
+            if (method[i] == which && group[i] == i) f(plan[i], group_members(group, n, i));
+    };
+    // Exact bf16 layers row after row: their launch takes a workgroup's set-up, a CU for each workgroup and partial results, and what
+    // is left of the run keeps launches of its own.  Three shapes share it well -- four where bf16 layers that it does not take (2x2
+    // planes) would share the row-window kernel's -- and two where nothing else is exact and each tile has twelve blocks of four
+    // rows and more, from 320 blocks in all.  (Of 700 runs timed both ways 140 were slower row after row where any two exact
+    // layers sufficed, 512 -> 512 @ 4x4 beside 2x2 planes, N = 64, 18 us against 35; by this line one, 172 against 184.)
+    int nexact = 0, nrows = 0, others = 0;
+    long blocks = 0, tiles = 0;
+    each(WGRAD_EXACT, [&](LayerPlan &p, int members) {
+        ++nexact;
+        others += p.ex.mm16 && !p.ex.rows;
+        if (p.ex.rows != 1) return;
+        ++nrows;
+        blocks += rows_blocks(p.g) * rows_tiles(p.g) * members;
+        tiles += (long)rows_tiles(p.g) * members;
+    });
+    const bool rows = blocks >= 320 && (nrows >= (others ? 4 : 3) || (nrows == 2 && nexact == 2 && blocks >= 12 * tiles));
+    each(WGRAD_EXACT, [&](LayerPlan &p, int) { if (!rows) p.ex.rows = 0; });
+}
+
 static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X, const void *const *dY,
                              float *const *dW, const uint8_t *method, int32_t nlayers, int topk, float scale,
                              float sigma, uint64_t seed, uint64_t offset, void *ws, size_t ws_bytes,
@@ -324,6 +358,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     for (int i = 0; i < nlayers; ++i)
         if (method[i] == WGRAD_EXACT && !plan[group[i]].ex.ok) return WGRAD_UNSUPPORTED;
     if (!ws_ok(ws, ws_bytes, schedule_ws_bytes(group, plan, nlayers))) return WGRAD_WORKSPACE_TOO_SMALL;
+    choose_run_forms(method, nlayers, group, plan);
 
     // pass 2: enqueue on the caller's stream: one launch sequence per group of exact or approximated
     // layers, then one reduction of all their partial results, then the zero and the random fills
@@ -338,8 +373,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     // groups that the fp32 multi-shape launch carries (those of the 2x2-plane form add nothing to its shares)
     auto group_flops = [&](int i) {
         const ExactPlan &ex = plan[i].ex;
-        int members = 0;
-        for (int j = i; j < nlayers; ++j) members += group[j] == i;
+        const int members = group_members(group, nlayers, i);
         if (ex.plane2 || ex.x3 == 2 || ((ex.x3 == 3 || ex.x3_run) && members > 1)) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
@@ -373,7 +407,9 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     }
     Bf16Queue *bq = nbf16 > 1 && tune_int("WGRAD_BF16_MULTI", 1) ? bf16_queue_new(sq) : nullptr;
     X3Queue *xq = x3_queue_new();
-    RowsQueue *rq = rows_queue_new();
+    int nrows = 0;                   // exact bf16 groups that go row after row
+    for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows;
+    RowsQueue *rq = nrows > 0 ? rows_queue_new() : nullptr;
     int nsparse = 0;                 // approximated bf16 groups that go row after row
     for (int i = 0; i < nlayers; ++i) nsparse += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.rows;
     RowsQueue *rsq = nsparse > 0 ? rows_queue_new_sparse(sq) : nullptr;
@@ -384,10 +420,6 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
         nregs4 += plan[i].g.H == 4;
     }
     RegsQueue *rgq = nregs > 0 ? regs_queue_new() : nullptr;
-    int nrows = 0;
-    for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows == 1;
-    for (int i = 0; i < nlayers; ++i)
-        if (method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows == 3 && nrows == 0) plan[i].ex.rows = 0;
     char *ws_next = (char *)ws;
     int rc = WGRAD_OK;
     for (int i = 0; i < nlayers && rc == WGRAD_OK; ++i) {
@@ -437,8 +469,10 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     }
     if (rc == WGRAD_OK) rc = x3_flush(*xq, st, &queue);
     x3_queue_delete(xq);
-    if (rc == WGRAD_OK) rc = rows_flush(*rq, st, &queue);
-    rows_queue_delete(rq);
+    if (rq) {
+        if (rc == WGRAD_OK) rc = rows_flush(*rq, st, &queue);
+        rows_queue_delete(rq);
+    }
     if (rc == WGRAD_OK && mq) rc = multi_flush(multi, st);
     if (bq) {
         if (rc == WGRAD_OK) rc = bf16_flush(*bq, st);
@@ -475,6 +509,24 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     }
     return rc;
 }
+
+// The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 0
+// another.  For tests of the choice on the host.
+namespace wgrad {
+int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form)
+{
+    int group[4096];
+    std::vector<LayerPlan> plan;
+    const int rc = n > 0 && n <= 4096 ? plan_groups(layers, method, n, 0, group, plan) : WGRAD_INVALID_ARG;
+    if (rc != WGRAD_OK) return rc;
+    choose_run_forms(method, n, group, plan);
+    for (int i = 0; i < n; ++i) {
+        const LayerPlan &p = plan[group[i]];
+        form[i] = method[i] == WGRAD_EXACT && p.ex.rows ? 1 : (method[i] == WGRAD_APPROX && p.ap.rows ? 2 : 0);
+    }
+    return WGRAD_OK;
+}
+}  // namespace wgrad
 
 extern "C" int conv_wgrad_schedule_run(const wgrad_conv_desc *layers, const void *const *X, const void *const *dY,
                             float *const *dW, const uint8_t *method, int32_t nlayers, float scale,

@@ -80,8 +80,9 @@ bool rows_takes(const Geometry &g)
     return tune_int("WGRAD_ROWS", 1) && (long)g.N * g.H * g.W * 2 * std::max(g.C, g.K) < (1l << 31);
 }
 
-static int rows_tiles(const Geometry &g) { return (g.K / kRowsTile) * ((g.C + kRowsTile - 1) / kRowsTile); }
+int rows_tiles(const Geometry &g) { return (g.K / kRowsTile) * ((g.C + kRowsTile - 1) / kRowsTile); }
 static int rows_groups(const Geometry &g) { return (g.N + rows_images(g.W) - 1) / rows_images(g.W); }
+long rows_blocks(const Geometry &g) { return (long)rows_groups(g) * (g.H / 4); }
 
 // How the batches of `n` groups of layers, launched together, are cut: chunks[i] workgroups share the images of every tile
 // of group i.  A workgroup has a CU to itself and takes block_us for each block of four rows; finer cuts fill the CUs more
@@ -91,7 +92,7 @@ static void rows_cut(const RowsItem *const *it, int n, bool sparse, int *chunks,
     const double block_us = sparse ? tune_int("WGRAD_ROWS_SPARSE_NS", 900) * 1e-3 : tune_int("WGRAD_ROWS_BLOCK_NS", 1600) * 1e-3, fixed_us = 9.0;
     static const double kShare[] = {1.5, 1.25, 1.1, 1.0, 0.9, 0.8, 0.67, 0.57, 0.5, 0.4, 0.33, 0.25, 0.2};
     double total = 0;
-    for (int i = 0; i < n; ++i) total += (double)rows_groups(it[i]->g) * (it[i]->g.H / 4) * rows_tiles(it[i]->g) * it[i]->b.n;
+    for (int i = 0; i < n; ++i) total += (double)rows_blocks(it[i]->g) * rows_tiles(it[i]->g) * it[i]->b.n;
     double best = 1e30;
     for (const double share : kShare) {
         const double target = total / kNumCU * share;

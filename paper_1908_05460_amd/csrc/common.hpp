@@ -100,7 +100,7 @@ struct ExactPlan {
     int direct;                      // general form: no tile of whole output rows fits the LDS
     int x3;                          // exact_x3.hip's form: 0 no, 1 if alone, 2 always, 3 in a run of several layers only
     X3Plan x3p;
-    int rows;                        // bf16_rows.hip's form: 0 no, 1 in a run of several exact layers, 3 in a run with a layer of 1
+    int rows;                        // bf16_rows.hip's form, in a run with enough work for it: 0 no, 1 yes, 3 beside layers of 1
     int rows_chunks;                 // ... the most batch chunks
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     int x3_run;                      // x3's form also in a run, for two and more layers of a shape
@@ -133,6 +133,8 @@ int launch_exact_x3(const Geometry &g, const X3Plan &plan, const Batch &b, void 
 double makespan_us(int slots, const double *life, const long *count, int n);
 // bf16, planes of 4x4, 8x8, 16x16 or 32x32, row after row (bf16_rows.hip)
 bool rows_takes(const Geometry &g);
+int rows_tiles(const Geometry &g);                   // 64 x 64 channels
+long rows_blocks(const Geometry &g);                 // of four rows of a group of images, in each tile
 int rows_max_chunks(const Geometry &g, bool sparse = false, int cap = 1 << 20);
 struct RowsQueue;
 struct SelectQueue;

@@ -674,7 +674,7 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
 ExactPlan plan_exact(const Geometry &g)
 {
     ExactPlan pl = plan_exact_x3_or_older(g);
-    // bf16 on 4x4 to 32x32 planes, row after row: in a run of several layers, where one launch takes them all (VGG-19 exact, N =
+    // bf16 on 4x4 to 32x32 planes, row after row: in a run of enough such work, which one launch takes (VGG-19 exact, N =
     // 16 / 64 / 160 / 512: 104 / 143 / 211 / 470 us -> 58 / 85 / 154 / 372; under half the masks of a schedule 1.4 to 1.7 times as
     // fast).  Not alone: it needs 256 partial results of a tile to fill the chip, the row-window kernel half as many, and the
     // workspace is that one's (38.7 GFLOP, 64 -> 64 @ 32x32 / 128 -> 128 @ 16x16 / 512 -> 512 @ 8x8: 52.3 / 49.6 / 145 us, here with
@@ -741,7 +741,7 @@ static int launch_exact_staged(const Geometry &g, const ExactPlan &pl, const voi
 int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void *ws, hipStream_t st, CombineQueue *defer,
                  MultiQueue *mq, int mq_blocks, Bf16Queue *bq, X3Queue *xq, RowsQueue *rq)
 {
-    if (plan.rows != 0 && mq && batch_aligned(g, b, 8, 8))
+    if (plan.rows && rq && batch_aligned(g, b, 8, 8))
         return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
     if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || ((plan.x3 == 3 || plan.x3_run) && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);

@@ -6,6 +6,7 @@ import pytest
 import oracle
 from paper_1908_05460_amd import binding as B
 from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
+from tests.test_run_forms import ROWS, SPARSE_ROWS, forms
 
 pytestmark = pytest.mark.gpu
 
@@ -22,14 +23,24 @@ def desc(t):
     return B.desc(N, C, HW, HW, K, R=3, S=3, pad=1, dtype=B.BF16)
 
 
-def run_exact(ds, data):
+def run_layers(ds, Xs, dYs, method, scale=1.0):
+    """The layers in one run, beside a layer of zeros that is work enough for this form to take the run."""
     import torch
+    more = desc((320, 64, 16, 64))
+    ds = ds + [more]
+    Xs, dYs = Xs + [torch.zeros((320, 64, 16, 16), dtype=torch.bfloat16, device="cuda")], dYs + [torch.zeros((320, 64, 16, 16), dtype=torch.bfloat16, device="cuda")]
+    assert forms([(method, "bf16", d.N, d.C, d.H, d.K, 1) for d in ds]) == [ROWS if method == B.EXACT else SPARSE_ROWS] * len(ds)
     out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
-    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
-    mask = np.full(len(ds), B.EXACT, np.uint8)
-    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)))
+    S = B.Schedule(ds, Xs, dYs, out)
+    mask = np.full(len(ds), method, np.uint8)
+    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)), scale=scale)
     torch.cuda.synchronize()
-    return [o.cpu().numpy() for o in out]
+    assert not out[-1].any()
+    return out[:-1]
+
+
+def run_exact(ds, data):
+    return [o.cpu().numpy() for o in run_layers(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], B.EXACT)]
 
 
 @pytest.mark.parametrize("hw", [4, 8, 16, 32])
@@ -96,14 +107,9 @@ def test_approximated_alone(t):
 
 def test_approximated_runs():
     """All shapes in one launch; more groups than one carries."""
-    import torch
     ds = [desc(t) for t in SHAPES if t[2] <= 16]
     data = [rand_inputs(d, 80 + i, "bf16") for i, d in enumerate(ds)]
-    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
-    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
-    mask = np.full(len(ds), B.APPROX, np.uint8)
-    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)), scale=0.25)
-    torch.cuda.synchronize()
+    out = run_layers(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], B.APPROX, scale=0.25)
     for d, (X, dY), got in zip(ds, data, out):
         idx, sums = oracle.select(oracle_shape(d), dY)
         want = oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx, sums)) * 0.25
@@ -129,12 +135,8 @@ def test_tensors_aligned_to_8_and_to_16_bytes(hw, by):
     data = [rand_inputs(d, 30 + i, "bf16") for i, d in enumerate(ds)]
     Xs, dYs = [shifted(x, by) for x, _ in data], [shifted(y, by) for _, y in data]
     assert all(x.data_ptr() % 16 == by * 2 % 16 for x in Xs)
-    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for d in ds]
-    S = B.Schedule(ds, Xs, dYs, out)
     for method in (B.EXACT, B.APPROX):
-        mask = np.full(len(ds), method, np.uint8)
-        S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)), scale=1.0)
-        torch.cuda.synchronize()
+        out = run_layers(ds, Xs, dYs, method)
         for d, X, dY, (x, y), run in zip(ds, Xs, dYs, data, out):
             if method == B.EXACT:
                 alone, want = B.conv_wgrad_exact(d, X, dY), oracle.wgrad_exact(oracle_shape(d), x, y)

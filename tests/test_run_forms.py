@@ -1,0 +1,54 @@
+"""Which form the layers of a run take (host code of libwgrad): forms that pay only where enough work shares their launch, by runs
+that were timed both ways."""
+import ctypes as ct
+
+import pytest
+
+from paper_1908_05460_amd import binding as B, inputs
+
+ROWS, SPARSE_ROWS = 1, 2            # bf16 layers row after row, exact and approximated
+E, A = B.EXACT, B.APPROX
+
+
+def forms(run):
+    """run: [(method, type, N, C, H = W, K, layers)] -> the forms of its shapes"""
+    descs, methods, at = [], [], []
+    for method, dtype, n, c, hw, k, count in run:
+        at.append(len(descs))
+        descs += [B.desc(n, c, hw, hw, k, dtype=B.BF16 if dtype == "bf16" else B.F32)] * count
+        methods += [method] * count
+    f = B.load()._ZN5wgrad14schedule_formsEPK15wgrad_conv_descPKhiPi
+    f.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_int, ct.c_void_p]
+    n = len(descs)
+    out = (ct.c_int * n)()
+    assert f((B.ConvDesc * n)(*descs), (ct.c_uint8 * n)(*methods), n, out) == 0
+    return [out[i] for i in at]
+
+
+def stack(layers, method, dtype, n):
+    return [(method(i) if callable(method) else method, dtype, n, l.C, l.H, l.K, 1) for i, l in enumerate(layers)]
+
+
+# us before the form / with it
+@pytest.mark.parametrize("run, taken", [
+    ([(E, "bf16", 64, 512, 4, 512, 1), (E, "bf16", 64, 512, 2, 512, 1)], [0, 0]),                       # 18.1 / 35.4
+    ([(E, "bf16", 512, 512, 4, 512, 1), (E, "bf16", 512, 16, 32, 16, 1)], [0, 0]),                      # 46.1 / 56.8
+    ([(E, "bf16", 64, 128, 4, 128, 4), (E, "fp32", 64, 16, 16, 16, 1)], [0, 0]),                        # 22.6 / 33.0
+    ([(E, "bf16", 200, 256, 8, 256, 1), (E, "bf16", 200, 128, 2, 128, 1)], [0, 0]),                     # 32.9 / 40.1
+    ([(E, "bf16", 16, 512, 4, 512, 1), (E, "bf16", 16, 512, 8, 512, 1)], [0, 0]),                       # 18.7 / 25.6
+    ([(E, "bf16", 64, 3, 32, 64, 1), (E, "bf16", 64, 64, 8, 64, 1)], [0, 0]),                           # 17.8 / 22.7
+    ([(E, "bf16", 9, 256, 4, 256, 5), (E, "bf16", 9, 512, 4, 512, 1), (E, "bf16", 9, 64, 4, 64, 1)], [0, 0, 0]),   # too short
+    ([(E, "bf16", 512, 512, 4, 512, 1), (E, "bf16", 512, 512, 8, 512, 1)], [ROWS, ROWS]),               # 203.7 / 142.2
+    ([(E, "bf16", 200, 512, 4, 512, 4), (E, "bf16", 200, 512, 8, 512, 1)], [ROWS, ROWS]),               # 133.8 / 96.5
+])
+def test_exact_bf16_row_after_row(run, taken):
+    assert forms(run) == taken
+
+
+@pytest.mark.parametrize("n", [16, 64, 160, 512])
+def test_exact_bf16_vgg19_goes_row_after_row(n):
+    """All but the 2x2 planes and, in long batches, the first layer; also with every other layer approximated."""
+    layers = inputs.vgg19_stack()
+    for every in (1, 2):
+        got = forms(stack(layers, lambda i: E if i % every == 0 else A, "bf16", n))
+        assert [f == ROWS for f in got] == [i % every == 0 and l.H >= 4 and (l.C >= 16 or n < 512) for i, l in enumerate(layers)]
