@@ -328,6 +328,23 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     });
     const bool rows = blocks >= 320 && (nrows >= (others ? 4 : 3) || (nrows == 2 && nexact == 2 && blocks >= 12 * tiles));
     each(WGRAD_EXACT, [&](LayerPlan &p, int) { if (!rows) p.ex.rows = 0; });
+    // Approximated bf16 layers row after row: from 1280 blocks on, 512 of four shapes and more, or where they are two and more layers of
+    // one shape, wider than 4x4, and all that the run has for the bf16 matrix core; not for one layer alone, which goes as in a call of its own
+    // where nothing else is on that core.  (Of 830 timed runs 91 were slower where any two layers sufficed, 128 -> 128 @ 4x4, three
+    // layers, N = 64, 11.6 us against 22.2; by this line three, 64 -> 64 @ 8x8, three layers, N = 200, by 4 to 9 %.)
+    int nsparse = 0, sparse_layers = 0, sparse_wide = 0, on_bf16 = 0;
+    blocks = 0;
+    each(WGRAD_EXACT, [&](LayerPlan &p, int) { on_bf16 += p.ex.mm16; });
+    each(WGRAD_APPROX, [&](LayerPlan &p, int members) {
+        on_bf16 += p.ap.mm;
+        if (!p.ap.rows) return;
+        ++nsparse;
+        sparse_layers += members;
+        sparse_wide += p.g.W > 4;
+        blocks += rows_blocks(p.g) * rows_tiles(p.g) * members;
+    });
+    const bool sparse = sparse_layers > 1 && (blocks >= (nsparse >= 4 ? 512 : 1280) || (sparse_wide == 1 && on_bf16 == 1));
+    each(WGRAD_APPROX, [&](LayerPlan &p, int) { if (p.ap.rows && sparse) p.ap.rows = 2; });
 }
 
 static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X, const void *const *dY,
@@ -410,8 +427,8 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     int nrows = 0;                   // exact bf16 groups that go row after row
     for (int i = 0; i < nlayers; ++i) nrows += method[i] == WGRAD_EXACT && group[i] == i && plan[i].ex.rows;
     RowsQueue *rq = nrows > 0 ? rows_queue_new() : nullptr;
-    int nsparse = 0;                 // approximated bf16 groups that go row after row
-    for (int i = 0; i < nlayers; ++i) nsparse += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.rows;
+    int nsparse = 0;                 // approximated ones
+    for (int i = 0; i < nlayers; ++i) nsparse += method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.rows == 2;
     RowsQueue *rsq = nsparse > 0 ? rows_queue_new_sparse(sq) : nullptr;
     int nregs = 0, nregs4 = 0;       // groups that the form of planes in registers takes; those on 4x4 planes
     for (int i = 0; i < nlayers; ++i) {
@@ -453,7 +470,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
             continue;
         }
         else rc = launch_approx(g, plan[i].ap, b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq,
-                                plan[i].ap.regs == 2 && nregs4 == 0 ? nullptr : rgq, nsparse == 1 && b.n == 1 ? nullptr : rsq);
+                                plan[i].ap.regs == 2 && nregs4 == 0 ? nullptr : rgq, plan[i].ap.rows == 2 ? rsq : nullptr);
         ws_next += align_up(plan[i].ws) * b.n;
     }
     if (sq) {
@@ -522,7 +539,7 @@ int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, 
     choose_run_forms(method, n, group, plan);
     for (int i = 0; i < n; ++i) {
         const LayerPlan &p = plan[group[i]];
-        form[i] = method[i] == WGRAD_EXACT && p.ex.rows ? 1 : (method[i] == WGRAD_APPROX && p.ap.rows ? 2 : 0);
+        form[i] = method[i] == WGRAD_EXACT && p.ex.rows ? 1 : (method[i] == WGRAD_APPROX && p.ap.rows == 2 ? 2 : 0);
     }
     return WGRAD_OK;
 }

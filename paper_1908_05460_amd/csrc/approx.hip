@@ -1834,11 +1834,11 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     }
     bool aligned16 = true;
     for (int i = 0; i < b.n; ++i) aligned16 = aligned16 && ((uintptr_t)b.X[i] % 16) == 0;
-    // 2x2 planes, and 4x4 planes alone unless the batch is long and the tiles few: the position-major kernel, its A operand built
-    // from the selections; it writes dW itself, a workgroup all images.  (512 -> 512 @ 4x4, N = 512, alone: 36 us, row after row
-    // 52; three such layers in a run 84 against 76; 64 -> 64 30 against 19)
-    const bool few = g.N >= 384 && (g.K / 64) * ((g.C + 63) / 64) <= 4;
-    if (pl.mm && planes_bf16_takes(g) && aligned16 && (g.H <= 2 || (!rsq && !few))) {
+    // 2x2 planes, and 4x4 planes where no other group shares a launch unless the batch is long and the tiles few: the position-major
+    // kernel, its A operand built from the selections; it writes dW itself, a workgroup all images.  (512 -> 512 @ 4x4, N = 512,
+    // alone: 36 us, row after row 52; three such layers in a run 84 against 76; 64 -> 64 30 against 19)
+    const bool alone = !bq && b.n == 1, few = g.N >= 384 && (g.K / 64) * ((g.C + 63) / 64) <= 4;
+    if (pl.mm && planes_bf16_takes(g) && aligned16 && (g.H <= 2 || (!rsq && !bq && !(alone && few)))) {
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, nullptr);
         if (rc != WGRAD_OK) return rc;
         SparseA sp{};
@@ -1848,7 +1848,7 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     }
     // (a handful of positions alone: 64 -> 64 @ 4x4, N = 4: 14.3 us, 13.6 below; it copies X in 16-byte pieces, the form below
     // reads 8 bytes at a time)
-    if (pl.mm && pl.rows && aligned16 && (rsq || g.N * g.H * g.W >= 128)) {
+    if (pl.mm && pl.rows && aligned16 && (rsq || (alone && g.N * g.H * g.W >= 128))) {
         ab.hw_word = 1;
         for (int i = 0; i < kMaxBatch; ++i) ab.sum[i] = nullptr;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rsq ? sq : nullptr);   // (a queued consumer issues queued selections first)

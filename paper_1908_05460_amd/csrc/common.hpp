@@ -178,7 +178,7 @@ struct ApproxPlan {
     int chunks, chunk_n;             // batch chunks whose partial sums are combined afterwards
     int use_lds, fused, m, nb, pitch, wp, ctiles, ktiles;   // LDS form of the gather: tile shape
     int gather_n;                    // images of the LDS form's batch chunk alone; also where `regs` stands in for that form, which loses no more to rounding
-    int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm), and the most batch chunks
+    int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm): 0 no, 1 a layer alone, 2 in a run with enough such work; the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
     int regs;                        // fp32, planes held in registers (approx_regs.hip): 0 no, 1 always, 2 in a run beside layers on 4x4 planes
     int sx;                          // fp32, planes of up to four positions: exact kernel on the sparsified dY

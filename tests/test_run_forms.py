@@ -52,3 +52,30 @@ def test_exact_bf16_vgg19_goes_row_after_row(n):
     for every in (1, 2):
         got = forms(stack(layers, lambda i: E if i % every == 0 else A, "bf16", n))
         assert [f == ROWS for f in got] == [i % every == 0 and l.H >= 4 and (l.C >= 16 or n < 512) for i, l in enumerate(layers)]
+
+
+@pytest.mark.parametrize("run, taken", [
+    ([(A, "bf16", 64, 128, 4, 128, 3)], [0]),                                                           # 11.6 / 22.2
+    ([(A, "bf16", 16, 512, 4, 512, 1), (A, "bf16", 16, 512, 2, 512, 1)], [0, 0]),                       # 21.5 / 39.2
+    ([(A, "bf16", 200, 128, 4, 128, 1), (A, "bf16", 200, 128, 2, 128, 1)], [0, 0]),                     # 25.3 / 38.3
+    ([(A, "bf16", 16, 256, 8, 256, 3), (A, "bf16", 16, 64, 16, 64, 1)], [0, 0]),                        # 23.9 / 30.0
+    ([(A, "bf16", 48, 512, 4, 512, 1), (A, "bf16", 48, 512, 2, 512, 1)], [0, 0]),                       # 26.3 / 41.0
+    ([(A, "bf16", 512, 512, 4, 512, 1), (E, "bf16", 512, 64, 16, 64, 1)], [0, 0]),                      # one layer
+    ([(A, "bf16", 512, 512, 4, 512, 3)], [SPARSE_ROWS]),                                                # 95.4 / 75.6
+    ([(A, "bf16", 64, 64, 16, 64, 3)], [SPARSE_ROWS]),                                                  # 27.5 / 23.3
+    ([(A, "bf16", 256, 64, 8, 64, 5), (A, "bf16", 256, 16, 32, 16, 7)], [SPARSE_ROWS, 0]),              # (ResNet-20) 72.2 / 65.2
+    ([(A, "bf16", 64, 64, 8, 64, 4), (E, "bf16", 64, 64, 8, 64, 1)], [0, 0]),
+    ([(A, "bf16", 200, 128, 16, 128, 1), (A, "bf16", 200, 64, 16, 64, 1)], [SPARSE_ROWS, SPARSE_ROWS]),  # 56.7 / 37.1
+    ([(A, "bf16", 200, 256, 8, 256, 2), (E, "bf16", 200, 64, 16, 64, 1)], [SPARSE_ROWS, 0]),            # 113.4 / 54.5
+])
+def test_approximated_bf16_row_after_row(run, taken):
+    assert forms(run) == taken
+
+
+@pytest.mark.parametrize("n", [16, 64, 160, 512])
+def test_approximated_bf16_vgg19_goes_row_after_row(n):
+    """All on 4x4 to 16x16 planes; also, from N = 64 on, with every other layer exact."""
+    layers = inputs.vgg19_stack()
+    for every in (1, 2) if n >= 64 else (1,):
+        got = forms(stack(layers, lambda i: A if i % every == every - 1 else E, "bf16", n))
+        assert [f == SPARSE_ROWS for f in got] == [i % every == every - 1 and 4 <= l.H <= 16 for i, l in enumerate(layers)]
