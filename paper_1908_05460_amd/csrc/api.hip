@@ -314,36 +314,45 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     // Exact bf16 layers row after row: their launch takes a workgroup's set-up, a CU for each workgroup and partial results, and what
     // is left of the run keeps launches of its own.  Three shapes share it well -- four where bf16 layers that it does not take (2x2
     // planes) would share the row-window kernel's -- and two where nothing else is exact and each tile has twelve blocks of four
-    // rows and more, from 320 blocks in all.  (Of 700 runs timed both ways 140 were slower row after row where any two exact
+    // rows and more, from 320 blocks in all.  One shape of two and more layers wider than 4x4 gains where the run has other exact
+    // layers, none of them for the row-window kernel or a first layer, which leaves that kernel no launch to share (64 -> 64 @ 8x8, five
+    // layers, beside ResNet-20's narrower ones, N = 256: 83.7 us against 77.6), and in long batches alone (512 -> 512 @ 8x8, two
+    // layers, N = 200: 112 us against 95).  (Of 700 runs timed both ways 140 were slower row after row where any two exact
     // layers sufficed, 512 -> 512 @ 4x4 beside 2x2 planes, N = 64, 18 us against 35; by this line one, 172 against 184.)
-    int nexact = 0, nrows = 0, others = 0;
+    int nexact = 0, nrows = 0, others = 0, first = 0, wide_pairs = 0;
     long blocks = 0, tiles = 0;
     each(WGRAD_EXACT, [&](LayerPlan &p, int members) {
         ++nexact;
         others += p.ex.mm16 && !p.ex.rows;
+        first += p.ex.rows == 3;
         if (p.ex.rows != 1) return;
         ++nrows;
+        wide_pairs += members > 1 && p.g.W > 4;
         blocks += rows_blocks(p.g) * rows_tiles(p.g) * members;
         tiles += (long)rows_tiles(p.g) * members;
     });
-    const bool rows = blocks >= 320 && (nrows >= (others ? 4 : 3) || (nrows == 2 && nexact == 2 && blocks >= 12 * tiles));
+    const bool one_shape = nrows == 1 && wide_pairs == 1 && !others && !first && blocks >= (nexact > 1 ? 12 : 100) * tiles && (nexact > 1 || blocks >= 3072);
+    const bool rows = one_shape || (blocks >= 320 && (nrows >= (others ? 4 : 3) || (nrows == 2 && nexact == 2 && blocks >= 12 * tiles)));
     each(WGRAD_EXACT, [&](LayerPlan &p, int) { if (!rows) p.ex.rows = 0; });
-    // Approximated bf16 layers row after row: from 1280 blocks on, 512 of four shapes and more, or where they are two and more layers of
-    // one shape, wider than 4x4, and all that the run has for the bf16 matrix core; not for one layer alone, which goes as in a call of its own
-    // where nothing else is on that core.  (Of 830 timed runs 91 were slower where any two layers sufficed, 128 -> 128 @ 4x4, three
+    // Approximated bf16 layers row after row: from 1280 blocks on, from 512 where they are of four shapes and more or the exact layers do
+    // not share the row-window kernel's launch with them, or where they are two and more layers of one shape, wider than 4x4, and
+    // all that the run has for the bf16 matrix core -- or all but exact layers, with 80 blocks a tile; not for one layer alone, which
+    // goes as in a call of its own where nothing else is on that core.  (Of 830 timed runs 91 were slower where any two layers sufficed, 128 -> 128 @ 4x4, three
     // layers, N = 64, 11.6 us against 22.2; by this line three, 64 -> 64 @ 8x8, three layers, N = 200, by 4 to 9 %.)
-    int nsparse = 0, sparse_layers = 0, sparse_wide = 0, on_bf16 = 0;
-    blocks = 0;
-    each(WGRAD_EXACT, [&](LayerPlan &p, int) { on_bf16 += p.ex.mm16; });
+    int nsparse = 0, sparse_layers = 0, sparse_wide = 0, nmm = 0, nmm_exact = 0;
+    blocks = tiles = 0;
+    each(WGRAD_EXACT, [&](LayerPlan &p, int) { nmm_exact += p.ex.mm16; });
     each(WGRAD_APPROX, [&](LayerPlan &p, int members) {
-        on_bf16 += p.ap.mm;
+        nmm += p.ap.mm;
         if (!p.ap.rows) return;
         ++nsparse;
         sparse_layers += members;
         sparse_wide += p.g.W > 4;
         blocks += rows_blocks(p.g) * rows_tiles(p.g) * members;
+        tiles += (long)rows_tiles(p.g) * members;
     });
-    const bool sparse = sparse_layers > 1 && (blocks >= (nsparse >= 4 ? 512 : 1280) || (sparse_wide == 1 && on_bf16 == 1));
+    const bool sparse = sparse_layers > 1 && (blocks >= (nsparse >= 4 || rows ? 512 : 1280) ||
+                                              (sparse_wide == 1 && nmm == 1 && (nmm_exact == 0 || blocks >= 80 * tiles)));
     each(WGRAD_APPROX, [&](LayerPlan &p, int) { if (p.ap.rows && sparse) p.ap.rows = 2; });
 }
 

@@ -40,6 +40,12 @@ def stack(layers, method, dtype, n):
     ([(E, "bf16", 9, 256, 4, 256, 5), (E, "bf16", 9, 512, 4, 512, 1), (E, "bf16", 9, 64, 4, 64, 1)], [0, 0, 0]),   # too short
     ([(E, "bf16", 512, 512, 4, 512, 1), (E, "bf16", 512, 512, 8, 512, 1)], [ROWS, ROWS]),               # 203.7 / 142.2
     ([(E, "bf16", 200, 512, 4, 512, 4), (E, "bf16", 200, 512, 8, 512, 1)], [ROWS, ROWS]),               # 133.8 / 96.5
+    ([(E, "bf16", 256, 64, 8, 64, 5), (E, "bf16", 256, 16, 32, 16, 7)], [ROWS, 0]),                     # (ResNet-20) 83.7 / 77.6
+    ([(E, "bf16", 200, 512, 8, 512, 2)], [ROWS]),                                                       # 111.9 / 95.7
+    ([(E, "bf16", 64, 512, 8, 512, 2)], [0]),                                                           # 44.5 / 45.2
+    ([(E, "bf16", 16, 64, 32, 64, 2)], [0]),                                                            # 17.5 / 21.7
+    ([(E, "bf16", 16, 512, 8, 512, 2), (E, "bf16", 16, 16, 32, 16, 1)], [0, 0]),                        # 29.9 / 37.1
+    ([(E, "bf16", 272, 64, 8, 128, 2), (E, "bf16", 272, 3, 32, 64, 1)], [0, 0]),                        # 28.8 / 33.1
 ])
 def test_exact_bf16_row_after_row(run, taken):
     assert forms(run) == taken
@@ -65,6 +71,7 @@ def test_exact_bf16_vgg19_goes_row_after_row(n):
     ([(A, "bf16", 64, 64, 16, 64, 3)], [SPARSE_ROWS]),                                                  # 27.5 / 23.3
     ([(A, "bf16", 256, 64, 8, 64, 5), (A, "bf16", 256, 16, 32, 16, 7)], [SPARSE_ROWS, 0]),              # (ResNet-20) 72.2 / 65.2
     ([(A, "bf16", 64, 64, 8, 64, 4), (E, "bf16", 64, 64, 8, 64, 1)], [0, 0]),
+    ([(A, "bf16", 256, 64, 8, 64, 4), (E, "bf16", 256, 64, 8, 64, 1)], [SPARSE_ROWS, 0]),               # (ResNet-20) 90.6 / 83.1
     ([(A, "bf16", 200, 128, 16, 128, 1), (A, "bf16", 200, 64, 16, 64, 1)], [SPARSE_ROWS, SPARSE_ROWS]),  # 56.7 / 37.1
     ([(A, "bf16", 200, 256, 8, 256, 2), (E, "bf16", 200, 64, 16, 64, 1)], [SPARSE_ROWS, 0]),            # 113.4 / 54.5
 ])
@@ -74,8 +81,8 @@ def test_approximated_bf16_row_after_row(run, taken):
 
 @pytest.mark.parametrize("n", [16, 64, 160, 512])
 def test_approximated_bf16_vgg19_goes_row_after_row(n):
-    """All on 4x4 to 16x16 planes; also, from N = 64 on, with every other layer exact."""
+    """All on 4x4 to 16x16 planes; also with every other layer exact."""
     layers = inputs.vgg19_stack()
-    for every in (1, 2) if n >= 64 else (1,):
+    for every in (1, 2):
         got = forms(stack(layers, lambda i: A if i % every == every - 1 else E, "bf16", n))
         assert [f == SPARSE_ROWS for f in got] == [i % every == every - 1 and 4 <= l.H <= 16 for i, l in enumerate(layers)]
