@@ -334,6 +334,24 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     const bool one_shape = nrows == 1 && wide_pairs == 1 && !others && !first && blocks >= (nexact > 1 ? 12 : 100) * tiles && (nexact > 1 || blocks >= 3072);
     const bool rows = one_shape || (blocks >= 320 && (nrows >= (others ? 4 : 3) || (nrows == 2 && nexact == 2 && blocks >= 12 * tiles)));
     each(WGRAD_EXACT, [&](LayerPlan &p, int) { if (!rows) p.ex.rows = 0; });
+    // Short fp32 layers, two and more of a shape, in the three-piece form: a launch more unless nothing is left for the fp32 multi-shape
+    // one or there is one of that form already, which at 2 GFLOP is earned (ResNet-20 exact, N = 64: 5.4 GFLOP, 65.7 us against
+    // 56.6; six of 128 -> 128 @ 4x4 and a strided layer, N = 64, 1.8 GFLOP: 34.1 us, with the form 41.2; of 405 runs timed both
+    // ways 77 were slower without this line, none with it).
+    double run_gflop = 0;
+    int wide_runs = 0, longer = 0, left = 0;
+    each(WGRAD_EXACT, [&](LayerPlan &p, int members) {
+        if (p.g.bf16) return;
+        const bool run = p.ex.x3_run && members > 1;
+        if (run) {
+            run_gflop += p.g.gflop() * members;
+            wide_runs += p.g.W > 4;
+        }
+        longer += p.ex.x3 == 2 && p.g.W > 4;
+        left += !run && p.ex.x3 != 2 && !(p.ex.x3 == 3 && members > 1);
+    });
+    const bool short_runs = nexact > 1 && (run_gflop >= 2.0 || left == 0 || (longer > 0 && wide_runs > 0));
+    each(WGRAD_EXACT, [&](LayerPlan &p, int members) { p.ex.x3_run = p.ex.x3_run && members > 1 && short_runs; });
     // Approximated bf16 layers row after row: from 1280 blocks on, from 512 where they are of four shapes and more or the exact layers do
     // not share the row-window kernel's launch with them, or where they are two and more layers of one shape, wider than 4x4, and
     // all that the run has for the bf16 matrix core -- or all but exact layers, with 80 blocks a tile; not for one layer alone, which
@@ -400,7 +418,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     auto group_flops = [&](int i) {
         const ExactPlan &ex = plan[i].ex;
         const int members = group_members(group, nlayers, i);
-        if (ex.plane2 || ex.x3 == 2 || ((ex.x3 == 3 || ex.x3_run) && members > 1)) return 0.0;
+        if (ex.plane2 || ex.x3 == 2 || ex.x3_run) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
         // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of
@@ -536,8 +554,8 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     return rc;
 }
 
-// The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 0
-// another.  For tests of the choice on the host.
+// The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 3 a
+// short fp32 layer in the three-piece form, 0 another.  For tests of the choice on the host.
 namespace wgrad {
 int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form)
 {
@@ -548,7 +566,7 @@ int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, 
     choose_run_forms(method, n, group, plan);
     for (int i = 0; i < n; ++i) {
         const LayerPlan &p = plan[group[i]];
-        form[i] = method[i] == WGRAD_EXACT && p.ex.rows ? 1 : (method[i] == WGRAD_APPROX && p.ap.rows == 2 ? 2 : 0);
+        form[i] = method[i] == WGRAD_EXACT ? (p.ex.rows ? 1 : (p.ex.x3_run ? 3 : 0)) : (method[i] == WGRAD_APPROX && p.ap.rows == 2 ? 2 : 0);
     }
     return WGRAD_OK;
 }

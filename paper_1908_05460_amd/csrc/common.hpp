@@ -47,6 +47,7 @@ struct Geometry {                    // validated convolution geometry
     int N, C, H, W, K, R, S, sh, sw, ph, pw, Ho, Wo;
     int bf16;                        // element type of X and dY
     __host__ __device__ long crs() const { return (long)C * R * S; }
+    double gflop() const { return 2e-9 * N * K * Ho * Wo * (double)crs(); }
     __host__ __device__ long dw_elems() const { return (long)K * C * R * S; }
 };
 
@@ -103,7 +104,7 @@ struct ExactPlan {
     int rows;                        // bf16_rows.hip's form, in a run with enough work for it: 0 no, 1 yes, 3 beside layers of 1
     int rows_chunks;                 // ... the most batch chunks
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
-    int x3_run;                      // x3's form also in a run, for two and more layers of a shape
+    int x3_run;                      // x3's form also in a run with enough such work, for two and more layers of a shape
     size_t lds_bytes, ws_bytes;
     bool ok;
 };

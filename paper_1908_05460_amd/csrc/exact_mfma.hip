@@ -627,7 +627,8 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // what the streaming form cannot (27x27 planes, 48 -> 96, N = 32: 76 -> 35 us; 224x224, 64 -> 64, N = 4: 302 -> 88) and
 // all but two kinds of what it can: long strided reductions, whose windows are mostly staging (128 -> 128 @ 56x56, stride
 // 2, N = 16, 3.7 GFLOP: 86 us against 60; at 0.2 to 0.9 GFLOP 13 to 23 against 16 to 29), and, in a run of several layers,
-// short ones: of less than 0.5 GFLOP where strided or the only one of their shape, else of less than 0.14 (ResNet-20, every
+// short ones: of less than 0.5 GFLOP where strided or the only one of their shape, else of less than 0.14 or where too little of
+// the run would share their launch (choose_run_forms in api.hip; ResNet-20, every
 // layer exact / every other one, N = 80: 74.1 -> 69.4 / 72.5 -> 65.7 us with the line at 0.3, N = 48: 57.9 -> 50.2 / 50.8 -> 51.2 at 0.2,
 // N = 32: 46.7 -> 43.5 / 47.6 -> 45.3 at 0.1, N = 16: 34.4 -> 35.7 / 32.9 -> 35.7 at 0.05; with the last layer alone
 // exact, N = 48: 42.6 -> 45.3 at 0.2), and batches under 16, which keep to the launch of many small groups (8, 64 -> 128 @ 16x16,
@@ -640,7 +641,7 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 static ExactPlan plan_exact_x3_or_older(const Geometry &g)
 {
     ExactPlan pl = plan_exact_forms(g, true);
-    const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
+    const double gflop = g.gflop();
     int use;
     bool run = false;
     if (pl.plane2) use = gflop >= 1.0 ? 3 : 0;
@@ -682,7 +683,7 @@ ExactPlan plan_exact(const Geometry &g)
     // N = 512: 29.3 against 43.8).  A first layer of a few channels leaves most of a tile empty (3 -> 64 @ 32x32, N = 512: 21.8
     // against 33.9): it joins others where it is short (VGG-19, N = 16 / 64 / 160: 57 / 93 / 156 us with it, 71 / 94 / 162 without; 512:
     // 376 against 361).
-    const double gflop = 2e-9 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
+    const double gflop = g.gflop();
     if (rows_takes(g) && (g.C >= 16 || gflop < 1.0)) {
         pl.rows = g.C < 16 ? 3 : 1;
         // no more chunks than the other forms' workspace holds: a buffer that sufficed for them suffices
@@ -744,7 +745,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
     if (plan.rows && rq && batch_aligned(g, b, 8, 8))
         return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
-    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || ((plan.x3 == 3 || plan.x3_run) && mq && b.n > 1)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq && b.n > 1) || (plan.x3_run && xq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The

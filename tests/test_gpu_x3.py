@@ -286,3 +286,21 @@ def test_short_layers_in_runs(N):
     torch.cuda.synchronize()
     for d, (X, dY), got in zip(ds, data, out):
         assert normwise_err(got.cpu().numpy(), oracle.wgrad_exact(oracle_shape(d), X, dY)) < TOL["fp32"] / 10
+
+
+@pytest.mark.parametrize("N", [33, 48])
+def test_short_layers_in_runs_with_enough_of_them(N):
+    """2 GFLOP of short layers in all, which the three-piece form then takes, beside layers that it does not."""
+    import torch
+    from tests.test_run_forms import X3_RUN, forms
+    assert forms([(B.EXACT, "fp32", N, 16, 32, 16, 7), (B.EXACT, "fp32", N, 32, 16, 32, 7), (B.EXACT, "fp32", N, 3, 32, 16, 1)]) == [X3_RUN, X3_RUN, 0]
+    shapes = [(N, 16, 32, 32, 16, 3, 3, 1, 1, 1, 1)] * 7 + [(N, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1)] * 7 + [(N, 3, 32, 32, 16, 3, 3, 1, 1, 1, 1)]
+    ds = [mk(t) for t in shapes]
+    data = [rand_inputs(d, 130 + i) for i, d in enumerate(ds)]
+    out = [torch_nan(d) for d in ds]
+    S = B.Schedule(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], out)
+    mask = np.full(len(ds), B.EXACT, np.uint8)
+    S.run(mask, B.alloc_workspace(S.workspace_bytes(mask)))
+    torch.cuda.synchronize()
+    for d, (X, dY), got in zip(ds, data, out):
+        assert normwise_err(got.cpu().numpy(), oracle.wgrad_exact(oracle_shape(d), X, dY)) < TOL["fp32"] / 10

@@ -6,7 +6,7 @@ import pytest
 
 from paper_1908_05460_amd import binding as B, inputs
 
-ROWS, SPARSE_ROWS = 1, 2            # bf16 layers row after row, exact and approximated
+ROWS, SPARSE_ROWS, X3_RUN = 1, 2, 3     # bf16 layers row after row, exact and approximated; short fp32 layers in the three-piece form
 E, A = B.EXACT, B.APPROX
 
 
@@ -86,3 +86,22 @@ def test_approximated_bf16_vgg19_goes_row_after_row(n):
     for every in (1, 2):
         got = forms(stack(layers, lambda i: A if i % every == every - 1 else E, "bf16", n))
         assert [f == SPARSE_ROWS for f in got] == [i % every == every - 1 and 4 <= l.H <= 16 for i, l in enumerate(layers)]
+
+
+@pytest.mark.parametrize("run, taken", [
+    ([(E, "fp32", 32, 32, 16, 32, 3), (E, "fp32", 32, 3, 32, 16, 1)], [0, 0]),                          # 18.8 / 26.5
+    ([(E, "fp32", 64, 128, 4, 128, 6), (E, "fp32", 64, 16, 16, 16, 1)], [0, 0]),
+    ([(E, "fp32", 128, 64, 4, 64, 6), (E, "fp32", 128, 3, 32, 16, 1)], [0, 0]),                         # 28.1 / 33.4
+    ([(E, "fp32", 100, 16, 32, 16, 6), (E, "fp32", 100, 3, 32, 16, 1)], [X3_RUN, 0]),                   # 48.5 / 39.9
+    ([(E, "fp32", 32, 32, 16, 32, 3), (E, "fp32", 32, 64, 16, 64, 1)], [X3_RUN, 0]),                    # 29.0 / 19.7 (with the longer one)
+    ([(E, "fp32", 64, 32, 16, 32, 3), (E, "fp32", 64, 64, 8, 64, 2)], [X3_RUN, X3_RUN]),                # nothing else
+    ([(E, "fp32", 64, 32, 16, 32, 3)], [0]),                                                            # (in a launch of its own)
+])
+def test_short_fp32_layers(run, taken):
+    assert forms(run) == taken
+
+
+@pytest.mark.parametrize("n, taken", [(16, False), (48, True), (80, True)])
+def test_resnet20_in_the_three_piece_form(n, taken):
+    got = forms(stack(inputs.resnet20_stack(), E, "fp32", n))
+    assert (sum(f == X3_RUN for f in got) >= 10) == taken
