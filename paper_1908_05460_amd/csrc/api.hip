@@ -296,20 +296,15 @@ extern "C" size_t conv_wgrad_schedule_topk_workspace_bytes(const wgrad_conv_desc
     return topk >= 1 && topk <= kTopKMax ? schedule_ws_bytes(layers, method, nlayers, topk) : 0;
 }
 
-static int group_members(const int *group, int n, int first)
-{
-    int members = 0;
-    for (int j = first; j < n; ++j) members += group[j] == first;
-    return members;
-}
-
 // Which groups take the forms that pay in a run only where enough work shares their launch.  On entry the plans say which could, on
 // return which do.
 static void choose_run_forms(const uint8_t *method, int n, const int *group, std::vector<LayerPlan> &plan)
 {
+    std::vector<int> members(n, 0);
+    for (int i = 0; i < n; ++i) ++members[group[i]];
     auto each = [&](int which, auto &&f) {
         for (int i = 0; i < n; ++i)
-            if (method[i] == which && group[i] == i) f(plan[i], group_members(group, n, i));
+            if (method[i] == which && group[i] == i) f(plan[i], members[i]);
     };
     // Exact bf16 layers row after row: their launch takes a workgroup's set-up, a CU for each workgroup and partial results, and what
     // is left of the run keeps launches of its own.  Three shapes share it well -- four where bf16 layers that it does not take (2x2
@@ -355,8 +350,9 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     // Approximated bf16 layers row after row: from 1280 blocks on, from 512 where they are of four shapes and more or the exact layers do
     // not share the row-window kernel's launch with them, or where they are two and more layers of one shape, wider than 4x4, and
     // all that the run has for the bf16 matrix core -- or all but exact layers, with 80 blocks a tile; not for one layer alone, which
-    // goes as in a call of its own where nothing else is on that core.  (Of 830 timed runs 91 were slower where any two layers sufficed, 128 -> 128 @ 4x4, three
-    // layers, N = 64, 11.6 us against 22.2; by this line three, 64 -> 64 @ 8x8, three layers, N = 200, by 4 to 9 %.)
+    // goes as in a call of its own where nothing else is on that core.  (Of 830 timed runs 91 were slower where any two layers sufficed,
+    // 128 -> 128 @ 4x4, three layers, N = 64, 11.6 us against 22.2; by this line five, by 4 to 9 %, 64 -> 64 @ 8x8, three layers, N = 200
+    // the most.)
     int nsparse = 0, sparse_layers = 0, sparse_wide = 0, nmm = 0, nmm_exact = 0;
     blocks = tiles = 0;
     each(WGRAD_EXACT, [&](LayerPlan &p, int) { nmm_exact += p.ex.mm16; });
@@ -372,6 +368,17 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     const bool sparse = sparse_layers > 1 && (blocks >= (nsparse >= 4 || rows ? 512 : 1280) ||
                                               (sparse_wide == 1 && nmm == 1 && (nmm_exact == 0 || blocks >= 80 * tiles)));
     each(WGRAD_APPROX, [&](LayerPlan &p, int) { if (p.ap.rows && sparse) p.ap.rows = 2; });
+    // Approximated fp32 layers on 2x2 planes, held in registers beside layers on 4x4 ones, whose launch and selections they share (7 us
+    // each), unless in long batches those are little beside them (512 -> 512 @ 2x2, two layers, beside 64 -> 128 @ 4x4, N = 64 / 128 /
+    // 256: 36.3 / 47.5 / 67.6 us in the sparsified form, 29.3 / 48.8 / 83.6 in registers)
+    double on4 = 0, on2 = 0;
+    each(WGRAD_APPROX, [&](LayerPlan &p, int members) {
+        if (p.ap.regs && p.g.H == 4) on4 += (double)p.g.dw_elems() * members;
+        if (p.g.H == 2 && regs_takes(p.g)) on2 += (double)p.g.dw_elems() * members;
+    });
+    each(WGRAD_APPROX, [&](LayerPlan &p, int) {
+        if (p.g.H == 2 && on4 > 0 && (p.g.N <= 64 || 8 * on4 >= on2)) plan_approx_regs(p.g, p.ap);
+    });
 }
 
 static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X, const void *const *dY,
@@ -417,7 +424,8 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     // groups that the fp32 multi-shape launch carries (those of the 2x2-plane form add nothing to its shares)
     auto group_flops = [&](int i) {
         const ExactPlan &ex = plan[i].ex;
-        const int members = group_members(group, nlayers, i);
+        int members = 0;
+        for (int j = i; j < nlayers; ++j) members += group[j] == i;
         if (ex.plane2 || ex.x3 == 2 || ex.x3_run) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
@@ -457,12 +465,8 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
     int nsparse = 0;                 // approximated ones
     for (int i = 0; i < nlayers; ++i) nsparse += method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.rows == 2;
     RowsQueue *rsq = nsparse > 0 ? rows_queue_new_sparse(sq) : nullptr;
-    int nregs = 0, nregs4 = 0;       // groups that the form of planes in registers takes; those on 4x4 planes
-    for (int i = 0; i < nlayers; ++i) {
-        if (topk != 0 || method[i] != WGRAD_APPROX || group[i] != i || !plan[i].ap.regs) continue;
-        ++nregs;
-        nregs4 += plan[i].g.H == 4;
-    }
+    int nregs = 0;                   // groups that the form of planes in registers takes
+    for (int i = 0; i < nlayers; ++i) nregs += topk == 0 && method[i] == WGRAD_APPROX && group[i] == i && plan[i].ap.regs;
     RegsQueue *rgq = nregs > 0 ? regs_queue_new() : nullptr;
     char *ws_next = (char *)ws;
     int rc = WGRAD_OK;
@@ -497,7 +501,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
             continue;
         }
         else rc = launch_approx(g, plan[i].ap, b, scale, nullptr, nullptr, ws_next, st, &queue, fq, bq, gq, sq,
-                                plan[i].ap.regs == 2 && nregs4 == 0 ? nullptr : rgq, plan[i].ap.rows == 2 ? rsq : nullptr);
+                                rgq, plan[i].ap.rows == 2 ? rsq : nullptr);
         ws_next += align_up(plan[i].ws) * b.n;
     }
     if (sq) {
@@ -555,7 +559,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
 }
 
 // The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 3 a
-// short fp32 layer in the three-piece form, 0 another.  For tests of the choice on the host.
+// short fp32 layer in the three-piece form, 4 planes in registers, 0 another.  For tests of the choice on the host.
 namespace wgrad {
 int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form)
 {
@@ -566,7 +570,7 @@ int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, 
     choose_run_forms(method, n, group, plan);
     for (int i = 0; i < n; ++i) {
         const LayerPlan &p = plan[group[i]];
-        form[i] = method[i] == WGRAD_EXACT ? (p.ex.rows ? 1 : (p.ex.x3_run ? 3 : 0)) : (method[i] == WGRAD_APPROX && p.ap.rows == 2 ? 2 : 0);
+        form[i] = method[i] == WGRAD_EXACT ? (p.ex.rows ? 1 : (p.ex.x3_run ? 3 : 0)) : (method[i] == WGRAD_APPROX ? (p.ap.rows == 2 ? 2 : (p.ap.regs ? 4 : 0)) : 0);
     }
     return WGRAD_OK;
 }

@@ -1437,29 +1437,43 @@ int fused_flush(FusedQueue &q, hipStream_t st)
 #define WGRAD_GATHER_BLOCKS 512
 #endif
 
-ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool allow_mm, bool allow_regs)
+// `pl`, the plan of a layer that the form of planes in registers takes, becomes that form's where the older form's workspace has
+// room for its selections; the batch is cut into no more chunks than it holds.  (Tensors that are not 16-byte aligned take the
+// older form, in the same workspace.)
+bool plan_approx_regs(const Geometry &g, ApproxPlan &pl)
+{
+    const ApproxPlan alt = pl;
+    const size_t maps = align_up((size_t)g.N * g.K * 4);
+    if (!regs_takes(g) || alt.ws_bytes < 2 * maps) return false;
+    pl = ApproxPlan{};
+    pl.regs = 1;
+    pl.off_idx = 0; pl.off_sum = maps; pl.off_part = 2 * maps;
+    if (alt.use_lds) {
+        pl.ctiles = alt.ctiles; pl.ktiles = alt.ktiles; pl.gather_n = alt.gather_n;
+    }
+    pl.chunks = (int)std::max<size_t>(1, std::min<size_t>((alt.ws_bytes - pl.off_part) / ((size_t)g.dw_elems() * 4), 1024));
+    pl.chunk_n = (g.N + pl.chunks - 1) / pl.chunks;
+    pl.ws_bytes = alt.ws_bytes;
+    return true;
+}
+
+// the plan without that form
+static ApproxPlan plan_approx_older(const Geometry &g, bool allow_lds = true, bool allow_fused = true, bool allow_mm = true);
+
+ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool allow_mm)
+{
+    ApproxPlan pl = plan_approx_older(g, allow_lds, allow_fused, allow_mm);
+    // 2x2 planes: too little work to fill the chip with an image after the other (512 -> 512, N = 128, alone: 35 us against 21 of
+    // the sparsified form); see choose_run_forms
+    if (allow_lds && allow_fused && allow_mm && g.H > 2) plan_approx_regs(g, pl);
+    return pl;
+}
+
+static ApproxPlan plan_approx_older(const Geometry &g, bool allow_lds, bool allow_fused, bool allow_mm)
 {
     ApproxPlan pl{};
     const long outs = g.dw_elems();
     const int HW = g.H * g.W;
-    if (allow_regs && allow_lds && allow_fused && allow_mm && regs_takes(g)) {
-        // (tensors that are not 16-byte aligned take the form below: the workspace is that one's, and the batch is not
-        // cut into more chunks than it holds)
-        const ApproxPlan alt = plan_approx(g, true, true, true, false);
-        pl.regs = g.H == 2 ? 2 : 1;
-        size_t off = 0;
-        pl.off_idx = off; off += align_up((size_t)g.N * g.K * 4);
-        pl.off_sum = off; off += align_up((size_t)g.N * g.K * 4);
-        pl.off_part = off;
-        const size_t room = alt.ws_bytes > off ? (alt.ws_bytes - off) / ((size_t)outs * 4) : 0;
-        if (alt.use_lds) {
-            pl.ctiles = alt.ctiles; pl.ktiles = alt.ktiles; pl.gather_n = alt.gather_n;
-        }
-        pl.chunks = std::max(regs_max_chunks(g, room < 2 ? 1 : (int)std::min<size_t>(room, 64)), alt.use_lds ? alt.chunks : 1);
-        pl.chunk_n = (g.N + pl.chunks - 1) / pl.chunks;
-        pl.ws_bytes = std::max(alt.ws_bytes, off);
-        return pl;
-    }
     // bf16 inputs, shapes the bf16 matrix-core kernel takes: the approximated gradient is the exact
     // one of the sparsified dY (Section 2.4), and contracting that on the matrix core -- the operand
     // built in registers from each map's selected position and sum -- outruns any gather from LDS
@@ -1480,7 +1494,7 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
             if (alt > pl.ws_bytes) pl.ws_bytes = alt;
             if (rows_takes(g) && tune_int("WGRAD_ROWS_SPARSE", 1)) {
                 pl.rows = 1;
-                pl.rows_chunks = rows_max_chunks(g, true, ex.splits);
+                pl.rows_chunks = ex.splits;
             }
             return pl;
         }
@@ -1759,9 +1773,7 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
     bool aligned = true;
     for (int i = 0; i < b.n; ++i)
         aligned = aligned && ((uintptr_t)b.X[i] % (g.bf16 ? 8 : 16)) == 0 && ((uintptr_t)b.dY[i] % (g.bf16 ? 8 : 16)) == 0;
-    // 2x2 planes: too little work to fill the chip with an image after the other (512 -> 512, N = 128, alone: 35 us against 21 of
-    // the sparsified form; four such layers 44 against 49), but beside layers on 4x4 planes they take 7 us each
-    ApproxPlan pl = (plan.regs && !aligned) || (plan.regs == 2 && !rgq) ? plan_approx(g, true, true, true, false) : plan;
+    ApproxPlan pl = plan.regs && !aligned ? plan_approx_older(g) : plan;
     if ((pl.use_lds || pl.fused || pl.mm) && !aligned) pl = plan_approx(g, false, false, false);   // (the sparsified form has no alignment needs: the exact launcher falls back by itself)
     const long outs = g.dw_elems();
     if (pl.use_lds) {

@@ -401,18 +401,20 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
         if (!fits) continue;
         const bool big = it[0]->g.H == 8;
         const int most = big ? RegsLayout<8>::OCC : RegsLayout<4>::OCC, slots = kNumCU * 4 * most / waves;
+        int now[kRegsMultiMax] = {};
         for (int want = 1; want <= 64; want += want < 8 ? 1 : want / 4) {     // chunks of a layer (2x2 planes: half as many, an image is half the work)
-            int now[kRegsMultiMax];
             double partial = 0, all_waves = 0;
+            bool same = true;                        // (as with fewer wanted: the limits are reached)
             for (int i = 0; i < n; ++i) {
                 const Geometry &g = it[i]->g;
-                int ch = g.H == 2 ? (want + 1) / 2 : want;
-                ch = regs_allowed(*it[i], ch);
-                const int per = (g.N + ch - 1) / ch;
-                now[i] = (g.N + per - 1) / per;
+                const int ch = regs_allowed(*it[i], g.H == 2 ? (want + 1) / 2 : want);
+                const int per = (g.N + ch - 1) / ch, cut = (g.N + per - 1) / per;
+                same = same && cut == now[i];
+                now[i] = cut;
                 if (now[i] > 1) partial += (double)now[i] * g.dw_elems() * 4 * it[i]->b.n;
                 all_waves += (double)now[i] * (g.C / 64) * (g.K / regs_kw(g.H)) * it[i]->b.n;
             }
+            if (same) continue;
             const double occ = std::min((double)most, std::max(waves / 4.0, all_waves / (kNumCU * 4)));
             double sorted[kRegsMultiMax], lf[kRegsMultiMax];
             long count[kRegsMultiMax];
@@ -438,18 +440,6 @@ static int regs_cut(const RegsItem *const *it, int n, int *chunks, double *life)
         }
     }
     return best_waves;
-}
-
-// the most chunks a call may cut a layer into (the workspace holds their partial results): as for the layer alone
-int regs_max_chunks(const Geometry &g, int cap)
-{
-    RegsItem I{};
-    I.g = g; I.b.n = 1; I.max_chunks = cap; I.most_n = g.N;
-    const RegsItem *one = &I;
-    int ch;
-    double life;
-    regs_cut(&one, 1, &ch, &life);
-    return ch;
 }
 
 static int regs_launch(const RegsItem *const *it, int n, bool big, hipStream_t st, CombineQueue *combine)

@@ -123,18 +123,6 @@ static void rows_cut(const RowsItem *const *it, int n, bool sparse, int *chunks,
     }
 }
 
-// The most chunks a call may cut a layer into (the workspace holds their partial results): as for the layer alone.
-int rows_max_chunks(const Geometry &g, bool sparse, int cap)
-{
-    RowsItem I{};
-    I.g = g; I.b.n = 1; I.max_chunks = cap;
-    const RowsItem *one = &I;
-    int ch;
-    double life;
-    rows_cut(&one, 1, sparse, &ch, &life);
-    return ch;
-}
-
 int rows_flush(RowsQueue &q, hipStream_t st, CombineQueue *combine)
 {
     if (q.n == 0) return WGRAD_OK;

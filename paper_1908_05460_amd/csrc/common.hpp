@@ -136,7 +136,6 @@ double makespan_us(int slots, const double *life, const long *count, int n);
 bool rows_takes(const Geometry &g);
 int rows_tiles(const Geometry &g);                   // 64 x 64 channels
 long rows_blocks(const Geometry &g);                 // of four rows of a group of images, in each tile
-int rows_max_chunks(const Geometry &g, bool sparse = false, int cap = 1 << 20);
 struct RowsQueue;
 struct SelectQueue;
 RowsQueue *rows_queue_new();
@@ -181,12 +180,13 @@ struct ApproxPlan {
     int gather_n;                    // images of the LDS form's batch chunk alone; also where `regs` stands in for that form, which loses no more to rounding
     int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm): 0 no, 1 a layer alone, 2 in a run with enough such work; the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
-    int regs;                        // fp32, planes held in registers (approx_regs.hip): 0 no, 1 always, 2 in a run beside layers on 4x4 planes
+    int regs;                        // fp32, planes held in registers (approx_regs.hip)
     int sx;                          // fp32, planes of up to four positions: exact kernel on the sparsified dY
     ExactPlan ex;                    // its plan
     size_t off_idx, off_sum, off_part, off_sparse, ws_bytes;
 };
-ApproxPlan plan_approx(const Geometry &g, bool allow_lds = true, bool allow_fused = true, bool allow_mm = true, bool allow_regs = true);
+ApproxPlan plan_approx(const Geometry &g, bool allow_lds = true, bool allow_fused = true, bool allow_mm = true);
+bool plan_approx_regs(const Geometry &g, ApproxPlan &pl);
 struct FusedQueue;
 struct GatherQueue;
 struct RegsQueue;
@@ -206,7 +206,6 @@ int launch_approx(const Geometry &g, const ApproxPlan &pl, const Batch &b, float
 struct RegsPosition { int row, col, base; };
 bool regs_takes(const Geometry &g);
 RegsPosition regs_position(const Geometry &g);
-int regs_max_chunks(const Geometry &g, int cap);
 RegsQueue *regs_queue_new();
 void regs_queue_delete(RegsQueue *q);
 bool regs_full(const RegsQueue &q);

@@ -6,7 +6,8 @@ import pytest
 
 from paper_1908_05460_amd import binding as B, inputs
 
-ROWS, SPARSE_ROWS, X3_RUN = 1, 2, 3     # bf16 layers row after row, exact and approximated; short fp32 layers in the three-piece form
+# bf16 layers row after row, exact and approximated; short fp32 layers in the three-piece form; approximated fp32 layers' planes in registers
+ROWS, SPARSE_ROWS, X3_RUN, REGS = 1, 2, 3, 4
 E, A = B.EXACT, B.APPROX
 
 
@@ -105,3 +106,17 @@ def test_short_fp32_layers(run, taken):
 def test_resnet20_in_the_three_piece_form(n, taken):
     got = forms(stack(inputs.resnet20_stack(), E, "fp32", n))
     assert (sum(f == X3_RUN for f in got) >= 10) == taken
+
+
+@pytest.mark.parametrize("run, taken", [
+    ([(A, "fp32", 256, 512, 2, 512, 2), (A, "fp32", 256, 64, 4, 128, 1)], [0, REGS]),                   # 67.6 / 83.6
+    ([(A, "fp32", 128, 512, 2, 512, 2), (A, "fp32", 128, 64, 4, 128, 1)], [0, REGS]),                   # 47.5 / 48.8
+    ([(A, "fp32", 64, 512, 2, 512, 2), (A, "fp32", 64, 64, 4, 128, 1)], [REGS, REGS]),                  # 36.3 / 29.3
+    ([(A, "fp32", 256, 512, 2, 512, 4), (A, "fp32", 256, 512, 4, 512, 1)], [REGS, REGS]),               # 191.8 / 107.6
+    ([(A, "fp32", 256, 128, 2, 128, 1), (A, "fp32", 256, 64, 4, 128, 1)], [REGS, REGS]),                # 46.8 / 22.6
+    ([(A, "fp32", 128, 512, 2, 512, 4)], [0]),
+    ([(A, "fp32", 128, 512, 2, 512, 4), (A, "fp32", 128, 256, 8, 256, 1)], [0, REGS]),
+    ([(A, "fp32", 128, 512, 2, 512, 1), (E, "fp32", 128, 512, 4, 512, 1)], [0, 0]),
+])
+def test_planes_in_registers(run, taken):
+    assert forms(run) == taken
