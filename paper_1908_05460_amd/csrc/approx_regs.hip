@@ -54,6 +54,7 @@ template <int KW> struct RegsScalars { typedef rg_i8 at; typedef rg_f8 sum; };
 template <> struct RegsScalars<4> { typedef rg_i4 at; typedef rg_f4 sum; };
 
 #define RG_CLOBBER "memory"
+#define RG_CLOBBER_M0 "memory", "m0"     // (s_set_gpr_idx_* keep the offset there)
 
 // nine taps of one patch into the sums of output channel J: v[...] += sum * X[tap]
 #define RG_TAP(J, T, AT) "v_fmac_f32 v[%[A]+9*" #J "+" #T "], %[s" #J "], v[%[X]+" AT "]\n\t"
@@ -134,6 +135,8 @@ __device__ __forceinline__ void regs_load4(uint32_t rd, rg_i4 (&at)[4], rg_f4 (&
 }
 
 // the patches of one image; 2x2: of the one in the I-th four registers
+#pragma clang diagnostic push
+#pragma clang diagnostic ignored "-Winline-asm"     // (m0 named: see rows_copy)
 template <int HW, int I, class AT, class SUM>
 __device__ __forceinline__ void regs_patches(const AT &at, const SUM &sum)
 {
@@ -141,12 +144,13 @@ __device__ __forceinline__ void regs_patches(const AT &at, const SUM &sum)
     if constexpr (HW >= 4)
         asm volatile("s_set_gpr_idx_on %[i0], gpr_idx(SRC1)\n\t"
                      RG_PATCH(0) RG_PATCH(1) RG_PATCH(2) RG_PATCH(3) RG_PATCH(4) RG_PATCH(5) RG_PATCH(6) RG_PATCH(7)
-                     "s_set_gpr_idx_off" :: [X] "n"(L::X), [A] "n"(L::ACC), [P] "n"(L::PITCH), RG_SCALARS(at, sum) : RG_CLOBBER);
+                     "s_set_gpr_idx_off" :: [X] "n"(L::X), [A] "n"(L::ACC), [P] "n"(L::PITCH), RG_SCALARS(at, sum) : RG_CLOBBER_M0);
     else
         asm volatile("s_set_gpr_idx_on %[i0], gpr_idx(SRC2,DST)\n\t"
                      RG_PATCH2(0) RG_PATCH2(1) RG_PATCH2(2) RG_PATCH2(3)
-                     "s_set_gpr_idx_off" :: [X] "n"(L::X + 4 * I), [A] "n"(L::ACC), RG_SCALARS4(at, sum) : RG_CLOBBER);
+                     "s_set_gpr_idx_off" :: [X] "n"(L::X + 4 * I), [A] "n"(L::ACC), RG_SCALARS4(at, sum) : RG_CLOBBER_M0);
 }
+#pragma clang diagnostic pop
 
 template <int... I, class F>
 __device__ __forceinline__ void regs_each(std::integer_sequence<int, I...>, F &&f) { (f(std::integral_constant<int, I>()), ...); }
@@ -326,7 +330,7 @@ __device__ __forceinline__ void regs_group(F &&body)
 __global__ __launch_bounds__(64 * kRegsWaves, RegsLayout<4>::OCC) __attribute__((amdgpu_num_vgpr(RegsLayout<4>::FREE)))
 void approx_gather_regs(const RegsMulti)
 {
-    extern __shared__ char regs_smem[];
+    extern __shared__ __attribute__((aligned(2 * RegsLayout<4>::STAGE))) char regs_smem[];    // (the two stages' addresses differ in one bit)
     regs_group([&](const RegsParams &p, int bid, int nblk, int prob, int waves) {
         if (p.hw == 4) regs_body<4>(p, regs_smem, bid, nblk, prob, waves);
         else regs_body<2>(p, regs_smem, bid, nblk, prob, waves);
@@ -337,8 +341,8 @@ void approx_gather_regs(const RegsMulti)
 __global__ __launch_bounds__(64 * kRegsWaves, RegsLayout<8>::OCC) __attribute__((amdgpu_num_vgpr(RegsLayout<8>::FREE)))
 void approx_gather_regs8(const RegsMulti)
 {
-    extern __shared__ char regs_smem[];
-    regs_group([&](const RegsParams &p, int bid, int nblk, int prob, int waves) { regs_body<8>(p, regs_smem, bid, nblk, prob, waves); });
+    extern __shared__ __attribute__((aligned(2 * RegsLayout<8>::STAGE))) char regs8_smem[];
+    regs_group([&](const RegsParams &p, int bid, int nblk, int prob, int waves) { regs_body<8>(p, regs8_smem, bid, nblk, prob, waves); });
 }
 
 // ---- host ----
