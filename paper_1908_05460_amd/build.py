@@ -1,5 +1,6 @@
 """Builds libwgrad.so (the HIP kernels + C ABI) for gfx950 with hipcc, in-tree."""
 import os
+import re
 import subprocess
 import sys
 from concurrent.futures import ThreadPoolExecutor
@@ -25,6 +26,29 @@ def hipcc():
     raise RuntimeError("hipcc not found")
 
 
+def numbered_registers():
+    """{kernel of approx_regs.hip: the first vector register that only its asm blocks may touch}"""
+    text = open(os.path.join(CSRC, "approx_regs.hip")).read()
+    free = {int(hw): int(n) for hw, n in re.findall(r"struct RegsLayout<(\d)> \{.*?\bFREE = (\d+)", text)}
+    if set(free) != {2, 4, 8} or free[2] != free[4]:
+        raise RuntimeError(f"approx_regs.hip: numbered registers of the layouts not found: {free}")
+    return {"approx_gather_regs": free[4], "approx_gather_regs8": free[8]}
+
+
+def check_numbered_registers(asm, first):
+    """Raises unless the kernels of `first` keep, outside their asm blocks, below the registers that those number, and spill none.  The
+    compiler is told how many registers it has, not that the others are taken: one that went beyond would give wrong sums."""
+    for kernel, most in first.items():
+        body = re.search(r"^(_ZN5wgrad%d%s\w*):.*?^\s*\.end_amdhsa_kernel" % (len(kernel), kernel), asm, re.M | re.S)
+        if not body:
+            raise RuntimeError(f"{kernel}: not in the assembly")
+        text = re.sub(r"#ASMSTART.*?#ASMEND", "", body.group(0), flags=re.S)
+        code = "\n".join(line.split(";")[0] for line in text.splitlines())
+        used = [int(hi or lo) for lo, hi in re.findall(r"\bv\[?(\d+)(?::(\d+))?", code)]
+        if not used or max(used) >= most or re.search(r"\ba\[?\d|\bscratch_", code):
+            raise RuntimeError(f"{kernel}: the compiler uses v{max(used, default=-1)} (v{most} on are the asm blocks'), or spills")
+
+
 def build(extra_flags=(), out=LIB, objdir=None, verbose=False):
     objdir = objdir or os.path.join(HERE, "_build")
     os.makedirs(objdir, exist_ok=True)
@@ -42,8 +66,18 @@ def build(extra_flags=(), out=LIB, objdir=None, verbose=False):
             print(msgs, file=sys.stderr)
         return obj
 
+    def check_registers():
+        asm = os.path.join(objdir, "approx_regs.s")
+        r = subprocess.run([cc, *FLAGS, *extra_flags, "-S", "--cuda-device-only", os.path.join(CSRC, "approx_regs.hip"), "-o", asm],
+                           capture_output=True, text=True)
+        if r.returncode != 0:
+            raise RuntimeError(f"hipcc failed on approx_regs.hip:\n{r.stderr}")
+        check_numbered_registers(open(asm).read(), numbered_registers())
+
     with ThreadPoolExecutor(max_workers=8) as ex:
+        checked = ex.submit(check_registers)
         objs = list(ex.map(compile_one, SOURCES))
+        checked.result()
     # -no-hip-rt: the library does not name a HIP runtime of its own; it binds to the one the
     # host process has already loaded (a process must never run two HIP runtimes side by side,
     # and PyTorch wheels bundle theirs).  A plain C program links -lamdhip64 itself.
