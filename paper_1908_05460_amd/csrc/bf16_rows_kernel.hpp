@@ -14,16 +14,17 @@
 // So 8 or 10 matrix instructions come with about 13 others.  That ratio is what bounds such a kernel here: measured on this core,
 // a vector instruction between 32x32x16 instructions costs 1.3 clocks of their 36, between 16x16x32 ones 2 of 19 -- they
 // do not run side by side -- and the row-window kernel (exact_bf16_kernel.hpp) has 3.6 of them to each.
-//   - X and dY go to LDS by loads that bypass the registers, four rows (16 KB of each) at a time, the next four while these
-//     are multiplied; one barrier in four steps.  A channel's 16-byte pieces are permuted by its number (XOR), so that the
+//   - X and dY go to LDS by loads that bypass the registers, four rows (16 KB of each) at a time, into a ring: while four are
+//     multiplied, the copies of the next three times four are under way; one barrier in four steps.  A channel's 16-byte pieces are permuted by its number (XOR), so that the
 //     lanes of an operand read fall on all banks.  Loads past the end of a tensor bring zeros: ragged batches and
 //     channel tiles need nothing else.
 //   - A sum of many products in one register loses more to rounding than the older kernel's many short ones did, so every
 //     kRowsFold blocks the sums are added to a second set of registers.  That is what the split of the taps buys: nine taps of
 //     32 x 32 channels in one wavefront leave no room for it.  (Split into three filter columns and twelve wavefronts the
 //     operands' reads were half again as many, and LDS bound the kernel: 128 -> 128 @ 16x16, N = 512: 44 us against 37.)
-// 38.7 GFLOP alone (64 -> 64 @ 32x32 to 512 -> 512 @ 4x4, N = 512): 36 to 41 us, 9 of them set-up and write-out (the row-window
-// kernel: 44 to 55); VGG-19's run, 395 GFLOP: 320 us, where the card's power, not the kernel's instructions, sets the clock.
+// The kernel without the reduction behind it: 38.7 GFLOP in a launch (64 -> 64 @ 32x32 to 512 -> 512 @ 4x4, N = 512) 36 to 41 us, 9 of
+// them set-up and write-out (the row-window kernel: 44 to 55); VGG-19's run, 395 GFLOP, 277 us of 350, where the card's power, not the
+// kernel's instructions, sets the clock.
 //
 // SPARSE: the approximated gradient, which is the exact one of a dY with one value in each map (planes of up to 16x16).  That is a
 // structured-sparse operand: of four consecutive positions at most one is not zero, and v_smfmac_f32_32x32x32_bf16
@@ -34,6 +35,9 @@
 //   - Each group has the sum in one of two kept places and the position's column as its index; which row and group of four
 //     the position is in decides, by one comparison a group and step, whether it is there or a zero.
 //   - One value a map and image: the sums need no second set of registers.
+//   - A kept place is multiplied also where its value is zero, so that an infinity or a NaN of X that a map did not select makes NaNs
+//     at that map's column and the next kept one's (column 3 of four): fewer than the row-window kernel's sparse operand, which
+//     multiplies all of them.
 #pragma once
 #include <type_traits>
 

@@ -127,3 +127,18 @@ def test_length_of_the_sums(t, most, beside):
         got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY)).cpu().numpy()
     lost = d.N - 1 - (got - 2.0 ** 24)
     assert 0 <= lost.min() and lost.max() <= most               # (most - 1, and one where the sum is odd)
+
+
+def test_infinite_and_nan_map_sums_on_2x2_planes():
+    """Neither the registers (in the run) nor the plain product (alone) multiply the padding: the same NaNs, fewer than the definition's."""
+    ds = [desc((6, 64, 2, 128, 1)), desc((7, 64, 4, 128, 1))]
+    data = [rand_inputs(d, 11) for d in ds]
+    Y = data[0][1]
+    Y[1, 3, 0, 0], Y[2, 40, -1, -1], Y[5, 127, 0, -1] = np.inf, -np.inf, np.nan
+    with np.errstate(all="ignore"):
+        want = oracle.wgrad_approx(oracle_shape(ds[0]), *data[0])[0]
+    run, alone = run_approx(ds, data)[0] * 4, B.conv_wgrad_approx(ds[0], *map(to_gpu, data[0])).cpu().numpy()
+    assert np.array_equal(np.isnan(run), np.isnan(alone)) and not np.isfinite(run).all()
+    assert np.array_equal(run[np.isinf(want)], want[np.isinf(want)].astype(np.float32))
+    fine = np.isfinite(want)
+    assert np.isfinite(run[fine]).all() and normwise_err(run[fine], want[fine]) < BOUND

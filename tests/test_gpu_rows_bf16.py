@@ -111,10 +111,54 @@ def test_approximated_runs():
     data = [rand_inputs(d, 80 + i, "bf16") for i, d in enumerate(ds)]
     out = run_layers(ds, [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data], B.APPROX, scale=0.25)
     for d, (X, dY), got in zip(ds, data, out):
-        idx, sums = oracle.select(oracle_shape(d), dY)
-        want = oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx, sums)) * 0.25
-        # a sum in 32 bits may round the other way than one in 64: one map's term of N in error by 2^-8
-        assert normwise_err(got.cpu().numpy(), want) < 2.0 ** -8
+        idx, sums = B.conv_wgrad_select(d, to_gpu(dY))      # (a sum in 32 bits may round the other way than one in 64)
+        assert np.array_equal(idx.cpu().numpy(), oracle.select(oracle_shape(d), dY)[0])
+        want = oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx.cpu().numpy(), sums.cpu().numpy())) * 0.25
+        assert normwise_err(got.cpu().numpy(), want) < TOL["fp32"] / 50
+
+
+def approximated(ds, data, alone):
+    """-> [(dW, what the exact oracle makes of the rounded sums)]"""
+    Xs, dYs = [to_gpu(x) for x, _ in data], [to_gpu(y) for _, y in data]
+    out = [B.conv_wgrad_approx(d, x, y) for d, x, y in zip(ds, Xs, dYs)] if alone else run_layers(ds, Xs, dYs, B.APPROX)
+    for d, (X, dY), y, got in zip(ds, data, dYs, out):
+        idx, sums = (t.cpu().numpy() for t in B.conv_wgrad_select(d, y))
+        with np.errstate(all="ignore"):
+            yield got.cpu().numpy(), oracle.wgrad_exact(oracle_shape(d), X, rounded_sums(d, idx, sums))
+
+
+@pytest.mark.parametrize("alone", [True, False])
+@pytest.mark.parametrize("bad", [0x7F80, 0xFF80, 0x7FC0])
+def test_approximated_infinite_and_nan_sums(bad, alone):
+    """A map whose sum is not finite, kept in a first, a last and an inner row: NaNs of the padding's zeros as in the exact gradient of the
+    sparsified map."""
+    ds = [desc(t) for t in ((40, 33, 4, 64), (9, 33, 8, 64), (5, 33, 16, 64), (9, 100, 8, 128))]
+    data = [rand_inputs(d, 7, "bf16") for d in ds]
+    for d, (X, dY) in zip(ds, data):
+        for at in ((0, 0, 0, 0), (-1, -1, -1, -1), (0, 1, 0, d.W // 2), (-1, 2, d.H // 2, 0), (2, 3, d.H - 1, 1), (1, 5, 1, d.W - 1)):
+            dY[at] = bad
+    for got, want in approximated(ds, data, alone):
+        fine = np.isfinite(want)
+        assert not fine.all() and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+        assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / 50
+
+
+@pytest.mark.parametrize("alone", [True, False])
+def test_approximated_infinities_of_X(alone):
+    """The operand's kept places of value zero make NaNs of an infinity that no position selected; other channels, and what is
+    not a NaN, are as without it."""
+    ds = [desc(t) for t in ((40, 33, 4, 64), (9, 33, 8, 64), (5, 33, 16, 64), (9, 100, 8, 128))]
+    data = [rand_inputs(d, 8, "bf16") for d in ds]
+    for d, (X, dY) in zip(ds, data):
+        X[2, 3, d.H - 1, 0], X[4, 20, 0, d.W - 1] = 0x7F80, 0xFF80
+    finite = [(np.where(X & 0x7F80 == 0x7F80, 0, X).astype(np.uint16), dY) for X, dY in data]
+    for (got, _), (_, want), d, (X, dY) in zip(approximated(ds, data, alone), approximated(ds, finite, alone), ds, data):
+        with np.errstate(all="ignore"):
+            selected = oracle.wgrad_approx(oracle_shape(d), X, dY)[0]       # the definition: the selected patches only
+        assert np.isfinite(np.delete(got, [3, 20], 1)).all() and np.isnan(got[np.isnan(selected)]).all()
+        assert not np.isfinite(got[~np.isfinite(selected)]).any() and np.isfinite(got).any(axis=(0, 2, 3)).all()
+        fine = np.isfinite(got)
+        assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / 50
 
 
 def shifted(a, by):
