@@ -305,7 +305,7 @@ def run_workload(args, name, machine, steps, warmup, headline):
     mfma_measured = None
     if machine:
         mfma_measured = round(machine["mfma_bf16_32x32x16_tflops"] / 6, 1) if dtype == "fp32" else machine["mfma_bf16_16x16x32_tflops"]
-    roofline = {"kernel": "exact phase = wgrad_exact_x3 + wgrad_exact_x3_planes (fp32 as bf16 pieces, groups of a variant in one launch), wgrad_exact_multi | wgrad_exact_stream (fp32 matrix core: strided and small layers) | wgrad_exact_bf16_multi + wgrad_exact_bf16_planes (bf16), + combine_table",
+    roofline = {"kernel": "exact phase = wgrad_exact_x3 + wgrad_exact_x3_planes (fp32 as bf16 pieces, groups of a variant in one launch), wgrad_exact_multi | wgrad_exact_stream (fp32 matrix core: strided and small layers) | wgrad_bf16_rows + wgrad_exact_bf16_multi + wgrad_exact_bf16_planes (bf16), + combine_table",
                 "bound": "mfma", "achieved": round(achieved_tf, 3), "peak": EXACT_PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
                 "frac": round(achieved_tf / EXACT_PEAK_TFLOPS[dtype], 4),
                 "traffic": traffic["exact_phase_bytes"] if traffic else None, "traffic_source": traffic_src if traffic else None,
@@ -328,7 +328,7 @@ def run_workload(args, name, machine, steps, warmup, headline):
                                        "tflops": round(tot["flops"] / tot["exact_us"] / 1e6, 2)} if single else None}
     achieved_gbs = tot["approx_bytes"] / phase_ms["approx"] / 1e6
     read_measured = machine["hbm_read_gbs"] if machine else None
-    roofline_approx = {"kernel": "approx phase = approx_fused_multi | approx_select_multi + (approx_gather_lds_multi | approx_gather_direct | wgrad_exact_bf16_multi<SPARSE>) | sparsify_small + wgrad_exact_plane2, + combine_table",
+    roofline_approx = {"kernel": "approx phase = approx_fused_multi | approx_select_multi + (approx_gather_regs + approx_gather_regs8 | approx_gather_lds_multi | approx_gather_direct | approx_bf16_rows | wgrad_exact_bf16_multi<SPARSE> | wgrad_exact_bf16_planes<SPARSE>) | sparsify_small + wgrad_exact_plane2, + combine_table",
                        "bound": "hbm", "achieved": round(achieved_gbs, 1), "peak": HBM_PEAK_GBS, "unit": "GB/s",
                        "frac": round(achieved_gbs / HBM_PEAK_GBS, 4),
                        "traffic": traffic["approx_phase_bytes"] if traffic else None, "traffic_source": traffic_src if traffic else None,
