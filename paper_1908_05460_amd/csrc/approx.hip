@@ -95,7 +95,7 @@ struct ApproxBatch {
     int32_t *hw[kMaxBatch];      // packed (row << 16 | col) of every map
     float *sum[kMaxBatch];       // signed sum of every map
     float *out[kMaxBatch];       // dW, or the batch-chunk partials
-    int hw_row = 65536, hw_col = 1, hw_base = 0;   // hw = row * hw_row + col * hw_col + hw_base, for a consumer that wants another form
+    int hw_row = 65536, hw_col = 1;   // hw = row * hw_row + col * hw_col, for a consumer that wants another form
     int hw_word = 0;             // hw = the sum, rounded to bf16, << 16 | position
 };
 
@@ -156,7 +156,7 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
         if (hw_out && ab.hw_word) {
             const uint32_t b = __float_as_uint(sum);
             hw_out[map] = (int32_t)(((b + 0x7fffu + ((b >> 16) & 1u)) & 0xffff0000u) | (uint32_t)pos);
-        } else if (hw_out) hw_out[map] = __mul24(pos / Wo, ab.hw_row) + __mul24(pos % Wo, ab.hw_col) + ab.hw_base;   // for the gather
+        } else if (hw_out) hw_out[map] = __mul24(pos / Wo, ab.hw_row) + __mul24(pos % Wo, ab.hw_col);   // for the gather
         if (sum_a) sum_a[map] = sum;
         if (sum_b) sum_b[map] = sum;
     }
@@ -1818,7 +1818,7 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
             if (rc != WGRAD_OK) return rc;
         }
         const RegsPosition at = regs_position(g);
-        ab.hw_row = at.row; ab.hw_col = at.col; ab.hw_base = at.base;
+        ab.hw_row = at.row; ab.hw_col = at.col;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rgq ? sq : nullptr);
         if (rc != WGRAD_OK) return rc;
         // (no more lost to rounding than the LDS gather loses, as it would cut the batch here)

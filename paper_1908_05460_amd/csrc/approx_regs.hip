@@ -359,8 +359,8 @@ bool regs_takes(const Geometry &g)
 
 RegsPosition regs_position(const Geometry &g)
 {
-    if (g.H == 2) return RegsPosition{8 * g.sh, 4 * g.sw, 0};
-    return RegsPosition{(g.H == 8 ? RegsLayout<8>::PITCH : RegsLayout<4>::PITCH) * g.sh, g.sw, 0};
+    if (g.H == 2) return RegsPosition{8 * g.sh, 4 * g.sw};
+    return RegsPosition{(g.H == 8 ? RegsLayout<8>::PITCH : RegsLayout<4>::PITCH) * g.sh, g.sw};
 }
 
 struct RegsItem {

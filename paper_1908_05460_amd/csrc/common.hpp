@@ -202,8 +202,8 @@ int launch_approx(const Geometry &g, const ApproxPlan &pl, const Batch &b, float
                   FusedQueue *fq = nullptr, Bf16Queue *bq = nullptr, GatherQueue *gq = nullptr,
                   SelectQueue *sq = nullptr, RegsQueue *rgq = nullptr, RowsQueue *rsq = nullptr);
 // approximated fp32 layers on 8x8, 4x4 and 2x2 planes (approx_regs.hip); a map's position as the kernel reads it is
-// row * its row + col * its col + its base
-struct RegsPosition { int row, col, base; };
+// row * its row + col * its col
+struct RegsPosition { int row, col; };
 bool regs_takes(const Geometry &g);
 RegsPosition regs_position(const Geometry &g);
 RegsQueue *regs_queue_new();
