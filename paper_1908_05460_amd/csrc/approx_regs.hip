@@ -370,7 +370,8 @@ struct RegsItem {
     const float *sum[kMaxBatch];
     char *part;                      // partial results of the first problem; the next problem's lie `stride` bytes on
     size_t stride;
-    int max_chunks, most_n;          // most chunks, most images of one (see regs_allowed)
+    int max_chunks;                  // that the workspace has room for
+    int fewest, least, most, additions;      // see regs_limits
     float scale;
 };
 struct RegsQueue {
@@ -380,16 +381,31 @@ struct RegsQueue {
 RegsQueue *regs_queue_new() { return new RegsQueue; }
 void regs_queue_delete(RegsQueue *q) { delete q; }
 
-// The number of chunks nearest to `want` that loses no more to rounding than chunks of most_n images do.  Those are the longest: the
-// square of the error against 64 bits grows by 0.011e-14 for each image of a chunk, beside 0.66e-14 (512 -> 512 @ 4x4, N = 128
-// in one / two / four chunks 1.45e-7 / 1.21e-7 / 1.09e-7).  Several chunks cost about as much as three images each (N = 8 in one 0.86e-7, in
-// two 0.87e-7; N = 16 in one 0.915e-7, in four 0.915e-7), so a short batch may stay whole, and others are not cut into less than
-// sixteen images (128 -> 160 @ 4x4, N = 128, two layers 1.11e-7 in sixteen chunks, 1.07e-7 in seven).
+// Which numbers of chunks lose no more to rounding than chunks of most_n images do, `least` of them.  What counts is how many
+// additions in a row lie between a product and the result: a chunk's images and the reduction of the chunks, fewer and longer chunks
+// where that is no more than with chunks of most_n (512 -> 512 @ 4x4, N = 128 in one / two / four chunks 1.45e-7 / 1.21e-7 / 1.09e-7;
+// 64 -> 256 @ 4x4, N = 229 in 29 chunks, whose reduction is spread over lanes, 1.10e-7, in four 1.23e-7).  A partial result costs more than
+// an image where X and the padding bring zeros, which round nothing, so that no chunk is cut into less than sixteen images without
+// need (128 -> 160 @ 4x4, N = 128, two layers 1.11e-7 in sixteen chunks, 1.07e-7 in seven).
+static int regs_additions(const RegsItem &I, int images)
+{
+    const int ch = (I.g.N + images - 1) / images;
+    return images + (ch > 1 ? combine_chain(I.g.dw_elems(), ch) : 0);
+}
+static void regs_limits(RegsItem &I, int most_n)
+{
+    const int N = I.g.N, limit = regs_additions(I, most_n);
+    I.additions = limit;
+    I.least = (N + most_n - 1) / most_n;
+    I.most = std::min(I.max_chunks, std::max(I.least, (N + 15) / 16));
+    I.fewest = (N + limit - 1) / limit;
+    while (I.fewest < I.least && regs_additions(I, (N + I.fewest - 1) / I.fewest) > limit) ++I.fewest;
+}
 static int regs_allowed(const RegsItem &I, int want)
 {
-    const int N = I.g.N, least = (N + I.most_n - 1) / I.most_n, most = std::min(I.max_chunks, std::max(least, (N + 15) / 16));
-    if (want < least && N <= I.most_n + 3 * least) return 1;
-    return std::max(least, std::min(want, most));
+    if (want <= I.fewest) return I.fewest;
+    if (want >= I.least) return std::min(want, I.most);
+    return regs_additions(I, (I.g.N + want - 1) / want) <= I.additions ? want : I.least;
 }
 
 // How the batches of n groups of layers, launched together, are cut, and how many wavefronts a workgroup has (eight share the
@@ -512,7 +528,8 @@ int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, con
     RegsQueue local;
     RegsQueue &q = queue ? *queue : local;
     RegsItem &I = q.item[q.n++];
-    I.g = g; I.b = b; I.max_chunks = max_chunks; I.most_n = most_n; I.scale = scale; I.part = (char *)part; I.stride = stride;
+    I.g = g; I.b = b; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride;
+    regs_limits(I, most_n);
     for (int i = 0; i < b.n; ++i) { I.at[i] = at[i]; I.sum[i] = sum[i]; }
     return queue ? WGRAD_OK : regs_flush(local, st, defer);
 }

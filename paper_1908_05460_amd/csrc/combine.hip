@@ -76,6 +76,19 @@ __global__ __launch_bounds__(kBlock) void combine_table(const CombineTable t)
     }
 }
 
+// log2 of the lanes that share an output: few outputs and many partials are spread over lanes
+static int combine_lanes_log(long elems, int nparts)
+{
+    return elems <= 16 * 1024 && nparts >= 64 ? 4 : (elems <= 256 * 1024 && nparts >= 16 ? 2 : 0);
+}
+
+// additions in a row that the reduction of a tensor's partials makes
+int combine_chain(long elems, int nparts)
+{
+    const int lg = combine_lanes_log(elems, nparts);
+    return lg ? ((nparts - 1) >> lg) + 1 + (1 << lg) : nparts;
+}
+
 int combine_flush(CombineQueue &q, hipStream_t st)
 {
     for (size_t first = 0; first < q.item.size(); first += kTableMax) {
@@ -85,8 +98,7 @@ int combine_flush(CombineQueue &q, hipStream_t st)
         int blocks = 0;
         for (int i = 0; i < n; ++i) {
             const CombineItem &c = q.item[first + i];
-            // spread the partial index over lanes when there are few outputs and many partials
-            int lg = (c.elems <= 16 * 1024 && c.nparts >= 64) ? 4 : ((c.elems <= 256 * 1024 && c.nparts >= 16) ? 2 : 0);
+            int lg = combine_lanes_log(c.elems, c.nparts);
             int ob = kBlock >> lg;
             if (lg == 0 && c.elems >= 64 * 1024 && c.elems % 4 == 0 && ((uintptr_t)c.part % 16) == 0 && ((uintptr_t)c.dW % 16) == 0) {
                 lg = kVec4;

@@ -265,6 +265,7 @@ struct CombineQueue {              // grows as needed; nothing is launched befor
     std::vector<CombineItem> item;
 };
 int combine_flush(CombineQueue &q, hipStream_t st);
+int combine_chain(long elems, int nparts);          // additions in a row that the reduction of a tensor's partials makes
 
 // dW[i][o] = scale * sum_j partials[i * prob_stride + j * elems + o] for the nprob problems of a batch;
 // with a queue the work is only recorded there
