@@ -16,8 +16,8 @@
 // touched by the asm blocks below only.  4x4 and 2x2: 127 registers, four wavefronts a SIMD, which hide each other's LDS and
 // scalar latencies; 8x8: 233, two, bound by reading the planes (128 clocks of the CU's LDS a wavefront and image against 72 of
 // multiply-adds).  X reaches LDS by loads that bypass the registers, a stage of 16 or 32 KB ahead.
-// VGG-19 fp32 at N = 128: layers on 4x4 and 2x2 planes 85 us (54 of them the multiply-adds' own issue, 14 the result's way to
-// memory), on 8x8 planes 29 to 34; the LDS gather took 197 for those on 8x8 and 4x4 planes, and the exact kernel on a sparsified dY
+// VGG-19 fp32 at N = 128: layers on 4x4 and 2x2 planes 87 us (54 of them the multiply-adds' own issue, 17 the results' way to
+// memory), on 8x8 planes 28; the LDS gather took 197 for those on 8x8 and 4x4 planes, and the exact kernel on a sparsified dY
 // 49 for those on 2x2 ones.
 #include <algorithm>
 #include <utility>

@@ -11,7 +11,8 @@
 //   - Filter columns 0 and 2 are X shifted by one element (v_alignbit), made once per row; a wavefront needs one of them.
 //   - Rows above and below the plane are not multiplied; columns beside it are zeros that the shift brings in.  (Where dY
 //     holds an infinity or a NaN in its first or last row, whose product with the padding is a NaN: see the end.)
-// So 8 or 10 matrix instructions come with about 13 others.  That ratio is what bounds such a kernel here: measured on this core,
+// So a step's 8 or 10 matrix instructions come with about 13 others (over VGG-19's run, folds, copies and write-out included, 3.3 to each,
+// matrix core busy 58 %).  That ratio is what bounds such a kernel here: measured on this core,
 // a vector instruction between 32x32x16 instructions costs 1.3 clocks of their 36, between 16x16x32 ones 2 of 19 -- they
 // do not run side by side -- and the row-window kernel (exact_bf16_kernel.hpp) has 3.6 of them to each.
 //   - X and dY go to LDS by loads that bypass the registers, four rows (16 KB of each) at a time, into a ring: while four are
