@@ -23,6 +23,10 @@
 //     kRowsFold blocks the sums are added to a second set of registers.  That is what the split of the taps buys: nine taps of
 //     32 x 32 channels in one wavefront leave no room for it.  (Split into three filter columns and twelve wavefronts the
 //     operands' reads were half again as many, and LDS bound the kernel: 128 -> 128 @ 16x16, N = 512: 44 us against 37.)
+//   - A workgroup of few blocks (short batches) adds them to the second set after each or every other block: a chain of n additions
+//     costs about n / 2 of the squared error, eight a block in the first set, one a fold in the second, so the two balance (8x8 planes, N =
+//     9 / 16 / 33, error against 64 bits with four blocks to a sum 8.7e-8 / 9.2e-8 / 9.3e-8, so 6.5e-8 / 7.0e-8 / 7.5e-8, the row-window
+//     kernel 5.7e-8 / 6.4e-8 / 7.6e-8).  It costs VGG-19 at N = 16 / 64 / 128 2 / 5 / 3 us (53 / 80 / 116).
 // The kernel without the reduction behind it: 38.7 GFLOP in a launch (64 -> 64 @ 32x32 to 512 -> 512 @ 4x4, N = 512) 36 to 41 us, 9 of
 // them set-up and write-out (the row-window kernel: 44 to 55); VGG-19's run, 395 GFLOP, 277 us of 350, where the card's power, not the
 // kernel's instructions, sets the clock.
@@ -60,6 +64,7 @@ constexpr int kRowsSlot = 2 * kRowsBlock;            // X and dY
 constexpr int kRowsRing = 4;                         // slots: the copies of three blocks are under way while one is multiplied
 constexpr int kRowsPitch = kRowsTile * 9 + 4;        // floats of a row of the result on its way out
 constexpr int kRowsLds = kRowsRing * kRowsSlot > kRowsTile * kRowsPitch * 4 ? kRowsRing * kRowsSlot : kRowsTile * kRowsPitch * 4;
+constexpr int kRowsShort = 12;                       // up to so many blocks a sum runs over one, up to twice as many over two
 constexpr int kRowsFold = 4;                         // blocks that a sum runs over before it is added to the rest
 
 constexpr int kRowsSparseSlot = kRowsBlock + 4096;   // SPARSE: X, and the maps of up to 16 images, 256 bytes an image
@@ -79,7 +84,8 @@ struct RowsParams {
 __host__ __device__ constexpr int rows_images(int W) { return 32 / W; }
 
 // S: 0: the wavefront has the taps of filter column 0 and the centre, 2: those of filter column 2 and the rest of column 1
-template <int W, int S, bool SPARSE>
+// SHORT: few blocks, after each or every other of which the sums are added to the rest
+template <int W, int S, bool SPARSE, bool SHORT>
 __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int bid, int nblk, int prob)
 {
     constexpr int GI = rows_images(W), H = W;
@@ -241,7 +247,8 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
     br_u8 a[2];                                      // and of dY a[q % 2]
     br_u8 ahead;                                     // SPARSE: the row of X after the next step's
     const uint32_t xbase = (uint32_t)cw * 8192, ybase = kRowsBlock + (uint32_t)kw * 8192;
-    int slot = 0, b = 0, fold = kRowsFold;
+    const int every = SHORT ? (blocks <= kRowsShort ? 1 : 2) : kRowsFold;
+    int slot = 0, b = 0, fold = every;
     // One block of four steps.  PH: the number (mod 3) of its first row in the stream; FIRST, LAST: its place in the
     // plane.  At the start of a step its row of dY and the rows of X up to its own are in registers.
     auto block = [&](auto ph_c, auto first_c, auto last_c, auto at_c) {
@@ -319,6 +326,10 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
             for (int i = 0; i < 16; ++i) acc[r][i] = 0.f;
         }
     };
+    auto short_fold = [&]() {                        // (a branch that is always taken where `every` is 1: without it the registers do not suffice)
+        if constexpr (SHORT)
+            if (b >= fold) { fold = b + every; fold_sums(); }
+    };
     typedef std::integral_constant<int, 0> i0;
     typedef std::integral_constant<int, 1> i1;
     typedef std::integral_constant<int, 2> i2;
@@ -352,30 +363,38 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
             x[0] = x[1]; m[0] = m[1];
         } else if constexpr (NB == 2) {
             block(i0(), yes(), no(), i0());
+            short_fold();
             block(i1(), no(), yes(), i1());
             x[0] = x[2]; m[0] = m[2];
         } else if constexpr (NB == 4) {
             block(i0(), yes(), no(), i0());
+            short_fold();
             block(i1(), no(), no(), i1());
+            short_fold();
             block(i2(), no(), no(), i2());
+            short_fold();
             block(i0(), no(), yes(), i3());
             x[0] = x[1]; m[0] = m[1];
         } else {
             block(i0(), yes(), no(), i0());
+            short_fold();
 #pragma unroll 1
             for (int q = 0; q < 2; ++q) {
                 block(i1(), no(), no(), i0());       // (the last argument is for SPARSE alone, which has no such planes)
+                short_fold();
                 block(i2(), no(), no(), i0());
+                short_fold();
                 block(i0(), no(), no(), i0());
-                fold_sums();
+                if constexpr (SHORT) short_fold();
+                else fold_sums();
             }
             block(i1(), no(), yes(), i0());
             x[0] = x[2]; m[0] = m[2];
         }
         // (before the loop is left: after the test the compiler moves all accumulators through memory)
-        if constexpr (NB == 4) fold_sums();
-        if constexpr (NB < 4 && !SPARSE)
-            if (b >= fold) { fold = b + kRowsFold; fold_sums(); }
+        if constexpr (NB == 4 && !SHORT) fold_sums();
+        if constexpr ((NB < 4 && !SPARSE) || SHORT)
+            if (b >= fold) { fold = b + every; fold_sums(); }
         if (b == blocks) break;
     }
     }
@@ -448,8 +467,15 @@ __device__ __forceinline__ void rows_wave(const RowsParams &p, char *smem, int b
 template <int W, bool SPARSE>
 __device__ __forceinline__ void rows_body(const RowsParams &p, char *smem, int bid, int nblk, int prob)
 {
-    if (__builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) == 0) rows_wave<W, 0, SPARSE>(p, smem, bid, nblk, prob);
-    else rows_wave<W, 2, SPARSE>(p, smem, bid, nblk, prob);
+    const bool first = __builtin_amdgcn_readfirstlane((int)threadIdx.x >> 8) == 0;
+    if constexpr (!SPARSE)
+        if (p.chunk_n / rows_images(W) * (W / 4) <= 2 * kRowsShort) {
+            if (first) rows_wave<W, 0, SPARSE, true>(p, smem, bid, nblk, prob);
+            else rows_wave<W, 2, SPARSE, true>(p, smem, bid, nblk, prob);
+            return;
+        }
+    if (first) rows_wave<W, 0, SPARSE, false>(p, smem, bid, nblk, prob);
+    else rows_wave<W, 2, SPARSE, false>(p, smem, bid, nblk, prob);
 }
 
 }  // namespace wgrad
