@@ -329,7 +329,7 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     const bool one_shape = nrows == 1 && wide_pairs == 1 && !others && !first && blocks >= (nexact > 1 ? 12 : 100) * tiles && (nexact > 1 || blocks >= 3072);
     const bool rows = one_shape || (blocks >= 320 && (nrows >= (others ? 4 : 3) || (nrows == 2 && nexact == 2 && blocks >= 12 * tiles)));
     each(WGRAD_EXACT, [&](LayerPlan &p, int) { if (!rows) p.ex.rows = 0; });
-    // Short fp32 layers, two and more of a shape, in the three-piece form: a launch more unless nothing is left for the fp32 multi-shape
+    // Short fp32 layers, two and more of a shape, in the form of 16-bit pieces: a launch more unless nothing is left for the fp32 multi-shape
     // one or there is one of that form already, which at 2 GFLOP is earned (ResNet-20 exact, N = 64: 5.4 GFLOP, 65.7 us against
     // 56.6; six of 128 -> 128 @ 4x4 and a strided layer, N = 64, 1.8 GFLOP: 34.1 us, with the form 41.2; of 405 runs timed both
     // ways 77 were slower without this line, none with it).
@@ -559,7 +559,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
 }
 
 // The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 3 a
-// short fp32 layer in the three-piece form, 4 planes in registers, 0 another.  For tests of the choice on the host.
+// short fp32 layer in the form of 16-bit pieces, 4 planes in registers, 0 another.  For tests of the choice on the host.
 namespace wgrad {
 int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form)
 {

@@ -81,7 +81,7 @@ __device__ __forceinline__ int xcd_contiguous_id(int bid, int nblocks)
 __device__ __forceinline__ float bf16_bits_to_float(uint16_t b) { return __uint_as_float((uint32_t)b << 16); }
 
 // ---- internal launchers (host). Each validates nothing: the C ABI layer did. ----
-// fp32 as three bf16 pieces, or bf16, on the bf16 matrix core (exact_x3.hip)
+// fp32 as bf16 or fp16 pieces, or bf16, on the 16-bit matrix cores (exact_x3.hip)
 struct X3Plan {
     int variant, ktiles, ctiles, splits;
     int nti, ht, iht, twc, h_tiles, w_tiles, n_groups, nch, ch, packed, halo, vlo, xcol0;

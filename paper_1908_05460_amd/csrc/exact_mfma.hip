@@ -585,7 +585,7 @@ static ExactPlan size_exact(const Geometry &g, ExactPlan pl)
     return pl;
 }
 
-// Where the forms above are the faster ones although the three-piece form takes the shape (of 2000 shapes timed both ways;
+// Where the forms above are the faster ones although the form of 16-bit pieces takes the shape (of 2000 shapes timed both ways;
 // us of this form / of the older one, N, C -> K @ H x W):
 static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan &x3, double gflop)
 {
@@ -623,7 +623,7 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
     return gflop >= 1.0 && (g.Wo <= 4 || (g.Wo == 5 && g.C % 64 == 0 && g.K % 64 == 0));
 }
 
-// The plan of a shape: the fp32 and bf16 forms above, and beside them the three-piece form (exact_x3.hip), which takes
+// The plan of a shape: the fp32 and bf16 forms above, and beside them the form of 16-bit pieces (exact_x3.hip), which takes
 // what the streaming form cannot (27x27 planes, 48 -> 96, N = 32: 76 -> 35 us; 224x224, 64 -> 64, N = 4: 302 -> 88) and
 // all but two kinds of what it can: long strided reductions, whose windows are mostly staging (128 -> 128 @ 56x56, stride
 // 2, N = 16, 3.7 GFLOP: 86 us against 60; at 0.2 to 0.9 GFLOP 13 to 23 against 16 to 29), and, in a run of several layers,

@@ -1,4 +1,4 @@
-// Host side of the three-piece bf16 form of the exact filter gradient (exact_x3_kernel.hpp): which shapes take it,
+// Host side of the exact filter gradient in 16-bit pieces (exact_x3_kernel.hpp): which shapes take it,
 // their tiles, and launches that carry several shapes.
 #include <algorithm>
 #include <vector>
@@ -7,13 +7,13 @@
 
 namespace wgrad {
 
-struct X3Variant { int bf, sh, ntc, s, sw, rag, halo, nch, di, xi, kp, cp, ch, lds, occ, plane; };
+struct X3Variant { int kind, sh, ntc, s, sw, rag, halo, nch, di, xi, kp, cp, ch, lds, occ, plane; };
 static const X3Variant kVariant[kX3Variants] = {
 #define X(ID, ...) {__VA_ARGS__, X3Config<__VA_ARGS__>::kLds, X3Config<__VA_ARGS__>::kOcc, 0},
     WGRAD_X3_VARIANTS_FP32(X)
     WGRAD_X3_VARIANTS_BF16(X)
 #undef X
-    {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(4), 2, 4}, {0, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(2), 2, 2},
+    {kX3Three, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(4), 2, 4}, {kX3Three, 32, 0, 3, 1, 0, 0, 0, 0, 0, 0, 0, 0, x3_planes_lds(2), 2, 2},
 };
 // workgroups that the chip holds at once
 static int x3_resident(const X3Variant &v) { return kNumCU * std::max(1, std::min(160 * 1024 / v.lds, v.occ)); }
@@ -102,8 +102,8 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
 static double x3_tile_us(const X3Variant &v, int share)
 {
     if (v.plane) return 1.1 * (v.plane == 4 ? std::max(share * 2.8, 4.2) : std::max(share * 0.85, 1.8));
-    const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.bf ? 1 : 6) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
-    const double stage = 0.3 + (v.rag && v.sw > 1 ? 0.6 : (v.bf ? 0.1 : 0.33)) * (v.di + v.xi * v.sw);
+    const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.kind == kX3Bf16 ? 1 : 6) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
+    const double stage = 0.3 + (v.rag && v.sw > 1 ? 0.6 : (v.kind == kX3Bf16 ? 0.1 : 0.33)) * (v.di + v.xi * v.sw);
     return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
 }
 static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(v) / kNumCU); }
@@ -113,7 +113,11 @@ static double x3_tile_us(const X3Variant &v) { return x3_tile_us(v, x3_resident(
 // tiles of 32 chunks are two steps each: 182 -> 211 @ 22x8, N = 61, 1.9e-7 at 31 of them, 1.4e-7 at 16, the fp32 matrix
 // core's kernel 1.3e-7.  The position form rounds its sums far less often (512 -> 512, N = 512, one sum of 64 / 32 tiles:
 // 2.0e-7 at 4x4, 7.7e-8 at 2x2).
-static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : (v.bf && v.sh == 16 && v.nch == 32 ? 16 : 32); }
+static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : (v.kind == kX3Bf16 && v.sh == 16 && v.nch == 32 ? 16 : 32); }
+// 4x4 planes: stages that a workgroup adds up from which on it takes two fp16 pieces to a number.  By themselves these are 1.3 to
+// 1.5e-7 off whatever the sum's length, three bf16 pieces 0.65e-7 after 2 stages, 1.0e-7 after 8 and 1.9e-7 after 16 (VGG-19's run, N =
+// 128); shorter sums would gain a fifth of their time (N = 128 alone, 4 stages: 50 us, 42).
+constexpr long kX3HalfStages = 12;
 constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
 
 // How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of
@@ -179,7 +183,7 @@ static int x3_choose_splits(const Geometry &g, const X3Plan &pl, int nprob)
 }
 
 // whether the variant reads bf16 rows in 8-byte pieces (4-byte aligned tensors), not element by element
-bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].bf && !kVariant[pl.variant].rag; }
+bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].kind == kX3Bf16 && !kVariant[pl.variant].rag; }
 
 // whether the variant stages rows of any width and cut rows; output channels of its tile
 bool x3_ragged(const X3Plan &pl) { return kVariant[pl.variant].rag; }
@@ -210,7 +214,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
     double best_cost = 1e30;
     for (int id = 0; id < kX3Variants; ++id) {
         const X3Variant &v = kVariant[id];
-        if (v.plane || v.bf != g.bf16 || v.s != g.S || v.sw != g.sw) continue;
+        if (v.plane || (v.kind == kX3Bf16) != (g.bf16 != 0) || v.s != g.S || v.sw != g.sw) continue;
         X3Plan pl{};
         if (!x3_tile(g, id, pl)) continue;
         // Matrix instructions, in units of a 16x16 tile of the result.  Long reductions do better with 32x32 tiles (a
@@ -221,7 +225,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
                       (v.sh == 32 ? 4.0 : (gflop < (g.bf16 ? 12.0 : 2.0) ? 0.9 : 1.15));
         // (ragged bf16 rows are loaded element by element: 64 -> 64 @ 56x56, stride 2, N = 128, 162 us that way, 53 with whole
         // rows and fewer of them to a tile)
-        cost *= v.rag ? (v.bf ? (v.sw > 1 ? 2.5 : 1.5) : 1.1) : (v.halo ? 1.02 : 1.0);
+        cost *= v.rag ? (g.bf16 ? (v.sw > 1 ? 2.5 : 1.5) : 1.1) : (v.halo ? 1.02 : 1.0);
         if (cost < best_cost) { best_cost = cost; best = pl; }
     }
     if (best_cost >= 1e30) return false;
@@ -286,7 +290,11 @@ static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
         lds = std::max(lds, (size_t)q.pl.lds);
     }
     m.begin[n] = blocks;
-    if (const int hw = kVariant[it[0]->pl.variant].plane) return x3_launch_planes(hw, m, blocks, lds, st);
+    if (const int hw = kVariant[it[0]->pl.variant].plane) {
+        bool half = hw == 4;
+        for (int i = 0; i < n; ++i) half = half && it[i]->pl.n_groups >= kX3HalfStages * it[i]->pl.splits;
+        return x3_launch_planes(hw, half, m, blocks, lds, st);
+    }
     if (it[0]->pl.variant >= kX3FirstBf16) return x3_launch_bf16(it[0]->pl.variant, m, blocks, lds, st);
     switch (it[0]->pl.variant) {
 #define X(ID, ...) case ID: return x3_launch(wgrad_exact_x3<X3Config<__VA_ARGS__>>, m, blocks, lds, st);

@@ -1,14 +1,26 @@
-// Exact filter gradient for fp32 inputs on the bf16 matrix core.
+// Exact filter gradient for fp32 inputs on the 16-bit matrix cores, with fp32 accumulation: a number is the sum of 16-bit
+// pieces, a product of two numbers the sum of the larger products of their pieces, each exact in fp32.
 //
-// An fp32 number is the exact sum of three bf16 numbers (8 significant bits each, rounded to nearest:
-// x = h + m + l with |m| <= 2^-8 |x|, |l| <= 2^-17 |x|), a product of two bf16 numbers is exact in fp32, and of
-// the nine products of two such sums the six largest leave out less than 2^-24 |x y|: the rounding of one fp32
-// product.  Six bf16 matrix instructions (1/16 of the fp32 instruction's time per product) therefore replace one
-// fp32 one, with fp32 accumulation as before.  bf16's smallest step is 2^-133, so both operands are scaled by 2^16 as
-// they are split, and the sums scaled back: every fp32 number then has its 24 bits in the pieces (unscaled, numbers
-// below 2^-110 lost bits of them: a tensor of 1e-36 was 2.5e-5 off).  What holds an infinity, a NaN or a number beyond
-// 2^111, or has a sum beyond 2^96, is recomputed by its workgroup on the fp32 matrix core, from the same tiles: the
-// pieces would make NaNs of infinities.
+// Three bf16 pieces (8 significant bits each, rounded to nearest: x = h + m + l exactly), six of nine products: what is left
+// out is below 2^-24 |x y|, the rounding of one fp32 product.  bf16's smallest step is 2^-133, so both operands are scaled by
+// 2^16 as they are split, and the sums scaled back: every fp32 number then has its 24 bits in the pieces (unscaled, a tensor
+// of 1e-36 was 2.5e-5 off).
+//
+// Two fp16 pieces (11 bits and a sign: 23 bits of the 24 at least), three of four products: half the matrix instructions and
+// 5 instead of 8 ns a number and SIMD of splitting.  fp16's range is met by a scale for every channel of a workgroup's tile, a
+// power of two taken from the largest number of the channel so far: tile by tile the numbers, still in registers, are compared
+// with fp16's range, and where one lies beyond it the channel's scale and the sums so far change to the new one (`rescale`;
+// always in a workgroup's first tile, rarely later).  A number down to 2^-16 of its channel's largest has its 23 bits, a
+// smaller one an error of 2^-39 of that; where a number or an item is below 2^-31 of it the workgroup recomputes as below.
+// What the pieces leave out and what the core rounds inside of products of 22 bits is 1e-7 of a result, whatever the length
+// of its sums, so this is the form of long sums: of the 32-wide tiles (VGG-19's run, N = 128: 4.5e-7 off with bf16 pieces,
+// 3.5e-7; N = 16 to 40: 2.5 -> 2.1e-7) and of 4x4 planes (exact_x3_planes.hip), where it is no further from 64 bits; 16-wide
+// tiles, whose sums are short or kept apart (64 -> 64 @ 8x8, N = 50: 0.86e-7, fp16 pieces 1.1e-7), keep bf16 pieces.
+// 64 -> 64 @ 32x32 / 256 -> 256 @ 8x8, N = 128: 62 / 59 us with bf16 pieces, 48 / 45; VGG-19's run 490 -> 342 us.
+//
+// What holds an infinity or a NaN, or numbers too large for the scale of bf16 pieces (beyond 2^111, sums beyond 2^96) or too
+// small beside their channel's largest for fp16's, is recomputed by its workgroup on the fp32 matrix core, from the same
+// tiles: the pieces would make NaNs of infinities.
 //
 // Implicit GEMM, rows = output channels k, columns = (input channel, filter row), reduction = "slots": the columns
 // of X (stride 1) or of one phase of X (column mod stride), eight consecutive slots of one output row being one
@@ -22,7 +34,10 @@
 // tile in their accumulators, and add them up through LDS at the end, so that a workgroup writes one partial
 // result.  All irregularity -- odd widths, any padding, strides, ragged last tiles, any alignment -- is met while
 // staging: dY and X rows are loaded in 16-byte pieces (4-byte aligned), split, and written to LDS as chunks of
-// each piece, zero outside the tensors.  Two workgroups share a CU: one stages while the other multiplies.
+// each piece, zero outside the tensors.  Two workgroups and more share a CU: one stages while another multiplies.  Timestamps
+// (64 -> 64 @ 32x32, N = 128, 512 workgroups of 8 tiles, 36 us each): set-up and first loads 4.3, the first tile's scales 2.4,
+// then a tile 0.7 of splitting, 0.5 of asking for the next, 1.4 of matrix instructions (0.9 alone), 0.4 at barriers; the
+// exchange and write-out 4.9; loads are never waited for.
 // bf16 inputs are their own only piece: the same kernel with one product per pair serves the bf16 shapes that
 // exact_bf16_kernel.hpp does not take.
 #pragma once
@@ -33,7 +48,8 @@
 namespace wgrad {
 
 typedef __bf16 x3_bf8 __attribute__((ext_vector_type(8)));
-typedef __bf16 x3_bf2 __attribute__((ext_vector_type(2)));
+typedef _Float16 x3_h8 __attribute__((ext_vector_type(8)));
+typedef _Float16 x3_h2 __attribute__((ext_vector_type(2)));
 typedef float x3_f16 __attribute__((ext_vector_type(16)));
 typedef uint32_t x3_u4 __attribute__((ext_vector_type(4)));
 
@@ -69,7 +85,7 @@ __host__ __device__ constexpr int x3_phase(int s, int S, int SW) { return (s - S
 
 // A = dY chunk as words w[0..3] with its neighbour words; element i of the result is element i - D of the row.
 template <int D>
-__device__ __forceinline__ x3_bf8 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
+__device__ __forceinline__ x3_u4 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
 {
     x3_u4 o;
     auto mid = [](uint32_t lo, uint32_t hi) { return __builtin_amdgcn_alignbit(hi, lo, 16); };
@@ -78,13 +94,14 @@ __device__ __forceinline__ x3_bf8 x3_shifted(uint32_t L, x3_u4 w, uint32_t R)
     else if (D == 1) o = x3_u4{mid(L, w[0]), mid(w[0], w[1]), mid(w[1], w[2]), mid(w[2], w[3])};
     else if (D == -2) o = x3_u4{w[1], w[2], w[3], R};
     else o = x3_u4{L, w[0], w[1], w[2]};
-    return __builtin_bit_cast(x3_bf8, o);
+    return o;
 }
 
-constexpr float kX3Scale = 65536.f, kX3Unscale = 1.f / (kX3Scale * kX3Scale);      // of an operand; of a sum of products
+constexpr int kX3Bf16 = 0, kX3Three = 1, kX3Half = 2;       // bf16 inputs; fp32 as three bf16 pieces, as two fp16 pieces
 
-// Two fp32 numbers, scaled -> one word (bf16 pair) of each piece
-__device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t &h, uint32_t &m, uint32_t &l, float scale = kX3Scale)
+constexpr float kX3Scale = 65536.f, kX3Unscale = 1.f / (kX3Scale * kX3Scale);      // bf16 pieces: of an operand; of a sum of products
+// Two fp32 numbers, scaled -> one word (bf16 pair) of each of three pieces
+__device__ __forceinline__ void x3_split3(float x0, float x1, float scale, uint32_t &h, uint32_t &m, uint32_t &l)
 {
     x0 *= scale;
     x1 *= scale;
@@ -99,6 +116,60 @@ __device__ __forceinline__ void x3_split2(float x0, float x1, uint32_t &h, uint3
     m = pk(r0, r1);
     const float q0 = r0 - __uint_as_float(m << 16), q1 = r1 - __uint_as_float(m & 0xffff0000u);
     l = pk(q0, q1);
+}
+
+// fp16 pieces: the power of two that takes a channel's numbers to at most 2^15, given the bits of the largest so far (that to 2^14 at
+// least), and of the channel that has only zeros yet: 2^127 takes every number below 2^-112 there.
+constexpr int kX3Unset = 127;
+constexpr uint32_t kX3Finite = 0x7f7fffffu;             // an infinity's channel is scaled like that of the largest number
+__device__ __forceinline__ int x3_exponent(uint32_t top) { const int e = 141 - (int)(top >> 23); return e < kX3Unset ? e : kX3Unset; }
+__device__ __forceinline__ float x3_power(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
+constexpr float kX3Most = 65504.f;                      // fp16's largest number
+constexpr float kX3Least = 0x1p-17f;                    // (see x3_range)
+
+// Two fp32 numbers, scaled -> one word (fp16 pair) of each piece.  (v_fma_mixlo_f16, which would scale, subtract and round at
+// once, takes 3.6 ns a SIMD, these 1.2, 1.2, 1.8, 1.9, 1.9 and 1.8.)
+__device__ __forceinline__ void x3_split2(float x0, float x1, float scale, uint32_t &h, uint32_t &l)
+{
+    auto pk = [](float a, float b) {
+        uint32_t v;
+        asm("v_cvt_pk_f16_f32 %0, %1, %2" : "=v"(v) : "v"(a), "v"(b));
+        return v;
+    };
+    h = pk(x0 * scale, x1 * scale);
+    float r0, r1;
+    asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel_hi:[0,0,1]" : "=v"(r0) : "v"(x0), "v"(scale), "v"(h));
+    asm("v_fma_mix_f32 %0, %1, %2, -%3 op_sel:[0,0,1] op_sel_hi:[0,0,1]" : "=v"(r1) : "v"(x1), "v"(scale), "v"(h));
+    l = pk(r0, r1);
+}
+
+// What the items of a thread (runs of numbers of one channel) say about the channels' scales: a number beyond fp16's
+// range, or an item all of whose numbers are so small that their pieces keep less than seven bits.
+struct X3Range {
+    float hi = 0.f;
+    uint32_t lo = ~0u;
+    __device__ __forceinline__ void item(float largest, float scale)
+    {
+        const float t = largest * __builtin_fabsf(scale);
+        hi = __builtin_fmaxf(hi, t);
+        const uint32_t b = __float_as_uint(t) - 1u;     // (zeros are no small numbers)
+        lo = b < lo ? b : lo;
+    }
+    template <int N> __device__ __forceinline__ void each(const uint32_t *v, float scale)      // every number an item of its own
+    {
+#pragma unroll
+        for (int i = 0; i < N; ++i) item(__builtin_fabsf(__uint_as_float(v[i])), scale);
+    }
+    __device__ __forceinline__ bool over() const { return hi > kX3Most; }
+    __device__ __forceinline__ bool under() const { return lo < __float_as_uint(kX3Least) - 1u; }
+};
+template <int N>
+__device__ __forceinline__ float x3_largest(const uint32_t *v)
+{
+    float m = 0.f;
+#pragma unroll
+    for (int i = 0; i < N; i += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(__uint_as_float(v[i]))), __builtin_fabsf(__uint_as_float(v[i + 1])));
+    return m;
 }
 
 // v = four columns loaded at a column clamped into the row, d = wanted column - loaded column: the wanted four,
@@ -117,17 +188,31 @@ __device__ __forceinline__ void x3_realign(float (&v)[4], int d)
     }
 }
 
-// BF: bf16 inputs, which are their own only piece.  SH: rows and columns of the matrix instruction (32: 32x32x16, 16: 16x16x32).  NTC: column tiles.  S: filter width.
+template <int KIND>
+__device__ __forceinline__ void x3_mfma(x3_f16 &z, x3_u4 a, x3_u4 b)
+{
+    if constexpr (KIND == kX3Half) z = __builtin_amdgcn_mfma_f32_32x32x16_f16(__builtin_bit_cast(x3_h8, a), __builtin_bit_cast(x3_h8, b), z, 0, 0, 0);
+    else z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(__builtin_bit_cast(x3_bf8, a), __builtin_bit_cast(x3_bf8, b), z, 0, 0, 0);
+}
+template <int KIND>
+__device__ __forceinline__ void x3_mfma(float4_t &z, x3_u4 a, x3_u4 b)
+{
+    if constexpr (KIND == kX3Half) z = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(x3_h8, a), __builtin_bit_cast(x3_h8, b), z, 0, 0, 0);
+    else z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(x3_bf8, a), __builtin_bit_cast(x3_bf8, b), z, 0, 0, 0);
+}
+
+// KIND: the pieces of a number (bf16 inputs are their own only piece).  SH: rows and columns of the matrix instruction (32: 32x32x16, 16: 16x16x32).  NTC: column tiles.  S: filter width.
 // SW: column stride.  RAG: rows whose width is not a multiple of four, or that start before column 0 of a tensor.
 // HALO: tiles may be parts of rows.  NCH: chunks of a tile; DI, XI:
 // staging items per thread; KP, CP: LDS chunks per channel of dY and of X (odd: conflict-free 16-byte reads); CH: channels
 // of X (compile-time, so that the operand reads have immediate offsets).
-template <bool BF_, int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
+template <int KIND_, int SH_, int NTC_, int S_, int SW_, bool RAG_, bool HALO_, int NCH_, int DI_, int XI_, int KP_, int CP_, int CH_>
 struct X3Config {
     static constexpr int SH = SH_, NTC = NTC_, S = S_, SW = SW_, NCH = NCH_, DI = DI_, XI = XI_, KP = KP_, CP = CP_, CH = CH_, NW = 4;
-    static constexpr bool BF = BF_, RAG = RAG_, HALO = HALO_;
-    static constexpr int NP = BF ? 1 : 3;                               // pieces of a number
-    static constexpr bool OWN = !BF && SH == 16 && S <= 3;                // the smaller products have sums of their own
+    static constexpr int KIND = KIND_;
+    static constexpr bool BF = KIND == kX3Bf16, HALF = KIND == kX3Half, RAG = RAG_, HALO = HALO_;
+    static constexpr int NP = BF ? 1 : (HALF ? 2 : 3);                  // pieces of a number
+    static constexpr bool OWN = KIND == kX3Three && SH == 16 && S <= 3;   // the smaller products have sums of their own
     static constexpr int DR = BF && !RAG ? 4 : 8;                       // registers of a chunk on its way to LDS
     static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG || (OWN && NTC > 1) ? 3 : 4);      // workgroups that share a CU
     static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
@@ -135,9 +220,14 @@ struct X3Config {
     static constexpr int SR = SH == 32 ? 1 : S;                         // filter columns per round of the final exchange
     static constexpr int kEx = NW * SR * SH * (SH + 4) * 4;             // bytes of a round (two alternate)
     static constexpr int kOutP = NTC * SH * S + 4;                      // pitch of the result tile gathered in LDS (16-byte rows)
-    static constexpr int kHead = NCH * 4 + 16;                          // the chunk table and a flag
+    static constexpr int kTop = HALF ? ((SH + CH) * 8 + 15) / 16 * 16 : 0;      // the channels' largest numbers and scales
+    static constexpr int kScales = HALF ? (DI + XI + (HALO ? 1 : 0)) * kBlock * 4 : 0;      // the scales of every thread's staging items
+    static constexpr bool PARK = HALF && HALO && SH == 32 && NTC > 1;     // the items themselves are kept in LDS too
+    static constexpr int kItems = PARK ? (DI + XI + 1) * kBlock * 8 : 0;
+    static constexpr int kFix = NCH * 4 + 16 + kTop;                    // the chunk table, flags, the channels' scales
+    static constexpr int kHead = kFix + kScales + kItems;               // ... and what the loop alone needs
     static constexpr int kTail = 2 * kEx + SH * kOutP * 4;
-    static constexpr int kLds = kHead + (kBuf > kTail ? kBuf : kTail);
+    static constexpr int kLds = kHead + kBuf > kFix + kTail ? kHead + kBuf : kFix + kTail;
 };
 
 template <class T>
@@ -146,7 +236,8 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 {
     constexpr int SH = T::SH, NTC = T::NTC, S = T::S, SW = T::SW, NCH = T::NCH, DI = T::DI, XI = T::XI, KP = T::KP, CP = T::CP,
                   NW = T::NW, NTHR = 64 * NW;
-    constexpr bool BF = T::BF, RAG = T::RAG, HALO = T::HALO;
+    constexpr int KIND = T::KIND;
+    constexpr bool BF = T::BF, HALF = T::HALF, RAG = T::RAG, HALO = T::HALO;
     constexpr int NP = T::NP, DR = T::DR, ESZ = BF ? 2 : 4;
     constexpr int CPS = 64 / SH;                        // chunks per step (lane groups of an operand)
     constexpr int NST = NCH / (CPS * NW);                // steps per wavefront and tile
@@ -160,7 +251,16 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     const int R = g.R, CRS = g.C * R * S, L = g.Ho * g.Wo;
 
     uint32_t *const tab = (uint32_t *)smem;                       // [NCH] chunk -> A offset | B offset << 12 | mask left << 30 | mask right << 31
-    uint32_t *const flag = tab + NCH;                        // set when the pieces cannot represent the tile
+    uint32_t *const flag = tab + NCH;                        // set when the pieces cannot represent a tile
+    uint32_t *const over = flag + 1;                         // set when a tile's numbers ask for smaller scales
+    uint32_t *const top = flag + 4;                          // per channel of dY [SH] and X [CH]: bits of the largest number so far
+    int *const expo = (int *)(top + SH + T::CH);             // ... and the exponent of its scale
+    // Per staging item of a thread, the scale of its channel; PARK: what is known of the item.  (In registers these would be
+    // what spills, and a reload among the loads of a tile waits for all of those: 64 -> 64 @ 224x224, N = 4, 82 us
+    // against 79.)
+    float *const scales = (float *)(smem + T::kFix);
+    auto scale_at = [&](int item) -> float & { return scales[item * NTHR + (int)threadIdx.x]; };
+    uint2 *const parked = (uint2 *)(smem + T::kFix + T::kScales);
     char *const buf = smem + T::kHead;                  // dY [NP][SH][KP] chunks, X [NP][CH][CP] chunks
     constexpr int dy_piece = T::kDy, x_piece = T::kX, kDyAt = 16, kXAt = 16 + NP * T::kDy + 16;
 
@@ -178,46 +278,62 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     const int wt_begin = (int)((long)split * tiles_total / p.splits);
     const int wt_end = (int)((long)(split + 1) * tiles_total / p.splits);
 
-    // ---- staging items, decoded once: where in the tile (LDS chunk | image << 16 | row << 20 | chunk column << 28, all
-    //      ones: none) and the row's element offset from the tile's first row ----
-    uint32_t d_at[DI], d_off[DI], x_at[XI], x_off[XI], h_at = ~0u, h_off = 0;
+    // ---- staging items, decoded once: where in the tile (LDS chunk | row << 20 | chunk column << 28, all ones: none) and the
+    //      byte offset of the row (of the chunk, where rows are whole) from the tile's first row ----
+    constexpr uint32_t kDead = 0x80000000u;
+    uint32_t d_at[DI], d_off[DI], x_at[XI], x_off[XI], h_at = ~0u, h_off = kDead;
     auto at_dst = [](uint32_t a) { return (a & 0xffffu) * 16u; };
-    auto at_n = [](uint32_t a) { return (int)(a >> 16 & 15u); };
     auto at_row = [](uint32_t a) { return (int)(a >> 20 & 255u); };
     auto at_wc = [](uint32_t a) { return (int)(a >> 28); };
 #pragma unroll
     for (int u = 0; u < DI; ++u) {
         const int e = tid + u * NTHR;
-        d_at[u] = ~0u; d_off[u] = 0;
+        d_at[u] = ~0u; d_off[u] = kDead;
         if (e < SH * p.nch) {
             uint32_t k_l, chk, row, wc, n_l, h_l;
             p.d_nch.divmod(e, k_l, chk);
             p.d_twc.divmod(chk, row, wc);
             p.d_ht.divmod(row, n_l, h_l);
             const uint32_t idx = HALO && p.halo ? 1 + row * (p.twc + 1) + wc : chk;
-            if (k0 + (int)k_l < g.K) d_at[u] = (k_l * KP + idx) | n_l << 16 | h_l << 20 | wc << 28;
+            if (k0 + (int)k_l < g.K) d_at[u] = (k_l * KP + idx) | h_l << 20 | wc << 28;
             d_off[u] = (n_l * g.K + k_l) * L + h_l * g.Wo;
+            d_off[u] = d_at[u] == ~0u ? kDead : (d_off[u] + (RAG ? 0 : wc * 8)) * ESZ;
         }
     }
     if (HALO && p.halo && tid < SH * p.nti * p.ht * 2) {           // one of a row's two neighbour words per thread
         const uint32_t side = tid & 1, k_l = (tid >> 1) / (p.nti * p.ht), row = (tid >> 1) % (p.nti * p.ht);
-        if (k0 + (int)k_l < g.K) h_at = (k_l * KP + row * (p.twc + 1) + (side ? p.twc + 1 : 0)) | row / p.ht << 16 | row % p.ht << 20 | side << 28;
-        h_off = (row / p.ht * g.K + k_l) * L + row % p.ht * g.Wo;
+        if (k0 + (int)k_l < g.K) h_at = (k_l * KP + row * (p.twc + 1) + (side ? p.twc + 1 : 0)) | row % p.ht << 20 | side << 28;
+        if (h_at != ~0u) h_off = ((row / p.ht * g.K + k_l) * L + row % p.ht * g.Wo) * ESZ;
     }
 #pragma unroll
     for (int u = 0; u < XI; ++u) {
         const int e = tid + u * NTHR;
-        x_at[u] = ~0u; x_off[u] = 0;
+        x_at[u] = ~0u; x_off[u] = kDead;
         if (e < p.ch * (int)p.d_xrow.d) {
             uint32_t c_l, rem, row, wc, n_l, ih_l;
             p.d_xrow.divmod(e, c_l, rem);
             p.d_twc.divmod(rem, row, wc);
             p.d_iht.divmod(row, n_l, ih_l);
-            if (c_first + (int)c_l < g.C) x_at[u] = (c_l * CP + row * p.twc * SW + wc) | n_l << 16 | ih_l << 20 | wc << 28;
+            if (c_first + (int)c_l < g.C) x_at[u] = (c_l * CP + row * p.twc * SW + wc) | ih_l << 20 | wc << 28;
             x_off[u] = (n_l * g.C + c_l) * (g.H * g.W) + ih_l * g.W;
+            x_off[u] = x_at[u] == ~0u ? kDead : (x_off[u] + (RAG ? 0 : wc * 8 * SW)) * ESZ;
         }
     }
 
+    auto park = [&](int item, uint32_t at, uint32_t off) { parked[item * NTHR + tid] = uint2{at, off}; };
+    if constexpr (T::PARK) {
+#pragma unroll
+        for (int u = 0; u < DI; ++u) park(u, d_at[u], d_off[u]);
+#pragma unroll
+        for (int u = 0; u < XI; ++u) park(DI + u, x_at[u], x_off[u]);
+        park(DI + XI, h_at, h_off);
+    }
+    // (opaque: the fields are taken out of the word where they are used, not kept in registers of their own across the loop)
+    auto fresh = [](uint32_t v) { asm volatile("" : "+v"(v)); return v; };
+    auto item = [&](int item, uint32_t at, uint32_t off) {
+        if constexpr (T::PARK) return parked[item * NTHR + (int)threadIdx.x];
+        else return uint2{fresh(at), off};
+    };
     uint32_t dr[DI][DR], xr[XI][DR * SW], hr[2];
     struct Tile { int n0, h0, wc0; };
     auto tile_of = [&](int wt) {
@@ -226,30 +342,36 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         p.d_htiles.divmod(q, ng, hti);
         return Tile{(int)ng * p.nti, (int)hti * p.ht, (int)wti * p.twc};
     };
-    // Loads go through a buffer descriptor of 2^31 bytes from the tile's first row; what is to be zero is asked for
-    // beyond it, and the hardware answers 0 without a memory access: nothing is masked afterwards.
-    constexpr uint32_t kDead = 0x80000000u;
-    auto rsrc_of = [&](const char *base) { return __builtin_amdgcn_make_buffer_rsrc((void *)base, 0, kDead, 0x00020000); };
-    // Four columns of a row (element offset `row`) from any column.  fp32 rows that are ragged are read at a column
-    // clamped into the row and realigned when they are staged; ragged bf16 rows (2-byte aligned) element by element.
-    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, bool live, uint32_t row, int col, int width, uint32_t *v) {
-        if constexpr (BF && RAG) {
-#pragma unroll
-            for (int e = 0; e < 4; ++e)
-                v[e] = __builtin_amdgcn_raw_buffer_load_b16(rs, live && (unsigned)(col + e) < (unsigned)width ? (row + (uint32_t)(col + e)) * 2u : kDead, 0, 0);
-        } else if constexpr (BF) {
-            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, live && col < width ? (row + (uint32_t)col) * 2u : kDead, 0, 0);
+    // Loads go through a buffer descriptor from the tile's first row to the end of the tensor, 2^31 bytes at most; what is to be
+    // zero is asked for beyond that, as the images past the last are anyway, and the hardware answers 0 without a memory
+    // access: nothing is masked afterwards.
+    auto rsrc_of = [&](const char *base, long at, long elems) {
+        const long left = (elems - at) * ESZ;
+        return __builtin_amdgcn_make_buffer_rsrc((void *)(base + at * ESZ), 0, left < (long)kDead ? (uint32_t)left : kDead, 0x00020000);
+    };
+    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, int first, uint32_t *v) {      // whole pieces of a row
+        if constexpr (BF) {
+            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, off, first, 0);
             v[0] = q[0]; v[1] = q[1];
         } else {
-            int c = col;
-            if (RAG) c = col < 0 ? 0 : (col > width - 4 ? width - 4 : col);
-            live = live && (RAG ? (unsigned)(col + 3) < (unsigned)(width + 3) : col < width);
-            const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, live ? (row + (uint32_t)c) * 4u : kDead, 0, 0);
+            const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, off, first, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = q[e];
         }
     };
-    constexpr bool FIX = RAG && !BF;
+    // Four columns of a ragged row (byte offset `row`) from any column.  fp32 rows are read at a column clamped into the
+    // row and realigned when they are staged; bf16 rows (2-byte aligned) element by element.
+    auto load4_ragged = [&](__amdgpu_buffer_rsrc_t rs, bool live, uint32_t row, int col, int width, uint32_t *v) {
+        if constexpr (BF) {
+#pragma unroll
+            for (int e = 0; e < 4; ++e)
+                v[e] = __builtin_amdgcn_raw_buffer_load_b16(rs, live && (unsigned)(col + e) < (unsigned)width ? row + (uint32_t)(col + e) * 2u : kDead, 0, 0);
+        } else {
+            const int c = col < 0 ? 0 : (col > width - 4 ? width - 4 : col);
+            load4(rs, live && (unsigned)(col + 3) < (unsigned)(width + 3) ? row + (uint32_t)c * 4u : kDead, 0, v);
+        }
+    };
+    constexpr bool FIX = RAG && !BF, SHIFT = FIX && SW == 1;
     auto fix4 = [&](int col, int width, uint32_t *v) {   // the four that were clamped into the row, back to their columns
         float q[4];
 #pragma unroll
@@ -258,72 +380,101 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
         for (int e = 0; e < 4; ++e) v[e] = __float_as_uint(q[e]);
     };
-    auto halo_col = [&](const Tile &t) { return (t.wc0 + (at_wc(h_at) ? p.twc : 0)) * 8 + p.vlo - (at_wc(h_at) ? 0 : 2); };
-    // (opaque: the fields are taken out of the word where they are used, not kept in registers of their own across the loop)
-    auto fresh = [](uint32_t v) { asm volatile("" : "+v"(v)); return v; };
     auto load_tile = [&](int wt) {
         const Tile t = tile_of(wt);
-        const int n_left = g.N - t.n0, h_left = g.Ho - t.h0;
-        const auto yb = rsrc_of(dYp + (((long)t.n0 * g.K + k0) * L + (long)t.h0 * g.Wo) * ESZ);
+        const int h_left = g.Ho - t.h0;
+        const int wy = HALO ? t.wc0 * 8 * ESZ : 0, wx = wy * SW;        // the tile's first column (added to what is in range without it)
+        const auto yb = rsrc_of(dYp, ((long)t.n0 * g.K + k0) * L + (long)t.h0 * g.Wo, (long)g.N * g.K * L);
 #pragma unroll
         for (int u = 0; u < DI; ++u) {
-            const uint32_t at = fresh(d_at[u]);
-            const bool live = at != ~0u && at_n(at) < n_left && at_row(at) < h_left;
-            const int col = (at_wc(at) + t.wc0) * 8 + p.vlo;
-            load4(yb, live, d_off[u], col, g.Wo, dr[u]);
-            load4(yb, live, d_off[u], col + 4, g.Wo, dr[u] + DR / 2);
+            const auto [at, off0] = item(u, d_at[u], d_off[u]);
+            if constexpr (RAG) {
+                const bool live = at_row(at) < h_left;
+                const int col = (at_wc(at) + t.wc0) * 8 + p.vlo;
+                load4_ragged(yb, live, off0, col, g.Wo, dr[u]);
+                load4_ragged(yb, live, off0, col + 4, g.Wo, dr[u] + DR / 2);
+            } else {
+                const uint32_t off = at_row(at) < h_left ? off0 : kDead;
+                const int left = g.Wo - t.wc0 * 8 - at_wc(at) * 8;
+                load4(yb, !HALO || left > 0 ? off : kDead, wy, dr[u]);
+                load4(yb, left > 4 ? off + 4 * ESZ : kDead, wy, dr[u] + DR / 2);
+            }
         }
         if (HALO && p.halo) {
-            const int col = halo_col(t);
-            const bool live = h_at != ~0u && at_n(h_at) < n_left && at_row(h_at) < h_left;
+            const auto [at, off0] = item(DI + XI, h_at, h_off);
+            const int col = (t.wc0 + (at_wc(at) ? p.twc : 0)) * 8 + p.vlo - (at_wc(at) ? 0 : 2);
+            const bool live = at_row(at) < h_left;
 #pragma unroll
             for (int e = 0; e < 2; ++e) {
-                const uint32_t off = live && (unsigned)(col + e) < (unsigned)g.Wo ? (h_off + col + e) * (uint32_t)ESZ : kDead;
+                const uint32_t off = live && (unsigned)(col + e) < (unsigned)g.Wo ? off0 + (uint32_t)(col + e) * ESZ : kDead;
                 if constexpr (BF) hr[e] = __builtin_amdgcn_raw_buffer_load_b16(yb, off, 0, 0);
                 else hr[e] = __builtin_amdgcn_raw_buffer_load_b32(yb, off, 0, 0);
             }
         }
         // (the first input row of a tile may lie above the plane: offsets count from it, dead rows are never asked for)
         const int ih0 = t.h0 * g.sh - g.ph;
-        const auto xb = rsrc_of(Xp + ((long)t.n0 * g.C + c_first) * g.H * g.W * ESZ);
-        const uint32_t row0 = (uint32_t)(ih0 * g.W);
+        const auto xb = rsrc_of(Xp, ((long)t.n0 * g.C + c_first) * g.H * g.W + (long)ih0 * g.W, (long)g.N * g.C * g.H * g.W);
 #pragma unroll
         for (int u = 0; u < XI; ++u) {
-            const uint32_t at = fresh(x_at[u]);
-            const int ih = ih0 + at_row(at);
-            const bool live = at != ~0u && at_n(at) < n_left && (unsigned)ih < (unsigned)g.H;
-            const int col = (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
+            const auto [at, off0] = item(DI + u, x_at[u], x_off[u]);
+            const bool in = (unsigned)(ih0 + at_row(at)) < (unsigned)g.H;
+            if constexpr (RAG) {
+                const int col = (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
 #pragma unroll
-            for (int q = 0; q < 2 * SW; ++q) load4(xb, live, x_off[u] + row0, col + 4 * q, g.W, xr[u] + DR / 2 * q);
+                for (int q = 0; q < 2 * SW; ++q) load4_ragged(xb, in, off0, col + 4 * q, g.W, xr[u] + DR / 2 * q);
+            } else {
+                const uint32_t off = in ? off0 : kDead;
+                const int left = g.W - t.wc0 * 8 * SW - at_wc(at) * 8 * SW;
+#pragma unroll
+                for (int q = 0; q < 2 * SW; ++q) load4(xb, left > 4 * q ? off + 4 * q * ESZ : kDead, wx, xr[u] + DR / 2 * q);
+            }
         }
     };
-    // The matrix core rounds downwards what it adds to a larger sum, and five of the six products are small: the sums of the
-    // products come out low, by as much as 4.5e-7 of the result's size (64 -> 64 @ 224x224, N = 4).  Every other workgroup of
-    // a reduction sums the negated products, so that what they lose cancels.
-    const float dy_scale = split & 1 ? -kX3Scale : kX3Scale;
-    // a chunk's pieces (plain: its fp32 numbers, in the place of the first two) to LDS; v(e): its element e (fp32 bits, or bf16 bits in the low half)
-    auto put = [&](auto v, char *dst, int piece, float scale, auto plain) {
+    // The matrix core rounds downwards what it adds to a larger sum, and most of the products are small: the sums of the
+    // products come out low, by as much as 4.5e-7 of the result's size (bf16 pieces, 64 -> 64 @ 224x224, N = 4).  Every other
+    // workgroup of a reduction sums the negated products, so that what they lose cancels.
+    const float sign = split & 1 ? -1.f : 1.f, dy_scale = sign * kX3Scale;
+    auto range = [&]() {
+        X3Range r;
+#pragma unroll
+        for (int u = 0; u < DI; ++u) r.item(x3_largest<8>(dr[u]), scale_at(u));
+        if (HALO && p.halo) r.hi = __builtin_fmaxf(r.hi, x3_largest<2>(hr) * __builtin_fabsf(scale_at(DI + XI)));
+#pragma unroll
+        for (int u = 0; u < XI; ++u) r.item(x3_largest<8 * SW>(xr[u]), scale_at(DI + u));
+        return r;
+    };
+    // a chunk's pieces (plain: its fp32 numbers, in the place of the first two) to LDS; v(e): its element e (fp32 bits, or bf16
+    // bits in the low half); lo, hi: bits by which its two groups of four columns, loaded clamped into the row, lie too high
+    auto put = [&](auto v, char *dst, int piece, float scale, uint32_t lo, uint32_t hi, auto plain) {
         if constexpr (decltype(plain)::value && !BF) {
             *(x3_u4 *)dst = x3_u4{v(0), v(1), v(2), v(3)};
             *(x3_u4 *)(dst + piece) = x3_u4{v(4), v(5), v(6), v(7)};
             return;
         }
-        x3_u4 h, m, l;
+        x3_u4 w[NP];
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-            if constexpr (BF) h[e] = __builtin_amdgcn_perm(v(2 * e + 1), v(2 * e), 0x05040100u);
+            if constexpr (BF) w[0][e] = __builtin_amdgcn_perm(v(2 * e + 1), v(2 * e), 0x05040100u);
             else {
                 uint32_t a, b, c;
-                x3_split2(__uint_as_float(v(2 * e)), __uint_as_float(v(2 * e + 1)), a, b, c, scale);
-                h[e] = a; m[e] = b; l[e] = c;
+                if constexpr (HALF) x3_split2(__uint_as_float(v(2 * e)), __uint_as_float(v(2 * e + 1)), scale, a, b);
+                else x3_split3(__uint_as_float(v(2 * e)), __uint_as_float(v(2 * e + 1)), scale, a, b, c);
+                w[0][e] = a; w[1][e] = b;
+                if constexpr (!HALF) w[2][e] = c;
             }
         }
-        *(x3_u4 *)dst = h;
-        if constexpr (!BF) {
-            *(x3_u4 *)(dst + piece) = m;
-            *(x3_u4 *)(dst + 2 * piece) = l;
+#pragma unroll
+        for (int q = 0; q < NP; ++q) {
+            if constexpr (SHIFT) {
+                const uint64_t a = ((uint64_t)w[q][1] << 32 | w[q][0]) >> (lo & 63), b = ((uint64_t)w[q][3] << 32 | w[q][2]) >> (hi & 63);
+                w[q] = x3_u4{(uint32_t)a, (uint32_t)(a >> 32), (uint32_t)b, (uint32_t)(b >> 32)};
+            }
+            *(x3_u4 *)(dst + q * piece) = w[q];
         }
     };
+    // columns by which the four of `col` on, loaded at a column clamped into the row from the right, lie too far right (of four
+    // that lie outside altogether nothing was loaded)
+    auto behind = [](int col, int width) { return (uint32_t)(col > width - 4 ? col - (width - 4) : 0); };
     // element i of a run of columns in staging registers
     auto elem = [&](const uint32_t *v, int i) -> uint32_t {
         if constexpr (DR == 4) return i & 1 ? v[i / 2] >> 16 : v[i / 2];
@@ -332,49 +483,62 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     auto commit_tile = [&](int wt, auto plain) {
         Tile t{0, 0, 0};
         if (FIX) t = tile_of(wt);
+        // (rows that start left of the tensor's were also clamped from the left: rare, and put right in registers)
+        const bool regs = SW > 1 || decltype(plain)::value;
 #pragma unroll
         for (int u = 0; u < DI; ++u) {
-            const uint32_t at = fresh(d_at[u]);
+            const auto [at, off0] = item(u, d_at[u], d_off[u]);
+            uint32_t lo = 0, hi = 0;
             if constexpr (FIX) {
                 const int col = (at_wc(at) + t.wc0) * 8 + p.vlo;
-                fix4(col, g.Wo, dr[u]);
-                fix4(col + 4, g.Wo, dr[u] + 4);
+                if (regs || p.vlo < 0) {
+                    fix4(col, g.Wo, dr[u]);
+                    fix4(col + 4, g.Wo, dr[u] + 4);
+                } else {
+                    lo = behind(col, g.Wo) * 16u;
+                    hi = behind(col + 4, g.Wo) * 16u;
+                }
             }
             if (at != ~0u) {
                 if constexpr (DR == 4) *(x3_u4 *)(buf + kDyAt + at_dst(at)) = x3_u4{dr[u][0], dr[u][1], dr[u][2], dr[u][3]};
-                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, dy_scale, plain);
+                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, HALF ? scale_at(u) : dy_scale, lo, hi, plain);
             }
         }
-        if (HALO && p.halo && h_at != ~0u) {
-            char *const chunk = buf + kDyAt + at_dst(h_at);
-            if constexpr (decltype(plain)::value && !BF) {
-                *(uint2 *)(chunk + (at_wc(h_at) ? 0 : dy_piece + 8)) = uint2{hr[0], hr[1]};
+        if (HALO && p.halo) {
+            const uint32_t at = item(DI + XI, h_at, h_off).x;
+            char *const chunk = buf + kDyAt + at_dst(at);
+            if (at == ~0u) {
+            } else if constexpr (decltype(plain)::value && !BF) {
+                *(uint2 *)(chunk + (at_wc(at) ? 0 : dy_piece + 8)) = uint2{hr[0], hr[1]};
             } else {
-                uint32_t h, m = 0, l = 0;
-                if constexpr (BF) h = hr[0] | hr[1] << 16;
-                else x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), h, m, l, dy_scale);
-                char *const dst = chunk + (at_wc(h_at) ? 0 : 12);
-                *(uint32_t *)dst = h;
-                if constexpr (!BF) {
-                    *(uint32_t *)(dst + dy_piece) = m;
-                    *(uint32_t *)(dst + 2 * dy_piece) = l;
-                }
+                uint32_t w[3];
+                if constexpr (BF) w[0] = hr[0] | hr[1] << 16;
+                else if constexpr (HALF) x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), scale_at(DI + XI), w[0], w[1]);
+                else x3_split3(__uint_as_float(hr[0]), __uint_as_float(hr[1]), dy_scale, w[0], w[1], w[2]);
+#pragma unroll
+                for (int q = 0; q < NP; ++q) *(uint32_t *)(chunk + (at_wc(at) ? 0 : 12) + q * dy_piece) = w[q];
             }
         }
 #pragma unroll
         for (int u = 0; u < XI; ++u) {
-            const uint32_t at = fresh(x_at[u]);
+            const auto [at, off0] = item(DI + u, x_at[u], x_off[u]);
+            uint32_t lo = 0, hi = 0;
             if constexpr (FIX) {
                 const int col = (at_wc(at) + t.wc0) * 8 * SW + p.xcol0;
+                if (regs || p.xcol0 < 0) {
 #pragma unroll
-                for (int q = 0; q < 2 * SW; ++q) fix4(col + 4 * q, g.W, xr[u] + 4 * q);
+                    for (int q = 0; q < 2 * SW; ++q) fix4(col + 4 * q, g.W, xr[u] + 4 * q);
+                } else {
+                    lo = behind(col, g.W) * 16u;
+                    hi = behind(col + 4, g.W) * 16u;
+                }
             }
             if (at != ~0u) {
                 if constexpr (DR == 4 && SW == 1) *(x3_u4 *)(buf + kXAt + at_dst(at)) = x3_u4{xr[u][0], xr[u][1], xr[u][2], xr[u][3]};
                 else {
 #pragma unroll
                     for (int f = 0; f < SW; ++f)
-                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, kX3Scale, plain);
+                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, HALF ? scale_at(DI + u) : kX3Scale, lo, hi, plain);
                 }
             }
         }
@@ -396,13 +560,19 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         }
         tab[q] = e;
     }
-    if (tid == 0) *flag = 0;
+    if (tid == 0) *flag = *over = 0;
+    if constexpr (HALF) {
+        if (tid < SH + T::CH) { top[tid] = 0; expo[tid] = kX3Unset; }
+#pragma unroll
+        for (int u = 0; u < DI + XI + (HALO ? 1 : 0); ++u) scale_at(u) = x3_power(kX3Unset);
+    }
     for (int e = tid; e < NP * SH; e += NTHR) *(x3_u4 *)(buf + kDyAt + (e * KP + KP - 1) * 16) = x3_u4{0u, 0u, 0u, 0u};
     if (k0 + SH > g.K || c_first + T::CH > g.C) {
         // rows and columns beyond the result are never staged: zeros, so that no left-over bits make infinities of them
         for (int e = tid; e < T::kBuf / 16; e += NTHR) *(x3_u4 *)(buf + e * 16) = x3_u4{0u, 0u, 0u, 0u};
-        __syncthreads();
+        if (!HALF) __syncthreads();
     }
+    if (HALF) __syncthreads();
 
     acc_t acc[NTC][S];
 #pragma unroll
@@ -422,24 +592,91 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
             for (int v = 0; v < AV; ++v) small[t][s][v] = 0.f;
 
+    // column `col` of column tile t: its channel (of those staged) and filter row
+    auto column = [&](int t, int col, int &c_l, int &r) {
+        c_l = col; r = t;
+        if (p.packed) {
+            const int q = coltile * NTC * SH + t * SH + col;
+            uint32_t c, rr;
+            p.d_r.divmod(q < g.C * R ? q : c_first * R, c, rr);
+            c_l = (int)c - c_first; r = (int)rr;
+        }
+        if (c_l >= p.ch) c_l = p.ch - 1;                // a column beyond C: some staged channel, never written out
+    };
     // this lane's columns: byte offset of (channel, filter row) in a piece of X
     int coloff[NTC];
     const int row_bytes = p.twc * SW * 16;
 #pragma unroll
     for (int t = 0; t < NTC; ++t) {
-        int c_l = i, r = t;
-        if (p.packed) {
-            const int col = coltile * NTC * SH + t * SH + i;
-            uint32_t c, rr;
-            p.d_r.divmod(col < g.C * R ? col : c_first * R, c, rr);
-            c_l = (int)c - c_first; r = (int)rr;
-        }
-        if (c_l >= p.ch) c_l = p.ch - 1;                // a column beyond C: some staged channel, never written out
+        int c_l, r;
+        column(t, i, c_l, r);
         coloff[t] = c_l * CP * 16 + r * row_bytes;
     }
     const char *const a_row = buf + kDyAt + i * KP * 16, *const Xs = buf + kXAt;
+    // A tile has a number beyond fp16's range at the scale of its channel (in a workgroup's first tile they all do): scales
+    // for the largest numbers so far, and the sums so far in units of them.
+    auto rescale = [&](bool sums) {
+        auto note = [&](int row, const float m) {
+            if (m > 0.f) { const uint32_t b = __float_as_uint(m); atomicMax(top + row, b < kX3Finite ? b : kX3Finite); }
+        };
+        uint32_t row[DI + XI + 1], rem;
+#pragma unroll
+        for (int u = 0; u < DI; ++u) {
+            p.d_nch.divmod(tid + u * NTHR, row[u], rem);
+            if (item(u, d_at[u], d_off[u]).x == ~0u) row[u] = 0;
+            note((int)row[u], x3_largest<8>(dr[u]));
+        }
+#pragma unroll
+        for (int u = 0; u < XI; ++u) {
+            p.d_xrow.divmod(tid + u * NTHR, row[DI + u], rem);
+            row[DI + u] = item(DI + u, x_at[u], x_off[u]).x == ~0u ? SH : SH + row[DI + u];
+            note((int)row[DI + u], x3_largest<8 * SW>(xr[u]));
+        }
+        row[DI + XI] = 0;
+        if (HALO && p.halo) {
+            if (item(DI + XI, h_at, h_off).x != ~0u) row[DI + XI] = (tid >> 1) / (p.nti * p.ht);
+            note((int)row[DI + XI], x3_largest<2>(hr));
+        }
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < DI + XI + (HALO ? 1 : 0); ++u)
+            scale_at(u) = (u < DI || u == DI + XI ? sign : 1.f) * x3_power(x3_exponent(top[row[u]]));
+        if (sums) {
+            auto change = [&](int row) { return x3_exponent(top[row]) - expo[row]; };
+#pragma unroll
+            for (int t = 0; t < NTC; ++t) {
+                int c_l, r;
+                column(t, i, c_l, r);
+                const int dc = change(SH + c_l);
+#pragma unroll
+                for (int v = 0; v < AV; ++v) {
+                    const int d = dc + change(SH == 32 ? 8 * (v / 4) + 4 * kk + v % 4 : 4 * kk + v);
+#pragma unroll
+                    for (int s = 0; s < S; ++s) acc[t][s][v] = __builtin_ldexpf(acc[t][s][v], d);
+                    __builtin_amdgcn_sched_barrier(0);       // (one exponent at a time: there are no registers for all)
+                }
+            }
+        }
+        // (a number that sets a scale hides what is small beside it in its item: here each is looked at by itself)
+        X3Range r;
+#pragma unroll
+        for (int u = 0; u < DI; ++u) r.each<8>(dr[u], scale_at(u));
+#pragma unroll
+        for (int u = 0; u < XI; ++u) r.each<8 * SW>(xr[u], scale_at(DI + u));
+        if (r.under()) *flag = 1;
+        __syncthreads();
+        if (tid < SH + T::CH) expo[tid] = x3_exponent(top[tid]);
+        if (tid == 0) *over = 0;
+    };
     for (int wt = wt_begin; wt < wt_end; ++wt) {
-        if (wt != wt_begin) __syncthreads();            // everyone has left the previous tile
+        if constexpr (HALF) {
+            const X3Range r = range();
+            if (r.over()) *over = 1;
+            if (r.under()) *flag = 1;
+        }
+        if (HALF || wt != wt_begin) __syncthreads();    // everyone has left the previous tile
+        if constexpr (HALF)
+            if (*(volatile uint32_t *)over) rescale(wt != wt_begin);
         // The scheduling fences keep the matrix instructions out of the staging: an instruction that waits for the matrix
         // core holds up what follows it, and then both workgroups of a CU stage while neither multiplies (N = 512,
         // 128 -> 128 @ 16x16: 190 us without them, 155 with).
@@ -462,7 +699,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 uint32_t lw = *(const uint32_t *)(ap + qa * dy_piece - 4), rw = *(const uint32_t *)(ap + qa * dy_piece + 16);
                 if (e & (1u << 30)) lw = 0;
                 if (e & (1u << 31)) rw = 0;
-                x3_bf8 a[S];
+                x3_u4 a[S];
                 a[0] = x3_shifted<x3_shift(0, S, SW)>(lw, w, rw);
                 a[1] = x3_shifted<x3_shift(1, S, SW)>(lw, w, rw);
                 a[2] = x3_shifted<x3_shift(2, S, SW)>(lw, w, rw);
@@ -475,13 +712,12 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                         const char *const q0 = bp + coloff[t] + f * p.twc * 16;
 #pragma unroll
                         for (int qb = NP - 1 - qa; qb >= 0; --qb) {
-                            const x3_bf8 b = *(const x3_bf8 *)(q0 + qb * x_piece);
+                            const x3_u4 b = *(const x3_u4 *)(q0 + qb * x_piece);
 #pragma unroll
                             for (int s = 0; s < S; ++s) {
                                 if (x3_phase(s, S, SW) != f) continue;
                                 acc_t &z = T::OWN && qa + qb ? small[T::OWN ? t : 0][T::OWN ? s : 0] : acc[t][s];
-                                if constexpr (SH == 32) z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[s], b, z, 0, 0, 0);
-                                else z = __builtin_amdgcn_mfma_f32_16x16x32_bf16(a[s], b, z, 0, 0, 0);
+                                x3_mfma<KIND>(z, a[s], b);
                             }
                         }
                     }
@@ -509,13 +745,15 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     const float any = (worst[0] + worst[1]) + (worst[2] + worst[3]);
     if (any != any) *flag = 1;
     __syncthreads();
-    float unscale = BF ? 1.f : (split & 1 ? -kX3Unscale : kX3Unscale);
+    bool scaled = HALF;
+    float unscale = KIND == kX3Three ? sign * kX3Unscale : 1.f;
     if (*(volatile uint32_t *)flag) {
         // Once more on the fp32 matrix core, with the tiles' numbers as they are: a lane's chunk goes through it column by
         // column, dY's own eight and the two on each side, each with the X of its tap's slot.  X counts only where that
         // column of dY exists (an infinity of X is no product of a row's end), and a column whose slot lies before the
         // first chunk or behind the last meets the padding's zero.  (64 -> 64 @ 32x32, N = 128, 60 us: one infinity 128, an
         // infinity to every map or nothing but NaNs 190; with scalar multiply-adds from memory 4900 and 6500.)
+        scaled = false;
         unscale = 1.f;
 #pragma unroll
         for (int t = 0; t < NTC; ++t)
@@ -595,17 +833,18 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     // ---- the wavefronts' sums: through LDS, SR filter columns of a column tile at a time (four rows of a lane side by
     //      side, two buffers, one barrier a round), gathered as rows of the result and written out in whole lines ----
     constexpr int KTP = SH + 4, SR = T::SR, P = T::kOutP;
-    float *const rows = (float *)(buf + 2 * T::kEx);    // [SH][P]
+    char *const tail = smem + T::kFix;
+    float *const rows = (float *)(tail + 2 * T::kEx);   // [SH][P]
 #pragma unroll
     for (int ts = 0; ts < NTC * S; ts += SR) {
         const int t = ts / S, s0 = ts % S;
-        float *const red = (float *)(buf + (ts / SR & 1) * T::kEx);      // [NW][SR][SH columns][KTP]
+        float *const red = (float *)(tail + (ts / SR & 1) * T::kEx);      // [NW][SR][SH columns][KTP]
 #pragma unroll
         for (int s = 0; s < SR; ++s)
 #pragma unroll
             for (int v = 0; v < AV / 4; ++v) {
                 acc_t z = acc[ts / S][ts % S + s];
-                if (!BF) z *= unscale;                  // (before they are added up, which could leave fp32's range)
+                if (KIND == kX3Three) z *= unscale;     // (before they are added up, which could leave fp32's range)
                 *(float4_t *)(red + ((wq * SR + s) * SH + i) * KTP + (SH == 32 ? 8 * v + 4 * kk : 4 * kk)) =
                     float4_t{z[4 * v], z[4 * v + 1], z[4 * v + 2], z[4 * v + 3]};
             }
@@ -617,6 +856,13 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             for (int w = 1; w < NW; ++w) sum += *(const float4_t *)(red + ((w * SR + sl) * SH + col) * KTP + 4 * rq);
             // entry of an output channel's row: (c * R + r) * S + s
             const int lc = (p.packed ? t * SH + col : col * R + t) * S + s0 + sl;
+            if (HALF && scaled) {
+                int c_l, r;
+                column(t, col, c_l, r);
+                const int e = expo[SH + c_l];
+#pragma unroll
+                for (int v = 0; v < 4; ++v) sum[v] = sign * __builtin_ldexpf(sum[v], -(e + expo[4 * rq + v]));
+            }
 #pragma unroll
             for (int v = 0; v < 4; ++v) rows[(4 * rq + v) * P + lc] = sum[v];
         }
@@ -642,21 +888,21 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     }
 }
 
-// (id, BF, SH, NTC, S, SW, RAG, HALO, NCH, DI, XI, KP, CP, CH)
+// (id, KIND, SH, NTC, S, SW, RAG, HALO, NCH, DI, XI, KP, CP, CH)
 #define WGRAD_X3_VARIANTS_FP32(X) \
-    X(0, false, 32, 3, 3, 1, false, false, 16, 2, 3, 17, 25, 32) X(1, false, 32, 3, 3, 1, false, true, 16, 2, 3, 23, 25, 32) \
-    X(2, false, 32, 3, 3, 1, true, true, 16, 2, 3, 23, 25, 32) X(3, false, 16, 3, 3, 1, false, false, 16, 1, 2, 17, 33, 16) \
-    X(4, false, 16, 3, 3, 1, true, true, 16, 1, 2, 23, 33, 16) X(5, false, 16, 3, 3, 2, false, false, 16, 1, 3, 17, 69, 16) \
-    X(6, false, 16, 3, 3, 2, true, true, 16, 1, 3, 23, 69, 16) X(7, false, 16, 1, 3, 1, false, false, 16, 1, 1, 17, 25, 7) \
-    X(8, false, 16, 1, 3, 1, true, true, 16, 1, 1, 23, 25, 7) X(9, false, 32, 1, 3, 1, false, false, 16, 2, 2, 17, 25, 12) \
-    X(10, false, 32, 1, 3, 1, true, true, 16, 2, 2, 23, 25, 12) X(11, false, 16, 5, 5, 1, true, true, 16, 1, 3, 23, 49, 16)
+    X(0, kX3Half, 32, 3, 3, 1, false, false, 16, 2, 3, 17, 25, 32) X(1, kX3Half, 32, 3, 3, 1, false, true, 16, 2, 3, 23, 25, 32) \
+    X(2, kX3Half, 32, 3, 3, 1, true, true, 16, 2, 3, 23, 25, 32) X(3, kX3Three, 16, 3, 3, 1, false, false, 16, 1, 2, 17, 33, 16) \
+    X(4, kX3Three, 16, 3, 3, 1, true, true, 16, 1, 2, 23, 33, 16) X(5, kX3Three, 16, 3, 3, 2, false, false, 16, 1, 3, 17, 69, 16) \
+    X(6, kX3Three, 16, 3, 3, 2, true, true, 16, 1, 3, 23, 69, 16) X(7, kX3Three, 16, 1, 3, 1, false, false, 16, 1, 1, 17, 25, 7) \
+    X(8, kX3Three, 16, 1, 3, 1, true, true, 16, 1, 1, 23, 25, 7) X(9, kX3Half, 32, 1, 3, 1, false, false, 16, 2, 2, 17, 25, 12) \
+    X(10, kX3Half, 32, 1, 3, 1, true, true, 16, 2, 2, 23, 25, 12) X(11, kX3Three, 16, 5, 5, 1, true, true, 16, 1, 3, 23, 49, 16)
 #define WGRAD_X3_VARIANTS_BF16(X) \
-    X(12, true, 32, 3, 3, 1, false, false, 32, 4, 5, 33, 41, 32) X(13, true, 32, 3, 3, 1, false, true, 16, 2, 3, 23, 25, 32) \
-    X(14, true, 32, 3, 3, 1, true, true, 16, 2, 3, 23, 25, 32) X(15, true, 16, 3, 3, 1, false, false, 32, 2, 3, 33, 41, 16) \
-    X(16, true, 16, 3, 3, 1, true, true, 32, 2, 3, 43, 41, 16) X(17, true, 16, 3, 3, 2, false, false, 16, 1, 3, 17, 69, 16) \
-    X(18, true, 16, 3, 3, 2, true, true, 16, 1, 3, 23, 69, 16) X(19, true, 16, 1, 3, 1, false, false, 32, 2, 2, 33, 41, 7) \
-    X(20, true, 16, 1, 3, 1, true, true, 32, 2, 2, 43, 41, 7) X(21, true, 32, 1, 3, 1, false, false, 32, 4, 2, 33, 41, 12) \
-    X(22, true, 32, 1, 3, 1, true, true, 16, 2, 2, 23, 25, 12) X(23, true, 16, 5, 5, 1, true, true, 16, 1, 3, 23, 49, 16)
+    X(12, kX3Bf16, 32, 3, 3, 1, false, false, 32, 4, 5, 33, 41, 32) X(13, kX3Bf16, 32, 3, 3, 1, false, true, 16, 2, 3, 23, 25, 32) \
+    X(14, kX3Bf16, 32, 3, 3, 1, true, true, 16, 2, 3, 23, 25, 32) X(15, kX3Bf16, 16, 3, 3, 1, false, false, 32, 2, 3, 33, 41, 16) \
+    X(16, kX3Bf16, 16, 3, 3, 1, true, true, 32, 2, 3, 43, 41, 16) X(17, kX3Bf16, 16, 3, 3, 2, false, false, 16, 1, 3, 17, 69, 16) \
+    X(18, kX3Bf16, 16, 3, 3, 2, true, true, 16, 1, 3, 23, 69, 16) X(19, kX3Bf16, 16, 1, 3, 1, false, false, 32, 2, 2, 33, 41, 7) \
+    X(20, kX3Bf16, 16, 1, 3, 1, true, true, 32, 2, 2, 43, 41, 7) X(21, kX3Bf16, 32, 1, 3, 1, false, false, 32, 4, 2, 33, 41, 12) \
+    X(22, kX3Bf16, 32, 1, 3, 1, true, true, 16, 2, 2, 23, 25, 12) X(23, kX3Bf16, 16, 5, 5, 1, true, true, 16, 1, 3, 23, 49, 16)
 constexpr int kX3FirstBf16 = 12, kX3Planes4 = 24, kX3Planes2 = 25, kX3Variants = 26;
 
 // The parameters are read through the kernel-argument segment pointer: indexing the by-value argument with a run-time
@@ -685,7 +931,7 @@ inline int x3_launch(void (*kernel)(const X3Multi), const X3Multi &m, int blocks
 }
 // 2x2 and 4x4 planes, position by position (exact_x3_planes.hip)
 int x3_planes_lds(int hw);
-int x3_launch_planes(int hw, const X3Multi &m, int blocks, size_t lds, hipStream_t st);
+int x3_launch_planes(int hw, bool half, const X3Multi &m, int blocks, size_t lds, hipStream_t st);
 int x3_launch_bf16(int variant, const X3Multi &m, int blocks, size_t lds, hipStream_t st);      // instantiated in a file of their own
 
 }  // namespace wgrad

@@ -1,4 +1,4 @@
-// The three-piece form of the exact filter gradient (exact_x3_kernel.hpp) on 2x2 and 4x4 planes, position by position
+// The exact filter gradient in 16-bit pieces (exact_x3_kernel.hpp) on 2x2 and 4x4 planes, position by position
 // (fp32, 3x3 filters, stride 1, padding 1):
 //
 //     dW[k][c][r][s] = sum over positions p = (h, w) whose tap (r, s) lies inside X, q = (h + r - 1, w + s - 1), of
@@ -7,10 +7,10 @@
 // The reduction of a G_pq runs over images, so an operand is "eight images of one position" and the (position, tap)
 // pairs whose tap meets only padding are never multiplied: 100 of 144 are left on a 4x4 plane, 16 of 36 on a 2x2 plane.
 // Matrix instructions and the staging's vector instructions (three to each) take turns: the matrix core is busy 43 % of
-// the cycles of VGG-19's launch, at 2.27 GHz, so a product left out is time saved.  512 -> 512 @ 4x4 takes 16.9 / 53.8 /
-// 150 us at N = 16 / 128 / 512 (the fp32 matrix core 28.8 / 72 / 228, the row form of exact_x3_kernel.hpp 63 at N = 128),
-// 2x2 15.4 -> 45.7 us where the fp32 matrix core takes 49.7 (N = 512) and half of its time in a run of layers; VGG-19's
-// run 526 -> 489 us.
+// the cycles of VGG-19's launch, at 2.27 GHz, so a product left out is time saved.  512 -> 512 @ 4x4 takes 16.9 / 50 us at
+// N = 16 / 128 with three bf16 pieces (the fp32 matrix core 28.8 / 72, the row form of exact_x3_kernel.hpp 63 at N = 128),
+// 154 -> 103 us at N = 512 with two fp16 pieces, which long sums take (kX3HalfStages); 2x2 15.4 -> 45.7 us where the fp32 matrix
+// core takes 49.7 (N = 512) and half of its time in a run of layers.
 //
 // A workgroup owns 64 output channels x 32 input channels; its four wavefronts share the taps out (13, 12, 12 and 15
 // steps of a 4x4 plane's stage, 4 each of a 2x2 plane's; which wavefront has which changes with the workgroup), so that
@@ -28,12 +28,15 @@ namespace {
 
 constexpr int kPK = 64, kPC = 32;                       // channels of the result tile
 
-template <int HW>
+template <int HW, int KIND>
 struct PlaneCfg {
     static constexpr int P = HW * HW, U = HW == 4 ? 16 : 8;            // positions; operand slots of a stage (2x2: position, image group)
     static constexpr int IMG = HW == 4 ? 8 : 16;                        // images of a stage
     static constexpr int kA = U * kPK * 16, kB = U * kPC * 16;          // bytes of one piece
-    static constexpr int kLds = 16 + 3 * (kA + kB);
+    static constexpr bool HALF = KIND == kX3Half;
+    static constexpr int NP = HALF ? 2 : 3;                             // pieces of a number
+    static constexpr int kHead = 16 + (HALF ? (kPK + kPC) * 8 : 0);     // flags; the channels' largest numbers and scales
+    static constexpr int kLds = kHead + NP * (kA + kB);
 };
 
 // taps (r * 3 + s) of a role
@@ -60,14 +63,14 @@ template <int HW> constexpr int tap_count(int tap)
     return n;
 }
 
-template <int HW, int ROLE>
+template <int HW, int KIND, int ROLE>
 struct PlaneRole {
     static constexpr int NT = (role_taps<HW>(ROLE, 0) >= 0) + (role_taps<HW>(ROLE, 1) >= 0) + (role_taps<HW>(ROLE, 2) >= 0) + (role_taps<HW>(ROLE, 3) >= 0);
 
     template <int T, int STEP>
-    static __device__ __forceinline__ void step(x3_f16 (&acc)[NT][2], x3_f16 (&small)[2], const char *a0, const char *b0, int kk)
+    static __device__ __forceinline__ void step(x3_f16 (&acc)[NT][2], x3_f16 (&part)[2], const char *a0, const char *b0, int kk)
     {
-        typedef PlaneCfg<HW> C;
+        typedef PlaneCfg<HW, KIND> C;
         constexpr int tap = role_taps<HW>(ROLE, T), shift = (tap / 3 - 1) * HW + tap % 3 - 1;
         // operand slots of lane groups 0 and 1
         constexpr int p0 = tap_position<HW>(tap, HW == 4 ? 2 * STEP : STEP), p1 = HW == 4 ? tap_position<HW>(tap, 2 * STEP + 1) : p0;
@@ -76,48 +79,47 @@ struct PlaneRole {
         constexpr int ua0 = HW == 4 ? p0 : 2 * p0, ua1 = HW == 4 ? q1 : 2 * p0 + 1;
         constexpr int ub0 = HW == 4 ? p0 + shift : 2 * (p0 + shift), ub1 = HW == 4 ? q1 + shift : 2 * (p0 + shift) + 1;
         const char *const ap = a0 + (kk ? ua1 : ua0) * (kPK * 16), *const bp = b0 + (kk ? ub1 : ub0) * (kPC * 16);
-        x3_bf8 b[3];
+        x3_u4 b[C::NP];
 #pragma unroll
-        for (int q = 0; q < 3; ++q) b[q] = *(const x3_bf8 *)(bp + q * C::kB);
+        for (int q = 0; q < C::NP; ++q) b[q] = *(const x3_u4 *)(bp + q * C::kB);
 #pragma unroll
-        for (int qa = 2; qa >= 0; --qa) {
-            x3_bf8 a[2];
+        for (int qa = C::NP - 1; qa >= 0; --qa) {
+            x3_u4 a[2];
 #pragma unroll
             for (int m = 0; m < 2; ++m) {
-                x3_u4 v = *(const x3_u4 *)(ap + qa * C::kA + m * 32 * 16);
-                if (odd && kk) v = x3_u4{0u, 0u, 0u, 0u};               // the last of an odd number of positions
-                a[m] = __builtin_bit_cast(x3_bf8, v);
+                a[m] = *(const x3_u4 *)(ap + qa * C::kA + m * 32 * 16);
+                if (odd && kk) a[m] = x3_u4{0u, 0u, 0u, 0u};            // the last of an odd number of positions
             }
 #pragma unroll
-            for (int qb = 2 - qa; qb >= 0; --qb)
+            for (int qb = C::NP - 1 - qa; qb >= 0; --qb)
 #pragma unroll
                 for (int m = 0; m < 2; ++m) {
-                    // the five smaller products of a stage's steps have a sum of their own, 2^-8 of the whole: it rounds that
-                    // much finer, and the whole is rounded once a step instead of six times
-                    x3_f16 &z = qa + qb ? small[m] : acc[T][m];
-                    z = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a[m], b[qb], z, 0, 0, 0);
+                    // Three pieces: the five smaller products of a stage's steps have a sum of their own, 2^-8 of the whole: it
+                    // rounds that much finer, and the whole is rounded once a step instead of six times.  Two pieces: all
+                    // products of a stage have, and the whole is rounded once a stage.
+                    x3_mfma<KIND>(C::HALF || qa + qb ? part[m] : acc[T][m], a[m], b[qb]);
                 }
         }
     }
     template <int T, int STEP>
-    static __device__ __forceinline__ void steps(x3_f16 (&acc)[NT][2], x3_f16 (&small)[2], const char *a0, const char *b0, int kk)
+    static __device__ __forceinline__ void steps(x3_f16 (&acc)[NT][2], x3_f16 (&part)[2], const char *a0, const char *b0, int kk, float sign)
     {
         constexpr int n = tap_count<HW>(role_taps<HW>(ROLE, T)), all = HW == 4 ? (n + 1) / 2 : n;
         if constexpr (STEP == 0) {
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) small[m][v] = 0.f;
+                for (int v = 0; v < 16; ++v) part[m][v] = 0.f;
         }
-        step<T, STEP>(acc, small, a0, b0, kk);
-        if constexpr (STEP + 1 < all) steps<T, STEP + 1>(acc, small, a0, b0, kk);
+        step<T, STEP>(acc, part, a0, b0, kk);
+        if constexpr (STEP + 1 < all) steps<T, STEP + 1>(acc, part, a0, b0, kk, sign);
         else {
 #pragma unroll
             for (int m = 0; m < 2; ++m)
 #pragma unroll
-                for (int v = 0; v < 16; ++v) acc[T][m][v] += small[m][v];
+                for (int v = 0; v < 16; ++v) acc[T][m][v] = KIND == kX3Half ? __builtin_fmaf(part[m][v], sign, acc[T][m][v]) : acc[T][m][v] + part[m][v];
             __builtin_amdgcn_sched_barrier(0);       // (across taps the scheduler's liking for early reads costs 67 spilled registers)
-            if constexpr (T + 1 < NT) steps<T + 1, 0>(acc, small, a0, b0, kk);
+            if constexpr (T + 1 < NT) steps<T + 1, 0>(acc, part, a0, b0, kk, sign);
         }
     }
 
@@ -127,7 +129,7 @@ struct PlaneRole {
     template <int T>
     static __device__ __forceinline__ void plain_steps(x3_f16 (&acc)[NT][2], const char *a0, const char *b0, int kk)
     {
-        typedef PlaneCfg<HW> C;
+        typedef PlaneCfg<HW, KIND> C;
         constexpr int tap = role_taps<HW>(ROLE, T), dh = tap / 3 - 1, dw = tap % 3 - 1;
 #pragma unroll 1
         for (int step = 0; step < (HW == 4 ? C::P / 2 : C::P); ++step) {
@@ -151,17 +153,19 @@ struct PlaneRole {
     }
 };
 
-template <int HW, int ROLE>
+template <int HW, int KIND, int ROLE>
 __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, const float *dYp, float *out, char *smem, int k0, int c0,
                                             int st_begin, int st_end)
 {
-    typedef PlaneCfg<HW> C;
-    typedef PlaneRole<HW, ROLE> R;
+    typedef PlaneCfg<HW, KIND> C;
+    typedef PlaneRole<HW, KIND, ROLE> R;
     const Geometry &g = p.g;
     const int tid = threadIdx.x, lane = tid & 63;
     const int i = lane & 31, kk = lane >> 5;
     uint32_t *const flag = (uint32_t *)smem;
-    char *const As = smem + 16, *const Bs = As + 3 * C::kA;
+    uint32_t *const over = flag + 1, *const top = flag + 4;             // (see exact_x3_kernel.hpp; dY's channels, then X's)
+    int *const expo = (int *)(top + kPK + kPC);
+    char *const As = smem + C::kHead, *const Bs = As + C::NP * C::kA;
 
     // Staging items: (channel, four positions [4x4: a row of the plane], eight images).  4x4: every thread has one of dY and
     // half of one of X (four images); 2x2: 128 of dY, 64 of X, one for a thread.
@@ -169,7 +173,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     constexpr int SETS = HW == 4 ? 2 : 1;
     uint32_t src[SETS], dst[SETS];                                      // byte offset of the first image's piece; LDS byte offset
     bool is_a[SETS];
-    int first[SETS];                                                    // the item's first image in the stage
+    int first[SETS], chan[SETS];                                        // the item's first image in the stage; its row of `top`
     auto items = [&](int tid) {
 #pragma unroll
         for (int u = 0; u < SETS; ++u) {
@@ -187,10 +191,11 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
                 grp = is_a[u] ? f / kPK : f / kPC;                          // group of eight images (2 and more: no item)
                 first[u] = 8 * grp;
             }
+            chan[u] = is_a[u] ? row : kPK + row;
             const bool live = HW == 4 || grp < 2;
             const int chans = is_a[u] ? g.K : g.C, rows = is_a[u] ? kPK : kPC;
             src[u] = live && (is_a[u] ? k0 : c0) + row < chans ? (uint32_t)((first[u] * chans + row) * C::P + (HW == 4 ? grp * 4 : 0)) * 4u : kDead;
-            dst[u] = live ? (uint32_t)((is_a[u] ? 0 : 3 * C::kA) + ((HW == 4 ? 4 * grp : grp) * rows + row) * 16 + 8 * half) : ~0u;
+            dst[u] = live ? (uint32_t)((is_a[u] ? 0 : C::NP * C::kA) + ((HW == 4 ? 4 * grp : grp) * rows + row) * 16 + 8 * half) : ~0u;
         }
     };
     items(tid);
@@ -212,7 +217,19 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
         images(reg0, 0, 8);
         if constexpr (SETS > 1) images(reg1, 1, 4);
     };
-    auto commit = [&](auto plain) {
+    float scale[SETS];
+#pragma unroll
+    for (int u = 0; u < SETS; ++u) scale[u] = x3_power(kX3Unset);
+    auto largest = [&](auto &reg, auto words) {
+        float m = 0.f;
+#pragma unroll
+        for (int j = 0; j < 2 * decltype(words)::value; ++j)
+#pragma unroll
+            for (int q = 0; q < 4; q += 2)
+                m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(__uint_as_float(reg[j][q]))), __builtin_fabsf(__uint_as_float(reg[j][q + 1])));
+        return m;
+    };
+    auto commit = [&](float sign, auto plain) {
         auto images = [&](auto &reg, int u, auto words) {
             constexpr int NW = decltype(words)::value;                  // words of a piece: pairs of images
             if (dst[u] == ~0u) return;
@@ -229,17 +246,18 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
 #pragma unroll
                 for (int q = 0; q < 4; ++q) {                          // position q of the item
                     typedef uint32_t words_t __attribute__((ext_vector_type(NW)));
-                    words_t h, m, l;
+                    words_t w[C::NP];
 #pragma unroll
                     for (int e = 0; e < NW; ++e) {
+                        const float x0 = __uint_as_float(reg[2 * e][q]), x1 = __uint_as_float(reg[2 * e + 1][q]);
                         uint32_t x, y, z;
-                        x3_split2(__uint_as_float(reg[2 * e][q]), __uint_as_float(reg[2 * e + 1][q]), x, y, z);
-                        h[e] = x; m[e] = y; l[e] = z;
+                        if constexpr (C::HALF) x3_split2(x0, x1, is_a[u] ? sign * scale[u] : scale[u], x, y);
+                        else x3_split3(x0, x1, kX3Scale, x, y, z);
+                        w[0][e] = x; w[1][e] = y;
+                        if constexpr (!C::HALF) w[2][e] = z;
                     }
-                    char *const d = As + dst[u] + (HW == 4 ? q : 2 * q) * rows * 16;
-                    *(words_t *)d = h;
-                    *(words_t *)(d + piece) = m;
-                    *(words_t *)(d + 2 * piece) = l;
+#pragma unroll
+                    for (int p = 0; p < C::NP; ++p) *(words_t *)(As + dst[u] + p * piece + (HW == 4 ? q : 2 * q) * rows * 16) = w[p];
                 }
             }
         };
@@ -248,7 +266,11 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     };
 
     load(st_begin);
-    if (tid == 0) *flag = 0;
+    if (tid == 0) *flag = *over = 0;
+    if constexpr (C::HALF) {
+        if (tid < kPK + kPC) { top[tid] = 0; expo[tid] = kX3Unset; }
+        __syncthreads();
+    }
     x3_f16 acc[R::NT][2];
     auto clear = [&]() {
 #pragma unroll
@@ -260,16 +282,62 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     };
     clear();
     const char *const a0 = As + i * 16, *const b0 = Bs + i * 16;
+    auto rescale = [&](float m0, float m1, bool sums) {                // (see exact_x3_kernel.hpp)
+                    auto note = [&](int u, float m) {
+                        if (m > 0.f) { const uint32_t b = __float_as_uint(m); atomicMax(top + chan[u], b < kX3Finite ? b : kX3Finite); }
+                    };
+                    note(0, m0);
+                    if constexpr (SETS > 1) note(1, m1);
+                    __syncthreads();
+                    X3Range r;
+        #pragma unroll
+                    for (int u = 0; u < SETS; ++u) scale[u] = x3_power(x3_exponent(top[chan[u]]));
+        #pragma unroll
+                    for (int j = 0; j < 8; ++j)
+        #pragma unroll
+                        for (int q = 0; q < 4; ++q) r.item(__builtin_fabsf(__uint_as_float(reg0[j][q])), scale[0]);
+                    if constexpr (SETS > 1)
+        #pragma unroll
+                        for (int j = 0; j < 4; ++j)
+        #pragma unroll
+                            for (int q = 0; q < 4; ++q) r.item(__builtin_fabsf(__uint_as_float(reg1[j][q])), scale[1]);
+                    if (r.under()) *flag = 1;
+                    if (sums) {
+                        auto change = [&](int row) { return x3_exponent(top[row]) - expo[row]; };
+                        const int dc = change(kPK + i);
+        #pragma unroll
+                        for (int m = 0; m < 2; ++m)
+        #pragma unroll
+                            for (int v = 0; v < 16; ++v) {
+                                const int d = dc + change(m * 32 + 8 * (v / 4) + 4 * kk + v % 4);
+        #pragma unroll
+                                for (int t = 0; t < R::NT; ++t) acc[t][m][v] = __builtin_ldexpf(acc[t][m][v], d);
+                                __builtin_amdgcn_sched_barrier(0);
+                            }
+                    }
+                    __syncthreads();
+                    if (tid < kPK + kPC) expo[tid] = x3_exponent(top[tid]);
+                    if (tid == 0) *over = 0;
+    };
     for (int st = st_begin; st < st_end; ++st) {
-        if (st != st_begin) __syncthreads();
+        if constexpr (C::HALF) {
+            const float m0 = largest(reg0, std::integral_constant<int, 4>{}), m1 = SETS > 1 ? largest(reg1, std::integral_constant<int, 2>{}) : 0.f;
+            X3Range r;
+            r.item(m0, scale[0]);
+            if constexpr (SETS > 1) r.item(m1, scale[1]);
+            if (r.over()) *over = 1;
+            if (r.under()) *flag = 1;
+            __syncthreads();
+            if (*(volatile uint32_t *)over) rescale(m0, m1, st != st_begin);
+        } else if (st != st_begin) __syncthreads();
         __builtin_amdgcn_sched_barrier(0);                             // (see exact_x3_kernel.hpp)
-        commit(std::false_type{});
+        commit(C::HALF && st & 1 ? -1.f : 1.f, std::false_type{});
         __builtin_amdgcn_sched_barrier(0);
         if (st + 1 < st_end) load(st + 1);
         __builtin_amdgcn_sched_barrier(0);
         __syncthreads();
-        x3_f16 small[2];
-        R::template steps<0, 0>(acc, small, a0, b0, kk);
+        x3_f16 part[2];
+        R::template steps<0, 0>(acc, part, a0, b0, kk, C::HALF && st & 1 ? -1.f : 1.f);
         __builtin_amdgcn_sched_barrier(0);
     }
     float worst = 0.f;
@@ -281,8 +349,10 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
             for (int v = 0; v < 16; ++v) worst = fmaf(acc[t][m][v], 0.f, worst);
     if (worst != worst) *flag = 1;
     __syncthreads();
-    float unscale = kX3Unscale;
+    bool scaled = C::HALF;
+    float unscale = C::HALF ? 1.f : kX3Unscale;
     if (*(volatile uint32_t *)flag) {                                  // (see exact_x3_kernel.hpp)
+        scaled = false;
         unscale = 1.f;
         int again = tid;
         asm volatile("" : "+v"(again));             // (decoded again, not kept in registers over the loop above)
@@ -291,7 +361,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
         load(st_begin);
         for (int st = st_begin; st < st_end; ++st) {
             __syncthreads();
-            commit(std::true_type{});
+            commit(1.f, std::true_type{});
             if (st + 1 < st_end) load(st + 1);
             __syncthreads();
             R::template plain_steps<0>(acc, a0, b0, kk);
@@ -299,7 +369,8 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     }
     // the result by half tiles of 32 output channels, gathered in LDS as rows of the tensor
     constexpr int Q = kPC * 9, PITCH = Q + 4;
-    float *const rows = (float *)(smem + 16);
+    float *const rows = (float *)As;
+    const int col_e = scaled ? expo[kPK + i] : 0;
     const int n = (g.C - c0 < kPC ? g.C - c0 : kPC) * 9, CRS = g.C * 9;
 #pragma unroll
     for (int m = 0; m < 2; ++m) {
@@ -307,8 +378,13 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
 #pragma unroll
         for (int t = 0; t < R::NT; ++t)
 #pragma unroll
-            for (int v = 0; v < 16; ++v)
-                rows[(8 * (v / 4) + 4 * kk + v % 4) * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = acc[t][m][v] * unscale;
+            for (int v = 0; v < 16; ++v) {
+                const int row = 8 * (v / 4) + 4 * kk + v % 4;
+                float z = acc[t][m][v];
+                if constexpr (C::HALF) z = __builtin_ldexpf(z, scaled ? -(col_e + expo[m * 32 + row]) : 0);
+                else z *= unscale;
+                rows[row * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = z;
+            }
         __syncthreads();
         const int kb = k0 + m * 32;
         if (n == Q && kb + 32 <= g.K && CRS % 4 == 0 && ((uintptr_t)out & 15) == 0) {
@@ -324,7 +400,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     }
 }
 
-template <int HW>
+template <int HW, int KIND>
 __global__ __launch_bounds__(kBlock, 2) void wgrad_exact_x3_planes(const X3Multi)
 {
     extern __shared__ __align__(16) char x3_smem[];
@@ -342,10 +418,10 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_exact_x3_planes(const X3Multi
     float *const out = mp->out[mp->first[gi] + prob] + (long)split * p.g.K * p.g.C * 9;
     // (the barriers inside are reached by all four wavefronts the same number of times, whatever their role)
     switch (__builtin_amdgcn_readfirstlane(((int)(threadIdx.x >> 6) + ((int)blockIdx.x >> 8)) & 3)) {
-        case 0: planes_body<HW, 0>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
-        case 1: planes_body<HW, 1>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
-        case 2: planes_body<HW, 2>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
-        default: planes_body<HW, 3>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        case 0: planes_body<HW, KIND, 0>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        case 1: planes_body<HW, KIND, 1>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        case 2: planes_body<HW, KIND, 2>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
+        default: planes_body<HW, KIND, 3>(p, X, dY, out, x3_smem, k0, c0, st_begin, st_end); break;
     }
 }
 
@@ -353,12 +429,13 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_exact_x3_planes(const X3Multi
 
 int x3_planes_lds(int hw)
 {
-    const int tail = 16 + 32 * (kPC * 9 + 4) * 4, stage = hw == 4 ? PlaneCfg<4>::kLds : PlaneCfg<2>::kLds;
+    const int tail = PlaneCfg<4, kX3Half>::kHead + 32 * (kPC * 9 + 4) * 4, stage = hw == 4 ? PlaneCfg<4, kX3Three>::kLds : PlaneCfg<2, kX3Three>::kLds;
     return stage > tail ? stage : tail;
 }
-int x3_launch_planes(int hw, const X3Multi &m, int blocks, size_t lds, hipStream_t st)
+int x3_launch_planes(int hw, bool half, const X3Multi &m, int blocks, size_t lds, hipStream_t st)
 {
-    return hw == 4 ? x3_launch(wgrad_exact_x3_planes<4>, m, blocks, lds, st) : x3_launch(wgrad_exact_x3_planes<2>, m, blocks, lds, st);
+    if (hw == 2) return x3_launch(wgrad_exact_x3_planes<2, kX3Three>, m, blocks, lds, st);
+    return half ? x3_launch(wgrad_exact_x3_planes<4, kX3Half>, m, blocks, lds, st) : x3_launch(wgrad_exact_x3_planes<4, kX3Three>, m, blocks, lds, st);
 }
 
 }  // namespace wgrad

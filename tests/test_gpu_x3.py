@@ -1,4 +1,4 @@
-"""The exact gradient of fp32 layers as three bf16 pieces on the bf16 matrix core, and of bf16 layers as one: the shapes
+"""The exact gradient of fp32 layers as three bf16 or two fp16 pieces on the matrix core, and of bf16 layers as one: the shapes
 where its tiles, its staging and its result tile have edges, the inputs that the pieces cannot represent, and its error
 against fp64."""
 import numpy as np
@@ -268,6 +268,39 @@ def test_infinities_in_a_run_of_layers():
         got, fine = got.cpu().numpy(), np.isfinite(want)
         assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
         assert normwise_err(got[fine], want[fine]) < TOL["fp32"]
+
+
+# Two fp16 pieces to a number: 32-wide tiles (whole rows, cut rows, ragged rows, (channel, filter row) columns) and 4x4 planes in
+# sums of twelve stages and more
+HALVES = [t for v, t, _, _ in PLANS if v in (0, 1, 2, 9, 10)] + [(97, 1000, 4, 4, 1040, 3, 3, 1, 1, 1, 1)]
+
+
+@pytest.mark.parametrize("t", HALVES)
+@pytest.mark.parametrize("how", ["growing", "shrinking", "channels", "hidden"])
+def test_scales_of_fp16_pieces(t, how):
+    """The scales of a workgroup's channels change along its sum, differ between the channels of both tensors, or are set by
+    one huge number that meets only zeros, beside which the others would have no bits left: those are summed as they are."""
+    d = mk(t)
+    X, dY = rand_inputs(d, 23)
+    n = np.arange(d.N)[:, None, None, None]
+    if how in ("growing", "shrinking"):
+        dY *= np.exp2((1 if how == "growing" else -1) * (7 * n % 41) * 1.0).astype(np.float32)
+        X *= np.exp2((1 if how == "growing" else -1) * (5 * n % 23) * 0.5).astype(np.float32)
+    elif how == "channels":
+        dY *= np.exp2(np.linspace(-60, 60, d.K)).astype(np.float32)[None, :, None, None]
+        X *= np.exp2(np.linspace(50, -50, d.C)).astype(np.float32)[None, :, None, None]
+    else:
+        X[0] = 0
+        dY[0, ::3] *= np.float32(1e25)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    if how == "channels":
+        want, got = want.reshape(d.K * d.C, -1), got.reshape(d.K * d.C, -1)
+        assert (np.abs(got - want).max(1) / np.abs(want).max(1)).max() < TOL["fp32"] / 5    # (of the nine taps of a pair)
+    else:
+        assert normwise_err(got, want) < TOL["fp32"] / 50
+        for k in range(d.K):
+            assert normwise_err(got[k], want[k]) < TOL["fp32"] / 25
 
 
 # ResNet-20's shapes in runs, on both sides of the lines for short layers: 0.14 GFLOP for two layers of a shape, 0.5 for one and
