@@ -144,11 +144,17 @@ def _torch():
 
 
 def _stream():
-    return ctypes.c_void_p(_torch().cuda.current_stream().cuda_stream)
+    """The current device's current stream.  (As a number from torch's runtime: the stream object of the public call takes 3.1 of
+    the 13 us that a program waits per single call of a small layer, this 0.2.)"""
+    torch = _torch()
+    raw = getattr(torch._C, "_cuda_getCurrentRawStream", None)
+    if raw is None:
+        return torch.cuda.current_stream().cuda_stream
+    return raw(torch.cuda.current_device())
 
 
 def _ptr(t):
-    return ctypes.c_void_p(t.data_ptr() if t is not None else None)
+    return t.data_ptr() if t is not None else None
 
 
 def _check_inputs(d, X, dY):
@@ -170,8 +176,8 @@ def alloc_workspace(nbytes, device="cuda"):
 
 def _ws_args(ws):
     if ws is None:
-        return ctypes.c_void_p(None), 0
-    return _ptr(ws), ws.numel() * ws.element_size()
+        return None, 0
+    return ws.data_ptr(), ws.numel() * ws.element_size()
 
 
 def _new_dW(d, like):
