@@ -1013,7 +1013,7 @@ __device__ __forceinline__ void fused_body(const ApproxBatch &ab, const Geometry
     const int j_end = CRS - j_base < kFusedJ * 64 ? CRS - j_base : kFusedJ * 64;
     for (int jl = tid; jl < j_end; jl += kBlock) {
         const int j = j_base + jl;
-        const float v = (red[0][jl] + red[1][jl] + red[2][jl] + red[3][jl]) * fp.scale;
+        const float v = (float)((double)red[0][jl] + red[1][jl] + red[2][jl] + red[3][jl]) * fp.scale;
         if (!NHWC || fp.dw_layout == WGRAD_DW_OHWI) {
             o[j] = v;
         } else {
@@ -1254,7 +1254,7 @@ __device__ __forceinline__ void fused3_body(const ApproxBatch &ab, const Geometr
     float *o = out + ((long)by * g.K + k) * CRS;
     const int j_end = CRS - j_base < kFusedJ * 64 ? CRS - j_base : kFusedJ * 64;
     for (int jl = tid; jl < j_end; jl += kBlock)
-        o[j_base + jl] = (red[0][jl] + red[1][jl] + red[2][jl] + red[3][jl]) * fp.scale;
+        o[j_base + jl] = (float)((double)red[0][jl] + red[1][jl] + red[2][jl] + red[3][jl]) * fp.scale;
 }
 
 template <int J3>
@@ -1764,6 +1764,17 @@ static int gather_chunk_n(const ApproxPlan &pl, int N, int nprob, bool shared)
     return chunks < (N + pl.gather_n - 1) / pl.gather_n ? (int)((N + chunks - 1) / chunks) : pl.gather_n;
 }
 
+// A layer alone whose images a workgroup of each output channel walks in less time than the reduction of its batch chunks
+// would take as a second launch (3 us and more): 16 images, four to a wavefront, and 32 where an image is quickly walked.  us
+// of a call, with chunks / in one launch: 16 -> 16 @ 32x32, N = 16 / 32 / 48: 10.0 / 9.9 / 9.7, 7.0 / 8.0 / 11.0; 64 -> 64 @
+// 32x32, N = 16 / 24: 9.9 / 10.2, 8.6 / 11.0; 64 -> 64 @ 8x8, N = 32 / 64: 9.9 / 9.9, 7.3 / 10.3; 30 -> 20 @ 27x30, N = 16: 12.9,
+// 13.6 (maps of other sizes over 256 positions, which are read in conditional pieces).
+static bool fused_in_one_launch(const Geometry &g)
+{
+    const int L = g.Ho * g.Wo;
+    return (L <= 256 || L == 1024) && (g.N <= 16 || (g.N <= 32 && (L <= 256 || g.crs() <= 192)));
+}
+
 int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, float scale,
                   int32_t *idx_out, float *sum_out, void *ws, hipStream_t st, CombineQueue *defer, FusedQueue *fq,
                   Bf16Queue *bq, GatherQueue *gq, SelectQueue *sq, RegsQueue *rgq, RowsQueue *rsq)
@@ -1799,6 +1810,7 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
             pl.chunks = (g.N + pl.chunk_n - 1) / pl.chunk_n;
         }
     }
+    if (pl.fused && !fq && b.n == 1 && fused_in_one_launch(g)) { pl.chunks = 1; pl.chunk_n = g.N; }
     // problem i owns the i-th slice (plan.ws_bytes each) of the workspace
     ApproxBatch ab{};
     for (int i = 0; i < kMaxBatch; ++i) {

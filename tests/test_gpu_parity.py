@@ -77,6 +77,22 @@ def test_approx_matches_oracle(t, dtype):
     assert normwise_err(got, want) <= TOL[dtype]
 
 
+# A layer alone in one launch, each output channel's workgroup walking the whole batch, or in batch chunks: both sides of the lines
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("N", [9, 16, 17, 32, 33])
+@pytest.mark.parametrize("t", [(16, 32, 32, 20), (64, 32, 32, 9), (40, 8, 8, 33), (72, 16, 16, 17), (5, 27, 30, 6)])
+def test_approx_of_short_batches(t, N, dtype):
+    import torch
+    C, H, W, K = t
+    d = B.desc(N, C, H, W, K, dtype=B.BF16 if dtype == "bf16" else B.F32)
+    X, dY = rand_inputs(d, 1700 + N, dtype)
+    idx, S = torch.empty((N, K), dtype=torch.int32, device="cuda"), torch.empty((N, K), dtype=torch.float32, device="cuda")
+    got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY), scale=1 / 128, idx_out=idx, sum_out=S).cpu().numpy()
+    want, _, _ = oracle.wgrad_approx(oracle_shape(d), X, dY, scale=1 / 128)
+    check_select(d, dY, idx.cpu().numpy(), S.cpu().numpy())
+    assert normwise_err(got, want) <= TOL[dtype] / (50 if dtype == "fp32" else 1)
+
+
 # 3x3, stride 1, padding 1 on planes of 4, 8, 16 and 32 columns with 32 or 64 output channels: the position orders of
 # the streaming kernel that leave out the taps which meet only padding (column-uniform; image-uniform on 4x4 planes
 # in tiles of eight images), and their neighbours that fall back to the row-major order (batches the tiles do not divide)
