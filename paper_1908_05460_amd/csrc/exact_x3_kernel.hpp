@@ -345,16 +345,18 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     // Loads go through a buffer descriptor from the tile's first row to the end of the tensor, 2^31 bytes at most; what is to be
     // zero is asked for beyond that, as the images past the last are anyway, and the hardware answers 0 without a memory
     // access: nothing is masked afterwards.
+    // (The whole offset is the lanes': the check subtracts a scalar one from the size, which wraps where it is the larger.  Wide
+    // padding puts a tile's first row behind the plane, and at the tensor's end nothing is left.)
     auto rsrc_of = [&](const char *base, long at, long elems) {
-        const long left = (elems - at) * ESZ;
+        const long left = elems > at ? (elems - at) * ESZ : 0;
         return __builtin_amdgcn_make_buffer_rsrc((void *)(base + at * ESZ), 0, left < (long)kDead ? (uint32_t)left : kDead, 0x00020000);
     };
-    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, int first, uint32_t *v) {      // whole pieces of a row
+    auto load4 = [&](__amdgpu_buffer_rsrc_t rs, uint32_t off, uint32_t *v) {      // whole pieces of a row
         if constexpr (BF) {
-            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, off, first, 0);
+            const auto q = __builtin_amdgcn_raw_buffer_load_b64(rs, off, 0, 0);
             v[0] = q[0]; v[1] = q[1];
         } else {
-            const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, off, first, 0);
+            const x3_u4 q = __builtin_amdgcn_raw_buffer_load_b128(rs, off, 0, 0);
 #pragma unroll
             for (int e = 0; e < 4; ++e) v[e] = q[e];
         }
@@ -368,7 +370,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 v[e] = __builtin_amdgcn_raw_buffer_load_b16(rs, live && (unsigned)(col + e) < (unsigned)width ? row + (uint32_t)(col + e) * 2u : kDead, 0, 0);
         } else {
             const int c = col < 0 ? 0 : (col > width - 4 ? width - 4 : col);
-            load4(rs, live && (unsigned)(col + 3) < (unsigned)(width + 3) ? row + (uint32_t)c * 4u : kDead, 0, v);
+            load4(rs, live && (unsigned)(col + 3) < (unsigned)(width + 3) ? row + (uint32_t)c * 4u : kDead, v);
         }
     };
     constexpr bool FIX = RAG && !BF, SHIFT = FIX && SW == 1;
@@ -383,7 +385,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     auto load_tile = [&](int wt) {
         const Tile t = tile_of(wt);
         const int h_left = g.Ho - t.h0;
-        const int wy = HALO ? t.wc0 * 8 * ESZ : 0, wx = wy * SW;        // the tile's first column (added to what is in range without it)
+        const uint32_t wy = HALO ? t.wc0 * 8 * ESZ : 0, wx = wy * SW;   // the tile's first column
         const auto yb = rsrc_of(dYp, ((long)t.n0 * g.K + k0) * L + (long)t.h0 * g.Wo, (long)g.N * g.K * L);
 #pragma unroll
         for (int u = 0; u < DI; ++u) {
@@ -394,10 +396,10 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 load4_ragged(yb, live, off0, col, g.Wo, dr[u]);
                 load4_ragged(yb, live, off0, col + 4, g.Wo, dr[u] + DR / 2);
             } else {
-                const uint32_t off = at_row(at) < h_left ? off0 : kDead;
+                const uint32_t off = at_row(at) < h_left ? off0 + wy : kDead;
                 const int left = g.Wo - t.wc0 * 8 - at_wc(at) * 8;
-                load4(yb, !HALO || left > 0 ? off : kDead, wy, dr[u]);
-                load4(yb, left > 4 ? off + 4 * ESZ : kDead, wy, dr[u] + DR / 2);
+                load4(yb, !HALO || left > 0 ? off : kDead, dr[u]);
+                load4(yb, left > 4 ? off + 4 * ESZ : kDead, dr[u] + DR / 2);
             }
         }
         if (HALO && p.halo) {
@@ -423,10 +425,10 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
 #pragma unroll
                 for (int q = 0; q < 2 * SW; ++q) load4_ragged(xb, in, off0, col + 4 * q, g.W, xr[u] + DR / 2 * q);
             } else {
-                const uint32_t off = in ? off0 : kDead;
+                const uint32_t off = in ? off0 + wx : kDead;
                 const int left = g.W - t.wc0 * 8 * SW - at_wc(at) * 8 * SW;
 #pragma unroll
-                for (int q = 0; q < 2 * SW; ++q) load4(xb, left > 4 * q ? off + 4 * q * ESZ : kDead, wx, xr[u] + DR / 2 * q);
+                for (int q = 0; q < 2 * SW; ++q) load4(xb, left > 4 * q ? off + 4 * q * ESZ : kDead, xr[u] + DR / 2 * q);
             }
         }
     };

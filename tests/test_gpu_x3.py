@@ -187,6 +187,16 @@ def test_scales_far_from_one(t, scale):
     assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), want) < TOL["fp32"] / 50
 
 
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("t", [(2, 17, 6, 40, 24, 3, 3, 1, 1, 9, 1), (2, 33, 6, 40, 70, 3, 3, 1, 1, 9, 1), (1, 33, 5, 300, 40, 3, 3, 1, 1, 8, 1),
+                               (2, 17, 6, 41, 24, 3, 3, 1, 1, 9, 1), (3, 17, 5, 40, 24, 3, 3, 2, 2, 9, 1)])
+def test_rows_of_padding_behind_the_last_plane(t, dtype):
+    """Padding so high that a tile's first input row lies behind the tensor's last: nothing is left to read there."""
+    d = mk(t, dtype)
+    X, dY = rand_inputs(d, 41, dtype)
+    assert normwise_err(run(d, to_gpu(X), to_gpu(dY)), oracle.wgrad_exact(oracle_shape(d), X, dY)) < TOL["fp32"] / 50
+
+
 def test_wide_range_of_magnitudes_within_a_tensor():
     """Elements of 2^-40 .. 2^40 side by side: every product keeps fp32's relative precision, so an output channel of
     small gradients is as exact as one of large ones."""
