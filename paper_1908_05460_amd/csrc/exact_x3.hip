@@ -258,6 +258,12 @@ static void x3_fill(const X3Group &it, X3Shape &s)
     s.h_tiles = pl.h_tiles; s.w_tiles = pl.w_tiles; s.n_groups = pl.n_groups;
     s.nch = pl.nch; s.ch = pl.ch; s.packed = pl.packed;
     s.halo = pl.halo; s.vlo = pl.vlo; s.xcol0 = pl.xcol0;
+    const int tiles = pl.w_tiles * pl.h_tiles * pl.n_groups;
+    s.tiles_each = tiles / pl.splits;
+    s.tiles_more = tiles % pl.splits;
+    s.d_prob = X3Div(s.per_prob);
+    s.d_ctiles = X3Div(pl.ctiles);
+    s.d_ktiles = X3Div(pl.ktiles);
     if (kVariant[pl.variant].plane) return;
     s.d_nch = FastDiv(pl.nch);
     s.d_twc = FastDiv(pl.twc);
@@ -267,6 +273,7 @@ static void x3_fill(const X3Group &it, X3Shape &s)
     s.d_htiles = FastDiv(pl.h_tiles);
     s.d_wtiles = FastDiv(pl.w_tiles);
     s.d_r = FastDiv(g.R);
+    s.d_rows = FastDiv(pl.nti * pl.ht);
 }
 
 static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)

@@ -53,6 +53,19 @@ typedef _Float16 x3_h2 __attribute__((ext_vector_type(2)));
 typedef float x3_f16 __attribute__((ext_vector_type(16)));
 typedef uint32_t x3_u4 __attribute__((ext_vector_type(4)));
 
+// Division of any 32-bit number by a run-time constant: the estimate is at most one low, and is put right.
+struct X3Div {
+    uint32_t d, m;
+    __host__ __device__ X3Div() : d(1), m(0xffffffffu) {}
+    __host__ explicit X3Div(uint32_t div) : d(div), m(div > 1 ? (uint32_t)((1ull << 32) / div) : 0xffffffffu) {}
+    __device__ __forceinline__ void divmod(uint32_t n, uint32_t &q, uint32_t &r) const
+    {
+        q = __umulhi(n, m);
+        r = n - q * d;
+        if (r >= d) { ++q; r -= d; }
+    }
+};
+
 struct X3Shape {
     Geometry g;
     int per_prob, ktiles, ctiles, splits;
@@ -63,7 +76,9 @@ struct X3Shape {
     int packed;                  // columns numbered c * R + r; otherwise column tile t is filter row t of SH channels
     int halo;                    // staged rows of dY carry their neighbours' words (tiles that are not whole rows)
     int vlo, xcol0;              // slot 0: its dY column, its X column in phase 0
-    FastDiv d_nch, d_twc, d_ht, d_xrow, d_iht, d_htiles, d_wtiles, d_r;
+    FastDiv d_nch, d_twc, d_ht, d_xrow, d_iht, d_htiles, d_wtiles, d_r, d_rows;      // (d_rows: output rows of a tile)
+    X3Div d_prob, d_ctiles, d_ktiles;
+    int tiles_each, tiles_more;  // tiles of a split; the first tiles_more splits have one more
 };
 
 constexpr int kX3MultiMax = 9;       // groups per launch
@@ -217,16 +232,13 @@ struct X3Config {
     static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG || (OWN && NTC > 1) ? 3 : 4);      // workgroups that share a CU
     static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
     static constexpr int kBuf = 16 + NP * kDy + 16 + NP * kX;            // of a tile (16 spare bytes before each: a word left of a chunk 0)
-    static constexpr int SR = SH == 32 ? 1 : S;                         // filter columns per round of the final exchange
-    static constexpr int kEx = NW * SR * SH * (SH + 4) * 4;             // bytes of a round (two alternate)
-    static constexpr int kOutP = NTC * SH * S + 4;                      // pitch of the result tile gathered in LDS (16-byte rows)
     static constexpr int kTop = HALF ? ((SH + CH) * 8 + 15) / 16 * 16 : 0;      // the channels' largest numbers and scales
     static constexpr int kScales = HALF ? (DI + XI + (HALO ? 1 : 0)) * kBlock * 4 : 0;      // the scales of every thread's staging items
     static constexpr bool PARK = HALF && HALO && SH == 32 && NTC > 1;     // the items themselves are kept in LDS too
     static constexpr int kItems = PARK ? (DI + XI + 1) * kBlock * 8 : 0;
     static constexpr int kFix = NCH * 4 + 16 + kTop;                    // the chunk table, flags, the channels' scales
     static constexpr int kHead = kFix + kScales + kItems;               // ... and what the loop alone needs
-    static constexpr int kTail = 2 * kEx + SH * kOutP * 4;
+    static constexpr int kTail = NW * NTC * S * SH * SH * 2;            // the final exchange: half of every wavefront's sums
     static constexpr int kLds = kHead + kBuf > kFix + kTail ? kHead + kBuf : kFix + kTail;
 };
 
@@ -265,18 +277,22 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     constexpr int dy_piece = T::kDy, x_piece = T::kX, kDyAt = 16, kXAt = 16 + NP * T::kDy + 16;
 
     const int logical_all = xcd_contiguous_id(bid, nblk);
-    const int prob = logical_all / p.per_prob;
-    const int logical = logical_all - prob * p.per_prob;
+    // (divisions by numbers that the host has prepared: the compiler's, of run-time numbers, are a hundred instructions each)
+    uint32_t prob, logical, rest, coltile, ktile, split;
+    p.d_prob.divmod((uint32_t)logical_all, prob, logical);
+    p.d_ctiles.divmod(logical, rest, coltile);
+    p.d_ktiles.divmod(rest, split, ktile);
     const char *const Xp = (const char *)Xt[prob], *const dYp = (const char *)dYt[prob];
-    const int coltile = logical % p.ctiles;
-    const int ktile = (logical / p.ctiles) % p.ktiles;
-    const int split = logical / (p.ctiles * p.ktiles);
-    const int k0 = ktile * SH;
-    const int c_first = p.packed ? coltile * NTC * SH / R : coltile * SH;
+    const int k0 = (int)ktile * SH;
+    int c_first = (int)coltile * SH;
+    if (p.packed) {
+        uint32_t q, r;
+        p.d_r.divmod(coltile * NTC * SH, q, r);
+        c_first = (int)q;
+    }
 
-    const int tiles_total = p.h_tiles * p.w_tiles * p.n_groups;
-    const int wt_begin = (int)((long)split * tiles_total / p.splits);
-    const int wt_end = (int)((long)(split + 1) * tiles_total / p.splits);
+    const int wt_begin = (int)split * p.tiles_each + min((int)split, p.tiles_more);
+    const int wt_end = wt_begin + p.tiles_each + ((int)split < p.tiles_more);
 
     // ---- staging items, decoded once: where in the tile (LDS chunk | row << 20 | chunk column << 28, all ones: none) and the
     //      byte offset of the row (of the chunk, where rows are whole) from the tile's first row ----
@@ -301,9 +317,12 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         }
     }
     if (HALO && p.halo && tid < SH * p.nti * p.ht * 2) {           // one of a row's two neighbour words per thread
-        const uint32_t side = tid & 1, k_l = (tid >> 1) / (p.nti * p.ht), row = (tid >> 1) % (p.nti * p.ht);
-        if (k0 + (int)k_l < g.K) h_at = (k_l * KP + row * (p.twc + 1) + (side ? p.twc + 1 : 0)) | row % p.ht << 20 | side << 28;
-        if (h_at != ~0u) h_off = ((row / p.ht * g.K + k_l) * L + row % p.ht * g.Wo) * ESZ;
+        uint32_t k_l, row, n_l, h_l;
+        const uint32_t side = tid & 1;
+        p.d_rows.divmod(tid >> 1, k_l, row);
+        p.d_ht.divmod(row, n_l, h_l);
+        if (k0 + (int)k_l < g.K) h_at = (k_l * KP + row * (p.twc + 1) + (side ? p.twc + 1 : 0)) | h_l << 20 | side << 28;
+        if (h_at != ~0u) h_off = ((n_l * g.K + k_l) * L + h_l * g.Wo) * ESZ;
     }
 #pragma unroll
     for (int u = 0; u < XI; ++u) {
@@ -598,7 +617,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     auto column = [&](int t, int col, int &c_l, int &r) {
         c_l = col; r = t;
         if (p.packed) {
-            const int q = coltile * NTC * SH + t * SH + col;
+            const int q = (int)coltile * NTC * SH + t * SH + col;
             uint32_t c, rr;
             p.d_r.divmod(q < g.C * R ? q : c_first * R, c, rr);
             c_l = (int)c - c_first; r = (int)rr;
@@ -636,7 +655,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         }
         row[DI + XI] = 0;
         if (HALO && p.halo) {
-            if (item(DI + XI, h_at, h_off).x != ~0u) row[DI + XI] = (tid >> 1) / (p.nti * p.ht);
+            if (item(DI + XI, h_at, h_off).x != ~0u) p.d_rows.divmod(tid >> 1, row[DI + XI], rem);
             note((int)row[DI + XI], x3_largest<2>(hr));
         }
         __syncthreads();
@@ -832,61 +851,80 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         __syncthreads();
     }
     float *const out = outt[prob] + (long)split * g.K * CRS;
-    // ---- the wavefronts' sums: through LDS, SR filter columns of a column tile at a time (four rows of a lane side by
-    //      side, two buffers, one barrier a round), gathered as rows of the result and written out in whole lines ----
-    constexpr int KTP = SH + 4, SR = T::SR, P = T::kOutP;
+    // ---- the wavefronts' sums: each pair of wavefronts two apart exchanges halves of its sums through LDS, then each
+    //      neighbouring pair quarters, so that every wavefront has a quarter of the rows, which it lays out as rows of the
+    //      result in LDS of its own and writes in whole lines: two barriers.  (With a round and a barrier for every filter tap a
+    //      32-wide workgroup took 4.9 us of its life, 4.3 now, of which the partial results' way to memory, all workgroups at
+    //      once, is most; 100 -> 100 @ 31x33, N = 20: 74.3 -> 72.2 us, bf16 64 -> 64 @ 56x56, N = 64: 41.4 -> 39.9.) ----
+    constexpr int NTS = NTC * S, Q = AV / 4, COLS = NTC * SH * S, QROWS = SH / 4;
+    typedef float quarter_t __attribute__((ext_vector_type(Q)));
     char *const tail = smem + T::kFix;
-    float *const rows = (float *)(tail + 2 * T::kEx);   // [SH][P]
+    constexpr int kQuarter = 64 * Q * 4, kSlot = NTS * 2 * kQuarter;                // bytes: of all lanes' quarter of a tile; of a wavefront's halves
+    static_assert(QROWS * COLS * 4 == NTS * kQuarter, "rows of a quarter fill half a slot");
+    const int hi = wq >> 1, lo = wq & 1;
+    auto quarter = [&](int ts, int b) {
+        quarter_t z;
 #pragma unroll
-    for (int ts = 0; ts < NTC * S; ts += SR) {
-        const int t = ts / S, s0 = ts % S;
-        float *const red = (float *)(tail + (ts / SR & 1) * T::kEx);      // [NW][SR][SH columns][KTP]
+        for (int e = 0; e < Q; ++e) z[e] = acc[ts / S][ts % S][b * Q + e];
+        if (KIND == kX3Three) z *= unscale;             // (before they are added up, which could leave fp32's range)
+        return z;
+    };
+    quarter_t mine[NTS][2];                             // quarters 2 hi and 2 hi + 1
+    char *const own = tail + wq * kSlot + lane * Q * 4, *const theirs = tail + (wq ^ 2) * kSlot + lane * Q * 4;
 #pragma unroll
-        for (int s = 0; s < SR; ++s)
+    for (int ts = 0; ts < NTS; ++ts)
 #pragma unroll
-            for (int v = 0; v < AV / 4; ++v) {
-                acc_t z = acc[ts / S][ts % S + s];
-                if (KIND == kX3Three) z *= unscale;     // (before they are added up, which could leave fp32's range)
-                *(float4_t *)(red + ((wq * SR + s) * SH + i) * KTP + (SH == 32 ? 8 * v + 4 * kk : 4 * kk)) =
-                    float4_t{z[4 * v], z[4 * v + 1], z[4 * v + 2], z[4 * v + 3]};
-            }
-        __syncthreads();
-        for (int o = tid; o < SH / 4 * SH * SR; o += NTHR) {
-            const int col = o % SH, rq = o / SH % (SH / 4), sl = o / (SH * SH / 4);
-            float4_t sum = *(const float4_t *)(red + (sl * SH + col) * KTP + 4 * rq);
-#pragma unroll
-            for (int w = 1; w < NW; ++w) sum += *(const float4_t *)(red + ((w * SR + sl) * SH + col) * KTP + 4 * rq);
-            // entry of an output channel's row: (c * R + r) * S + s
-            const int lc = (p.packed ? t * SH + col : col * R + t) * S + s0 + sl;
-            if (HALF && scaled) {
-                int c_l, r;
-                column(t, col, c_l, r);
-                const int e = expo[SH + c_l];
-#pragma unroll
-                for (int v = 0; v < 4; ++v) sum[v] = sign * __builtin_ldexpf(sum[v], -(e + expo[4 * rq + v]));
-            }
-#pragma unroll
-            for (int v = 0; v < 4; ++v) rows[(4 * rq + v) * P + lc] = sum[v];
+        for (int h = 0; h < 2; ++h) {
+            const quarter_t low = quarter(ts, h), high = quarter(ts, 2 + h);
+            *(quarter_t *)(own + (ts * 2 + h) * kQuarter) = hi ? low : high;
+            mine[ts][h] = hi ? high : low;
         }
+    __syncthreads();
+#pragma unroll
+    for (int ts = 0; ts < NTS; ++ts)
+#pragma unroll
+        for (int h = 0; h < 2; ++h) mine[ts][h] += *(const quarter_t *)(theirs + (ts * 2 + h) * kQuarter);
+    // (into the slot that nobody but this wavefront reads)
+#pragma unroll
+    for (int ts = 0; ts < NTS; ++ts) {
+        *(quarter_t *)(theirs + ts * kQuarter) = lo ? mine[ts][0] : mine[ts][1];
+        if (lo) mine[ts][0] = mine[ts][1];
     }
     __syncthreads();
-    {
-        const int j0 = (p.packed ? coltile * NTC * SH : c_first * R) * S;
-        const int cols = p.packed ? NTC * SH * S : SH * R * S, n = CRS - j0 < cols ? CRS - j0 : cols;
-        if (n == NTC * SH * S && k0 + SH <= g.K && CRS % 4 == 0 && j0 % 4 == 0 && ((uintptr_t)out & 15) == 0) {
-            constexpr int Q = NTC * SH * S / 4, IT = (SH * Q + NTHR - 1) / NTHR;
-            float *const dst = out + (long)k0 * CRS + j0;
+    float *const rows = (float *)(tail + (wq ^ 2) * kSlot + kSlot / 2);             // [QROWS][COLS]
+    const char *const last = tail + (wq ^ 3) * kSlot + lane * Q * 4;                // what the neighbour put into its slot
+    const int part = 2 * hi + lo;
+    auto row_of = [&](int r) { return SH == 32 ? 8 * part + r : 4 * r + part; };    // row of the quarter -> row of the tile
 #pragma unroll
-            for (int u = 0; u < IT; ++u) {
-                const int e = tid + u * NTHR, row = e / Q, x = e % Q * 4;
-                if (SH * Q % NTHR == 0 || e < SH * Q) *(float4_t *)(dst + (long)row * CRS + x) = *(const float4_t *)(rows + row * P + x);
-            }
-        } else {
-            for (int row = wq; row < SH && k0 + row < g.K; row += NW) {
-                float *const dst = out + (long)(k0 + row) * CRS + j0;
-                for (int x = lane; x < n; x += 64) dst[x] = rows[row * P + x];
-            }
+    for (int ts = 0; ts < NTS; ++ts) {
+        const int t = ts / S, s = ts % S;
+        quarter_t z = mine[ts][0] + *(const quarter_t *)(last + ts * kQuarter);
+        if (HALF && scaled) {
+            int c_l, r;
+            column(t, i, c_l, r);
+            const int e = expo[SH + c_l];
+#pragma unroll
+            for (int v = 0; v < Q; ++v) z[v] = sign * __builtin_ldexpf(z[v], -(e + expo[row_of(Q * kk + v)]));
         }
+        // entry of an output channel's row: (c * R + r) * S + s
+        const int lc = (p.packed ? t * SH + i : i * R + t) * S + s;
+#pragma unroll
+        for (int v = 0; v < Q; ++v) rows[(Q * kk + v) * COLS + lc] = z[v];
+    }
+    const int j0 = (p.packed ? (int)coltile * NTC * SH : c_first * R) * S;
+    const int cols = p.packed ? COLS : SH * R * S, n = CRS - j0 < cols ? CRS - j0 : cols;
+    if (n == COLS && k0 + SH <= g.K && CRS % 4 == 0 && j0 % 4 == 0 && ((uintptr_t)out & 15) == 0) {
+        constexpr int P = COLS / 4, IT = (QROWS * P + 63) / 64;
+#pragma unroll
+        for (int u = 0; u < IT; ++u) {
+            const int e = lane + u * 64, row = e / P, x = e % P * 4;
+            if (QROWS * P % 64 == 0 || e < QROWS * P) *(float4_t *)(out + (long)(k0 + row_of(row)) * CRS + j0 + x) = *(const float4_t *)(rows + row * COLS + x);
+        }
+    } else {
+#pragma unroll 1
+        for (int row = 0; row < QROWS; ++row)
+            if (k0 + row_of(row) < g.K)
+                for (int x = lane; x < n; x += 64) out[(long)(k0 + row_of(row)) * CRS + j0 + x] = rows[row * COLS + x];
     }
 }
 

@@ -410,10 +410,12 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_exact_x3_planes(const X3Multi
     const int bid = (int)blockIdx.x - mp->begin[gi], nblk = mp->count[gi];
     if (bid >= nblk) return;
     const X3Shape &p = mp->s[gi];
-    const int all = xcd_contiguous_id(bid, nblk), prob = all / p.per_prob, logical = all - prob * p.per_prob;
-    const int coltile = logical % p.ctiles, ktile = logical / p.ctiles % p.ktiles, split = logical / (p.ctiles * p.ktiles);
-    const int st_begin = (int)((long)split * p.n_groups / p.splits), st_end = (int)((long)(split + 1) * p.n_groups / p.splits);
-    const int k0 = ktile * kPK, c0 = coltile * kPC;
+    uint32_t prob, logical, rest, coltile, ktile, split;
+    p.d_prob.divmod((uint32_t)xcd_contiguous_id(bid, nblk), prob, logical);
+    p.d_ctiles.divmod(logical, rest, coltile);
+    p.d_ktiles.divmod(rest, split, ktile);
+    const int st_begin = (int)split * p.tiles_each + min((int)split, p.tiles_more), st_end = st_begin + p.tiles_each + ((int)split < p.tiles_more);
+    const int k0 = (int)ktile * kPK, c0 = (int)coltile * kPC;
     const float *const X = (const float *)mp->X[mp->first[gi] + prob], *const dY = (const float *)mp->dY[mp->first[gi] + prob];
     float *const out = mp->out[mp->first[gi] + prob] + (long)split * p.g.K * p.g.C * 9;
     // (the barriers inside are reached by all four wavefronts the same number of times, whatever their role)
