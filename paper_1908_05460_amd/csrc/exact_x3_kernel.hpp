@@ -229,7 +229,7 @@ struct X3Config {
     static constexpr int NP = BF ? 1 : (HALF ? 2 : 3);                  // pieces of a number
     static constexpr bool OWN = KIND == kX3Three && SH == 16 && S <= 3;   // the smaller products have sums of their own
     static constexpr int DR = BF && !RAG ? 4 : 8;                       // registers of a chunk on its way to LDS
-    static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG || (OWN && NTC > 1) ? 3 : 4);      // workgroups that share a CU
+    static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG || SH == 32 || (OWN && NTC > 1) ? 3 : 4);      // workgroups that share a CU
     static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
     static constexpr int kBuf = 16 + NP * kDy + 16 + NP * kX;            // of a tile (16 spare bytes before each: a word left of a chunk 0)
     static constexpr int kTop = HALF ? ((SH + CH) * 8 + 15) / 16 * 16 : 0;      // the channels' largest numbers and scales
