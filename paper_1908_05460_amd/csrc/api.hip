@@ -346,7 +346,14 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
         left += !run && p.ex.x3 != 2 && !(p.ex.x3 == 3 && members > 1);
     });
     const bool short_runs = nexact > 1 && (run_gflop >= 2.0 || left == 0 || (longer > 0 && wide_runs > 0));
-    each(WGRAD_EXACT, [&](LayerPlan &p, int members) { p.ex.x3_run = p.ex.x3_run && members > 1 && short_runs; });
+    // Strided layers and first ones of a few channels share the launch of 16-wide tiles where there is one (exact_x3_mix.hip; alone
+    // they would be a launch more beside those, or keep to the fp32 multi-shape one).
+    bool host = false;
+    each(WGRAD_EXACT, [&](LayerPlan &p, int members) {
+        p.ex.x3_run = p.ex.x3_run && members > 1 && short_runs;
+        host = host || ((p.ex.x3_run || p.ex.x3 == 2) && !p.g.bf16 && x3_mixes(p.ex.x3p));
+    });
+    each(WGRAD_EXACT, [&](LayerPlan &p, int) { p.ex.x3_join = p.ex.x3_join && host; });
     // Approximated bf16 layers row after row: from 1280 blocks on, from 512 where they are of four shapes and more or the exact layers do
     // not share the row-window kernel's launch with them, or where they are two and more layers of one shape, wider than 4x4, and
     // all that the run has for the bf16 matrix core -- or all but exact layers, with 80 blocks a tile; not for one layer alone, which
@@ -426,7 +433,7 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
         const ExactPlan &ex = plan[i].ex;
         int members = 0;
         for (int j = i; j < nlayers; ++j) members += group[j] == i;
-        if (ex.plane2 || ex.x3 == 2 || ex.x3_run) return 0.0;
+        if (ex.plane2 || ex.x3 == 2 || ex.x3_run || ex.x3_join) return 0.0;
         const Geometry &g = plan[i].g;
         double w = 2.0 * g.N * g.K * g.Ho * g.Wo * (double)g.crs();
         // layers that are not bound by the matrix core take longer than their FLOPs say: a handful of

@@ -105,6 +105,7 @@ struct ExactPlan {
     int rows_chunks;                 // ... the most batch chunks
     int plane2;                      // 2x2 planes, fp32: the plain matrix product over (position, element) pairs
     int x3_run;                      // x3's form also in a run with enough such work, for two and more layers of a shape
+    int x3_join;                     // ... and in a run in which others do, whose launch it then shares
     size_t lds_bytes, ws_bytes;
     bool ok;
 };
@@ -123,6 +124,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &pl);
 bool x3_needs_alignment(const X3Plan &pl);
 bool x3_ragged(const X3Plan &pl);
 int x3_tile_rows(const X3Plan &pl);
+bool x3_mixes(const X3Plan &pl);                     // whether its launch can carry groups of other variants
 bool x3_fit(X3Plan &pl, long room);
 struct X3Queue;
 X3Queue *x3_queue_new();

@@ -658,13 +658,23 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
         run = g.sw == 1 && g.N >= 16 && gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 140) * 1e-3;
     }
     X3Plan x3{};
-    if (!tune_int("WGRAD_X3", 1) || (!use && !run) || !plan_exact_x3(g, x3) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) return size_exact(g, pl);
+    if (!tune_int("WGRAD_X3", 1)) return size_exact(g, pl);
+    // strided and first layers of a few channels, beside others in a run
+    const bool join = !g.bf16 && pl.stream && use != 2 && g.N >= 16 && (g.sw > 1 || g.C < 16);
+    if ((!use && !run && !join) || !plan_exact_x3(g, x3)) return size_exact(g, pl);
+    if ((!use && !run) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) {
+        pl = size_exact(g, pl);
+        pl.x3_join = join && x3_mixes(x3) && x3_fit(x3, (long)(pl.ws_bytes / ((size_t)g.dw_elems() * 4)));
+        if (pl.x3_join) pl.x3p = x3;
+        return pl;
+    }
     // (the other form's split and workspace only where a call may come back to it)
     if (use != 2 || x3_needs_alignment(x3)) pl = size_exact(g, pl);
     // (in a run only: the workspace stays the other form's)
     if (!use && !x3_fit(x3, (long)(pl.ws_bytes / ((size_t)g.dw_elems() * 4)))) return pl;
     pl.x3 = use;
     pl.x3_run = run;
+    pl.x3_join = join && x3_mixes(x3);
     pl.x3p = x3;
     const size_t need = use && x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
     if (need > pl.ws_bytes) pl.ws_bytes = need;
@@ -745,7 +755,7 @@ int launch_exact(const Geometry &g, const ExactPlan &plan, const Batch &b, void 
     if (plan.rows && rq && batch_aligned(g, b, 8, 8))
         return launch_rows(g, b, plan.rows_chunks, ws, align_up(plan.ws_bytes), st, defer, rq);
     if (planes_bf16_takes(g) && batch_aligned(g, b, 8, 8)) return launch_exact_bf16_planes(g, b, st);   // bf16, 2x2 and 4x4 planes: no split, no partial sums
-    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq && b.n > 1) || (plan.x3_run && xq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
+    if ((plan.x3 == 2 || (plan.x3 == 1 && !mq && !bq) || (plan.x3 == 3 && mq && b.n > 1) || ((plan.x3_run || plan.x3_join) && xq)) && (!x3_needs_alignment(plan.x3p) || batch_aligned(g, b, 2, 2))) return launch_exact_x3(g, plan.x3p, b, ws, align_up(plan.ws_bytes), st, defer, xq);
     if (plan.plane2 && batch_aligned(g, b, 4, 4)) return launch_exact_plane2(g, b, st, mq);   // no split, no partial sums
     if ((plan.stream || plan.mm16) && batch_aligned(g, b, plan.xv, plan.mm16 ? 8 : 4)) {
         // one launch for the whole batch; problem i owns the i-th slice of the workspace.  The

@@ -99,10 +99,10 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
 
 // us that a workgroup spends on a tile when `share` of them are on its CU: bounded by the matrix instructions of all, or
 // by its own staging and matrix instructions one after the other
-static double x3_tile_us(const X3Variant &v, int share)
+static double x3_tile_us(const X3Variant &v, int share, bool half = false)
 {
     if (v.plane) return 1.1 * (v.plane == 4 ? std::max(share * 2.8, 4.2) : std::max(share * 0.85, 1.8));
-    const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.kind == kX3Bf16 ? 1 : 6) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
+    const double mfma = (double)v.nch / (64 / v.sh) / 4 * (v.kind == kX3Bf16 ? 1 : (half ? 3 : 6)) * v.ntc * v.s * (v.sh == 32 ? 32 : 16) / 1900.0;
     const double stage = 0.3 + (v.rag && v.sw > 1 ? 0.6 : (v.kind == kX3Bf16 ? 0.1 : 0.33)) * (v.di + v.xi * v.sw);
     return 1.1 * std::max(std::max(mfma * share, 0.3 * stage * share), mfma + stage);
 }
@@ -118,6 +118,9 @@ static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : (v.kind ==
 // 1.5e-7 off whatever the sum's length, three bf16 pieces 0.65e-7 after 2 stages, 1.0e-7 after 8 and 1.9e-7 after 16 (VGG-19's run, N =
 // 128); shorter sums would gain a fifth of their time (N = 128 alone, 4 stages: 50 us, 42).
 constexpr long kX3HalfStages = 12;
+// a launch of several variants, bf16 pieces: 24 tiles (ResNet-20, N = 90 to 128, sums of 18 / 24 / 28 tiles, error over that of the
+// launches before: 64 -> 64 @ 8x8 0.86 / 0.97 / 1.17, the others less)
+constexpr long kX3MixMost = 24;
 constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
 
 // How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of
@@ -188,6 +191,7 @@ bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].kind == 
 // whether the variant stages rows of any width and cut rows; output channels of its tile
 bool x3_ragged(const X3Plan &pl) { return kVariant[pl.variant].rag; }
 int x3_tile_rows(const X3Plan &pl) { return kVariant[pl.variant].sh; }
+bool x3_mixes(const X3Plan &pl) { return x3_mix_body(pl.variant) >= 0; }
 
 // at most `room` partial results; false if a workgroup would then add up more tiles than x3_most_tiles
 bool x3_fit(X3Plan &pl, long room)
@@ -240,6 +244,7 @@ struct X3Group {
     Batch b;
     float *ws;                   // the group's slice of the workspace: slice_stride floats per problem
     long slice_stride;
+    bool half;                   // two fp16 pieces where a launch of several variants could take three bf16 ones
 };
 struct X3Queue {
     std::vector<X3Group> item;
@@ -257,6 +262,8 @@ static void x3_fill(const X3Group &it, X3Shape &s)
     s.nti = pl.nti; s.ht = pl.ht; s.iht = pl.iht; s.twc = pl.twc;
     s.h_tiles = pl.h_tiles; s.w_tiles = pl.w_tiles; s.n_groups = pl.n_groups;
     s.nch = pl.nch; s.ch = pl.ch; s.packed = pl.packed;
+    s.body = x3_mix_body(pl.variant);
+    if (it.half) s.body = 3;
     s.halo = pl.halo; s.vlo = pl.vlo; s.xcol0 = pl.xcol0;
     const int tiles = pl.w_tiles * pl.h_tiles * pl.n_groups;
     s.tiles_each = tiles / pl.splits;
@@ -281,6 +288,7 @@ static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
     X3Multi m{};
     m.n = n;
     size_t lds = 0;
+    bool mixed = false;
     int blocks = 0, tensors = 0;
     for (int i = 0; i < n; ++i) {
         const X3Group &q = *it[i];
@@ -295,8 +303,10 @@ static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
         }
         blocks += (m.count[i] + 7) / 8 * 8;
         lds = std::max(lds, (size_t)q.pl.lds);
+        mixed = mixed || q.pl.variant != it[0]->pl.variant;
     }
     m.begin[n] = blocks;
+    if (mixed) return x3_launch_mix(m, blocks, st);
     if (const int hw = kVariant[it[0]->pl.variant].plane) {
         bool half = hw == 4;
         for (int i = 0; i < n; ++i) half = half && it[i]->pl.n_groups >= kX3HalfStages * it[i]->pl.splits;
@@ -317,26 +327,43 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
 {
     int rc = WGRAD_OK;
     auto tiles_of = [](const X3Group &it) { return (long)it.pl.w_tiles * it.pl.h_tiles * it.pl.n_groups; };
-    std::stable_sort(q.item.begin(), q.item.end(), [](const X3Group &a, const X3Group &b) { return a.pl.variant < b.pl.variant; });
+    auto key = [](const X3Group &g) { return x3_mixes(g.pl) ? -1 : g.pl.variant; };      // (those that share a launch side by side)
+    std::stable_sort(q.item.begin(), q.item.end(), [&](const X3Group &a, const X3Group &b) { return key(a) < key(b) || (key(a) == key(b) && a.pl.variant < b.pl.variant); });
     for (size_t first = 0; first < q.item.size() && rc == WGRAD_OK;) {
         X3Group *sel[kX3MultiMax];
         int n = 0, tensors = 0;
-        const X3Variant &v = kVariant[q.item[first].pl.variant];
+        // (one variant, or the 16-wide ones that a launch can mix)
+        const int variant = q.item[first].pl.variant;
         while (first < q.item.size() && n < kX3MultiMax && tensors + q.item[first].b.n <= kX3Tensors &&
-               &kVariant[q.item[first].pl.variant] == &v) {
+               (q.item[first].pl.variant == variant || (x3_mix_body(variant) >= 0 && x3_mix_body(q.item[first].pl.variant) >= 0))) {
             tensors += q.item[first].b.n;
             sel[n++] = &q.item[first++];
         }
-        const int slots = x3_resident(v);
-        const double t = x3_tile_us(v);
+        const X3Variant &v = kVariant[variant];
+        bool mixed = false;
+        for (int i = 1; i < n; ++i) mixed = mixed || sel[i]->pl.variant != variant;
+        const int slots = mixed ? 3 * kNumCU : x3_resident(v);
+        double t[kX3MultiMax];
+        for (int i = 0; i < n; ++i) t[i] = x3_tile_us(kVariant[sel[i]->pl.variant], slots / kNumCU);
+        if (mixed) {
+            // One round of workgroups would add up more tiles than three bf16 pieces may (kX3MixMost): fp16 pieces, which err no
+            // more at that length, on rows of more than one chunk (ResNet-20 exact, N = 128: 89 us in bf16 pieces, two rounds, 80
+            // so; on 8x8 planes they err 1.15 times as much as bf16 pieces in the launches before)
+            double rounds = 0;
+            for (int i = 0; i < n; ++i) rounds += (double)tiles_of(*sel[i]) * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n * t[i] / t[0];
+            for (int i = 0; i < n; ++i) {
+                sel[i]->half = 1.08 * rounds > (double)slots * kX3MixMost && x3_mix_body(sel[i]->pl.variant) == 0 && sel[i]->g.Wo > 8;
+                if (sel[i]->half) t[i] = x3_tile_us(kVariant[sel[i]->pl.variant], slots / kNumCU, true);
+            }
+        }
         // Candidates: workgroups of `share` of the launch's even share of work, the first of a pair where the result is
         // large (its partial results are what splitting costs), the second elsewhere, to fill what those leave free.  (Shares
         // over 1 leave slots empty: 4x4 layers of 512 channels, whose partial sums weigh most, VGG-19 at N = 64 285 -> 269 us.)
-        static const double kShare[][2] = {{1.4, 1.4}, {1.0, 1.0}, {1.0, 0.5}, {1.0, 0.33}, {0.67, 0.67}, {0.67, 0.33}, {0.5, 0.5}, {0.5, 0.25}, {0.33, 0.33}, {0.25, 0.25}};
+        static const double kShare[][2] = {{1.4, 1.4}, {1.0, 1.0}, {1.0, 0.5}, {1.0, 0.33}, {0.67, 0.67}, {0.67, 0.33}, {0.5, 0.5}, {0.5, 0.25}, {0.33, 0.33}, {0.25, 0.25}, {1.07, 1.07}, {1.15, 1.15}, {1.25, 1.25}, {0.54, 0.54}, {0.58, 0.58}, {0.62, 0.62}, {0.36, 0.36}, {0.4, 0.4}};
         long largest = 0;
         double total = 0;                                // workgroup-tiles
         for (int i = 0; i < n; ++i) {
-            total += (double)tiles_of(*sel[i]) * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n;
+            total += (double)tiles_of(*sel[i]) * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n * t[i] / t[0];
             largest = std::max(largest, sel[i]->g.dw_elems());
         }
         double best_cost = 1e30, life[kX3MultiMax], best_life[kX3MultiMax];
@@ -346,13 +373,14 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
             long count[kX3MultiMax];
             for (int i = 0; i < n; ++i) {
                 const long tiles = tiles_of(*sel[i]);
-                const double target = std::max(1.0, total / slots * share[2 * sel[i]->g.dw_elems() < largest]);
+                const double target = std::max(1.0, total / slots * share[2 * sel[i]->g.dw_elems() < largest] * t[0] / t[i]);
                 long s = (long)(tiles / target + 0.95);
-                s = std::max(s, (tiles + x3_most_tiles(v) - 1) / x3_most_tiles(v));
+                const long longest = mixed && !sel[i]->half ? kX3MixMost : x3_most_tiles(kVariant[sel[i]->pl.variant]);
+                s = std::max(s, (tiles + longest - 1) / longest);
                 s = std::max(1l, std::min(s, (long)std::min<long>(sel[i]->pl.splits, tiles)));
                 now[i] = (int)s;
                 partial += x3_partial_us(sel[i]->g, s, sel[i]->b.n);
-                life[i] = kX3Fixed + (double)((tiles + s - 1) / s) * t;
+                life[i] = kX3Fixed + (double)((tiles + s - 1) / s) * t[i];
                 int j = i;
                 for (; j > 0 && sorted[j - 1] < life[i]; --j) { sorted[j] = sorted[j - 1]; count[j] = count[j - 1]; }
                 sorted[j] = life[i];
@@ -385,7 +413,7 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
 int launch_exact_x3(const Geometry &g, const X3Plan &plan, const Batch &b, void *ws, size_t slice_bytes, hipStream_t st,
                     CombineQueue *defer, X3Queue *q)
 {
-    X3Group it{g, plan, b, (float *)ws, (long)(slice_bytes / 4)};
+    X3Group it{g, plan, b, (float *)ws, (long)(slice_bytes / 4), false};
     if (q) {
         q->item.push_back(it);
         return WGRAD_OK;

@@ -15,7 +15,8 @@
 // What the pieces leave out and what the core rounds inside of products of 22 bits is 1e-7 of a result, whatever the length
 // of its sums, so this is the form of long sums: of the 32-wide tiles (VGG-19's run, N = 128: 4.5e-7 off with bf16 pieces,
 // 3.5e-7; N = 16 to 40: 2.5 -> 2.1e-7) and of 4x4 planes (exact_x3_planes.hip), where it is no further from 64 bits; 16-wide
-// tiles, whose sums are short or kept apart (64 -> 64 @ 8x8, N = 50: 0.86e-7, fp16 pieces 1.1e-7), keep bf16 pieces.
+// tiles, whose sums are short or kept apart (64 -> 64 @ 8x8, N = 50: 0.86e-7, fp16 pieces 1.1e-7), keep bf16 pieces but for a
+// run's strided and longest ones (exact_x3_mix.hip), with all four products.
 // 64 -> 64 @ 32x32 / 256 -> 256 @ 8x8, N = 128: 62 / 59 us with bf16 pieces, 48 / 45; VGG-19's run 490 -> 342 us.
 //
 // What holds an infinity or a NaN, or numbers too large for the scale of bf16 pieces (beyond 2^111, sums beyond 2^96) or too
@@ -71,6 +72,7 @@ struct X3Shape {
     int per_prob, ktiles, ctiles, splits;
     int nti, ht, iht, twc;       // tile: images, output rows, input rows, chunks per row
     int h_tiles, w_tiles, n_groups;
+    int body;                    // of a launch that mixes variants (exact_x3_mix.hip)
     int nch;                     // live chunks of a tile (the table points the rest at a chunk of zeros)
     int ch;                      // channels staged per column tile
     int packed;                  // columns numbered c * R + r; otherwise column tile t is filter row t of SH channels
@@ -228,6 +230,7 @@ struct X3Config {
     static constexpr bool BF = KIND == kX3Bf16, HALF = KIND == kX3Half, RAG = RAG_, HALO = HALO_;
     static constexpr int NP = BF ? 1 : (HALF ? 2 : 3);                  // pieces of a number
     static constexpr bool OWN = KIND == kX3Three && SH == 16 && S <= 3;   // the smaller products have sums of their own
+    static constexpr bool STEP = HALF && SH == 16;                        // a step's products have
     static constexpr int DR = BF && !RAG ? 4 : 8;                       // registers of a chunk on its way to LDS
     static constexpr int kOcc = (SH == 32 && NTC > 1) || SW > 1 || S > 3 ? 2 : (RAG || SH == 32 || (OWN && NTC > 1) ? 3 : 4);      // workgroups that share a CU
     static constexpr int kDy = SH * KP * 16, kX = CH * CP * 16;         // bytes of one piece
@@ -712,20 +715,51 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             const uint32_t e = tab[(wq * NST + st) * CPS + kk];
             const char *const ap = a_row + (e & 0xfff);
             const char *const bp = Xs + ((e >> 12) & 0x3fff);
-            // the products of dY's smallest piece first; a piece's shifted operands serve every column tile, X's pieces
-            // are read again for each (reads that the LDS has to spare, against 24 registers that the loop has not)
-#pragma unroll
-            for (int qa = NP - 1; qa >= 0; --qa) {
+            auto shifted = [&](int qa, x3_u4 (&a)[S]) {
                 const x3_u4 w = *(const x3_u4 *)(ap + qa * dy_piece);
                 uint32_t lw = *(const uint32_t *)(ap + qa * dy_piece - 4), rw = *(const uint32_t *)(ap + qa * dy_piece + 16);
                 if (e & (1u << 30)) lw = 0;
                 if (e & (1u << 31)) rw = 0;
-                x3_u4 a[S];
                 a[0] = x3_shifted<x3_shift(0, S, SW)>(lw, w, rw);
                 a[1] = x3_shifted<x3_shift(1, S, SW)>(lw, w, rw);
                 a[2] = x3_shifted<x3_shift(2, S, SW)>(lw, w, rw);
                 if constexpr (S > 3) a[3] = x3_shifted<x3_shift(3, S, SW)>(lw, w, rw);
                 if constexpr (S > 4) a[4] = x3_shifted<x3_shift(4, S, SW)>(lw, w, rw);
+            };
+            if constexpr (T::STEP) {
+                // 16-wide fp16 pieces: a step's products are summed by themselves, and that is added to the whole, which is then
+                // rounded once a step, to nearest, and not three times, downwards
+                x3_u4 a[2][S];
+                shifted(0, a[0]);
+                shifted(1, a[1]);
+#pragma unroll
+                for (int t = 0; t < NTC; ++t)
+#pragma unroll
+                    for (int f = 0; f < SW; ++f) {
+                        const char *const q0 = bp + coloff[t] + f * p.twc * 16;
+                        const x3_u4 h = *(const x3_u4 *)q0, l = *(const x3_u4 *)(q0 + x_piece);
+                        acc_t z[S];
+#pragma unroll
+                        for (int s = 0; s < S; ++s)
+#pragma unroll
+                            for (int v = 0; v < AV; ++v) z[s][v] = 0.f;
+#pragma unroll
+                        for (int q = 0; q < 4; ++q)     // (all four products: 32 -> 32 @ 16x16 in ResNet-20's run, N = 128, 1.36e-7 off, without the smallest 1.43e-7)
+#pragma unroll
+                            for (int s = 0; s < S; ++s)
+                                if (x3_phase(s, S, SW) == f) x3_mfma<KIND>(z[s], a[q < 2][s], q % 2 == 0 ? l : h);
+#pragma unroll
+                        for (int s = 0; s < S; ++s)
+                            if (x3_phase(s, S, SW) == f) acc[t][s] += z[s];
+                    }
+                continue;
+            }
+            // the products of dY's smallest piece first; a piece's shifted operands serve every column tile, X's pieces
+            // are read again for each (reads that the LDS has to spare, against 24 registers that the loop has not)
+#pragma unroll
+            for (int qa = NP - 1; qa >= 0; --qa) {
+                x3_u4 a[S];
+                shifted(qa, a);
 #pragma unroll
                 for (int t = 0; t < NTC; ++t) {
 #pragma unroll
@@ -972,6 +1006,10 @@ inline int x3_launch(void (*kernel)(const X3Multi), const X3Multi &m, int blocks
 // 2x2 and 4x4 planes, position by position (exact_x3_planes.hip)
 int x3_planes_lds(int hw);
 int x3_launch_planes(int hw, bool half, const X3Multi &m, int blocks, size_t lds, hipStream_t st);
+// 16-wide fp32 variants of several kinds in one launch (exact_x3_mix.hip): the body of a variant, or -1; a launch's LDS
+int x3_mix_body(int variant);
+int x3_mix_lds();
+int x3_launch_mix(const X3Multi &m, int blocks, hipStream_t st);
 int x3_launch_bf16(int variant, const X3Multi &m, int blocks, size_t lds, hipStream_t st);      // instantiated in a file of their own
 
 }  // namespace wgrad

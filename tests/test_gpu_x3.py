@@ -313,6 +313,33 @@ def test_scales_of_fp16_pieces(t, how):
             assert normwise_err(got[k], want[k]) < TOL["fp32"] / 25
 
 
+# ResNet-20's layers with a stride and its first one beside the others in one launch; from N = 118 on with fp16 pieces in the long sums
+@pytest.mark.parametrize("bad", [False, True])
+@pytest.mark.parametrize("N", [31, 128])
+def test_layers_of_several_kinds_in_one_launch(N, bad):
+    shapes = [(N, 3, 32, 32, 16, 3, 3, 1, 1, 1, 1)] + [(N, 16, 32, 32, 16, 3, 3, 1, 1, 1, 1)] * 7 + [(N, 16, 32, 32, 32, 3, 3, 2, 2, 1, 1)] \
+        + [(N, 32, 16, 16, 32, 3, 3, 1, 1, 1, 1)] * 6 + [(N, 32, 16, 16, 64, 3, 3, 2, 2, 1, 1)] + [(N, 64, 8, 8, 64, 3, 3, 1, 1, 1, 1)] * 5
+    ds = [mk(t) for t in shapes]
+    kept = (0, 1, 8, 9, 15, 16)                                     # the first layer of each kind is compared with the oracle
+    data = {i: rand_inputs(ds[i], 300 + i) for i in kept}
+    if bad:
+        for X, dY in data.values():
+            dY[0, 0, 0, 0], dY[-1, 5, -1, -1], X[1, 2, 0, 0] = np.inf, np.nan, -np.inf
+    on_gpu = {i: (to_gpu(X), to_gpu(dY)) for i, (X, dY) in data.items()}
+    of = [max(i for i in kept if i <= j) for j in range(len(ds))]
+    out = [torch_nan(d) for d in ds]
+    s = B.Schedule(ds, [on_gpu[i][0] for i in of], [on_gpu[i][1] for i in of], out)
+    m = [B.EXACT] * len(ds)
+    s.run(m, B.alloc_workspace(s.workspace_bytes(m)))
+    for i in kept:
+        with np.errstate(all="ignore"):
+            want = oracle.wgrad_exact(oracle_shape(ds[i]), *data[i])
+        fine = np.isfinite(want)
+        for j, got in enumerate(o.cpu().numpy() for k, o in enumerate(out) if of[k] == i):
+            assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+            assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / (1 if bad else 50), (i, j)
+
+
 # ResNet-20's shapes in runs, on both sides of the lines for short layers: 0.14 GFLOP for two layers of a shape, 0.5 for one and
 # for strides
 @pytest.mark.parametrize("N", [29, 30, 48, 107])
