@@ -121,6 +121,7 @@ struct MultiQueue;
 int launch_exact_plane2(const Geometry &g, const Batch &b, hipStream_t st, MultiQueue *mq = nullptr);
 struct CombineQueue;
 bool plan_exact_x3(const Geometry &g, X3Plan &pl);
+long exact_older_room(const Geometry &g);            // partial results in the workspace of the streaming form
 bool x3_needs_alignment(const X3Plan &pl);
 bool x3_ragged(const X3Plan &pl);
 int x3_tile_rows(const X3Plan &pl);

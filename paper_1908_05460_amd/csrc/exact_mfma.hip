@@ -585,6 +585,13 @@ static ExactPlan size_exact(const Geometry &g, ExactPlan pl)
     return pl;
 }
 
+// partial results that the streaming form's workspace has room for (no end of them where that form does not take the shape)
+long exact_older_room(const Geometry &g)
+{
+    const ExactPlan pl = plan_exact_forms(g, true);
+    return pl.stream ? std::max(1l, (long)(size_exact(g, pl).ws_bytes / ((size_t)g.dw_elems() * 4))) : 1l << 30;
+}
+
 // Where the forms above are the faster ones although the form of 16-bit pieces takes the shape (of 2000 shapes timed both ways;
 // us of this form / of the older one, N, C -> K @ H x W):
 static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan &x3, double gflop)
@@ -615,6 +622,8 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
     if (pl.nt == 2 && (strided ? g.Wo >= 12 : pl.stream && g.Wo >= 16)) return true;
     // of four (up to seven channels; 37, 7 -> 97 @ 64x64: 67 / 43; stride 2, 58, 4 -> 126 @ 30x146: 60 / 48)
     if (pl.nt == 4 && (strided ? g.C <= 5 && g.Wo >= 8 && gflop >= 0.15 : pl.stream && g.Wo >= 40 && gflop >= 0.5 && x3_tile_rows(x3) == 16)) return true;
+    // short ones on ragged rows (above plan_exact_x3_or_older)
+    if (strided && pl.stream && x3_ragged(x3) && gflop < 0.5 && (gflop < 0.03 || g.K <= 16 || g.C <= 16)) return true;
     if (g.S == 5 && pl.stream && g.C <= 5 && gflop >= 1.2) return true;              // 8, 3 -> 128 @ 112x112, 5x5: 78 / 65
     if (pl.nt != 9 || !strided) return false;
     // strides: planes of four columns, half of whose chunks are empty (44, 128 -> 512 @ 8x8: 31 / 25; 145, 256 -> 256 @ 7x7:
@@ -632,9 +641,10 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // layer exact / every other one, N = 80: 74.1 -> 69.4 / 72.5 -> 65.7 us with the line at 0.3, N = 48: 57.9 -> 50.2 / 50.8 -> 51.2 at 0.2,
 // N = 32: 46.7 -> 43.5 / 47.6 -> 45.3 at 0.1, N = 16: 34.4 -> 35.7 / 32.9 -> 35.7 at 0.05; with the last layer alone
 // exact, N = 48: 42.6 -> 45.3 at 0.2), and batches under 16, which keep to the launch of many small groups (8, 64 -> 128 @ 16x16,
-// two layers and a small one, 34 us there, 27 here).  Such a layer alone takes it down to 0.03 GFLOP (64 -> 64 @
-// 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18), with 16 channels on a side not (16 -> 16 @ 32x32, N = 16: 15.6
-// against 14.8).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
+// two layers and a small one, 34 us there, 27 here).  Such a layer alone takes it down to 0.02 GFLOP (64 -> 64 @
+// 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18; of 30 shapes of 16 channels on a side or less than 0.03 GFLOP none was
+// slower, but short ragged strided rows; the smallest stay in the older forms' workspace: 16 -> 16 @ 32x32, N = 8 / 16 / 64 / 100: 13.4 / 14.3 / 14.7 / 19.3 -> 10.8 / 12.8 / 12.1 / 14.4;
+// 16 -> 100, N = 4: 16.7 -> 10.3; 32 -> 32 @ 8x8, N = 4: 13.4 -> 7.8; 8 -> 12 @ 12x12, stride 2, N = 30: 12.1, 16.6 here).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
 // of its own is what costs, and two or more of one shape at a time (with a small layer beside them, N = 64 / 128 / 256: one 23 /
 // 31 / 46 us against 34 / 47 / 62 that way, two 38 / 49 / 76 against 37 / 49 / 73, four 44 / 65 / 104 against 42 / 56 / 84);
 // alone the plain product is the faster one (512 -> 512, N = 128: 15.4 us against 24.3).
@@ -654,7 +664,7 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
     } else if (pl.stream && g.sw > 1 && gflop >= 1.5) use = 0;
     else if (!pl.stream || gflop >= 0.5) use = 2;
     else {
-        use = gflop >= 0.03 && g.K > 16 && g.C > 16 ? 1 : 0;
+        use = gflop >= 0.02 ? 1 : 0;
         run = g.sw == 1 && g.N >= 16 && gflop >= tune_int("WGRAD_X3_RUN_MFLOP", 140) * 1e-3;
     }
     X3Plan x3{};

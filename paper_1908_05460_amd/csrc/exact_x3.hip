@@ -203,6 +203,12 @@ bool x3_fit(X3Plan &pl, long room)
 
 bool plan_exact_x3(const Geometry &g, X3Plan &best)
 {
+    // Short layers of few channels, which the older forms took before, in the workspace of those
+    auto small_room = [&](X3Plan &pl) {
+        const double gflop = g.gflop();
+        if (g.bf16 || gflop >= 0.5 || (gflop >= 0.03 && g.K > 16 && g.C > 16)) return true;
+        return x3_fit(pl, exact_older_room(g));
+    };
     if (!g.bf16 && g.H == g.W && (g.W == 2 || g.W == 4)) {
         // (every such layer: no slower than the row form or the fp32 matrix core anywhere, 64 -> 64 @ 4x4 at N = 128 14.5 us
         // against 16.7, 512 -> 512 at N = 2 11.5 against 11.4, at N = 512 153 against 227; figures in exact_x3_planes.hip)
@@ -210,7 +216,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
         if (x3_tile(g, g.W == 4 ? kX3Planes4 : kX3Planes2, pl)) {
             best = pl;
             best.splits = x3_choose_splits(g, best, 1);
-            return true;
+            return small_room(best);
         }
     }
     if (g.W < 4 || g.Wo < 4 || g.pw >= 4096) return false;
@@ -234,7 +240,7 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
     }
     if (best_cost >= 1e30) return false;
     best.splits = x3_choose_splits(g, best, 1);
-    return true;
+    return small_room(best);
 }
 
 // ---- launches ----
