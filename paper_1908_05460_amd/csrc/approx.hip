@@ -13,9 +13,12 @@
 namespace wgrad {
 
 // ------------------------------------------------------------------------------------
-// select: a group of G lanes (power of two, <= 64) owns one map; each lane walks the
-// map in 16-byte pieces G pieces apart, keeps its own best (|v| bits, position) and
-// partial sum, then the group reduces with a butterfly over lane-xor shuffles.
+// select: a group of G lanes (a power of two, up to the workgroup's 256) owns one map; each lane walks the
+// map in 16-byte pieces G pieces apart, four of them in flight, keeps its own best (|v| bits, position) and
+// partial sum, then the group reduces with a butterfly over lane-xor shuffles, and over LDS where it is the workgroup.
+// Bound by the loads of dY.  One load at a time (a loop that may end between two) and at most a wavefront to a map took, us:
+// VGG-19 fp32 at N = 128, maps of 4x4 to 16x16, 25.5, now 21.2; 64 -> 64 @ 63x61, N = 16, the whole call 30.6, now 14.9; @ 128x128,
+// N = 8, 32.1, now 15.0.
 //
 // The comparison is done on the magnitude bits as unsigned integers, which orders
 // finite floats (and infinities) exactly as |v| does; +0/-0 and +v/-v compare equal.
@@ -109,46 +112,70 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
     int32_t *__restrict__ hw_out = ab.hw[by];
     float *__restrict__ sum_a = ab.sum[by];
     const int lane = threadIdx.x & 63;
-    const int maps_per_wave = 64 / G;
+    const bool wide = G == kBlock;                   // (as many workgroups as maps, then)
+    const int maps_per_wave = wide ? 1 : 64 / G;
     const long wave_global = (long)bx * (kBlock / 64) + (threadIdx.x >> 6);
-    const long map = wave_global * maps_per_wave + lane / G;
-    const int gl = lane % G;
+    const long map = wide ? bx : wave_global * maps_per_wave + lane / G;
+    const int gl = wide ? threadIdx.x : lane % G;
 
-    uint32_t best_key = 0, best_pos = 0;
-    bool have = false;
+    int best_key = -1;
+    uint32_t best_pos = 0;
     float sum = 0.f;
     if (map < maps) {
         const long base = map * len;
-#pragma unroll 4
-        for (int e = gl * VEC; e < len; e += G * VEC) {
-            uint32_t bits[VEC];
-            if (VEC == 1) {
-                bits[0] = BF16 ? (uint32_t)((const uint16_t *)dY)[base + e] << 16
-                               : ((const uint32_t *)dY)[base + e];
-            } else if (BF16) {   // VEC == 8 : one 16-byte load of 8 bf16
-                const uint4 raw = *(const uint4 *)((const uint16_t *)dY + base + e);
-                const uint32_t w[4] = {raw.x, raw.y, raw.z, raw.w};
+        // several loads, then their elements: a loop that ends between two loads waits for each
+        auto batch = [&](int e0, auto deep, auto whole) {       // not whole: a piece behind the map's end is the first one again and counts nothing
+            constexpr int DEEP = decltype(deep)::value;
+            constexpr bool WHOLE = decltype(whole)::value;
+            uint32_t raw[DEEP][VEC == 1 ? 1 : 4];
+            bool in[DEEP];
 #pragma unroll
-                for (int i = 0; i < 4; ++i) { bits[2 * i] = w[i] << 16; bits[2 * i + 1] = w[i] & 0xffff0000u; }
-            } else {             // VEC == 4 : one 16-byte load of 4 fp32
-                const uint4 raw = *(const uint4 *)((const uint32_t *)dY + base + e);
-                bits[0] = raw.x; bits[1] = raw.y; bits[2] = raw.z; bits[3] = raw.w;
+            for (int u = 0; u < DEEP; ++u) {
+                const int e = e0 + u * G * VEC;
+                in[u] = WHOLE || e < len;
+                const long at = base + (in[u] ? e : e0);
+                if (VEC == 1) raw[u][0] = BF16 ? (uint32_t)((const uint16_t *)dY)[at] << 16 : ((const uint32_t *)dY)[at];
+                else {               // one 16-byte load of 8 bf16 or 4 fp32
+                    const uint4 r = BF16 ? *(const uint4 *)((const uint16_t *)dY + at) : *(const uint4 *)((const uint32_t *)dY + at);
+                    raw[u][0] = r.x; raw[u][1] = r.y; raw[u][2] = r.z; raw[u][3] = r.w;
+                }
             }
 #pragma unroll
-            for (int i = 0; i < VEC; ++i) {
-                const uint32_t key = mag_key<BF16>(bits[i]);
-                if (!have || key > best_key) { best_key = key; best_pos = e + i; have = true; }
-                sum += __uint_as_float(bits[i]);
-            }
-        }
+            for (int u = 0; u < DEEP; ++u)
+#pragma unroll
+                for (int i = 0; i < VEC; ++i) {
+                    const uint32_t b = VEC == 8 ? (i & 1 ? raw[u][i / 2] & 0xffff0000u : raw[u][i / 2] << 16) : raw[u][i % 4];
+                    const int key = in[u] ? (int)mag_key<BF16>(b) : -1;
+                    if (key > best_key) { best_key = key; best_pos = e0 + u * G * VEC + i; }
+                    sum += in[u] ? __uint_as_float(b) : 0.f;
+                }
+        };
+        auto walk = [&](auto deep) {
+            const int step = decltype(deep)::value * G * VEC;
+            int e = gl * VEC;
+            for (; e + step - G * VEC < len; e += step) batch(e, deep, std::true_type{});
+            if (e < len) batch(e, deep, std::false_type{});
+        };
+        // (element by element, a workgroup to a map: eight; 100 -> 50 @ 225x225, bf16, N = 4: 31.2 us with four, 23.1)
+        if (VEC == 1 && wide) walk(std::integral_constant<int, 8>{});
+        else walk(std::integral_constant<int, 4>{});
     }
     // lanes that saw nothing (len smaller than the group's reach) must lose every comparison
-    unsigned long long packed = have ? ((unsigned long long)best_key << 32) | (uint32_t)~best_pos : 0ull;
-    for (int d = G >> 1; d > 0; d >>= 1) {
+    unsigned long long packed = best_key >= 0 ? ((unsigned long long)(uint32_t)best_key << 32) | (uint32_t)~best_pos : 0ull;
+    for (int d = wide ? 32 : G >> 1; d > 0; d >>= 1) {
         const unsigned long long other = __shfl_xor(packed, d, 64);
         const float osum = __shfl_xor(sum, d, 64);
         packed = other > packed ? other : packed;
         sum += osum;
+    }
+    if (wide) {
+        __shared__ unsigned long long wave_packed[kBlock / 64];
+        __shared__ float wave_sum[kBlock / 64];
+        if (lane == 0) { wave_packed[threadIdx.x >> 6] = packed; wave_sum[threadIdx.x >> 6] = sum; }
+        __syncthreads();
+        sum = (wave_sum[0] + wave_sum[1]) + (wave_sum[2] + wave_sum[3]);
+#pragma unroll
+        for (int w = 0; w < kBlock / 64; ++w) packed = wave_packed[w] > packed ? wave_packed[w] : packed;
     }
     if (map < maps && gl == 0) {
         const int32_t pos = (int32_t)~(uint32_t)packed;
@@ -240,7 +267,9 @@ static int launch_select_impl(const Geometry &g, const ApproxBatch &ab, int npro
     // lanes per map: enough that each lane issues about four accesses
     int G = 1;
     while (G < 64 && G * vec * 4 < len) G <<= 1;
-    const long waves = (maps + 64 / G - 1) / (64 / G);
+    // a workgroup to a map where each of its lanes has four accesses
+    if (kBlock * vec * 4 <= len && maps < (1l << 31)) G = kBlock;
+    const long waves = G == kBlock ? maps * (kBlock / 64) : (maps + 64 / G - 1) / (64 / G);
     const int grid = (int)((waves + kBlock / 64 - 1) / (kBlock / 64));
     if (sq && !flat_out && !sum_b) {
         if (sq->n == kSelectMultiMax || (sq->n > 0 && (sq->bf16 != g.bf16 || sq->vec != vec))) {

@@ -270,6 +270,25 @@ def test_select_with_heavy_ties(hw, dtype):
     check_select(d, dY, idx.cpu().numpy(), S.cpu().numpy())
 
 
+# Maps of a workgroup each or of a wavefront, in whole batches of loads or with a tail, in 16-byte pieces or element by element: both
+# sides of the lines; maps of a few values, and of distinct ones whose largest lies first, last or anywhere
+@pytest.mark.parametrize("dtype", ["fp32", "bf16"])
+@pytest.mark.parametrize("hw", [(31, 33), (32, 33), (45, 47), (64, 63), (64, 64), (68, 64), (91, 90), (64, 128), (65, 128), (101, 83)])
+def test_select_of_large_maps(hw, dtype):
+    Ho, Wo = hw
+    d = B.desc(3, 1, Ho, Wo, 7, R=1, S=1, pad=0, dtype=B.BF16 if dtype == "bf16" else B.F32)
+    rng = np.random.default_rng(Ho * 1000 + Wo)
+    dY = rng.standard_normal((d.N, d.K, Ho, Wo)).astype(np.float32)
+    dY[0] = rng.integers(-3, 4, size=dY[0].shape) * 0.25
+    dY[1, 0].flat[0], dY[1, 1].flat[-1] = -9.0, 9.0
+    dY[1, 2] = 0.0; dY[1, 2].flat[-1] = -1e-20
+    dY[1, 3] = -0.0
+    if dtype == "bf16":
+        dY = inputs.float32_to_bf16_bits(dY)
+    idx, S = B.conv_wgrad_select(d, to_gpu(dY))
+    check_select(d, dY, idx.cpu().numpy(), S.cpu().numpy())
+
+
 @pytest.mark.parametrize("dtype", ["fp32", "bf16"])
 @pytest.mark.parametrize("hw", [(2, 2), (4, 4), (8, 8), (16, 16), (32, 32), (7, 9)])
 def test_select_ranks_nan_as_zero(hw, dtype):
