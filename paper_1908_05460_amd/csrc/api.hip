@@ -380,11 +380,22 @@ static void choose_run_forms(const uint8_t *method, int n, const int *group, std
     // 256: 36.3 / 47.5 / 67.6 us in the sparsified form, 29.3 / 48.8 / 83.6 in registers)
     double on4 = 0, on2 = 0;
     each(WGRAD_APPROX, [&](LayerPlan &p, int members) {
-        if (p.ap.regs && p.g.H == 4) on4 += (double)p.g.dw_elems() * members;
+        if (p.ap.regs == 1 && p.g.H == 4) on4 += (double)p.g.dw_elems() * members;
         if (p.g.H == 2 && regs_takes(p.g)) on2 += (double)p.g.dw_elems() * members;
     });
     each(WGRAD_APPROX, [&](LayerPlan &p, int) {
         if (p.g.H == 2 && on4 > 0 && (p.g.N <= 64 || 8 * on4 >= on2)) plan_approx_regs(p.g, p.ap);
+    });
+    // Those held in LDS that the fused form takes too, whose launch and selection they are spared there beside others: from 1.8 million
+    // (image, channel of X, channel of dY) on.  (VGG-19's run of two such layers, N = 64, 1.6 million: 129.7 us fused, 130.9 in LDS; N =
+    // 96, 2.4 million: 167.6, 159.9.)
+    double in_lds = 0;
+    auto both = [](const LayerPlan &p) { return p.ap.regs == 2 && plan_approx_without_planes(p.g).fused; };
+    each(WGRAD_APPROX, [&](LayerPlan &p, int members) {
+        if (both(p)) in_lds += (double)p.g.N * p.g.C * p.g.K * members;
+    });
+    each(WGRAD_APPROX, [&](LayerPlan &p, int) {
+        if (in_lds < 1.8e6 && both(p)) p.ap = plan_approx_without_planes(p.g);
     });
 }
 

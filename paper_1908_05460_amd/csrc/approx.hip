@@ -140,6 +140,7 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
                     raw[u][0] = r.x; raw[u][1] = r.y; raw[u][2] = r.z; raw[u][3] = r.w;
                 }
             }
+            float part[DEEP * VEC];                  // (added in pairs: dW's error against 64 bits, 64 -> 64 @ 128x128, N = 8, 1.76e-7 one by one, 1.11e-7)
 #pragma unroll
             for (int u = 0; u < DEEP; ++u)
 #pragma unroll
@@ -147,8 +148,13 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
                     const uint32_t b = VEC == 8 ? (i & 1 ? raw[u][i / 2] & 0xffff0000u : raw[u][i / 2] << 16) : raw[u][i % 4];
                     const int key = in[u] ? (int)mag_key<BF16>(b) : -1;
                     if (key > best_key) { best_key = key; best_pos = e0 + u * G * VEC + i; }
-                    sum += in[u] ? __uint_as_float(b) : 0.f;
+                    part[u * VEC + i] = in[u] ? __uint_as_float(b) : 0.f;
                 }
+#pragma unroll
+            for (int d = 1; d < DEEP * VEC; d *= 2)
+#pragma unroll
+                for (int i = 0; i < DEEP * VEC; i += 2 * d) part[i] += part[i + d];
+            sum += part[0];
         };
         auto walk = [&](auto deep) {
             const int step = decltype(deep)::value * G * VEC;
@@ -199,7 +205,7 @@ __global__ __launch_bounds__(kBlock) void approx_select(ApproxBatch ab, long map
 
 // The selections of several layer groups of a schedule run as one grid (each is a few microseconds of HBM
 // streaming; launched one by one they are mostly ramp and tail).  Group table in the kernel arguments, read in place.
-constexpr int kSelectMultiMax = 6;
+constexpr int kSelectMultiMax = 8;   // (a seventh group, VGG-19's at N = 128, in a launch of its own: 4 us)
 struct SelectGroup {
     ApproxBatch ab;
     long maps;
@@ -231,6 +237,8 @@ struct SelectQueue {
 
 SelectQueue *select_queue_new() { return new SelectQueue; }
 void select_queue_delete(SelectQueue *q) { delete q; }
+
+static_assert(sizeof(SelectMulti) <= 4096, "kernel arguments");
 
 int select_flush(SelectQueue &q, hipStream_t st)
 {
@@ -1466,16 +1474,26 @@ int fused_flush(FusedQueue &q, hipStream_t st)
 #define WGRAD_GATHER_BLOCKS 512
 #endif
 
+static bool plan_approx_selected(const Geometry &g, int form, ApproxPlan &pl);
 // `pl`, the plan of a layer that the form of planes in registers takes, becomes that form's where the older form's workspace has
 // room for its selections; the batch is cut into no more chunks than it holds.  (Tensors that are not 16-byte aligned take the
 // older form, in the same workspace.)
 bool plan_approx_regs(const Geometry &g, ApproxPlan &pl)
 {
+    return regs_takes(g) && plan_approx_selected(g, 1, pl);
+}
+// the same for the form of planes in LDS
+static bool plan_approx_planes(const Geometry &g, ApproxPlan &pl)
+{
+    return planes_takes(g, pl) && plan_approx_selected(g, 2, pl);
+}
+static bool plan_approx_selected(const Geometry &g, int form, ApproxPlan &pl)
+{
     const ApproxPlan alt = pl;
     const size_t maps = align_up((size_t)g.N * g.K * 4);
-    if (!regs_takes(g) || alt.ws_bytes < 2 * maps) return false;
+    if (alt.ws_bytes < 2 * maps) return false;
     pl = ApproxPlan{};
-    pl.regs = 1;
+    pl.regs = form;
     pl.off_idx = 0; pl.off_sum = maps; pl.off_part = 2 * maps;
     if (alt.use_lds) {
         pl.ctiles = alt.ctiles; pl.ktiles = alt.ktiles; pl.gather_n = alt.gather_n;
@@ -1494,9 +1512,11 @@ ApproxPlan plan_approx(const Geometry &g, bool allow_lds, bool allow_fused, bool
     ApproxPlan pl = plan_approx_older(g, allow_lds, allow_fused, allow_mm);
     // 2x2 planes: too little work to fill the chip with an image after the other (512 -> 512, N = 128, alone: 35 us against 21 of
     // the sparsified form); see choose_run_forms
-    if (allow_lds && allow_fused && allow_mm && g.H > 2) plan_approx_regs(g, pl);
+    if (allow_lds && allow_fused && allow_mm && !(g.H > 2 && plan_approx_regs(g, pl))) plan_approx_planes(g, pl);
     return pl;
 }
+
+ApproxPlan plan_approx_without_planes(const Geometry &g) { return plan_approx_older(g); }
 
 static ApproxPlan plan_approx_older(const Geometry &g, bool allow_lds, bool allow_fused, bool allow_mm)
 {
@@ -1858,13 +1878,13 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
             if (rc == WGRAD_OK) rc = regs_flush(*rgq, st, defer);
             if (rc != WGRAD_OK) return rc;
         }
-        const RegsPosition at = regs_position(g);
+        const RegsPosition at = pl.regs == 2 ? planes_position(g) : regs_position(g);
         ab.hw_row = at.row; ab.hw_col = at.col;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rgq ? sq : nullptr);
         if (rc != WGRAD_OK) return rc;
         // (no more lost to rounding than the LDS gather loses, as it would cut the batch here)
         const int most_n = pl.gather_n > 0 ? gather_chunk_n(pl, g.N, b.n, gq != nullptr) : g.N;
-        return launch_regs(g, b, ab.hw, ab.sum, pl.chunks, most_n, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
+        return launch_regs(g, pl.regs == 2, b, ab.hw, ab.sum, pl.chunks, most_n, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
     }
     if (pl.sx) {
         // the group's workspace (b.n slices of plan.ws_bytes, contiguous) is cut anew: the sparsified tensors of

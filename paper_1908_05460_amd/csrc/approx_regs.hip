@@ -306,7 +306,6 @@ __device__ __forceinline__ void regs_body(const RegsParams &p, char *smem, int b
     regs_each(std::make_integer_sequence<int, L::KW>(), put);
 }
 
-constexpr int kRegsMultiMax = 8;
 struct RegsMulti {
     int n, waves;
     int begin[kRegsMultiMax + 1];    // first workgroup of each group (multiples of 8); begin[n] = grid size
@@ -363,17 +362,6 @@ RegsPosition regs_position(const Geometry &g)
     return RegsPosition{(g.H == 8 ? RegsLayout<8>::PITCH : RegsLayout<4>::PITCH) * g.sh, g.sw};
 }
 
-struct RegsItem {
-    Geometry g;
-    Batch b;
-    const int32_t *at[kMaxBatch];
-    const float *sum[kMaxBatch];
-    char *part;                      // partial results of the first problem; the next problem's lie `stride` bytes on
-    size_t stride;
-    int max_chunks;                  // that the workspace has room for
-    int fewest, least, most, additions;      // see regs_limits
-    float scale;
-};
 struct RegsQueue {
     int n = 0;
     RegsItem item[kRegsMultiMax];
@@ -509,12 +497,12 @@ static int regs_launch(const RegsItem *const *it, int n, bool big, hipStream_t s
 int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine)
 {
     int rc = WGRAD_OK;
-    for (int big = 0; big < 2 && rc == WGRAD_OK; ++big) {
+    for (int kind = 0; kind < 3 && rc == WGRAD_OK; ++kind) {       // 4x4 and 2x2 planes, 8x8 ones, those in LDS
         const RegsItem *it[kRegsMultiMax];
         int n = 0;
         for (int i = 0; i < q.n; ++i)
-            if ((q.item[i].g.H == 8) == (big != 0)) it[n++] = &q.item[i];
-        rc = regs_launch(it, n, big != 0, st, combine);
+            if ((q.item[i].planes ? 2 : q.item[i].g.H == 8) == kind) it[n++] = &q.item[i];
+        rc = kind == 2 ? planes_launch(it, n, st, combine) : regs_launch(it, n, kind == 1, st, combine);
     }
     q.n = 0;
     return rc;
@@ -522,14 +510,14 @@ int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine)
 
 // One group of identical layers, selected already (or recorded to be, where the launch is): its own launch, or (with a queue)
 // collected for regs_flush.
-int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, int most_n, float scale,
+int launch_regs(const Geometry &g, bool planes, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, int most_n, float scale,
                 void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue)
 {
     RegsQueue local;
     RegsQueue &q = queue ? *queue : local;
     RegsItem &I = q.item[q.n++];
-    I.g = g; I.b = b; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride;
-    regs_limits(I, most_n);
+    I.g = g; I.b = b; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride; I.planes = planes;
+    if (!planes) regs_limits(I, most_n);
     for (int i = 0; i < b.n; ++i) { I.at[i] = at[i]; I.sum[i] = sum[i]; }
     return queue ? WGRAD_OK : regs_flush(local, st, defer);
 }

@@ -183,13 +183,14 @@ struct ApproxPlan {
     int gather_n;                    // images of the LDS form's batch chunk alone; also where `regs` stands in for that form, which loses no more to rounding
     int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm): 0 no, 1 a layer alone, 2 in a run with enough such work; the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
-    int regs;                        // fp32, planes held in registers (approx_regs.hip)
+    int regs;                        // fp32, planes held in registers (1, approx_regs.hip) or in LDS (2, approx_planes.hip)
     int sx;                          // fp32, planes of up to four positions: exact kernel on the sparsified dY
     ExactPlan ex;                    // its plan
     size_t off_idx, off_sum, off_part, off_sparse, ws_bytes;
 };
 ApproxPlan plan_approx(const Geometry &g, bool allow_lds = true, bool allow_fused = true, bool allow_mm = true);
 bool plan_approx_regs(const Geometry &g, ApproxPlan &pl);
+ApproxPlan plan_approx_without_planes(const Geometry &g);   // in LDS, whatever the size
 struct FusedQueue;
 struct GatherQueue;
 struct RegsQueue;
@@ -209,11 +210,28 @@ int launch_approx(const Geometry &g, const ApproxPlan &pl, const Batch &b, float
 struct RegsPosition { int row, col; };
 bool regs_takes(const Geometry &g);
 RegsPosition regs_position(const Geometry &g);
+constexpr int kRegsMultiMax = 8;     // groups of layers in a launch
+struct RegsItem {
+    Geometry g;
+    Batch b;
+    const int32_t *at[kMaxBatch];
+    const float *sum[kMaxBatch];
+    char *part;                      // partial results of the first problem; the next problem's lie `stride` bytes on
+    size_t stride;
+    int max_chunks;                  // that the workspace has room for
+    int fewest, least, most, additions;      // see regs_limits
+    float scale;
+    bool planes;                     // approx_planes.hip's
+};
+// those on other planes, in LDS (approx_planes.hip), of the same queue; alt: the plan without that form
+bool planes_takes(const Geometry &g, const ApproxPlan &alt);
+RegsPosition planes_position(const Geometry &g);
+int planes_launch(const RegsItem *const *it, int n, hipStream_t st, CombineQueue *combine);
 RegsQueue *regs_queue_new();
 void regs_queue_delete(RegsQueue *q);
 bool regs_full(const RegsQueue &q);
 int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine);
-int launch_regs(const Geometry &g, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, int most_n, float scale,
+int launch_regs(const Geometry &g, bool planes, const Batch &b, const int32_t *const *at, const float *const *sum, int max_chunks, int most_n, float scale,
                 void *part, size_t stride, hipStream_t st, CombineQueue *defer, RegsQueue *queue);
 // LDS-form gathers of several layer groups, collected for one launch
 GatherQueue *gather_queue_new(SelectQueue *selects = nullptr);

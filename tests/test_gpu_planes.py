@@ -1,0 +1,59 @@
+"""Approximated fp32 layers on planes of up to 256 positions in LDS: tiles of input and output channels with a remainder, planes of one and of
+several positions a lane, the largest plane LDS holds, strides and paddings, batches that leave wavefronts without an image, alone
+and in a run, against the oracle on every dW entry."""
+import numpy as np
+import pytest
+
+import oracle
+from paper_1908_05460_amd import binding as B
+from tests.gpu_util import TOL, normwise_err, oracle_shape, rand_inputs, to_gpu
+from tests.test_gpu_regs import run_approx
+
+pytestmark = pytest.mark.gpu
+BOUND = TOL["fp32"] / 50        # fp32 sums of a few products a wavefront, added in 64 bits
+
+# (N, C, H, W, K, stride, padding)
+SHAPES = [(100, 61, 5, 5, 65, 1, 1), (200, 41, 2, 3, 70, 1, 1), (21, 130, 7, 9, 129, 1, 1), (40, 66, 8, 8, 300, 2, 0), (130, 33, 13, 13, 71, 1, 1), (47, 131, 16, 16, 128, 1, 1),
+          (92, 128, 16, 16, 64, 2, 1), (9, 300, 16, 16, 320, 1, 0), (30, 110, 4, 64, 256, 1, 1), (50, 125, 64, 4, 128, 1, 1), (70, 67, 15, 17, 70, 2, 0)]
+
+
+def desc(t):
+    N, C, H, W, K, stride, pad = t
+    return B.desc(N, C, H, W, K, R=3, S=3, stride=stride, pad=pad)
+
+
+@pytest.mark.parametrize("t", SHAPES)
+def test_alone_matches_the_oracle(t):
+    import torch
+    d = desc(t)
+    X, dY = rand_inputs(d, 31)
+    want, want_idx, _ = oracle.wgrad_approx(oracle_shape(d), X, dY)
+    idx = torch.full((d.N, d.K), -1, dtype=torch.int32, device="cuda")
+    got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY), idx_out=idx).cpu().numpy()
+    assert normwise_err(got, want) < BOUND
+    assert np.array_equal(idx.cpu().numpy(), want_idx)
+
+
+def test_run_matches_the_oracle():
+    """More groups than a launch carries, layers of one shape, others in registers beside them; selections element by element and in pieces."""
+    shapes = SHAPES[:10] + [SHAPES[5]] * 2 + [(5, 64, 8, 8, 128, 1, 1), (5, 64, 4, 4, 128, 1, 1)]
+    ds = [desc(t) for t in shapes]
+    data = [rand_inputs(d, 50 + i) for i, d in enumerate(ds)]
+    for d, (X, dY), got in zip(ds, data, run_approx(ds, data)):
+        assert normwise_err(got * 4, oracle.wgrad_approx(oracle_shape(d), X, dY)[0]) < BOUND
+
+
+@pytest.mark.parametrize("where", ["X", "dY"])
+@pytest.mark.parametrize("t", [SHAPES[0], SHAPES[5], SHAPES[6]])
+def test_infinities_and_nans(t, where):
+    """As in the definition: one of X reaches the taps that see it, a map's sum its patch, the padding's zeros among it."""
+    d = desc(t)
+    X, dY = rand_inputs(d, 33)
+    A = X if where == "X" else dY
+    A[3, 5, 0, 0], A[7, 11, -1, -1], A[8, 2, 1, 1] = np.inf, -np.inf, np.nan
+    with np.errstate(all="ignore"):
+        want = oracle.wgrad_approx(oracle_shape(d), X, dY)[0]
+    got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY)).cpu().numpy()
+    fine = np.isfinite(want)
+    assert not fine.all() and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
+    assert normwise_err(got[fine], want[fine]) < BOUND
