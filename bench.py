@@ -32,9 +32,9 @@ sys.path.insert(0, ROOT)
 
 HBM_PEAK_GBS = 8000.0
 MFMA_PEAK_TFLOPS = {"fp32": 157.3, "bf16": 2500.0}   # dense matrix-core peaks of MI355X
-# what bounds the exact gradient: fp32 numbers go through the bf16 matrix core as three pieces and six products each
-# (small and some strided layers still through the fp32 one, whose 157.3 is below that)
-EXACT_PEAK_TFLOPS = {"fp32": round(2500.0 / 6, 1), "bf16": 2500.0}
+# what bounds the exact gradient: fp32 numbers go through the 16-bit matrix cores as two fp16 pieces and three products each
+# (16-wide tiles and short sums as three bf16 pieces and six, the smallest layers through the fp32 core, both below that)
+EXACT_PEAK_TFLOPS = {"fp32": round(2500.0 / 3, 1), "bf16": 2500.0}
 LDS_PEAK_GBS = 256 * 128 * 2.4                       # 256 CUs x 128 B/clk x 2.4 GHz
 HEADLINE = "vgg19_n128_fp32"
 OTHER_CONFIGS = ("single3x3_n16_fp32", "resnet20_n128_fp32", "vgg19_n512_bf16", "resnet20_schedule_sweep")
@@ -304,8 +304,8 @@ def run_workload(args, name, machine, steps, warmup, headline):
     achieved_tf = tot["flops"] / phase_ms["exact"] / 1e9
     mfma_measured = None
     if machine:
-        mfma_measured = round(machine["mfma_bf16_32x32x16_tflops"] / 6, 1) if dtype == "fp32" else machine["mfma_bf16_16x16x32_tflops"]
-    roofline = {"kernel": "exact phase = wgrad_exact_x3 + wgrad_exact_x3_planes (fp32 as bf16 pieces, groups of a variant in one launch), wgrad_exact_multi | wgrad_exact_stream (fp32 matrix core: strided and small layers) | wgrad_bf16_rows + wgrad_exact_bf16_multi + wgrad_exact_bf16_planes (bf16), + combine_table",
+        mfma_measured = round(machine["mfma_bf16_32x32x16_tflops"] / 3, 1) if dtype == "fp32" else machine["mfma_bf16_16x16x32_tflops"]
+    roofline = {"kernel": "exact phase = wgrad_exact_x3 + wgrad_exact_x3_mix + wgrad_exact_x3_planes (fp32 as fp16 or bf16 pieces, groups of a variant in one launch), wgrad_exact_multi | wgrad_exact_stream (fp32 matrix core: strided and small layers) | wgrad_bf16_rows + wgrad_exact_bf16_multi + wgrad_exact_bf16_planes (bf16), + combine_table",
                 "bound": "mfma", "achieved": round(achieved_tf, 3), "peak": EXACT_PEAK_TFLOPS[dtype], "unit": "TFLOP/s",
                 "frac": round(achieved_tf / EXACT_PEAK_TFLOPS[dtype], 4),
                 "traffic": traffic["exact_phase_bytes"] if traffic else None, "traffic_source": traffic_src if traffic else None,
@@ -313,7 +313,7 @@ def run_workload(args, name, machine, steps, warmup, headline):
                 "frac_of_measured": round(achieved_tf / mfma_measured, 4) if mfma_measured else None,
                 "achieved_valid_taps": round(tot["valid_flops"] / phase_ms["exact"] / 1e9, 3),
                 "frac_valid_taps": round(tot["valid_flops"] / phase_ms["exact"] / 1e9 / EXACT_PEAK_TFLOPS[dtype], 4),
-                "note": "fp32 peak: the bf16 one over the six products of a number; "
+                "note": "fp32 peak: the 16-bit one over the three products of two fp16 pieces (layers on three bf16 pieces make six); "
                         "achieved counts nominal FLOPs (padding taps included, the usual convention); kernels of small planes leave out "
                         "matrix instructions whose taps meet only padding, so the matrix core's own rate is bounded by "
                         "achieved_valid_taps (products that do not multiply padding) from below and achieved from above",

@@ -38,7 +38,7 @@
 // each piece, zero outside the tensors.  Two workgroups and more share a CU: one stages while another multiplies.  Timestamps
 // (64 -> 64 @ 32x32, N = 128, 512 workgroups of 8 tiles, 36 us each): set-up and first loads 4.3, the first tile's scales 2.4,
 // then a tile 0.7 of splitting, 0.5 of asking for the next, 1.4 of matrix instructions (0.9 alone), 0.4 at barriers; the
-// exchange and write-out 4.9; loads are never waited for.
+// exchange and write-out 4.3; loads are never waited for.
 // bf16 inputs are their own only piece: the same kernel with one product per pair serves the bf16 shapes that
 // exact_bf16_kernel.hpp does not take.
 #pragma once
