@@ -1,4 +1,5 @@
-// Approximated filter gradient of fp32 layers (3x3, padding up to 1) on planes of up to 256 positions: the planes in LDS.
+// Approximated filter gradient of layers (3x3, padding up to 1) on planes of up to 256 positions: the planes in LDS, as fp32.  (bf16: what the
+// matrix-core forms do not take.)
 //
 // dW[k][c][tap] = sum over n of sum[n][k] * X[n][c][position(n, k) + tap].  A lane is an output channel, so that a map's position is
 // an address of its lane: the nine taps are LDS reads at offsets that all lanes share, and nothing moves to scalar registers.  Four input channels lie
@@ -9,7 +10,7 @@
 // and the exchange at the end.  128 -> 128 @ 16x16, N = 128: 9.9 us (channels in planes of their own, a read for each
 // multiply-add: 11.5; two tiles of output channels to a lane spill), 1.7 TB/s; VGG-19's two such layers 15.4 where the fused
 // form, whose patches come from L2, took 47 with their selections, 8 here.  Whole calls, before and now: that layer 27.0, 17.7;
-// 200 -> 150 @ 9x9, N = 60: 42.3, 13.8; 200 -> 200 @ 7x7, N = 100: 66.6, 13.9; 128 -> 256 @ 16x16, stride 2, N = 128: 39.5, 18.5.
+// 200 -> 150 @ 9x9, N = 60: 42.3, 13.8 (bf16 41.7, 14.0); 200 -> 200 @ 7x7, N = 100: 66.6, 13.9; 128 -> 256 @ 16x16, stride 2, N = 128: 39.5, 18.5.
 #include <algorithm>
 #include <type_traits>
 
@@ -20,7 +21,7 @@ namespace wgrad {
 constexpr int kPlanesWaves = 8;
 
 struct PlanesParams {
-    const float *X[kMaxBatch];
+    const void *X[kMaxBatch];
     const int32_t *at[kMaxBatch];                    // [N][K]: byte offset of a map's window in a plane with its border
     const float *sum[kMaxBatch];
     float *out[kMaxBatch];                           // dW, or the partials of the batch chunks
@@ -34,7 +35,10 @@ struct PlanesParams {
 
 typedef float pl_f4 __attribute__((ext_vector_type(4)));
 
-template <int NL>
+__device__ __forceinline__ float planes_value(float x) { return x; }
+__device__ __forceinline__ float planes_value(uint16_t x) { return bf16_bits_to_float(x); }
+
+template <bool BF16, int NL>
 __device__ __forceinline__ void planes_body(const PlanesParams &p, pl_f4 *smem, int bid, int prob)
 {
     constexpr int CW = 4;
@@ -44,7 +48,8 @@ __device__ __forceinline__ void planes_body(const PlanesParams &p, pl_f4 *smem, 
     const int c0 = ct * CW, k0 = kt * 64;
     const int n_begin = chunk * p.chunk_n, n_end = min(n_begin + p.chunk_n, p.N);
     if (n_begin >= n_end) return;
-    const float *X = p.X[prob] + (size_t)c0 * p.HW;
+    typedef std::conditional_t<BF16, uint16_t, float> elem;
+    const elem *X = (const elem *)p.X[prob] + (size_t)c0 * p.HW;
     const int32_t *at = p.at[prob];
     const float *sum = p.sum[prob];
     const int per_wave = p.plane + 1;                // (the last one takes what lanes without a position write)
@@ -70,13 +75,14 @@ __device__ __forceinline__ void planes_body(const PlanesParams &p, pl_f4 *smem, 
 #pragma unroll
         for (int t = 0; t < 9; ++t) acc[c][t] = 0.f;
 
-    float x[2][NL][CW], s[2];
+    elem x[2][NL][CW];
+    float s[2];
     int a[2];
     const size_t image = (size_t)p.C * p.HW;
     auto load = [&](auto set, int n) {               // (behind the chunk's last image: that one again, so that as many loads are in flight)
         constexpr int i = decltype(set)::value;
         const int nn = min(n, n_end - 1);
-        const float *from = X + nn * image;
+        const elem *from = X + nn * image;
 #pragma unroll
         for (int u = 0; u < NL; ++u)
 #pragma unroll
@@ -87,7 +93,7 @@ __device__ __forceinline__ void planes_body(const PlanesParams &p, pl_f4 *smem, 
     auto step = [&](auto set, int n) {
         constexpr int i = decltype(set)::value;
 #pragma unroll
-        for (int u = 0; u < NL; ++u) mine[dst[u]] = pl_f4{x[i][u][0], x[i][u][1], x[i][u][2], x[i][u][3]};
+        for (int u = 0; u < NL; ++u) mine[dst[u]] = pl_f4{planes_value(x[i][u][0]), planes_value(x[i][u][1]), planes_value(x[i][u][2]), planes_value(x[i][u][3])};
         const pl_f4 *const w = (const pl_f4 *)((const char *)(mine + p.first) + a[i]);
         const float sv = live ? s[i] : 0.f;
         load(set, n + 2 * kPlanesWaves);
@@ -143,6 +149,7 @@ struct PlanesMulti {
 };
 static_assert(sizeof(PlanesMulti) <= 4096, "kernel arguments");
 
+template <bool BF16>
 __global__ __launch_bounds__(64 * kPlanesWaves, 4) void approx_gather_planes(const PlanesMulti)
 {
     extern __shared__ __attribute__((aligned(16))) pl_f4 planes_smem[];
@@ -152,26 +159,28 @@ __global__ __launch_bounds__(64 * kPlanesWaves, 4) void approx_gather_planes(con
     for (int i = 1; i < n; ++i) gi += (int)blockIdx.x >= mp->begin[i];
     const PlanesParams &p = mp->p[gi];
     const int bid = (int)blockIdx.x - mp->begin[gi], prob = bid / mp->per_prob[gi], at = bid - prob * mp->per_prob[gi];
-    if (p.HW <= 64) planes_body<1>(p, planes_smem, at, prob);
-    else planes_body<4>(p, planes_smem, at, prob);
+    if (p.HW <= 64) planes_body<BF16, 1>(p, planes_smem, at, prob);
+    else planes_body<BF16, 4>(p, planes_smem, at, prob);
 }
 
 // ---- host ----
 // Against the direct form, which reads a patch an entry from L2, from 300 000 (image, channel of X, channel of dY) on (60 -> 150 @ 9x9, N = 20:
 // 12.0 us there, 12.3 here, 540 000: 19.3, 13.2; 60 -> 50 @ 13x13, N = 30: 11.7, 12.3); against the fused one, which selects in the same launch,
-// from 750 000 (128 -> 128 @ 16x16, N = 32: 10.4, 13.0; N = 48: 15.5, 14.3; 16 -> 128, N = 200: 14.4, 17.6) and where three
+// from 750 000 (128 -> 128 @ 16x16, N = 32: 10.4, 13.0; N = 48: 15.5, 14.3; 16 -> 128, N = 200: 14.4, 17.6), in bf16, whose maps stream in half the time, from a million (128 -> 128 @ 16x16, stride 2, N = 48: 12.9, 14.0; N = 64: 15.5,
+// 14.9), and where three
 // lanes of four have an output channel.  The LDS gather keeps its layers, 8x8 planes that the form in registers does not take, unmeasured.
 bool planes_takes(const Geometry &g, const ApproxPlan &alt)
 {
-    if (g.bf16 || g.R != 3 || g.S != 3 || g.ph > 1 || g.pw > 1 || alt.sx || alt.use_lds) return false;
+    if (g.R != 3 || g.S != 3 || g.ph > 1 || g.pw > 1 || alt.sx || alt.mm || alt.use_lds) return false;
     if (g.H * g.W > 256 || kPlanesWaves * 16l * ((g.H + 2l) * (g.W + 1) + 2) > 64 * 1024) return false;
     const double work = (double)g.N * g.C * g.K;
-    if (alt.fused) return work >= 750e3 && 4 * g.K >= 3 * ((g.K + 63) / 64 * 64);
+    if (alt.fused) return work >= (g.bf16 ? 1e6 : 750e3) && 4 * g.K >= 3 * ((g.K + 63) / 64 * 64);
     return work >= 300e3;
 }
 
 RegsPosition planes_position(const Geometry &g) { return RegsPosition{(g.W + 1) * g.sh * 16, g.sw * 16}; }
 
+// (of one element type)
 int planes_launch(const RegsItem *const *it, int n, hipStream_t st, CombineQueue *combine)
 {
     if (n == 0) return WGRAD_OK;
@@ -199,7 +208,7 @@ int planes_launch(const RegsItem *const *it, int n, hipStream_t st, CombineQueue
         p.scale = ch > 1 ? 1.0f : I.scale;
         for (int j = 0; j < kMaxBatch; ++j) {
             const int k = j < I.b.n ? j : 0;
-            p.X[j] = (const float *)I.b.X[k]; p.at[j] = I.at[k]; p.sum[j] = I.sum[k];
+            p.X[j] = I.b.X[k]; p.at[j] = I.at[k]; p.sum[j] = I.sum[k];
             p.out[j] = ch > 1 ? (float *)(I.part + k * I.stride) : I.b.dW[k];
         }
         lds = std::max(lds, (size_t)kPlanesWaves * std::max(16 * (p.plane + 1), 64 * 19 * 4));
@@ -208,7 +217,8 @@ int planes_launch(const RegsItem *const *it, int n, hipStream_t st, CombineQueue
         blocks += m.per_prob[i] * I.b.n;
     }
     m.begin[n] = blocks;
-    WGRAD_LAUNCH(approx_gather_planes, dim3((unsigned)blocks), dim3(64 * kPlanesWaves), lds, st, m);
+    if (it[0]->g.bf16) WGRAD_LAUNCH(approx_gather_planes<true>, dim3((unsigned)blocks), dim3(64 * kPlanesWaves), lds, st, m);
+    else WGRAD_LAUNCH(approx_gather_planes<false>, dim3((unsigned)blocks), dim3(64 * kPlanesWaves), lds, st, m);
     int rc = launch_status();
     for (int i = 0; i < n && rc == WGRAD_OK; ++i)
         if (chunks[i] > 1)

@@ -497,12 +497,12 @@ static int regs_launch(const RegsItem *const *it, int n, bool big, hipStream_t s
 int regs_flush(RegsQueue &q, hipStream_t st, CombineQueue *combine)
 {
     int rc = WGRAD_OK;
-    for (int kind = 0; kind < 3 && rc == WGRAD_OK; ++kind) {       // 4x4 and 2x2 planes, 8x8 ones, those in LDS
+    for (int kind = 0; kind < 4 && rc == WGRAD_OK; ++kind) {       // 4x4 and 2x2 planes, 8x8 ones, those in LDS, fp32 and bf16
         const RegsItem *it[kRegsMultiMax];
         int n = 0;
         for (int i = 0; i < q.n; ++i)
-            if ((q.item[i].planes ? 2 : q.item[i].g.H == 8) == kind) it[n++] = &q.item[i];
-        rc = kind == 2 ? planes_launch(it, n, st, combine) : regs_launch(it, n, kind == 1, st, combine);
+            if ((q.item[i].planes ? 2 + (q.item[i].g.bf16 != 0) : q.item[i].g.H == 8) == kind) it[n++] = &q.item[i];
+        rc = kind >= 2 ? planes_launch(it, n, st, combine) : regs_launch(it, n, kind == 1, st, combine);
     }
     q.n = 0;
     return rc;

@@ -183,7 +183,7 @@ struct ApproxPlan {
     int gather_n;                    // images of the LDS form's batch chunk alone; also where `regs` stands in for that form, which loses no more to rounding
     int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm): 0 no, 1 a layer alone, 2 in a run with enough such work; the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
-    int regs;                        // fp32, planes held in registers (1, approx_regs.hip) or in LDS (2, approx_planes.hip)
+    int regs;                        // planes held in registers (1, fp32, approx_regs.hip) or in LDS (2, approx_planes.hip)
     int sx;                          // fp32, planes of up to four positions: exact kernel on the sparsified dY
     ExactPlan ex;                    // its plan
     size_t off_idx, off_sum, off_part, off_sparse, ws_bytes;

@@ -1,4 +1,4 @@
-"""Approximated fp32 layers on planes of up to 256 positions in LDS: tiles of input and output channels with a remainder, planes of one and of
+"""Approximated layers on planes of up to 256 positions in LDS: tiles of input and output channels with a remainder, planes of one and of
 several positions a lane, the largest plane LDS holds, strides and paddings, batches that leave wavefronts without an image, alone
 and in a run, against the oracle on every dW entry."""
 import numpy as np
@@ -17,16 +17,17 @@ SHAPES = [(100, 61, 5, 5, 65, 1, 1), (200, 41, 2, 3, 70, 1, 1), (21, 130, 7, 9, 
           (92, 128, 16, 16, 64, 2, 1), (9, 300, 16, 16, 320, 1, 0), (30, 110, 4, 64, 256, 1, 1), (50, 125, 64, 4, 128, 1, 1), (70, 67, 15, 17, 70, 2, 0)]
 
 
-def desc(t):
+def desc(t, dtype="fp32"):
     N, C, H, W, K, stride, pad = t
-    return B.desc(N, C, H, W, K, R=3, S=3, stride=stride, pad=pad)
+    return B.desc(N, C, H, W, K, R=3, S=3, stride=stride, pad=pad, dtype=B.BF16 if dtype == "bf16" else B.F32)
 
 
-@pytest.mark.parametrize("t", SHAPES)
-def test_alone_matches_the_oracle(t):
+# bf16: those that no matrix-core form takes
+@pytest.mark.parametrize("t,dtype", [(t, "fp32") for t in SHAPES] + [(t, "bf16") for t in SHAPES[:5] + [(66, 128, 16, 16, 128, 2, 1)]])
+def test_alone_matches_the_oracle(t, dtype):
     import torch
-    d = desc(t)
-    X, dY = rand_inputs(d, 31)
+    d = desc(t, dtype)
+    X, dY = rand_inputs(d, 31, dtype)
     want, want_idx, _ = oracle.wgrad_approx(oracle_shape(d), X, dY)
     idx = torch.full((d.N, d.K), -1, dtype=torch.int32, device="cuda")
     got = B.conv_wgrad_approx(d, to_gpu(X), to_gpu(dY), idx_out=idx).cpu().numpy()
@@ -37,8 +38,10 @@ def test_alone_matches_the_oracle(t):
 def test_run_matches_the_oracle():
     """More groups than a launch carries, layers of one shape, others in registers beside them; selections element by element and in pieces."""
     shapes = SHAPES[:10] + [SHAPES[5]] * 2 + [(5, 64, 8, 8, 128, 1, 1), (5, 64, 4, 4, 128, 1, 1)]
-    ds = [desc(t) for t in shapes]
-    data = [rand_inputs(d, 50 + i) for i, d in enumerate(ds)]
+    dtypes = ["fp32"] * len(shapes) + ["bf16"] * 3
+    shapes += [SHAPES[0], SHAPES[2], SHAPES[4]]
+    ds = [desc(t, dtype) for t, dtype in zip(shapes, dtypes)]
+    data = [rand_inputs(d, 50 + i, dtype) for i, (d, dtype) in enumerate(zip(ds, dtypes))]
     for d, (X, dY), got in zip(ds, data, run_approx(ds, data)):
         assert normwise_err(got * 4, oracle.wgrad_approx(oracle_shape(d), X, dY)[0]) < BOUND
 
