@@ -338,36 +338,58 @@ __global__ __launch_bounds__(kBlock) void sparsify_small(ApproxBatch ab, long ma
 // gather, direct form: one thread per filter-gradient entry (k, c, r, s) and batch
 // chunk; it walks the chunk's images, reads the map's (row, col, S) and the one input
 // element its tap sees.  Used when the patches touch only part of each input plane
-// (few output channels, large planes) and for filters other than 3x3.
+// (few output channels, large planes) and for filters other than 3x3.  Bound by those loads: eight images'
+// are in flight at a time (an image after the other waits for its position, then for its element), and an XCD takes whole
+// chunks, so that a chunk's lines are fetched into one L2.  Whole calls, us: 64 -> 64 @ 23x23, N = 100: 24.0, now 17.2; @ 50x50, bf16,
+// N = 64: 26.5, 20.2; 30 -> 60 @ 40x40, 5x5, N = 60: 22.9, 18.6.
 // ------------------------------------------------------------------------------------
 template <bool BF16>
 __global__ __launch_bounds__(kBlock) void approx_gather_direct(ApproxBatch ab, Geometry g,
                                                                int chunk_n, float scale)
 {
-    const void *__restrict__ X = ab.X[blockIdx.z];
-    const int32_t *__restrict__ hw = ab.hw[blockIdx.z];
-    const float *__restrict__ sum = ab.sum[blockIdx.z];
-    float *__restrict__ out = ab.out[blockIdx.z];
-    const long o = (long)blockIdx.x * kBlock + threadIdx.x;
+    const int gx = gridDim.x, gy = gridDim.y;
+    const int logical = __builtin_amdgcn_readfirstlane(
+        xcd_contiguous_id((int)((blockIdx.z * gy + blockIdx.y) * gx + blockIdx.x), (int)(gx * gy * gridDim.z)));
+    const int bx = logical % gx, by = logical / gx % gy, bz = logical / gx / gy;
+    const void *__restrict__ X = ab.X[bz];
+    const int32_t *__restrict__ hw = ab.hw[bz];
+    const float *__restrict__ sum = ab.sum[bz];
+    float *__restrict__ out = ab.out[bz];
+    const long o = (long)bx * kBlock + threadIdx.x;
     const int RS = g.R * g.S, CRS = g.C * RS;
     if (o >= (long)g.K * CRS) return;
     const int k = (int)(o / CRS), j = (int)(o % CRS);
-    const int c = j / RS, r = (j % RS) / g.S, s = j % g.S;
-    const int n_begin = blockIdx.y * chunk_n;
+    const int c = j / RS, r = (j % RS) / g.S - g.ph, s = j % g.S - g.pw;
+    const int n_begin = by * chunk_n;
     const int n_end = n_begin + chunk_n < g.N ? n_begin + chunk_n : g.N;
     float acc = 0.f;
-#pragma unroll 4
-    for (int n = n_begin; n < n_end; ++n) {
-        const int p = hw[(long)n * g.K + k];
-        const float sv = sum[(long)n * g.K + k];
-        const int ih = (p >> 16) * g.sh + r - g.ph, iw = (p & 0xffff) * g.sw + s - g.pw;
-        if (ih >= 0 && ih < g.H && iw >= 0 && iw < g.W) {
-            const long xi = (((long)n * g.C + c) * g.H + ih) * g.W + iw;
-            const float xv = BF16 ? bf16_bits_to_float(((const uint16_t *)X)[xi]) : ((const float *)X)[xi];
-            acc = fmaf(sv, xv, acc);
+    auto batch = [&](int n0, auto deep) {            // that many images
+        constexpr int DEEP = decltype(deep)::value;
+        int p[DEEP];
+        float sv[DEEP], xv[DEEP];
+        bool seen[DEEP];
+#pragma unroll
+        for (int u = 0; u < DEEP; ++u) {
+            const long m = (long)(n0 + u) * g.K + k;
+            p[u] = hw[m];
+            sv[u] = sum[m];
         }
-    }
-    out[(long)blockIdx.y * g.K * CRS + o] = acc * scale;
+#pragma unroll
+        for (int u = 0; u < DEEP; ++u) {
+            const int ih = (p[u] >> 16) * g.sh + r, iw = (p[u] & 0xffff) * g.sw + s;
+            seen[u] = (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+            const long xi = ((long)(n0 + u) * g.C + c) * g.H * g.W + (seen[u] ? (long)ih * g.W + iw : 0);
+            xv[u] = BF16 ? bf16_bits_to_float(((const uint16_t *)X)[xi]) : ((const float *)X)[xi];
+        }
+#pragma unroll
+        for (int u = 0; u < DEEP; ++u) acc = seen[u] ? fmaf(sv[u], xv[u], acc) : acc;
+    };
+    int n = n_begin;
+    for (; n + 8 <= n_end; n += 8) batch(n, std::integral_constant<int, 8>{});
+    if (n + 4 <= n_end) { batch(n, std::integral_constant<int, 4>{}); n += 4; }
+    if (n + 2 <= n_end) { batch(n, std::integral_constant<int, 2>{}); n += 2; }
+    if (n < n_end) batch(n, std::integral_constant<int, 1>{});
+    out[(long)by * g.K * CRS + o] = acc * scale;
 }
 
 // ------------------------------------------------------------------------------------

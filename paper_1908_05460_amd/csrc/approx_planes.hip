@@ -164,8 +164,8 @@ __global__ __launch_bounds__(64 * kPlanesWaves, 4) void approx_gather_planes(con
 }
 
 // ---- host ----
-// Against the direct form, which reads a patch an entry from L2, from 300 000 (image, channel of X, channel of dY) on (60 -> 150 @ 9x9, N = 20:
-// 12.0 us there, 12.3 here, 540 000: 19.3, 13.2; 60 -> 50 @ 13x13, N = 30: 11.7, 12.3); against the fused one, which selects in the same launch,
+// Against the direct form, which reads a patch an entry from L2, from 350 000 (image, channel of X, channel of dY) on (60 -> 150 @ 9x9, N = 35 /
+// 45 / 60: 14.1 / 13.5 / 15.3 us there, 14.9 / 13.4 / 13.6 here; 30 -> 200 @ 13x13, N = 60 / 100: 16.9 / 21.8, 16.5 / 19.5); against the fused one, which selects in the same launch,
 // from 750 000 (128 -> 128 @ 16x16, N = 32: 10.4, 13.0; N = 48: 15.5, 14.3; 16 -> 128, N = 200: 14.4, 17.6), in bf16, whose maps stream in half the time, from a million (128 -> 128 @ 16x16, stride 2, N = 48: 12.9, 14.0; N = 64: 15.5,
 // 14.9), and where three
 // lanes of four have an output channel.  The LDS gather keeps its layers, 8x8 planes that the form in registers does not take, unmeasured.
@@ -175,7 +175,7 @@ bool planes_takes(const Geometry &g, const ApproxPlan &alt)
     if (g.H * g.W > 256 || kPlanesWaves * 16l * ((g.H + 2l) * (g.W + 1) + 2) > 64 * 1024) return false;
     const double work = (double)g.N * g.C * g.K;
     if (alt.fused) return work >= (g.bf16 ? 1e6 : 750e3) && 4 * g.K >= 3 * ((g.K + 63) / 64 * 64);
-    return work >= 300e3;
+    return work >= 350e3;
 }
 
 RegsPosition planes_position(const Geometry &g) { return RegsPosition{(g.W + 1) * g.sh * 16, g.sw * 16}; }

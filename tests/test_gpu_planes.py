@@ -13,7 +13,7 @@ pytestmark = pytest.mark.gpu
 BOUND = TOL["fp32"] / 50        # fp32 sums of a few products a wavefront, added in 64 bits
 
 # (N, C, H, W, K, stride, padding)
-SHAPES = [(100, 61, 5, 5, 65, 1, 1), (200, 41, 2, 3, 70, 1, 1), (21, 130, 7, 9, 129, 1, 1), (40, 66, 8, 8, 300, 2, 0), (130, 33, 13, 13, 71, 1, 1), (47, 131, 16, 16, 128, 1, 1),
+SHAPES = [(100, 61, 5, 5, 65, 1, 1), (200, 41, 2, 3, 70, 1, 1), (21, 130, 7, 9, 129, 1, 1), (40, 66, 8, 8, 300, 2, 0), (160, 33, 13, 13, 71, 1, 1), (47, 131, 16, 16, 128, 1, 1),
           (92, 128, 16, 16, 64, 2, 1), (9, 300, 16, 16, 320, 1, 0), (30, 110, 4, 64, 256, 1, 1), (50, 125, 64, 4, 128, 1, 1), (70, 67, 15, 17, 70, 2, 0)]
 
 
