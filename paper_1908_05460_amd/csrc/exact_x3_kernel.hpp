@@ -11,17 +11,22 @@
 // power of two taken from the largest number of the channel so far: tile by tile the numbers, still in registers, are compared
 // with fp16's range, and where one lies beyond it the channel's scale and the sums so far change to the new one (`rescale`;
 // always in a workgroup's first tile, rarely later).  A number down to 2^-16 of its channel's largest has its 23 bits, a
-// smaller one an error of 2^-39 of that; where a number or an item is below 2^-31 of it the workgroup recomputes as below.
-// What the pieces leave out and what the core rounds inside of products of 22 bits is 1e-7 of a result, whatever the length
-// of its sums, so this is the form of long sums: of the 32-wide tiles (VGG-19's run, N = 128: 4.5e-7 off with bf16 pieces,
-// 3.5e-7; N = 16 to 40: 2.5 -> 2.1e-7) and of 4x4 planes (exact_x3_planes.hip), where it is no further from 64 bits; 16-wide
-// tiles, whose sums are short or kept apart (64 -> 64 @ 8x8, N = 50: 0.86e-7, fp16 pieces 1.1e-7), keep bf16 pieces but for a
-// run's strided and longest ones (exact_x3_mix.hip), with all four products.
-// 64 -> 64 @ 32x32 / 256 -> 256 @ 8x8, N = 128: 62 / 59 us with bf16 pieces, 48 / 45; VGG-19's run 490 -> 342 us.
+// smaller one an error of 2^-39 of that.  That is less than fp32's roundings of a sum that the channel's larger numbers enter, but
+// all there is of one whose larger numbers meet only zeros: such results are found at the end, by their own size (`judge`), looked
+// at more closely, and summed in full (64 -> 64 @ 32x32 / 512 -> 512 @ 4x4, N = 128 / 512, 48 / 101 us: 70 / 126 where the products are
+// so sparse that many results are zero, 4 to 5 times as long where every other image is 2^26 larger and meets zeros).  The product
+// left out is 2^-22 of the whole at most, where every number has the same bits behind its eleventh (all 1 + 2^-11, N = 128: 2.4e-7
+// off, bf16 pieces 1.1 to 2.4e-7).  Of normally distributed numbers what the pieces leave out and what the core rounds inside of
+// products of 22 bits is 1e-7 of a result, whatever the length of its sums, so this is the form of long sums: of the 32-wide tiles
+// (VGG-19's run, N = 128: 4.5e-7 off with bf16 pieces, 2.8e-7; N = 16 to 40: 2.5 -> 2.1e-7) and of 4x4 planes
+// (exact_x3_planes.hip), where it is no further from 64 bits; 16-wide tiles, whose sums are short or kept apart (64 -> 64 @ 8x8,
+// N = 50: 0.86e-7, fp16 pieces 1.1e-7), keep bf16 pieces but for a run's strided and longest ones (exact_x3_mix.hip), with all four
+// products.
+// 64 -> 64 @ 32x32 / 256 -> 256 @ 8x8, N = 128: 62 / 59 us with bf16 pieces, 48 / 44; VGG-19's run 490 -> 342 us.
 //
-// What holds an infinity or a NaN, or numbers too large for the scale of bf16 pieces (beyond 2^111, sums beyond 2^96) or too
-// small beside their channel's largest for fp16's, is recomputed by its workgroup on the fp32 matrix core, from the same
-// tiles: the pieces would make NaNs of infinities.
+// What holds an infinity or a NaN, or numbers too large for the scale of bf16 pieces (beyond 2^111, sums beyond 2^96), or, in fp16
+// pieces, more than a few results of numbers too small beside their channel's largest, is recomputed by its workgroup on the fp32
+// matrix core, from the same tiles: the pieces would make NaNs of infinities.
 //
 // Implicit GEMM, rows = output channels k, columns = (input channel, filter row), reduction = "slots": the columns
 // of X (stride 1) or of one phase of X (column mod stride), eight consecutive slots of one output row being one
@@ -136,13 +141,19 @@ __device__ __forceinline__ void x3_split3(float x0, float x1, float scale, uint3
 }
 
 // fp16 pieces: the power of two that takes a channel's numbers to at most 2^15, given the bits of the largest so far (that to 2^14 at
-// least), and of the channel that has only zeros yet: 2^127 takes every number below 2^-112 there.
+// least; what is below 2^-111 is scaled by 2^126, where fp32's smallest step is one that fp16 has), and kX3Unset for a channel that
+// has only zeros yet.
 constexpr int kX3Unset = 127;
 constexpr uint32_t kX3Finite = 0x7f7fffffu;             // an infinity's channel is scaled like that of the largest number
-__device__ __forceinline__ int x3_exponent(uint32_t top) { const int e = 141 - (int)(top >> 23); return e < kX3Unset ? e : kX3Unset; }
+__device__ __forceinline__ int x3_exponent(uint32_t top) { const int e = 141 - (int)(top >> 23); return top == 0 ? kX3Unset : (e < kX3Unset ? e : kX3Unset - 1); }
 __device__ __forceinline__ float x3_power(int e) { return __uint_as_float((uint32_t)(e + 127) << 23); }
 constexpr float kX3Most = 65504.f;                      // fp16's largest number
-constexpr float kX3Least = 0x1p-17f;                    // (see x3_range)
+
+// What fp16 pieces of scaled numbers leave out: 2^-23 of a number from kX3Whole on, 2^-25 of one below, which from kX3Coarse
+// on is 2^-9 of it at most: no product of such numbers is lost altogether.  Of a sum of n products no more than m 2^-10 is left
+// out that way, m of their 2 n numbers being below kX3Whole: within n roundings of fp32, 2^-24 each, of a sum of m kX3Need / n.
+constexpr float kX3Whole = 0x1p-2f, kX3Coarse = 0x1p-16f, kX3Need = 0x1p14f;
+constexpr int kX3Few = 32;                              // results of a workgroup that are summed by themselves (x3_dot)
 
 // Two fp32 numbers, scaled -> one word (fp16 pair) of each piece.  (v_fma_mixlo_f16, which would scale, subtract and round at
 // once, takes 3.6 ns a SIMD, these 1.2, 1.2, 1.8, 1.9, 1.9 and 1.8.)
@@ -160,26 +171,33 @@ __device__ __forceinline__ void x3_split2(float x0, float x1, float scale, uint3
     l = pk(r0, r1);
 }
 
-// What the items of a thread (runs of numbers of one channel) say about the channels' scales: a number beyond fp16's
-// range, or an item all of whose numbers are so small that their pieces keep less than seven bits.
+// A channel's scale as its items keep it, given the largest number so far: an infinity for the channel that has only zeros yet, whose
+// first other number is then beyond fp16's range (and 0 x infinity, a NaN, is not); and the scale that the split takes.
+__device__ __forceinline__ float x3_scale(uint32_t top) { return top == 0 ? __builtin_inff() : x3_power(x3_exponent(top)); }
+__device__ __forceinline__ float x3_finite(float scale) { return __builtin_amdgcn_fmed3f(scale, -x3_power(kX3Unset), x3_power(kX3Unset)); }
+
+// Whether an item of a thread (a run of numbers of one channel, the largest given) lies beyond fp16's range at its channel's scale.
 struct X3Range {
     float hi = 0.f;
-    uint32_t lo = ~0u;
-    __device__ __forceinline__ void item(float largest, float scale)
-    {
-        const float t = largest * __builtin_fabsf(scale);
-        hi = __builtin_fmaxf(hi, t);
-        const uint32_t b = __float_as_uint(t) - 1u;     // (zeros are no small numbers)
-        lo = b < lo ? b : lo;
-    }
-    template <int N> __device__ __forceinline__ void each(const uint32_t *v, float scale)      // every number an item of its own
-    {
-#pragma unroll
-        for (int i = 0; i < N; ++i) item(__builtin_fabsf(__uint_as_float(v[i])), scale);
-    }
+    __device__ __forceinline__ void item(float largest, float scale) { hi = __builtin_fmaxf(hi, largest * __builtin_fabsf(scale)); }
     __device__ __forceinline__ bool over() const { return hi > kX3Most; }
-    __device__ __forceinline__ bool under() const { return lo < __float_as_uint(kX3Least) - 1u; }
 };
+// N numbers of a channel: how many are not zero and below kX3Whole at its scale, and whether one is below kX3Coarse (bit 31).
+template <int N>
+__device__ __forceinline__ uint32_t x3_small(const uint32_t *v, float scale)
+{
+    const float inverse = __uint_as_float(0x7f000000u - (__float_as_uint(scale) & 0x7fffffffu));     // (a channel of zeros: an infinity)
+    auto twice = [](float x) { return (__float_as_uint(x) << 1) - 2u; };
+    const uint32_t whole = twice(kX3Whole * inverse), coarse = twice(kX3Coarse * inverse);
+    uint32_t n = 0, least = ~0u;
+#pragma unroll
+    for (int i = 0; i < N; ++i) {
+        const uint32_t m = (v[i] - 1u) << 1;            // twice a number's magnitude; most of a zero's
+        n += m < whole;
+        least = m < least ? m : least;
+    }
+    return n | (least < coarse ? 1u << 31 : 0u);
+}
 template <int N>
 __device__ __forceinline__ float x3_largest(const uint32_t *v)
 {
@@ -187,6 +205,28 @@ __device__ __forceinline__ float x3_largest(const uint32_t *v)
 #pragma unroll
     for (int i = 0; i < N; i += 2) m = __builtin_fmaxf(__builtin_fmaxf(m, __builtin_fabsf(__uint_as_float(v[i]))), __builtin_fabsf(__uint_as_float(v[i + 1])));
     return m;
+}
+
+// A wavefront's sum of `count` products of fp32 numbers, in 64 bits; at(e, xi, yi): the places of the e-th, false if there is none
+template <class F>
+__device__ __forceinline__ double x3_dot(const float *X, const float *dY, int count, F at)
+{
+    double sum = 0;
+#pragma unroll 1
+    for (int e0 = threadIdx.x & 63; e0 < count; e0 += 64 * 8) {
+        float x[8], y[8];
+#pragma unroll
+        for (int u = 0; u < 8; ++u) {
+            long xi, yi;
+            const bool live = e0 + 64 * u < count && at(e0 + 64 * u, xi, yi);
+            x[u] = X[live ? xi : 0];
+            y[u] = live ? dY[live ? yi : 0] : 0.f;
+        }
+#pragma unroll
+        for (int u = 0; u < 8; ++u) sum += y[u] == 0.f ? 0. : (double)x[u] * y[u];
+    }
+    for (int d = 32; d > 0; d >>= 1) sum += __shfl_xor(sum, d, 64);
+    return sum;
 }
 
 // v = four columns loaded at a column clamped into the row, d = wanted column - loaded column: the wanted four,
@@ -239,10 +279,12 @@ struct X3Config {
     static constexpr int kScales = HALF ? (DI + XI + (HALO ? 1 : 0)) * kBlock * 4 : 0;      // the scales of every thread's staging items
     static constexpr bool PARK = HALF && HALO && SH == 32 && NTC > 1;     // the items themselves are kept in LDS too
     static constexpr int kItems = PARK ? (DI + XI + 1) * kBlock * 8 : 0;
-    static constexpr int kFix = NCH * 4 + 16 + kTop;                    // the chunk table, flags, the channels' scales
+    static constexpr int NB = HALF ? NTC * S * (SH * SH / 64) : 0, WORDS = (NB + 31) / 32;      // a lane's sums, a bit each
+    static constexpr int kFix = NCH * 4 + 16 + kTop + WORDS * 256;      // the chunk table, flags, the channels' scales, those bits
     static constexpr int kHead = kFix + kScales + kItems;               // ... and what the loop alone needs
     static constexpr int kTail = NW * NTC * S * SH * SH * 2;            // the final exchange: half of every wavefront's sums
-    static constexpr int kLds = kHead + kBuf > kFix + kTail ? kHead + kBuf : kFix + kTail;
+    static constexpr int kCounts = HALF ? 2 * (SH + CH) * 4 + WORDS * 256 : 0;      // the second look at a workgroup's numbers (behind the tile, whose zeros stay)
+    static constexpr int kLds = kHead + kBuf + kCounts > kFix + kTail ? kHead + kBuf + kCounts : kFix + kTail;
 };
 
 template <class T>
@@ -270,6 +312,8 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     uint32_t *const over = flag + 1;                         // set when a tile's numbers ask for smaller scales
     uint32_t *const top = flag + 4;                          // per channel of dY [SH] and X [CH]: bits of the largest number so far
     int *const expo = (int *)(top + SH + T::CH);             // ... and the exponent of its scale
+    constexpr int NB = T::NB, WORDS = T::WORDS;
+    uint32_t *const mark = (uint32_t *)(smem + T::kFix - WORDS * 256);      // [WORDS][64]: whether a sum is known to be well held (`judge`)
     // Per staging item of a thread, the scale of its channel; PARK: what is known of the item.  (In registers these would be
     // what spills, and a reload among the loads of a tile waits for all of those: 64 -> 64 @ 224x224, N = 4, 82 us
     // against 79.)
@@ -462,7 +506,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         X3Range r;
 #pragma unroll
         for (int u = 0; u < DI; ++u) r.item(x3_largest<8>(dr[u]), scale_at(u));
-        if (HALO && p.halo) r.hi = __builtin_fmaxf(r.hi, x3_largest<2>(hr) * __builtin_fabsf(scale_at(DI + XI)));
+        if (HALO && p.halo) r.item(x3_largest<2>(hr), scale_at(DI + XI));
 #pragma unroll
         for (int u = 0; u < XI; ++u) r.item(x3_largest<8 * SW>(xr[u]), scale_at(DI + u));
         return r;
@@ -525,7 +569,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             }
             if (at != ~0u) {
                 if constexpr (DR == 4) *(x3_u4 *)(buf + kDyAt + at_dst(at)) = x3_u4{dr[u][0], dr[u][1], dr[u][2], dr[u][3]};
-                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, HALF ? scale_at(u) : dy_scale, lo, hi, plain);
+                else put([&](int e) { return elem(dr[u], e); }, buf + kDyAt + at_dst(at), dy_piece, HALF ? x3_finite(scale_at(u)) : dy_scale, lo, hi, plain);
             }
         }
         if (HALO && p.halo) {
@@ -537,7 +581,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             } else {
                 uint32_t w[3];
                 if constexpr (BF) w[0] = hr[0] | hr[1] << 16;
-                else if constexpr (HALF) x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), scale_at(DI + XI), w[0], w[1]);
+                else if constexpr (HALF) x3_split2(__uint_as_float(hr[0]), __uint_as_float(hr[1]), x3_finite(scale_at(DI + XI)), w[0], w[1]);
                 else x3_split3(__uint_as_float(hr[0]), __uint_as_float(hr[1]), dy_scale, w[0], w[1], w[2]);
 #pragma unroll
                 for (int q = 0; q < NP; ++q) *(uint32_t *)(chunk + (at_wc(at) ? 0 : 12) + q * dy_piece) = w[q];
@@ -562,7 +606,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 else {
 #pragma unroll
                     for (int f = 0; f < SW; ++f)
-                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, HALF ? scale_at(DI + u) : kX3Scale, lo, hi, plain);
+                        put([&](int e) { return elem(xr[u], e * SW + f); }, buf + kXAt + at_dst(at) + f * p.twc * 16, x_piece, HALF ? x3_finite(scale_at(DI + u)) : kX3Scale, lo, hi, plain);
                 }
             }
         }
@@ -587,8 +631,9 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     if (tid == 0) *flag = *over = 0;
     if constexpr (HALF) {
         if (tid < SH + T::CH) { top[tid] = 0; expo[tid] = kX3Unset; }
+        for (int e = tid; e < WORDS * 64; e += NTHR) mark[e] = 0;
 #pragma unroll
-        for (int u = 0; u < DI + XI + (HALO ? 1 : 0); ++u) scale_at(u) = x3_power(kX3Unset);
+        for (int u = 0; u < DI + XI + (HALO ? 1 : 0); ++u) scale_at(u) = __builtin_inff();
     }
     for (int e = tid; e < NP * SH; e += NTHR) *(x3_u4 *)(buf + kDyAt + (e * KP + KP - 1) * 16) = x3_u4{0u, 0u, 0u, 0u};
     if (k0 + SH > g.K || c_first + T::CH > g.C) {
@@ -637,34 +682,39 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         coloff[t] = c_l * CP * 16 + r * row_bytes;
     }
     const char *const a_row = buf + kDyAt + i * KP * 16, *const Xs = buf + kXAt;
+    // the rows of `top` that the thread's staging items belong to (items that there are not load zeros)
+    auto item_rows = [&](uint32_t (&row)[DI + XI + 1]) {
+        uint32_t rem;
+#pragma unroll
+        for (int u = 0; u < DI; ++u) {
+            p.d_nch.divmod(tid + u * NTHR, row[u], rem);
+            if (item(u, d_at[u], d_off[u]).x == ~0u) row[u] = 0;
+        }
+#pragma unroll
+        for (int u = 0; u < XI; ++u) {
+            p.d_xrow.divmod(tid + u * NTHR, row[DI + u], rem);
+            row[DI + u] = item(DI + u, x_at[u], x_off[u]).x == ~0u ? SH : SH + row[DI + u];
+        }
+        row[DI + XI] = 0;
+        if (HALO && p.halo && item(DI + XI, h_at, h_off).x != ~0u) p.d_rows.divmod(tid >> 1, row[DI + XI], rem);
+    };
     // A tile has a number beyond fp16's range at the scale of its channel (in a workgroup's first tile they all do): scales
     // for the largest numbers so far, and the sums so far in units of them.
     auto rescale = [&](bool sums) {
         auto note = [&](int row, const float m) {
             if (m > 0.f) { const uint32_t b = __float_as_uint(m); atomicMax(top + row, b < kX3Finite ? b : kX3Finite); }
         };
-        uint32_t row[DI + XI + 1], rem;
+        uint32_t row[DI + XI + 1];
+        item_rows(row);
 #pragma unroll
-        for (int u = 0; u < DI; ++u) {
-            p.d_nch.divmod(tid + u * NTHR, row[u], rem);
-            if (item(u, d_at[u], d_off[u]).x == ~0u) row[u] = 0;
-            note((int)row[u], x3_largest<8>(dr[u]));
-        }
+        for (int u = 0; u < DI; ++u) note((int)row[u], x3_largest<8>(dr[u]));
 #pragma unroll
-        for (int u = 0; u < XI; ++u) {
-            p.d_xrow.divmod(tid + u * NTHR, row[DI + u], rem);
-            row[DI + u] = item(DI + u, x_at[u], x_off[u]).x == ~0u ? SH : SH + row[DI + u];
-            note((int)row[DI + u], x3_largest<8 * SW>(xr[u]));
-        }
-        row[DI + XI] = 0;
-        if (HALO && p.halo) {
-            if (item(DI + XI, h_at, h_off).x != ~0u) p.d_rows.divmod(tid >> 1, row[DI + XI], rem);
-            note((int)row[DI + XI], x3_largest<2>(hr));
-        }
+        for (int u = 0; u < XI; ++u) note((int)row[DI + u], x3_largest<8 * SW>(xr[u]));
+        if (HALO && p.halo) note((int)row[DI + XI], x3_largest<2>(hr));
         __syncthreads();
 #pragma unroll
         for (int u = 0; u < DI + XI + (HALO ? 1 : 0); ++u)
-            scale_at(u) = (u < DI || u == DI + XI ? sign : 1.f) * x3_power(x3_exponent(top[row[u]]));
+            scale_at(u) = (u < DI || u == DI + XI ? sign : 1.f) * x3_scale(top[row[u]]);
         if (sums) {
             auto change = [&](int row) { return x3_exponent(top[row]) - expo[row]; };
 #pragma unroll
@@ -681,22 +731,13 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
                 }
             }
         }
-        // (a number that sets a scale hides what is small beside it in its item: here each is looked at by itself)
-        X3Range r;
-#pragma unroll
-        for (int u = 0; u < DI; ++u) r.each<8>(dr[u], scale_at(u));
-#pragma unroll
-        for (int u = 0; u < XI; ++u) r.each<8 * SW>(xr[u], scale_at(DI + u));
-        if (r.under()) *flag = 1;
         __syncthreads();
         if (tid < SH + T::CH) expo[tid] = x3_exponent(top[tid]);
         if (tid == 0) *over = 0;
     };
     for (int wt = wt_begin; wt < wt_end; ++wt) {
         if constexpr (HALF) {
-            const X3Range r = range();
-            if (r.over()) *over = 1;
-            if (r.under()) *flag = 1;
+            if (range().over()) *over = 1;
         }
         if (HALF || wt != wt_begin) __syncthreads();    // everyone has left the previous tile
         if constexpr (HALF)
@@ -799,10 +840,139 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             for (int v = 0; v < AV; ++v) worst[v & 3] = fmaf(acc[t][s][v], 0.f, worst[v & 3]);
     const float any = (worst[0] + worst[1]) + (worst[2] + worst[3]);
     if (any != any) *flag = 1;
+    // fp16 pieces: numbers far below their channel's largest lose bits, which is nothing to a sum that larger ones enter, and
+    // all to one whose larger ones meet only zeros.  Each wavefront's sum of a result's products is at most what the products'
+    // magnitudes add up to: a result is well held if one of the four is large beside what the pieces can have left out of a sum of
+    // that many products (channels of zeros need nothing).  A bit a result, set by judge, which shifts in the sign of
+    // beyond(sum, its row's word of `of`, its column's): of normally distributed numbers, ReLU's zeros among them, no workgroup in
+    // 10^4 has a result without one.
+    [[maybe_unused]] auto judge = [&](uint32_t (&good)[WORDS > 0 ? WORDS : 1], const uint32_t *of, auto beyond) {
+        uint32_t nc[NTC];
+        x3_u4 nk[AV / 4];
+#pragma unroll
+        for (int t = 0; t < NTC; ++t) {
+            int c_l, r;
+            column(t, i, c_l, r);
+            nc[t] = of[SH + c_l];
+        }
+#pragma unroll
+        for (int v = 0; v < AV / 4; ++v) nk[v] = *(const x3_u4 *)(of + (SH == 32 ? 8 * v : 0) + 4 * kk);
+#pragma unroll
+        for (int v = 0; v < AV; ++v)
+#pragma unroll
+            for (int t = 0; t < NTC; ++t)
+#pragma unroll
+                for (int s = 0; s < S; ++s) {
+                    uint32_t &w = good[((v * NTC + t) * S + s) / 32];
+                    w = __builtin_amdgcn_alignbit(w, __float_as_uint(beyond(__builtin_fabsf(acc[t][s][v]), nk[v / 4][v % 4], nc[t])), 31);
+                }
+    };
+    auto bits = [](int w) { return NB - 32 * w < 32 ? (1u << (NB - 32 * w)) - 1u : ~0u; };        // those of a word
+    if constexpr (HALF) {
+        uint32_t good[WORDS] = {};
+        judge(good, top, [](float sum, uint32_t row, uint32_t) { return (row == 0 ? -1.f : 2.f * kX3Need) - sum; });
+#pragma unroll
+        for (int t = 0; t < NTC; ++t) {
+            int c_l, r;
+            column(t, i, c_l, r);
+            uint32_t of[WORDS] = {};                        // bits of this column
+#pragma unroll
+            for (int e = 0; e < NB; ++e)
+                if (e / S % NTC == t) of[e / 32] |= 1u << ((NB - e / 32 * 32 < 32 ? NB - e / 32 * 32 : 32) - 1 - e % 32);
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) good[w] |= top[SH + c_l] == 0 ? of[w] : 0u;
+        }
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) atomicOr(mark + w * 64 + lane, good[w]);
+    }
     __syncthreads();
-    bool scaled = HALF;
+    bool scaled = HALF, again = *(volatile uint32_t *)flag;
     float unscale = KIND == kX3Three ? sign * kX3Unscale : 1.f;
-    if (*(volatile uint32_t *)flag) {
+    // a result by its bit's number and lane
+    struct Result { int k, c, r, s, row, lc; };
+    auto result = [&](uint32_t id) {
+        const int v = (int)(id >> 8) / (NTC * S), t = (int)(id >> 8) / S % NTC, s = (int)(id >> 8) % S, i = id & (SH - 1), kk = (int)(id & 63) / SH;
+        const int row = SH == 32 ? 8 * (v / 4) + 4 * kk + v % 4 : 4 * kk + v;
+        int c_l, r;
+        column(t, i, c_l, r);
+        return Result{k0 + row, c_first + c_l, r, s, row, (p.packed ? t * SH + i : i * R + t) * S + s};
+    };
+    int few = 0;
+    if constexpr (HALF) {
+        bool doubt = false;
+#pragma unroll
+        for (int w = 0; w < WORDS; ++w) doubt = doubt || mark[w * 64 + lane] != bits(w);
+        if (!again && __any(doubt)) {
+            // The numbers once more, to count in each channel those that lose bits: a result is well held, too, if a sum is large beside
+            // what so many can have lost, or if all are 0 and no number is so small that a product may have gone.
+            uint32_t *const count = (uint32_t *)(buf + T::kBuf), *const tiny = count + SH + T::CH, *const some = tiny + SH + T::CH;     // some: [WORDS][64]
+            for (int e = tid; e < T::kCounts / 4; e += NTHR) count[e] = 0;
+            uint32_t row[DI + XI + 1];
+            item_rows(row);
+            __syncthreads();
+            auto note = [&](uint32_t row, uint32_t small) {
+                if (small & 0x7fffffffu) atomicAdd(count + row, small & 0x7fffffffu);
+                if (small >> 31) tiny[row] = 1;
+            };
+#pragma unroll 1
+            for (int wt = wt_begin; wt < wt_end; ++wt) {
+                load_tile(wt);
+#pragma unroll
+                for (int u = 0; u < DI; ++u) note(row[u], x3_small<8>(dr[u], scale_at(u)));
+#pragma unroll
+                for (int u = 0; u < XI; ++u) note(row[DI + u], x3_small<8 * SW>(xr[u], scale_at(DI + u)));
+                if (HALO && p.halo) note(row[DI + XI], x3_small<2>(hr, scale_at(DI + XI)));
+            }
+            __syncthreads();
+            uint32_t good[WORDS] = {}, held[WORDS] = {};
+            const float one = kX3Need / (float)(p.nch * 8 * (wt_end - wt_begin));
+            judge(good, count, [&](float sum, uint32_t row, uint32_t col) { return one * (float)(row + col) - sum; });
+            judge(held, tiny, [](float sum, uint32_t row, uint32_t col) { return 0.f - ((float)(row + col) + sum); });
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) {
+                atomicOr(mark + w * 64 + lane, good[w]);
+                atomicOr(some + w * 64 + lane, held[w]);
+            }
+            __syncthreads();
+            // A few that are left (sums that happen to be small, as one in 2^10 of few products is) are summed by themselves, a
+            // wavefront to each.  mark: their number, the results, the sums.
+            uint32_t left[WORDS];
+#pragma unroll
+            for (int w = 0; w < WORDS; ++w) left[w] = some[w * 64 + lane] & ~mark[w * 64 + lane];
+            __syncthreads();
+            if (tid == 0) mark[0] = 0;
+            __syncthreads();
+            if (wq == 0)
+#pragma unroll
+                for (int w = 0; w < WORDS; ++w)
+                    for (uint32_t rest = left[w]; rest; rest &= rest - 1) {
+                        const uint32_t at = atomicAdd(mark, 1u), bit = (NB - 32 * w < 32 ? NB - 32 * w : 32) - 1 - __builtin_ctz(rest);
+                        if (at < (uint32_t)kX3Few) mark[1 + at] = (32 * w + bit) << 8 | (uint32_t)lane;
+                    }
+            __syncthreads();
+            again = mark[0] > (uint32_t)kX3Few;
+            few = again ? 0 : (int)mark[0];
+            for (int e = wq; e < few; e += NW) {
+                const Result q = result(mark[1 + e]);
+                const int shift = x3_shift(q.s, S, SW);
+                const double sum = q.k >= g.K || q.c >= g.C ? 0. : x3_dot((const float *)Xp, (const float *)dYp, p.nch * 8 * (wt_end - wt_begin), [&](int at, long &xi, long &yi) {
+                    uint32_t wt, chk, row, wc, n_l, h_l;
+                    p.d_nch.divmod((uint32_t)at >> 3, wt, chk);
+                    p.d_twc.divmod(chk, row, wc);
+                    p.d_ht.divmod(row, n_l, h_l);
+                    const Tile t = tile_of(wt_begin + (int)wt);
+                    const int n = t.n0 + (int)n_l, h = t.h0 + (int)h_l, w = (t.wc0 + (int)wc) * 8 + (at & 7) + p.vlo - shift;
+                    const int ih = h * g.sh + q.r - g.ph, iw = w * g.sw + q.s - g.pw;
+                    xi = (((long)n * g.C + q.c) * g.H + ih) * g.W + iw;
+                    yi = (((long)n * g.K + q.k) * g.Ho + h) * g.Wo + w;
+                    return n < g.N && h < g.Ho && (unsigned)w < (unsigned)g.Wo && (unsigned)ih < (unsigned)g.H && (unsigned)iw < (unsigned)g.W;
+                });
+                if (lane == 0) mark[1 + kX3Few + e] = __float_as_uint((float)sum);
+            }
+            __syncthreads();
+        }
+    }
+    if (again) {
         // Once more on the fp32 matrix core, with the tiles' numbers as they are: a lane's chunk goes through it column by
         // column, dY's own eight and the two on each side, each with the X of its tap's slot.  X counts only where that
         // column of dY exists (an infinity of X is no product of a row's end), and a column whose slot lies before the
@@ -944,6 +1114,11 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
         const int lc = (p.packed ? t * SH + i : i * R + t) * S + s;
 #pragma unroll
         for (int v = 0; v < Q; ++v) rows[(Q * kk + v) * COLS + lc] = z[v];
+    }
+    if (HALF && lane < few) {
+        const Result q = result(mark[1 + lane]);
+        const int r = SH == 32 ? q.row - 8 * part : q.row / 4;
+        if (SH == 32 ? q.row / 8 == part : q.row % 4 == part) rows[r * COLS + q.lc] = __uint_as_float(mark[1 + kX3Few + lane]);
     }
     const int j0 = (p.packed ? (int)coltile * NTC * SH : c_first * R) * S;
     const int cols = p.packed ? COLS : SH * R * S, n = CRS - j0 < cols ? CRS - j0 : cols;

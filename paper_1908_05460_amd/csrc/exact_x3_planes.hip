@@ -35,7 +35,8 @@ struct PlaneCfg {
     static constexpr int kA = U * kPK * 16, kB = U * kPC * 16;          // bytes of one piece
     static constexpr bool HALF = KIND == kX3Half;
     static constexpr int NP = HALF ? 2 : 3;                             // pieces of a number
-    static constexpr int kHead = 16 + (HALF ? (kPK + kPC) * 8 : 0);     // flags; the channels' largest numbers and scales
+    static constexpr int kMark = HALF ? 4 * kBlock * 4 : 0;             // a bit for each of a thread's results
+    static constexpr int kHead = 16 + (HALF ? (kPK + kPC) * 8 : 0) + kMark;     // flags; the channels' largest numbers and scales; those bits
     static constexpr int kLds = kHead + NP * (kA + kB);
 };
 
@@ -163,7 +164,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     const int tid = threadIdx.x, lane = tid & 63;
     const int i = lane & 31, kk = lane >> 5;
     uint32_t *const flag = (uint32_t *)smem;
-    uint32_t *const over = flag + 1, *const top = flag + 4;             // (see exact_x3_kernel.hpp; dY's channels, then X's)
+    uint32_t *const over = flag + 1, *const asked = flag + 2, *const top = flag + 4;             // (see exact_x3_kernel.hpp; dY's channels, then X's)
     int *const expo = (int *)(top + kPK + kPC);
     char *const As = smem + C::kHead, *const Bs = As + C::NP * C::kA;
 
@@ -219,7 +220,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     };
     float scale[SETS];
 #pragma unroll
-    for (int u = 0; u < SETS; ++u) scale[u] = x3_power(kX3Unset);
+    for (int u = 0; u < SETS; ++u) scale[u] = __builtin_inff();
     auto largest = [&](auto &reg, auto words) {
         float m = 0.f;
 #pragma unroll
@@ -234,6 +235,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
             constexpr int NW = decltype(words)::value;                  // words of a piece: pairs of images
             if (dst[u] == ~0u) return;
             const int rows = is_a[u] ? kPK : kPC, piece = is_a[u] ? C::kA : C::kB;
+            const float by = (is_a[u] ? sign : 1.f) * x3_finite(scale[u]);
             if constexpr (decltype(plain)::value) {
                 const int half = NW == 2 ? first[u] / 4 : 0;            // an item of four images is the first or the second four
 #pragma unroll
@@ -251,7 +253,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
                     for (int e = 0; e < NW; ++e) {
                         const float x0 = __uint_as_float(reg[2 * e][q]), x1 = __uint_as_float(reg[2 * e + 1][q]);
                         uint32_t x, y, z;
-                        if constexpr (C::HALF) x3_split2(x0, x1, is_a[u] ? sign * scale[u] : scale[u], x, y);
+                        if constexpr (C::HALF) x3_split2(x0, x1, by, x, y);
                         else x3_split3(x0, x1, kX3Scale, x, y, z);
                         w[0][e] = x; w[1][e] = y;
                         if constexpr (!C::HALF) w[2][e] = z;
@@ -266,9 +268,11 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     };
 
     load(st_begin);
-    if (tid == 0) *flag = *over = 0;
+    if (tid == 0) *flag = *over = *asked = 0;
     if constexpr (C::HALF) {
         if (tid < kPK + kPC) { top[tid] = 0; expo[tid] = kX3Unset; }
+#pragma unroll
+        for (int t = 0; t < R::NT; ++t) ((uint32_t *)(smem + C::kHead - C::kMark))[t * kBlock + tid] = 0;
         __syncthreads();
     }
     x3_f16 acc[R::NT][2];
@@ -282,42 +286,62 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     };
     clear();
     const char *const a0 = As + i * 16, *const b0 = Bs + i * 16;
+    // Whether a result is known to be well held, a bit each (see exact_x3_kernel.hpp).  Here a wavefront has all of a result's products:
+    // it looks at the sums after half of its stages, too.
+    uint32_t *const mark = (uint32_t *)(smem + C::kHead - C::kMark);
+    auto good = [&](int t) -> uint32_t & { return mark[t * kBlock + tid]; };
+    auto judge = [&](uint32_t (&good)[R::NT], const uint32_t *of, auto beyond) {
+        const uint32_t nc = of[kPK + i];
+#pragma unroll
+        for (int m = 0; m < 2; ++m) {
+            x3_u4 nk[4];
+#pragma unroll
+            for (int v = 0; v < 4; ++v) nk[v] = *(const x3_u4 *)(of + m * 32 + 8 * v + 4 * kk);
+#pragma unroll
+            for (int v = 0; v < 16; ++v)
+#pragma unroll
+                for (int t = 0; t < R::NT; ++t)
+                    good[t] = __builtin_amdgcn_alignbit(good[t], __float_as_uint(beyond(__builtin_fabsf(acc[t][m][v]), nk[v / 4][v % 4], nc)), 31);
+        }
+    };
+    auto look = [&]() {
+        uint32_t now[R::NT] = {};
+        judge(now, top, [](float sum, uint32_t row, uint32_t) { return (row == 0 ? -1.f : 2.f * kX3Need) - sum; });
+        const uint32_t none = top[kPK + i] == 0 ? ~0u : 0u;
+#pragma unroll
+        for (int t = 0; t < R::NT; ++t) good(t) |= now[t] | none;
+    };
     auto rescale = [&](float m0, float m1, bool sums) {                // (see exact_x3_kernel.hpp)
-                    auto note = [&](int u, float m) {
-                        if (m > 0.f) { const uint32_t b = __float_as_uint(m); atomicMax(top + chan[u], b < kX3Finite ? b : kX3Finite); }
-                    };
-                    note(0, m0);
-                    if constexpr (SETS > 1) note(1, m1);
-                    __syncthreads();
-                    X3Range r;
-        #pragma unroll
-                    for (int u = 0; u < SETS; ++u) scale[u] = x3_power(x3_exponent(top[chan[u]]));
-        #pragma unroll
-                    for (int j = 0; j < 8; ++j)
-        #pragma unroll
-                        for (int q = 0; q < 4; ++q) r.item(__builtin_fabsf(__uint_as_float(reg0[j][q])), scale[0]);
-                    if constexpr (SETS > 1)
-        #pragma unroll
-                        for (int j = 0; j < 4; ++j)
-        #pragma unroll
-                            for (int q = 0; q < 4; ++q) r.item(__builtin_fabsf(__uint_as_float(reg1[j][q])), scale[1]);
-                    if (r.under()) *flag = 1;
-                    if (sums) {
-                        auto change = [&](int row) { return x3_exponent(top[row]) - expo[row]; };
-                        const int dc = change(kPK + i);
-        #pragma unroll
-                        for (int m = 0; m < 2; ++m)
-        #pragma unroll
-                            for (int v = 0; v < 16; ++v) {
-                                const int d = dc + change(m * 32 + 8 * (v / 4) + 4 * kk + v % 4);
-        #pragma unroll
-                                for (int t = 0; t < R::NT; ++t) acc[t][m][v] = __builtin_ldexpf(acc[t][m][v], d);
-                                __builtin_amdgcn_sched_barrier(0);
-                            }
-                    }
-                    __syncthreads();
-                    if (tid < kPK + kPC) expo[tid] = x3_exponent(top[tid]);
-                    if (tid == 0) *over = 0;
+        auto note = [&](int u, float m) {
+            if (m > 0.f) { const uint32_t b = __float_as_uint(m); atomicMax(top + chan[u], b < kX3Finite ? b : kX3Finite); }
+        };
+        note(0, m0);
+        if constexpr (SETS > 1) note(1, m1);
+        __syncthreads();
+#pragma unroll
+        for (int u = 0; u < SETS; ++u) scale[u] = x3_scale(top[chan[u]]);
+        if (sums) {
+            auto change = [&](int row) { return x3_exponent(top[row]) - expo[row]; };
+            const int dc = change(kPK + i);
+            uint32_t changed = 0;
+#pragma unroll
+            for (int m = 0; m < 2; ++m)
+#pragma unroll
+                for (int v = 0; v < 16; ++v) {
+                    const int d = dc + change(m * 32 + 8 * (v / 4) + 4 * kk + v % 4);
+#pragma unroll
+                    for (int t = 0; t < R::NT; ++t) acc[t][m][v] = __builtin_ldexpf(acc[t][m][v], d);
+                    changed = changed << 1 | (d != 0);
+                    __builtin_amdgcn_sched_barrier(0);
+                }
+            // (what was large may be small in the new units)
+#pragma unroll
+            for (int t = 0; t < R::NT; ++t) good(t) &= ~changed;
+            look();
+        }
+        __syncthreads();
+        if (tid < kPK + kPC) expo[tid] = x3_exponent(top[tid]);
+        if (tid == 0) *over = 0;
     };
     for (int st = st_begin; st < st_end; ++st) {
         if constexpr (C::HALF) {
@@ -326,7 +350,6 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
             r.item(m0, scale[0]);
             if constexpr (SETS > 1) r.item(m1, scale[1]);
             if (r.over()) *over = 1;
-            if (r.under()) *flag = 1;
             __syncthreads();
             if (*(volatile uint32_t *)over) rescale(m0, m1, st != st_begin);
         } else if (st != st_begin) __syncthreads();
@@ -339,6 +362,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
         x3_f16 part[2];
         R::template steps<0, 0>(acc, part, a0, b0, kk, C::HALF && st & 1 ? -1.f : 1.f);
         __builtin_amdgcn_sched_barrier(0);
+        if (C::HALF && st + 1 == (st_begin + st_end) / 2) look();
     }
     float worst = 0.f;
 #pragma unroll
@@ -348,9 +372,77 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
 #pragma unroll
             for (int v = 0; v < 16; ++v) worst = fmaf(acc[t][m][v], 0.f, worst);
     if (worst != worst) *flag = 1;
+    if constexpr (C::HALF) {
+        look();
+        bool doubt = false;
+#pragma unroll
+        for (int t = 0; t < R::NT; ++t) doubt = doubt || ~good(t);
+        if (doubt) *asked = 1;
+    }
     __syncthreads();
     bool scaled = C::HALF;
+    int few = 0;
     float unscale = C::HALF ? 1.f : kX3Unscale;
+    if constexpr (C::HALF) {
+        if (!*(volatile uint32_t *)flag && *(volatile uint32_t *)asked) {       // (see exact_x3_kernel.hpp)
+            uint32_t *const count = (uint32_t *)As, *const tiny = count + kPK + kPC;
+            for (int e = tid; e < 2 * (kPK + kPC); e += kBlock) count[e] = 0;
+            int again = tid;
+            asm volatile("" : "+v"(again));
+            items(again);
+            __syncthreads();
+            auto note = [&](int u, uint32_t small) {
+                if (small & 0x7fffffffu) atomicAdd(count + chan[u], small & 0x7fffffffu);
+                if (small >> 31) tiny[chan[u]] = 1;
+            };
+#pragma unroll 1
+            for (int st = st_begin; st < st_end; ++st) {
+                load(st);
+#pragma unroll
+                for (int j = 0; j < 8; ++j) {
+                    const uint32_t v[4] = {reg0[j][0], reg0[j][1], reg0[j][2], reg0[j][3]};
+                    note(0, x3_small<4>(v, scale[0]));
+                }
+                if constexpr (SETS > 1)
+#pragma unroll
+                    for (int j = 0; j < 4; ++j) {
+                        const uint32_t v[4] = {reg1[j][0], reg1[j][1], reg1[j][2], reg1[j][3]};
+                        note(1, x3_small<4>(v, scale[1]));
+                    }
+            }
+            __syncthreads();
+            uint32_t held[R::NT] = {}, now[R::NT] = {};
+            const float one = kX3Need / (float)(C::IMG * C::P * (st_end - st_begin));
+            judge(now, count, [&](float sum, uint32_t row, uint32_t col) { return one * (float)(row + col) - sum; });
+            judge(held, tiny, [](float sum, uint32_t row, uint32_t col) { return 0.f - ((float)(row + col) + sum); });
+#pragma unroll
+            for (int t = 0; t < R::NT; ++t) held[t] &= ~(good(t) | now[t]);
+            __syncthreads();
+            if (tid == 0) mark[0] = 0;
+            __syncthreads();
+#pragma unroll
+            for (int t = 0; t < R::NT; ++t)
+                for (uint32_t rest = held[t]; rest; rest &= rest - 1) {
+                    const uint32_t at = atomicAdd(mark, 1u), bit = 31 - __builtin_ctz(rest);        // m * 16 + v
+                    if (at < (uint32_t)kX3Few) mark[1 + at] = (uint32_t)role_taps<HW>(ROLE, t) << 16 | (uint32_t)i << 8 | (bit / 4 * 8 + 4 * kk + bit % 4);
+                }
+            __syncthreads();
+            few = mark[0] > (uint32_t)kX3Few ? 0 : (int)mark[0];
+            if (mark[0] > (uint32_t)kX3Few) *flag = 1;
+            for (int e = tid >> 6; e < few; e += kBlock / 64) {
+                const uint32_t id = mark[1 + e];
+                const int k = k0 + (int)(id & 255), c = c0 + (int)(id >> 8 & 255), tap = id >> 16;
+                const double sum = k >= g.K || c >= g.C ? 0. : x3_dot(Xp, dYp, C::IMG * C::P * (st_end - st_begin), [&](int at, long &xi, long &yi) {
+                    const int n = st_begin * C::IMG + at / C::P, pos = at % C::P, h = pos / HW + tap / 3 - 1, w = pos % HW + tap % 3 - 1;
+                    xi = ((long)n * g.C + c) * C::P + h * HW + w;
+                    yi = ((long)n * g.K + k) * C::P + pos;
+                    return n < g.N && (unsigned)h < (unsigned)HW && (unsigned)w < (unsigned)HW;
+                });
+                if (lane == 0) mark[1 + kX3Few + e] = __float_as_uint((float)sum);
+            }
+            __syncthreads();
+        }
+    }
     if (*(volatile uint32_t *)flag) {                                  // (see exact_x3_kernel.hpp)
         scaled = false;
         unscale = 1.f;
@@ -386,6 +478,11 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
                 rows[row * PITCH + i * 9 + role_taps<HW>(ROLE, t)] = z;
             }
         __syncthreads();
+        if (few > 0) {
+            const uint32_t id = mark[1 + (tid < few ? tid : 0)];
+            if (tid < few && (int)(id & 255) / 32 == m) rows[(id & 31) * PITCH + (id >> 8 & 255) * 9 + (id >> 16)] = __uint_as_float(mark[1 + kX3Few + tid]);
+            __syncthreads();
+        }
         const int kb = k0 + m * 32;
         if (n == Q && kb + 32 <= g.K && CRS % 4 == 0 && ((uintptr_t)out & 15) == 0) {
 #pragma unroll
@@ -429,15 +526,16 @@ __global__ __launch_bounds__(kBlock, 2) void wgrad_exact_x3_planes(const X3Multi
 
 }  // namespace
 
-int x3_planes_lds(int hw)
+template <int HW, int KIND> constexpr int planes_lds()
 {
-    const int tail = PlaneCfg<4, kX3Half>::kHead + 32 * (kPC * 9 + 4) * 4, stage = hw == 4 ? PlaneCfg<4, kX3Three>::kLds : PlaneCfg<2, kX3Three>::kLds;
+    constexpr int tail = PlaneCfg<HW, KIND>::kHead + 32 * (kPC * 9 + 4) * 4, stage = PlaneCfg<HW, KIND>::kLds;
     return stage > tail ? stage : tail;
 }
+int x3_planes_lds(int hw) { return hw == 4 ? planes_lds<4, kX3Three>() : planes_lds<2, kX3Three>(); }
 int x3_launch_planes(int hw, bool half, const X3Multi &m, int blocks, size_t lds, hipStream_t st)
 {
     if (hw == 2) return x3_launch(wgrad_exact_x3_planes<2, kX3Three>, m, blocks, lds, st);
-    return half ? x3_launch(wgrad_exact_x3_planes<4, kX3Half>, m, blocks, lds, st) : x3_launch(wgrad_exact_x3_planes<4, kX3Three>, m, blocks, lds, st);
+    return half ? x3_launch(wgrad_exact_x3_planes<4, kX3Half>, m, blocks, (size_t)planes_lds<4, kX3Half>(), st) : x3_launch(wgrad_exact_x3_planes<4, kX3Three>, m, blocks, lds, st);
 }
 
 }  // namespace wgrad

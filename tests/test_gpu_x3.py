@@ -198,8 +198,8 @@ def test_rows_of_padding_behind_the_last_plane(t, dtype):
 
 
 def test_wide_range_of_magnitudes_within_a_tensor():
-    """Elements of 2^-40 .. 2^40 side by side: every product keeps fp32's relative precision, so an output channel of
-    small gradients is as exact as one of large ones."""
+    """Output channels of 2^-40 .. 2^40 side by side, each of them uniform (16-wide tiles in bf16 pieces): one of small gradients is as
+    exact as one of large ones.  Magnitudes that differ within a channel: test_small_numbers_beside_large_ones_that_meet_zeros."""
     d = mk((4, 32, 12, 12, 64, 3, 3, 1, 1, 1, 1))
     X, dY = rand_inputs(d, 13)
     dY *= np.exp2(np.linspace(-40, 40, d.K)).astype(np.float32)[None, :, None, None]
@@ -313,8 +313,47 @@ def test_scales_of_fp16_pieces(t, how):
             assert normwise_err(got[k], want[k]) < TOL["fp32"] / 25
 
 
+@pytest.mark.parametrize("t", HALVES)
+@pytest.mark.parametrize("where, factor", [("images", f) for f in (14, 18, 22, 26, 30, 40, 66)] + [("columns", f) for f in (22, 40, 66)])
+def test_small_numbers_beside_large_ones_that_meet_zeros(t, where, factor):
+    """Every other image of dY, or its first column, is 2^factor times the rest and meets only zeros of X: the result consists of numbers
+    far below their channel's largest, in which an fp16 piece has few bits left or none, and is as exact as without the others."""
+    d = mk(t)
+    X, dY = rand_inputs(d, 29)
+    if where == "images":
+        X[::2] = 0
+        dY[::2] *= np.float32(2.0 ** factor)
+    else:
+        X[..., :max(0, d.S - d.pad_w)] = 0
+        dY[..., 0] *= np.float32(2.0 ** factor)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    for k in range(d.K):
+        assert normwise_err(got[k], want[k]) < TOL["fp32"] / 50
+
+
+@pytest.mark.parametrize("t", HALVES)
+def test_single_results_of_small_numbers(t):
+    """Channels of X that are zero but for one number, whose partner in a few channels of dY is far below those channels' largest: a few
+    results of a workgroup consist of such a product alone, and are as exact as any."""
+    d = mk(t)
+    X, dY = rand_inputs(d, 37)
+    n, h, w = d.N - 1, d.Ho - 1, d.Wo // 2
+    y, x = h * d.stride_h + d.R // 2 - d.pad_h, w * d.stride_w + d.S // 2 - d.pad_w     # what the middle tap sees from there
+    few = [(5, 1), (11, 1), (d.K - 1, d.C - 2), (8, d.C - 2), (9, d.C - 2)]
+    for k, c in few:
+        X[:, c] = 0
+        X[n, c, y, x] = 1.7
+        dY[n, k, h, w] = 0.3 * 2.0 ** -(24 + 2 * k % 37)
+    want = oracle.wgrad_exact(oracle_shape(d), X, dY)
+    got = run(d, to_gpu(X), to_gpu(dY))
+    assert normwise_err(got, want) < TOL["fp32"] / 50
+    for k, c in few:
+        assert abs(got[k, c, d.R // 2, d.S // 2] - want[k, c, d.R // 2, d.S // 2]) <= 2.0 ** -23 * abs(want[k, c, d.R // 2, d.S // 2]) and want[k, c, d.R // 2, d.S // 2] != 0
+
+
 # ResNet-20's layers with a stride and its first one beside the others in one launch; from N = 118 on with fp16 pieces in the long sums
-@pytest.mark.parametrize("bad", [False, True])
+@pytest.mark.parametrize("bad", [False, True, "hidden"])
 @pytest.mark.parametrize("N", [31, 128])
 def test_layers_of_several_kinds_in_one_launch(N, bad):
     shapes = [(N, 3, 32, 32, 16, 3, 3, 1, 1, 1, 1)] + [(N, 16, 32, 32, 16, 3, 3, 1, 1, 1, 1)] * 7 + [(N, 16, 32, 32, 32, 3, 3, 2, 2, 1, 1)] \
@@ -322,8 +361,11 @@ def test_layers_of_several_kinds_in_one_launch(N, bad):
     ds = [mk(t) for t in shapes]
     kept = (0, 1, 8, 9, 15, 16)                                     # the first layer of each kind is compared with the oracle
     data = {i: rand_inputs(ds[i], 300 + i) for i in kept}
-    if bad:
-        for X, dY in data.values():
+    for X, dY in data.values():
+        if bad == "hidden":                                         # (as above)
+            X[::2] = 0
+            dY[::2] *= np.float32(2.0 ** 28)
+        elif bad:
             dY[0, 0, 0, 0], dY[-1, 5, -1, -1], X[1, 2, 0, 0] = np.inf, np.nan, -np.inf
     on_gpu = {i: (to_gpu(X), to_gpu(dY)) for i, (X, dY) in data.items()}
     of = [max(i for i in kept if i <= j) for j in range(len(ds))]
@@ -337,7 +379,7 @@ def test_layers_of_several_kinds_in_one_launch(N, bad):
         fine = np.isfinite(want)
         for j, got in enumerate(o.cpu().numpy() for k, o in enumerate(out) if of[k] == i):
             assert np.array_equal(np.isnan(got), np.isnan(want)) and np.array_equal(got[~fine], want[~fine].astype(np.float32), equal_nan=True)
-            assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / (1 if bad else 50), (i, j)
+            assert normwise_err(got[fine], want[fine]) < TOL["fp32"] / (1 if bad is True else 50), (i, j)
 
 
 # ResNet-20's shapes in runs, on both sides of the lines for short layers: 0.14 GFLOP for two layers of a shape, 0.5 for one and
