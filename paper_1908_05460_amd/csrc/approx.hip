@@ -1496,6 +1496,7 @@ int fused_flush(FusedQueue &q, hipStream_t st)
 #define WGRAD_GATHER_BLOCKS 512
 #endif
 
+constexpr int kFusedImages = 8;      // of a wavefront of the fused form in a launch of many groups
 static bool plan_approx_selected(const Geometry &g, int form, ApproxPlan &pl);
 // `pl`, the plan of a layer that the form of planes in registers takes, becomes that form's where the older form's workspace has
 // room for its selections; the batch is cut into no more chunks than it holds.  (Tensors that are not 16-byte aligned take the
@@ -1519,6 +1520,10 @@ static bool plan_approx_selected(const Geometry &g, int form, ApproxPlan &pl)
     pl.off_idx = 0; pl.off_sum = maps; pl.off_part = 2 * maps;
     if (alt.use_lds) {
         pl.ctiles = alt.ctiles; pl.ktiles = alt.ktiles; pl.gather_n = alt.gather_n;
+    }
+    if (form == 2) {
+        pl.gather_n = alt.fused ? (alt.chunk_n + 3) / 4 : alt.chunk_n;
+        pl.gather_run = alt.fused ? std::max(pl.gather_n, std::min(kFusedImages, (g.N + 3) / 4)) : pl.gather_n;
     }
     pl.chunks = (int)std::max<size_t>(1, std::min<size_t>((alt.ws_bytes - pl.off_part) / ((size_t)g.dw_elems() * 4), 1024));
     pl.chunk_n = (g.N + pl.chunks - 1) / pl.chunks;
@@ -1868,7 +1873,7 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
             // part of a launch of many groups, which fills the chip anyway: chunk for the images a wavefront
             // walks -- eight: fewer (more, shorter workgroups) loses to the per-workgroup set-up and to the
             // larger partial sums, more leaves too few workgroups to balance the tail
-            const int per_wave = tune_int("WGRAD_FUSED_IPW", 8);
+            const int per_wave = tune_int("WGRAD_FUSED_IPW", kFusedImages);
             chunks = (g.N + 4 * per_wave - 1) / (4 * per_wave);
         } else {
             // the workgroup target is for the whole launch: a batch chunks each problem less finely
@@ -1904,8 +1909,9 @@ int launch_approx(const Geometry &g, const ApproxPlan &plan, const Batch &b, flo
         ab.hw_row = at.row; ab.hw_col = at.col;
         rc = launch_select_impl(g, ab, b.n, idx_out, sum_out, st, rgq ? sq : nullptr);
         if (rc != WGRAD_OK) return rc;
-        // (no more lost to rounding than the LDS gather loses, as it would cut the batch here)
-        const int most_n = pl.gather_n > 0 ? gather_chunk_n(pl, g.N, b.n, gq != nullptr) : g.N;
+        // (no more lost to rounding than the LDS gather loses, as it would cut the batch here; planes in LDS: than the fused or direct
+        // form, whose longest sum that is)
+        const int most_n = pl.regs == 2 ? (rgq ? pl.gather_run : pl.gather_n) : (pl.gather_n > 0 ? gather_chunk_n(pl, g.N, b.n, gq != nullptr) : g.N);
         return launch_regs(g, pl.regs == 2, b, ab.hw, ab.sum, pl.chunks, most_n, scale, (char *)ws + pl.off_part, plan.ws_bytes, st, defer, rgq);
     }
     if (pl.sx) {

@@ -202,6 +202,9 @@ int planes_launch(const RegsItem *const *it, int n, hipStream_t st, CombineQueue
         p.ctiles = (g.C + 3) / 4; p.ktiles = (g.K + 63) / 64;
         const double share = 512 * (double)g.N * g.C * g.K * I.b.n / work;
         int ch = (int)(share / ((double)p.ctiles * p.ktiles * I.b.n) + 0.5);
+        // ... in no longer sums than the fused or direct form's (24 layers of 64 -> 64 @ 8x16, N = 1000, which would be one chunk each:
+        // 1.55e-7 off and 310 us, so 1.0e-7 and 308; the fused form 1.23e-7)
+        ch = std::max(ch, (g.N + kPlanesWaves * I.in_a_row - 1) / (kPlanesWaves * I.in_a_row));
         ch = std::max(1, std::min(std::min(ch, I.max_chunks), (g.N + kPlanesWaves - 1) / kPlanesWaves));
         p.chunk_n = (g.N + ch - 1) / ch;
         ch = chunks[i] = (g.N + p.chunk_n - 1) / p.chunk_n;

@@ -517,7 +517,8 @@ int launch_regs(const Geometry &g, bool planes, const Batch &b, const int32_t *c
     RegsQueue &q = queue ? *queue : local;
     RegsItem &I = q.item[q.n++];
     I.g = g; I.b = b; I.max_chunks = max_chunks; I.scale = scale; I.part = (char *)part; I.stride = stride; I.planes = planes;
-    if (!planes) regs_limits(I, most_n);
+    if (planes) I.in_a_row = most_n;
+    else regs_limits(I, most_n);
     for (int i = 0; i < b.n; ++i) { I.at[i] = at[i]; I.sum[i] = sum[i]; }
     return queue ? WGRAD_OK : regs_flush(local, st, defer);
 }

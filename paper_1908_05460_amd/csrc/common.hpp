@@ -181,6 +181,7 @@ struct ApproxPlan {
     int chunks, chunk_n;             // batch chunks whose partial sums are combined afterwards
     int use_lds, fused, m, nb, pitch, wp, ctiles, ktiles;   // LDS form of the gather: tile shape
     int gather_n;                    // images of the LDS form's batch chunk alone; also where `regs` stands in for that form, which loses no more to rounding
+    int gather_run;                  // (planes in LDS: images that the older form adds up in a row, alone [gather_n] and in a run)
     int rows, rows_chunks;           // bf16_rows.hip's form of it (beside mm): 0 no, 1 a layer alone, 2 in a run with enough such work; the most batch chunks
     int mm;                          // contraction on the bf16 matrix core from the selection results
     int regs;                        // planes held in registers (1, fp32, approx_regs.hip) or in LDS (2, approx_planes.hip)
@@ -222,6 +223,7 @@ struct RegsItem {
     int fewest, least, most, additions;      // see regs_limits
     float scale;
     bool planes;                     // approx_planes.hip's
+    int in_a_row;                    // ... the most images of a wavefront
 };
 // those on other planes, in LDS (approx_planes.hip), of the same queue; alt: the plan without that form
 bool planes_takes(const Geometry &g, const ApproxPlan &alt);

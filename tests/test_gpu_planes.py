@@ -46,6 +46,23 @@ def test_run_matches_the_oracle():
         assert normwise_err(got * 4, oracle.wgrad_approx(oracle_shape(d), X, dY)[0]) < BOUND
 
 
+def test_many_layers_in_a_run_are_not_summed_in_longer_rows():
+    """24 layers share the chip's workgroups, N = 1000: the fused form, in chunks of its own, is 1.23e-7 of the result (2-norm) off, this one
+    1.0e-7, with as many chunks as fill the chip alone 1.55e-7."""
+    import torch
+    d = desc((1000, 64, 8, 16, 64, 1, 1))
+    X, dY = rand_inputs(d, 61)
+    Xg, Yg = to_gpu(X), to_gpu(dY)
+    out = [torch.full((d.K, d.C, 3, 3), float("nan"), device="cuda") for _ in range(24)]
+    s = B.Schedule([d] * 24, [Xg] * 24, [Yg] * 24, out)
+    m = [B.APPROX] * 24
+    s.run(m, B.alloc_workspace(s.workspace_bytes(m)), scale=1.0)
+    want = oracle.wgrad_approx(oracle_shape(d), X, dY)[0]
+    for got in out:
+        err = np.linalg.norm(got.cpu().numpy() - want) / np.linalg.norm(want)
+        assert err < 1.35e-7, err
+
+
 @pytest.mark.parametrize("where", ["X", "dY"])
 @pytest.mark.parametrize("t", [SHAPES[0], SHAPES[5], SHAPES[6]])
 def test_infinities_and_nans(t, where):
