@@ -126,6 +126,7 @@ bool x3_needs_alignment(const X3Plan &pl);
 bool x3_ragged(const X3Plan &pl);
 int x3_tile_rows(const X3Plan &pl);
 bool x3_mixes(const X3Plan &pl);                     // whether its launch can carry groups of other variants
+bool x3_joins(const X3Plan &pl);                     // whether a layer that the fp32 core takes by itself may go there
 bool x3_fit(X3Plan &pl, long room);
 struct X3Queue;
 X3Queue *x3_queue_new();

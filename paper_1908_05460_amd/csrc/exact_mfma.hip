@@ -674,7 +674,7 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
     if ((!use && !run && !join) || !plan_exact_x3(g, x3)) return size_exact(g, pl);
     if ((!use && !run) || (!pl.plane2 && older_form_wins(g, pl, x3, gflop))) {
         pl = size_exact(g, pl);
-        pl.x3_join = join && x3_mixes(x3) && x3_fit(x3, (long)(pl.ws_bytes / ((size_t)g.dw_elems() * 4)));
+        pl.x3_join = join && x3_fit(x3, (long)(pl.ws_bytes / ((size_t)g.dw_elems() * 4))) && x3_joins(x3);
         if (pl.x3_join) pl.x3p = x3;
         return pl;
     }
@@ -684,7 +684,7 @@ static ExactPlan plan_exact_x3_or_older(const Geometry &g)
     if (!use && !x3_fit(x3, (long)(pl.ws_bytes / ((size_t)g.dw_elems() * 4)))) return pl;
     pl.x3 = use;
     pl.x3_run = run;
-    pl.x3_join = join && x3_mixes(x3);
+    pl.x3_join = join && x3_joins(x3);
     pl.x3p = x3;
     const size_t need = use && x3.splits > 1 ? align_up((size_t)x3.splits * g.dw_elems() * 4) : 0;
     if (need > pl.ws_bytes) pl.ws_bytes = need;

@@ -119,7 +119,9 @@ static long x3_most_tiles(const X3Variant &v) { return v.plane ? 64 : (v.kind ==
 // 128); shorter sums would gain a fifth of their time (N = 128 alone, 4 stages: 50 us, 42).
 constexpr long kX3HalfStages = 12;
 // a launch of several variants, bf16 pieces: 24 tiles (ResNet-20, N = 90 to 128, sums of 18 / 24 / 28 tiles, error over that of the
-// launches before: 64 -> 64 @ 8x8 0.86 / 0.97 / 1.17, the others less)
+// launches before: 64 -> 64 @ 8x8 0.86 / 0.97 / 1.17, the others less), and as many of the strided ones' fp16 pieces.  Layers that take
+// bf16 pieces only in such a launch are in it where their workspace has room for that (x3_joins); the others' partial results are as
+// many as in a launch of their own, x3_most_tiles to a sum.
 constexpr long kX3MixMost = 24;
 constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
 
@@ -192,6 +194,10 @@ bool x3_needs_alignment(const X3Plan &pl) { return kVariant[pl.variant].kind == 
 bool x3_ragged(const X3Plan &pl) { return kVariant[pl.variant].rag; }
 int x3_tile_rows(const X3Plan &pl) { return kVariant[pl.variant].sh; }
 bool x3_mixes(const X3Plan &pl) { return x3_mix_body(pl.variant) >= 0; }
+bool x3_joins(const X3Plan &pl)
+{
+    return x3_mixes(pl) && (x3_mix_body(pl.variant) == 1 || (long)pl.w_tiles * pl.h_tiles * pl.n_groups <= kX3MixMost * pl.splits);
+}
 
 // at most `room` partial results; false if a workgroup would then add up more tiles than x3_most_tiles
 bool x3_fit(X3Plan &pl, long room)
