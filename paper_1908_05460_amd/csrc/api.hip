@@ -577,9 +577,10 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
 }
 
 // The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 3 a
-// short fp32 layer in the form of 16-bit pieces, 4 planes in registers, 0 another.  For tests of the choice on the host.
+// short fp32 layer in the form of 16-bit pieces, 4 planes in registers, 5 planes in LDS, 0 another; joins (may be null): whether the layer
+// is in the launch of 16-wide tiles in 16-bit pieces because others are.  For tests of the choice on the host.
 namespace wgrad {
-int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form)
+int schedule_joins(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form, int *joins)
 {
     int group[4096];
     std::vector<LayerPlan> plan;
@@ -588,10 +589,18 @@ int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, 
     choose_run_forms(method, n, group, plan);
     for (int i = 0; i < n; ++i) {
         const LayerPlan &p = plan[group[i]];
-        form[i] = method[i] == WGRAD_EXACT ? (p.ex.rows ? 1 : (p.ex.x3_run ? 3 : 0)) : (method[i] == WGRAD_APPROX ? (p.ap.rows == 2 ? 2 : (p.ap.regs ? 4 : 0)) : 0);
+        form[i] = method[i] == WGRAD_EXACT ? (p.ex.rows ? 1 : (p.ex.x3_run ? 3 : 0)) : (method[i] == WGRAD_APPROX ? (p.ap.rows == 2 ? 2 : (p.ap.regs ? 3 + p.ap.regs : 0)) : 0);
+        if (joins) joins[i] = method[i] == WGRAD_EXACT && p.ex.x3_join && !p.ex.x3_run;
     }
     return WGRAD_OK;
 }
+// the same of an approximated layer alone, or -1
+int approx_form(const wgrad_conv_desc *layer)
+{
+    Geometry g;
+    return make_geometry(layer, g) == WGRAD_OK ? (plan_approx(g).regs ? 3 + plan_approx(g).regs : 0) : -1;
+}
+int schedule_forms(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form) { return schedule_joins(layers, method, n, form, nullptr); }
 }  // namespace wgrad
 
 extern "C" int conv_wgrad_schedule_run(const wgrad_conv_desc *layers, const void *const *X, const void *const *dY,

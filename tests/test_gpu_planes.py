@@ -14,7 +14,10 @@ BOUND = TOL["fp32"] / 50        # fp32 sums of a few products a wavefront, added
 
 # (N, C, H, W, K, stride, padding)
 SHAPES = [(100, 61, 5, 5, 65, 1, 1), (200, 41, 2, 3, 70, 1, 1), (21, 130, 7, 9, 129, 1, 1), (40, 66, 8, 8, 300, 2, 0), (160, 33, 13, 13, 71, 1, 1), (47, 131, 16, 16, 128, 1, 1),
-          (92, 128, 16, 16, 64, 2, 1), (9, 300, 16, 16, 320, 1, 0), (30, 110, 4, 64, 256, 1, 1), (50, 125, 64, 4, 128, 1, 1), (70, 67, 15, 17, 70, 2, 0)]
+          (92, 128, 16, 16, 64, 2, 1), (9, 300, 16, 16, 320, 1, 0), (30, 110, 4, 64, 256, 1, 1), (50, 125, 64, 4, 128, 1, 1), (70, 67, 15, 17, 70, 2, 0),
+          (100, 67, 15, 17, 128, 2, 0), (60, 90, 7, 7, 90, 2, 0)]
+OLDER = [SHAPES[3], SHAPES[10]]     # beside them, shapes that the LDS gather and the fused form keep (tests/test_run_forms.py)
+BF16 = SHAPES[:5] + [(66, 128, 16, 16, 128, 2, 1)]
 
 
 def desc(t, dtype="fp32"):
@@ -23,7 +26,7 @@ def desc(t, dtype="fp32"):
 
 
 # bf16: those that no matrix-core form takes
-@pytest.mark.parametrize("t,dtype", [(t, "fp32") for t in SHAPES] + [(t, "bf16") for t in SHAPES[:5] + [(66, 128, 16, 16, 128, 2, 1)]])
+@pytest.mark.parametrize("t,dtype", [(t, "fp32") for t in SHAPES] + [(t, "bf16") for t in BF16])
 def test_alone_matches_the_oracle(t, dtype):
     import torch
     d = desc(t, dtype)

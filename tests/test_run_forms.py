@@ -6,18 +6,23 @@ import pytest
 
 from paper_1908_05460_amd import binding as B, inputs
 
-# bf16 layers row after row, exact and approximated; short fp32 layers in the three-piece form; approximated fp32 layers' planes in registers
-ROWS, SPARSE_ROWS, X3_RUN, REGS = 1, 2, 3, 4
+# bf16 layers row after row, exact and approximated; short fp32 layers in 16-bit pieces; approximated layers' planes in registers and in LDS
+ROWS, SPARSE_ROWS, X3_RUN, REGS, LDS = 1, 2, 3, 4, 5
 E, A = B.EXACT, B.APPROX
 
 
-def forms(run):
-    """run: [(method, type, N, C, H = W, K, layers)] -> the forms of its shapes"""
+def flat(run):
     descs, methods, at = [], [], []
-    for method, dtype, n, c, hw, k, count in run:
+    for method, dtype, n, c, hw, k, count, *stride in run:
         at.append(len(descs))
-        descs += [B.desc(n, c, hw, hw, k, dtype=B.BF16 if dtype == "bf16" else B.F32)] * count
+        descs += [B.desc(n, c, hw, hw, k, stride=stride[0] if stride else 1, dtype=B.BF16 if dtype == "bf16" else B.F32)] * count
         methods += [method] * count
+    return descs, methods, at
+
+
+def forms(run):
+    """run: [(method, type, N, C, H = W, K, layers[, stride])] -> the forms of its shapes"""
+    descs, methods, at = flat(run)
     f = B.load()._ZN5wgrad14schedule_formsEPK15wgrad_conv_descPKhiPi
     f.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_int, ct.c_void_p]
     n = len(descs)
@@ -120,3 +125,61 @@ def test_resnet20_in_the_three_piece_form(n, taken):
 ])
 def test_planes_in_registers(run, taken):
     assert forms(run) == taken
+
+
+def joins(run):
+    """Whether the shapes of a run are in the launch of 16-wide tiles because others are"""
+    descs, methods, at = flat(run)
+    f = B.load()._ZN5wgrad14schedule_joinsEPK15wgrad_conv_descPKhiPiS5_
+    f.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_int, ct.c_void_p, ct.c_void_p]
+    n = len(descs)
+    form, out = (ct.c_int * n)(), (ct.c_int * n)()
+    assert f((B.ConvDesc * n)(*descs), (ct.c_uint8 * n)(*methods), n, form, out) == 0
+    return [bool(out[i]) for i in at]
+
+
+@pytest.mark.parametrize("n, taken", [(16, False), (32, True), (48, True), (80, True), (128, True)])
+def test_resnet20_strided_and_first_layers_join_the_others(n, taken):
+    """(44 / 53 / 76 / 100 us at N = 32 / 48 / 80 / 128 without, 30 / 38 / 57 / 80 with them)"""
+    layers = inputs.resnet20_stack()
+    got = joins([(E, "fp32", n, l.C, l.H, l.K, 1, l.stride) for l in layers])
+    assert got == [taken and (l.stride == 2 or l.C == 3) for l in layers]
+
+
+def test_nothing_joins_without_a_host():
+    assert joins([(E, "fp32", 64, 3, 32, 16, 1), (E, "fp32", 64, 16, 32, 32, 1, 2)]) == [False, False]
+    assert joins([(E, "fp32", 64, 3, 32, 16, 1), (E, "fp32", 64, 512, 4, 512, 2)]) == [False, False]      # (no 16-wide tiles)
+
+
+@pytest.mark.parametrize("n, taken", [(64, False), (96, True), (128, True)])                               # 129.7 / 130.9, 167.6 / 159.9
+def test_vgg19_planes_in_lds(n, taken):
+    layers = inputs.vgg19_stack()
+    assert [f == LDS for f in forms(stack(layers, A, "fp32", n))] == [taken and l.H == 16 for l in layers]
+
+
+def alone(d):
+    f = B.load()._ZN5wgrad11approx_formEPK15wgrad_conv_desc
+    f.argtypes = [ct.c_void_p]
+    return f(ct.byref(d))
+
+
+# us before the form / with it
+@pytest.mark.parametrize("d, taken", [
+    (B.desc(32, 128, 16, 16, 128), 0),                                          # 10.4 / 13.0
+    (B.desc(48, 128, 16, 16, 128), LDS),                                        # 15.5 / 14.3
+    (B.desc(48, 128, 16, 16, 128, stride=2, dtype=B.BF16), 0),                  # 12.9 / 14.0
+    (B.desc(64, 128, 16, 16, 128, stride=2, dtype=B.BF16), LDS),                # 15.5 / 14.9
+    (B.desc(35, 60, 9, 9, 150), 0),                                             # 14.1 / 14.9
+    (B.desc(60, 60, 9, 9, 150), LDS),                                           # 15.3 / 13.6
+    (B.desc(128, 128, 8, 8, 128), REGS),
+])
+def test_planes_in_lds_alone(d, taken):
+    assert alone(d) == taken
+
+
+def test_shapes_of_the_gpu_tests_take_planes_in_lds():
+    from tests import test_gpu_planes as P
+    for t in P.SHAPES:
+        assert alone(P.desc(t)) == (0 if t in P.OLDER else LDS), t
+    for t in P.BF16:
+        assert alone(P.desc(t, "bf16")) == (0 if t in P.OLDER else LDS), t
