@@ -134,7 +134,7 @@ __device__ __forceinline__ void select_body(const ApproxBatch &ab, long maps, in
                 const int e = e0 + u * G * VEC;
                 in[u] = WHOLE || e < len;
                 const long at = base + (in[u] ? e : e0);
-                if (VEC == 1) raw[u][0] = BF16 ? (uint32_t)((const uint16_t *)dY)[at] << 16 : ((const uint32_t *)dY)[at];
+                if constexpr (VEC == 1) raw[u][0] = BF16 ? (uint32_t)((const uint16_t *)dY)[at] << 16 : ((const uint32_t *)dY)[at];
                 else {               // one 16-byte load of 8 bf16 or 4 fp32
                     const uint4 r = BF16 ? *(const uint4 *)((const uint16_t *)dY + at) : *(const uint4 *)((const uint32_t *)dY + at);
                     raw[u][0] = r.x; raw[u][1] = r.y; raw[u][2] = r.z; raw[u][3] = r.w;

@@ -168,7 +168,9 @@ __global__ __launch_bounds__(64 * kPlanesWaves, 4) void approx_gather_planes(con
 // 45 / 60: 14.1 / 13.5 / 15.3 us there, 14.9 / 13.4 / 13.6 here; 30 -> 200 @ 13x13, N = 60 / 100: 16.9 / 21.8, 16.5 / 19.5); against the fused one, which selects in the same launch,
 // from 750 000 (128 -> 128 @ 16x16, N = 32: 10.4, 13.0; N = 48: 15.5, 14.3; 16 -> 128, N = 200: 14.4, 17.6), in bf16, whose maps stream in half the time, from a million (128 -> 128 @ 16x16, stride 2, N = 48: 12.9, 14.0; N = 64: 15.5,
 // 14.9), and where three
-// lanes of four have an output channel.  The LDS gather keeps its layers, 8x8 planes that the form in registers does not take, unmeasured.
+// lanes of four have an output channel.  The LDS gather keeps its layers, planes that the form in registers does not take, which would be
+// faster here (66 -> 300 @ 8x8, stride 2, N = 40: 25.1 us there, 14.5 here; 100 -> 200, N = 60: 20.6, 14.9; 64 -> 300 @ 6x6, N = 128: 28.0, 16.1): the
+// line is not drawn by these.
 bool planes_takes(const Geometry &g, const ApproxPlan &alt)
 {
     if (g.R != 3 || g.S != 3 || g.ph > 1 || g.pw > 1 || alt.sx || alt.mm || alt.use_lds) return false;

@@ -643,8 +643,8 @@ static bool older_form_wins(const Geometry &g, const ExactPlan &pl, const X3Plan
 // exact, N = 48: 42.6 -> 45.3 at 0.2), and batches under 16, which keep to the launch of many small groups (8, 64 -> 128 @ 16x16,
 // two layers and a small one, 34 us there, 27 here).  Such a layer alone takes it down to 0.02 GFLOP (64 -> 64 @
 // 8x8, N = 8 to 64: 13 to 14 us against 16.5 to 18; of 30 shapes of 16 channels on a side or less than 0.03 GFLOP none was
-// slower, but short ragged strided rows; the smallest stay in the older forms' workspace: 16 -> 16 @ 32x32, N = 8 / 16 / 64 / 100: 13.4 / 14.3 / 14.7 / 19.3 -> 10.8 / 12.8 / 12.1 / 14.4;
-// 16 -> 100, N = 4: 16.7 -> 10.3; 32 -> 32 @ 8x8, N = 4: 13.4 -> 7.8; 8 -> 12 @ 12x12, stride 2, N = 30: 12.1, 16.6 here).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
+// slower, but short ragged strided rows; the smallest stay in the older forms' workspace: 16 -> 16 @ 32x32, N = 8 / 16 / 64 / 100: 13.4 / 14.2 / 14.4 / 18.4 -> 11.1 / 11.7 / 11.9 / 14.0;
+// 16 -> 100, N = 4: 16.6 -> 10.4; 8 -> 12 @ 12x12, stride 2, N = 30: 12.1, 16.6 here).  2x2 planes of whole 16-channel tiles go there in a run of layers only, where the plain product's launch
 // of its own is what costs, and two or more of one shape at a time (with a small layer beside them, N = 64 / 128 / 256: one 23 /
 // 31 / 46 us against 34 / 47 / 62 that way, two 38 / 49 / 76 against 37 / 49 / 73, four 44 / 65 / 104 against 42 / 56 / 84);
 // alone the plain product is the faster one (512 -> 512, N = 128: 15.4 us against 24.3).

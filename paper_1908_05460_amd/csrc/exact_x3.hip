@@ -98,7 +98,9 @@ static bool x3_tile(const Geometry &g, int id, X3Plan &pl)
 }
 
 // us that a workgroup spends on a tile when `share` of them are on its CU: bounded by the matrix instructions of all, or
-// by its own staging and matrix instructions one after the other
+// by its own staging and matrix instructions one after the other.  (Fitted to bf16 pieces and their six products; `half`, the longest
+// rows of a launch of several variants, counts three.  The 32-wide tiles and 4x4 planes of fp16 pieces are cut by this figure as
+// well, 4.2 us a tile where they take 3.0: their splits are those that were timed, not a minimum of the model.)
 static double x3_tile_us(const X3Variant &v, int share, bool half = false)
 {
     if (v.plane) return 1.1 * (v.plane == 4 ? std::max(share * 2.8, 4.2) : std::max(share * 0.85, 1.8));
@@ -233,7 +235,8 @@ bool plan_exact_x3(const Geometry &g, X3Plan &best)
         if (v.plane || (v.kind == kX3Bf16) != (g.bf16 != 0) || v.s != g.S || v.sw != g.sw) continue;
         X3Plan pl{};
         if (!x3_tile(g, id, pl)) continue;
-        // Matrix instructions, in units of a 16x16 tile of the result.  Long reductions do better with 32x32 tiles (a
+        // Matrix instructions, in units of a 16x16 tile of the result, six products to either kind (32-wide tiles take fp16 pieces now,
+        // and three: the line between the two, and its figures, are of bf16 pieces).  Long reductions do better with 32x32 tiles (a
         // staged element serves twice as many of them; 128 -> 128 @ 16x16, N = 128: 56 us against 65), short ones with
         // 16x16 tiles, whose workgroups are quicker to set up and share a CU by four (N = 16: 21 us against 22.5;
         // 48 -> 96 @ 27x27, N = 32, where 32x32 tiles would be a third padding besides: 35 against 49).
