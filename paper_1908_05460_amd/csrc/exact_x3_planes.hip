@@ -6,10 +6,10 @@
 //
 // The reduction of a G_pq runs over images, so an operand is "eight images of one position" and the (position, tap)
 // pairs whose tap meets only padding are never multiplied: 100 of 144 are left on a 4x4 plane, 16 of 36 on a 2x2 plane.
-// Matrix instructions and the staging's vector instructions (three to each) take turns: the matrix core is busy 43 % of
-// the cycles of VGG-19's launch, at 2.27 GHz, so a product left out is time saved.  512 -> 512 @ 4x4 takes 16.9 / 50 us at
+// Matrix instructions and the staging's vector instructions (three to each with three pieces, five with two) take turns: the matrix
+// core is busy 43 % of the cycles of VGG-19's launch with three pieces, 32 % with two, at 2.2 GHz, so a product left out is time saved.  512 -> 512 @ 4x4 takes 16.9 / 50 us at
 // N = 16 / 128 with three bf16 pieces (the fp32 matrix core 28.8 / 72, the row form of exact_x3_kernel.hpp 63 at N = 128),
-// 154 -> 103 us at N = 512 with two fp16 pieces, which long sums take (kX3HalfStages); 2x2 15.4 -> 45.7 us where the fp32 matrix
+// 152 -> 101 us at N = 512 with two fp16 pieces, which long sums take (kX3HalfStages); 2x2 15.4 -> 45.7 us where the fp32 matrix
 // core takes 49.7 (N = 512) and half of its time in a run of layers.
 //
 // A workgroup owns 64 output channels x 32 input channels; its four wavefronts share the taps out (13, 12, 12 and 15

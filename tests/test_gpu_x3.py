@@ -352,6 +352,32 @@ def test_single_results_of_small_numbers(t):
         assert abs(got[k, c, d.R // 2, d.S // 2] - want[k, c, d.R // 2, d.S // 2]) <= 2.0 ** -23 * abs(want[k, c, d.R // 2, d.S // 2]) and want[k, c, d.R // 2, d.S // 2] != 0
 
 
+@pytest.mark.parametrize("t", HALVES)
+@pytest.mark.parametrize("how", ["numbers", "images", "sparse"])
+def test_every_result_of_numbers_of_many_magnitudes(t, how):
+    """Magnitudes over 2^40 from number to number or image to image, or over 2^30 in products so rare that many results are a few or none:
+    no result is further off than an fp32 sum of its products may be, a rounding of 2^-24 of their magnitudes or two for each."""
+    d = mk(t)
+    X, dY = rand_inputs(d, 41)
+    rng = np.random.default_rng(43)
+    if how == "images":
+        dY *= np.exp2(-40 * rng.random((d.N, 1, 1, 1), np.float32))
+    elif how == "sparse":
+        X *= rng.random(X.shape) < 4 / (d.N * d.H * d.W)
+        dY *= np.exp2(-30 * rng.random(dY.shape, np.float32))
+    else:
+        X *= np.exp2(-40 * rng.random(X.shape, np.float32)) * (rng.random(X.shape) < 0.5)
+        dY *= np.exp2(-40 * rng.random(dY.shape, np.float32)) * (rng.random(dY.shape) < 0.5)
+    g = oracle_shape(d)
+    want, size = oracle.wgrad_exact(g, X, dY), oracle.wgrad_exact(g, np.abs(X), np.abs(dY))
+    got = run(d, to_gpu(X), to_gpu(dY))
+    p = plan(t, "fp32")[0]
+    # products of a workgroup's sum (4x4 planes: eight images a stage); of the rare ones sixteen at most, two of them on average
+    terms = 8 if how == "sparse" else -(-p.tiles // p.splits) * (p.nch * 8 if p.nch else 128)
+    assert (np.abs(got - want) <= 2 * terms * 2.0 ** -24 * size).all()
+    assert np.median(np.abs(got - want)[size > 0] / size[size > 0]) < 2.0 ** -23
+
+
 # ResNet-20's layers with a stride and its first one beside the others in one launch; from N = 118 on with fp16 pieces in the long sums
 @pytest.mark.parametrize("bad", [False, True, "hidden"])
 @pytest.mark.parametrize("N", [31, 128])
