@@ -577,8 +577,9 @@ static int schedule_run_impl(const wgrad_conv_desc *layers, const void *const *X
 }
 
 // The form of each layer of a run (tensors aligned as torch allocates them): 1 exact row after row, 2 approximated row after row, 3 a
-// short fp32 layer in the form of 16-bit pieces, 4 planes in registers, 5 planes in LDS, 0 another; joins (may be null): whether the layer
-// is in the launch of 16-wide tiles in 16-bit pieces because others are.  For tests of the choice on the host.
+// short fp32 layer in the form of 16-bit pieces, 4 planes in registers, 5 planes in LDS, 0 another; joins (may be null): 1 if the layer
+// is in the launch of 16-wide tiles in 16-bit pieces because others are, 2 if it is there in two pieces where three could be (one such
+// launch assumed).  For tests of the choice on the host.
 namespace wgrad {
 int schedule_joins(const wgrad_conv_desc *layers, const uint8_t *method, int n, int *form, int *joins)
 {
@@ -591,6 +592,22 @@ int schedule_joins(const wgrad_conv_desc *layers, const uint8_t *method, int n, 
         const LayerPlan &p = plan[group[i]];
         form[i] = method[i] == WGRAD_EXACT ? (p.ex.rows ? 1 : (p.ex.x3_run ? 3 : 0)) : (method[i] == WGRAD_APPROX ? (p.ap.rows == 2 ? 2 : (p.ap.regs ? 3 + p.ap.regs : 0)) : 0);
         if (joins) joins[i] = method[i] == WGRAD_EXACT && p.ex.x3_join && !p.ex.x3_run;
+    }
+    if (joins) {
+        std::vector<X3Kind> kind;
+        std::vector<int> first;
+        bool mixed = false;
+        for (int i = 0; i < n; ++i) {
+            const ExactPlan &ex = plan[group[i]].ex;
+            if (method[i] != WGRAD_EXACT || plan[group[i]].g.bf16 || !(ex.x3 == 2 || ex.x3_run || ex.x3_join) || !x3_mixes(ex.x3p)) continue;
+            if (group[i] == i) { kind.push_back(X3Kind{&plan[i].g, &plan[i].ex.x3p, 1, false}); first.push_back(i); }
+            else for (size_t k = 0; k < first.size(); ++k) kind[k].layers += first[k] == group[i];
+            mixed = mixed || kind[0].pl->variant != ex.x3p.variant;
+        }
+        if (mixed) x3_choose_pieces(kind.data(), (int)kind.size());
+        for (int i = 0; i < n; ++i)
+            for (size_t k = 0; k < first.size(); ++k)
+                if (kind[k].half && first[k] == group[i]) joins[i] = 2;
     }
     return WGRAD_OK;
 }

@@ -128,6 +128,14 @@ int x3_tile_rows(const X3Plan &pl);
 bool x3_mixes(const X3Plan &pl);                     // whether its launch can carry groups of other variants
 bool x3_joins(const X3Plan &pl);                     // whether a layer that the fp32 core takes by itself may go there
 bool x3_fit(X3Plan &pl, long room);
+// layers of one shape in a launch of several variants; half: whether rows that could take three bf16 pieces take two fp16 ones
+struct X3Kind {
+    const Geometry *g;
+    const X3Plan *pl;
+    int layers;
+    bool half;
+};
+void x3_choose_pieces(X3Kind *kind, int n);
 struct X3Queue;
 X3Queue *x3_queue_new();
 void x3_queue_delete(X3Queue *q);

@@ -125,6 +125,7 @@ constexpr long kX3HalfStages = 12;
 // bf16 pieces only in such a launch are in it where their workspace has room for that (x3_joins); the others' partial results are as
 // many as in a launch of their own, x3_most_tiles to a sum.
 constexpr long kX3MixMost = 24;
+constexpr int kX3MixSlots = 3 * kNumCU;      // workgroups of such a launch that the chip holds at once
 constexpr double kX3Fixed = 9.0;       // a workgroup's set-up, first loads and write-out
 
 // How long a launch runs: its workgroups, longest first, each on the slot that is free earliest.  `n` kinds of
@@ -338,6 +339,21 @@ static int x3_launch_groups(const X3Group *const *it, int n, hipStream_t st)
 
 // Issues what was collected, in launches of several groups (longest workgroups first), cut so that a launch's workgroups
 // fill the chip about evenly; the partial results are recorded in `combine`.
+// A launch of several variants: where one round of workgroups would add up more tiles than three bf16 pieces may (kX3MixMost), fp16
+// pieces, which err no more at that length, on rows of more than one chunk (ResNet-20 exact, N = 128: 89 us in bf16 pieces, two
+// rounds, 80 so; on 8x8 planes they err 1.15 times as much as bf16 pieces in the launches before)
+void x3_choose_pieces(X3Kind *kind, int n)
+{
+    auto tile_us = [&](const X3Kind &k) { return x3_tile_us(kVariant[k.pl->variant], kX3MixSlots / kNumCU); };
+    double rounds = 0;
+    for (int i = 0; i < n; ++i) {
+        const X3Plan &pl = *kind[i].pl;
+        rounds += (double)((long)pl.w_tiles * pl.h_tiles * pl.n_groups) * pl.ktiles * pl.ctiles * kind[i].layers * tile_us(kind[i]) / tile_us(kind[0]);
+    }
+    for (int i = 0; i < n; ++i)
+        kind[i].half = 1.08 * rounds > (double)kX3MixSlots * kX3MixMost && x3_mix_body(kind[i].pl->variant) == 0 && kind[i].g->Wo > 8;
+}
+
 int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
 {
     int rc = WGRAD_OK;
@@ -357,17 +373,15 @@ int x3_flush(X3Queue &q, hipStream_t st, CombineQueue *combine)
         const X3Variant &v = kVariant[variant];
         bool mixed = false;
         for (int i = 1; i < n; ++i) mixed = mixed || sel[i]->pl.variant != variant;
-        const int slots = mixed ? 3 * kNumCU : x3_resident(v);
+        const int slots = mixed ? kX3MixSlots : x3_resident(v);
         double t[kX3MultiMax];
         for (int i = 0; i < n; ++i) t[i] = x3_tile_us(kVariant[sel[i]->pl.variant], slots / kNumCU);
         if (mixed) {
-            // One round of workgroups would add up more tiles than three bf16 pieces may (kX3MixMost): fp16 pieces, which err no
-            // more at that length, on rows of more than one chunk (ResNet-20 exact, N = 128: 89 us in bf16 pieces, two rounds, 80
-            // so; on 8x8 planes they err 1.15 times as much as bf16 pieces in the launches before)
-            double rounds = 0;
-            for (int i = 0; i < n; ++i) rounds += (double)tiles_of(*sel[i]) * sel[i]->pl.ktiles * sel[i]->pl.ctiles * sel[i]->b.n * t[i] / t[0];
+            X3Kind kind[kX3MultiMax];
+            for (int i = 0; i < n; ++i) kind[i] = X3Kind{&sel[i]->g, &sel[i]->pl, sel[i]->b.n, false};
+            x3_choose_pieces(kind, n);
             for (int i = 0; i < n; ++i) {
-                sel[i]->half = 1.08 * rounds > (double)slots * kX3MixMost && x3_mix_body(sel[i]->pl.variant) == 0 && sel[i]->g.Wo > 8;
+                sel[i]->half = kind[i].half;
                 if (sel[i]->half) t[i] = x3_tile_us(kVariant[sel[i]->pl.variant], slots / kNumCU, true);
             }
         }

@@ -378,7 +378,7 @@ def test_every_result_of_numbers_of_many_magnitudes(t, how):
     assert np.median(np.abs(got - want)[size > 0] / size[size > 0]) < 2.0 ** -23
 
 
-# ResNet-20's layers with a stride and its first one beside the others in one launch; from N = 118 on with fp16 pieces in the long sums
+# ResNet-20's layers with a stride and its first one beside the others in one launch; from N = 74 on with fp16 pieces in the long sums
 @pytest.mark.parametrize("bad", [False, True, "hidden"])
 @pytest.mark.parametrize("N", [31, 128])
 def test_layers_of_several_kinds_in_one_launch(N, bad):

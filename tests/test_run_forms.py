@@ -128,14 +128,14 @@ def test_planes_in_registers(run, taken):
 
 
 def joins(run):
-    """Whether the shapes of a run are in the launch of 16-wide tiles because others are"""
+    """1: the shape is in the launch of 16-wide tiles because others are; 2: it is there in two fp16 pieces where three bf16 ones could be"""
     descs, methods, at = flat(run)
     f = B.load()._ZN5wgrad14schedule_joinsEPK15wgrad_conv_descPKhiPiS5_
     f.argtypes = [ct.c_void_p, ct.c_void_p, ct.c_int, ct.c_void_p, ct.c_void_p]
     n = len(descs)
     form, out = (ct.c_int * n)(), (ct.c_int * n)()
     assert f((B.ConvDesc * n)(*descs), (ct.c_uint8 * n)(*methods), n, form, out) == 0
-    return [bool(out[i]) for i in at]
+    return [out[i] for i in at]
 
 
 @pytest.mark.parametrize("n, taken", [(16, False), (32, True), (48, True), (80, True), (128, True)])
@@ -143,12 +143,19 @@ def test_resnet20_strided_and_first_layers_join_the_others(n, taken):
     """(44 / 53 / 76 / 100 us at N = 32 / 48 / 80 / 128 without, 30 / 38 / 57 / 80 with them)"""
     layers = inputs.resnet20_stack()
     got = joins([(E, "fp32", n, l.C, l.H, l.K, 1, l.stride) for l in layers])
-    assert got == [taken and (l.stride == 2 or l.C == 3) for l in layers]
+    assert [f == 1 for f in got] == [taken and (l.stride == 2 or l.C == 3) for l in layers]
+
+
+@pytest.mark.parametrize("n, taken", [(73, False), (74, True), (128, True)])                               # 89 us in bf16 pieces, 80 (N = 128)
+def test_resnet20_long_rows_in_two_pieces(n, taken):
+    layers = inputs.resnet20_stack()
+    got = joins([(E, "fp32", n, l.C, l.H, l.K, 1, l.stride) for l in layers])
+    assert [f == 2 for f in got] == [taken and l.stride == 1 and l.C >= 16 and l.H > 8 for l in layers]
 
 
 def test_nothing_joins_without_a_host():
-    assert joins([(E, "fp32", 64, 3, 32, 16, 1), (E, "fp32", 64, 16, 32, 32, 1, 2)]) == [False, False]
-    assert joins([(E, "fp32", 64, 3, 32, 16, 1), (E, "fp32", 64, 512, 4, 512, 2)]) == [False, False]      # (no 16-wide tiles)
+    assert joins([(E, "fp32", 64, 3, 32, 16, 1), (E, "fp32", 64, 16, 32, 32, 1, 2)]) == [0, 0]
+    assert joins([(E, "fp32", 64, 3, 32, 16, 1), (E, "fp32", 64, 512, 4, 512, 2)]) == [0, 0]      # (no 16-wide tiles)
 
 
 @pytest.mark.parametrize("n, taken", [(64, False), (96, True), (128, True)])                               # 129.7 / 130.9, 167.6 / 159.9
