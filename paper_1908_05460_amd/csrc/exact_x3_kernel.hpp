@@ -12,7 +12,7 @@
 // with fp16's range, and where one lies beyond it the channel's scale and the sums so far change to the new one (`rescale`;
 // always in a workgroup's first tile, rarely later).  A number down to 2^-16 of its channel's largest has its 23 bits, a
 // smaller one an error of 2^-39 of that.  That is less than fp32's roundings of a sum that the channel's larger numbers enter, but
-// all there is of one whose larger numbers meet only zeros: such results are found at the end, by their own size (`judge`), looked
+// all there is of one whose larger numbers meet only zeros: such results are found at the end, by their own size (`weigh`), looked
 // at more closely, and summed in full (64 -> 64 @ 32x32 / 512 -> 512 @ 4x4, N = 128 / 512, 48 / 101 us: 70 / 126 where the products are
 // so sparse that many results are zero, 4 to 5 times as long where every other image is 2^26 larger and meets zeros).  The product
 // left out is 2^-22 of the whole at most, where every number has the same bits behind its eleventh (all 1 + 2^-11, N = 128: 2.4e-7
@@ -313,7 +313,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     uint32_t *const top = flag + 4;                          // per channel of dY [SH] and X [CH]: bits of the largest number so far
     int *const expo = (int *)(top + SH + T::CH);             // ... and the exponent of its scale
     constexpr int NB = T::NB, WORDS = T::WORDS;
-    uint32_t *const mark = (uint32_t *)(smem + T::kFix - WORDS * 256);      // [WORDS][64]: whether a sum is known to be well held (`judge`)
+    uint32_t *const mark = (uint32_t *)(smem + T::kFix - WORDS * 256);      // [WORDS][64]: whether a sum is known to be well held (`weigh`)
     // Per staging item of a thread, the scale of its channel; PARK: what is known of the item.  (In registers these would be
     // what spills, and a reload among the loads of a tile waits for all of those: 64 -> 64 @ 224x224, N = 4, 82 us
     // against 79.)
@@ -842,11 +842,11 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     if (any != any) *flag = 1;
     // fp16 pieces: numbers far below their channel's largest lose bits, which is nothing to a sum that larger ones enter, and
     // all to one whose larger ones meet only zeros.  Each wavefront's sum of a result's products is at most what the products'
-    // magnitudes add up to: a result is well held if one of the four is large beside what the pieces can have left out of a sum of
-    // that many products (channels of zeros need nothing).  A bit a result, set by judge, which shifts in the sign of
-    // beyond(sum, its row's word of `of`, its column's): of normally distributed numbers, ReLU's zeros among them, no workgroup in
+    // magnitudes add up to: a result is well held if one of the four is so large (2 kX3Need) that what the pieces can have left out
+    // of n products is within n roundings of fp32 of it; channels of zeros need nothing.  A bit a result: weigh shifts in the sign of
+    // beyond(sum, its row's word of `of`, its column's).  Of normally distributed numbers, ReLU's zeros among them, no workgroup in
     // 10^4 has a result without one.
-    [[maybe_unused]] auto judge = [&](uint32_t (&good)[WORDS > 0 ? WORDS : 1], const uint32_t *of, auto beyond) {
+    [[maybe_unused]] auto weigh = [&](uint32_t (&good)[WORDS > 0 ? WORDS : 1], const uint32_t *of, auto beyond) {
         uint32_t nc[NTC];
         x3_u4 nk[AV / 4];
 #pragma unroll
@@ -870,7 +870,7 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
     auto bits = [](int w) { return NB - 32 * w < 32 ? (1u << (NB - 32 * w)) - 1u : ~0u; };        // those of a word
     if constexpr (HALF) {
         uint32_t good[WORDS] = {};
-        judge(good, top, [](float sum, uint32_t row, uint32_t) { return (row == 0 ? -1.f : 2.f * kX3Need) - sum; });
+        weigh(good, top, [](float sum, uint32_t row, uint32_t) { return (row == 0 ? -1.f : 2.f * kX3Need) - sum; });
 #pragma unroll
         for (int t = 0; t < NTC; ++t) {
             int c_l, r;
@@ -926,8 +926,8 @@ __device__ __forceinline__ void x3_body(const X3Shape &p, const void *const *Xt,
             __syncthreads();
             uint32_t good[WORDS] = {}, held[WORDS] = {};
             const float one = kX3Need / (float)(p.nch * 8 * (wt_end - wt_begin));
-            judge(good, count, [&](float sum, uint32_t row, uint32_t col) { return one * (float)(row + col) - sum; });
-            judge(held, tiny, [](float sum, uint32_t row, uint32_t col) { return 0.f - ((float)(row + col) + sum); });
+            weigh(good, count, [&](float sum, uint32_t row, uint32_t col) { return one * (float)(row + col) - sum; });
+            weigh(held, tiny, [](float sum, uint32_t row, uint32_t col) { return 0.f - ((float)(row + col) + sum); });
 #pragma unroll
             for (int w = 0; w < WORDS; ++w) {
                 atomicOr(mark + w * 64 + lane, good[w]);

@@ -290,7 +290,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     // it looks at the sums after half of its stages, too.
     uint32_t *const mark = (uint32_t *)(smem + C::kHead - C::kMark);
     auto good = [&](int t) -> uint32_t & { return mark[t * kBlock + tid]; };
-    auto judge = [&](uint32_t (&good)[R::NT], const uint32_t *of, auto beyond) {
+    auto weigh = [&](uint32_t (&good)[R::NT], const uint32_t *of, auto beyond) {
         const uint32_t nc = of[kPK + i];
 #pragma unroll
         for (int m = 0; m < 2; ++m) {
@@ -306,7 +306,7 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
     };
     auto look = [&]() {
         uint32_t now[R::NT] = {};
-        judge(now, top, [](float sum, uint32_t row, uint32_t) { return (row == 0 ? -1.f : 2.f * kX3Need) - sum; });
+        weigh(now, top, [](float sum, uint32_t row, uint32_t) { return (row == 0 ? -1.f : 2.f * kX3Need) - sum; });
         const uint32_t none = top[kPK + i] == 0 ? ~0u : 0u;
 #pragma unroll
         for (int t = 0; t < R::NT; ++t) good(t) |= now[t] | none;
@@ -413,8 +413,8 @@ __device__ __forceinline__ void planes_body(const X3Shape &p, const float *Xp, c
             __syncthreads();
             uint32_t held[R::NT] = {}, now[R::NT] = {};
             const float one = kX3Need / (float)(C::IMG * C::P * (st_end - st_begin));
-            judge(now, count, [&](float sum, uint32_t row, uint32_t col) { return one * (float)(row + col) - sum; });
-            judge(held, tiny, [](float sum, uint32_t row, uint32_t col) { return 0.f - ((float)(row + col) + sum); });
+            weigh(now, count, [&](float sum, uint32_t row, uint32_t col) { return one * (float)(row + col) - sum; });
+            weigh(held, tiny, [](float sum, uint32_t row, uint32_t col) { return 0.f - ((float)(row + col) + sum); });
 #pragma unroll
             for (int t = 0; t < R::NT; ++t) held[t] &= ~(good(t) | now[t]);
             __syncthreads();
